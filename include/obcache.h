@@ -40,7 +40,7 @@
  *   - obc_score picks its kernels from the shapes: bf16 with head_dim 128 runs on the matrix
  *     cores; a one-row window (W = 1, the decoding case) over a bf16 cache of up to ~1e5
  *     head-tokens runs on kernels shaped for memory round trips; everything else (fp32,
- *     bf16 with head_dim 64 and W > 1) on general vector-ALU kernels.  The routing depends
+ *     bf16 with head_dim 64 and W > 1) on general kernels (fp64 logits and cross terms).  The routing depends
  *     on the arguments only (and on obc_set_score_path, a test hook declared at the end of
  *     this file); the process environment is never read.
  */
@@ -332,7 +332,7 @@ int obc_probe_read_bandwidth(const void *buf, size_t bytes, uint32_t *sink, void
  * scoring call (both read the same setting, so a workspace sized by obc_score_workspace_bytes
  * always fits the call that follows unless the setting is changed in between).
  *   OBC_PATH_AUTO    routing by shape (the default)
- *   OBC_PATH_PLAIN   the general vector-ALU kernels for every shape
+ *   OBC_PATH_PLAIN   the general kernels for every shape
  *   OBC_PATH_MFMA    one-row windows stay on the matrix-core kernels
  *   OBC_PATH_DECODE  one-row windows go to the decode kernels whatever the cache size
  * Returns OBC_EINVAL for any other value.  Results of all paths agree within the dtype's tolerance.

@@ -29,12 +29,6 @@ struct ScoreArgs {
 
 // Workspace carve-up for obc_score; offsets in bytes from a 256-byte aligned base.
 struct ScoreWorkspace {
-    size_t row_max;    // float [B*Hq*W]      max over visible keys of the scaled logit (natural log units)
-    size_t row_sum;    // float [B*Hq*W]      sum over visible keys of exp(z - row_max)
-    size_t out_f32;    // float [B*Hq*W*d]    o_i = sum_p A_ip v_p
-    size_t out_rest_f32;  // float [B*Hq*W*d] attention output of the row over every key but its top-logit one
-    size_t rest_frac;  // float [B*Hq*W]      1 - A_{i,p*}: share of the row's attention not on its top-logit key
-    size_t top_token;  // int32 [B*Hq*W]      p*: lowest index among the keys attaining the row max
     size_t out_bf16;   // bf16  [2][B*Hkv*m_pad*d]  o_i as two bf16 pieces (high, residual); rows of a KV head padded to a multiple of 32
     size_t row_const;  // float [B*Hkv*m_pad*4]  per padded row: 2*(max + log2 sum) in log2 units, ||o||^2, last visible key, spare
     size_t part_ml;    // float [B*Hkv*splits*m_pad*4]  per sequence split: row max (raw q.k), row sum, spare x2
@@ -47,8 +41,19 @@ struct ScoreWorkspace {
     int splits;        // sequence splits in the first sweep
     int split_len;     // tokens per split (multiple of 64)
     int range_len;     // tokens per workgroup in the second sweep (multiple of 64)
-    int use_mfma;      // 1: matrix-core path, 0: plain path
+    int use_mfma;      // 1: bf16 matrix-core path, 0: general path
     int use_wide;      // 1: the second sweep runs in its register-blocked form (score_mfma_wide.hip)
+    // General path: see score_plain.hip.  One piece of the work is `pl_heads` KV heads x `pl_rows` window rows x
+    // `pl_seg` tokens; its buffers are reused by the next one.
+    size_t pl_z;       // float [heads*rows*seg]     scaled logits
+    size_t pl_best;    // float2 [heads*rows*ranges] largest visible logit of a token range, lowest token attaining it
+    size_t pl_records; // RowRecord [heads*rows]
+    size_t pl_out;     // float [heads*rows*d]       o_i = sum_p A_ip v_p
+    size_t pl_part_l;  // float [heads*splits*rows]  sum of exp(z - max) of a split, without the row's top token
+    size_t pl_part_o;  // float [heads*splits*rows*d]  unnormalised output of a split, likewise
+    int pl_heads, pl_rows, pl_seg;
+    int pl_range, pl_ranges;   // tokens per range, ranges
+    int pl_split, pl_splits;   // tokens per split (a multiple of 64), splits
     // Decode path (one window row per query head): see score_decode.hip.
     size_t dec_z;      // float [B*Hkv*N*dec_rows]  scaled logits, token-major
     size_t dec_part;   // float [B*Hkv*dec_splits*dec_rows*(d+4)]  per-range partial records
@@ -67,7 +72,12 @@ int tuned_splits();
 int tuned_range();
 int tuned_sweep2_form();     // 0: by shape, 1: 32 rows per wave, 2: 64 rows per wave where the shape allows
 
-int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, ScoreWorkspace *ws);
+// `plain_cap`: bytes the general path should stay within (it works in pieces).
+constexpr size_t kPlainWorkspace = (size_t)96 << 20;
+int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, ScoreWorkspace *ws,
+                         size_t plain_cap = kPlainWorkspace);
+// Adds the general path's buffers to the plan, advancing *off (bytes).
+void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWorkspace *ws, size_t *off);
 // Adds the matrix-core path's buffers to the plan, advancing *off (bytes).
 void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWorkspace *ws, size_t *off);
 

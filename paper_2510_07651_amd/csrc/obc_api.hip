@@ -56,16 +56,16 @@ static int check_score_shape(int B, int N, int W, int Hq, int Hkv, int d, int dt
 }
 
 // obc_set_score_path pins the scoring path for comparisons: OBC_PATH_PLAIN routes everything through the
-// general vector-ALU kernels, OBC_PATH_MFMA keeps one-row windows on the matrix-core path, OBC_PATH_DECODE
+// general kernels, OBC_PATH_MFMA keeps one-row windows on the matrix-core path, OBC_PATH_DECODE
 // sends them to the decode kernels whatever the cache size.
 static bool score_path_is(int path) { return g_score_path.load(std::memory_order_relaxed) == path; }
 
-int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, ScoreWorkspace *ws) {
+int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, ScoreWorkspace *ws,
+                         size_t plain_cap) {
     const int rc = check_score_shape(B, N, W, Hq, Hkv, d, dtype, variant);
     if (rc != OBC_OK) return rc;
     std::memset(ws, 0, sizeof(*ws));
     const int G = Hq / Hkv;
-    const size_t rows = (size_t)B * Hq * W;
     const bool pinned = score_path_is(OBC_PATH_PLAIN) || score_path_is(OBC_PATH_MFMA);
     ws->use_decode = (decode_path_covers(B, N, W, Hq, Hkv, d, dtype, variant, score_path_is(OBC_PATH_DECODE)) && !pinned) ? 1 : 0;
     ws->use_mfma = (!ws->use_decode && dtype == OBC_BF16 && d == 128 && !score_path_is(OBC_PATH_PLAIN)) ? 1 : 0;
@@ -75,13 +75,8 @@ int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype,
         decode_plan(B, N, Hq, Hkv, d, ws, &off);
     } else if (ws->use_mfma) {
         mfma_plan(B, N, W, Hq, Hkv, d, variant, ws, &off);
-    } else {                                     // the plain path's per-row statistics and outputs
-        ws->row_max = off;  off = align_up(off + rows * sizeof(float), 256);
-        ws->row_sum = off;  off = align_up(off + rows * sizeof(float), 256);
-        ws->out_f32 = off;  off = align_up(off + rows * d * sizeof(float), 256);
-        ws->out_rest_f32 = off;  off = align_up(off + rows * d * sizeof(float), 256);
-        ws->rest_frac = off;  off = align_up(off + rows * sizeof(float), 256);
-        ws->top_token = off;  off = align_up(off + rows * sizeof(int32_t), 256);
+    } else {
+        plain_plan(B, N, W, Hq, Hkv, d, plain_cap, ws, &off);
     }
     ws->total = align_up(off, 256);
     return OBC_OK;
@@ -197,7 +192,7 @@ static int score_impl(const void *q, const void *k, const void *v, int N, int W,
     if ((((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) & 15) != 0 || ((uintptr_t)scores & 3) != 0) return OBC_EINVAL;
     if (stage_mask < 1 || stage_mask > OBC_STAGE_ALL) return OBC_EINVAL;
     ScoreWorkspace ws;
-    int rc = plan_score_workspace(B, N, W, Hq, Hkv, d, dtype, variant, &ws);
+    int rc = plan_score_workspace(B, N, W, Hq, Hkv, d, dtype, variant, &ws, own_scratch ? OBC_STATIC_SCRATCH_BYTES : kPlainWorkspace);
     if (rc != OBC_OK) return rc;
     ScoreArgs a;
     std::memset(&a, 0, sizeof(a));

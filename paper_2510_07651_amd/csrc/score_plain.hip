@@ -1,321 +1,664 @@
-// Plain (vector-ALU) scoring path: direct evaluation of every norm, fp32 arithmetic with
-// the logit dot products accumulated in fp64.
+// General scoring path: fp32 inputs, bf16 with head_dim 64, and anything pinned to it (obc_set_score_path).
+// Logits and cross terms are accumulated in fp64 on the matrix cores, attention outputs in fp32 there.
 //
-// Used for fp32 inputs and for shapes the matrix-core path is not built for.  Two
-// kernels:
-//   plain_window_attention  Section 3 of the paper for the W window rows of one
-//                           query head: row max, row sum, o_i = sum_p A_ip v_p.
-//   plain_score             Eq. 4-6 per (window row, token) in their direct forms
-//                           ||v_p||^2, ||v_p - o_i||^2, ||(1+Z)v_p - Z o_i||^2 (the
-//                           completed square of Eq. 6), summed over the window
-//                           (Eq. 9) and the query heads of the KV head (Appendix A.5).
+// Four kernels over a group of KV heads (Section 3 of the paper, then Eq. 4-6 summed over the window, Eq. 9, and the
+// query heads of the KV head, Appendix A.5):
+//   plain_logits   Z = Q K^T / sqrt(d): fp64 dot products rounded once to fp32 and stored, and per row the largest
+//                  visible logit of every token range with the lowest token that attains it.
+//   plain_weights  the row's maximum over all ranges; weights exp(z - max), their sum and P V per sequence split.
+//   plain_merge    per row: sums of the splits, the attention output o_i and the constants the scores need.
+//   plain_score    V O^T in fp64, A and Z from the stored logits, the three closed forms, summed over the rows.
+// Every logit is computed once: a group is as many KV heads as leave their logits within the workspace plan (they
+// then pass through the caches between the kernels).  Where even one head's rows do not fit, the rows, and beyond that
+// the tokens, are taken in pieces and the logits of a piece recomputed when they are needed again.
 //
-// Cancellation guard.  When one key takes almost all of a row's attention, o_i is almost
-// v_p and fp32 cannot hold their difference.  Each row therefore keeps its top-logit
-// token p* out of the running sums: with l' = sum_{q != p*} exp(z_q - z_p*) and
-// o' = sum_{q != p*} exp(z_q - z_p*) v_q / l',
+// Cancellation guard.  When one key takes almost all of a row's attention, o_i is almost v_p and fp32 cannot hold their
+// difference.  Each row therefore keeps its top-logit token p* out of the running sums: with
+// l' = sum_{q != p*} exp(z_q - z_p*) and o' = sum_{q != p*} exp(z_q - z_p*) v_q / l',
 //     v_p* - o_i = (l' / (1 + l')) (v_p* - o')        (exact, no cancellation)
 //     o_i        = v_p* - (v_p* - o_i)
-// and the (row, p*) pair is scored from the first identity.  For every pair,
-// (1+Z) v_p - Z o_i is formed as v_p + Z (v_p - o_i).
+// and the (row, p*) pair is scored from the first identity, in the merge kernel.  For every other pair ||v_p - o_i||^2
+// and ||v_p + Z (v_p - o_i)||^2 are formed from ||v_p||^2, ||o_i||^2 and v_p.o_i in fp64: their cancellation costs bits
+// far below the fp32 of o_i itself.
+//
+// What bounds it: the two fp64 contractions, 2 * 2 d flop per (row, token) pair at the 79 TFLOP/s of the fp64 matrix
+// cores (a wave's 16 x 16 x 4 op occupies its SIMD's matrix core for 64 cycles, so operands from LDS, the conversion
+// of fp32 to fp64 and the exponentials ride in its shadow), then P V on the fp32 matrix cores (twice that rate).
+// The vector-ALU kernels this replaced took one fp64 multiply-add per element and lane with a block per query head.
 // Sums run in a fixed order, so results are bit-reproducible.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace obc {
 namespace {
 
-constexpr int kTile = 64;        // tokens per tile
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kTile = 64;        // tokens per tile; each of the four waves owns 16 of them
 constexpr int kThreads = 256;    // 4 waves
+constexpr int kMaxRanges = 64;   // token ranges with a row maximum of their own, at most
+constexpr int kMaxSplits = 32;   // sequence splits of P V, at most
+constexpr int kNoToken = 0x7fffffff;
+
+// What one launch works on: KV heads bg0 .. bg0 + gridDim.z - 1, their window rows r0 .. r0 + nr - 1 (of the G*W rows
+// that share the KV head), tokens s0 .. s1 - 1.  Buffers of the group are indexed from (bg0, r0, s0).
+struct Piece {
+    int bg0, r0, nr, s0, s1;
+    int z_stride;                // floats between the logits of consecutive rows
+};
+
+// Constants of one row, written by plain_weights (m, top) and plain_merge (the rest).
+struct RowRecord {
+    float m;                     // largest visible logit
+    int top;                     // lowest token that attains it
+    float inv_l;                 // 1 / sum of exp(z - m)
+    float top_dk, top_dj;        // ||v - o||^2 and ||v + Z (v - o)||^2 of the top token
+    float pad;
+    double oo;                   // ||o_i||^2
+};
 
 template <typename T> __device__ __forceinline__ float load_as_float(const T *p);
 template <> __device__ __forceinline__ float load_as_float<float>(const float *p) { return *p; }
 template <> __device__ __forceinline__ float load_as_float<uint16_t>(const uint16_t *p) { return bf16_bits_to_float(*p); }
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-    return x;
-}
-__device__ __forceinline__ int wave_min(int x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x = min(x, __shfl_xor(x, off));
-    return x;
-}
 // Fixed-order tree sum over the 64 lanes.
-__device__ __forceinline__ float wave_sum(float x) {
+template <typename F>
+__device__ __forceinline__ F wave_sum(F x) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
     return x;
 }
 
-// Scaled logit q.k/sqrt(D) (Section 3).  Products of fp32 values are exact in fp64, so the
-// only rounding is the final one to fp32; both kernels call this with identical operands
-// and get identical bits.
-template <int D>
-__device__ __forceinline__ float scaled_logit(const float *__restrict__ qrow, const float *__restrict__ krow) {
-    double dot = 0.0;
-    for (int j = 0; j < D; ++j) dot = fma((double)qrow[j], (double)krow[j], dot);
-    return (float)(dot * (1.0 / sqrt((double)D)));
-}
-
-// Copies `kTile` rows starting at token t0 into LDS as fp32 with row stride D+1;
-// rows at or beyond `len` are zero-filled (their memory is never read).
-template <typename T, int D>
-__device__ __forceinline__ void stage_rows(const T *__restrict__ base, int t0, int len, float *dst) {
-    for (int e = threadIdx.x; e < kTile * D; e += kThreads) {
-        const int row = e / D, col = e % D;
-        const int p = t0 + row;
-        dst[row * (D + 1) + col] = p < len ? load_as_float(base + (size_t)p * D + col) : 0.f;
+// (max, lowest token attaining it) merged across the lanes whose index differs in the bits of `below`.
+template <int kLanes>
+__device__ __forceinline__ void lanes_best(float &m, int &at) {
+#pragma unroll
+    for (int off = kLanes / 2; off > 0; off >>= 1) {
+        const float om = __shfl_xor(m, off);
+        const int oat = __shfl_xor(at, off);
+        const bool take = om > m || (om == m && oat < at);
+        m = take ? om : m;
+        at = take ? oat : at;
     }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void plain_window_attention(
-    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, int N, int W, int Hq, int Hkv,
-    int ragged, SeqLens lens, float *__restrict__ row_max, float *__restrict__ row_sum, float *__restrict__ out,
-    float *__restrict__ out_rest, float *__restrict__ rest_frac, int32_t *__restrict__ top_token) {
-    __shared__ float smem[OBC_MAX_WINDOW * D + kTile * (D + 1) + OBC_MAX_WINDOW * (kTile + 1) + 2 * OBC_MAX_WINDOW];
-    float *qs = smem;                                // [OBC_MAX_WINDOW][D]
-    float *ts = qs + OBC_MAX_WINDOW * D;             // [kTile][D+1]  K tile, then V tile
-    float *ps = ts + kTile * (D + 1);                // [OBC_MAX_WINDOW][kTile+1] unnormalised weights of the tile
-    float *ms = ps + OBC_MAX_WINDOW * (kTile + 1);   // [OBC_MAX_WINDOW] row max
-    int *top = (int *)(ms + OBC_MAX_WINDOW);         // [OBC_MAX_WINDOW] lowest token index attaining the row max
+// ------------------------------------------------------------------------------------
+// Tiles: `kRows` rows of D values, in LDS as fp32 with row stride D + 4 (16-byte pieces of 16 consecutive rows then
+// start in different banks).  Global memory is read in 16-byte pieces through registers, so that a tile can be in
+// flight while the one before it is worked on.
+// ------------------------------------------------------------------------------------
+template <int D> constexpr int kStride = D + 4;
 
-    const int bh = blockIdx.x;
-    const int b = bh / Hq, h = bh % Hq, g = h / (Hq / Hkv);
+template <typename T, int D, int kRows>
+struct TileRegs {
+    static constexpr int kPieces = D * (int)sizeof(T) / 16;          // 16-byte pieces per row
+    static constexpr int kCount = (kRows * kPieces + kThreads - 1) / kThreads;
+    uint4 x[kCount];
+
+    // Rows at or beyond `limit` become zeros; their memory is never read.
+    __device__ __forceinline__ void load(const T *__restrict__ base, int row0, int limit) {
+#pragma unroll
+        for (int i = 0; i < kCount; ++i) {
+            const int e = (int)threadIdx.x + i * kThreads, r = e / kPieces, c = e % kPieces;
+            const bool ok = r < kRows && row0 + r < limit;
+            x[i] = ok ? *(const uint4 *)((const char *)(base + (size_t)(row0 + r) * D) + c * 16) : make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+    __device__ __forceinline__ void store(float *__restrict__ lds) const {
+#pragma unroll
+        for (int i = 0; i < kCount; ++i) {
+            const int e = (int)threadIdx.x + i * kThreads, r = e / kPieces, c = e % kPieces;
+            if (kRows * kPieces % kThreads != 0 && r >= kRows) continue;
+            float *dst = lds + r * kStride<D>;
+            if (sizeof(T) == 4) {
+                *(uint4 *)(dst + 4 * c) = x[i];
+            } else {
+                *(uint4 *)(dst + 8 * c) = make_uint4(x[i].x << 16, x[i].x & 0xffff0000u, x[i].y << 16, x[i].y & 0xffff0000u);
+                *(uint4 *)(dst + 8 * c + 4) = make_uint4(x[i].z << 16, x[i].z & 0xffff0000u, x[i].w << 16, x[i].w & 0xffff0000u);
+            }
+        }
+    }
+};
+
+// fp64 dot products of 16 kRt rows and this wave's 16 tokens: acc[rt][r] is row 16 rt + 4 r + lane / 16, token lane % 16.
+// The four k values of a matrix op are components c of the four lane groups' 16-byte pieces: any assignment of
+// elements to k will do as long as both operands use the same, and this one reads LDS 16 bytes at a time.
+template <int D, int kRt>
+__device__ __forceinline__ void tile_dots(const float *rows, const float *toks, int lane, f64x4 (&acc)[kRt]) {
+    const float *rp = rows + (lane & 15) * kStride<D> + 4 * (lane >> 4);
+    const float *tp = toks + (lane & 15) * kStride<D> + 4 * (lane >> 4);
+#pragma unroll 2
+    for (int s = 0; s < D / 16; ++s) {
+        const f32x4 t = *(const f32x4 *)(tp + 16 * s);
+        f32x4 a[kRt];
+#pragma unroll
+        for (int rt = 0; rt < kRt; ++rt) a[rt] = *(const f32x4 *)(rp + rt * 16 * kStride<D> + 16 * s);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int rt = 0; rt < kRt; ++rt)
+                acc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[rt][c], (double)t[c], acc[rt], 0, 0, 0);
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// Logits.  Grid: x = token range of the piece, y = chunk of 16 kRt rows, z = KV head.
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int kRt>
+__global__ __launch_bounds__(kThreads, 2) void plain_logits(const T *__restrict__ q, const T *__restrict__ k, int N, int W,
+                                                            int Hq, int Hkv, int ragged, SeqLens lens, Piece w,
+                                                            int range_len, int n_ranges, float *__restrict__ z,
+                                                            float2 *__restrict__ range_best) {
+    constexpr int kRows = 16 * kRt;
+    __shared__ __attribute__((aligned(16))) float rows_s[kRows * kStride<D>], toks_s[kTile * kStride<D>];
+    __shared__ float2 best_s[4][kRows];
+
+    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv, g = bg % Hkv, M = Hq / Hkv * W;
     const int len = seq_len_of(lens, ragged, b, N);
-    const T *kg = k + ((size_t)b * Hkv + g) * (size_t)N * D;
-    const T *vg = v + ((size_t)b * Hkv + g) * (size_t)N * D;
-    const T *qh = q + (size_t)bh * W * D;
+    const int range = w.s0 / range_len + blockIdx.x;
+    const int t_begin = range * range_len, t_end = min(min(t_begin + range_len, w.s1), len);
+    if (t_begin >= t_end) return;                            // uniform: nothing of this range is live
+    const int row0 = blockIdx.y * kRows;                     // first row of the chunk inside the piece
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 
-    const int tok = threadIdx.x % kTile;
-    const int rq = threadIdx.x / kTile;              // == wave index: rows rq, rq+4, ...
-    constexpr int kRowsPerThread = OBC_MAX_WINDOW / 4;
-
-    for (int e = threadIdx.x; e < W * D; e += kThreads) qs[e] = load_as_float(qh + e);
-
-    // Sweep 1: row maxima of the scaled logits over the visible keys, and where they sit.
-    float mymax[kRowsPerThread];
-    int myarg[kRowsPerThread];
+    const T *kg = k + (size_t)bg * N * D;
+    TileRegs<T, D, kTile> next;
+    next.load(kg, t_begin, len);
+    {
+        TileRegs<T, D, kRows> qr;
+        qr.load(q + ((size_t)b * Hq * W + (size_t)g * M + w.r0) * D, row0, w.nr);
+        qr.store(rows_s);
+    }
+    float m[kRt * 4];
+    int at[kRt * 4];
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) { mymax[i] = -INFINITY; myarg[i] = 0x7fffffff; }
-    for (int t0 = 0; t0 < len; t0 += kTile) {
+    for (int i = 0; i < kRt * 4; ++i) { m[i] = -INFINITY; at[i] = kNoToken; }
+    for (int t0 = t_begin; t0 < t_end; t0 += kTile) {
+        __syncthreads();                                     // the tile before this one has been read
+        next.store(toks_s);
         __syncthreads();
-        stage_rows<T, D>(kg, t0, len, ts);
-        __syncthreads();
-        const int p = t0 + tok;
+        if (t0 + kTile < t_end) next.load(kg, t0 + kTile, len);
+        f64x4 acc[kRt];
 #pragma unroll
-        for (int i = 0; i < kRowsPerThread; ++i) {
-            const int r = rq + 4 * i;
-            if (r < W && p <= len - W + r) {
-                const float z = scaled_logit<D>(qs + r * D, ts + tok * (D + 1));
-                if (z > mymax[i]) { mymax[i] = z; myarg[i] = p; }     // strict: keeps the thread's lowest index
+        for (int rt = 0; rt < kRt; ++rt) acc[rt] = f64x4{0.0, 0.0, 0.0, 0.0};
+        tile_dots<D, kRt>(rows_s, toks_s + wave * 16 * kStride<D>, lane, acc);
+        const int p = t0 + wave * 16 + (lane & 15);
+        float *zp = z + ((size_t)hl * w.nr + row0) * w.z_stride + (p - w.s0);
+#pragma unroll
+        for (int rt = 0; rt < kRt; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * rt + 4 * r + (lane >> 4), i = rt * 4 + r;
+                const float x = (float)(acc[rt][r] * (1.0 / sqrt((double)D)));   // scaled logit: the only rounding
+                if (p < t_end && row0 + row < w.nr) {
+                    zp[(size_t)row * w.z_stride] = x;
+                    // (tokens ascend: strict keeps the lane's lowest)
+                    if (p <= len - W + (w.r0 + row0 + row) % W && x > m[i]) { m[i] = x; at[i] = p; }
+                }
             }
-        }
     }
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) {
-        const float m = wave_max(mymax[i]);
-        const int arg = wave_min(mymax[i] == m ? myarg[i] : 0x7fffffff);
-        if (tok == 0 && rq + 4 * i < W) { ms[rq + 4 * i] = m; top[rq + 4 * i] = arg; }
+    for (int i = 0; i < kRt * 4; ++i) {
+        lanes_best<16>(m[i], at[i]);
+        if ((lane & 15) == 0) best_s[wave][16 * (i >> 2) + 4 * (i & 3) + (lane >> 4)] = make_float2(m[i], __int_as_float(at[i]));
     }
-
-    // Sweep 2: weights exp(z - max) of every visible key except the top one, their sums,
-    // and the weighted sum of V rows.
-    float mysum[kRowsPerThread];
+    __syncthreads();
+    const int row = threadIdx.x;
+    if (row < kRows && row0 + row < w.nr) {
+        float2 best = best_s[0][row];
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) mysum[i] = 0.f;
-    constexpr int kColsPerThread = D / 4;            // thread owns out[row = tid/4][cols (tid%4)*D/4 ...)
-    const int orow = threadIdx.x / 4, ocol0 = (threadIdx.x % 4) * kColsPerThread;
-    float oacc[kColsPerThread];
-#pragma unroll
-    for (int j = 0; j < kColsPerThread; ++j) oacc[j] = 0.f;
-
-    for (int t0 = 0; t0 < len; t0 += kTile) {
-        __syncthreads();
-        stage_rows<T, D>(kg, t0, len, ts);
-        __syncthreads();
-        const int p = t0 + tok;
-#pragma unroll
-        for (int i = 0; i < kRowsPerThread; ++i) {
-            const int r = rq + 4 * i;
-            if (r < W) {
-                float w = 0.f;
-                if (p <= len - W + r && p != top[r])
-                    w = expf(scaled_logit<D>(qs + r * D, ts + tok * (D + 1)) - ms[r]);
-                mysum[i] += w;
-                ps[r * (kTile + 1) + tok] = w;
-            }
+        for (int c = 1; c < 4; ++c) {
+            const float2 o = best_s[c][row];
+            if (o.x > best.x || (o.x == best.x && __float_as_int(o.y) < __float_as_int(best.y))) best = o;
         }
-        __syncthreads();
-        stage_rows<T, D>(vg, t0, len, ts);
-        __syncthreads();
-        if (orow < W) {
-            for (int t = 0; t < kTile; ++t) {
-                const float w = ps[orow * (kTile + 1) + t];
-#pragma unroll
-                for (int j = 0; j < kColsPerThread; ++j) oacc[j] = fmaf(w, ts[t * (D + 1) + ocol0 + j], oacc[j]);
+        range_best[((size_t)hl * w.nr + row0 + row) * n_ranges + range] = best;
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// Weights.  Grid: x = split of the piece, y = chunk of 16 kRt rows, z = KV head.  Without kNeedO (Eq. 4, 8 and the
+// l1 form) only the sums are formed.
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int kRt, bool kNeedO>
+__global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict__ v, int N, int W, int Hq, int Hkv,
+                                                             int ragged, SeqLens lens, Piece w, int range_len, int n_ranges,
+                                                             int split_len, int n_splits, const float *__restrict__ z,
+                                                             const float2 *__restrict__ range_best,
+                                                             RowRecord *__restrict__ records, float *__restrict__ part_l,
+                                                             float *__restrict__ part_o) {
+    constexpr int kRows = 16 * kRt, kPs = kTile + 4;
+    constexpr int kCt = D / 64;                              // 16-column tiles of V per wave
+    __shared__ __attribute__((aligned(16))) float p_s[kNeedO ? kRows * kPs : 4], v_s[kNeedO ? kTile * kStride<D> : 4];
+    __shared__ float m_s[kRows];
+    __shared__ int top_s[kRows];
+
+    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
+    const int len = seq_len_of(lens, ragged, b, N);
+    const int split = w.s0 / split_len + blockIdx.x;
+    const int t_begin = split * split_len, t_end = min(min(t_begin + split_len, w.s1), len);
+    if (t_begin >= t_end) return;                            // uniform
+    const int row0 = blockIdx.y * kRows;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+
+    const T *vg = v + (size_t)bg * N * D;
+    TileRegs<T, D, kTile> next;
+    if (kNeedO) next.load(vg, t_begin, len);
+    {
+        // the row's maximum over its ranges: kThreads / kRows lanes per row
+        constexpr int kSub = kThreads / kRows;
+        const int row = threadIdx.x / kSub, live = (len + range_len - 1) / range_len;
+        float m = -INFINITY;
+        int at = kNoToken;
+        if (row0 + row < w.nr)
+            for (int i = threadIdx.x % kSub; i < live; i += kSub) {
+                const float2 o = range_best[((size_t)hl * w.nr + row0 + row) * n_ranges + i];
+                if (o.x > m || (o.x == m && __float_as_int(o.y) < at)) { m = o.x; at = __float_as_int(o.y); }
+            }
+        lanes_best<kSub>(m, at);
+        if (threadIdx.x % kSub == 0) {
+            m_s[row] = row0 + row < w.nr ? m : 0.f;
+            top_s[row] = at;
+            if (split == 0 && row0 + row < w.nr) {
+                RowRecord *rec = records + (size_t)hl * w.nr + row0 + row;
+                rec->m = m;
+                rec->top = at;
             }
         }
     }
     __syncthreads();
-    float *ls = ps;                                   // reuse: [OBC_MAX_WINDOW] sums without the top token
+    constexpr int kMine = kRows / 4;                         // this thread's rows: wave, wave + 4, ...
+    float m[kMine], sum[kMine];
+    int top[kMine], last[kMine];
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) {
-        const float s = wave_sum(mysum[i]);
-        if (tok == 0 && rq + 4 * i < W) ls[rq + 4 * i] = s;
+    for (int i = 0; i < kMine; ++i) {
+        const int row = wave + 4 * i;
+        m[i] = m_s[row];
+        top[i] = top_s[row];
+        last[i] = row0 + row < w.nr ? min(len - W + (w.r0 + row0 + row) % W, t_end - 1) : -1;     // last token it sees here
+        sum[i] = 0.f;
     }
-    __syncthreads();
-    if ((int)threadIdx.x < W) {
-        const size_t row = (size_t)bh * W + threadIdx.x;
-        const float lr = ls[threadIdx.x];
-        row_max[row] = ms[threadIdx.x];
-        row_sum[row] = 1.0f + lr;                     // the top token's own weight is exp(0) = 1
-        rest_frac[row] = lr / (1.0f + lr);            // 1 - A_{i,p*}
-        top_token[row] = top[threadIdx.x];
-    }
-    if (orow < W) {
-        const float lr = ls[orow];
-        const float inv = lr > 0.f ? 1.0f / lr : 0.f;
-        const float frac = lr / (1.0f + lr);
-        const T *vtop = vg + (size_t)top[orow] * D + ocol0;
-        const size_t off = ((size_t)bh * W + orow) * D + ocol0;
+    f32x4 acc[kRt][kCt > 0 ? kCt : 1];
 #pragma unroll
-        for (int j = 0; j < kColsPerThread; ++j) {
-            const float orest = oacc[j] * inv;        // attention output over everything but the top token
-            const float vt = load_as_float(vtop + j);
-            out_rest[off + j] = orest;
-            out[off + j] = vt - frac * (vt - orest);
+    for (int rt = 0; rt < kRt; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < kCt; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int t0 = t_begin; t0 < t_end; t0 += kTile) {
+        const int p = t0 + lane;
+        float x[kMine];
+#pragma unroll
+        for (int i = 0; i < kMine; ++i)
+            x[i] = p <= last[i] ? z[((size_t)hl * w.nr + row0 + wave + 4 * i) * w.z_stride + (p - w.s0)] : 0.f;
+        if (kNeedO) {
+            __syncthreads();                                 // the tiles before these have been read
+            next.store(v_s);
         }
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            const float e = p <= last[i] && p != top[i] ? expf(x[i] - m[i]) : 0.f;
+            sum[i] += e;
+            if (kNeedO) p_s[(wave + 4 * i) * kPs + lane] = e;
+        }
+        if (!kNeedO) continue;
+        __syncthreads();
+        if (t0 + kTile < t_end) next.load(vg, t0 + kTile, len);
+        // P V: this wave's 16 kCt columns of every row.  k value j of a matrix op is token 4 j + c of the sixteen.
+#pragma unroll
+        for (int s = 0; s < kTile / 16; ++s) {
+            f32x4 a[kRt];
+#pragma unroll
+            for (int rt = 0; rt < kRt; ++rt)
+                a[rt] = *(const f32x4 *)(p_s + (16 * rt + (lane & 15)) * kPs + 16 * s + 4 * (lane >> 4));
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int ct = 0; ct < kCt; ++ct) {
+                    const float vv = v_s[(16 * s + 4 * (lane >> 4) + c) * kStride<D> + (wave * kCt + ct) * 16 + (lane & 15)];
+#pragma unroll
+                    for (int rt = 0; rt < kRt; ++rt)
+                        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rt][c], vv, acc[rt][ct], 0, 0, 0);
+                }
+        }
+    }
+    const size_t out_row = ((size_t)hl * n_splits + split) * w.nr + row0;
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+        const float s = wave_sum(sum[i]);
+        if (lane == 0 && row0 + wave + 4 * i < w.nr) part_l[out_row + wave + 4 * i] = s;
+    }
+    if (!kNeedO) return;
+#pragma unroll
+    for (int rt = 0; rt < kRt; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < kCt; ++ct)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * rt + 4 * (lane >> 4) + r;
+                if (row0 + row < w.nr) part_o[(out_row + row) * D + (wave * kCt + ct) * 16 + (lane & 15)] = acc[rt][ct][r];
+            }
+}
+
+// ------------------------------------------------------------------------------------
+// Merge.  One wave per row, D / 64 elements per lane.  Grid: x = four rows of the piece, z = KV head.
+// ------------------------------------------------------------------------------------
+template <typename T, int D, bool kNeedO>
+__global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int Hkv, int ragged, SeqLens lens,
+                                                        Piece w, int split_len, int n_splits,
+                                                        const float *__restrict__ part_l, const float *__restrict__ part_o,
+                                                        RowRecord *__restrict__ records, float *__restrict__ out) {
+    constexpr int kE = D / 64;
+    const int hl = blockIdx.z, bg = w.bg0 + hl, row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (row >= w.nr) return;                                 // uniform over the wave
+    const int len = seq_len_of(lens, ragged, bg / Hkv, N);
+    const int live = (len + split_len - 1) / split_len;
+    RowRecord *rec = records + (size_t)hl * w.nr + row;
+    const int top = rec->top;
+    const float m = rec->m;
+    float vt[kE], o[kE];
+#pragma unroll
+    for (int e = 0; e < kE; ++e) {
+        vt[e] = kNeedO ? load_as_float(v + ((size_t)bg * N + top) * D + lane + 64 * e) : 0.f;
+        o[e] = 0.f;
+    }
+    float l = 0.f;
+#pragma unroll 8
+    for (int s = 0; s < live; ++s) {
+        const size_t at = ((size_t)hl * n_splits + s) * w.nr + row;
+        l += part_l[at];
+#pragma unroll
+        for (int e = 0; e < kE; ++e)
+            if (kNeedO) o[e] += part_o[at * D + lane + 64 * e];
+    }
+    const float frac = l / (1.0f + l);                       // 1 - A_{i,top}; the top token's own weight is exp(0) = 1
+    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    double oo = 0.0, dk = 0.0, dj = 0.0;
+    if (kNeedO) {
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+            const float diff = frac * (vt[e] - o[e] * inv);  // v_top - o_i
+            const float oi = vt[e] - diff;
+            const float comb = fmaf(m, diff, vt[e]);         // (1+Z) v_top - Z o_i
+            out[((size_t)hl * w.nr + row) * D + lane + 64 * e] = oi;
+            oo += (double)oi * oi;
+            dk += (double)diff * diff;
+            dj += (double)comb * comb;
+        }
+        oo = wave_sum(oo);
+        dk = wave_sum(dk);
+        dj = wave_sum(dj);
+    }
+    if (lane == 0) {
+        rec->inv_l = 1.0f / (1.0f + l);
+        rec->top_dk = (float)dk;
+        rec->top_dj = (float)dj;
+        rec->oo = oo;
     }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void plain_score(
-    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, int N, int W, int Hq, int Hkv,
-    int ragged, SeqLens lens, int variant, const float *__restrict__ row_max, const float *__restrict__ row_sum,
-    const float *__restrict__ out, const float *__restrict__ out_rest, const float *__restrict__ rest_frac,
-    const int32_t *__restrict__ top_token, float *__restrict__ scores, size_t variant_stride, int accumulate) {
-    __shared__ float smem[2 * kTile * (D + 1) + 4 * D + 4 * kTile * 3];
-    float *ks = smem;                          // [kTile][D+1]
-    float *vs = ks + kTile * (D + 1);          // [kTile][D+1]
-    float *qs = vs + kTile * (D + 1);          // [4][D] the query row each wave is working on
-    float *red = qs + 4 * D;                   // [4][kTile][3]
+// ------------------------------------------------------------------------------------
+// Scores.  Grid: x = tile of 64 tokens of the piece, z = KV head.  `add`: on top of what `scores` holds (the caller's
+// running scores, or the rows of an earlier piece).
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int kRt, int kVariant>
+__global__ __launch_bounds__(kThreads, 2) void plain_score(const T *__restrict__ v, int N, int W, int Hq, int Hkv,
+                                                           int ragged, SeqLens lens, Piece w, const float *__restrict__ z,
+                                                           const RowRecord *__restrict__ records,
+                                                           const float *__restrict__ out, float *__restrict__ scores,
+                                                           size_t variant_stride, int add) {
+    constexpr int kRows = 16 * kRt;
+    constexpr bool kAttnLike = kVariant == OBC_ATTN || kVariant == OBC_VATP;
+    constexpr bool kNeedO = kVariant == OBC_KEY || kVariant == OBC_JOINT || kVariant == OBC_ALL;
+    constexpr bool kNeedV = kVariant != OBC_ATTN;
+    __shared__ __attribute__((aligned(16))) float toks_s[kNeedV ? kTile * kStride<D> : 4], rows_s[kNeedO ? kRows * kStride<D> : 4];
+    __shared__ __attribute__((aligned(16))) RowRecord rec_s[kRows];
 
-    const int bg = blockIdx.y;
-    const int b = bg / Hkv, g = bg % Hkv, G = Hq / Hkv;
+    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int t0 = blockIdx.x * kTile;
-    const int tok = threadIdx.x % kTile;
-    const int rq = __builtin_amdgcn_readfirstlane(threadIdx.x / kTile);
-    const int p = t0 + tok;
-
-    const bool attn_like = variant == OBC_ATTN || variant == OBC_VATP;   // these use the first accumulator
+    const int t0 = w.s0 + blockIdx.x * kTile;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int p = t0 + wave * 16 + (lane & 15), j = lane >> 4;
     float acc_v = 0.f, acc_k = 0.f, acc_j = 0.f;
-    if (t0 < len) {                            // uniform per block
-        stage_rows<T, D>(k + (size_t)bg * N * D, t0, len, ks);
-        stage_rows<T, D>(v + (size_t)bg * N * D, t0, len, vs);
-        __syncthreads();
-        const float *kp = ks + tok * (D + 1), *vp = vs + tok * (D + 1);
-        float *qw = qs + rq * D;               // private to this wave: no block barrier needed around it
-        float vv = 0.f, l1 = 0.f;
-        for (int j = 0; j < D; ++j) { vv = fmaf(vp[j], vp[j], vv); l1 += fabsf(vp[j]); }
-        for (int hh = 0; hh < G; ++hh) {
-            const int h = g * G + hh;
-            for (int r = rq; r < W; r += 4) {
-                if (t0 > len - W + r) continue;            // uniform: whole tile hidden from this row
-                const size_t row = ((size_t)b * Hq + h) * W + r;
-                for (int j = tok; j < D; j += kTile) qw[j] = load_as_float(q + row * D + j);
-                const float *orow = out + row * D, *orest = out_rest + row * D;
-                const float m = row_max[row], inv_l = 1.0f / row_sum[row], frac = rest_frac[row];
-                const int ptop = top_token[row];
-                if (p <= len - W + r) {
-                    const float z = scaled_logit<D>(qw, kp);
-                    const bool is_top = p == ptop;
-                    const float a = is_top ? inv_l : expf(z - m) * inv_l;
-                    if (attn_like) {                       // Eq. 8: only the weight itself is summed
-                        acc_v += a;
-                        continue;
+    if (t0 < len) {                                          // uniform
+        const bool live = p < len;
+        double vv = 0.0;
+        float l1 = 0.f;
+        if (kNeedV) {
+            TileRegs<T, D, kTile> tile;
+            tile.load(v + (size_t)bg * N * D, t0, len);
+            tile.store(toks_s);
+        }
+        for (int row0 = 0; row0 < w.nr; row0 += kRows) {
+            TileRegs<float, D, kRows> orow;
+            if (kNeedO) orow.load(out + (size_t)hl * w.nr * D, row0, w.nr);
+            float x[kRt * 4];
+#pragma unroll
+            for (int i = 0; i < kRt * 4; ++i) {
+                const int row = row0 + 4 * i + j;
+                x[i] = live && row < w.nr ? z[((size_t)hl * w.nr + row) * w.z_stride + (p - w.s0)] : 0.f;
+            }
+            if (row0 > 0) __syncthreads();                   // the rows before these have been read
+            if (kNeedO) orow.store(rows_s);
+            if ((int)threadIdx.x < kRows && row0 + (int)threadIdx.x < w.nr)
+                rec_s[threadIdx.x] = records[(size_t)hl * w.nr + row0 + threadIdx.x];
+            __syncthreads();
+            if (kNeedV && row0 == 0) {                       // ||v_p||^2 (and ||v_p||_1): four lanes per token
+                const float *vp = toks_s + (wave * 16 + (lane & 15)) * kStride<D> + 4 * j;
+#pragma unroll 4
+                for (int s = 0; s < D / 16; ++s) {
+                    const f32x4 y = *(const f32x4 *)(vp + 16 * s);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        vv += (double)y[c] * y[c];
+                        l1 += fabsf(y[c]);
                     }
-                    const float a2 = a * a;
-                    const float f = is_top ? frac : 1.0f;
-                    float dk = 0.f, dj = 0.f;
-                    for (int j = 0; j < D; ++j) {
-                        const float ref = is_top ? orest[j] : orow[j];
-                        const float diff = f * (vp[j] - ref);        // v_p - o_i
-                        const float comb = fmaf(z, diff, vp[j]);     // (1+Z) v_p - Z o_i
-                        dk = fmaf(diff, diff, dk);
-                        dj = fmaf(comb, comb, dj);
+                }
+                vv += __shfl_xor(vv, 16);
+                vv += __shfl_xor(vv, 32);
+                l1 += __shfl_xor(l1, 16);
+                l1 += __shfl_xor(l1, 32);
+            }
+            f64x4 acc[kRt];
+#pragma unroll
+            for (int rt = 0; rt < kRt; ++rt) acc[rt] = f64x4{0.0, 0.0, 0.0, 0.0};
+            if (kNeedO) tile_dots<D, kRt>(rows_s, toks_s + wave * 16 * kStride<D>, lane, acc);
+#pragma unroll
+            for (int i = 0; i < kRt * 4; ++i) {
+                const int row = row0 + 4 * i + j;
+                if (!live || row >= w.nr || p > len - W + (w.r0 + row) % W) continue;
+                const RowRecord &rec = rec_s[4 * i + j];
+                const float a = expf(x[i] - rec.m) * rec.inv_l;
+                if (kAttnLike) {                             // Eq. 8: only the weight itself is summed
+                    acc_v += a;
+                    continue;
+                }
+                const float a2 = a * a;
+                acc_v = fmaf(a2, (float)vv, acc_v);
+                if (kNeedO) {
+                    const double vo = acc[i >> 2][i & 3], zd = x[i];
+                    const double d2 = (vv + rec.oo) - 2.0 * vo;                          // ||v_p - o_i||^2
+                    const bool is_top = p == rec.top;
+                    if (kVariant != OBC_JOINT)
+                        acc_k = fmaf(a2 * x[i] * x[i], is_top ? rec.top_dk : fmaxf((float)d2, 0.f), acc_k);
+                    if (kVariant != OBC_KEY) {
+                        const double dj = vv + zd * (2.0 * (vv - vo) + zd * d2);         // ||v_p + Z (v_p - o_i)||^2
+                        acc_j = fmaf(a2, is_top ? rec.top_dj : fmaxf((float)dj, 0.f), acc_j);
                     }
-                    acc_v = fmaf(a2, vv, acc_v);
-                    acc_k = fmaf(a2 * z * z, dk, acc_k);
-                    acc_j = fmaf(a2, dj, acc_j);
                 }
             }
         }
-        if (variant == OBC_VATP) acc_v *= l1;
+        if (kVariant == OBC_VATP) acc_v *= l1;
+        acc_v += __shfl_xor(acc_v, 16);                      // the four lanes of a token held different rows
+        acc_v += __shfl_xor(acc_v, 32);
+        acc_k += __shfl_xor(acc_k, 16);
+        acc_k += __shfl_xor(acc_k, 32);
+        acc_j += __shfl_xor(acc_j, 16);
+        acc_j += __shfl_xor(acc_j, 32);
     }
-    red[(rq * kTile + tok) * 3 + 0] = acc_v;
-    red[(rq * kTile + tok) * 3 + 1] = acc_k;
-    red[(rq * kTile + tok) * 3 + 2] = acc_j;
-    __syncthreads();
-    if (threadIdx.x < kTile && p < N) {
-        float s[3];
+    if (j == 0 && p < min(w.s1, N)) {
+        float *dst = scores + (size_t)bg * N + p;
+        const float s[3] = {acc_v, acc_k, acc_j};
+        constexpr int kFirst = kVariant == OBC_ALL || kAttnLike ? 0 : kVariant, kCount = kVariant == OBC_ALL ? 3 : 1;
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
-            s[c] = (red[(0 * kTile + tok) * 3 + c] + red[(1 * kTile + tok) * 3 + c]) +
-                   (red[(2 * kTile + tok) * 3 + c] + red[(3 * kTile + tok) * 3 + c]);
-        const size_t idx = (size_t)bg * N + p;
-        const bool live = p < len;
-        if (accumulate) {                       // running scores: add this call's increment, leave the padding alone
-            if (live) {
-                if (variant == OBC_ALL) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) scores[c * variant_stride + idx] += s[c];
-                } else {
-                    scores[idx] += s[attn_like ? 0 : variant];
-                }
-            }
-        } else if (variant == OBC_ALL) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) scores[c * variant_stride + idx] = live ? s[c] : 0.f;
-        } else {
-            scores[idx] = live ? s[attn_like ? 0 : variant] : 0.f;
+        for (int c = 0; c < kCount; ++c) {
+            float *d = dst + c * variant_stride;
+            if (!add) *d = p < len ? s[kFirst + c] : 0.f;
+            else if (p < len) *d += s[kFirst + c];           // running scores: the padding is left alone
         }
     }
 }
 
-template <typename T, int D>
+// ------------------------------------------------------------------------------------
+// Host
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int kRt>
 hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
-    float *row_max = (float *)(base + ws.row_max), *row_sum = (float *)(base + ws.row_sum);
-    float *out = (float *)(base + ws.out_f32), *out_rest = (float *)(base + ws.out_rest_f32);
-    float *rest_frac = (float *)(base + ws.rest_frac);
-    int32_t *top_token = (int32_t *)(base + ws.top_token);
-    hipError_t e;      // (both kernels size their LDS statically: nothing to configure before a launch)
-    if (a.stage_mask & OBC_STAGE_SWEEP1) {      // the plain path has no separate combine stage
-        plain_window_attention<T, D><<<dim3(a.B * a.Hq), dim3(kThreads), 0, stream>>>(
-            (const T *)a.q, (const T *)a.k, (const T *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, row_max, row_sum,
-            out, out_rest, rest_frac, top_token);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    const T *q = (const T *)a.q, *k = (const T *)a.k, *v = (const T *)a.v;
+    float *z = (float *)(base + ws.pl_z), *part_l = (float *)(base + ws.pl_part_l), *part_o = (float *)(base + ws.pl_part_o);
+    float *out = (float *)(base + ws.pl_out);
+    float2 *best = (float2 *)(base + ws.pl_best);
+    RowRecord *rec = (RowRecord *)(base + ws.pl_records);
+    const bool need_o = a.variant == OBC_KEY || a.variant == OBC_JOINT || a.variant == OBC_ALL;
+    const int BH = a.B * a.Hkv, M = a.G * a.W;
+    const size_t variant_stride = (size_t)BH * a.N;
+    const bool one_piece = ws.pl_heads >= BH && ws.pl_rows >= M && ws.pl_seg >= a.N;
+    // A piece's buffers hold nothing of the other pieces: with several, a later stage repeats the earlier ones.
+    const int mask = one_piece ? a.stage_mask : a.stage_mask & OBC_STAGE_SWEEP2 ? (int)OBC_STAGE_ALL
+                     : a.stage_mask & OBC_STAGE_COMBINE ? OBC_STAGE_SWEEP1 | OBC_STAGE_COMBINE : a.stage_mask;
+    const int segs = (a.N + ws.pl_seg - 1) / ws.pl_seg;
+    hipError_t e = hipSuccess;
+    for (int bg0 = 0; bg0 < BH; bg0 += ws.pl_heads)
+        for (int r0 = 0; r0 < M; r0 += ws.pl_rows) {
+            Piece w;
+            w.bg0 = bg0; w.r0 = r0; w.nr = std::min(ws.pl_rows, M - r0); w.z_stride = ws.pl_seg;
+            const unsigned heads = std::min(ws.pl_heads, BH - bg0), chunks = (w.nr + 16 * kRt - 1) / (16 * kRt);
+            auto segment = [&](int i) { w.s0 = i * ws.pl_seg; w.s1 = std::min(w.s0 + ws.pl_seg, a.N); };
+            auto logits = [&]() {
+                plain_logits<T, D, kRt><<<dim3((w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range, chunks, heads), dim3(kThreads), 0, stream>>>(
+                    q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, ws.pl_range, ws.pl_ranges, z, best);
+                e = hipGetLastError();
+                return e == hipSuccess;
+            };
+            if (mask & OBC_STAGE_SWEEP1) {
+                for (int i = 0; i < segs; ++i) {             // every range's maximum first
+                    segment(i);
+                    if (!logits()) return e;
+                }
+                for (int i = 0; i < segs; ++i) {
+                    segment(i);
+                    if (segs > 1 && !logits()) return e;
+                    const dim3 grid((w.s1 - w.s0 + ws.pl_split - 1) / ws.pl_split, chunks, heads);
+                    if (need_o)
+                        plain_weights<T, D, kRt, true><<<grid, dim3(kThreads), 0, stream>>>(
+                            v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
+                            best, rec, part_l, part_o);
+                    else
+                        plain_weights<T, D, kRt, false><<<grid, dim3(kThreads), 0, stream>>>(
+                            v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
+                            best, rec, part_l, part_o);
+                    if ((e = hipGetLastError()) != hipSuccess) return e;
+                }
+            }
+            if (mask & OBC_STAGE_COMBINE) {
+                const dim3 grid((w.nr + 3) / 4, 1, heads);
+                if (need_o)
+                    plain_merge<T, D, true><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, a.lens, w, ws.pl_split,
+                                                                                 ws.pl_splits, part_l, part_o, rec, out);
+                else
+                    plain_merge<T, D, false><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, a.lens, w, ws.pl_split,
+                                                                                  ws.pl_splits, part_l, part_o, rec, out);
+                if ((e = hipGetLastError()) != hipSuccess) return e;
+            }
+            if (!(mask & OBC_STAGE_SWEEP2)) continue;
+            for (int i = 0; i < segs; ++i) {
+                segment(i);
+                if (segs > 1 && !logits()) return e;
+                const dim3 grid((w.s1 - w.s0 + kTile - 1) / kTile, 1, heads);
+                const int add = a.accumulate || r0 > 0;
+#define OBC_PLAIN_SCORE(variant)                                                                                       \
+    plain_score<T, D, kRt, variant><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, z, rec, \
+                                                                         out, a.scores, variant_stride, add)
+                switch (a.variant) {
+                    case OBC_VALUE: OBC_PLAIN_SCORE(OBC_VALUE); break;
+                    case OBC_KEY: OBC_PLAIN_SCORE(OBC_KEY); break;
+                    case OBC_JOINT: OBC_PLAIN_SCORE(OBC_JOINT); break;
+                    case OBC_ATTN: OBC_PLAIN_SCORE(OBC_ATTN); break;
+                    case OBC_VATP: OBC_PLAIN_SCORE(OBC_VATP); break;
+                    default: OBC_PLAIN_SCORE(OBC_ALL); break;
+                }
+#undef OBC_PLAIN_SCORE
+                if ((e = hipGetLastError()) != hipSuccess) return e;
+            }
+        }
+    return hipSuccess;
+}
+
+// 16-row tiles of a workgroup: four where the rows fill them (a workgroup reads its tokens once for all of them).
+int row_tiles(int rows) { return rows <= 16 ? 1 : (rows + 31) / 32 % 2 ? 2 : 4; }
+
+template <typename T, int D>
+hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+    switch (row_tiles(std::min(ws.pl_rows, a.G * a.W))) {
+        case 1: return run<T, D, 1>(a, ws, base, stream);
+        case 2: return run<T, D, 2>(a, ws, base, stream);
+        default: return run<T, D, 4>(a, ws, base, stream);
     }
-    if (!(a.stage_mask & OBC_STAGE_SWEEP2)) return hipSuccess;
-    const dim3 grid((a.N + kTile - 1) / kTile, a.B * a.Hkv);
-    plain_score<T, D><<<grid, dim3(kThreads), 0, stream>>>(
-        (const T *)a.q, (const T *)a.k, (const T *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, a.variant, row_max,
-        row_sum, out, out_rest, rest_frac, top_token, a.scores, (size_t)a.B * a.Hkv * a.N, a.accumulate);
-    return hipGetLastError();
 }
 
 }  // namespace
 
+// Pieces.  `cap` bounds the workspace: as many KV heads at a time as fit, then as many rows of one head, then as many
+// tokens.  Within it a launch should have work for 256 CUs: two workgroups each of the logit kernel with up to kMaxRanges
+// ranges per row (every later workgroup reads the maxima of all of them), two of the weight kernel.
+void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWorkspace *ws, size_t *off) {
+    auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
+    const int BH = B * Hkv, M = Hq / Hkv * W;
+    ws->pl_range = (int)align_up((N + kMaxRanges - 1) / kMaxRanges, kTile);
+    ws->pl_ranges = (N + ws->pl_range - 1) / ws->pl_range;
+    const long long chunks = (long long)BH * ((M + 63) / 64);
+    const long long most = std::min<long long>(kMaxSplits, (N + kTile - 1) / kTile);
+    const long long splits = std::max<long long>(1, std::min<long long>(most, (512 + chunks - 1) / chunks));
+    ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
+    ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
+    auto row_bytes = [&]() {                                 // of one row, beside its logits
+        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * 4 + (size_t)ws->pl_splits * (d + 1) * 4;
+    };
+    const size_t per_row = row_bytes() + (size_t)N * 4;
+    cap -= 6 * 256;                                          // alignment of the buffers
+    ws->pl_seg = N;
+    ws->pl_rows = M;
+    ws->pl_heads = (int)std::min<size_t>(BH, cap / (per_row * M));
+    if (ws->pl_heads < 1) {
+        ws->pl_heads = 1;
+        ws->pl_rows = (int)std::min<size_t>(M, cap / per_row / 16 * 16);
+        if (ws->pl_rows < 1) {
+            // One tile of rows at a time and as many tokens as fit, in whole splits (here also the ranges).
+            ws->pl_rows = std::min(M, 16);
+            ws->pl_split = ws->pl_range = (int)align_up((N + 1023) / 1024, kTile);
+            ws->pl_splits = ws->pl_ranges = (N + ws->pl_split - 1) / ws->pl_split;
+            const size_t room = cap / ws->pl_rows / 4, taken = row_bytes() / 4;
+            const size_t seg = room > taken ? (room - taken) / ws->pl_split * ws->pl_split : 0;
+            ws->pl_seg = (int)std::min<size_t>(align_up(N, ws->pl_split), std::max<size_t>(seg, ws->pl_split));
+        }
+    }
+    const size_t rows = (size_t)ws->pl_heads * ws->pl_rows;
+    auto take = [&](size_t *at, size_t bytes) { *at = *off; *off = align_up(*off + bytes, 256); };
+    take(&ws->pl_z, rows * ws->pl_seg * 4);
+    take(&ws->pl_best, rows * ws->pl_ranges * sizeof(float2));
+    take(&ws->pl_records, rows * sizeof(RowRecord));
+    take(&ws->pl_out, rows * d * 4);
+    take(&ws->pl_part_l, rows * ws->pl_splits * 4);
+    take(&ws->pl_part_o, rows * ws->pl_splits * d * 4);
+}
+
 hipError_t launch_score_plain(const ScoreArgs &a, const ScoreWorkspace &ws, char *ws_base, hipStream_t stream) {
     if (a.dtype == OBC_F32) {
-        if (a.d == 64) return run<float, 64>(a, ws, ws_base, stream);
-        if (a.d == 128) return run<float, 128>(a, ws, ws_base, stream);
+        if (a.d == 64) return run_rows<float, 64>(a, ws, ws_base, stream);
+        if (a.d == 128) return run_rows<float, 128>(a, ws, ws_base, stream);
     } else {
-        if (a.d == 64) return run<uint16_t, 64>(a, ws, ws_base, stream);
-        if (a.d == 128) return run<uint16_t, 128>(a, ws, ws_base, stream);
+        if (a.d == 64) return run_rows<uint16_t, 64>(a, ws, ws_base, stream);
+        if (a.d == 128) return run_rows<uint16_t, 128>(a, ws, ws_base, stream);
     }
     return hipErrorInvalidValue;
 }

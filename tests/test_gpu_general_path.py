@@ -1,0 +1,72 @@
+"""The general scoring path where its tiles and pieces can go wrong, against the oracle and against itself.
+
+Row counts around the 16-row tiles and their chunks, token counts around the 64-token tiles, ranges and splits, both
+types and head sizes; then caches whose logits exceed the workspace plan, which are scored in pieces of rows and of tokens.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2510_07651_amd import binding as obc
+
+from parity_util import TOL, score_error
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, d, G, W, N, lens): rows G*W and tokens at and next to tile edges
+EDGES = [("fp32", 64, 1, 1, 1, None), ("fp32", 128, 1, 15, 63, None), ("fp32", 64, 1, 16, 64, [64, 17]),
+         ("fp32", 128, 1, 17, 65, [65, 64]), ("bf16", 64, 2, 16, 129, None), ("fp32", 64, 3, 11, 4097, [4097, 4032]),
+         ("bf16", 64, 7, 9, 4160, [4160, 4159]), ("fp32", 128, 4, 16, 4161, None), ("bf16", 64, 13, 5, 1000, [1000, 65]),
+         ("fp32", 128, 8, 64, 300, [300, 64]), ("bf16", 128, 3, 43, 700, [700, 321])]
+
+
+def _inputs(dtype, d, G, W, N, B, Hkv, seed):
+    gen = torch.Generator().manual_seed(seed)
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    q, k, v = (torch.randn(B, H, n, d, generator=gen).to(dt) for H, n in ((G * Hkv, W), (Hkv, N), (Hkv, N)))
+    k[:, :, 0] = (3 * q.float().view(B, Hkv, G * W, d).mean(dim=2)).to(dt)
+    return q, k, v
+
+
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: "%s_d%d_%dx%d_%d" % c[:5])
+def test_tile_edges_match_oracle(case, score_path):
+    dtype, d, G, W, N, lens = case
+    B, Hkv = (1 if lens is None else len(lens)), 2
+    q, k, v = _inputs(dtype, d, G, W, N, B, Hkv, 31)
+    ref = oracle.score(q, k, v, seq_lens=lens)
+    if lens is not None:
+        for b, n in enumerate(lens):
+            k[b, :, n:] = float("nan")
+            v[b, :, n:] = float("nan")
+    score_path("plain")
+    qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
+    got = obc.obc_score(qd, kd, vd, "all", seq_lens=lens)
+    budget = max(1, min(lens or [N]) // 4)
+    for i, name in enumerate(("value", "key", "joint")):
+        err, where = score_error(got[i].cpu().numpy(), ref[i], budget, lens, TOL["fp32"])
+        assert err <= TOL["fp32"], (name, err, where)       # the path's own precision, whatever the storage type
+        one = obc.obc_score(qd, kd, vd, name, seq_lens=lens)
+        assert torch.equal(one, got[i]), name
+    run = torch.full_like(got[2], 2.0)
+    obc.obc_score(qd, kd, vd, "joint", seq_lens=lens, scores=run, accumulate=True)
+    for b, n in enumerate(lens or [N]):
+        assert torch.equal(run[b, :, :n], got[2][b, :, :n] + 2.0) and bool((run[b, :, n:] == 2.0).all())
+
+
+# (G, W, N, Hkv): static scratch holds the logits of a few heads / of a part of one head's rows / of a part of the tokens
+PIECES = [(4, 32, 13001, 12), (8, 64, 40003, 1), (1, 16, 900003, 1)]
+
+
+@pytest.mark.parametrize("case", PIECES, ids=["heads", "rows", "tokens"])
+def test_pieces_agree_with_one_piece(case):
+    G, W, N, Hkv = case
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn(1, H, n, 64, generator=gen, device="cuda") for H, n in ((G * Hkv, W), (Hkv, N), (Hkv, N)))
+    assert obc.obc_score_workspace_bytes(1, N, W, G * Hkv, Hkv, 64, obc.OBC_F32, obc.OBC_ALL) > obc.OBC_STATIC_SCRATCH_BYTES
+    want = obc.obc_score(q, k, v, "all")
+    got = torch.full_like(want, -1.0)
+    obc.obc_score_static(q, k, v, "all", got)
+    for i in range(3):
+        err, where = score_error(got[i].cpu().numpy(), want[i].cpu().numpy().astype(np.float64), 1000, None, TOL["fp32"])
+        assert err <= TOL["fp32"], (i, err, where)
