@@ -40,6 +40,7 @@ constexpr int kTile = 64;        // tokens per tile; each of the four waves owns
 constexpr int kThreads = 256;    // 4 waves
 constexpr int kMaxRanges = 64;   // token ranges with a row maximum of their own, at most
 constexpr int kMaxSplits = 32;   // sequence splits of P V, at most
+constexpr int kResident = 1024;  // workgroups the chip holds at four per CU: a launch is cut into about this many
 constexpr int kNoToken = 0x7fffffff;
 
 // What one launch works on: KV heads bg0 .. bg0 + gridDim.z - 1, their window rows r0 .. r0 + nr - 1 (of the G*W rows
@@ -55,13 +56,23 @@ struct RowRecord {
     int top;                     // lowest token that attains it
     float inv_l;                 // 1 / sum of exp(z - m)
     float top_dk, top_dj;        // ||v - o||^2 and ||v + Z (v - o)||^2 of the top token
-    float pad;
+    int last;                    // last token the row sees
     double oo;                   // ||o_i||^2
 };
 
 template <typename T> __device__ __forceinline__ float load_as_float(const T *p);
 template <> __device__ __forceinline__ float load_as_float<float>(const float *p) { return *p; }
 template <> __device__ __forceinline__ float load_as_float<uint16_t>(const uint16_t *p) { return bf16_bits_to_float(*p); }
+
+// exp(x) for x <= 0.  The product x log2(e) is carried as a pair, so that the argument of exp2 keeps full fp32 accuracy
+// however large |x| is: exp(x) = 2^t (1 + ln2 r) with t + r = x log2(e).  Results below 2^-126 become 0.
+__device__ __forceinline__ float exp_nonpositive(float x) {
+    const float log2e = 1.44269504f, log2e_rest = 1.925963033500e-8f;      // log2(e) = 1.44269504 (as fp32) + the rest
+    const float t = x * log2e;
+    const float r = fmaf(x, log2e_rest, fmaf(x, log2e, -t));
+    const float e = __builtin_amdgcn_exp2f(t);
+    return fmaf(e, r * 0.693147181f, e);
+}
 
 // Fixed-order tree sum over the 64 lanes.
 template <typename F>
@@ -122,24 +133,50 @@ struct TileRegs {
     }
 };
 
-// fp64 dot products of 16 kRt rows and this wave's 16 tokens: acc[rt][r] is row 16 rt + 4 r + lane / 16, token lane % 16.
-// The four k values of a matrix op are components c of the four lane groups' 16-byte pieces: any assignment of
-// elements to k will do as long as both operands use the same, and this one reads LDS 16 bytes at a time.
-template <int D, int kRt>
-__device__ __forceinline__ void tile_dots(const float *rows, const float *toks, int lane, f64x4 (&acc)[kRt]) {
-    const float *rp = rows + (lane & 15) * kStride<D> + 4 * (lane >> 4);
-    const float *tp = toks + (lane & 15) * kStride<D> + 4 * (lane >> 4);
-#pragma unroll 2
-    for (int s = 0; s < D / 16; ++s) {
-        const f32x4 t = *(const f32x4 *)(tp + 16 * s);
-        f32x4 a[kRt];
+// One row of a tile in the registers of the four lanes that share it (lane = row % 16 + 16 j): the 16-byte pieces
+// 4 j .. 4 j + 3 of every sixteen elements, as fp32.
+template <typename T, int D>
+struct RowRegs {
+    f32x4 x[D / 16];
+    // (a row at or beyond `limit` becomes zeros; its memory is never read)
+    __device__ __forceinline__ void load(const T *__restrict__ base, int row, int limit, int j) {
+        const T *src = base + (size_t)row * D + 4 * j;
 #pragma unroll
-        for (int rt = 0; rt < kRt; ++rt) a[rt] = *(const f32x4 *)(rp + rt * 16 * kStride<D> + 16 * s);
+        for (int s = 0; s < D / 16; ++s) {
+            if (sizeof(T) == 4) {
+                x[s] = row < limit ? *(const f32x4 *)(src + 16 * s) : f32x4{0.f, 0.f, 0.f, 0.f};
+            } else {
+                const uint2 h = row < limit ? *(const uint2 *)(src + 16 * s) : make_uint2(0u, 0u);
+                x[s] = f32x4{__uint_as_float(h.x << 16), __uint_as_float(h.x & 0xffff0000u), __uint_as_float(h.y << 16),
+                             __uint_as_float(h.y & 0xffff0000u)};
+            }
+        }
+    }
+};
+
+// fp64 dot products of 16 kRt rows in LDS and this wave's 16 tokens: acc[rt][r] is row 16 rt + 4 r + lane / 16, token
+// lane % 16.  The four k values of a matrix op are components c of the four lane groups' 16-byte pieces: any assignment
+// of elements to k will do as long as both operands use the same, and this one reads 16 bytes at a time.
+template <typename T, int D, int kRt>
+__device__ __forceinline__ void tile_dots(const float *rows, const RowRegs<T, D> &tok, int lane, f64x4 (&acc)[kRt]) {
+    const float *rp = rows + (lane & 15) * kStride<D> + 4 * (lane >> 4);
+    asm volatile("" ::: "memory");                           // (the row operands are not to be kept across calls)
+    f32x4 a[2][kRt];
+#pragma unroll
+    for (int rt = 0; rt < kRt; ++rt) a[0][rt] = *(const f32x4 *)(rp + rt * 16 * kStride<D>);
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) {
+        if (s + 1 < D / 16)
+#pragma unroll
+            for (int rt = 0; rt < kRt; ++rt) a[(s + 1) & 1][rt] = *(const f32x4 *)(rp + rt * 16 * kStride<D> + 16 * (s + 1));
+        __builtin_amdgcn_sched_barrier(0);                   // (one step's operands ahead, no more: registers)
+        f32x4 t = tok.x[s];
+        asm volatile("" : "+v"(t));                          // (nor its fp64 form, which is twice as large)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
             for (int rt = 0; rt < kRt; ++rt)
-                acc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[rt][c], (double)t[c], acc[rt], 0, 0, 0);
+                acc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s & 1][rt][c], (double)t[c], acc[rt], 0, 0, 0);
     }
 }
 
@@ -147,13 +184,14 @@ __device__ __forceinline__ void tile_dots(const float *rows, const float *toks, 
 // Logits.  Grid: x = token range of the piece, y = chunk of 16 kRt rows, z = KV head.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int kRt>
-__global__ __launch_bounds__(kThreads, 2) void plain_logits(const T *__restrict__ q, const T *__restrict__ k, int N, int W,
+__global__ __launch_bounds__(kThreads, 4) void plain_logits(const T *__restrict__ q, const T *__restrict__ k, int N, int W,
                                                             int Hq, int Hkv, int ragged, SeqLens lens, Piece w,
                                                             int range_len, int n_ranges, float *__restrict__ z,
                                                             float2 *__restrict__ range_best) {
     constexpr int kRows = 16 * kRt;
-    __shared__ __attribute__((aligned(16))) float rows_s[kRows * kStride<D>], toks_s[kTile * kStride<D>];
+    __shared__ __attribute__((aligned(16))) float rows_s[kRows * kStride<D>];
     __shared__ float2 best_s[4][kRows];
+    __shared__ int last_s[kRows];                            // last token each row sees; -1: no such row
 
     const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv, g = bg % Hkv, M = Hq / Hkv * W;
     const int len = seq_len_of(lens, ragged, b, N);
@@ -164,27 +202,29 @@ __global__ __launch_bounds__(kThreads, 2) void plain_logits(const T *__restrict_
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 
     const T *kg = k + (size_t)bg * N * D;
-    TileRegs<T, D, kTile> next;
-    next.load(kg, t_begin, len);
+    RowRegs<T, D> tok;
+    tok.load(kg, t_begin + wave * 16 + (lane & 15), t_end, lane >> 4);
     {
         TileRegs<T, D, kRows> qr;
         qr.load(q + ((size_t)b * Hq * W + (size_t)g * M + w.r0) * D, row0, w.nr);
         qr.store(rows_s);
     }
+    if ((int)threadIdx.x < kRows) {
+        const int row = row0 + threadIdx.x;
+        last_s[threadIdx.x] = row < w.nr ? len - W + (w.r0 + row) % W : -1;
+    }
     float m[kRt * 4];
     int at[kRt * 4];
 #pragma unroll
     for (int i = 0; i < kRt * 4; ++i) { m[i] = -INFINITY; at[i] = kNoToken; }
+    __syncthreads();
     for (int t0 = t_begin; t0 < t_end; t0 += kTile) {
-        __syncthreads();                                     // the tile before this one has been read
-        next.store(toks_s);
-        __syncthreads();
-        if (t0 + kTile < t_end) next.load(kg, t0 + kTile, len);
+        const int p = t0 + wave * 16 + (lane & 15);
         f64x4 acc[kRt];
 #pragma unroll
         for (int rt = 0; rt < kRt; ++rt) acc[rt] = f64x4{0.0, 0.0, 0.0, 0.0};
-        tile_dots<D, kRt>(rows_s, toks_s + wave * 16 * kStride<D>, lane, acc);
-        const int p = t0 + wave * 16 + (lane & 15);
+        tile_dots<T, D, kRt>(rows_s, tok, lane, acc);
+        if (t0 + kTile < t_end) tok.load(kg, p + kTile, t_end, lane >> 4);
         float *zp = z + ((size_t)hl * w.nr + row0) * w.z_stride + (p - w.s0);
 #pragma unroll
         for (int rt = 0; rt < kRt; ++rt)
@@ -192,11 +232,11 @@ __global__ __launch_bounds__(kThreads, 2) void plain_logits(const T *__restrict_
             for (int r = 0; r < 4; ++r) {
                 const int row = 16 * rt + 4 * r + (lane >> 4), i = rt * 4 + r;
                 const float x = (float)(acc[rt][r] * (1.0 / sqrt((double)D)));   // scaled logit: the only rounding
-                if (p < t_end && row0 + row < w.nr) {
-                    zp[(size_t)row * w.z_stride] = x;
-                    // (tokens ascend: strict keeps the lane's lowest)
-                    if (p <= len - W + (w.r0 + row0 + row) % W && x > m[i]) { m[i] = x; at[i] = p; }
-                }
+                const bool seen = p < t_end && p <= last_s[row];             // (what a row does not see is never read)
+                if (seen) zp[(size_t)row * w.z_stride] = x;
+                const bool better = seen && x > m[i];                        // (tokens ascend: strict keeps the lowest)
+                m[i] = better ? x : m[i];
+                at[i] = better ? p : at[i];
             }
     }
 #pragma unroll
@@ -228,9 +268,10 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
                                                              const float2 *__restrict__ range_best,
                                                              RowRecord *__restrict__ records, float *__restrict__ part_l,
                                                              float *__restrict__ part_o) {
-    constexpr int kRows = 16 * kRt, kPs = kTile + 4;
+    // Tiles of 32 tokens, two of each in LDS: while the matrix cores take one, the weights of the next are formed.
+    constexpr int kRows = 16 * kRt, kTok = 32, kPs = kTok + 4;
     constexpr int kCt = D / 64;                              // 16-column tiles of V per wave
-    __shared__ __attribute__((aligned(16))) float p_s[kNeedO ? kRows * kPs : 4], v_s[kNeedO ? kTile * kStride<D> : 4];
+    __shared__ __attribute__((aligned(16))) float p_s[2][kNeedO ? kRows * kPs : 4], v_s[2][kNeedO ? kTok * kStride<D> : 4];
     __shared__ float m_s[kRows];
     __shared__ int top_s[kRows];
 
@@ -243,8 +284,8 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 
     const T *vg = v + (size_t)bg * N * D;
-    TileRegs<T, D, kTile> next;
-    if (kNeedO) next.load(vg, t_begin, len);
+    TileRegs<T, D, kTok> next;
+    if (kNeedO) next.load(vg, t_begin, t_end);
     {
         // the row's maximum over its ranges: kThreads / kRows lanes per row
         constexpr int kSub = kThreads / kRows;
@@ -252,6 +293,7 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
         float m = -INFINITY;
         int at = kNoToken;
         if (row0 + row < w.nr)
+#pragma unroll 4
             for (int i = threadIdx.x % kSub; i < live; i += kSub) {
                 const float2 o = range_best[((size_t)hl * w.nr + row0 + row) * n_ranges + i];
                 if (o.x > m || (o.x == m && __float_as_int(o.y) < at)) { m = o.x; at = __float_as_int(o.y); }
@@ -268,65 +310,81 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
         }
     }
     __syncthreads();
-    constexpr int kMine = kRows / 4;                         // this thread's rows: wave, wave + 4, ...
-    float m[kMine], sum[kMine];
+    constexpr int kMine = kRows / 8;                         // this thread's rows: first, first + 8, ...
+    const int first = 2 * wave + (lane >> 5), col = lane & 31;
+    float m[kMine], sum[kMine], x[kMine];
     int top[kMine], last[kMine];
+    const float *zp[kMine];
 #pragma unroll
     for (int i = 0; i < kMine; ++i) {
-        const int row = wave + 4 * i;
+        const int row = first + 8 * i;
         m[i] = m_s[row];
         top[i] = top_s[row];
         last[i] = row0 + row < w.nr ? min(len - W + (w.r0 + row0 + row) % W, t_end - 1) : -1;     // last token it sees here
         sum[i] = 0.f;
+        zp[i] = z + ((size_t)hl * w.nr + row0 + row) * w.z_stride - w.s0;
     }
-    f32x4 acc[kRt][kCt > 0 ? kCt : 1];
+    auto fetch = [&](int t0) {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) x[i] = t0 + col <= last[i] ? zp[i][t0 + col] : 0.f;
+    };
+    auto weigh = [&](int t0, int slot) {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            const float e = t0 + col <= last[i] && t0 + col != top[i] ? exp_nonpositive(x[i] - m[i]) : 0.f;
+            sum[i] += e;
+            if (kNeedO) p_s[slot][(first + 8 * i) * kPs + col] = e;
+        }
+        if (kNeedO) next.store(v_s[slot]);
+    };
+    f32x4 acc[kRt][kCt];
 #pragma unroll
     for (int rt = 0; rt < kRt; ++rt)
 #pragma unroll
         for (int ct = 0; ct < kCt; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    for (int t0 = t_begin; t0 < t_end; t0 += kTile) {
-        const int p = t0 + lane;
-        float x[kMine];
-#pragma unroll
-        for (int i = 0; i < kMine; ++i)
-            x[i] = p <= last[i] ? z[((size_t)hl * w.nr + row0 + wave + 4 * i) * w.z_stride + (p - w.s0)] : 0.f;
+    fetch(t_begin);
+    weigh(t_begin, 0);
+    if (t_begin + kTok < t_end) {
+        fetch(t_begin + kTok);
+        if (kNeedO) next.load(vg, t_begin + kTok, t_end);
+    }
+    for (int t0 = t_begin, slot = 0; t0 < t_end; t0 += kTok, slot ^= 1) {
         if (kNeedO) {
-            __syncthreads();                                 // the tiles before these have been read
-            next.store(v_s);
+            __syncthreads();                                 // this tile is in LDS, the one before it has been read
+            // P V: this wave's 16 kCt columns of every row.  k value j of a matrix op is token 4 j + c of sixteen.
+#pragma unroll
+            for (int s = 0; s < kTok / 16; ++s) {
+                f32x4 a[kRt];
+#pragma unroll
+                for (int rt = 0; rt < kRt; ++rt)
+                    a[rt] = *(const f32x4 *)(p_s[slot] + (16 * rt + (lane & 15)) * kPs + 16 * s + 4 * (lane >> 4));
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int ct = 0; ct < kCt; ++ct) {
+                        const float vv = v_s[slot][(16 * s + 4 * (lane >> 4) + c) * kStride<D> + (wave * kCt + ct) * 16 + (lane & 15)];
+#pragma unroll
+                        for (int rt = 0; rt < kRt; ++rt)
+                            acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rt][c], vv, acc[rt][ct], 0, 0, 0);
+                    }
+            }
         }
-#pragma unroll
-        for (int i = 0; i < kMine; ++i) {
-            const float e = p <= last[i] && p != top[i] ? expf(x[i] - m[i]) : 0.f;
-            sum[i] += e;
-            if (kNeedO) p_s[(wave + 4 * i) * kPs + lane] = e;
-        }
-        if (!kNeedO) continue;
-        __syncthreads();
-        if (t0 + kTile < t_end) next.load(vg, t0 + kTile, len);
-        // P V: this wave's 16 kCt columns of every row.  k value j of a matrix op is token 4 j + c of the sixteen.
-#pragma unroll
-        for (int s = 0; s < kTile / 16; ++s) {
-            f32x4 a[kRt];
-#pragma unroll
-            for (int rt = 0; rt < kRt; ++rt)
-                a[rt] = *(const f32x4 *)(p_s + (16 * rt + (lane & 15)) * kPs + 16 * s + 4 * (lane >> 4));
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int ct = 0; ct < kCt; ++ct) {
-                    const float vv = v_s[(16 * s + 4 * (lane >> 4) + c) * kStride<D> + (wave * kCt + ct) * 16 + (lane & 15)];
-#pragma unroll
-                    for (int rt = 0; rt < kRt; ++rt)
-                        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rt][c], vv, acc[rt][ct], 0, 0, 0);
-                }
+        if (t0 + kTok < t_end) {
+            weigh(t0 + kTok, slot ^ 1);
+            if (t0 + 2 * kTok < t_end) {
+                fetch(t0 + 2 * kTok);
+                if (kNeedO) next.load(vg, t0 + 2 * kTok, t_end);
+            }
         }
     }
     const size_t out_row = ((size_t)hl * n_splits + split) * w.nr + row0;
 #pragma unroll
     for (int i = 0; i < kMine; ++i) {
-        const float s = wave_sum(sum[i]);
-        if (lane == 0 && row0 + wave + 4 * i < w.nr) part_l[out_row + wave + 4 * i] = s;
+        float s = sum[i];
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        if (col == 0 && row0 + first + 8 * i < w.nr) part_l[out_row + first + 8 * i] = s;
     }
     if (!kNeedO) return;
 #pragma unroll
@@ -344,7 +402,7 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
 // Merge.  One wave per row, D / 64 elements per lane.  Grid: x = four rows of the piece, z = KV head.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, bool kNeedO>
-__global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int Hkv, int ragged, SeqLens lens,
+__global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, SeqLens lens,
                                                         Piece w, int split_len, int n_splits,
                                                         const float *__restrict__ part_l, const float *__restrict__ part_o,
                                                         RowRecord *__restrict__ records, float *__restrict__ out) {
@@ -390,6 +448,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
         dj = wave_sum(dj);
     }
     if (lane == 0) {
+        rec->last = len - W + (w.r0 + row) % W;
         rec->inv_l = 1.0f / (1.0f + l);
         rec->top_dk = (float)dk;
         rec->top_dj = (float)dj;
@@ -398,12 +457,13 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
 }
 
 // ------------------------------------------------------------------------------------
-// Scores.  Grid: x = tile of 64 tokens of the piece, z = KV head.  `add`: on top of what `scores` holds (the caller's
-// running scores, or the rows of an earlier piece).
+// Scores.  Grid: x = `n_tiles` tiles of 64 tokens of the piece, z = KV head.  `add`: on top of what `scores` holds (the
+// caller's running scores, or the rows of an earlier piece).
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int kRt, int kVariant>
-__global__ __launch_bounds__(kThreads, 2) void plain_score(const T *__restrict__ v, int N, int W, int Hq, int Hkv,
-                                                           int ragged, SeqLens lens, Piece w, const float *__restrict__ z,
+__global__ __launch_bounds__(kThreads, 4) void plain_score(const T *__restrict__ v, int N, int Hkv,
+                                                           int ragged, SeqLens lens, Piece w, int n_tiles,
+                                                           const float *__restrict__ z,
                                                            const RowRecord *__restrict__ records,
                                                            const float *__restrict__ out, float *__restrict__ scores,
                                                            size_t variant_stride, int add) {
@@ -411,100 +471,99 @@ __global__ __launch_bounds__(kThreads, 2) void plain_score(const T *__restrict__
     constexpr bool kAttnLike = kVariant == OBC_ATTN || kVariant == OBC_VATP;
     constexpr bool kNeedO = kVariant == OBC_KEY || kVariant == OBC_JOINT || kVariant == OBC_ALL;
     constexpr bool kNeedV = kVariant != OBC_ATTN;
-    __shared__ __attribute__((aligned(16))) float toks_s[kNeedV ? kTile * kStride<D> : 4], rows_s[kNeedO ? kRows * kStride<D> : 4];
+    __shared__ __attribute__((aligned(16))) float rows_s[kNeedO ? kRows * kStride<D> : 4];
     __shared__ __attribute__((aligned(16))) RowRecord rec_s[kRows];
 
     const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int t0 = w.s0 + blockIdx.x * kTile;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int p = t0 + wave * 16 + (lane & 15), j = lane >> 4;
-    float acc_v = 0.f, acc_k = 0.f, acc_j = 0.f;
-    if (t0 < len) {                                          // uniform
-        const bool live = p < len;
-        double vv = 0.0;
-        float l1 = 0.f;
-        if (kNeedV) {
-            TileRegs<T, D, kTile> tile;
-            tile.load(v + (size_t)bg * N * D, t0, len);
-            tile.store(toks_s);
-        }
-        for (int row0 = 0; row0 < w.nr; row0 += kRows) {
-            TileRegs<float, D, kRows> orow;
-            if (kNeedO) orow.load(out + (size_t)hl * w.nr * D, row0, w.nr);
-            float x[kRt * 4];
+    const int t_begin = w.s0 + blockIdx.x * n_tiles * kTile, t_end = min(t_begin + n_tiles * kTile, w.s1);
+    const int t_live = min(t_end, len);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, j = lane >> 4;
+    const T *vg = v + (size_t)bg * N * D;
+
+    for (int t0 = t_begin; t0 < t_end; t0 += kTile) {
+        const int p = t0 + wave * 16 + (lane & 15);
+        float acc_v = 0.f, acc_k = 0.f, acc_j = 0.f;
+        if (t0 < t_live) {                                   // uniform
+            RowRegs<T, D> tok;
+            double vv = 0.0;
+            float l1 = 0.f;
+            if (kNeedV) {                                    // ||v_p||^2 (and ||v_p||_1): four lanes per token
+                tok.load(vg, p, t_live, j);
 #pragma unroll
-            for (int i = 0; i < kRt * 4; ++i) {
-                const int row = row0 + 4 * i + j;
-                x[i] = live && row < w.nr ? z[((size_t)hl * w.nr + row) * w.z_stride + (p - w.s0)] : 0.f;
-            }
-            if (row0 > 0) __syncthreads();                   // the rows before these have been read
-            if (kNeedO) orow.store(rows_s);
-            if ((int)threadIdx.x < kRows && row0 + (int)threadIdx.x < w.nr)
-                rec_s[threadIdx.x] = records[(size_t)hl * w.nr + row0 + threadIdx.x];
-            __syncthreads();
-            if (kNeedV && row0 == 0) {                       // ||v_p||^2 (and ||v_p||_1): four lanes per token
-                const float *vp = toks_s + (wave * 16 + (lane & 15)) * kStride<D> + 4 * j;
-#pragma unroll 4
-                for (int s = 0; s < D / 16; ++s) {
-                    const f32x4 y = *(const f32x4 *)(vp + 16 * s);
+                for (int s = 0; s < D / 16; ++s)
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        vv += (double)y[c] * y[c];
-                        l1 += fabsf(y[c]);
+                        vv += (double)tok.x[s][c] * tok.x[s][c];
+                        l1 += fabsf(tok.x[s][c]);
                     }
-                }
                 vv += __shfl_xor(vv, 16);
                 vv += __shfl_xor(vv, 32);
                 l1 += __shfl_xor(l1, 16);
                 l1 += __shfl_xor(l1, 32);
             }
-            f64x4 acc[kRt];
+            for (int row0 = 0; row0 < w.nr; row0 += kRows) {
+                TileRegs<float, D, kRows> orow;
+                if (kNeedO) orow.load(out + (size_t)hl * w.nr * D, row0, w.nr);
+                float x[kRt * 4];
 #pragma unroll
-            for (int rt = 0; rt < kRt; ++rt) acc[rt] = f64x4{0.0, 0.0, 0.0, 0.0};
-            if (kNeedO) tile_dots<D, kRt>(rows_s, toks_s + wave * 16 * kStride<D>, lane, acc);
-#pragma unroll
-            for (int i = 0; i < kRt * 4; ++i) {
-                const int row = row0 + 4 * i + j;
-                if (!live || row >= w.nr || p > len - W + (w.r0 + row) % W) continue;
-                const RowRecord &rec = rec_s[4 * i + j];
-                const float a = expf(x[i] - rec.m) * rec.inv_l;
-                if (kAttnLike) {                             // Eq. 8: only the weight itself is summed
-                    acc_v += a;
-                    continue;
+                for (int i = 0; i < kRt * 4; ++i) {
+                    const int row = row0 + 4 * i + j;
+                    x[i] = p < t_live && row < w.nr ? z[((size_t)hl * w.nr + row) * w.z_stride + (p - w.s0)] : 0.f;
                 }
-                const float a2 = a * a;
-                acc_v = fmaf(a2, (float)vv, acc_v);
-                if (kNeedO) {
-                    const double vo = acc[i >> 2][i & 3], zd = x[i];
-                    const double d2 = (vv + rec.oo) - 2.0 * vo;                          // ||v_p - o_i||^2
-                    const bool is_top = p == rec.top;
-                    if (kVariant != OBC_JOINT)
-                        acc_k = fmaf(a2 * x[i] * x[i], is_top ? rec.top_dk : fmaxf((float)d2, 0.f), acc_k);
-                    if (kVariant != OBC_KEY) {
-                        const double dj = vv + zd * (2.0 * (vv - vo) + zd * d2);         // ||v_p + Z (v_p - o_i)||^2
-                        acc_j = fmaf(a2, is_top ? rec.top_dj : fmaxf((float)dj, 0.f), acc_j);
+                __syncthreads();                             // the rows before these have been read
+                if (kNeedO) orow.store(rows_s);
+                if ((int)threadIdx.x < kRows && row0 + (int)threadIdx.x < w.nr)
+                    rec_s[threadIdx.x] = records[(size_t)hl * w.nr + row0 + threadIdx.x];
+                __syncthreads();
+                f64x4 acc[kRt];
+#pragma unroll
+                for (int rt = 0; rt < kRt; ++rt) acc[rt] = f64x4{0.0, 0.0, 0.0, 0.0};
+                if (kNeedO) tile_dots<T, D, kRt>(rows_s, tok, lane, acc);
+#pragma unroll
+                for (int i = 0; i < kRt * 4; ++i) {
+                    __builtin_amdgcn_sched_barrier(0);       // (one row's constants at a time: registers)
+                    const int row = row0 + 4 * i + j;
+                    const RowRecord &r = rec_s[4 * i + j];
+                    if (row >= w.nr || p > r.last) continue;
+                    const float a = exp_nonpositive(x[i] - r.m) * r.inv_l;
+                    if (kAttnLike) {                         // Eq. 8: only the weight itself is summed
+                        acc_v += a;
+                        continue;
+                    }
+                    const float a2 = a * a;
+                    acc_v = fmaf(a2, (float)vv, acc_v);
+                    if (kNeedO) {
+                        const double vo = acc[i >> 2][i & 3], zd = x[i];
+                        const double d2 = (vv + r.oo) - 2.0 * vo;                        // ||v_p - o_i||^2
+                        const bool is_top = p == r.top;
+                        if (kVariant != OBC_JOINT)
+                            acc_k = fmaf(a2 * x[i] * x[i], is_top ? r.top_dk : fmaxf((float)d2, 0.f), acc_k);
+                        if (kVariant != OBC_KEY) {
+                            const double dj = vv + zd * (2.0 * (vv - vo) + zd * d2);     // ||v_p + Z (v_p - o_i)||^2
+                            acc_j = fmaf(a2, is_top ? r.top_dj : fmaxf((float)dj, 0.f), acc_j);
+                        }
                     }
                 }
             }
+            if (kVariant == OBC_VATP) acc_v *= l1;
+            acc_v += __shfl_xor(acc_v, 16);                  // the four lanes of a token held different rows
+            acc_v += __shfl_xor(acc_v, 32);
+            acc_k += __shfl_xor(acc_k, 16);
+            acc_k += __shfl_xor(acc_k, 32);
+            acc_j += __shfl_xor(acc_j, 16);
+            acc_j += __shfl_xor(acc_j, 32);
         }
-        if (kVariant == OBC_VATP) acc_v *= l1;
-        acc_v += __shfl_xor(acc_v, 16);                      // the four lanes of a token held different rows
-        acc_v += __shfl_xor(acc_v, 32);
-        acc_k += __shfl_xor(acc_k, 16);
-        acc_k += __shfl_xor(acc_k, 32);
-        acc_j += __shfl_xor(acc_j, 16);
-        acc_j += __shfl_xor(acc_j, 32);
-    }
-    if (j == 0 && p < min(w.s1, N)) {
-        float *dst = scores + (size_t)bg * N + p;
-        const float s[3] = {acc_v, acc_k, acc_j};
-        constexpr int kFirst = kVariant == OBC_ALL || kAttnLike ? 0 : kVariant, kCount = kVariant == OBC_ALL ? 3 : 1;
+        if (j == 0 && p < t_end) {
+            float *dst = scores + (size_t)bg * N + p;
+            const float s[3] = {acc_v, acc_k, acc_j};
+            constexpr int kFirst = kVariant == OBC_ALL || kAttnLike ? 0 : kVariant, kCount = kVariant == OBC_ALL ? 3 : 1;
 #pragma unroll
-        for (int c = 0; c < kCount; ++c) {
-            float *d = dst + c * variant_stride;
-            if (!add) *d = p < len ? s[kFirst + c] : 0.f;
-            else if (p < len) *d += s[kFirst + c];           // running scores: the padding is left alone
+            for (int c = 0; c < kCount; ++c) {
+                float *d = dst + c * variant_stride;
+                if (!add) *d = p < len ? s[kFirst + c] : 0.f;
+                else if (p < len) *d += s[kFirst + c];       // running scores: the padding is left alone
+            }
         }
     }
 }
@@ -527,6 +586,9 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
     const int mask = one_piece ? a.stage_mask : a.stage_mask & OBC_STAGE_SWEEP2 ? (int)OBC_STAGE_ALL
                      : a.stage_mask & OBC_STAGE_COMBINE ? OBC_STAGE_SWEEP1 | OBC_STAGE_COMBINE : a.stage_mask;
     const int segs = (a.N + ws.pl_seg - 1) / ws.pl_seg;
+    // Row tiles of the fp64 kernels: not more than two, which leaves registers for four waves per SIMD.  (With four and
+    // two the kernels keep more of each tile in flight and come out 0-10 % behind.)
+    constexpr int kFewRt = kRt < 2 ? kRt : 2;
     hipError_t e = hipSuccess;
     for (int bg0 = 0; bg0 < BH; bg0 += ws.pl_heads)
         for (int r0 = 0; r0 < M; r0 += ws.pl_rows) {
@@ -535,7 +597,7 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
             const unsigned heads = std::min(ws.pl_heads, BH - bg0), chunks = (w.nr + 16 * kRt - 1) / (16 * kRt);
             auto segment = [&](int i) { w.s0 = i * ws.pl_seg; w.s1 = std::min(w.s0 + ws.pl_seg, a.N); };
             auto logits = [&]() {
-                plain_logits<T, D, kRt><<<dim3((w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range, chunks, heads), dim3(kThreads), 0, stream>>>(
+                plain_logits<T, D, kFewRt><<<dim3((w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range, (w.nr + 16 * kFewRt - 1) / (16 * kFewRt), heads), dim3(kThreads), 0, stream>>>(
                     q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 e = hipGetLastError();
                 return e == hipSuccess;
@@ -563,10 +625,10 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
             if (mask & OBC_STAGE_COMBINE) {
                 const dim3 grid((w.nr + 3) / 4, 1, heads);
                 if (need_o)
-                    plain_merge<T, D, true><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, a.lens, w, ws.pl_split,
+                    plain_merge<T, D, true><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, a.lens, w, ws.pl_split,
                                                                                  ws.pl_splits, part_l, part_o, rec, out);
                 else
-                    plain_merge<T, D, false><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, a.lens, w, ws.pl_split,
+                    plain_merge<T, D, false><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, a.lens, w, ws.pl_split,
                                                                                   ws.pl_splits, part_l, part_o, rec, out);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
@@ -574,10 +636,11 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
             for (int i = 0; i < segs; ++i) {
                 segment(i);
                 if (segs > 1 && !logits()) return e;
-                const dim3 grid((w.s1 - w.s0 + kTile - 1) / kTile, 1, heads);
+                const int tiles = (w.s1 - w.s0 + kTile - 1) / kTile, n_tiles = (int)((tiles * (long long)heads + kResident - 1) / kResident);
+                const dim3 grid((tiles + n_tiles - 1) / n_tiles, 1, heads);
                 const int add = a.accumulate || r0 > 0;
 #define OBC_PLAIN_SCORE(variant)                                                                                       \
-    plain_score<T, D, kRt, variant><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, z, rec, \
+    plain_score<T, D, kFewRt, variant><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, a.lens, w, n_tiles, z, rec, \
                                                                          out, a.scores, variant_stride, add)
                 switch (a.variant) {
                     case OBC_VALUE: OBC_PLAIN_SCORE(OBC_VALUE); break;
@@ -594,31 +657,29 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
     return hipSuccess;
 }
 
-// 16-row tiles of a workgroup: four where the rows fill them (a workgroup reads its tokens once for all of them).
-int row_tiles(int rows) { return rows <= 16 ? 1 : (rows + 31) / 32 % 2 ? 2 : 4; }
-
 template <typename T, int D>
 hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
-    switch (row_tiles(std::min(ws.pl_rows, a.G * a.W))) {
-        case 1: return run<T, D, 1>(a, ws, base, stream);
-        case 2: return run<T, D, 2>(a, ws, base, stream);
-        default: return run<T, D, 4>(a, ws, base, stream);
-    }
+    // 16-row tiles of a workgroup: four where the rows fill them (a workgroup reads its tokens once for all of them).
+    const int rows = std::min(ws.pl_rows, a.G * a.W);
+    if (rows <= 16) return run<T, D, 1>(a, ws, base, stream);
+    if ((rows + 31) / 32 % 2 != 0) return run<T, D, 2>(a, ws, base, stream);
+    return run<T, D, 4>(a, ws, base, stream);
 }
 
 }  // namespace
 
 // Pieces.  `cap` bounds the workspace: as many KV heads at a time as fit, then as many rows of one head, then as many
-// tokens.  Within it a launch should have work for 256 CUs: two workgroups each of the logit kernel with up to kMaxRanges
-// ranges per row (every later workgroup reads the maxima of all of them), two of the weight kernel.
+// tokens.  Within it a launch should fill the chip once (kResident), so that no workgroup pays a prologue more than
+// needed and no last wave of workgroups is nearly empty; a row has at most kMaxRanges maxima, which every workgroup of the
+// weight kernel reads.
 void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv, M = Hq / Hkv * W;
-    ws->pl_range = (int)align_up((N + kMaxRanges - 1) / kMaxRanges, kTile);
+    const long long chunks = (long long)BH * ((M + 63) / 64), tiles = (N + kTile - 1) / kTile;
+    const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, (2 * tiles * chunks + kResident - 1) / kResident);     // (chunks of 64 rows here, of 32 there)
+    ws->pl_range = (int)(std::min(range_tiles, tiles) * kTile);
     ws->pl_ranges = (N + ws->pl_range - 1) / ws->pl_range;
-    const long long chunks = (long long)BH * ((M + 63) / 64);
-    const long long most = std::min<long long>(kMaxSplits, (N + kTile - 1) / kTile);
-    const long long splits = std::max<long long>(1, std::min<long long>(most, (512 + chunks - 1) / chunks));
+    const long long splits = std::max<long long>(1, std::min<long long>(std::min<long long>(kMaxSplits, tiles), (kResident / 2 + chunks - 1) / chunks));
     ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
     ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
     auto row_bytes = [&]() {                                 // of one row, beside its logits
