@@ -24,6 +24,8 @@ struct ScoreArgs {
     int ragged;       // 0: every sequence has length N
     int stage_mask;   // OBC_STAGE_* bits to run
     int accumulate;   // 1: add to the scores already in `scores` (positions beyond the true length untouched)
+    int find_lowest;  // 1 (decode path only): every range reports its lowest-scored token among evict_first <= p < len - evict_tail
+    int evict_first, evict_tail;
     SeqLens lens;     // valid for b < B when ragged
 };
 
@@ -56,7 +58,9 @@ struct ScoreWorkspace {
     int pl_split, pl_splits;   // tokens per split (a multiple of 64), splits
     // Decode path (one window row per query head): see score_decode.hip.
     size_t dec_z;      // float [B*Hkv*N*dec_rows]  scaled logits, token-major
-    size_t dec_part;   // float [B*Hkv*dec_splits*dec_rows*(d+4)]  per-range partial records
+    size_t dec_head;   // float4 [B*Hkv*dec_splits*dec_rows]  per-range partial records, their vectors below
+    size_t dec_vec;    // float [B*Hkv*dec_splits*dec_rows*2d]
+    size_t dec_lowest; // uint64 [B*Hkv*dec_splits]  a range's evict_candidate
     size_t dec_final;  // float [B*Hkv*dec_rows*(2d+4)]  merged row records
     int use_decode;    // 1: decode path (takes precedence over the other two)
     int dec_rows;      // query heads per KV head, padded to 1, 2, 4 or 8
@@ -107,16 +111,40 @@ hipError_t launch_compact(const void *k, const void *v, const int32_t *keep_idx,
                           int Hkv, int N, int budget, int row_bytes, hipStream_t stream);
 hipError_t launch_compact_in_place(void *k, void *v, float *scores, const int32_t *keep_idx, int B, int Hkv, int N,
                                    int budget, int row_bytes, hipStream_t stream);
-// Evict-one of a decoding step: picks, per (sequence, KV head), the lowest-scored token among first <= p < len - tail
-// (ties: the highest index) into `evicted`, then closes the gap in k, v and scores.
-hipError_t launch_evict_one(void *k, void *v, float *scores, int32_t *evicted, int B, int Hkv, int N, int ragged,
-                            const SeqLens &lens, int first, int tail, int row_bytes, hipStream_t stream);
+// Evict-one of a decoding step: the lowest-scored token of each (sequence, KV head) among first <= p < len - tail (ties:
+// the highest index) leaves k, v and scores, the gap is closed, and its position goes to `evicted` if that is not NULL.
+// `lowest` [B*Hkv, n_lowest]: candidates the scoring kernel has reported; with n_lowest == 0 they are found here, one per
+// head, and written there.
+hipError_t launch_evict_one(void *k, void *v, float *scores, int32_t *evicted, unsigned long long *lowest, int n_lowest,
+                            int B, int Hkv, int N, int ragged, const SeqLens &lens, int first, int tail, int row_bytes,
+                            hipStream_t stream);
 hipError_t launch_gather_scores(const float *in, const int32_t *keep_idx, float *out, int BH, int N, int budget,
                                  int n_out, hipStream_t stream);
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, int blocks, hipStream_t stream);
 
 __device__ __forceinline__ int seq_len_of(const SeqLens &lens, int ragged, int b, int N) {
     return ragged ? lens.len[b] : N;
+}
+
+// A token that may be evicted, packed so that one unsigned minimum picks the lowest score and the highest index among
+// equals (a protected selection of all but one competing token keeps the lower index).  Scores are ordered as the
+// selection kernels order them: -0 folded onto +0, NaN lowest.
+__device__ __forceinline__ unsigned long long evict_candidate(float score, int p) {
+    uint32_t u = __float_as_uint(score);
+    if (u == 0x80000000u) u = 0u;
+    u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    if (score != score) u = 0u;
+    return ((unsigned long long)u << 32) | (uint32_t)~p;
+}
+__device__ __forceinline__ int evict_candidate_token(unsigned long long c) { return (int)~(uint32_t)c; }
+
+__device__ __forceinline__ unsigned long long wave_min(unsigned long long x) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(x, off);
+        x = o < x ? o : x;
+    }
+    return x;
 }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t h) {

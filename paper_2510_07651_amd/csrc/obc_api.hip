@@ -158,7 +158,8 @@ int obc_score(const void *q, const void *k, const void *v, int N, int W, int Hq,
 
 static int score_impl(const void *q, const void *k, const void *v, int N, int W, int Hq, int Hkv, int d, int variant,
                       float *scores, int B, int dtype, const int32_t *seq_lens_host, void *workspace,
-                      size_t workspace_bytes, void *hip_stream, int stage_mask, int accumulate);
+                      size_t workspace_bytes, void *hip_stream, int stage_mask, int accumulate, int evict_first = -1,
+                      int evict_tail = 0);
 
 int obc_score_stages(const void *q, const void *k, const void *v, int N, int W, int Hq, int Hkv, int d, int variant,
                      float *scores, int B, int dtype, const int32_t *seq_lens_host, void *workspace,
@@ -183,9 +184,11 @@ int obc_score_static(const void *q, const void *k, const void *v, int N, int W, 
 }
 
 // `accumulate` bit 0: add to the scores; bit 1: use the library's static scratch (workspace must be NULL).
+// `evict_first` >= 0: the decode path also reports eviction candidates among evict_first <= p < len - evict_tail.
 static int score_impl(const void *q, const void *k, const void *v, int N, int W, int Hq, int Hkv, int d, int variant,
                       float *scores, int B, int dtype, const int32_t *seq_lens_host, void *workspace,
-                      size_t workspace_bytes, void *hip_stream, int stage_mask, int accumulate) {
+                      size_t workspace_bytes, void *hip_stream, int stage_mask, int accumulate, int evict_first,
+                      int evict_tail) {
     const bool own_scratch = (accumulate & 2) != 0;
     accumulate &= 1;
     if (!q || !k || !v || !scores) return OBC_EINVAL;
@@ -209,6 +212,9 @@ static int score_impl(const void *q, const void *k, const void *v, int N, int W,
     hipStream_t stream = (hipStream_t)hip_stream;
     a.stage_mask = stage_mask;
     a.accumulate = accumulate;
+    a.find_lowest = ws.use_decode && evict_first >= 0;
+    a.evict_first = evict_first;
+    a.evict_tail = evict_tail;
     const hipError_t e = ws.use_decode ? launch_score_decode(a, ws, (char *)workspace, stream)
                          : ws.use_mfma ? launch_score_mfma(a, ws, (char *)workspace, stream)
                                        : launch_score_plain(a, ws, (char *)workspace, stream);
@@ -332,7 +338,7 @@ int obc_decode_step_workspace_bytes(int B, int N, int Hq, int Hkv, int d, int dt
     ScoreWorkspace ws;
     const int rc = plan_score_workspace(B, N, 1, Hq, Hkv, d, dtype, variant, &ws);
     if (rc != OBC_OK) return rc;
-    *bytes_out = ws.total + align_up((size_t)B * Hkv * sizeof(int32_t), 256);
+    *bytes_out = ws.total + align_up((size_t)B * Hkv * sizeof(unsigned long long), 256);
     return OBC_OK;
 }
 
@@ -353,13 +359,17 @@ int obc_decode_step(const void *q, void *k, void *v, float *scores, int32_t *evi
     rc = fill_lens(seq_lens_host, B, N, (int)protect + 1, &ragged, &lens);
     if (rc != OBC_OK) return rc;
     if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need) return OBC_EWORKSPACE;
-    const size_t score_bytes = need - align_up((size_t)B * Hkv * sizeof(int32_t), 256);
-    rc = score_impl(q, k, v, N, 1, Hq, Hkv, d, variant, scores, B, dtype, seq_lens_host, workspace, score_bytes, hip_stream,
-                    OBC_STAGE_ALL, 1);
+    const size_t score_bytes = need - align_up((size_t)B * Hkv * sizeof(unsigned long long), 256);
+    ScoreWorkspace ws;
+    rc = plan_score_workspace(B, N, 1, Hq, Hkv, d, dtype, variant, &ws);
     if (rc != OBC_OK) return rc;
-    int32_t *pick = evicted ? evicted : (int32_t *)((char *)workspace + score_bytes);
+    rc = score_impl(q, k, v, N, 1, Hq, Hkv, d, variant, scores, B, dtype, seq_lens_host, workspace, score_bytes, hip_stream,
+                    OBC_STAGE_ALL, 1, num_sinks, num_recent);
+    if (rc != OBC_OK) return rc;
+    // The decode kernels have left every range's candidate; after the other paths one pass over the scores finds them.
+    unsigned long long *lowest = (unsigned long long *)((char *)workspace + (ws.use_decode ? ws.dec_lowest : score_bytes));
     const long long row_bytes = (long long)d * (dtype == OBC_F32 ? 4 : 2);
-    const hipError_t e = launch_evict_one(k, v, scores, pick, B, Hkv, N, ragged, lens, num_sinks, num_recent, (int)row_bytes,
+    const hipError_t e = launch_evict_one(k, v, scores, evicted, lowest, ws.use_decode ? ws.dec_splits : 0, B, Hkv, N, ragged, lens, num_sinks, num_recent, (int)row_bytes,
                                           (hipStream_t)hip_stream);
     return e == hipSuccess ? OBC_OK : OBC_ELAUNCH;
 }

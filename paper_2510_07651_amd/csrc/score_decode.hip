@@ -3,9 +3,9 @@
 //
 // With one row per query head a KV head sees only G = Hq/Hkv rows, far too few to fill a
 // matrix-core tile, and at the cache sizes of decoding the call is bound by memory round
-// trips, not by bandwidth.  The path is vector-ALU kernels with 128-bit coalesced loads (one
-// token row spread over d/8 lanes) in which a workgroup owns a short range of tokens and every
-// lane issues ALL its loads of the range before it computes:
+// trips and dependent instructions, not by bandwidth.  The path is vector-ALU kernels with 128-bit
+// coalesced loads (one token row spread over d/8 lanes) in which a workgroup owns a short range of
+// tokens and every lane issues ALL its loads of the range before it computes:
 //   decode_partial   per range: scaled logits Z = q.k/sqrt(d) (Section 3), kept in the
 //                    workspace so K is read once; range max, sum and unnormalised output
 //                    (the range's top-logit token is held out of both sums, see below)
@@ -14,12 +14,17 @@
 //   decode_score     Eq. 4-6 in their direct forms ||v_p||^2, ||v_p - o_i||^2 and
 //                    ||v_p + Z (v_p - o_i)||^2 (the completed square of Eq. 6), Eq. 8 and
 //                    the l1-weighted variant of Appendix C, summed over the query heads of
-//                    the KV head (Appendix A.5), written or added to the running scores.
+//                    the KV head (Appendix A.5), written or added to the running scores; for an
+//                    eviction step also the range's lowest-scored token.
+// Ranges are as short as keeps the inline merge possible while the chip has workgroups to spare
+// (2, 4 or 8 tokens per lane): a wave is alone on its SIMD here, so its instruction count is its
+// time.  8 KV heads x 1025 tokens, G = 4, d = 128, joint, per layer: 72 workgroups of 8 tokens per
+// lane 26 us for the two kernels, 264 workgroups of 2 tokens PARTIAL_SCORE_US.
 //
 // Cancellation guard.  When one key takes almost all of a row's attention, o_i is almost
 // v_p* and fp32 cannot hold their difference.  Every range keeps its top-logit token out of
-// its sums; the merge adds the held-out tokens of all ranges but the winning one back, so
-// with l' and o' the sum and the mean over every key but p*,
+// its sums and reports the output with and without it; the merge takes the sums with it from all
+// ranges but the winning one, so with l' and o' the sum and the mean over every key but p*,
 //     v_p* - o_i = (l' / (1 + l')) (v_p* - o')        (no cancellation)
 //     o_i        = v_p* - (v_p* - o_i)
 // and the (row, p*) pair is scored from the first identity.
@@ -31,18 +36,17 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kSteps = 8;            // token rows per lane: a range is kSteps workgroup-wide steps
-constexpr int kRecHead = 4;          // floats ahead of the vectors in a partial or final record
-constexpr int kInlineSplits = 16;    // most ranges per head the scoring kernel merges itself
+constexpr int kMaxSteps = 8;         // most token rows per lane: a range is 2, 4 or 8 workgroup-wide steps
+constexpr int kInlineSplits = 48;    // most ranges per head the scoring kernel merges itself
 constexpr int kMergeThreads = 1024;
 constexpr int kMergeOwn = 4;         // ranges per merging thread
 constexpr int kMaxSplits = kMergeThreads * kMergeOwn;
+constexpr int kRecHead = 4;          // floats ahead of the vectors in a final record
 
 __host__ __device__ constexpr int tokens_per_step(int d) { return kWaves * (64 / (d / 8)); }
-__host__ __device__ constexpr int range_tokens(int d) { return kSteps * tokens_per_step(d); }
-// Partial record of (KV head, range, row): {range max, sum without the top token, top token
-// (int bits, -1 for an empty range), spare, unnormalised output without the top token [d]}.
-__host__ __device__ constexpr int part_stride(int d) { return d + kRecHead; }
+// Partial record of (KV head, range, row): head {range max, sum without the top token, top token
+// (int bits, -1 for an empty range), spare}; vectors {unnormalised output without the top token [d],
+// the same with it [d]}, valid unless the range is empty.
 // Final record of (KV head, row): {row max, 1/sum, top token (int bits), spare, o_i [d],
 // v_p* - o_i [d]}.
 __host__ __device__ constexpr int final_stride(int d) { return 2 * d + kRecHead; }
@@ -72,12 +76,45 @@ __device__ __forceinline__ float group_sum(float x) {
     if (kLanes == 16) x = dpp_pair_sum<0x140>(x);
     return x;
 }
-// Butterfly sum over the token slots of a wave (lanes with equal position inside their group).
-template <int kLanes>
-__device__ __forceinline__ float slot_sum(float x) {
+// The values of the two lanes that differ in bit 4 (16) or 5 (32) of their index, lower one first.
+template <int kBit>
+__device__ __forceinline__ void both_of_pair(uint32_t x, uint32_t &lower, uint32_t &upper) {
+    const auto r = kBit == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false) : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    lower = r[0];
+    upper = r[1];
+}
+// Sums over the token slots of a wave (the lanes of equal position in their group), for kN values at once: each level
+// adds two values across lane pairs with one register exchange and leaves half of the values in each half of the pair.
+// Lane l then holds the sums of values i * (64 / kLanes) + (l / kLanes, its two or three bits taken highest first) in x[i].
+template <int kLanes, int kN>
+__device__ __forceinline__ void slot_sums(float (&x)[kN]) {
+    constexpr int kSlots = 64 / kLanes;
+    static_assert(kSlots == 4 || kSlots == 8, "head_dim 128 or 64");
 #pragma unroll
-    for (int off = kLanes; off < 64; off <<= 1) x += __shfl_xor(x, off);
-    return x;
+    for (int i = 0; i < kN / 2; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[2 * i]), __float_as_uint(x[2 * i + 1]), false, false);
+        x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < kN / 4; ++i) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[2 * i]), __float_as_uint(x[2 * i + 1]), false, false);
+        x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    if (kSlots == 8) {
+        // the two groups of 8 inside a row of 16: each keeps one of two values and gives the other away
+        const bool high = (threadIdx.x & 8) != 0;
+#pragma unroll
+        for (int i = 0; i < kN / 8; ++i) {
+            const float give = high ? x[2 * i] : x[2 * i + 1], keep = high ? x[2 * i + 1] : x[2 * i];
+            // row_ror:8 brings the value of lane l ^ 8
+            x[i] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), 0x128, 0xf, 0xf, false));
+        }
+    }
+}
+// Which of the kSlots values of a batch a lane ends up with in slot_sums.
+template <int kLanes>
+__device__ __forceinline__ int slot_sums_index(int lane) {
+    return kLanes == 16 ? 2 * ((lane >> 4) & 1) + (lane >> 5) : 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + (lane >> 5);
 }
 // (larger value, lower index on ties) of two candidates.
 __device__ __forceinline__ void take_better(float &bm, int &ba, float om, int oa) {
@@ -92,26 +129,26 @@ __device__ __forceinline__ int token_of(int t0, int u, int wave, int slot) {
 }
 
 // The scaled logits of the range, its row maxima and the unnormalised sums around them.
-template <int kG, int kD, bool kNeedO>
+template <int kG, int kD, int kSteps, bool kNeedO>
 __global__ __launch_bounds__(kThreads) void decode_partial(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, int N, int G,
-    int Hkv, int ragged, SeqLens lens, int splits, float *__restrict__ z_buf, float *__restrict__ part) {
+    int Hkv, int ragged, SeqLens lens, int splits, float *__restrict__ z_buf, float4 *__restrict__ part_head,
+    float *__restrict__ part_vec) {
     constexpr int kLpt = kD / 8;        // lanes per token row
+    constexpr int kSlots = 64 / kLpt;   // token rows per wave and step
     __shared__ float red_m[kWaves * kG];
     __shared__ int red_a[kWaves * kG];
     __shared__ float red_l[kWaves * kG];
-    __shared__ float red_o[kWaves * kG * kD];
+    __shared__ float red_o[kNeedO ? kWaves * kG * kD : 1];
+    __shared__ float top_v[kNeedO ? kG * kD : 1];   // V rows of the top tokens
 
     const int bh = blockIdx.y, b = bh / Hkv, split = blockIdx.x;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int t0 = split * range_tokens(kD);
-    const int t1 = min(t0 + range_tokens(kD), len);
-    float *rec = part + ((size_t)bh * splits + split) * kG * part_stride(kD);
+    const int t0 = split * kSteps * tokens_per_step(kD);
+    const int t1 = min(t0 + kSteps * tokens_per_step(kD), len);
+    float4 *head = part_head + ((size_t)bh * splits + split) * kG;
     if (t0 >= len) {                                // nothing of this sequence falls in the range
-        for (int e = threadIdx.x; e < kG * part_stride(kD); e += kThreads) {
-            const int c = e % part_stride(kD);
-            rec[e] = c == 0 ? -INFINITY : (c == 2 ? __int_as_float(-1) : 0.f);
-        }
+        if (threadIdx.x < kG) head[threadIdx.x] = make_float4(-INFINITY, 0.f, __int_as_float(-1), 0.f);
         return;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -173,8 +210,19 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
             const int p = token_of<kD>(t0, u, wave, slot);
             if (p < t1 && z[u][r] > bm) { bm = z[u][r]; ba = p; }
         }
-#pragma unroll
-        for (int off = kLpt; off < 64; off <<= 1) take_better(bm, ba, __shfl_xor(bm, off), __shfl_xor(ba, off));
+        if (kLpt == 8) take_better(bm, ba, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(bm), 0x128, 0xf, 0xf, false)),
+                                   __builtin_amdgcn_update_dpp(0, ba, 0x128, 0xf, 0xf, false));
+        uint32_t m0, m1, a0, a1;
+        both_of_pair<16>(__float_as_uint(bm), m0, m1);
+        both_of_pair<16>((uint32_t)ba, a0, a1);
+        bm = __uint_as_float(m0);
+        ba = (int)a0;
+        take_better(bm, ba, __uint_as_float(m1), (int)a1);
+        both_of_pair<32>(__float_as_uint(bm), m0, m1);
+        both_of_pair<32>((uint32_t)ba, a0, a1);
+        bm = __uint_as_float(m0);
+        ba = (int)a0;
+        take_better(bm, ba, __uint_as_float(m1), (int)a1);
         if (lane == 0) { red_m[wave * kG + r] = bm; red_a[wave * kG + r] = ba; }
     }
     __syncthreads();
@@ -189,12 +237,12 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
     }
 
     // Sums of exp(z - m) and of exp(z - m) v over the range without the top token.
-    float lsum[kG], acc[kG][8];
+    float lsum[kG], acc[kG * 8];
 #pragma unroll
     for (int r = 0; r < kG; ++r) {
         lsum[r] = 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[r][j] = 0.f;
+        for (int j = 0; j < 8; ++j) acc[r * 8 + j] = 0.f;
     }
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
@@ -204,135 +252,192 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
             if (kNeedO) unpack8(vw[u], vv);
 #pragma unroll
             for (int r = 0; r < kG; ++r) {
-                const float w = p == top[r] ? 0.f : __expf(z[u][r] - m[r]);
+                const bool is_top = p == top[r];
+                const float w = is_top ? 0.f : __expf(z[u][r] - m[r]);
                 lsum[r] += w;
                 if (kNeedO) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[r][j] = fmaf(w, vv[j], acc[r][j]);
+                    for (int j = 0; j < 8; ++j) acc[r * 8 + j] = fmaf(w, vv[j], acc[r * 8 + j]);
+                    if (is_top) {
+                        *(float4 *)(top_v + r * kD + sub * 8) = make_float4(vv[0], vv[1], vv[2], vv[3]);
+                        *(float4 *)(top_v + r * kD + sub * 8 + 4) = make_float4(vv[4], vv[5], vv[6], vv[7]);
+                    }
                 }
             }
         }
     }
 #pragma unroll
     for (int r = 0; r < kG; ++r) {
-        const float l = slot_sum<kLpt>(lsum[r]);
+        // the kLpt lanes of a slot hold the same sum
+        float l = lsum[r];
+        uint32_t x0, x1;
+        if (kLpt == 8) l += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(l), 0x128, 0xf, 0xf, false));
+        both_of_pair<16>(__float_as_uint(l), x0, x1);
+        l = __uint_as_float(x0) + __uint_as_float(x1);
+        both_of_pair<32>(__float_as_uint(l), x0, x1);
+        l = __uint_as_float(x0) + __uint_as_float(x1);
         if (lane == 0) red_l[wave * kG + r] = l;
-        if (kNeedO) {
+    }
+    if (kNeedO) {
+        slot_sums<kLpt>(acc);
+        const int c0 = slot_sums_index<kLpt>(lane);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float o = slot_sum<kLpt>(acc[r][j]);
-                if (slot == 0) red_o[(wave * kG + r) * kD + sub * 8 + j] = o;
-            }
+        for (int i = 0; i < kG * 8 / kSlots; ++i) {
+            const int e = i * kSlots + c0, r = e / 8, j = e % 8;
+            red_o[(wave * kG + r) * kD + j * kLpt + sub] = acc[i];      // (column-of-eight major: no bank conflicts)
         }
     }
     __syncthreads();
+    if (threadIdx.x < kG) {
+        const int r = threadIdx.x;
+        float l = red_l[r];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) l += red_l[w * kG + r];
+        float bm = red_m[r];
+        int ba = red_a[r];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) take_better(bm, ba, red_m[w * kG + r], red_a[w * kG + r]);
+        head[r] = make_float4(bm, l, __int_as_float(ba), 0.f);
+    }
+    if (!kNeedO) return;
+    float *vec = part_vec + ((size_t)bh * splits + split) * kG * 2 * kD;
     for (int e = threadIdx.x; e < kG * kD; e += kThreads) {
-        const int r = e / kD, c = e % kD;
-        float o = 0.f;
-        if (kNeedO) {
-            o = red_o[r * kD + c];
+        const int r = e / kD, c = e % kD, at = (c % 8) * kLpt + c / 8;
+        float o = red_o[r * kD + at];
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) o += red_o[(w * kG + r) * kD + c];
-        }
-        rec[r * part_stride(kD) + kRecHead + c] = o;
-        if (c == 0) {
-            float l = red_l[r];
-#pragma unroll
-            for (int w = 1; w < kWaves; ++w) l += red_l[w * kG + r];
-            rec[r * part_stride(kD) + 0] = m[r];
-            rec[r * part_stride(kD) + 1] = l;
-            rec[r * part_stride(kD) + 2] = __int_as_float(top[r]);
-            rec[r * part_stride(kD) + 3] = 0.f;
-        }
+        for (int w = 1; w < kWaves; ++w) o += red_o[(w * kG + r) * kD + at];
+        vec[r * 2 * kD + c] = o;
+        vec[r * 2 * kD + kD + c] = o + top_v[r * kD + c];
     }
 }
 
-// Closing step of a merge for column c of row r: from the sum l_rest and the weighted vector
-// sum o_rest over every key but the top one, the final record's entries of that column (and the
-// record's head when c == 0).
-template <int kD, bool kNeedO>
-__device__ __forceinline__ void merge_finish(float m, int top, float l_rest, float o_rest, float v_top, int r, int c,
-                                             float *fin) {
+// Closing step of a merge for column c of a row: from the sum l_rest and the weighted vector
+// sum o_rest over every key but the top one, the final record's entries of that column.
+template <int kD>
+__device__ __forceinline__ void merge_finish(float l_rest, float o_rest, float v_top, int c, float *rec) {
     const float inv_l = 1.f / (1.f + l_rest);
-    float *out = fin + (size_t)r * final_stride(kD);
-    if (kNeedO) {
-        const float d_top = l_rest > 0.f ? (l_rest * inv_l) * (v_top - o_rest / l_rest) : 0.f;
-        out[kRecHead + c] = v_top - d_top;
-        out[kRecHead + kD + c] = d_top;
-    }
-    if (c == 0) {
-        out[0] = m;
-        out[1] = inv_l;
-        out[2] = __int_as_float(top);
-        out[3] = 0.f;
-    }
+    const float d_top = l_rest > 0.f ? (l_rest * inv_l) * (v_top - o_rest / l_rest) : 0.f;
+    rec[kRecHead + c] = v_top - d_top;
+    rec[kRecHead + kD + c] = d_top;
 }
 
-// Merge of at most kInlineSplits ranges of one KV head for column c of row r, by one thread.
-// The loads come in two batches (the records; then the rows of the held-out tokens, whose
-// addresses the records give), so the merge costs two memory round trips.
-template <int kD, bool kNeedO>
-__device__ __forceinline__ void merge_few(const float *__restrict__ part_head, int splits, int kG, int r, int c,
-                                          const uint16_t *__restrict__ vg, float *fin) {
-    constexpr int ps = part_stride(kD);
-    float hm[kInlineSplits], hl[kInlineSplits], o_s[kInlineSplits], v_s[kInlineSplits];
-    int ht[kInlineSplits];
+// Merge of at most kInlineSplits ranges of one KV head by one workgroup, into final records in LDS.  The vectors of all
+// ranges are fetched while the heads are still on their way; only the winning range's two rows wait for them.
+template <int kG, int kD, bool kNeedO>
+__device__ __forceinline__ void merge_few(const float4 *__restrict__ part_head, const float *__restrict__ part_vec,
+                                          int splits, int G, const uint16_t *__restrict__ vg, float *fin) {
+    constexpr int kFs = final_stride(kD);
+    constexpr int kQuads = kG * kD / 4;                       // float4 columns of all rows
+    constexpr int kParts = kQuads >= kThreads ? 1 : kThreads / kQuads;      // threads that share one
+    constexpr int kOwn = (kInlineSplits + kParts - 1) / kParts, kHold = kOwn < 24 ? kOwn : 24;     // ranges a thread adds up, holds at once
+    __shared__ float w_s[kG * kInlineSplits];
+    __shared__ int best_s[kG];
+    __shared__ __attribute__((aligned(16))) float sum_s[kNeedO ? kParts * kG * kD : 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int quad = threadIdx.x % kQuads, part = threadIdx.x / kQuads, row = quad * 4 / kD, col = quad * 4 % kD;
+    const float *mine = part_vec + (size_t)row * 2 * kD + kD + col;         // sums that include the range's top token
+    float4 x[kHold];
+    if (kNeedO && part < kParts) {
 #pragma unroll
-    for (int s = 0; s < kInlineSplits; ++s) {
-        hm[s] = -INFINITY; hl[s] = 0.f; ht[s] = -1; o_s[s] = 0.f;
-        if (s < splits) {
-            const float *rec = part_head + ((size_t)s * kG + r) * ps;
-            hm[s] = rec[0];
-            hl[s] = rec[1];
-            ht[s] = __float_as_int(rec[2]);
-            if (kNeedO) o_s[s] = rec[kRecHead + c];
+        for (int i = 0; i < kHold; ++i) {
+            const int s = part + i * kParts;
+            x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (s < splits) x[i] = *(const float4 *)(mine + (size_t)s * kG * 2 * kD);
         }
     }
-    float m = -INFINITY;
-    int s_top = 0;
 #pragma unroll
-    for (int s = 0; s < kInlineSplits; ++s)
-        if (hm[s] > m) { m = hm[s]; s_top = s; }    // first range attaining the max: lowest token index
+    for (int r0 = 0; r0 < kG; r0 += kWaves) {                 // one wave per row, one lane per range
+        const int r = r0 + wave;
+        if (r >= kG || r >= G) continue;
+        float4 h = make_float4(-INFINITY, 0.f, __int_as_float(-1), 0.f);
+        if (lane < splits) h = part_head[(size_t)lane * kG + r];
+        float bm = h.x;
+        int bs = lane;
 #pragma unroll
-    for (int s = 0; s < kInlineSplits; ++s) {
-        v_s[s] = 0.f;
-        if (kNeedO && ht[s] >= 0) v_s[s] = bf16_bits_to_float(vg[(size_t)ht[s] * kD + c]);
-    }
-    int top = -1;
-    float v_top = 0.f, l_rest = 0.f, o_rest = 0.f;
+        for (int off = 32; off > 0; off >>= 1) take_better(bm, bs, __shfl_xor(bm, off), __shfl_xor(bs, off));
+        // (the first range attaining the max holds the lowest token that does)
+        const float w = h.x == -INFINITY ? 0.f : __expf(h.x - bm);
+        float l = fmaf(w, h.y, lane != bs ? w : 0.f);         // ranges other than the winning one count their top token
 #pragma unroll
-    for (int s = 0; s < kInlineSplits; ++s) {
-        if (s == s_top) { top = ht[s]; v_top = v_s[s]; }
-        if (hm[s] == -INFINITY) continue;
-        const float w = __expf(hm[s] - m);
-        l_rest = fmaf(w, hl[s], l_rest);
-        if (kNeedO) o_rest = fmaf(w, o_s[s], o_rest);
-        if (s != s_top) {                           // this range's held-out token is an ordinary one after all
-            l_rest += w;
-            if (kNeedO) o_rest = fmaf(w, v_s[s], o_rest);
+        for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+        if (lane < splits) w_s[r * kInlineSplits + lane] = lane == bs ? 0.f : w;
+        if (lane == bs) {
+            best_s[r] = bs;
+            float *rec = fin + r * kFs;
+            rec[0] = bm;
+            rec[1] = 1.f / (1.f + l);
+            rec[2] = h.z;
+            rec[3] = l;
         }
     }
-    merge_finish<kD, kNeedO>(m, top, l_rest, o_rest, v_top, r, c, fin);
+    if (!kNeedO) return;                                      // (the caller meets at a barrier)
+    __syncthreads();
+    // the winning range's rows: its sums without its top token (weight 1), and that token's own row
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint2 vt = make_uint2(0u, 0u);
+    const bool live = part < kParts && row < G;
+    if (live && part == 0) {
+        o = *(const float4 *)(mine - kD + (size_t)best_s[row] * kG * 2 * kD);
+        vt = *(const uint2 *)(vg + (size_t)__float_as_int(fin[row * kFs + 2]) * kD + col);
+    }
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (live) {
+        for (int i0 = 0; i0 < kOwn; i0 += kHold) {
+            if (i0 > 0) {
+#pragma unroll
+                for (int i = 0; i < kHold; ++i) {
+                    const int s = part + (i0 + i) * kParts;
+                    if (s < splits) x[i] = *(const float4 *)(mine + (size_t)s * kG * 2 * kD);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kHold; ++i) {
+                const int s = part + (i0 + i) * kParts;
+                const float w = s < splits ? w_s[row * kInlineSplits + s] : 0.f;
+                if (w != 0.f) {                               // (an empty range has no vectors)
+                    t.x = fmaf(w, x[i].x, t.x);
+                    t.y = fmaf(w, x[i].y, t.y);
+                    t.z = fmaf(w, x[i].z, t.z);
+                    t.w = fmaf(w, x[i].w, t.w);
+                }
+            }
+        }
+        if (kParts > 1) *(float4 *)(sum_s + part * kG * kD + quad * 4) = t;
+    }
+    if (kParts > 1) __syncthreads();
+    if (live && part == 0) {
+#pragma unroll
+        for (int i = 1; i < kParts; ++i) {
+            const float4 y = *(const float4 *)(sum_s + i * kG * kD + quad * 4);
+            t.x += y.x; t.y += y.y; t.z += y.z; t.w += y.w;
+        }
+        float *rec = fin + row * kFs;
+        const float l = rec[3];
+        merge_finish<kD>(l, t.x + o.x, __uint_as_float(vt.x << 16), col, rec);
+        merge_finish<kD>(l, t.y + o.y, __uint_as_float(vt.x & 0xffff0000u), col + 1, rec);
+        merge_finish<kD>(l, t.z + o.z, __uint_as_float(vt.y << 16), col + 2, rec);
+        merge_finish<kD>(l, t.w + o.w, __uint_as_float(vt.y & 0xffff0000u), col + 3, rec);
+    }
 }
 
 // Merge of many ranges: one workgroup per (row, KV head); up to kMergeOwn ranges per thread for
 // the scalar part, then columns x segments of ranges for the vector part; fixed summation order.
 template <int kG, int kD, bool kNeedO>
 __global__ __launch_bounds__(kMergeThreads) void decode_merge(const uint16_t *__restrict__ v, int N, int splits,
-                                                              const float *__restrict__ part,
-                                                              float *__restrict__ fin) {
-    constexpr int ps = part_stride(kD);
+                                                              const float4 *__restrict__ part_head_all,
+                                                              const float *__restrict__ part_vec, float *__restrict__ fin) {
     constexpr int kSeg = kMergeThreads / kD;
     constexpr int kMergeWaves = kMergeThreads / 64;
     constexpr int kBatch = 8;
     __shared__ float w_s[kMaxSplits];
-    __shared__ int tok_s[kMaxSplits];
+    __shared__ int top_s;
     __shared__ float red_m[kMergeWaves];
     __shared__ int red_a[kMergeWaves];
     __shared__ float red_l[kMergeWaves];
     __shared__ float red_o[kSeg * kD];
     const int r = blockIdx.x, bh = blockIdx.y;
-    const float *part_head = part + (size_t)bh * splits * kG * ps;
+    const float4 *part_head = part_head_all + (size_t)bh * splits * kG;
+    const float *vec = part_vec + ((size_t)bh * splits * kG + r) * 2 * kD;
     const uint16_t *vg = v + (size_t)bh * N * kD;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
@@ -343,10 +448,10 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge(const uint16_t *__
         const int s = i * kMergeThreads + threadIdx.x;
         hm[i] = -INFINITY; hl[i] = 0.f; ht[i] = -1;
         if (s < splits) {
-            const float *rec = part_head + ((size_t)s * kG + r) * ps;
-            hm[i] = rec[0];
-            hl[i] = rec[1];
-            ht[i] = __float_as_int(rec[2]);
+            const float4 h = part_head[(size_t)s * kG + r];
+            hm[i] = h.x;
+            hl[i] = h.y;
+            ht[i] = __float_as_int(h.z);
         }
     }
     float bm = -INFINITY;
@@ -369,8 +474,9 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge(const uint16_t *__
     for (int i = 0; i < kMergeOwn; ++i) {
         const int s = i * kMergeThreads + threadIdx.x;
         const float w = hm[i] == -INFINITY ? 0.f : __expf(hm[i] - m);
-        if (s < splits) { w_s[s] = w; tok_s[s] = ht[i]; }
-        // ranges other than the winning one give their held-out token back
+        if (s < splits) w_s[s] = w;
+        if (s == s_top) top_s = ht[i];
+        // ranges other than the winning one count their top token
         l += fmaf(w, hl[i], s != s_top ? w : 0.f);
     }
 #pragma unroll
@@ -380,7 +486,7 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge(const uint16_t *__
     float l_rest = red_l[0];
 #pragma unroll
     for (int x = 1; x < kMergeWaves; ++x) l_rest += red_l[x];
-    const int top = tok_s[s_top];
+    const int top = top_s;
 
     const int c = threadIdx.x % kD, seg = threadIdx.x / kD;
     float v_top = 0.f;
@@ -388,31 +494,36 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge(const uint16_t *__
         if (seg == 0) v_top = bf16_bits_to_float(vg[(size_t)top * kD + c]);
         float o = 0.f;
         for (int s0 = seg; s0 < splits; s0 += kBatch * kSeg) {
-            float po[kBatch], pv[kBatch], pw[kBatch];
+            float po[kBatch], pw[kBatch];
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
                 const int si = s0 + u * kSeg;
-                po[u] = 0.f; pv[u] = 0.f; pw[u] = 0.f;
-                if (si < splits && tok_s[si] >= 0) {
+                po[u] = 0.f; pw[u] = 0.f;
+                if (si < splits && w_s[si] != 0.f) {
                     pw[u] = w_s[si];
-                    po[u] = part_head[((size_t)si * kG + r) * ps + kRecHead + c];
-                    if (si != s_top) pv[u] = bf16_bits_to_float(vg[(size_t)tok_s[si] * kD + c]);
+                    po[u] = vec[(size_t)si * kG * 2 * kD + (si != s_top ? kD : 0) + c];
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) o = fmaf(pw[u], po[u] + pv[u], o);
+            for (int u = 0; u < kBatch; ++u) o = fmaf(pw[u], po[u], o);
         }
         red_o[seg * kD + c] = o;
     }
     __syncthreads();
     if (seg == 0) {
-        float o_rest = 0.f;
+        float *rec = fin + ((size_t)bh * kG + r) * final_stride(kD);
         if (kNeedO) {
-            o_rest = red_o[c];
+            float o_rest = red_o[c];
 #pragma unroll
             for (int x = 1; x < kSeg; ++x) o_rest += red_o[x * kD + c];
+            merge_finish<kD>(l_rest, o_rest, v_top, c, rec);
         }
-        merge_finish<kD, kNeedO>(m, top, l_rest, o_rest, v_top, r, c, fin + (size_t)bh * kG * final_stride(kD));
+        if (c == 0) {
+            rec[0] = m;
+            rec[1] = 1.f / (1.f + l_rest);
+            rec[2] = __int_as_float(top);
+            rec[3] = l_rest;
+        }
     }
 }
 
@@ -422,12 +533,14 @@ struct DecodeNeeds {
     static constexpr bool v = kVariant != OBC_ATTN;
 };
 
-// Scores of the range's tokens from the stored logits, the merged row statistics and V.
-template <int kG, int kD, int kVariant>
+// Scores of the range's tokens from the stored logits, the merged row statistics and V.  With `lowest`, also the
+// lowest (score, highest index) among the range's tokens first <= p < len - tail, as an evict_candidate.
+template <int kG, int kD, int kSteps, int kVariant>
 __global__ __launch_bounds__(kThreads) void decode_score(
     const uint16_t *__restrict__ v, int N, int G, int Hkv, int ragged, SeqLens lens, int splits,
-    const float *__restrict__ z_buf, const float *__restrict__ part, const float *__restrict__ fin_global,
-    int merge_here, float *__restrict__ scores, size_t plane_stride, int accumulate) {
+    const float *__restrict__ z_buf, const float4 *__restrict__ part_head, const float *__restrict__ part_vec,
+    const float *__restrict__ fin_global, int merge_here, float *__restrict__ scores, size_t plane_stride, int accumulate,
+    unsigned long long *__restrict__ lowest, int first, int tail) {
     constexpr int kLpt = kD / 8;
     constexpr bool kNeedO = DecodeNeeds<kVariant>::o;
     constexpr bool kNeedV = DecodeNeeds<kVariant>::v;
@@ -436,18 +549,20 @@ __global__ __launch_bounds__(kThreads) void decode_score(
     constexpr bool kDoJ = kVariant == OBC_JOINT || kVariant == OBC_ALL;
     constexpr int kPlanes = kVariant == OBC_ALL ? 3 : 1;
     constexpr int kFs = final_stride(kD);
-    __shared__ float fin[kG * kFs];
+    __shared__ __attribute__((aligned(16))) float fin[kG * kFs];
+    __shared__ unsigned long long lowest_s[kWaves];
 
     const int bh = blockIdx.y, b = bh / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int t0 = blockIdx.x * range_tokens(kD);
-    const int t1 = min(t0 + range_tokens(kD), N);
+    const int t0 = blockIdx.x * kSteps * tokens_per_step(kD);
+    const int t1 = min(t0 + kSteps * tokens_per_step(kD), N);
     const uint16_t *vg = v + (size_t)bh * N * kD;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int sub = lane % kLpt, slot = lane / kLpt;
     float *out = scores + (size_t)bh * N;
 
     if (t0 >= len) {                                // only padding here
+        if (lowest && threadIdx.x == 0) lowest[(size_t)bh * splits + blockIdx.x] = ~0ull;
         if (!accumulate) {
             for (int p = t0 + threadIdx.x; p < t1; p += kThreads) {
 #pragma unroll
@@ -481,12 +596,7 @@ __global__ __launch_bounds__(kThreads) void decode_score(
     }
 
     if (merge_here) {
-        const float *part_head = part + (size_t)bh * splits * kG * part_stride(kD);
-#pragma unroll
-        for (int e0 = 0; e0 < kG * kD; e0 += kThreads) {       // unrolled: the loads of all passes go out together
-            const int e = e0 + threadIdx.x;
-            if (e < G * kD) merge_few<kD, kNeedO>(part_head, splits, kG, e / kD, e % kD, vg, fin);
-        }
+        merge_few<kG, kD, kNeedO>(part_head + (size_t)bh * splits * kG, part_vec + (size_t)bh * splits * kG * 2 * kD, splits, G, vg, fin);
     } else {
         const float *src = fin_global + (size_t)bh * kG * kFs;
         for (int e = threadIdx.x; e < G * kFs; e += kThreads) fin[e] = src[e];
@@ -510,6 +620,7 @@ __global__ __launch_bounds__(kThreads) void decode_score(
         }
     }
 
+    unsigned long long low = ~0ull;
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
         const int p = token_of<kD>(t0, u, wave, slot);
@@ -576,41 +687,67 @@ __global__ __launch_bounds__(kThreads) void decode_score(
             } else {
                 const float sc = kVariant == OBC_VALUE ? s_v : kVariant == OBC_KEY ? s_k
                                : kVariant == OBC_JOINT ? s_j : s_a;
-                out[p] = old[u][0] + sc;
+                const float now = old[u][0] + sc;
+                out[p] = now;
+                if (p >= first && p < len - tail) {
+                    const unsigned long long cand = evict_candidate(now, p);
+                    low = cand < low ? cand : low;
+                }
             }
+        }
+    }
+    if (lowest) {                                               // uniform
+        low = wave_min(low);
+        if (lane == 0) lowest_s[wave] = low;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) low = lowest_s[w] < low ? lowest_s[w] : low;
+            lowest[(size_t)bh * splits + blockIdx.x] = low;
         }
     }
 }
 
-template <int kG, int kD, int kVariant>
-hipError_t launch_decode_variant(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+template <int kG, int kD, int kSteps, int kVariant>
+hipError_t launch_decode_steps(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
     constexpr bool kNeedO = DecodeNeeds<kVariant>::o;
     const int BH = a.B * a.Hkv;
     float *z_buf = (float *)(base + ws.dec_z);
-    float *part = (float *)(base + ws.dec_part);
+    float4 *part_head = (float4 *)(base + ws.dec_head);
+    float *part_vec = (float *)(base + ws.dec_vec);
     float *fin = (float *)(base + ws.dec_final);
     const dim3 grid(ws.dec_splits, BH);
-    if (ws.dec_splits > kMaxSplits || (long long)ws.dec_splits * range_tokens(kD) < a.N) return hipErrorInvalidValue;
+    if (ws.dec_splits > kMaxSplits || (long long)ws.dec_splits * kSteps * tokens_per_step(kD) < a.N) return hipErrorInvalidValue;
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
-        decode_partial<kG, kD, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
+        decode_partial<kG, kD, kSteps, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
             (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, a.lens,
-            ws.dec_splits, z_buf, part);
+            ws.dec_splits, z_buf, part_head, part_vec);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if ((a.stage_mask & OBC_STAGE_COMBINE) && !ws.dec_merge_inline) {
-        decode_merge<kG, kD, kNeedO><<<dim3(a.G, BH), dim3(kMergeThreads), 0, stream>>>((const uint16_t *)a.v, a.N,
-                                                                                        ws.dec_splits, part, fin);
+        decode_merge<kG, kD, kNeedO><<<dim3(a.G, BH), dim3(kMergeThreads), 0, stream>>>((const uint16_t *)a.v, a.N, ws.dec_splits,
+                                                                                        part_head, part_vec, fin);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (a.stage_mask & OBC_STAGE_SWEEP2) {
-        decode_score<kG, kD, kVariant><<<grid, dim3(kThreads), 0, stream>>>(
-            (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, a.lens, ws.dec_splits, z_buf, part, fin,
-            ws.dec_merge_inline, a.scores, (size_t)a.B * a.Hkv * a.N, a.accumulate);
+        decode_score<kG, kD, kSteps, kVariant><<<grid, dim3(kThreads), 0, stream>>>(
+            (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, a.lens, ws.dec_splits, z_buf, part_head, part_vec, fin,
+            ws.dec_merge_inline, a.scores, (size_t)a.B * a.Hkv * a.N, a.accumulate,
+            a.find_lowest ? (unsigned long long *)(base + ws.dec_lowest) : nullptr, a.evict_first, a.evict_tail);
         return hipGetLastError();
     }
     return hipSuccess;
+}
+
+template <int kG, int kD, int kVariant>
+hipError_t launch_decode_variant(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+    switch (ws.dec_range / tokens_per_step(kD)) {
+        case 2: return launch_decode_steps<kG, kD, 2, kVariant>(a, ws, base, stream);
+        case 4: return launch_decode_steps<kG, kD, 4, kVariant>(a, ws, base, stream);
+        default: return launch_decode_steps<kG, kD, 8, kVariant>(a, ws, base, stream);
+    }
 }
 
 template <int kG, int kD>
@@ -637,13 +774,13 @@ hipError_t launch_decode_dim(const ScoreArgs &a, const ScoreWorkspace &ws, char 
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-int splits_for(int N, int d) { return (N + range_tokens(d) - 1) / range_tokens(d); }
+int splits_for(int N, int d, int steps) { return (N + steps * tokens_per_step(d) - 1) / (steps * tokens_per_step(d)); }
 
 }  // namespace
 
 bool decode_path_covers(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, bool any_size) {
     if (dtype != OBC_BF16 || W != 1 || Hq / Hkv > kDecodeMaxGroup || (d != 64 && d != 128)) return false;
-    if (splits_for(N, d) > kMaxSplits) return false;            // what one merging workgroup takes
+    if (splits_for(N, d, kMaxSteps) > kMaxSplits) return false;            // what one merging workgroup takes
     // These kernels win while the call is bound by round trips.  On long caches the direct forms
     // of the norms make them vector-ALU bound and the matrix-core path is faster (measured
     // crossover on gfx950: about 1e5 head-tokens when o_i is needed, 2.6e5 when it is not).
@@ -655,14 +792,20 @@ bool decode_path_covers(int B, int N, int W, int Hq, int Hkv, int d, int dtype, 
 void decode_plan(int B, int N, int Hq, int Hkv, int d, ScoreWorkspace *ws, size_t *off) {
     const int G = Hq / Hkv;
     const int BH = B * Hkv;
-    const int splits = splits_for(N, d);
+    // The longest ranges that leave two workgroups per CU, and no shorter ones than the inline merge can take.
+    int steps = kMaxSteps;
+    while (steps > 2 && (long long)BH * splits_for(N, d, steps) < 512 && splits_for(N, d, steps / 2) <= kInlineSplits) steps /= 2;
+    const int splits = splits_for(N, d, steps);
     ws->dec_rows = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
-    ws->dec_range = range_tokens(d);
+    ws->dec_range = steps * tokens_per_step(d);
     ws->dec_splits = splits;
     ws->dec_merge_inline = splits <= kInlineSplits ? 1 : 0;
+    const size_t records = (size_t)BH * splits * ws->dec_rows;
     ws->dec_z = *off;      *off = align256(*off + (size_t)BH * N * ws->dec_rows * sizeof(float));
-    ws->dec_part = *off;   *off = align256(*off + (size_t)BH * splits * ws->dec_rows * part_stride(d) * sizeof(float));
+    ws->dec_head = *off;   *off = align256(*off + records * sizeof(float4));
+    ws->dec_vec = *off;    *off = align256(*off + records * 2 * d * sizeof(float));
     ws->dec_final = *off;  *off = align256(*off + (size_t)BH * ws->dec_rows * final_stride(d) * sizeof(float));
+    ws->dec_lowest = *off; *off = align256(*off + (size_t)BH * splits * sizeof(unsigned long long));
 }
 
 hipError_t launch_score_decode(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
