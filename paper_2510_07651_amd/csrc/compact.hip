@@ -1,6 +1,7 @@
 // K/V compaction (Appendix E, Algorithm 2: gather of the kept rows).  Pure byte moves:
 // each thread copies one 16-byte piece of one kept row with a 128-bit load and store.
 #include "internal.h"
+#include "wave_util.h"
 
 namespace obc {
 namespace {
@@ -165,15 +166,16 @@ __global__ __launch_bounds__(256) void evict_pick(const float *__restrict__ scor
 // Closes the gap the evicted token leaves: row j >= e takes row j + 1, for K, V (blockIdx.y = 0, 1; one 64-byte column
 // slice per workgroup, rows read chunk by chunk before they are overwritten, as in move_rows_in_place) and for the
 // running scores (blockIdx.y = 2), whose slots from len - 1 on are cleared.  Every wave takes the minimum of the head's
-// candidates itself: one memory round trip instead of a kernel of its own.
+// candidates itself: one memory round trip instead of a kernel of its own.  The head varies fastest in the grid, as in the
+// decode kernels: its workgroups then share an XCD with those that last touched its rows where the head count allows.
 __global__ __launch_bounds__(kMoveThreads) void evict_shift(uint4 *__restrict__ k, uint4 *__restrict__ v,
                                                             float *__restrict__ scores,
                                                             int32_t *__restrict__ evicted,
                                                             const unsigned long long *__restrict__ lowest, int n_lowest,
                                                             int N, int Hkv, int ragged, SeqLens lens, int row_vec) {
-    const size_t bg = blockIdx.z;
+    const size_t bg = blockIdx.x;
     const int len = seq_len_of(lens, ragged, (int)(bg / Hkv), N);
-    if (blockIdx.y == 2 && blockIdx.x != 0) return;
+    if (blockIdx.y == 2 && blockIdx.z != 0) return;
     unsigned long long low = ~0ull;
     for (int i = threadIdx.x & 63; i < n_lowest; i += 64) {
         const unsigned long long c = lowest[bg * n_lowest + i];
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(kMoveThreads) void evict_shift(uint4 *__restrict__ 
         return;
     }
     uint4 *rows = (blockIdx.y == 0 ? k : v) + bg * N * row_vec;
-    const int c = blockIdx.x * 4 + (threadIdx.x & 3);
+    const int c = blockIdx.z * 4 + (threadIdx.x & 3);
     const int r = threadIdx.x >> 2;
     for (int j0 = e; j0 < budget; j0 += kMoveChunk) {
         uint4 x[kMoveRows];
@@ -269,7 +271,7 @@ hipError_t launch_evict_one(void *k, void *v, float *scores, int32_t *evicted, u
         n_lowest = 1;
     }
     const int row_vec = row_bytes / 16;
-    const dim3 grid((row_vec + 3) / 4, 3, B * Hkv);
+    const dim3 grid(B * Hkv, 3, (row_vec + 3) / 4);
     evict_shift<<<grid, dim3(kMoveThreads), 0, stream>>>((uint4 *)k, (uint4 *)v, scores, evicted, lowest, n_lowest, N, Hkv, ragged,
                                                          lens, row_vec);
     return hipGetLastError();

@@ -138,15 +138,6 @@ __device__ __forceinline__ unsigned long long evict_candidate(float score, int p
 }
 __device__ __forceinline__ int evict_candidate_token(unsigned long long c) { return (int)~(uint32_t)c; }
 
-__device__ __forceinline__ unsigned long long wave_min(unsigned long long x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const unsigned long long o = __shfl_xor(x, off);
-        x = o < x ? o : x;
-    }
-    return x;
-}
-
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t h) {
     return __uint_as_float(((uint32_t)h) << 16);
 }

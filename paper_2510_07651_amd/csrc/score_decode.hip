@@ -30,13 +30,14 @@
 // and the (row, p*) pair is scored from the first identity.
 // Every sum runs in a fixed order: results are bit-reproducible.
 #include "internal.h"
+#include "wave_util.h"
 
 namespace obc {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
-constexpr int kMaxSteps = 8;         // most token rows per lane: a range is 2, 4 or 8 workgroup-wide steps
+constexpr int kMaxSteps = 4;         // most token rows per lane: a range is 1, 2 or 4 workgroup-wide steps
 constexpr int kInlineSplits = 48;    // most ranges per head the scoring kernel merges itself
 constexpr int kMergeThreads = 1024;
 constexpr int kMergeOwn = 4;         // ranges per merging thread
@@ -58,30 +59,15 @@ __device__ __forceinline__ void unpack8(const uint4 w, float *x) {
     x[6] = __uint_as_float(w.w << 16); x[7] = __uint_as_float(w.w & 0xffff0000u);
 }
 
-// x + (x of the lane a data-parallel-primitive control pairs this lane with); register-to-register,
-// no trip through LDS.  Call with every lane of the wave active.
-template <int kCtrl>
-__device__ __forceinline__ float dpp_pair_sum(float x) {
-    const int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, false);
-    return x + __int_as_float(y);
-}
 // Sum over the `kLanes` (8 or 16) consecutive lanes that share a token; all of them end with the
-// same bits.  Lane pairings: neighbours, neighbouring pairs (quad permutes 1032 and 2301), then
-// the mirror image inside each half row of 8 lanes and inside each row of 16.
+// same bits.
 template <int kLanes>
 __device__ __forceinline__ float group_sum(float x) {
-    x = dpp_pair_sum<0xB1>(x);
-    x = dpp_pair_sum<0x4E>(x);
-    x = dpp_pair_sum<0x141>(x);
-    if (kLanes == 16) x = dpp_pair_sum<0x140>(x);
+    x += dpp_pair<0xB1>(x);
+    x += dpp_pair<0x4E>(x);
+    x += dpp_pair<0x141>(x);
+    if (kLanes == 16) x += dpp_pair<0x140>(x);
     return x;
-}
-// The values of the two lanes that differ in bit 4 (16) or 5 (32) of their index, lower one first.
-template <int kBit>
-__device__ __forceinline__ void both_of_pair(uint32_t x, uint32_t &lower, uint32_t &upper) {
-    const auto r = kBit == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false) : __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    lower = r[0];
-    upper = r[1];
 }
 // Sums over the token slots of a wave (the lanes of equal position in their group), for kN values at once: each level
 // adds two values across lane pairs with one register exchange and leaves half of the values in each half of the pair.
@@ -106,8 +92,7 @@ __device__ __forceinline__ void slot_sums(float (&x)[kN]) {
 #pragma unroll
         for (int i = 0; i < kN / 8; ++i) {
             const float give = high ? x[2 * i] : x[2 * i + 1], keep = high ? x[2 * i + 1] : x[2 * i];
-            // row_ror:8 brings the value of lane l ^ 8
-            x[i] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), 0x128, 0xf, 0xf, false));
+            x[i] = keep + dpp_pair<0x128>(give);
         }
     }
 }
@@ -142,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
     __shared__ float red_o[kNeedO ? kWaves * kG * kD : 1];
     __shared__ float top_v[kNeedO ? kG * kD : 1];   // V rows of the top tokens
 
-    const int bh = blockIdx.y, b = bh / Hkv, split = blockIdx.x;
+    const int bh = blockIdx.x, b = bh / Hkv, split = blockIdx.y;
     const int len = seq_len_of(lens, ragged, b, N);
     const int t0 = split * kSteps * tokens_per_step(kD);
     const int t1 = min(t0 + kSteps * tokens_per_step(kD), len);
@@ -210,30 +195,27 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
             const int p = token_of<kD>(t0, u, wave, slot);
             if (p < t1 && z[u][r] > bm) { bm = z[u][r]; ba = p; }
         }
-        if (kLpt == 8) take_better(bm, ba, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(bm), 0x128, 0xf, 0xf, false)),
-                                   __builtin_amdgcn_update_dpp(0, ba, 0x128, 0xf, 0xf, false));
-        uint32_t m0, m1, a0, a1;
-        both_of_pair<16>(__float_as_uint(bm), m0, m1);
-        both_of_pair<16>((uint32_t)ba, a0, a1);
-        bm = __uint_as_float(m0);
-        ba = (int)a0;
-        take_better(bm, ba, __uint_as_float(m1), (int)a1);
-        both_of_pair<32>(__float_as_uint(bm), m0, m1);
-        both_of_pair<32>((uint32_t)ba, a0, a1);
-        bm = __uint_as_float(m0);
-        ba = (int)a0;
-        take_better(bm, ba, __uint_as_float(m1), (int)a1);
-        if (lane == 0) { red_m[wave * kG + r] = bm; red_a[wave * kG + r] = ba; }
+        // over the wave's token slots: the value first, then the lowest token that has it
+        const float own = bm;
+        if (kLpt == 8) bm = fmaxf(bm, dpp_pair<0x128>(bm));
+        bm = across_rows<MaxOp>(bm);
+        uint32_t at = own == bm ? (uint32_t)ba : 0x7fffffffu;
+        if (kLpt == 8) at = MinOp()(at, dpp_pair<0x128>(at));
+        at = across_rows<MinOp>(at);
+        if (lane == 0) { red_m[r * kWaves + wave] = bm; red_a[r * kWaves + wave] = (int)at; }
     }
     __syncthreads();
+    // over the waves: one row of 16 lanes per window row
 #pragma unroll
-    for (int r = 0; r < kG; ++r) {
-        float bm = red_m[r];
-        int ba = red_a[r];
+    for (int r0 = 0; r0 < kG; r0 += 4) {
+        const int e = kG >= 4 ? r0 * kWaves + lane : lane % (kG * kWaves);
+        const float own = red_m[e], bm = row16_reduce<MaxOp>(own);
+        const uint32_t at = row16_reduce<MinOp>(own == bm ? (uint32_t)red_a[e] : 0x7fffffffu);
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) take_better(bm, ba, red_m[w * kG + r], red_a[w * kG + r]);
-        m[r] = bm;
-        top[r] = ba;
+        for (int r = 0; r < 4 && r0 + r < kG; ++r) {
+            m[r0 + r] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(bm), 16 * r));
+            top[r0 + r] = __builtin_amdgcn_readlane((int)at, 16 * r);
+        }
     }
 
     // Sums of exp(z - m) and of exp(z - m) v over the range without the top token.
@@ -268,15 +250,10 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
     }
 #pragma unroll
     for (int r = 0; r < kG; ++r) {
-        // the kLpt lanes of a slot hold the same sum
-        float l = lsum[r];
-        uint32_t x0, x1;
-        if (kLpt == 8) l += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(l), 0x128, 0xf, 0xf, false));
-        both_of_pair<16>(__float_as_uint(l), x0, x1);
-        l = __uint_as_float(x0) + __uint_as_float(x1);
-        both_of_pair<32>(__float_as_uint(l), x0, x1);
-        l = __uint_as_float(x0) + __uint_as_float(x1);
-        if (lane == 0) red_l[wave * kG + r] = l;
+        float l = lsum[r];                          // (the kLpt lanes of a slot hold the same sum)
+        if (kLpt == 8) l += dpp_pair<0x128>(l);
+        l = across_rows<SumOp>(l);
+        if (lane == 0) red_l[r * kWaves + wave] = l;
     }
     if (kNeedO) {
         slot_sums<kLpt>(acc);
@@ -288,16 +265,15 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
         }
     }
     __syncthreads();
-    if (threadIdx.x < kG) {
-        const int r = threadIdx.x;
-        float l = red_l[r];
+    if (wave < (kG + 3) / 4) {                      // one row of 16 lanes per window row again
+        const int r = wave * 4 + (lane >> 4);
+        const float l = row16_reduce<SumOp>(r < kG ? red_l[r * kWaves + (lane & 15)] : 0.f);
+        float mr = m[0];
+        int tr = top[0];
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) l += red_l[w * kG + r];
-        float bm = red_m[r];
-        int ba = red_a[r];
-#pragma unroll
-        for (int w = 1; w < kWaves; ++w) take_better(bm, ba, red_m[w * kG + r], red_a[w * kG + r]);
-        head[r] = make_float4(bm, l, __int_as_float(ba), 0.f);
+        for (int x = 1; x < kG; ++x)
+            if (r == x) { mr = m[x]; tr = top[x]; }
+        if ((lane & 15) == 0 && r < kG) head[r] = make_float4(mr, l, __int_as_float(tr), 0.f);
     }
     if (!kNeedO) return;
     float *vec = part_vec + ((size_t)bh * splits + split) * kG * 2 * kD;
@@ -351,15 +327,10 @@ __device__ __forceinline__ void merge_few(const float4 *__restrict__ part_head, 
         if (r >= kG || r >= G) continue;
         float4 h = make_float4(-INFINITY, 0.f, __int_as_float(-1), 0.f);
         if (lane < splits) h = part_head[(size_t)lane * kG + r];
-        float bm = h.x;
-        int bs = lane;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) take_better(bm, bs, __shfl_xor(bm, off), __shfl_xor(bs, off));
-        // (the first range attaining the max holds the lowest token that does)
-        const float w = h.x == -INFINITY ? 0.f : __expf(h.x - bm);
-        float l = fmaf(w, h.y, lane != bs ? w : 0.f);         // ranges other than the winning one count their top token
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+        const float bm = wave_reduce<MaxOp>(h.x);
+        const int bs = __ffsll((unsigned long long)__ballot(h.x == bm)) - 1;    // the first range attaining the max holds
+        const float w = h.x == -INFINITY ? 0.f : __expf(h.x - bm);              // the lowest token that does
+        const float l = wave_reduce<SumOp>(fmaf(w, h.y, lane != bs ? w : 0.f));  // (other ranges count their top token)
         if (lane < splits) w_s[r * kInlineSplits + lane] = lane == bs ? 0.f : w;
         if (lane == bs) {
             best_s[r] = bs;
@@ -552,9 +523,9 @@ __global__ __launch_bounds__(kThreads) void decode_score(
     __shared__ __attribute__((aligned(16))) float fin[kG * kFs];
     __shared__ unsigned long long lowest_s[kWaves];
 
-    const int bh = blockIdx.y, b = bh / Hkv;
+    const int bh = blockIdx.x, b = bh / Hkv, split = blockIdx.y;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int t0 = blockIdx.x * kSteps * tokens_per_step(kD);
+    const int t0 = split * kSteps * tokens_per_step(kD);
     const int t1 = min(t0 + kSteps * tokens_per_step(kD), N);
     const uint16_t *vg = v + (size_t)bh * N * kD;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -562,7 +533,7 @@ __global__ __launch_bounds__(kThreads) void decode_score(
     float *out = scores + (size_t)bh * N;
 
     if (t0 >= len) {                                // only padding here
-        if (lowest && threadIdx.x == 0) lowest[(size_t)bh * splits + blockIdx.x] = ~0ull;
+        if (lowest && threadIdx.x == 0) lowest[(size_t)bh * splits + split] = ~0ull;
         if (!accumulate) {
             for (int p = t0 + threadIdx.x; p < t1; p += kThreads) {
 #pragma unroll
@@ -703,7 +674,7 @@ __global__ __launch_bounds__(kThreads) void decode_score(
         if (threadIdx.x == 0) {
 #pragma unroll
             for (int w = 1; w < kWaves; ++w) low = lowest_s[w] < low ? lowest_s[w] : low;
-            lowest[(size_t)bh * splits + blockIdx.x] = low;
+            lowest[(size_t)bh * splits + split] = low;
         }
     }
 }
@@ -716,7 +687,9 @@ hipError_t launch_decode_steps(const ScoreArgs &a, const ScoreWorkspace &ws, cha
     float4 *part_head = (float4 *)(base + ws.dec_head);
     float *part_vec = (float *)(base + ws.dec_vec);
     float *fin = (float *)(base + ws.dec_final);
-    const dim3 grid(ws.dec_splits, BH);
+    // (KV head fastest: the workgroups of a head then share an XCD, and its L2 the head's rows and records, where the
+    // head count allows)
+    const dim3 grid(BH, ws.dec_splits);
     if (ws.dec_splits > kMaxSplits || (long long)ws.dec_splits * kSteps * tokens_per_step(kD) < a.N) return hipErrorInvalidValue;
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
         decode_partial<kG, kD, kSteps, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
@@ -744,9 +717,9 @@ hipError_t launch_decode_steps(const ScoreArgs &a, const ScoreWorkspace &ws, cha
 template <int kG, int kD, int kVariant>
 hipError_t launch_decode_variant(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
     switch (ws.dec_range / tokens_per_step(kD)) {
+        case 1: return launch_decode_steps<kG, kD, 1, kVariant>(a, ws, base, stream);
         case 2: return launch_decode_steps<kG, kD, 2, kVariant>(a, ws, base, stream);
-        case 4: return launch_decode_steps<kG, kD, 4, kVariant>(a, ws, base, stream);
-        default: return launch_decode_steps<kG, kD, 8, kVariant>(a, ws, base, stream);
+        default: return launch_decode_steps<kG, kD, 4, kVariant>(a, ws, base, stream);
     }
 }
 
@@ -792,9 +765,9 @@ bool decode_path_covers(int B, int N, int W, int Hq, int Hkv, int d, int dtype, 
 void decode_plan(int B, int N, int Hq, int Hkv, int d, ScoreWorkspace *ws, size_t *off) {
     const int G = Hq / Hkv;
     const int BH = B * Hkv;
-    // The longest ranges that leave two workgroups per CU, and no shorter ones than the inline merge can take.
+    // The longest ranges that leave one workgroup per CU, and no shorter ones than the inline merge can take.
     int steps = kMaxSteps;
-    while (steps > 2 && (long long)BH * splits_for(N, d, steps) < 512 && splits_for(N, d, steps / 2) <= kInlineSplits) steps /= 2;
+    while (steps > 1 && (long long)BH * splits_for(N, d, steps) < 256 && splits_for(N, d, steps / 2) <= kInlineSplits) steps /= 2;
     const int splits = splits_for(N, d, steps);
     ws->dec_rows = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
     ws->dec_range = steps * tokens_per_step(d);
