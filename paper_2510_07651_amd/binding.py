@@ -122,7 +122,13 @@ def _lens_arg(seq_lens: Optional[Sequence[int]], B: int):
     return (ctypes.c_int32 * B)(*[int(x) for x in seq_lens])
 
 
+# The current stream's handle without the Stream object torch.cuda.current_stream builds (2 us, as much as a launch).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(t: torch.Tensor) -> int:
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
     return torch.cuda.current_stream(t.device).cuda_stream
 
 

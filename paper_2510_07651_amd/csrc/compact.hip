@@ -141,8 +141,9 @@ __global__ __launch_bounds__(kMoveThreads) void move_rows_in_place(uint4 *__rest
 // attention sinks, the most recent ones kept as well).
 // ------------------------------------------------------------------------------------
 // One workgroup per (sequence, KV head): its lowest evict_candidate among first <= p < len - tail.
+template <typename Lens>
 __global__ __launch_bounds__(256) void evict_pick(const float *__restrict__ scores, int N, int Hkv, int ragged,
-                                                  SeqLens lens, int first, int tail,
+                                                  Lens lens, int first, int tail,
                                                   unsigned long long *__restrict__ lowest) {
     __shared__ unsigned long long best_w[4];
     const int bg = blockIdx.x;
@@ -168,11 +169,12 @@ __global__ __launch_bounds__(256) void evict_pick(const float *__restrict__ scor
 // running scores (blockIdx.y = 2), whose slots from len - 1 on are cleared.  Every wave takes the minimum of the head's
 // candidates itself: one memory round trip instead of a kernel of its own.  The head varies fastest in the grid, as in the
 // decode kernels: its workgroups then share an XCD with those that last touched its rows where the head count allows.
+template <typename Lens>
 __global__ __launch_bounds__(kMoveThreads) void evict_shift(uint4 *__restrict__ k, uint4 *__restrict__ v,
                                                             float *__restrict__ scores,
                                                             int32_t *__restrict__ evicted,
                                                             const unsigned long long *__restrict__ lowest, int n_lowest,
-                                                            int N, int Hkv, int ragged, SeqLens lens, int row_vec) {
+                                                            int N, int Hkv, int ragged, Lens lens, int row_vec) {
     const size_t bg = blockIdx.x;
     const int len = seq_len_of(lens, ragged, (int)(bg / Hkv), N);
     if (blockIdx.y == 2 && blockIdx.z != 0) return;
@@ -264,17 +266,19 @@ hipError_t launch_compact_in_place(void *k, void *v, float *scores, const int32_
 hipError_t launch_evict_one(void *k, void *v, float *scores, int32_t *evicted, unsigned long long *lowest, int n_lowest,
                             int B, int Hkv, int N, int ragged, const SeqLens &lens, int first, int tail, int row_bytes,
                             hipStream_t stream) {
-    if (n_lowest == 0) {
-        evict_pick<<<dim3(B * Hkv), dim3(256), 0, stream>>>(scores, N, Hkv, ragged, lens, first, tail, lowest);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        n_lowest = 1;
-    }
-    const int row_vec = row_bytes / 16;
-    const dim3 grid(B * Hkv, 3, (row_vec + 3) / 4);
-    evict_shift<<<grid, dim3(kMoveThreads), 0, stream>>>((uint4 *)k, (uint4 *)v, scores, evicted, lowest, n_lowest, N, Hkv, ragged,
-                                                         lens, row_vec);
-    return hipGetLastError();
+    return with_lens(ragged, B, lens, [&](const auto &few) {
+        if (n_lowest == 0) {
+            evict_pick<<<dim3(B * Hkv), dim3(256), 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, lowest);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            n_lowest = 1;
+        }
+        const int row_vec = row_bytes / 16;
+        const dim3 grid(B * Hkv, 3, (row_vec + 3) / 4);
+        evict_shift<<<grid, dim3(kMoveThreads), 0, stream>>>((uint4 *)k, (uint4 *)v, scores, evicted, lowest, n_lowest, N, Hkv,
+                                                             ragged, few, row_vec);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_compact(const void *k, const void *v, const int32_t *keep_idx, void *k_out, void *v_out, int B,

@@ -11,9 +11,21 @@ namespace obc {
 
 // True lengths travel to the kernels by value (kernel-argument memory), so the
 // library needs no device allocation and no host-to-device copy of its own.
-struct SeqLens {
-    int32_t len[OBC_MAX_RAGGED_BATCH];
+template <int kMost>
+struct SeqLensOf {
+    int32_t len[kMost];
 };
+using SeqLens = SeqLensOf<OBC_MAX_RAGGED_BATCH>;
+// Kernels take the lengths as a template type.  Half a KB of kernel arguments costs the host 1.7 us per launch (4.5 us
+// against 2.8 us), as much as everything else, so equal lengths and batches of up to kFewLens travel in 32 bytes.
+constexpr int kFewLens = 8;
+template <typename Launch>
+inline hipError_t with_lens(int ragged, int B, const SeqLens &lens, Launch &&launch) {
+    if (ragged && B > kFewLens) return launch(lens);
+    SeqLensOf<kFewLens> few = {};
+    for (int b = 0; ragged && b < B; ++b) few.len[b] = lens.len[b];
+    return launch(few);
+}
 
 struct ScoreArgs {
     const void *q, *k, *v;
@@ -24,7 +36,7 @@ struct ScoreArgs {
     int ragged;       // 0: every sequence has length N
     int stage_mask;   // OBC_STAGE_* bits to run
     int accumulate;   // 1: add to the scores already in `scores` (positions beyond the true length untouched)
-    int find_lowest;  // 1 (decode path only): every range reports its lowest-scored token among evict_first <= p < len - evict_tail
+    int find_lowest;  // 1 (decode path only): every wave reports its lowest-scored token among evict_first <= p < len - evict_tail
     int evict_first, evict_tail;
     SeqLens lens;     // valid for b < B when ragged
 };
@@ -60,7 +72,8 @@ struct ScoreWorkspace {
     size_t dec_z;      // float [B*Hkv*N*dec_rows]  scaled logits, token-major
     size_t dec_head;   // float4 [B*Hkv*dec_splits*dec_rows]  per-range partial records, their vectors below
     size_t dec_vec;    // float [B*Hkv*dec_splits*dec_rows*2d]
-    size_t dec_lowest; // uint64 [B*Hkv*dec_splits]  a range's evict_candidate
+    size_t dec_lowest; // uint64 [B*Hkv*dec_lowest_per_head]  evict_candidates of the scoring kernel's waves
+    int dec_lowest_per_head;
     size_t dec_final;  // float [B*Hkv*dec_rows*(2d+4)]  merged row records
     int use_decode;    // 1: decode path (takes precedence over the other two)
     int dec_rows;      // query heads per KV head, padded to 1, 2, 4 or 8
@@ -122,7 +135,8 @@ hipError_t launch_gather_scores(const float *in, const int32_t *keep_idx, float 
                                  int n_out, hipStream_t stream);
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, int blocks, hipStream_t stream);
 
-__device__ __forceinline__ int seq_len_of(const SeqLens &lens, int ragged, int b, int N) {
+template <typename Lens>
+__device__ __forceinline__ int seq_len_of(const Lens &lens, int ragged, int b, int N) {
     return ragged ? lens.len[b] : N;
 }
 

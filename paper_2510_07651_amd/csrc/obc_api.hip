@@ -366,10 +366,10 @@ int obc_decode_step(const void *q, void *k, void *v, float *scores, int32_t *evi
     rc = score_impl(q, k, v, N, 1, Hq, Hkv, d, variant, scores, B, dtype, seq_lens_host, workspace, score_bytes, hip_stream,
                     OBC_STAGE_ALL, 1, num_sinks, num_recent);
     if (rc != OBC_OK) return rc;
-    // The decode kernels have left every range's candidate; after the other paths one pass over the scores finds them.
+    // The decode kernels have left their waves' candidates; after the other paths one pass over the scores finds them.
     unsigned long long *lowest = (unsigned long long *)((char *)workspace + (ws.use_decode ? ws.dec_lowest : score_bytes));
     const long long row_bytes = (long long)d * (dtype == OBC_F32 ? 4 : 2);
-    const hipError_t e = launch_evict_one(k, v, scores, evicted, lowest, ws.use_decode ? ws.dec_splits : 0, B, Hkv, N, ragged, lens, num_sinks, num_recent, (int)row_bytes,
+    const hipError_t e = launch_evict_one(k, v, scores, evicted, lowest, ws.use_decode ? ws.dec_lowest_per_head : 0, B, Hkv, N, ragged, lens, num_sinks, num_recent, (int)row_bytes,
                                           (hipStream_t)hip_stream);
     return e == hipSuccess ? OBC_OK : OBC_ELAUNCH;
 }

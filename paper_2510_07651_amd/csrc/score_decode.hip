@@ -15,11 +15,11 @@
 //                    ||v_p + Z (v_p - o_i)||^2 (the completed square of Eq. 6), Eq. 8 and
 //                    the l1-weighted variant of Appendix C, summed over the query heads of
 //                    the KV head (Appendix A.5), written or added to the running scores; for an
-//                    eviction step also the range's lowest-scored token.
+//                    eviction step also every wave's lowest-scored token.
 // Ranges are as short as keeps the inline merge possible while the chip has workgroups to spare
-// (2, 4 or 8 tokens per lane): a wave is alone on its SIMD here, so its instruction count is its
+// (1, 2 or 4 tokens per lane, sixteen waves): instructions of a lone wave issue one by one, so the count per wave is its
 // time.  8 KV heads x 1025 tokens, G = 4, d = 128, joint, per layer: 72 workgroups of 8 tokens per
-// lane 26 us for the two kernels, 264 workgroups of 2 tokens PARTIAL_SCORE_US.
+// lane, four waves each, 26 us for the two kernels; 136 workgroups of one token per lane, sixteen waves, 13 us.
 //
 // Cancellation guard.  When one key takes almost all of a row's attention, o_i is almost
 // v_p* and fp32 cannot hold their difference.  Every range keeps its top-logit token out of
@@ -114,10 +114,10 @@ __device__ __forceinline__ int token_of(int t0, int u, int wave, int slot) {
 }
 
 // The scaled logits of the range, its row maxima and the unnormalised sums around them.
-template <int kG, int kD, int kSteps, bool kNeedO>
+template <int kG, int kD, int kSteps, bool kNeedO, typename Lens>
 __global__ __launch_bounds__(kThreads) void decode_partial(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, int N, int G,
-    int Hkv, int ragged, SeqLens lens, int splits, float *__restrict__ z_buf, float4 *__restrict__ part_head,
+    int Hkv, int ragged, Lens lens, int splits, float *__restrict__ z_buf, float4 *__restrict__ part_head,
     float *__restrict__ part_vec) {
     constexpr int kLpt = kD / 8;        // lanes per token row
     constexpr int kSlots = 64 / kLpt;   // token rows per wave and step
@@ -300,33 +300,45 @@ __device__ __forceinline__ void merge_finish(float l_rest, float o_rest, float v
 // Merge of at most kInlineSplits ranges of one KV head by one workgroup, into final records in LDS.  The vectors of all
 // ranges are fetched while the heads are still on their way; only the winning range's two rows wait for them.
 template <int kG, int kD, bool kNeedO>
-__device__ __forceinline__ void merge_few(const float4 *__restrict__ part_head, const float *__restrict__ part_vec,
-                                          int splits, int G, const uint16_t *__restrict__ vg, float *fin) {
-    constexpr int kFs = final_stride(kD);
-    constexpr int kQuads = kG * kD / 4;                       // float4 columns of all rows
-    constexpr int kParts = kQuads >= kThreads ? 1 : kThreads / kQuads;      // threads that share one
-    constexpr int kOwn = (kInlineSplits + kParts - 1) / kParts, kHold = kOwn < 24 ? kOwn : 24;     // ranges a thread adds up, holds at once
+struct MergeFew {
+    static constexpr int kFs = final_stride(kD);
+    static constexpr int kQuads = kG * kD / 4;                // float4 columns of all rows
+    static constexpr int kParts = kThreads / kQuads;          // threads that share one
+    static constexpr int kOwn = (kInlineSplits + kParts - 1) / kParts;      // ranges a thread adds up
+    static_assert(kQuads <= kThreads, "one column per thread at most");
+    float4 h;                                                 // head of range `lane`, row `wave`
+    float4 x[kNeedO ? kOwn : 1];                              // this thread's columns of its ranges, top tokens included
+
+    // First in the caller's queue: what follows (the caller's own loads) is not waited for.
+    __device__ __forceinline__ void load(const float4 *__restrict__ part_head, const float *__restrict__ part_vec, int splits, int G) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        h = make_float4(-INFINITY, 0.f, __int_as_float(-1), 0.f);
+        if (wave < kG && wave < G && lane < splits) h = part_head[(size_t)lane * kG + wave];
+        if (!kNeedO) return;
+        const int quad = threadIdx.x % kQuads, part = threadIdx.x / kQuads, row = quad * 4 / kD, col = quad * 4 % kD;
+        const float *mine = part_vec + (size_t)row * 2 * kD + kD + col;
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) {
+            const int s = part + i * kParts;
+            x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (s < splits) x[i] = *(const float4 *)(mine + (size_t)s * kG * 2 * kD);
+        }
+    }
+    __device__ __forceinline__ void merge(const float *__restrict__ part_vec, int splits, int G,
+                                          const uint16_t *__restrict__ vg, float *fin);
+};
+
+template <int kG, int kD, bool kNeedO>
+__device__ __forceinline__ void MergeFew<kG, kD, kNeedO>::merge(const float *__restrict__ part_vec, int splits, int G,
+                                                                const uint16_t *__restrict__ vg, float *fin) {
     __shared__ float w_s[kG * kInlineSplits];
     __shared__ int best_s[kG];
     __shared__ __attribute__((aligned(16))) float sum_s[kNeedO ? kParts * kG * kD : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int quad = threadIdx.x % kQuads, part = threadIdx.x / kQuads, row = quad * 4 / kD, col = quad * 4 % kD;
     const float *mine = part_vec + (size_t)row * 2 * kD + kD + col;         // sums that include the range's top token
-    float4 x[kHold];
-    if (kNeedO && part < kParts) {
-#pragma unroll
-        for (int i = 0; i < kHold; ++i) {
-            const int s = part + i * kParts;
-            x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (s < splits) x[i] = *(const float4 *)(mine + (size_t)s * kG * 2 * kD);
-        }
-    }
-#pragma unroll
-    for (int r0 = 0; r0 < kG; r0 += kWaves) {                 // one wave per row, one lane per range
-        const int r = r0 + wave;
-        if (r >= kG || r >= G) continue;
-        float4 h = make_float4(-INFINITY, 0.f, __int_as_float(-1), 0.f);
-        if (lane < splits) h = part_head[(size_t)lane * kG + r];
+    if (wave < kG && wave < G) {                              // one wave per row, one lane per range
+        const int r = wave;
         const float bm = wave_reduce<MaxOp>(h.x);
         const int bs = __ffsll((unsigned long long)__ballot(h.x == bm)) - 1;    // the first range attaining the max holds
         const float w = h.x == -INFINITY ? 0.f : __expf(h.x - bm);              // the lowest token that does
@@ -346,31 +358,22 @@ __device__ __forceinline__ void merge_few(const float4 *__restrict__ part_head, 
     // the winning range's rows: its sums without its top token (weight 1), and that token's own row
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     uint2 vt = make_uint2(0u, 0u);
-    const bool live = part < kParts && row < G;
+    const bool live = row < G;
     if (live && part == 0) {
         o = *(const float4 *)(mine - kD + (size_t)best_s[row] * kG * 2 * kD);
         vt = *(const uint2 *)(vg + (size_t)__float_as_int(fin[row * kFs + 2]) * kD + col);
     }
     float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
     if (live) {
-        for (int i0 = 0; i0 < kOwn; i0 += kHold) {
-            if (i0 > 0) {
 #pragma unroll
-                for (int i = 0; i < kHold; ++i) {
-                    const int s = part + (i0 + i) * kParts;
-                    if (s < splits) x[i] = *(const float4 *)(mine + (size_t)s * kG * 2 * kD);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < kHold; ++i) {
-                const int s = part + (i0 + i) * kParts;
-                const float w = s < splits ? w_s[row * kInlineSplits + s] : 0.f;
-                if (w != 0.f) {                               // (an empty range has no vectors)
-                    t.x = fmaf(w, x[i].x, t.x);
-                    t.y = fmaf(w, x[i].y, t.y);
-                    t.z = fmaf(w, x[i].z, t.z);
-                    t.w = fmaf(w, x[i].w, t.w);
-                }
+        for (int i = 0; i < kOwn; ++i) {
+            const int s = part + i * kParts;
+            const float w = s < splits ? w_s[row * kInlineSplits + s] : 0.f;
+            if (w != 0.f) {                                   // (an empty range has no vectors)
+                t.x = fmaf(w, x[i].x, t.x);
+                t.y = fmaf(w, x[i].y, t.y);
+                t.z = fmaf(w, x[i].z, t.z);
+                t.w = fmaf(w, x[i].w, t.w);
             }
         }
         if (kParts > 1) *(float4 *)(sum_s + part * kG * kD + quad * 4) = t;
@@ -505,10 +508,10 @@ struct DecodeNeeds {
 };
 
 // Scores of the range's tokens from the stored logits, the merged row statistics and V.  With `lowest`, also the
-// lowest (score, highest index) among the range's tokens first <= p < len - tail, as an evict_candidate.
-template <int kG, int kD, int kSteps, int kVariant>
+// lowest (score, highest index) among each wave's tokens first <= p < len - tail, as an evict_candidate.
+template <int kG, int kD, int kSteps, int kVariant, typename Lens>
 __global__ __launch_bounds__(kThreads) void decode_score(
-    const uint16_t *__restrict__ v, int N, int G, int Hkv, int ragged, SeqLens lens, int splits,
+    const uint16_t *__restrict__ v, int N, int G, int Hkv, int ragged, Lens lens, int splits,
     const float *__restrict__ z_buf, const float4 *__restrict__ part_head, const float *__restrict__ part_vec,
     const float *__restrict__ fin_global, int merge_here, float *__restrict__ scores, size_t plane_stride, int accumulate,
     unsigned long long *__restrict__ lowest, int first, int tail) {
@@ -521,7 +524,6 @@ __global__ __launch_bounds__(kThreads) void decode_score(
     constexpr int kPlanes = kVariant == OBC_ALL ? 3 : 1;
     constexpr int kFs = final_stride(kD);
     __shared__ __attribute__((aligned(16))) float fin[kG * kFs];
-    __shared__ unsigned long long lowest_s[kWaves];
 
     const int bh = blockIdx.x, b = bh / Hkv, split = blockIdx.y;
     const int len = seq_len_of(lens, ragged, b, N);
@@ -533,7 +535,7 @@ __global__ __launch_bounds__(kThreads) void decode_score(
     float *out = scores + (size_t)bh * N;
 
     if (t0 >= len) {                                // only padding here
-        if (lowest && threadIdx.x == 0) lowest[(size_t)bh * splits + split] = ~0ull;
+        if (lowest && threadIdx.x < kWaves) lowest[((size_t)bh * splits + split) * kWaves + threadIdx.x] = ~0ull;
         if (!accumulate) {
             for (int p = t0 + threadIdx.x; p < t1; p += kThreads) {
 #pragma unroll
@@ -544,6 +546,8 @@ __global__ __launch_bounds__(kThreads) void decode_score(
     }
 
     // Every load of the range up front; they are in flight while the ranges are merged.
+    MergeFew<kG, kD, kNeedO> few;
+    if (merge_here) few.load(part_head + (size_t)bh * splits * kG, part_vec + (size_t)bh * splits * kG * 2 * kD, splits, G);
     uint4 vw[kSteps];
     float z[kSteps][kG], old[kSteps][kPlanes];
 #pragma unroll
@@ -567,27 +571,59 @@ __global__ __launch_bounds__(kThreads) void decode_score(
     }
 
     if (merge_here) {
-        merge_few<kG, kD, kNeedO>(part_head + (size_t)bh * splits * kG, part_vec + (size_t)bh * splits * kG * 2 * kD, splits, G, vg, fin);
+        few.merge(part_vec + (size_t)bh * splits * kG * 2 * kD, splits, G, vg, fin);
     } else {
         const float *src = fin_global + (size_t)bh * kG * kFs;
         for (int e = threadIdx.x; e < G * kFs; e += kThreads) fin[e] = src[e];
     }
     __syncthreads();
 
-    float m[kG], inv_l[kG], o[kG][8];
-    int top[kG];
+    // Rows outside, tokens inside: one row's constants and outputs at a time.
+    float vv[kSteps][8], a_sum[kSteps], a2_sum[kSteps], k_sum[kSteps], j_sum[kSteps];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+        if (kNeedV) unpack8(vw[u], vv[u]);
+        a_sum[u] = a2_sum[u] = k_sum[u] = j_sum[u] = 0.f;
+    }
 #pragma unroll
     for (int r = 0; r < kG; ++r) {
-        if (r < G) {
-            m[r] = fin[r * kFs];
-            inv_l[r] = fin[r * kFs + 1];
-            top[r] = __float_as_int(fin[r * kFs + 2]);
-        } else {
-            m[r] = 0.f; inv_l[r] = 0.f; top[r] = -1;
-        }
+        if (r >= G) continue;                                   // uniform
+        const float m = fin[r * kFs], inv_l = fin[r * kFs + 1];
+        const int top = __float_as_int(fin[r * kFs + 2]);
+        float o[8];
         if (kNeedO) {
+            const float4 lo = *(const float4 *)(fin + r * kFs + kRecHead + sub * 8), hi = *(const float4 *)(fin + r * kFs + kRecHead + sub * 8 + 4);
+            o[0] = lo.x; o[1] = lo.y; o[2] = lo.z; o[3] = lo.w;
+            o[4] = hi.x; o[5] = hi.y; o[6] = hi.z; o[7] = hi.w;
+        }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[r][j] = r < G ? fin[r * kFs + kRecHead + sub * 8 + j] : 0.f;
+        for (int u = 0; u < kSteps; ++u) {
+            const int p = token_of<kD>(t0, u, wave, slot);
+            const float zz = z[u][r];
+            const float a = p < len ? __expf(zz - m) * inv_l : 0.f;
+            const float a2 = a * a;
+            a_sum[u] += a;
+            a2_sum[u] += a2;
+            if (kNeedO) {
+                float dlt[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) dlt[j] = vv[u][j] - o[j];
+                if (p == top) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) dlt[j] = fin[r * kFs + kRecHead + kD + sub * 8 + j];
+                }
+                float dk = 0.f, dj = 0.f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    if (kDoK) dk = fmaf(dlt[j], dlt[j], dk);
+                    if (kDoJ) {
+                        const float t = fmaf(zz, dlt[j], vv[u][j]);
+                        dj = fmaf(t, t, dj);
+                    }
+                }
+                if (kDoK) k_sum[u] = fmaf(a2 * zz * zz, dk, k_sum[u]);
+                if (kDoJ) j_sum[u] = fmaf(a2, dj, j_sum[u]);
+            }
         }
     }
 
@@ -595,56 +631,20 @@ __global__ __launch_bounds__(kThreads) void decode_score(
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
         const int p = token_of<kD>(t0, u, wave, slot);
-        float s_v = 0.f, s_k = 0.f, s_j = 0.f, s_a = 0.f;
-        if (p < len) {
-            float vv[8];
-            if (kNeedV) unpack8(vw[u], vv);
-            float a2_sum = 0.f, a_sum = 0.f;
+        float s_v = 0.f, s_k = k_sum[u], s_j = j_sum[u], s_a = 0.f;
+        if (kDoV) {
+            float n2 = 0.f;
 #pragma unroll
-            for (int r = 0; r < kG; ++r) {
-                if (r < G) {
-                    const float zz = z[u][r];
-                    const float a = __expf(zz - m[r]) * inv_l[r];
-                    const float a2 = a * a;
-                    a_sum += a;
-                    a2_sum += a2;
-                    if (kNeedO) {
-                        float dlt[8];
-                        if (p == top[r]) {
-#pragma unroll
-                            for (int j = 0; j < 8; ++j) dlt[j] = fin[r * kFs + kRecHead + kD + sub * 8 + j];
-                        } else {
-#pragma unroll
-                            for (int j = 0; j < 8; ++j) dlt[j] = vv[j] - o[r][j];
-                        }
-                        float dk = 0.f, dj = 0.f;
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            if (kDoK) dk = fmaf(dlt[j], dlt[j], dk);
-                            if (kDoJ) {
-                                const float t = fmaf(zz, dlt[j], vv[j]);
-                                dj = fmaf(t, t, dj);
-                            }
-                        }
-                        if (kDoK) s_k = fmaf(a2 * zz * zz, dk, s_k);
-                        if (kDoJ) s_j = fmaf(a2, dj, s_j);
-                    }
-                }
-            }
-            if (kDoV) {
-                float n2 = 0.f;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) n2 = fmaf(vv[j], vv[j], n2);
-                s_v = a2_sum * n2;
-            }
-            if (kVariant == OBC_VATP) {
-                float n1 = 0.f;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) n1 += fabsf(vv[j]);
-                s_a = a_sum * n1;
-            }
-            if (kVariant == OBC_ATTN) s_a = a_sum;
+            for (int j = 0; j < 8; ++j) n2 = fmaf(vv[u][j], vv[u][j], n2);
+            s_v = a2_sum[u] * n2;
         }
+        if (kVariant == OBC_VATP) {
+            float n1 = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) n1 += fabsf(vv[u][j]);
+            s_a = a_sum[u] * n1;
+        }
+        if (kVariant == OBC_ATTN) s_a = a_sum[u];
         // per-lane pieces cover 8 of the d columns: add the pieces of the lanes sharing the token
         if (kDoV) s_v = group_sum<kLpt>(s_v);
         if (kDoK) s_k = group_sum<kLpt>(s_k);
@@ -667,20 +667,15 @@ __global__ __launch_bounds__(kThreads) void decode_score(
             }
         }
     }
-    if (lowest) {                                               // uniform
-        low = wave_min(low);
-        if (lane == 0) lowest_s[wave] = low;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int w = 1; w < kWaves; ++w) low = lowest_s[w] < low ? lowest_s[w] : low;
-            lowest[(size_t)bh * splits + split] = low;
-        }
+    if (lowest) {                                               // uniform; one candidate per wave
+        if (kLpt == 8) low = min64(low, dpp_pair<0x128>(low));
+        low = across_rows<Min64Op>(low);                        // (only lanes with sub == 0 have one: those of lane 0's place)
+        if (lane == 0) lowest[((size_t)bh * splits + split) * kWaves + wave] = low;
     }
 }
 
-template <int kG, int kD, int kSteps, int kVariant>
-hipError_t launch_decode_steps(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+template <int kG, int kD, int kSteps, int kVariant, typename Lens>
+hipError_t launch_decode_steps(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
     constexpr bool kNeedO = DecodeNeeds<kVariant>::o;
     const int BH = a.B * a.Hkv;
     float *z_buf = (float *)(base + ws.dec_z);
@@ -693,7 +688,7 @@ hipError_t launch_decode_steps(const ScoreArgs &a, const ScoreWorkspace &ws, cha
     if (ws.dec_splits > kMaxSplits || (long long)ws.dec_splits * kSteps * tokens_per_step(kD) < a.N) return hipErrorInvalidValue;
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
         decode_partial<kG, kD, kSteps, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
-            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, a.lens,
+            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, lens,
             ws.dec_splits, z_buf, part_head, part_vec);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -706,7 +701,7 @@ hipError_t launch_decode_steps(const ScoreArgs &a, const ScoreWorkspace &ws, cha
     }
     if (a.stage_mask & OBC_STAGE_SWEEP2) {
         decode_score<kG, kD, kSteps, kVariant><<<grid, dim3(kThreads), 0, stream>>>(
-            (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, a.lens, ws.dec_splits, z_buf, part_head, part_vec, fin,
+            (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, lens, ws.dec_splits, z_buf, part_head, part_vec, fin,
             ws.dec_merge_inline, a.scores, (size_t)a.B * a.Hkv * a.N, a.accumulate,
             a.find_lowest ? (unsigned long long *)(base + ws.dec_lowest) : nullptr, a.evict_first, a.evict_tail);
         return hipGetLastError();
@@ -716,11 +711,13 @@ hipError_t launch_decode_steps(const ScoreArgs &a, const ScoreWorkspace &ws, cha
 
 template <int kG, int kD, int kVariant>
 hipError_t launch_decode_variant(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
-    switch (ws.dec_range / tokens_per_step(kD)) {
-        case 1: return launch_decode_steps<kG, kD, 1, kVariant>(a, ws, base, stream);
-        case 2: return launch_decode_steps<kG, kD, 2, kVariant>(a, ws, base, stream);
-        default: return launch_decode_steps<kG, kD, 4, kVariant>(a, ws, base, stream);
-    }
+    return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) {
+        switch (ws.dec_range / tokens_per_step(kD)) {
+            case 1: return launch_decode_steps<kG, kD, 1, kVariant>(a, lens, ws, base, stream);
+            case 2: return launch_decode_steps<kG, kD, 2, kVariant>(a, lens, ws, base, stream);
+            default: return launch_decode_steps<kG, kD, 4, kVariant>(a, lens, ws, base, stream);
+        }
+    });
 }
 
 template <int kG, int kD>
@@ -778,7 +775,8 @@ void decode_plan(int B, int N, int Hq, int Hkv, int d, ScoreWorkspace *ws, size_
     ws->dec_head = *off;   *off = align256(*off + records * sizeof(float4));
     ws->dec_vec = *off;    *off = align256(*off + records * 2 * d * sizeof(float));
     ws->dec_final = *off;  *off = align256(*off + (size_t)BH * ws->dec_rows * final_stride(d) * sizeof(float));
-    ws->dec_lowest = *off; *off = align256(*off + (size_t)BH * splits * sizeof(unsigned long long));
+    ws->dec_lowest = *off; *off = align256(*off + (size_t)BH * splits * kWaves * sizeof(unsigned long long));
+    ws->dec_lowest_per_head = splits * kWaves;
 }
 
 hipError_t launch_score_decode(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {

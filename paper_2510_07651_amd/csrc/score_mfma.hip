@@ -312,11 +312,11 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
 // With kNeedO every row keeps its candidate for a dominant key (see kCandMargin) out of its sums and
 // reports it with the partial record; the combine step then forms v_cand - o_i without
 // cancellation for every row, and no row ever needs a second pass.
-template <bool kNeedO>
+template <bool kNeedO, typename Lens>
 __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__restrict__ q,
                                                            const uint16_t *__restrict__ k,
                                                            const uint16_t *__restrict__ v, int N, int W, int Hq,
-                                                           int Hkv, int ragged, SeqLens lens, int split_len,
+                                                           int Hkv, int ragged, Lens lens, int split_len,
                                                            int n_splits, int m_pad, float *__restrict__ part_ml,
                                                            float *__restrict__ part_o) {
     __shared__ __attribute__((aligned(1024))) char smem[kLdsTiles];
@@ -510,8 +510,9 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
 // ------------------------------------------------------------------------------------
 // Variants that need no o_i (Eq. 4, Eq. 8 and its l1-weighted form): the splits' row sums are merged into the
 // one constant per row the second sweep turns logits into weights with.
+template <typename Lens>
 __global__ __launch_bounds__(128) void mfma_combine(const float *__restrict__ part_ml, int N, int W, int Hq, int Hkv,
-                                                    int ragged, SeqLens lens, int split_len, int n_splits,
+                                                    int ragged, Lens lens, int split_len, int n_splits,
                                                     int m_pad, uint16_t *__restrict__ out_bf16,
                                                     float *__restrict__ row_const, float *__restrict__ special) {
     const int row = blockIdx.x, bg = blockIdx.y;
@@ -566,10 +567,11 @@ __global__ __launch_bounds__(128) void mfma_combine(const float *__restrict__ pa
 // without cancellation however much of the row's attention the candidate holds.  A candidate that
 // holds a large share is scored here from these (`special`) and skipped by the second sweep.
 // Grid: x = group of four padded rows, y = (b, KV head); 32 lanes per row, four head_dim elements per lane.
+template <typename Lens>
 __global__ __launch_bounds__(128) void mfma_combine_hold(const uint16_t *__restrict__ v,
                                                          const float *__restrict__ part_ml,
                                                          const float *__restrict__ part_o, int N, int W, int Hq,
-                                                         int Hkv, int ragged, SeqLens lens, int split_len,
+                                                         int Hkv, int ragged, Lens lens, int split_len,
                                                          int n_splits, int m_pad, uint16_t *__restrict__ out_bf16,
                                                          float *__restrict__ row_const,
                                                          float *__restrict__ special) {
@@ -847,11 +849,11 @@ __device__ __forceinline__ void sweep2_step(Sweep2Regs &R, const char *smem, uin
 // kVariant: OBC_VALUE / OBC_KEY / OBC_JOINT / OBC_ALL / OBC_ATTN / OBC_VATP.  Grid: x = token range, y = chunk, z = (b, KV head).
 // With one chunk the scores go straight to `scores`; with several, each chunk writes its
 // own plane and mfma_sum_planes adds them in chunk order.
-template <int kVariant>
+template <int kVariant, typename Lens>
 __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__restrict__ q,
                                                            const uint16_t *__restrict__ k,
                                                            const uint16_t *__restrict__ v, int N, int W, int Hq,
-                                                           int Hkv, int ragged, SeqLens lens, int range_len, int m_pad,
+                                                           int Hkv, int ragged, Lens lens, int range_len, int m_pad,
                                                            const uint16_t *__restrict__ out_bf16,
                                                            const float *__restrict__ row_const,
                                                            const float *__restrict__ special,
@@ -1051,8 +1053,8 @@ __global__ __launch_bounds__(256) void mfma_sum_planes(const float *__restrict__
     scores[i] = accumulate ? scores[i] + s : s;        // the planes hold 0 beyond the true length
 }
 
-template <int kVariant>
-hipError_t launch_sweep2(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+template <int kVariant, typename Lens>
+hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
     constexpr int nv = kVariant == OBC_ALL ? 3 : 1;
     hipError_t e;      // (the kernels size their LDS statically: nothing to configure before a launch)
     const size_t plane_elems = (size_t)a.B * a.Hkv * a.N;
@@ -1063,7 +1065,7 @@ hipError_t launch_sweep2(const ScoreArgs &a, const ScoreWorkspace &ws, char *bas
         e = launch_sweep2_wide(a, ws, base, dst, plane_elems, chunk_stride, stream);
     } else {
         mfma_sweep2<kVariant><<<grid, dim3(kThreads), 0, stream>>>(
-            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens,
+            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens,
             ws.range_len, ws.m_pad, (const uint16_t *)(base + ws.out_bf16), (const float *)(base + ws.row_const),
             (const float *)(base + ws.special), dst, plane_elems, chunk_stride,
             ws.n_chunks == 1 ? a.accumulate : 0);
@@ -1110,7 +1112,8 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     if (ws->n_chunks > 1) *off = align_up(*off + (size_t)ws->n_chunks * nv * BH * N * sizeof(float), 256);
 }
 
-hipError_t launch_score_mfma(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+template <typename Lens>
+static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
     const bool need_o = a.variant == OBC_KEY || a.variant == OBC_JOINT || a.variant == OBC_ALL;
     float *part_ml = (float *)(base + ws.part_ml), *part_o = (float *)(base + ws.part_o);
     hipError_t e = hipSuccess;
@@ -1119,11 +1122,11 @@ hipError_t launch_score_mfma(const ScoreArgs &a, const ScoreWorkspace &ws, char 
         if (need_o)
             mfma_sweep1<true><<<grid, dim3(kThreads), 0, stream>>>(
                 (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged,
-                a.lens, ws.split_len, ws.splits, ws.m_pad, part_ml, part_o);
+                lens, ws.split_len, ws.splits, ws.m_pad, part_ml, part_o);
         else
             mfma_sweep1<false><<<grid, dim3(kThreads), 0, stream>>>(
                 (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged,
-                a.lens, ws.split_len, ws.splits, ws.m_pad, part_ml, part_o);
+                lens, ws.split_len, ws.splits, ws.m_pad, part_ml, part_o);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1131,25 +1134,29 @@ hipError_t launch_score_mfma(const ScoreArgs &a, const ScoreWorkspace &ws, char 
         const dim3 grid(ws.m_pad, a.B * a.Hkv);
         if (need_o)
             mfma_combine_hold<<<dim3(ws.m_pad / 4, a.B * a.Hkv), dim3(128), 0, stream>>>(      // (m_pad: a multiple of 32)
-                (const uint16_t *)a.v, part_ml, part_o, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, ws.split_len,
+                (const uint16_t *)a.v, part_ml, part_o, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len,
                 ws.splits, ws.m_pad, (uint16_t *)(base + ws.out_bf16), (float *)(base + ws.row_const),
                 (float *)(base + ws.special));
         else
             mfma_combine<<<grid, dim3(128), 0, stream>>>(
-                part_ml, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, ws.split_len, ws.splits, ws.m_pad,
+                part_ml, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.splits, ws.m_pad,
                 (uint16_t *)(base + ws.out_bf16), (float *)(base + ws.row_const), (float *)(base + ws.special));
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (!(a.stage_mask & OBC_STAGE_SWEEP2)) return hipSuccess;
     switch (a.variant) {
-        case OBC_VALUE: return launch_sweep2<OBC_VALUE>(a, ws, base, stream);
-        case OBC_KEY: return launch_sweep2<OBC_KEY>(a, ws, base, stream);
-        case OBC_JOINT: return launch_sweep2<OBC_JOINT>(a, ws, base, stream);
-        case OBC_ATTN: return launch_sweep2<OBC_ATTN>(a, ws, base, stream);
-        case OBC_VATP: return launch_sweep2<OBC_VATP>(a, ws, base, stream);
-        default: return launch_sweep2<OBC_ALL>(a, ws, base, stream);
+        case OBC_VALUE: return launch_sweep2<OBC_VALUE>(a, lens, ws, base, stream);
+        case OBC_KEY: return launch_sweep2<OBC_KEY>(a, lens, ws, base, stream);
+        case OBC_JOINT: return launch_sweep2<OBC_JOINT>(a, lens, ws, base, stream);
+        case OBC_ATTN: return launch_sweep2<OBC_ATTN>(a, lens, ws, base, stream);
+        case OBC_VATP: return launch_sweep2<OBC_VATP>(a, lens, ws, base, stream);
+        default: return launch_sweep2<OBC_ALL>(a, lens, ws, base, stream);
     }
+}
+
+hipError_t launch_score_mfma(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+    return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) { return launch_with(a, lens, ws, base, stream); });
 }
 
 }  // namespace obc

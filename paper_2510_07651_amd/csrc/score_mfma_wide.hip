@@ -354,11 +354,11 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
 }
 
 // kVariant: OBC_KEY / OBC_JOINT / OBC_ALL.  Grid: x = token range, y = 128-row chunk, z = (b, KV head).
-template <int kVariant>
+template <int kVariant, typename Lens>
 __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *__restrict__ q,
                                                                 const uint16_t *__restrict__ k,
                                                                 const uint16_t *__restrict__ v, int N, int W, int Hq,
-                                                                int Hkv, int ragged, SeqLens lens, int range_len, int m_pad,
+                                                                int Hkv, int ragged, Lens lens, int range_len, int m_pad,
                                                                 const uint16_t *__restrict__ out_bf16,
                                                                 const float *__restrict__ row_const,
                                                                 const float *__restrict__ special,
@@ -575,11 +575,13 @@ template <int kVariant>
 static hipError_t launch_wide(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, float *dst, size_t plane_elems,
                               size_t chunk_stride, hipStream_t stream) {
     const dim3 grid((a.N + ws.range_len - 1) / ws.range_len, ws.n_chunks, a.B * a.Hkv);
-    mfma_sweep2_wide<kVariant><<<grid, dim3(kThreads), 0, stream>>>(
-        (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens,
-        ws.range_len, ws.m_pad, (const uint16_t *)(base + ws.out_bf16), (const float *)(base + ws.row_const),
-        (const float *)(base + ws.special), dst, plane_elems, chunk_stride, ws.n_chunks == 1 ? a.accumulate : 0);
-    return hipGetLastError();
+    return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) {
+        mfma_sweep2_wide<kVariant><<<grid, dim3(kThreads), 0, stream>>>(
+            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens,
+            ws.range_len, ws.m_pad, (const uint16_t *)(base + ws.out_bf16), (const float *)(base + ws.row_const),
+            (const float *)(base + ws.special), dst, plane_elems, chunk_stride, ws.n_chunks == 1 ? a.accumulate : 0);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_sweep2_wide(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, float *dst, size_t plane_elems,

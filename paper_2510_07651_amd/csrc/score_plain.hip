@@ -183,9 +183,9 @@ __device__ __forceinline__ void tile_dots(const float *rows, const RowRegs<T, D>
 // ------------------------------------------------------------------------------------
 // Logits.  Grid: x = token range of the piece, y = chunk of 16 kRt rows, z = KV head.
 // ------------------------------------------------------------------------------------
-template <typename T, int D, int kRt>
+template <typename T, int D, int kRt, typename Lens>
 __global__ __launch_bounds__(kThreads, 4) void plain_logits(const T *__restrict__ q, const T *__restrict__ k, int N, int W,
-                                                            int Hq, int Hkv, int ragged, SeqLens lens, Piece w,
+                                                            int Hq, int Hkv, int ragged, Lens lens, Piece w,
                                                             int range_len, int n_ranges, float *__restrict__ z,
                                                             float2 *__restrict__ range_best) {
     constexpr int kRows = 16 * kRt;
@@ -261,9 +261,9 @@ __global__ __launch_bounds__(kThreads, 4) void plain_logits(const T *__restrict_
 // Weights.  Grid: x = split of the piece, y = chunk of 16 kRt rows, z = KV head.  Without kNeedO (Eq. 4, 8 and the
 // l1 form) only the sums are formed.
 // ------------------------------------------------------------------------------------
-template <typename T, int D, int kRt, bool kNeedO>
+template <typename T, int D, int kRt, bool kNeedO, typename Lens>
 __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict__ v, int N, int W, int Hq, int Hkv,
-                                                             int ragged, SeqLens lens, Piece w, int range_len, int n_ranges,
+                                                             int ragged, Lens lens, Piece w, int range_len, int n_ranges,
                                                              int split_len, int n_splits, const float *__restrict__ z,
                                                              const float2 *__restrict__ range_best,
                                                              RowRecord *__restrict__ records, float *__restrict__ part_l,
@@ -401,8 +401,8 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
 // ------------------------------------------------------------------------------------
 // Merge.  One wave per row, D / 64 elements per lane.  Grid: x = four rows of the piece, z = KV head.
 // ------------------------------------------------------------------------------------
-template <typename T, int D, bool kNeedO>
-__global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, SeqLens lens,
+template <typename T, int D, bool kNeedO, typename Lens>
+__global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
                                                         Piece w, int split_len, int n_splits,
                                                         const float *__restrict__ part_l, const float *__restrict__ part_o,
                                                         RowRecord *__restrict__ records, float *__restrict__ out) {
@@ -460,9 +460,9 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
 // Scores.  Grid: x = `n_tiles` tiles of 64 tokens of the piece, z = KV head.  `add`: on top of what `scores` holds (the
 // caller's running scores, or the rows of an earlier piece).
 // ------------------------------------------------------------------------------------
-template <typename T, int D, int kRt, int kVariant>
+template <typename T, int D, int kRt, int kVariant, typename Lens>
 __global__ __launch_bounds__(kThreads, 4) void plain_score(const T *__restrict__ v, int N, int Hkv,
-                                                           int ragged, SeqLens lens, Piece w, int n_tiles,
+                                                           int ragged, Lens lens, Piece w, int n_tiles,
                                                            const float *__restrict__ z,
                                                            const RowRecord *__restrict__ records,
                                                            const float *__restrict__ out, float *__restrict__ scores,
@@ -571,8 +571,8 @@ __global__ __launch_bounds__(kThreads, 4) void plain_score(const T *__restrict__
 // ------------------------------------------------------------------------------------
 // Host
 // ------------------------------------------------------------------------------------
-template <typename T, int D, int kRt>
-hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+template <typename T, int D, int kRt, typename Lens>
+hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
     const T *q = (const T *)a.q, *k = (const T *)a.k, *v = (const T *)a.v;
     float *z = (float *)(base + ws.pl_z), *part_l = (float *)(base + ws.pl_part_l), *part_o = (float *)(base + ws.pl_part_o);
     float *out = (float *)(base + ws.pl_out);
@@ -598,7 +598,7 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
             auto segment = [&](int i) { w.s0 = i * ws.pl_seg; w.s1 = std::min(w.s0 + ws.pl_seg, a.N); };
             auto logits = [&]() {
                 plain_logits<T, D, kFewRt><<<dim3((w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range, (w.nr + 16 * kFewRt - 1) / (16 * kFewRt), heads), dim3(kThreads), 0, stream>>>(
-                    q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, ws.pl_range, ws.pl_ranges, z, best);
+                    q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 e = hipGetLastError();
                 return e == hipSuccess;
             };
@@ -613,11 +613,11 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
                     const dim3 grid((w.s1 - w.s0 + ws.pl_split - 1) / ws.pl_split, chunks, heads);
                     if (need_o)
                         plain_weights<T, D, kRt, true><<<grid, dim3(kThreads), 0, stream>>>(
-                            v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
+                            v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
                             best, rec, part_l, part_o);
                     else
                         plain_weights<T, D, kRt, false><<<grid, dim3(kThreads), 0, stream>>>(
-                            v, a.N, a.W, a.Hq, a.Hkv, a.ragged, a.lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
+                            v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
                             best, rec, part_l, part_o);
                     if ((e = hipGetLastError()) != hipSuccess) return e;
                 }
@@ -625,10 +625,10 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
             if (mask & OBC_STAGE_COMBINE) {
                 const dim3 grid((w.nr + 3) / 4, 1, heads);
                 if (need_o)
-                    plain_merge<T, D, true><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, a.lens, w, ws.pl_split,
+                    plain_merge<T, D, true><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split,
                                                                                  ws.pl_splits, part_l, part_o, rec, out);
                 else
-                    plain_merge<T, D, false><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, a.lens, w, ws.pl_split,
+                    plain_merge<T, D, false><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split,
                                                                                   ws.pl_splits, part_l, part_o, rec, out);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
@@ -640,7 +640,7 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
                 const dim3 grid((tiles + n_tiles - 1) / n_tiles, 1, heads);
                 const int add = a.accumulate || r0 > 0;
 #define OBC_PLAIN_SCORE(variant)                                                                                       \
-    plain_score<T, D, kFewRt, variant><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, a.lens, w, n_tiles, z, rec, \
+    plain_score<T, D, kFewRt, variant><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, \
                                                                          out, a.scores, variant_stride, add)
                 switch (a.variant) {
                     case OBC_VALUE: OBC_PLAIN_SCORE(OBC_VALUE); break;
@@ -655,6 +655,11 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
             }
         }
     return hipSuccess;
+}
+
+template <typename T, int D, int kRt>
+hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+    return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) { return run_with<T, D, kRt>(a, lens, ws, base, stream); });
 }
 
 template <typename T, int D>

@@ -367,9 +367,9 @@ __device__ __forceinline__ void load_batch(uint32_t (&keys)[kRegChunks][kItems],
 // kResident: the head has at most kRegChunks * 4096 tokens; its keys are loaded once and
 // live in registers.  Otherwise every pass streams the head in batches of kRegChunks
 // chunks (all loads of a batch are issued before any is used).
-template <int kRegChunks, bool kResident>
+template <int kRegChunks, bool kResident, typename Lens>
 __global__ __launch_bounds__(kSelThreads) void select_topk(const float *__restrict__ scores, int N, int budget,
-                                                           int Hkv, int ragged, SeqLens lens, int first, int tail,
+                                                           int Hkv, int ragged, Lens lens, int first, int tail,
                                                            int radius, int keys_in, int32_t *__restrict__ keep_idx) {
     __shared__ SelectShared sh;
     const int bg = blockIdx.x;
@@ -479,9 +479,9 @@ __device__ __forceinline__ void sum_slice_histograms(SelectShared &sh, const int
     sh.hist[2 * tid + 1] = hi;
 }
 
-template <int kStage>
+template <int kStage, typename Lens>
 __global__ __launch_bounds__(kSelThreads) void select_sliced(const float *__restrict__ scores, int N, int budget,
-                                                             int Hkv, int ragged, SeqLens lens, int first, int tail,
+                                                             int Hkv, int ragged, Lens lens, int first, int tail,
                                                              int radius, int keys_in, int n_slices, int *__restrict__ hist_a,
                                                              int *__restrict__ hist_b, SliceState *__restrict__ state,
                                                              int *__restrict__ counts,
@@ -594,8 +594,9 @@ __global__ __launch_bounds__(kSelThreads) void select_sliced(const float *__rest
 //   select          top Hkv * budget of the Hkv * N keys: ascending flat positions
 //   adaptive_split  flat positions -> per-head index lists and counts
 // ------------------------------------------------------------------------------------
+template <typename Lens>
 __global__ __launch_bounds__(256) void adaptive_keys(const float *__restrict__ scores, int N, int Hkv, int ragged,
-                                                     SeqLens lens, size_t total, uint32_t *__restrict__ keys) {
+                                                     Lens lens, size_t total, uint32_t *__restrict__ keys) {
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= total) return;
     const int p = (int)(t % N);
@@ -663,8 +664,11 @@ hipError_t launch_select_adaptive(const float *scores, int budget, int n_safe, i
     if (select_prefers_slices(B, Hkv, N)) { ws_head = base; ws_head_bytes = select_workspace_bytes(B, Hkv, N); }
     hipError_t e;
     const size_t total = BH * N;
-    adaptive_keys<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream>>>(scores, N, Hkv, ragged, lens, total, keys);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    e = with_lens(ragged, B, lens, [&](const auto &few) {
+        adaptive_keys<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream>>>(scores, N, Hkv, ragged, few, total, keys);
+        return hipGetLastError();
+    });
+    if (e != hipSuccess) return e;
     if (n_safe > 0) {
         e = launch_select(scores, n_safe, safe_idx, B, Hkv, N, ragged, lens, 0, 0, 0, ws_head, ws_head_bytes, stream, 0);
         if (e != hipSuccess) return e;
@@ -708,14 +712,16 @@ hipError_t launch_select_sliced(const float *scores, int budget, int32_t *keep_i
     SliceState *state = (SliceState *)base;         base += up(4 * BH * sizeof(SliceState));
     int *counts = (int *)base;
     const dim3 grid(n_slices, (unsigned)BH), block(kSelThreads);
-#define OBC_SLICED_ARGS scores, N, budget, Hkv, ragged, lens, first, tail, radius, keys_in, n_slices, hist_a, hist_b, state, counts, keep_idx
-    select_sliced<0><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-    select_sliced<1><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-    select_sliced<2><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-    select_sliced<3><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-    select_sliced<4><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
+    return with_lens(ragged, B, lens, [&](const auto &few) {
+#define OBC_SLICED_ARGS scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, n_slices, hist_a, hist_b, state, counts, keep_idx
+        select_sliced<0><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
+        select_sliced<1><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
+        select_sliced<2><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
+        select_sliced<3><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
+        select_sliced<4><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
 #undef OBC_SLICED_ARGS
-    return hipGetLastError();
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_select(const float *scores, int budget, int32_t *keep_idx, int B, int Hkv, int N, int ragged,
@@ -725,17 +731,19 @@ hipError_t launch_select(const float *scores, int budget, int32_t *keep_idx, int
         return launch_select_sliced(scores, budget, keep_idx, B, Hkv, N, ragged, lens, first, tail, radius, keys_in,
                                     workspace, stream);
     const dim3 grid(B * Hkv), block(kSelThreads);
-    if (N <= kChunk)             // (short heads: fewer unrolled chunk bodies to step through)
-        select_topk<1, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, lens, first, tail, radius, keys_in, keep_idx);
-    else if (N <= 2 * kChunk)
-        select_topk<2, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, lens, first, tail, radius, keys_in, keep_idx);
-    else if (N <= 8 * kChunk)
-        select_topk<8, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, lens, first, tail, radius, keys_in, keep_idx);
-    else if (N <= 16 * kChunk)
-        select_topk<16, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, lens, first, tail, radius, keys_in, keep_idx);
-    else
-        select_topk<8, false><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, lens, first, tail, radius, keys_in, keep_idx);
-    return hipGetLastError();
+    return with_lens(ragged, B, lens, [&](const auto &few) {
+        if (N <= kChunk)             // (short heads: fewer unrolled chunk bodies to step through)
+            select_topk<1, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+        else if (N <= 2 * kChunk)
+            select_topk<2, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+        else if (N <= 8 * kChunk)
+            select_topk<8, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+        else if (N <= 16 * kChunk)
+            select_topk<16, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+        else
+            select_topk<8, false><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace obc

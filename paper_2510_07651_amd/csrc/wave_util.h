@@ -16,6 +16,10 @@ __device__ __forceinline__ uint32_t dpp_pair(uint32_t x) {
 }
 template <int kCtrl>
 __device__ __forceinline__ float dpp_pair(float x) { return __uint_as_float(dpp_pair<kCtrl>(__float_as_uint(x))); }
+template <int kCtrl>
+__device__ __forceinline__ unsigned long long dpp_pair(unsigned long long x) {
+    return ((unsigned long long)dpp_pair<kCtrl>((uint32_t)(x >> 32)) << 32) | dpp_pair<kCtrl>((uint32_t)x);
+}
 
 // The values of the two lanes that differ in bit 4 (16) or 5 (32) of their index, lower one first.
 template <int kBit>
@@ -31,10 +35,21 @@ __device__ __forceinline__ void both_of_pair(float x, float &lower, float &upper
     lower = __uint_as_float(a);
     upper = __uint_as_float(b);
 }
+template <int kBit>
+__device__ __forceinline__ void both_of_pair(unsigned long long x, unsigned long long &lower, unsigned long long &upper) {
+    uint32_t lh, uh, ll, ul;
+    both_of_pair<kBit>((uint32_t)(x >> 32), lh, uh);
+    both_of_pair<kBit>((uint32_t)x, ll, ul);
+    lower = ((unsigned long long)lh << 32) | ll;
+    upper = ((unsigned long long)uh << 32) | ul;
+}
 
+__device__ __forceinline__ unsigned long long min64(unsigned long long a, unsigned long long b) { return a < b ? a : b; }
 struct SumOp { template <typename T> __device__ __forceinline__ T operator()(T a, T b) const { return a + b; } };
 struct MaxOp { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 struct MinOp { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; } };
+
+struct Min64Op { __device__ __forceinline__ unsigned long long operator()(unsigned long long a, unsigned long long b) const { return min64(a, b); } };
 
 // Over each row of 16 lanes.
 template <typename Op, typename T>
