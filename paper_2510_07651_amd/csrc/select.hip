@@ -1,13 +1,17 @@
 // Per-head top-`budget` selection (Section 3 "Cache Eviction"; Appendix E, Algorithm 2:
 // topk followed by an ascending sort of the kept indices).
 //
-// One workgroup per (sequence, KV head).  The budget-th largest score is found by a
-// most-significant-digit-first radix select over order-preserving 32-bit keys (digits of
-// 11, 11 and 10 bits; histograms are integer LDS atomics, and after the first pass only
-// the keys inside the selected digit class take part).  A final ordered sweep emits, in index
-// order, every token above the threshold plus the first tokens equal to it until the
+// The budget-th largest score of a head is found by a most-significant-digit-first radix
+// select over order-preserving 32-bit keys: a histogram of the leading digit over all keys picks
+// the digit class that holds the threshold, the class's keys (a percent or so of the head) are
+// collected into a list, and two more digits over the list fix the threshold.  A final ordered
+// sweep emits, in index order, every token above it plus the first tokens equal to it until the
 // budget is filled -- which is both the lowest-index tie-break and the ascending output
 // order.  Integer-only bookkeeping: results are exact and reproducible.
+//
+// Heads of up to 32768 tokens: one workgroup per head (select_topk).  Longer heads, given a
+// workspace, and the ranking of all heads of a layer together (head-adaptive budgets): slices of
+// a head on separate workgroups, in three short kernels (slices_*).
 //
 // Protected regions (Appendix E, Algorithm 2: only positions below the cutoff compete and the
 // recent tail is always kept; Appendix C: leading attention-sink tokens are always kept):
@@ -21,11 +25,12 @@
 // outside the competing range counting as zero.  The sum orders tokens as the average does
 // and needs no division.
 //
-// Heads of up to 65536 tokens are read from memory once (128-bit loads) and their keys
-// stay in registers for all passes; longer heads are streamed again in every pass.
-#include <cstring>
+// select_topk reads heads of up to 65536 tokens from memory once (128-bit loads) and keeps their
+// keys in registers; longer heads without a workspace are streamed again in every pass.
+#include <type_traits>
 
 #include "internal.h"
+#include "wave_util.h"
 
 namespace obc {
 namespace {
@@ -46,25 +51,45 @@ __device__ __forceinline__ uint32_t order_key(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-constexpr int kBins = 2048;
 constexpr int kMaxRadius = 7;                           // largest pooling window: 15 scores
 
 constexpr int kMaxRegChunks = 16;                       // chunks a block can keep in registers (64K scores)
+constexpr int kList = 4096;                             // keys of the threshold's class that fit the LDS list
 
-struct SelectShared {
-    int hist[kBins];
+// Digits, from the top.  Scores crowd into a few binades, and LDS atomics of a wave to one counter take turns: a block
+// that sees 32 keys per thread spreads its first digit over 13 bits (counting and picking it: 5.0 -> 3.4 us at 32K), where few keys per thread
+// would not pay for the larger table.
+template <int kFirstBits>
+struct Digits {
+    static constexpr int kBits0 = kFirstBits, kBits1 = kFirstBits == 13 ? 10 : 11, kBits2 = 32 - kBits0 - kBits1;
+    static constexpr int kShift0 = 32 - kBits0, kShift1 = kBits2;
+    static constexpr int kBins0 = 1 << kBits0, kBins1 = 1 << kBits1, kBins2 = 1 << kBits2;
+};
+constexpr int kSliceBits = 11;                          // first digit of the sliced kernels
+constexpr int kSliceBins = 1 << kSliceBits;
+
+struct PickShared {
     int wave_tot[kSelWaves];
-    uint32_t sel_digit;
-    int sel_remaining;
+    uint32_t digit;
+    int remaining, in_digit;
+};
+
+template <int kFirstBits>
+struct SelectShared {
+    using D = Digits<kFirstBits>;
+    int hist0[D::kBins0], hist1[D::kBins1], hist2[D::kBins2];
+    uint32_t list[kList];
+    int n_list;
+    PickShared pick;
     // ordered emission of a register-resident head: per (chunk, wave) the packed counts, then the
     // numbers of greater / equal keys that come before that (chunk, wave)
     int cw_tot[kMaxRegChunks * kSelWaves];
     int cw_gt[kMaxRegChunks * kSelWaves], cw_eq[kMaxRegChunks * kSelWaves];
 };
 
-__device__ __forceinline__ void histogram_add(int *hist, uint32_t digit, bool active) {
-    if (__ballot(active) == 0ull) return;              // uniform: nothing of this wave is in the class
-    if (active) atomicAdd(&hist[digit], 1);
+template <int kCount>
+__device__ __forceinline__ void clear_counters(int *h) {     // (kCount: a multiple of 4)
+    for (int i = threadIdx.x * 4; i < kCount; i += kSelThreads * 4) *(int4 *)(h + i) = make_int4(0, 0, 0, 0);
 }
 
 // Inclusive scan of one int per lane over the wave, register to register: four data-parallel-primitive steps inside
@@ -88,38 +113,63 @@ __device__ __forceinline__ int wave_scan(int x, int lane) {
     return x;
 }
 
-// After a histogram pass over `bins` bins: which digit holds the element of rank `remaining`
-// (from the top), and that element's rank inside the digit.  All threads get the same answer.
-__device__ __forceinline__ void pick_digit(SelectShared &sh, int remaining, uint32_t *digit, int *new_remaining) {
+// Which digit of a histogram of kBins counters holds the element of rank `remaining` (from the top), that element's rank
+// inside the digit, and how many elements the digit has.  All threads get the same answer.  Call when the histogram is
+// complete but before a barrier; the shared results are not written again before the barrier of the next call.
+template <int kBins>
+__device__ __forceinline__ void pick_digit(const int *hist, PickShared &sh, uint32_t *digit, int *remaining, int *in_digit) {
+    constexpr int kOwn = kBins >= kSelThreads ? kBins / kSelThreads : 1;       // consecutive counters of a thread
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __syncthreads();
-    // thread t owns digits 2t (lo) and 2t+1 (hi); suffix sums over threads t' > t
-    const int lo = sh.hist[2 * tid], hi = sh.hist[2 * tid + 1];
-    const int mine = lo + hi;
+    int c[kOwn], mine = 0;
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        c[i] = tid * kOwn < kBins ? hist[tid * kOwn + i] : 0;
+        mine += c[i];
+    }
     const int incl = wave_scan<true>(mine, lane);          // inclusive suffix scan inside the wave (towards higher lanes)
     if (lane == 0) sh.wave_tot[wave] = incl;
     __syncthreads();
-    int above = incl - mine;            // elements in digits of higher threads
+    int above = incl - mine;                               // elements in digits of higher threads
 #pragma unroll
     for (int w = 0; w < kSelWaves; ++w)
         if (w > wave) above += sh.wave_tot[w];
-    if (above < remaining && remaining <= above + mine) {        // exactly one thread satisfies this
-        if (remaining <= above + hi) {
-            sh.sel_digit = 2u * tid + 1u;
-            sh.sel_remaining = remaining - above;
-        } else {
-            sh.sel_digit = 2u * tid;
-            sh.sel_remaining = remaining - above - hi;
+    if (above < *remaining && *remaining <= above + mine) {      // exactly one thread satisfies this
+#pragma unroll
+        for (int i = kOwn - 1; i >= 0; --i) {
+            if (above < *remaining && *remaining <= above + c[i]) {
+                sh.digit = (uint32_t)(tid * kOwn + i);
+                sh.remaining = *remaining - above;
+                sh.in_digit = c[i];
+            }
+            above += c[i];
         }
     }
     __syncthreads();
-    *digit = sh.sel_digit;
-    *new_remaining = sh.sel_remaining;
-    __syncthreads();
+    *digit = sh.digit;
+    *remaining = sh.remaining;
+    *in_digit = sh.in_digit;
+}
+
+// The threshold inside a digit class from the class's keys.  `visit(f)` calls f(key) for this thread's share of them;
+// the two histograms are cleared.  `prefix`: the class's digit in place.  Leaves the threshold in `prefix`, how many keys
+// equal to it are kept in `remaining`, how many there are in `n_equal`.
+template <typename D, typename Visit>
+__device__ __forceinline__ void finish_class(int *hist1, int *hist2, PickShared &sh, Visit &&visit, uint32_t *prefix, int *remaining,
+                                             int *n_equal) {
+    uint32_t digit;
+    visit([&](uint32_t key) { atomicAdd(&hist1[(key >> D::kShift1) & (D::kBins1 - 1)], 1); });
+    pick_digit<D::kBins1>(hist1, sh, &digit, remaining, n_equal);
+    const uint32_t middle = digit;
+    visit([&](uint32_t key) {
+        if (((key >> D::kShift1) & (D::kBins1 - 1)) == middle) atomicAdd(&hist2[key & (D::kBins2 - 1)], 1);
+    });
+    pick_digit<D::kBins2>(hist2, sh, &digit, remaining, n_equal);
+    *prefix |= (middle << D::kShift1) | digit;
 }
 
 // Ordered emission of one chunk: position = #greater before + min(#equal before, need_eq).
-__device__ __forceinline__ void emit_chunk(SelectShared &sh, const uint32_t (&key)[kItems], int i0, int len,
+__device__ __forceinline__ void emit_chunk(int *wave_tot, const uint32_t (&key)[kItems], int i0, int len,
                                            uint32_t thr, int need_eq, int budget, int &gt_base, int &eq_base,
                                            int32_t *out) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -132,12 +182,12 @@ __device__ __forceinline__ void emit_chunk(SelectShared &sh, const uint32_t (&ke
         packed += (gt[e] ? 0x10000 : 0) + (eq[e] ? 1 : 0);
     }
     const int incl = wave_scan<false>(packed, lane);       // inclusive scan inside the wave
-    if (lane == 63) sh.wave_tot[wave] = incl;
+    if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
     int before = incl - packed, total = 0;
 #pragma unroll
     for (int w = 0; w < kSelWaves; ++w) {
-        const int t = sh.wave_tot[w];
+        const int t = wave_tot[w];
         if (w < wave) before += t;
         total += t;
     }
@@ -159,8 +209,8 @@ __device__ __forceinline__ void emit_chunk(SelectShared &sh, const uint32_t (&ke
 // Ordered emission of a head whose keys all sit in registers: the same positions as emit_chunk chunk after
 // chunk, with three barriers in all.  Every wave scans its 256 keys of every chunk; the first wave then
 // scans the (chunk, wave) totals in emission order; every thread places its keys.
-template <int kRegChunks>
-__device__ __forceinline__ void emit_resident(SelectShared &sh, const uint32_t (&keys)[kRegChunks][kItems], int n_chunks,
+template <int kRegChunks, typename Shared>
+__device__ __forceinline__ void emit_resident(Shared &sh, const uint32_t (&keys)[kRegChunks][kItems], int n_chunks,
                                               int len, uint32_t thr, int need_eq, int budget, int32_t *out) {
     static_assert(kRegChunks <= kMaxRegChunks, "cw_tot is sized for kMaxRegChunks chunks");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -227,23 +277,27 @@ __device__ __forceinline__ void emit_resident(SelectShared &sh, const uint32_t (
 }
 
 // The same when every key equal to the threshold is kept (no tie is cut: the usual case): a key is kept iff it is
-// >= the threshold, so one comparison and one count per key do.
-template <int kRegChunks>
-__device__ __forceinline__ void emit_resident_uncut(SelectShared &sh, const uint32_t (&keys)[kRegChunks][kItems],
+// >= the threshold.  A thread keeps at most 4 keys per chunk and a wave 256, so one wave scan carries three chunks.
+template <int kRegChunks, typename Shared>
+__device__ __forceinline__ void emit_resident_uncut(Shared &sh, const uint32_t (&keys)[kRegChunks][kItems],
                                                     int n_chunks, uint32_t thr, int budget, int32_t *out) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int before[kRegChunks];                     // kept keys of the wave's lower lanes in chunk c
+    constexpr int kPacks = (kRegChunks + 2) / 3;
+    int before[kPacks];                         // kept keys of the wave's lower lanes, 10 bits per chunk
 #pragma unroll
-    for (int c = 0; c < kRegChunks; ++c) {
-        int lower = 0, in_wave = 0;
+    for (int g = 0; g < kPacks; ++g) {
+        int mine = 0;
 #pragma unroll
-        for (int e = 0; e < kItems; ++e) {
-            const unsigned long long m = __ballot(keys[c][e] >= thr);
-            lower += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-            in_wave += __popcll(m);
+        for (int c = 3 * g; c < 3 * g + 3 && c < kRegChunks; ++c)
+#pragma unroll
+            for (int e = 0; e < kItems; ++e) mine += keys[c][e] >= thr ? 1 << (10 * (c - 3 * g)) : 0;
+        const int incl = wave_scan<false>(mine, lane);
+        before[g] = incl - mine;
+        if (lane == 63) {
+#pragma unroll
+            for (int c = 3 * g; c < 3 * g + 3 && c < kRegChunks; ++c)
+                sh.cw_tot[c * kSelWaves + wave] = (incl >> (10 * (c - 3 * g))) & 1023;
         }
-        if (lane == 0) sh.cw_tot[c * kSelWaves + wave] = in_wave;
-        before[c] = lower;
     }
     __syncthreads();
     if (wave == 0) {
@@ -271,13 +325,32 @@ __device__ __forceinline__ void emit_resident_uncut(SelectShared &sh, const uint
     for (int c = 0; c < kRegChunks; ++c) {
         if (c >= n_chunks) continue;                // uniform
         const int i0 = c * kChunk + tid * kItems;
-        int pos = sh.cw_gt[c * kSelWaves + wave] + before[c];
+        int pos = sh.cw_gt[c * kSelWaves + wave] + ((before[c / 3] >> (10 * (c % 3))) & 1023);
 #pragma unroll
         for (int e = 0; e < kItems; ++e) {
             const bool keep = keys[c][e] >= thr_again;
             if (keep && pos < budget) out[pos] = i0 + e;      // (pos < budget always holds; it guards the store)
             pos += keep ? 1 : 0;
         }
+    }
+}
+
+// Sum over the 2R+1 scores around each of four consecutive positions, in ascending position order, from aligned loads.
+template <int R>
+__device__ __forceinline__ void pooled_four(const float *__restrict__ s, int i0, uint32_t (&keys)[kItems]) {
+    constexpr int kSide = (R + kItems - 1) / kItems;          // groups of four on either side
+    float w[(2 * kSide + 1) * kItems];
+#pragma unroll
+    for (int g = 0; g < 2 * kSide + 1; ++g) {
+        const float4 f = *(const float4 *)(s + i0 + (g - kSide) * kItems);
+        w[g * kItems] = f.x; w[g * kItems + 1] = f.y; w[g * kItems + 2] = f.z; w[g * kItems + 3] = f.w;
+    }
+#pragma unroll
+    for (int e = 0; e < kItems; ++e) {
+        float sum = w[kSide * kItems + e - R];
+#pragma unroll
+        for (int j = 1; j <= 2 * R; ++j) sum = __fadd_rn(sum, w[kSide * kItems + e - R + j]);
+        keys[e] = order_key(sum);
     }
 }
 
@@ -327,7 +400,17 @@ __device__ __forceinline__ void load_batch(uint32_t (&keys)[kRegChunks][kItems],
     for (int c = 0; c < kRegChunks; ++c) {
         if (c0 + c < n_chunks) {                          // uniform
             const int i0 = (c0 + c) * kChunk + (int)threadIdx.x * kItems;
-            if (radius > 0) {                             // uniform: pooled ranking
+            if (radius > 0 && vec_ok && i0 - 2 * kItems >= first && i0 + 3 * kItems <= cutoff) {     // pooled, away from every edge
+                switch (radius) {                         // uniform
+                    case 1: pooled_four<1>(s, i0, keys[c]); break;
+                    case 2: pooled_four<2>(s, i0, keys[c]); break;
+                    case 3: pooled_four<3>(s, i0, keys[c]); break;
+                    case 4: pooled_four<4>(s, i0, keys[c]); break;
+                    case 5: pooled_four<5>(s, i0, keys[c]); break;
+                    case 6: pooled_four<6>(s, i0, keys[c]); break;
+                    default: pooled_four<7>(s, i0, keys[c]); break;
+                }
+            } else if (radius > 0) {                      // uniform: pooled ranking
                 float w[kItems + 2 * kMaxRadius];
 #pragma unroll
                 for (int j = 0; j < kItems + 2 * kMaxRadius; ++j) {
@@ -345,6 +428,10 @@ __device__ __forceinline__ void load_batch(uint32_t (&keys)[kRegChunks][kItems],
                 }
             } else if (keys_in) {                         // uniform: the input already holds order-preserving keys
                 const uint32_t *kin = (const uint32_t *)s;
+                if (vec_ok && i0 + kItems <= len) {
+                    const uint4 u = *(const uint4 *)(kin + i0);
+                    keys[c][0] = u.x; keys[c][1] = u.y; keys[c][2] = u.z; keys[c][3] = u.w;
+                } else
 #pragma unroll
                 for (int e = 0; e < kItems; ++e) keys[c][e] = i0 + e < len ? kin[i0 + e] : 0u;
             } else if (vec_ok && i0 + kItems <= len) {
@@ -355,7 +442,7 @@ __device__ __forceinline__ void load_batch(uint32_t (&keys)[kRegChunks][kItems],
 #pragma unroll
                 for (int e = 0; e < kItems; ++e) keys[c][e] = i0 + e < len ? order_key(s[i0 + e]) : 0u;
             }
-            if (i0 < first || i0 + kItems > cutoff) {     // some of these tokens are protected
+            if (!keys_in && (i0 < first || i0 + kItems > cutoff)) {     // some of these tokens are protected
 #pragma unroll
                 for (int e = 0; e < kItems; ++e)
                     if (i0 + e < first || (i0 + e >= cutoff && i0 + e < len)) keys[c][e] = 0xffffffffu;
@@ -370,378 +457,592 @@ __device__ __forceinline__ void load_batch(uint32_t (&keys)[kRegChunks][kItems],
 template <int kRegChunks, bool kResident, typename Lens>
 __global__ __launch_bounds__(kSelThreads) void select_topk(const float *__restrict__ scores, int N, int budget,
                                                            int Hkv, int ragged, Lens lens, int first, int tail,
-                                                           int radius, int keys_in, int32_t *__restrict__ keep_idx) {
-    __shared__ SelectShared sh;
+                                                           int radius, int32_t *__restrict__ keep_idx) {
+    constexpr int kFirstBits = kRegChunks >= 8 ? 13 : 11;
+    using D = Digits<kFirstBits>;
+    __shared__ __attribute__((aligned(16))) SelectShared<kFirstBits> sh;
     const int bg = blockIdx.x;
     const int len = seq_len_of(lens, ragged, bg / Hkv, N);
     const int cutoff = len - tail;                        // tokens at or beyond it are always kept
     const float *s = scores + (size_t)bg * N;
     int32_t *out = keep_idx + (size_t)bg * budget;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int n_chunks = (len + kChunk - 1) / kChunk;
     const bool vec_ok = ((size_t)s & 15) == 0;            // the head starts on a 16-byte boundary
 
+    clear_counters<D::kBins0>(sh.hist0);
+    clear_counters<D::kBins1>(sh.hist1);
+    clear_counters<D::kBins2>(sh.hist2);
+    if (tid == 0) sh.n_list = 0;
     uint32_t keys[kRegChunks][kItems];
 #pragma unroll
     for (int c = 0; c < kRegChunks; ++c)
 #pragma unroll
         for (int e = 0; e < kItems; ++e) keys[c][e] = 0u;
-    if (kResident) load_batch<kRegChunks>(keys, s, 0, n_chunks, len, vec_ok, first, cutoff, radius, keys_in != 0);
+    if (kResident) load_batch<kRegChunks>(keys, s, 0, n_chunks, len, vec_ok, first, cutoff, radius);
+    __syncthreads();
 
-    // ---- radix select: key of the budget-th largest element ----
-    uint32_t prefix = 0, mask = 0;
-    int remaining = budget;             // rank (1-based, from the top) still to resolve inside the prefix class
-    for (int pass = 0; pass < 3; ++pass) {
-        const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
-        const uint32_t dmask = pass == 2 ? 1023u : 2047u;
-        sh.hist[2 * tid] = 0;
-        sh.hist[2 * tid + 1] = 0;
-        __syncthreads();
-        if constexpr (kResident) {
-            // (positions past the length hold key 0: they land in the lowest class and are never reached)
+    // f(key) for this thread's keys; positions past the length hold key 0: they land in the lowest class and never
+    // reach the threshold.
+    auto visit_all = [&](auto &&f) {
+        for (int c0 = 0; c0 < (kResident ? 1 : n_chunks); c0 += kRegChunks) {
+            if (!kResident) load_batch<kRegChunks>(keys, s, c0, n_chunks, len, vec_ok, first, cutoff, radius);
 #pragma unroll
             for (int c = 0; c < kRegChunks; ++c) {
-                if (c < n_chunks) {                       // uniform
+                if (c0 + c < n_chunks) {                  // uniform
 #pragma unroll
-                    for (int e = 0; e < kItems; ++e)
-                        if ((keys[c][e] & mask) == prefix) atomicAdd(&sh.hist[(keys[c][e] >> shift) & dmask], 1);
-                }
-            }
-        } else {
-            for (int c0 = 0; c0 < n_chunks; c0 += kRegChunks) {
-                load_batch<kRegChunks>(keys, s, c0, n_chunks, len, vec_ok, first, cutoff, radius, keys_in != 0);
-#pragma unroll
-                for (int c = 0; c < kRegChunks; ++c) {
-                    if (c0 + c < n_chunks) {              // uniform
-#pragma unroll
-                        for (int e = 0; e < kItems; ++e) {
-                            const bool in = (c0 + c) * kChunk + tid * kItems + e < len;
-                            histogram_add(sh.hist, (keys[c][e] >> shift) & dmask, in && ((keys[c][e] & mask) == prefix));
-                        }
-                    }
+                    for (int e = 0; e < kItems; ++e) f(keys[c][e]);
                 }
             }
         }
-        uint32_t digit;
-        pick_digit(sh, remaining, &digit, &remaining);
-        prefix |= digit << shift;
-        mask |= dmask << shift;
+    };
+    visit_all([&](uint32_t key) { atomicAdd(&sh.hist0[key >> D::kShift0], 1); });
+    uint32_t digit;
+    int remaining = budget, n_equal;    // rank (1-based, from the top) still to resolve inside the class
+    pick_digit<D::kBins0>(sh.hist0, sh.pick, &digit, &remaining, &n_equal);
+    uint32_t thr = digit << D::kShift0;
+    const uint32_t first_digit = digit;
+    if (n_equal <= kList) {
+        // The class's keys into the list, in any order: one place per wave and its lanes' counts before it.
+        int mine = 0;
+        visit_all([&](uint32_t key) { mine += (key >> D::kShift0) == first_digit ? 1 : 0; });
+        const int incl = wave_scan<false>(mine, lane);
+        int base = 0;
+        if (lane == 63 && incl > 0) base = atomicAdd(&sh.n_list, incl);
+        int at = __builtin_amdgcn_readlane(base, 63) + incl - mine;
+        visit_all([&](uint32_t key) {
+            if ((key >> D::kShift0) == first_digit) sh.list[at++] = key;
+        });
+        __syncthreads();
+        const int n_list = n_equal;
+        finish_class<D>(sh.hist1, sh.hist2, sh.pick, [&](auto &&f) {
+            for (int j = tid; j < n_list; j += kSelThreads) f(sh.list[j]);
+        }, &thr, &remaining, &n_equal);
+    } else {
+        finish_class<D>(sh.hist1, sh.hist2, sh.pick, [&](auto &&f) {
+            visit_all([&](uint32_t key) { if ((key >> D::kShift0) == first_digit) f(key); });
+        }, &thr, &remaining, &n_equal);
     }
-    const uint32_t thr = prefix;        // key of the budget-th largest score
-    const int need_eq = remaining;      // how many tokens equal to it are kept (lowest indices first)
+    const int need_eq = remaining;      // how many tokens equal to the threshold are kept (lowest indices first)
 
     // ---- ordered sweep ----
-    int gt_base = 0, eq_base = 0;
     if constexpr (kResident) {
-        // (the last pass's counters are still in place: the threshold's own counter is the number of keys equal to it)
-        if (need_eq == sh.hist[thr & 1023u]) emit_resident_uncut<kRegChunks>(sh, keys, n_chunks, thr, budget, out);
+        if (need_eq == n_equal) emit_resident_uncut<kRegChunks>(sh, keys, n_chunks, thr, budget, out);
         else emit_resident<kRegChunks>(sh, keys, n_chunks, len, thr, need_eq, budget, out);
     } else {
+        int gt_base = 0, eq_base = 0;
         for (int c0 = 0; c0 < n_chunks; c0 += kRegChunks) {
-            load_batch<kRegChunks>(keys, s, c0, n_chunks, len, vec_ok, first, cutoff, radius, keys_in != 0);
+            load_batch<kRegChunks>(keys, s, c0, n_chunks, len, vec_ok, first, cutoff, radius);
 #pragma unroll
             for (int c = 0; c < kRegChunks; ++c)
                 if (c0 + c < n_chunks)
-                    emit_chunk(sh, keys[c], (c0 + c) * kChunk + tid * kItems, len, thr, need_eq, budget, gt_base, eq_base, out);
+                    emit_chunk(sh.pick.wave_tot, keys[c], (c0 + c) * kChunk + tid * kItems, len, thr, need_eq, budget, gt_base, eq_base, out);
         }
     }
 }
 
 // ------------------------------------------------------------------------------------
-// Sliced variant for few, long heads: one block per (slice of 8192 tokens, head), five
-// short kernels instead of one long block per head.  The same radix select, with the
-// per-pass histograms written per slice to a workspace and summed by every block of the
-// next kernel (no global atomics, nothing to clear, fixed order of integer sums):
-//   stage 0    histogram of digit 0                               -> hist A
-//   stage 1    pick digit 0 from A;  histogram of digit 1         -> hist B, state
-//   stage 2    pick digit 1 from B;  histogram of digit 2         -> hist A, state
-//   stage 3    pick digit 2 from A = threshold; count (above, equal) per slice -> counts, state
-//   stage 4    ordered emission, each slice starting at the totals of the slices before it
+// Slices of long heads on separate workgroups: a group (one head, or all heads of a sequence when they are ranked
+// together) is cut into slices of whole chunks, a slice never spans two heads, and three kernels do the select:
+//   slices_count    histogram of the first digit per slice
+//   slices_collect  sum of the group's histograms -> the threshold's class; the slice's keys in it -> its list; how many
+//                   of the slice's keys lie above the class
+//   slices_emit     the class's keys from all lists -> threshold; ordered emission of the slice, starting at what the
+//                   slices before it keep
+// No global atomics and nothing to clear; every workgroup of a group repeats the integer sums.  Bound by the launches
+// and their memory round trips (a 4 x 128K selection reads 2 MB): five kernels with a histogram of the whole slice per
+// digit took 52 us there, these three take 21.
 // ------------------------------------------------------------------------------------
-constexpr int kSliceChunks = 2;
-constexpr int kSliceTok = kSliceChunks * kChunk;          // 8192 tokens per block
-
-struct SliceState {      // per (stage, head), in the workspace: stage k reads slot k-1 and writes slot k
-    uint32_t prefix;     // digits picked so far, in place
-    int remaining;       // rank still to resolve inside the prefix class; after stage 3: how many equal keys are kept
+struct SliceState {      // of a group, written by slices_collect
+    uint32_t digit;      // first digit of the threshold
+    int remaining;       // its rank inside that class
 };
 
-// Sums the slices' histograms of one head into sh.hist (thread t: bins 2t and 2t+1).
-__device__ __forceinline__ void sum_slice_histograms(SelectShared &sh, const int *__restrict__ hist, int n_slices) {
-    const int tid = threadIdx.x;
-    int lo = 0, hi = 0;
-    for (int sl = 0; sl < n_slices; ++sl) {
-        const int2 h = *(const int2 *)(hist + (size_t)sl * kBins + 2 * tid);
-        lo += h.x;
-        hi += h.y;
+// Shape of a sliced selection and its buffers in the workspace.
+struct Slices {
+    int heads, per_head, chunks;     // heads per group, slices per head, chunks of 4096 scores per slice
+    int key_stride;                  // keys between the heads of `keys`: N rounded up to 4
+    int *hist;                       // [groups][slices][kSliceBins]
+    uint32_t *list;                  // [groups][slices][chunks * kChunk]
+    int *above, *count;              // [groups][slices] keys above the class, keys in the list
+    SliceState *state;               // [groups]
+    uint32_t *keys;                  // [heads of all groups][key_stride]; NULL: the keys are formed from the scores each time
+};
+
+constexpr int kMaxGroupSlices = 1024;    // of a group whose bookkeeping fits LDS; larger ones (that many heads) read it where it lies
+
+// Where a workgroup of the sliced kernels works: blockIdx.x = slice of the group, blockIdx.y = group.
+struct SlicePlace {
+    int slice, group, head, in_head;         // head: of all groups
+    int c0, c1, len;                         // chunks of the head, its true length
+    template <typename Lens>
+    __device__ __forceinline__ SlicePlace(const Slices &S, int N, int Hkv, int ragged, const Lens &lens) {
+        slice = blockIdx.x;
+        group = blockIdx.y;
+        head = group * S.heads + slice / S.per_head;
+        in_head = slice % S.per_head;
+        len = seq_len_of(lens, ragged, head / Hkv, N);
+        c0 = in_head * S.chunks;
+        c1 = min(c0 + S.chunks, (len + kChunk - 1) / kChunk);
     }
-    sh.hist[2 * tid] = lo;
-    sh.hist[2 * tid + 1] = hi;
+    __device__ __forceinline__ size_t flat() const { return (size_t)group * gridDim.x + slice; }
+};
+
+// The slice's keys, kBatch chunks at a time: f(keys, first chunk).  From the scores, or from S.keys once those hold them.
+// `prepare` runs once, after the first batch has been loaded: what it needs from memory was asked for before the call, so
+// both are one round trip.
+template <int kBatch, typename P, typename F>
+__device__ __forceinline__ void for_batches(const Slices &S, const SlicePlace &at, const float *__restrict__ scores, int N, int first,
+                                            int tail, int radius, bool from_keys, P &&prepare, F &&f) {
+    const float *s = from_keys ? (const float *)(S.keys + (size_t)at.head * S.key_stride) : scores + (size_t)at.head * N;
+    const bool vec_ok = ((size_t)s & 15) == 0;
+    uint32_t keys[kBatch][kItems];
+    auto load = [&](int c) {
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+#pragma unroll
+            for (int e = 0; e < kItems; ++e) keys[i][e] = 0u;
+        load_batch<kBatch>(keys, s, c, at.c1, at.len, vec_ok, first, at.len - tail, from_keys ? 0 : radius, from_keys);
+    };
+    load(at.c0);                             // (a slice past the length loads nothing)
+    prepare();
+    for (int c = at.c0; c < at.c1; c += kBatch) {
+        if (c != at.c0) load(c);
+        f(keys, c);
+    }
 }
 
-template <int kStage, typename Lens>
-__global__ __launch_bounds__(kSelThreads) void select_sliced(const float *__restrict__ scores, int N, int budget,
-                                                             int Hkv, int ragged, Lens lens, int first, int tail,
-                                                             int radius, int keys_in, int n_slices, int *__restrict__ hist_a,
-                                                             int *__restrict__ hist_b, SliceState *__restrict__ state,
-                                                             int *__restrict__ counts,
-                                                             int32_t *__restrict__ keep_idx) {
-    __shared__ SelectShared sh;
-    const int slice = blockIdx.x, bg = blockIdx.y;
-    const int len = seq_len_of(lens, ragged, bg / Hkv, N);
-    const int cutoff = len - tail;
-    const float *s = scores + (size_t)bg * N;
-    const int tid = threadIdx.x;
-    const int n_chunks = (len + kChunk - 1) / kChunk;     // of the whole head
-    const int c0 = slice * kSliceChunks;                   // first chunk of this slice
-    const bool vec_ok = ((size_t)s & 15) == 0;
-    // which histogram buffer this stage reads and which it writes
-    const int *hist_in = (kStage == 1 || kStage == 3) ? hist_a : hist_b;
-    int *hist_out = (kStage == 0 || kStage == 2) ? hist_a : hist_b;
-    const SliceState *state_in = state + (size_t)(kStage > 0 ? kStage - 1 : 0) * gridDim.y;
-    SliceState *state_out = state + (size_t)(kStage < 4 ? kStage : 0) * gridDim.y;
-    hist_in += (size_t)bg * n_slices * kBins;
-    hist_out += ((size_t)bg * n_slices + slice) * kBins;
+__device__ __forceinline__ void store_keys(const Slices &S, const SlicePlace &at, int i0, const uint32_t (&key)[kItems]) {
+    if (i0 < at.len)       // (rows are padded to whole groups of four)
+        *(uint4 *)(S.keys + (size_t)at.head * S.key_stride + i0) = make_uint4(key[0], key[1], key[2], key[3]);
+}
 
-    uint32_t keys[kSliceChunks][kItems];
+template <int kBatch, typename Lens>
+__global__ __launch_bounds__(kSelThreads) void slices_count(const float *__restrict__ scores, int N, int Hkv, int ragged, Lens lens,
+                                                            int first, int tail, int radius, Slices S) {
+    __shared__ __attribute__((aligned(16))) int hist[kSliceBins];
+    const SlicePlace at(S, N, Hkv, ragged, lens);
+    clear_counters<kSliceBins>(hist);
+    for_batches<kBatch>(S, at, scores, N, first, tail, radius, false, [&]() { __syncthreads(); }, [&](uint32_t (&keys)[kBatch][kItems], int c) {
 #pragma unroll
-    for (int c = 0; c < kSliceChunks; ++c)
+        for (int i = 0; i < kBatch; ++i) {
+            if (c + i >= at.c1) continue;                    // uniform
+            const int i0 = (c + i) * kChunk + (int)threadIdx.x * kItems;
 #pragma unroll
-        for (int e = 0; e < kItems; ++e) keys[c][e] = 0u;
-    load_batch<kSliceChunks>(keys, s, c0, n_chunks, len, vec_ok, first, cutoff, radius, keys_in != 0);
-
-    // ---- the digit the previous stage's histograms decide ----
-    uint32_t prefix = 0, mask = 0;
-    int remaining = budget;
-    if (kStage >= 1 && kStage <= 3) {
-        if (kStage >= 2) { prefix = state_in[bg].prefix; remaining = state_in[bg].remaining; }
-        mask = kStage == 1 ? 0u : (kStage == 2 ? (2047u << 21) : ((2047u << 21) | (2047u << 10)));
-        sum_slice_histograms(sh, hist_in, n_slices);
-        uint32_t digit;
-        pick_digit(sh, remaining, &digit, &remaining);
-        const int shift_prev = kStage == 1 ? 21 : (kStage == 2 ? 10 : 0);
-        prefix |= digit << shift_prev;
-        mask |= (kStage == 3 ? 1023u : 2047u) << shift_prev;
-    }
-    if (kStage == 4) { prefix = state_in[bg].prefix; remaining = state_in[bg].remaining; }
-
-    if (kStage <= 2) {
-        // ---- histogram of this stage's digit over the slice, restricted to the prefix class ----
-        const int shift = kStage == 0 ? 21 : (kStage == 1 ? 10 : 0);
-        const uint32_t dmask = kStage == 2 ? 1023u : 2047u;
-        __syncthreads();
-        sh.hist[2 * tid] = 0;
-        sh.hist[2 * tid + 1] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < kSliceChunks; ++c) {
-            if (c0 + c < n_chunks) {                      // uniform
-#pragma unroll
-                for (int e = 0; e < kItems; ++e) {
-                    const bool in = (c0 + c) * kChunk + tid * kItems + e < len;
-                    histogram_add(sh.hist, (keys[c][e] >> shift) & dmask, in && ((keys[c][e] & mask) == prefix));
-                }
-            }
+            for (int e = 0; e < kItems; ++e)
+                if (i0 + e < at.len) atomicAdd(&hist[keys[i][e] >> (32 - kSliceBits)], 1);
+            if (S.keys) store_keys(S, at, i0, keys[i]);
         }
-        __syncthreads();
-        *(int2 *)(hist_out + 2 * tid) = make_int2(sh.hist[2 * tid], sh.hist[2 * tid + 1]);
-        if (kStage >= 1 && slice == 0 && tid == 0) { state_out[bg].prefix = prefix; state_out[bg].remaining = remaining; }
-    } else if (kStage == 3) {
-        // ---- threshold known: how many keys of this slice lie above it, how many equal it ----
-        int packed = 0;
+    });
+    __syncthreads();
+    int *dst = S.hist + at.flat() * kSliceBins;
+    *(int2 *)(dst + 2 * threadIdx.x) = *(const int2 *)(hist + 2 * threadIdx.x);
+}
+
+template <int kBatch, typename Lens>
+__global__ __launch_bounds__(kSelThreads) void slices_collect(const float *__restrict__ scores, int N, int budget, int Hkv, int ragged,
+                                                              Lens lens, int first, int tail, int radius, Slices S) {
+    __shared__ __attribute__((aligned(16))) int hist[kSliceBins];
+    __shared__ PickShared pick;
+    __shared__ int n_list, n_above;
+    const SlicePlace at(S, N, Hkv, ragged, lens);
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid == 0) { n_list = 0; n_above = 0; }
+    // Sum of the group's histograms: four counters per thread, even slices by one half of the workgroup, odd ones by the other.
+    constexpr int kAhead = 16;                               // slices of a half in flight at once
+    const int half = tid / (kSliceBins / 4), bin = tid % (kSliceBins / 4) * 4, n = gridDim.x;
+    const int *src = S.hist + (size_t)at.group * n * kSliceBins + bin;
+    int4 h[kAhead];
+    auto fetch = [&](int s0) {
 #pragma unroll
-        for (int c = 0; c < kSliceChunks; ++c)
+        for (int i = 0; i < kAhead; ++i) {
+            const int sl = s0 + 2 * i + half;
+            h[i] = make_int4(0, 0, 0, 0);
+            if (sl < n) h[i] = *(const int4 *)(src + (size_t)sl * kSliceBins);
+        }
+    };
+    uint32_t digit;
+    auto pick_class = [&]() {
+        int4 sum = make_int4(0, 0, 0, 0);
+        for (int s0 = 0; s0 < n; s0 += 2 * kAhead) {
+            if (s0 > 0) fetch(s0);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) { sum.x += h[i].x; sum.y += h[i].y; sum.z += h[i].z; sum.w += h[i].w; }
+        }
+        int4 *dst = (int4 *)(hist + bin);
+        if (half == 0) *dst = sum;
+        __syncthreads();
+        if (half == 1) *dst = make_int4(dst->x + sum.x, dst->y + sum.y, dst->z + sum.z, dst->w + sum.w);
+        int remaining = budget, in_digit;
+        pick_digit<kSliceBins>(hist, pick, &digit, &remaining, &in_digit);
+        if (at.slice == 0 && tid == 0) S.state[at.group] = SliceState{digit, remaining};
+    };
+    fetch(0);
+    uint32_t *list = S.list + at.flat() * S.chunks * kChunk;
+    for_batches<kBatch>(S, at, scores, N, first, tail, radius, S.keys != nullptr, pick_class, [&](uint32_t (&keys)[kBatch][kItems], int c) {
+        int mine = 0;                                        // low 16 bits: in the class, high 16 bits: above it
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
 #pragma unroll
             for (int e = 0; e < kItems; ++e) {
-                const bool in = (c0 + c) * kChunk + tid * kItems + e < len;
-                packed += (in && keys[c][e] > prefix ? 0x10000 : 0) + (in && keys[c][e] == prefix ? 1 : 0);
+                const bool in = c + i < at.c1 && (c + i) * kChunk + tid * kItems + e < at.len;
+                const uint32_t d = keys[i][e] >> (32 - kSliceBits);
+                mine += in && d == digit ? 1 : in && d > digit ? 0x10000 : 0;
             }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) packed += __shfl_xor(packed, off);
-        __syncthreads();
-        if ((tid & 63) == 0) sh.wave_tot[tid >> 6] = packed;
-        __syncthreads();
-        if (tid == 0) {
-            int tot = 0;
-#pragma unroll
-            for (int w = 0; w < kSelWaves; ++w) tot += sh.wave_tot[w];
-            counts[((size_t)bg * n_slices + slice) * 2 + 0] = tot >> 16;
-            counts[((size_t)bg * n_slices + slice) * 2 + 1] = tot & 0xffff;
-            if (slice == 0) { state_out[bg].prefix = prefix; state_out[bg].remaining = remaining; }
+        const int incl = wave_scan<false>(mine, lane);
+        int base = 0;
+        if (lane == 63 && incl != 0) {
+            base = atomicAdd(&n_list, incl & 0xffff);
+            atomicAdd(&n_above, incl >> 16);
         }
-    } else {
-        // ---- ordered emission ----
-        int gt_base = 0, eq_base = 0;
-        for (int sl = 0; sl < slice; ++sl) {
-            gt_base += counts[((size_t)bg * n_slices + sl) * 2 + 0];
-            eq_base += counts[((size_t)bg * n_slices + sl) * 2 + 1];
-        }
-        int32_t *out = keep_idx + (size_t)bg * budget;
+        int pos = __builtin_amdgcn_readlane(base, 63) + ((incl - mine) & 0xffff);
 #pragma unroll
-        for (int c = 0; c < kSliceChunks; ++c)
-            if (c0 + c < n_chunks)
-                emit_chunk(sh, keys[c], (c0 + c) * kChunk + tid * kItems, len, prefix, remaining, budget, gt_base, eq_base, out);
+        for (int i = 0; i < kBatch; ++i)
+#pragma unroll
+            for (int e = 0; e < kItems; ++e) {
+                const bool in = c + i < at.c1 && (c + i) * kChunk + tid * kItems + e < at.len;
+                if (in && (keys[i][e] >> (32 - kSliceBits)) == digit) list[pos++] = keys[i][e];
+            }
+    });
+    __syncthreads();
+    if (tid == 0) { S.count[at.flat()] = n_list; S.above[at.flat()] = n_above; }
+}
+
+// The threshold of a group, and what of it lies where relative to a slice.
+struct SliceShared {
+    using D = Digits<kSliceBits>;
+    int hist1[D::kBins1], hist2[D::kBins2];
+    uint32_t list[kList];
+    int count[kMaxGroupSlices], offset[kMaxGroupSlices + 1];
+    PickShared pick;
+    int head_gt_before, head_gt, eq_before_head, eq_before, eq_head;
+};
+
+struct SliceThreshold {
+    uint32_t thr;
+    int need_eq, n_equal;    // keys equal to it: kept (the first ones of the group), all
+    int gt_before, gt_head;  // keys above it: in the head's earlier slices, in the head
+    int eq_before_head, eq_before, eq_head;    // keys equal to it: in earlier heads of the group, in earlier slices of the group, in the head
+};
+
+// What slice_threshold needs first, asked for ahead of it.
+struct SliceAhead {
+    SliceState state;
+    int count;               // of the slice with this thread's index
+    __device__ __forceinline__ SliceAhead(const Slices &S, const SlicePlace &at) {
+        state = S.state[at.group];
+        count = (int)gridDim.x <= kMaxGroupSlices && threadIdx.x < gridDim.x ? S.count[(size_t)at.group * gridDim.x + threadIdx.x] : 0;
     }
+};
+
+__device__ __forceinline__ SliceThreshold slice_threshold(SliceShared &sh, const Slices &S, const SlicePlace &at, const SliceAhead &ahead) {
+    using D = Digits<kSliceBits>;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = gridDim.x;
+    const int head0 = at.slice - at.in_head, head1 = head0 + S.per_head;       // the head's slices
+    const SliceState st = ahead.state;
+    clear_counters<D::kBins1>(sh.hist1);
+    clear_counters<D::kBins2>(sh.hist2);
+    if (tid == 0) sh.head_gt_before = sh.head_gt = sh.eq_before_head = sh.eq_before = sh.eq_head = 0;
+    const int *counts = S.count + (size_t)at.group * n, *aboves = S.above + (size_t)at.group * n;
+    const bool few = n <= kMaxGroupSlices;                   // uniform
+    if (few && tid < n) sh.count[tid] = ahead.count;
+    __syncthreads();
+    if (few && wave == 0) {                                  // offsets of the slices' lists laid end to end
+        int base = 0;
+        for (int s0 = 0; s0 < n; s0 += 64) {
+            const int c = s0 + lane < n ? sh.count[s0 + lane] : 0;
+            const int incl = wave_scan<false>(c, lane);
+            if (s0 + lane < n) sh.offset[s0 + lane] = base + incl - c;
+            base += __builtin_amdgcn_readlane(incl, 63);
+        }
+        if (lane == 0) sh.offset[n] = base;
+    } else if (wave == 1) {                                  // keys above the class in the head
+        int before = 0, all = 0;
+        for (int sl = head0 + lane; sl < head1; sl += 64) {
+            const int a = aboves[sl];
+            all += a;
+            before += sl < at.slice ? a : 0;
+        }
+        before = (int)wave_reduce<SumOp>((uint32_t)before);
+        all = (int)wave_reduce<SumOp>((uint32_t)all);
+        if (lane == 0) { atomicAdd(&sh.head_gt_before, before); atomicAdd(&sh.head_gt, all); }
+    }
+    __syncthreads();
+    const int n_list = few ? sh.offset[n] : 0;
+    const bool in_lds = few && n_list <= kList;              // uniform
+    const uint32_t *lists = S.list + (size_t)at.group * n * S.chunks * kChunk;
+    // f(key, slice) over the lists where they lie: a wave per slice
+    auto visit_global = [&](auto &&f) {
+        for (int sl = wave; sl < n; sl += kSelWaves) {
+            const uint32_t *src = lists + (size_t)sl * S.chunks * kChunk;
+            const int c = few ? sh.count[sl] : counts[sl];
+            for (int i = lane; i < c; i += 64) f(src[i], sl, i);
+        }
+    };
+    if (in_lds) {
+        visit_global([&](uint32_t key, int sl, int i) { sh.list[sh.offset[sl] + i] = key; });
+        __syncthreads();
+    }
+    SliceThreshold t;
+    t.thr = st.digit << (32 - kSliceBits);
+    t.need_eq = st.remaining;
+    finish_class<D>(sh.hist1, sh.hist2, sh.pick, [&](auto &&f) {
+        if (in_lds) for (int j = tid; j < n_list; j += kSelThreads) f(sh.list[j]);
+        else visit_global([&](uint32_t key, int, int) { f(key); });
+    }, &t.thr, &t.need_eq, &t.n_equal);
+    // class keys above and at the threshold, by where they lie
+    int gt_before = 0, gt_head = 0, eq_first = 0, eq_before = 0, eq_head = 0;
+    const int p_head0 = few ? sh.offset[head0] : 0, p_slice = few ? sh.offset[at.slice] : 0, p_head1 = few ? sh.offset[head1] : 0;
+    auto tally = [&](uint32_t key, bool before_head, bool before_slice, bool in_head) {
+        if (key > t.thr) {
+            gt_head += in_head ? 1 : 0;
+            gt_before += in_head && before_slice ? 1 : 0;
+        } else if (key == t.thr) {
+            eq_first += before_head ? 1 : 0;
+            eq_before += before_slice ? 1 : 0;
+            eq_head += in_head ? 1 : 0;
+        }
+    };
+    if (in_lds) for (int j = tid; j < n_list; j += kSelThreads) tally(sh.list[j], j < p_head0, j < p_slice, j >= p_head0 && j < p_head1);
+    else visit_global([&](uint32_t key, int sl, int) { tally(key, sl < head0, sl < at.slice, sl >= head0 && sl < head1); });
+    auto add = [&](int *to, int x) {
+        if (__ballot(x != 0) == 0ull) return;                // uniform
+        x = (int)wave_reduce<SumOp>((uint32_t)x);
+        if (lane == 0) atomicAdd(to, x);
+    };
+    add(&sh.head_gt_before, gt_before);
+    add(&sh.head_gt, gt_head);
+    add(&sh.eq_before_head, eq_first);
+    add(&sh.eq_before, eq_before);
+    add(&sh.eq_head, eq_head);
+    __syncthreads();
+    t.gt_before = sh.head_gt_before;
+    t.gt_head = sh.head_gt;
+    t.eq_before_head = sh.eq_before_head;
+    t.eq_before = sh.eq_before;
+    t.eq_head = sh.eq_head;
+    return t;
+}
+
+// `counts` == NULL: keep_idx [heads][room], every list full.  Otherwise the heads of a group share the budget: counts
+// [heads] receives how many each one keeps, and its list of `room` is filled up with -1.
+template <int kBatch, typename Lens>
+__global__ __launch_bounds__(kSelThreads) void slices_emit(const float *__restrict__ scores, int N, int room, int Hkv, int ragged,
+                                                           Lens lens, int first, int tail, int radius, Slices S,
+                                                           int32_t *__restrict__ keep_idx, int32_t *__restrict__ counts) {
+    __shared__ __attribute__((aligned(16))) SliceShared sh;
+    const SlicePlace at(S, N, Hkv, ragged, lens);
+    const SliceAhead ahead(S, at);
+    SliceThreshold t;
+    int32_t *out = keep_idx + (size_t)at.head * room;
+    int eq_skip, gt_base, eq_base;
+    for_batches<kBatch>(S, at, scores, N, first, tail, radius, S.keys != nullptr, [&]() {
+        t = slice_threshold(sh, S, at, ahead);
+        // kept keys equal to the threshold are the first need_eq of the group; positions count inside the head
+        eq_skip = min(t.eq_before_head, t.need_eq);
+        gt_base = t.gt_before - eq_skip;
+        eq_base = t.eq_before;
+    }, [&](uint32_t (&keys)[kBatch][kItems], int c) {
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+            if (c + i < at.c1)
+                emit_chunk(sh.pick.wave_tot, keys[i], (c + i) * kChunk + (int)threadIdx.x * kItems, at.len, t.thr, t.need_eq, room, gt_base,
+                           eq_base, out);
+    });
+    if (!counts) return;
+    const int kept = min(t.gt_head + min(t.eq_before_head + t.eq_head, t.need_eq) - eq_skip, room);
+    if (at.in_head == 0 && threadIdx.x == 0) counts[at.head] = kept;
+    for (int j = kept + at.in_head * kSelThreads + threadIdx.x; j < room; j += S.per_head * kSelThreads) out[j] = -1;
 }
 
 // ------------------------------------------------------------------------------------
 // Head-adaptive budgets (Appendix C, AdaKV paragraph): the layer's budget is spread over the
 // KV heads by ranking all (head, token) scores of a sequence together, after each head's own
-// top n_safe tokens (the safeguard) have been put beyond competition.  Done with the
-// selection above on a sequence's heads laid end to end, over order-preserving keys:
-//   adaptive_keys   key of every live token (>= 1), 0 for positions beyond the true length
-//   adaptive_mark   0xffffffff for every head's n_safe best (found by the per-head select)
-//   select          top Hkv * budget of the Hkv * N keys: ascending flat positions
-//   adaptive_split  flat positions -> per-head index lists and counts
+// top n_safe tokens (the safeguard) have been put beyond competition.  slices_count and
+// slices_collect find every head's class for n_safe; the kernel below finishes that selection and
+// turns the slice's scores into the keys of the second one (live tokens >= 1, 0 for positions
+// beyond the true length, 0xffffffff for the safeguard), with their histogram; then
+// slices_collect and slices_emit run over all heads of a sequence as one group.
 // ------------------------------------------------------------------------------------
-template <typename Lens>
-__global__ __launch_bounds__(256) void adaptive_keys(const float *__restrict__ scores, int N, int Hkv, int ragged,
-                                                     Lens lens, size_t total, uint32_t *__restrict__ keys) {
-    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total) return;
-    const int p = (int)(t % N);
-    const int b = (int)(t / ((size_t)N * Hkv));
-    const uint32_t key = order_key(scores[t]);
-    keys[t] = p < seq_len_of(lens, ragged, b, N) ? (key < 1u ? 1u : key) : 0u;
-}
-
-__global__ __launch_bounds__(256) void adaptive_mark(const int32_t *__restrict__ safe_idx, int N, int n_safe,
-                                                     size_t total, uint32_t *__restrict__ keys) {
-    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;       // (bg, j)
-    if (t >= total) return;
-    const size_t bg = t / n_safe;
-    const int p = safe_idx[t];
-    if (p >= 0 && p < N) keys[bg * N + p] = 0xffffffffu;
-}
-
-// One block per (head, sequence): the head's share of the ascending flat list is the run of
-// positions in [g N, (g+1) N); its ends are found by bisection.
-__global__ __launch_bounds__(256) void adaptive_split(const int32_t *__restrict__ flat_idx, int N, int total_budget,
-                                                      int cap, int32_t *__restrict__ keep_idx,
-                                                      int32_t *__restrict__ counts) {
-    const int g = blockIdx.x, b = blockIdx.y, Hkv = gridDim.x;
-    const int32_t *flat = flat_idx + (size_t)b * total_budget;
-    auto lower_bound = [&](int value) {
-        int lo = 0, hi = total_budget;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (flat[mid] < value) lo = mid + 1; else hi = mid;
+template <int kBatch, typename Lens>
+__global__ __launch_bounds__(kSelThreads) void slices_safeguard(const float *__restrict__ scores, int N, int n_safe, int Hkv, int ragged,
+                                                                Lens lens, Slices S, uint32_t *__restrict__ keys_out,
+                                                                int *__restrict__ hist_out) {
+    __shared__ __attribute__((aligned(16))) SliceShared sh;
+    __shared__ __attribute__((aligned(16))) int hist[kSliceBins];
+    const SlicePlace at(S, N, Hkv, ragged, lens);            // (a group is one head here)
+    clear_counters<kSliceBins>(hist);
+    const SliceAhead ahead(S, at);           // (not used without a safeguard: nothing has written it then)
+    SliceThreshold t = {};
+    int eq_base = 0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for_batches<kBatch>(S, at, scores, N, 0, 0, 0, false, [&]() {
+        if (n_safe > 0) t = slice_threshold(sh, S, at, ahead);
+        else __syncthreads();
+        eq_base = t.eq_before;
+    }, [&](uint32_t (&keys)[kBatch][kItems], int c) {
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            if (c + i >= at.c1) continue;                    // uniform
+            const int i0 = (c + i) * kChunk + (int)threadIdx.x * kItems;
+            int eq_before = 0;
+            if (n_safe > 0 && t.need_eq < t.n_equal) {       // uniform: the first need_eq of the equal keys are safe
+                int mine = 0;
+#pragma unroll
+                for (int e = 0; e < kItems; ++e) mine += i0 + e < at.len && keys[i][e] == t.thr ? 1 : 0;
+                const int incl = wave_scan<false>(mine, lane);
+                __syncthreads();
+                if (lane == 63) sh.pick.wave_tot[wave] = incl;
+                __syncthreads();
+                eq_before = eq_base + incl - mine;
+#pragma unroll
+                for (int w = 0; w < kSelWaves; ++w) {
+                    if (w < wave) eq_before += sh.pick.wave_tot[w];
+                    eq_base += sh.pick.wave_tot[w];
+                }
+            } else {
+                eq_before = -0x40000000;                     // all of them
+            }
+#pragma unroll
+            for (int e = 0; e < kItems; ++e) {
+                const bool live = i0 + e < at.len, eq = keys[i][e] == t.thr;
+                const bool safe = n_safe > 0 && live && (keys[i][e] > t.thr || (eq && eq_before < t.need_eq));
+                eq_before += eq ? 1 : 0;
+                keys[i][e] = !live ? 0u : safe ? 0xffffffffu : keys[i][e];
+                if (live) atomicAdd(&hist[keys[i][e] >> (32 - kSliceBits)], 1);
+            }
+            if (i0 < at.len)
+                *(uint4 *)(keys_out + (size_t)at.head * S.key_stride + i0) = make_uint4(keys[i][0], keys[i][1], keys[i][2], keys[i][3]);
         }
-        return lo;
-    };
-    const int begin = lower_bound(g * N), end = lower_bound((g + 1) * N);
-    const int count = min(end - begin, cap);
-    int32_t *out = keep_idx + ((size_t)b * Hkv + g) * cap;
-    for (int j = threadIdx.x; j < cap; j += 256) out[j] = j < count ? flat[begin + j] - g * N : -1;
-    if (threadIdx.x == 0) counts[(size_t)b * Hkv + g] = count;
+    });
+    __syncthreads();
+    int *dst = hist_out + at.flat() * kSliceBins;
+    *(int2 *)(dst + 2 * threadIdx.x) = *(const int2 *)(hist + 2 * threadIdx.x);
 }
 
 }  // namespace
 
 static size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
+// Slices of about 4096 scores, longer ones where a group would have more than 64 of them (every workgroup sums the
+// group's histograms, 8 KB per slice); 256 from 16K scores per slice on, where that is little beside the slice itself.
+static int slice_chunks(int heads, int N) {
+    int chunks = 1;
+    auto per_head = [&]() { return (N + (long long)chunks * kChunk - 1) / ((long long)chunks * kChunk); };
+    while (per_head() > 1 && heads * per_head() > (chunks < 4 ? 64 : 256)) chunks = chunks == 1 ? 4 : chunks * 2;
+    return chunks;
+}
+
+// Carves the buffers of a sliced selection out of `base` (nullptr: sizes only); returns the bytes.
+static size_t plan_slices(Slices *S, char *base, int groups, int heads, int N, bool own_keys) {
+    S->heads = heads;
+    S->chunks = slice_chunks(heads, N);
+    S->per_head = (int)((N + (long long)S->chunks * kChunk - 1) / ((long long)S->chunks * kChunk));
+    S->key_stride = (N + 3) / 4 * 4;
+    const size_t slices = (size_t)groups * heads * S->per_head;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { char *p = base + off; off += up256(bytes); return p; };
+    S->hist = (int *)take(slices * kSliceBins * sizeof(int));
+    S->list = (uint32_t *)take(slices * S->chunks * kChunk * sizeof(uint32_t));
+    S->above = (int *)take(slices * sizeof(int));
+    S->count = (int *)take(slices * sizeof(int));
+    S->state = (SliceState *)take((size_t)groups * sizeof(SliceState));
+    S->keys = own_keys ? (uint32_t *)take((size_t)groups * heads * S->key_stride * sizeof(uint32_t)) : nullptr;
+    return off;
+}
+
+template <typename F>
+static hipError_t with_batch(const Slices &S, F &&f) {
+    return S.chunks == 1 ? f(std::integral_constant<int, 1>()) : f(std::integral_constant<int, 4>());
+}
+
+size_t select_workspace_bytes(int B, int Hkv, int N) {
+    Slices S;
+    return plan_slices(&S, nullptr, B * Hkv, 1, N, true);
+}
+
+// Long heads take the sliced path: one workgroup per head keeps a 32K-token head in registers, but beyond that it
+// spills or re-streams the head in every pass (53 us at 64K, 390 us at 128K measured).
+bool select_prefers_slices(int B, int Hkv, int N) {
+    return N > 8 * kChunk && (long long)B * Hkv <= 65535;
+}
+
+static hipError_t launch_select_sliced(const float *scores, int budget, int32_t *keep_idx, int B, int Hkv, int N, int ragged,
+                                       const SeqLens &lens, int first, int tail, int radius, void *workspace, hipStream_t stream) {
+    Slices S;
+    plan_slices(&S, (char *)workspace, B * Hkv, 1, N, true);
+    if (radius == 0) S.keys = nullptr;       // (scores are as quick to turn into keys as keys are to read)
+    const dim3 grid(S.per_head, B * Hkv), block(kSelThreads);
+    return with_lens(ragged, B, lens, [&](const auto &few) {
+        return with_batch(S, [&](auto batch) {
+            constexpr int kBatch = decltype(batch)::value;
+            slices_count<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, radius, S);
+            slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S);
+            slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S, keep_idx,
+                                                            (int32_t *)nullptr);
+            return hipGetLastError();
+        });
+    });
+}
+
+// The per-head selection of the safeguard and the selection over a sequence's heads cut heads into the same slices.
+static size_t plan_adaptive(Slices *safe, Slices *all, char *base, int B, int Hkv, int N) {
+    size_t off = plan_slices(all, base, B, Hkv, N, true);
+    *safe = *all;
+    safe->heads = 1;
+    safe->keys = nullptr;                    // (formed from the scores; the second selection's keys are written beside)
+    const size_t slices = (size_t)B * Hkv * all->per_head;
+    safe->hist = (int *)(base + off);
+    off += up256(slices * kSliceBins * sizeof(int));
+    safe->state = (SliceState *)(base + off);
+    off += up256((size_t)B * Hkv * sizeof(SliceState));
+    return off;
+}
+
 size_t select_adaptive_workspace_bytes(int B, int Hkv, int N, int budget, int n_safe) {
-    const size_t BH = (size_t)B * Hkv;
-    size_t bytes = up256(BH * (size_t)(n_safe > 0 ? n_safe : 1) * sizeof(int32_t));     // safeguard indices
-    bytes += up256(BH * N * sizeof(uint32_t));                                           // keys
-    bytes += up256((size_t)B * Hkv * budget * sizeof(int32_t));                          // flat positions
-    if (select_prefers_slices(B, 1, Hkv * N)) bytes += select_workspace_bytes(B, 1, Hkv * N);
-    if (select_prefers_slices(B, Hkv, N)) bytes += select_workspace_bytes(B, Hkv, N);
-    return bytes;
+    (void)budget; (void)n_safe;
+    Slices a, b;
+    return plan_adaptive(&a, &b, nullptr, B, Hkv, N);
 }
 
 hipError_t launch_select_adaptive(const float *scores, int budget, int n_safe, int cap, int32_t *keep_idx,
                                   int32_t *counts, int B, int Hkv, int N, int ragged, const SeqLens &lens,
                                   void *workspace, hipStream_t stream) {
-    const size_t BH = (size_t)B * Hkv;
-    char *base = (char *)workspace;
-    int32_t *safe_idx = (int32_t *)base;   base += up256(BH * (size_t)(n_safe > 0 ? n_safe : 1) * sizeof(int32_t));
-    uint32_t *keys = (uint32_t *)base;     base += up256(BH * N * sizeof(uint32_t));
-    int32_t *flat_idx = (int32_t *)base;   base += up256((size_t)B * Hkv * budget * sizeof(int32_t));
-    void *ws_flat = nullptr, *ws_head = nullptr;
-    size_t ws_flat_bytes = 0, ws_head_bytes = 0;
-    if (select_prefers_slices(B, 1, Hkv * N)) { ws_flat = base; ws_flat_bytes = select_workspace_bytes(B, 1, Hkv * N); base += ws_flat_bytes; }
-    if (select_prefers_slices(B, Hkv, N)) { ws_head = base; ws_head_bytes = select_workspace_bytes(B, Hkv, N); }
-    hipError_t e;
-    const size_t total = BH * N;
-    e = with_lens(ragged, B, lens, [&](const auto &few) {
-        adaptive_keys<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream>>>(scores, N, Hkv, ragged, few, total, keys);
-        return hipGetLastError();
-    });
-    if (e != hipSuccess) return e;
-    if (n_safe > 0) {
-        e = launch_select(scores, n_safe, safe_idx, B, Hkv, N, ragged, lens, 0, 0, 0, ws_head, ws_head_bytes, stream, 0);
-        if (e != hipSuccess) return e;
-        const size_t marks = BH * n_safe;
-        adaptive_mark<<<dim3((unsigned)((marks + 255) / 256)), dim3(256), 0, stream>>>(safe_idx, N, n_safe, marks, keys);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    SeqLens none;
-    std::memset(&none, 0, sizeof(none));
-    e = launch_select((const float *)keys, Hkv * budget, flat_idx, B, 1, Hkv * N, 0, none, 0, 0, 0, ws_flat, ws_flat_bytes,
-                      stream, 1);
-    if (e != hipSuccess) return e;
-    adaptive_split<<<dim3(Hkv, B), dim3(256), 0, stream>>>(flat_idx, N, Hkv * budget, cap, keep_idx, counts);
-    return hipGetLastError();
-}
-
-size_t select_workspace_bytes(int B, int Hkv, int N) {
-    const size_t BH = (size_t)B * Hkv;
-    const size_t n_slices = ((size_t)N + kSliceTok - 1) / kSliceTok;
-    auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    return 2 * up(BH * n_slices * kBins * sizeof(int)) + up(4 * BH * sizeof(SliceState)) + up(BH * n_slices * 2 * sizeof(int));
-}
-
-// Long heads take the sliced path: one block per head keeps a 32K-token head in registers
-// (27 us, about what five launches cost), but beyond that it spills or re-streams the head
-// in every pass (53 us at 64K, 390 us at 128K measured) while the slices stay at 35-55 us.
-bool select_prefers_slices(int B, int Hkv, int N) {
-    const long long BH = (long long)B * Hkv;
-    return N > 8 * kChunk && BH * ((N + kSliceTok - 1) / kSliceTok) <= 2048;
-}
-
-hipError_t launch_select_sliced(const float *scores, int budget, int32_t *keep_idx, int B, int Hkv, int N, int ragged,
-                                const SeqLens &lens, int first, int tail, int radius, int keys_in, void *workspace,
-                                hipStream_t stream) {
-    const size_t BH = (size_t)B * Hkv;
-    const int n_slices = (N + kSliceTok - 1) / kSliceTok;
-    auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    char *base = (char *)workspace;
-    int *hist_a = (int *)base;                      base += up(BH * n_slices * kBins * sizeof(int));
-    int *hist_b = (int *)base;                      base += up(BH * n_slices * kBins * sizeof(int));
-    SliceState *state = (SliceState *)base;         base += up(4 * BH * sizeof(SliceState));
-    int *counts = (int *)base;
-    const dim3 grid(n_slices, (unsigned)BH), block(kSelThreads);
+    Slices safe, all;
+    plan_adaptive(&safe, &all, (char *)workspace, B, Hkv, N);
+    const dim3 by_head(all.per_head, B * Hkv), by_sequence(all.per_head * Hkv, B), block(kSelThreads);
     return with_lens(ragged, B, lens, [&](const auto &few) {
-#define OBC_SLICED_ARGS scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, n_slices, hist_a, hist_b, state, counts, keep_idx
-        select_sliced<0><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-        select_sliced<1><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-        select_sliced<2><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-        select_sliced<3><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-        select_sliced<4><<<grid, block, 0, stream>>>(OBC_SLICED_ARGS);
-#undef OBC_SLICED_ARGS
-        return hipGetLastError();
+        return with_batch(all, [&](auto batch) {
+            constexpr int kBatch = decltype(batch)::value;
+            if (n_safe > 0) {
+                slices_count<kBatch><<<by_head, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, safe);
+                slices_collect<kBatch><<<by_head, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, 0, 0, 0, safe);
+            }
+            slices_safeguard<kBatch><<<by_head, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, safe, all.keys, all.hist);
+            slices_collect<kBatch><<<by_sequence, block, 0, stream>>>(scores, N, Hkv * budget, Hkv, ragged, few, 0, 0, 0, all);
+            slices_emit<kBatch><<<by_sequence, block, 0, stream>>>(scores, N, cap, Hkv, ragged, few, 0, 0, 0, all, keep_idx, counts);
+            return hipGetLastError();
+        });
     });
 }
 
 hipError_t launch_select(const float *scores, int budget, int32_t *keep_idx, int B, int Hkv, int N, int ragged,
                          const SeqLens &lens, int first, int tail, int radius, void *workspace,
-                         size_t workspace_bytes, hipStream_t stream, int keys_in) {
+                         size_t workspace_bytes, hipStream_t stream) {
     if (workspace && select_prefers_slices(B, Hkv, N) && workspace_bytes >= select_workspace_bytes(B, Hkv, N))
-        return launch_select_sliced(scores, budget, keep_idx, B, Hkv, N, ragged, lens, first, tail, radius, keys_in,
-                                    workspace, stream);
+        return launch_select_sliced(scores, budget, keep_idx, B, Hkv, N, ragged, lens, first, tail, radius, workspace, stream);
     const dim3 grid(B * Hkv), block(kSelThreads);
     return with_lens(ragged, B, lens, [&](const auto &few) {
         if (N <= kChunk)             // (short heads: fewer unrolled chunk bodies to step through)
-            select_topk<1, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+            select_topk<1, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keep_idx);
         else if (N <= 2 * kChunk)
-            select_topk<2, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+            select_topk<2, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keep_idx);
         else if (N <= 8 * kChunk)
-            select_topk<8, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+            select_topk<8, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keep_idx);
         else if (N <= 16 * kChunk)
-            select_topk<16, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+            select_topk<16, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keep_idx);
         else
-            select_topk<8, false><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keys_in, keep_idx);
+            select_topk<8, false><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, keep_idx);
         return hipGetLastError();
     });
 }
