@@ -56,6 +56,8 @@ struct ScoreWorkspace {
     int split_len;     // tokens per split (multiple of 64)
     int range_len;     // tokens per workgroup in the second sweep (multiple of 64)
     int use_mfma;      // 1: bf16 matrix-core path, 0: general path
+    size_t z;          // float [B*Hkv*rows*z_stride]  raw q.k, kept by the first sweep when keep_z
+    int keep_z, z_stride;
     int use_wide;      // 1: the second sweep runs in its register-blocked form (score_mfma_wide.hip)
     // General path: see score_plain.hip.  One piece of the work is `pl_heads` KV heads x `pl_rows` window rows x
     // `pl_seg` tokens; its buffers are reused by the next one.
@@ -89,14 +91,13 @@ int tuned_splits();
 int tuned_range();
 int tuned_sweep2_form();     // 0: by shape, 1: 32 rows per wave, 2: 64 rows per wave where the shape allows
 
-// `plain_cap`: bytes the general path should stay within (it works in pieces).
-constexpr size_t kPlainWorkspace = (size_t)96 << 20;
-int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, ScoreWorkspace *ws,
-                         size_t plain_cap = kPlainWorkspace);
+// `cap`: bytes the plan should stay within where it has a choice (0: what is best).
+constexpr size_t kPlainWorkspace = (size_t)96 << 20;      // of the general path, which works in pieces
+int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, ScoreWorkspace *ws, size_t cap = 0);
 // Adds the general path's buffers to the plan, advancing *off (bytes).
 void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWorkspace *ws, size_t *off);
 // Adds the matrix-core path's buffers to the plan, advancing *off (bytes).
-void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWorkspace *ws, size_t *off);
+void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, size_t cap, ScoreWorkspace *ws, size_t *off);
 
 // Decode path: whether it covers the shape, its buffers (advancing *off), its launcher.
 bool decode_path_covers(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, bool any_size);

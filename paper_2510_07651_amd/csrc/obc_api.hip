@@ -61,7 +61,7 @@ static int check_score_shape(int B, int N, int W, int Hq, int Hkv, int d, int dt
 static bool score_path_is(int path) { return g_score_path.load(std::memory_order_relaxed) == path; }
 
 int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, ScoreWorkspace *ws,
-                         size_t plain_cap) {
+                         size_t cap) {
     const int rc = check_score_shape(B, N, W, Hq, Hkv, d, dtype, variant);
     if (rc != OBC_OK) return rc;
     std::memset(ws, 0, sizeof(*ws));
@@ -74,9 +74,9 @@ int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype,
     if (ws->use_decode) {
         decode_plan(B, N, Hq, Hkv, d, ws, &off);
     } else if (ws->use_mfma) {
-        mfma_plan(B, N, W, Hq, Hkv, d, variant, ws, &off);
+        mfma_plan(B, N, W, Hq, Hkv, d, variant, cap ? cap : SIZE_MAX, ws, &off);
     } else {
-        plain_plan(B, N, W, Hq, Hkv, d, plain_cap, ws, &off);
+        plain_plan(B, N, W, Hq, Hkv, d, cap ? cap : kPlainWorkspace, ws, &off);
     }
     ws->total = align_up(off, 256);
     return OBC_OK;
@@ -195,7 +195,7 @@ static int score_impl(const void *q, const void *k, const void *v, int N, int W,
     if ((((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) & 15) != 0 || ((uintptr_t)scores & 3) != 0) return OBC_EINVAL;
     if (stage_mask < 1 || stage_mask > OBC_STAGE_ALL) return OBC_EINVAL;
     ScoreWorkspace ws;
-    int rc = plan_score_workspace(B, N, W, Hq, Hkv, d, dtype, variant, &ws, own_scratch ? OBC_STATIC_SCRATCH_BYTES : kPlainWorkspace);
+    int rc = plan_score_workspace(B, N, W, Hq, Hkv, d, dtype, variant, &ws, own_scratch ? OBC_STATIC_SCRATCH_BYTES : 0);
     if (rc != OBC_OK) return rc;
     ScoreArgs a;
     std::memset(&a, 0, sizeof(a));

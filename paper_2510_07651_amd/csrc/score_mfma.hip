@@ -50,6 +50,7 @@
 // A and Z never touch HBM.  All sums have a fixed order: results are bit-reproducible.
 #include "internal.h"
 #include "mfma_util.h"
+#include "wave_util.h"
 
 namespace obc {
 using namespace mfma;
@@ -141,12 +142,12 @@ __device__ __forceinline__ void pack_weights(Sweep1Regs &R) {
 // its sums.  The step is then cut in two: K Q^T and the block's row maxima first; a vote whether
 // some row of the wave meets a new candidate in block n, and (rarely) the branch that deals with
 // it; then V^T P^T and the weights.  Without kNeedO the step is one basic block.
-template <int PH, bool kMasked, bool kNeedO>
+template <int PH, bool kMasked, bool kNeedO, bool kStoreZ>
 __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uint32_t lds0, int n, int t_begin,
                                             int t_end, int last_row, int vis, const char *kh, const char *vh,
                                             const int (&koff)[8], const int (&voff)[4], const uint32_t (&kdoff)[2],
                                             const uint32_t (&vdoff)[2], int wave, int lane, bool wave_active,
-                                            int2 *events) {
+                                            int2 *events, char *z_split, uint32_t z_off) {
     // K and V blocks live in rings of four 8 KB slots each (block j in slot j mod 4): K block
     // n+1 and V block n-1, both started three steps ago, are waited for here while the two
     // younger batches stay in flight; then K block n+4 and V block n+2 start in the slots
@@ -157,12 +158,22 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
     const float c2 = kLog2e * kInvSqrtD;
     const int half = lane >> 5;
 
-    wait_async_loads_keep<kNeedO ? 8 : 4>();
+    // (with kStoreZ the wave that has rows also has four stores per step in flight behind the loads of that step: from the
+    // third step on the two younger batches are twice as long)
+    constexpr int kBatch = kNeedO ? 4 : 2;
+    if (kStoreZ && wave_active && n > 1 && n * 32 < t_end - t_begin) wait_async_loads_keep<2 * kBatch + 8>();
+    else if (kStoreZ && wave_active && n == 1 && 32 < t_end - t_begin) wait_async_loads_keep<2 * kBatch + 4>();
+    else wait_async_loads_keep<2 * kBatch>();
     __syncthreads();
     block_load_async<kXor16>(kh, t_begin + (n + 4) * 32, last_row, lds0 + PH * kBlkBytes, wave, lane, kdoff);
     if (kNeedO)
         block_load_async<kRot4>(vh, t_begin + (n + 2) * 32, last_row, lds0 + (4 + ((PH + 2) & 3)) * kBlkBytes, wave, lane, vdoff);
     if (!wave_active) return;
+    if (kStoreZ && n * 32 < t_end - t_begin && z_off != ~0u) {      // raw q.k of block n for score_few_rows
+#pragma unroll
+        for (int r = 0; r < 16; r += 4)
+            *(float4 *)(z_split + n * 128 + 8 * r + z_off) = make_float4(R.s_cur[r], R.s_cur[r + 1], R.s_cur[r + 2], R.s_cur[r + 3]);
+    }
 
     // ---- matrix cores: block n+1 ----
     // (with kNeedO the operand reads of the whole chain are issued up front, so that one LDS latency is exposed
@@ -312,13 +323,13 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
 // With kNeedO every row keeps its candidate for a dominant key (see kCandMargin) out of its sums and
 // reports it with the partial record; the combine step then forms v_cand - o_i without
 // cancellation for every row, and no row ever needs a second pass.
-template <bool kNeedO, typename Lens>
+template <bool kNeedO, bool kStoreZ, typename Lens>
 __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__restrict__ q,
                                                            const uint16_t *__restrict__ k,
                                                            const uint16_t *__restrict__ v, int N, int W, int Hq,
                                                            int Hkv, int ragged, Lens lens, int split_len,
                                                            int n_splits, int m_pad, float *__restrict__ part_ml,
-                                                           float *__restrict__ part_o) {
+                                                           float *__restrict__ part_o, float *__restrict__ z, int z_stride) {
     __shared__ __attribute__((aligned(1024))) char smem[kLdsTiles];
     __shared__ int2 ev_list[kNeedO ? kThreads * kEvents : 1];   // per lane: parked former candidates (token, logit bits)
     int2 *events = ev_list + (kNeedO ? threadIdx.x * kEvents : 0);
@@ -410,19 +421,22 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     const int n_total = (n_blk + 3) & ~3;
     int n_plain = (vis_min + 1 - t_begin) / 32;       // leading blocks every row of this wave sees in full
     n_plain = max(0, min(n_plain, n_blk)) & ~3;
-#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, len - 1, vis, kh, vh, koff, voff, kdoff, vdoff, wave, lane, wave_active, events
+    // (kStoreZ: at most 32 rows, so they are the first wave's)
+    char *z_split = (char *)(z + (size_t)bg * M * z_stride + t_begin);
+    const uint32_t z_off = kStoreZ && row_valid ? (uint32_t)row * z_stride * 4 + 16 * half : ~0u;
+#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, len - 1, vis, kh, vh, koff, voff, kdoff, vdoff, wave, lane, wave_active, events, z_split, z_off
     int n = 0;
     for (; n < n_plain; n += 4) {
-        sweep1_step<0, false, kNeedO>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<1, false, kNeedO>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<2, false, kNeedO>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<3, false, kNeedO>(R, OBC_S1_ARGS); n -= 3;
+        sweep1_step<0, false, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<1, false, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<2, false, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<3, false, kNeedO, kStoreZ>(R, OBC_S1_ARGS); n -= 3;
     }
     for (; n < n_total; n += 4) {
-        sweep1_step<0, true, kNeedO>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<1, true, kNeedO>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<2, true, kNeedO>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<3, true, kNeedO>(R, OBC_S1_ARGS); n -= 3;
+        sweep1_step<0, true, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<1, true, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<2, true, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<3, true, kNeedO, kStoreZ>(R, OBC_S1_ARGS); n -= 3;
     }
 #undef OBC_S1_ARGS
     // A final candidate that holds less than half of its own split's weight cannot dominate the
@@ -1042,6 +1056,158 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__res
     }
 }
 
+// Second sweep for at most kFewRows window rows per KV head (a one-row window, typically): the logits were kept by the
+// first sweep, so only V is read again.  Grid: x = token range, y = (b, KV head); a wave takes 64 tokens at a time in four
+// tiles of 16.
+//
+// One 16x16x32 matrix op takes 16 tokens and all rows at once: rows 0-7 of its A operand are the high pieces of the
+// (scaled) o^_i, rows 8-15 the low ones, so their products meet in lanes l and l ^ 32.  V goes from memory straight into
+// the B operand (a tile's instruction reads 64 bytes of each of 16 rows), no LDS.  Bound by the read of V: 4 x 8 x 32768
+// tokens, G = 4, joint: 109 us for the second sweep over K and V, FEW_US for this.
+constexpr int kFewRows = 8;
+constexpr int kFewTiles = 4;
+
+template <int kVariant, typename Lens>
+__global__ __launch_bounds__(kThreads, 2) void score_few_rows(const uint16_t *__restrict__ v, int N, int M, int Hkv, int ragged,
+                                                              Lens lens, int range_len, int m_pad,
+                                                              const float *__restrict__ z, int z_stride,
+                                                              const uint16_t *__restrict__ out_bf16, size_t lo_plane,
+                                                              const float *__restrict__ row_const,
+                                                              const float *__restrict__ special,
+                                                              float *__restrict__ dst, size_t variant_stride, int accumulate) {
+    constexpr bool kDoV = kVariant == OBC_VALUE || kVariant == OBC_ALL;
+    constexpr bool kDoK = kVariant == OBC_KEY || kVariant == OBC_ALL;
+    constexpr bool kDoJ = kVariant == OBC_JOINT || kVariant == OBC_ALL;
+    constexpr bool kDoA = kVariant == OBC_ATTN || kVariant == OBC_VATP;
+    constexpr bool kNeedVO = kDoK || kDoJ, kNeedV = kVariant != OBC_ATTN;
+    const float c2x2 = 2.0f * kLog2e * kInvSqrtD;
+    const int bg = blockIdx.y, len = seq_len_of(lens, ragged, bg / Hkv, N);
+    const int t_begin = blockIdx.x * range_len, t_stop = min(t_begin + range_len, N), t_end = min(t_stop, len);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, j = lane >> 4;
+    float *out = dst + (size_t)bg * N;
+    if (!accumulate)
+        for (int t = max(t_begin, len) + (int)threadIdx.x; t < t_stop; t += kThreads)       // the padding
+#pragma unroll
+            for (int c = 0; c < (kVariant == OBC_ALL ? 3 : 1); ++c) out[c * variant_stride + t] = 0.f;
+    if (t_begin >= t_end) return;                            // uniform
+
+    const uint16_t *vg = v + (size_t)bg * N * kD;
+    const size_t cbase = (size_t)bg * m_pad;
+    // This lane's two rows, and with them its share of the epilogue.
+    const int row0 = 4 * (j & 1) + 2 * (j >> 1);
+    const float *z0 = z + ((size_t)bg * M + min(row0, M - 1)) * z_stride, *z1 = z + ((size_t)bg * M + min(row0 + 1, M - 1)) * z_stride;
+    bf16x8 vb[2][kFewTiles][4];
+    float zz[2][kFewTiles][2];
+    auto fetch = [&](int slot, int t0) {
+#pragma unroll
+        for (int i = 0; i < kFewTiles; ++i) {
+            const int t = min(t0 + 16 * i + n, t_end - 1);   // (tokens past the end repeat the last one and are not written)
+            if (kNeedV)
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) vb[slot][i][kk] = *(const bf16x8 *)(vg + (size_t)t * kD + kk * 32 + j * 8);
+            zz[slot][i][0] = z0[t];
+            zz[slot][i][1] = z1[t];
+        }
+    };
+    int t0 = t_begin + wave * 64;
+    if (t0 < t_end) fetch(0, t0);
+
+    bf16x8 o[4];
+    if (kNeedVO) {
+        const int row = n & 7;
+        const uint16_t *src = out_bf16 + (n < 8 ? 0 : lo_plane) + (cbase + min(row, M - 1)) * kD + j * 8;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) o[kk] = row < M ? *(const bf16x8 *)(src + kk * 32) : bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    }
+    float c_m2[2], c_oo[2], sp[2][3];
+    int vis[2], excl[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const bool ok = row0 + i < M;
+        const float4 rc = ok ? ((const float4 *)row_const)[cbase + row0 + i] : make_float4(1e30f, 0.f, __int_as_float(-1), 0.f);
+        const float4 s = ok && kNeedVO ? ((const float4 *)special)[cbase + row0 + i] : make_float4(__int_as_float(-1), 0.f, 0.f, 0.f);
+        c_m2[i] = rc.x; c_oo[i] = rc.y; vis[i] = __float_as_int(rc.z);
+        excl[i] = __float_as_int(s.x);
+        const bool none = excl[i] < 0;                       // (the terms are not written then)
+        sp[i][0] = none ? 0.f : s.y; sp[i][1] = none ? 0.f : s.z; sp[i][2] = none ? 0.f : s.w;
+    }
+
+    auto score = [&](int slot, int t0) {
+        float sum_v = 0.f, sum_k = 0.f, sum_j = 0.f;         // of token t0 + lane
+#pragma unroll
+        for (int i = 0; i < kFewTiles; ++i) {
+            f32x4 vo = {0.f, 0.f, 0.f, 0.f};
+            float vv = 0.f;
+            if (kNeedV)
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) {
+                    if (kVariant == OBC_VATP) vv = sumabs8(vb[slot][i][kk], vv);
+                    else vv = sumsq8(vb[slot][i][kk], vv);
+                    if (kNeedVO) vo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o[kk], vb[slot][i][kk], vo, 0, 0, 0);
+                }
+            if (kNeedV) vv = across_rows<SumOp>(vv);
+            const int tok = t0 + 16 * i + n;
+            float a_v = 0.f, a_k = 0.f, a_j = 0.f;
+            // high and low pieces meet: rows 4 (j & 1) + r
+            float w[4];
+            if (kNeedVO)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float lo, hi;
+                    both_of_pair<32>(vo[r], lo, hi);
+                    w[r] = lo + hi;
+                }
+            const float vv7 = vv * kCrossScale, vv2s = vv * (2.0f * kInvSqrtD);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float x = zz[slot][i][h];
+                float a2 = kDoA ? __builtin_amdgcn_exp2f(fmaf(x, 0.5f * c2x2, -0.5f * c_m2[h]))
+                                : __builtin_amdgcn_exp2f(fmaf(x, c2x2, -c_m2[h]));
+                if (tok > vis[h]) a2 = 0.f;
+                const bool apart = kNeedVO && tok == excl[h];          // scored by the combine step
+                if (kDoV || kDoA) a_v += apart ? 0.f : a2;
+                if (kNeedVO) {                                         // (as in sweep2_step)
+                    const float cross = j < 2 ? w[h] : w[2 + h];
+                    const float w7 = (vv7 + c_oo[h]) + cross;
+                    if (kDoK) a_k += apart ? sp[h][1] : a2 * x * x * w7;
+                    if (kDoJ) {
+                        const float g = fmaf(x, w7, fmaf(cross, kSqrtD, vv2s));
+                        a_j += apart ? sp[h][2] : a2 * fmaf(x, g, vv);
+                    }
+                }
+            }
+            if (kDoV || kVariant == OBC_VATP) {
+                a_v *= vv;
+                if (kDoV && kNeedVO)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) a_v += tok == excl[h] ? sp[h][0] : 0.f;
+            }
+            if (kDoV || kDoA) { a_v = across_rows<SumOp>(a_v); sum_v = j == i ? a_v : sum_v; }
+            if (kDoK) { a_k = fmaxf(across_rows<SumOp>(a_k), 0.f); sum_k = j == i ? a_k : sum_k; }
+            if (kDoJ) { a_j = fmaxf(across_rows<SumOp>(a_j), 0.f); sum_j = j == i ? a_j : sum_j; }
+        }
+        const int t = t0 + lane;                             // tile j, token n of it
+        if (t < t_end) {
+            int c = 0;
+            auto put = [&](float x) {
+                float *d = out + (c++) * variant_stride + t;
+                *d = accumulate ? *d + x : x;
+            };
+            if (kDoV || kDoA) put(sum_v);
+            if (kDoK) put(sum_k);
+            if (kDoJ) put(sum_j);
+        }
+    };
+    constexpr int kStep = kThreads;                          // tokens the workgroup takes at a time
+    for (; t0 < t_end; t0 += 2 * kStep) {                    // two buffers, both with constant indices
+        if (t0 + kStep < t_end) fetch(1, t0 + kStep);
+        score(0, t0);
+        if (t0 + kStep >= t_end) break;
+        if (t0 + 2 * kStep < t_end) fetch(0, t0 + 2 * kStep);
+        score(1, t0 + kStep);
+    }
+}
+
 // scores[c][idx] = sum over chunks of planes[chunk][c][idx], in chunk order.
 __global__ __launch_bounds__(256) void mfma_sum_planes(const float *__restrict__ planes, int n_chunks,
                                                        size_t chunk_stride, size_t total, float *__restrict__ scores,
@@ -1061,7 +1227,13 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
     float *dst = ws.n_chunks > 1 ? (float *)(base + ws.planes) : a.scores;
     const size_t chunk_stride = ws.n_chunks > 1 ? plane_elems * nv : 0;
     const dim3 grid((a.N + ws.range_len - 1) / ws.range_len, ws.n_chunks, a.B * a.Hkv);
-    if (ws.use_wide) {
+    if (ws.keep_z) {
+        score_few_rows<kVariant><<<dim3(grid.x, a.B * a.Hkv), dim3(kThreads), 0, stream>>>(
+            (const uint16_t *)a.v, a.N, a.G * a.W, a.Hkv, a.ragged, lens, ws.range_len, ws.m_pad, (const float *)(base + ws.z),
+            ws.z_stride, (const uint16_t *)(base + ws.out_bf16), (size_t)a.B * a.Hkv * ws.m_pad * kD, (const float *)(base + ws.row_const),
+            (const float *)(base + ws.special), dst, plane_elems, a.accumulate);
+        e = hipGetLastError();
+    } else if (ws.use_wide) {
         e = launch_sweep2_wide(a, ws, base, dst, plane_elems, chunk_stride, stream);
     } else {
         mfma_sweep2<kVariant><<<grid, dim3(kThreads), 0, stream>>>(
@@ -1080,7 +1252,7 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
 
 }  // namespace
 
-void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWorkspace *ws, size_t *off) {
+void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv;
     const int nv = variant == OBC_ALL ? 3 : 1;
@@ -1110,6 +1282,20 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     ws->part_o = *off;    *off = align_up(*off + rows * ws->splits * d * sizeof(float), 256);
     ws->planes = *off;
     if (ws->n_chunks > 1) *off = align_up(*off + (size_t)ws->n_chunks * nv * BH * N * sizeof(float), 256);
+    // With few rows the first sweep keeps their logits (4 bytes per pair) and the second reads them instead of K (256 bytes
+    // per token): beyond eight rows the gain fades.
+    const int M = Hq / Hkv * W;
+    ws->z_stride = (N + 31) / 32 * 32;
+    const size_t z_bytes = (size_t)BH * M * ws->z_stride * sizeof(float);
+    ws->keep_z = M <= kFewRows && *off + z_bytes <= cap && (long long)M * ws->z_stride < (1LL << 29) ? 1 : 0;    // (32-bit offsets)
+    if (ws->keep_z) {
+        ws->z = *off;
+        *off = align_up(*off + z_bytes, 256);
+        ws->use_wide = 0;
+        // Whole workgroup steps of 256 tokens; four workgroups per CU at least, where there are that many.
+        const long long r = ((long long)N * BH + 1023) / 1024;
+        ws->range_len = (int)(r < 512 ? 256 : (r > 4096 ? 4096 : r / 256 * 256));
+    }
 }
 
 template <typename Lens>
@@ -1119,14 +1305,15 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
     hipError_t e = hipSuccess;
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
         const dim3 grid(ws.splits, ws.n_chunks, a.B * a.Hkv);
-        if (need_o)
-            mfma_sweep1<true><<<grid, dim3(kThreads), 0, stream>>>(
-                (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged,
-                lens, ws.split_len, ws.splits, ws.m_pad, part_ml, part_o);
-        else
-            mfma_sweep1<false><<<grid, dim3(kThreads), 0, stream>>>(
-                (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged,
-                lens, ws.split_len, ws.splits, ws.m_pad, part_ml, part_o);
+#define OBC_SWEEP1(need_o, store_z)                                                                                    \
+    mfma_sweep1<need_o, store_z><<<grid, dim3(kThreads), 0, stream>>>(                                                 \
+        (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens,      \
+        ws.split_len, ws.splits, ws.m_pad, part_ml, part_o, (float *)(base + ws.z), ws.z_stride)
+        if (need_o && ws.keep_z) OBC_SWEEP1(true, true);
+        else if (need_o) OBC_SWEEP1(true, false);
+        else if (ws.keep_z) OBC_SWEEP1(false, true);
+        else OBC_SWEEP1(false, false);
+#undef OBC_SWEEP1
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
