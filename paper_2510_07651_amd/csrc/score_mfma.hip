@@ -1109,8 +1109,12 @@ __global__ __launch_bounds__(kThreads, 2) void score_few_rows(const uint16_t *__
             zz[slot][i][1] = z1[t];
         }
     };
-    int t0 = t_begin + wave * 64;
-    if (t0 < t_end) fetch(0, t0);
+    // From the end of the range to its start: the first sweep read the ends of its splits last, and what it read last is
+    // what the memory-side cache still holds.
+    constexpr int kStep = kThreads;                          // tokens the workgroup takes at a time
+    int t0 = t_begin + (t_end - t_begin - 1) / kStep * kStep + wave * 64;
+    if (t0 >= t_end) t0 -= kStep;
+    if (t0 >= t_begin) fetch(0, t0);
 
     bf16x8 o[4];
     if (kNeedVO) {
@@ -1198,13 +1202,12 @@ __global__ __launch_bounds__(kThreads, 2) void score_few_rows(const uint16_t *__
             if (kDoJ) put(sum_j);
         }
     };
-    constexpr int kStep = kThreads;                          // tokens the workgroup takes at a time
-    for (; t0 < t_end; t0 += 2 * kStep) {                    // two buffers, both with constant indices
-        if (t0 + kStep < t_end) fetch(1, t0 + kStep);
+    for (; t0 >= t_begin; t0 -= 2 * kStep) {                 // two buffers, both with constant indices
+        if (t0 - kStep >= t_begin) fetch(1, t0 - kStep);
         score(0, t0);
-        if (t0 + kStep >= t_end) break;
-        if (t0 + 2 * kStep < t_end) fetch(0, t0 + 2 * kStep);
-        score(1, t0 + kStep);
+        if (t0 - kStep < t_begin) break;
+        if (t0 - 2 * kStep >= t_begin) fetch(0, t0 - 2 * kStep);
+        score(1, t0 - kStep);
     }
 }
 
@@ -1292,9 +1295,8 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, size_t 
         ws->z = *off;
         *off = align_up(*off + z_bytes, 256);
         ws->use_wide = 0;
-        // Whole workgroup steps of 256 tokens; four workgroups per CU at least, where there are that many.
-        const long long r = ((long long)N * BH + 1023) / 1024;
-        ws->range_len = (int)(r < 512 ? 256 : (r > 4096 ? 4096 : r / 256 * 256));
+        // The first sweep's splits, in whole workgroup steps of 256 tokens (see score_few_rows for the order inside).
+        ws->range_len = (int)align_up(ws->split_len, 256);
     }
 }
 
