@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
 #pragma unroll
         for (int r = 0; r < 4 && r0 + r < kG; ++r) {
             m[r0 + r] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(bm), 16 * r));
-            top[r0 + r] = __builtin_amdgcn_readlane((int)at, 16 * r);
+            top[r0 + r] = min(__builtin_amdgcn_readlane((int)at, 16 * r), t1 - 1);   // (no logit was a number: any token)
         }
     }
 

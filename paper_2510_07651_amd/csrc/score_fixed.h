@@ -1,0 +1,624 @@
+// Part of score_plain.hip: its logits, weights and scores for more than 32 window rows per KV head.
+//
+// The fp64 matrix cores do 79 TFLOP/s and the fp32 ones 157, the 8-bit integer ones 5000 and the bf16 ones 2500, so the
+// contractions are taken apart into pieces the fast ones multiply exactly.
+//
+// Dot products (fixed_logits, fixed_score).  Each row of q, k, v and o is scaled by a power of two to fixed point, 38 bits
+// and a sign relative to the row's largest element (30 for bf16 inputs, whose elements have 8 significant bits), and
+// written as five (four) balanced base-256 digits, |digit| <= 128.  Products of digits are summed exactly in 32-bit
+// integers; pairs of digits beyond the fifth level are left out, and the levels are put together in fp64.  A dot product
+// is off by a few parts in 2^36 of |x|max |y|max before it is rounded to fp32: far below that rounding unless the sum
+// cancels to less than 2^-10 of its terms.  Where it does, in ||v_p - o_i||^2 of a v_p that is nearly o_i, the squares are
+// formed directly.  Fifteen integer ops replace 128 fp64 ones.
+//
+// P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each (exact), products of pieces down to 2^-18 of the
+// leading one (what is left out is below an fp32 rounding), fp32 accumulation: six bf16 ops (three for bf16 values, where
+// nothing is left out) replace sixteen fp32 ones.
+//
+// What bounds them: the vector ALUs.  Taking an element apart costs about 15 instructions (7 for bf16), paid once per
+// workgroup of up to 128 rows, and putting a dot product together about 12; below 33 rows the fp64 kernels are as fast.
+// fp32, 32/8 heads, d = 128, 8111 tokens, joint: FIXED_TIMES
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+
+template <typename T> constexpr int kDigits = sizeof(T) == 4 ? 5 : 4;
+constexpr int kRowDigits = 5;                  // of o_i, which is fp32 whatever the inputs are
+constexpr int kLevels = 5;
+
+// Maximum that lets a NaN through.
+struct MaximumOp { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_elementwise_maximum(a, b); } };
+__device__ __forceinline__ float max_abs(const float (&x)[4], float m) {
+    const MaximumOp op;
+    return op(op(op(op(m, fabsf(x[0])), fabsf(x[1])), fabsf(x[2])), fabsf(x[3]));
+}
+// Exponent e with |x|max < 2^e, kept where its scale is a normal number (a smaller maximum only loses bits no product shows).
+__device__ __forceinline__ int max_exponent(float amax) { return max((int)(__float_as_uint(amax) >> 23 & 255) - 126, -96); }
+// 2^(30 - e), which turns an element into its fixed-point integer ...
+__device__ __forceinline__ float digit_scale(int e) { return __uint_as_float((uint32_t)(157 - e) << 23); }
+// ... and 2^(e - 18), a row's share of the unit of a dot product; NaN where an element was infinite or not a number.
+__device__ __forceinline__ double row_unit(int e) { return e > 128 ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, e - 18); }
+
+// The digits of four elements, most significant first, one byte per element: 128 added to every digit of the fixed-point
+// integer makes its bytes the digits plus 128, carries included.
+template <int K>
+__device__ __forceinline__ void digits_of(const float (&x)[4], float scale, uint32_t (&plane)[K]) {
+    uint32_t w[4], low[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float y = x[i] * scale, h = rintf(y);           // |y| <= 2^30; both exact
+        w[i] = (uint32_t)(int)h + 0x80808080u;
+        if (K == 5) {
+            const uint32_t l = __float_as_uint(fmaf(y - h, 256.f, 12582912.f + 128.f)) & 511u;     // 0 .. 256
+            w[i] += l >> 8;
+            low[i] = l & 255u;
+        }
+    }
+    const uint32_t t0 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602), t1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602);
+    const uint32_t u0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400), u1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400);
+    plane[0] = __builtin_amdgcn_perm(t1, t0, 0x07060302) ^ 0x80808080u;
+    plane[1] = __builtin_amdgcn_perm(t1, t0, 0x05040100) ^ 0x80808080u;
+    plane[2] = __builtin_amdgcn_perm(u1, u0, 0x07060302) ^ 0x80808080u;
+    plane[3] = __builtin_amdgcn_perm(u1, u0, 0x05040100) ^ 0x80808080u;
+    if (K == 5) plane[K - 1] = (low[0] | low[1] << 8 | low[2] << 16 | low[3] << 24) ^ 0x80808080u;
+}
+
+// x . y of the two fixed-point vectors from the level sums, in units of row_unit(ex) row_unit(ey).
+__device__ __forceinline__ double join_levels(int l0, int l1, int l2, int l3, int l4) {
+    const int hi = (l0 << 8) + l1, lo = (l2 << 8) + l3 + (l4 >> 8);      // (at most 2^27 and 2^31: |digit| <= 128, the first one <= 64)
+    return fma((double)hi, 65536.0, (double)lo);
+}
+
+// Rows of digits in LDS, kTok rows x K planes of D bytes.  A row's 16-byte piece c sits at slot c ^ f(row), so that the 16
+// lanes of a read (same piece of 16 consecutive rows) touch every bank once.
+template <int D, int kTok>
+__device__ __forceinline__ int digit_offset(int plane, int row, int c) {
+    const int slot = D == 128 ? c ^ (row >> 1 & 7) : c ^ (row >> 2 & 3);
+    return (plane * kTok + row) * D + slot * 16;
+}
+
+// A span of memory by its bounds: loads beyond its end give zeros.  (One 32-bit address per lane instead of two words per
+// load; the workspace's cap keeps a workgroup's span far below 4 GB.)
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t span_of(const void *p, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)bytes, 0x00027000);
+}
+
+// ------------------------------------------------------------------------------------
+// Token tiles: kTok rows of k or v on their way from memory into LDS.
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int kTok>
+struct TokenTile {
+    static constexpr int kPer = 16 / (int)sizeof(T);                     // elements of a 16-byte piece
+    static constexpr int kLanes = D / kPer;                              // lanes per row
+    static constexpr int kCount = kTok * kLanes / kThreads;
+    static_assert(kTok * kLanes % kThreads == 0, "whole pieces per thread");
+    uint4 x[kCount];
+
+    __device__ __forceinline__ int row(int i) const { return ((int)threadIdx.x + i * kThreads) / kLanes; }
+    __device__ __forceinline__ int piece() const { return (int)threadIdx.x % kLanes; }
+    // Rows from row t of the span; rows beyond its end become zeros.
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t span, int t) {
+#pragma unroll
+        for (int i = 0; i < kCount; ++i) {
+            const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(span, (t * kLanes + (int)threadIdx.x + i * kThreads) * 16, 0, 0);
+            x[i] = make_uint4(u.x, u.y, u.z, u.w);
+        }
+    }
+    __device__ __forceinline__ void unpack(int i, float (&y)[kPer / 4][4]) const {
+        if constexpr (sizeof(T) == 4) {
+            y[0][0] = __uint_as_float(x[i].x); y[0][1] = __uint_as_float(x[i].y);
+            y[0][2] = __uint_as_float(x[i].z); y[0][3] = __uint_as_float(x[i].w);
+        } else {
+            y[0][0] = __uint_as_float(x[i].x << 16); y[0][1] = __uint_as_float(x[i].x & 0xffff0000u);
+            y[0][2] = __uint_as_float(x[i].y << 16); y[0][3] = __uint_as_float(x[i].y & 0xffff0000u);
+            y[1][0] = __uint_as_float(x[i].z << 16); y[1][1] = __uint_as_float(x[i].z & 0xffff0000u);
+            y[1][2] = __uint_as_float(x[i].w << 16); y[1][3] = __uint_as_float(x[i].w & 0xffff0000u);
+        }
+    }
+    // Over the lanes of a row.
+    template <typename Op, typename F>
+    static __device__ __forceinline__ F over_row(F v) {
+        const Op op;
+        v = op(v, dpp_pair<0xB1>(v));
+        v = op(v, dpp_pair<0x4E>(v));
+        v = op(v, dpp_pair<0x141>(v));
+        if (kLanes >= 16) v = op(v, dpp_pair<0x140>(v));
+        if (kLanes == 32) {
+            F a, b;
+            both_of_pair<16>(v, a, b);
+            v = op(a, b);
+        }
+        return v;
+    }
+    // Digits and units into LDS, with kNorms also the rows' squared norms.
+    template <bool kNorms, bool kDigitsToo = true>
+    __device__ __forceinline__ void store_digits(char *digits, double *units, double *vv) const {
+        constexpr int K = kDigits<T>;
+#pragma unroll
+        for (int i = 0; i < kCount; ++i) {
+            float y[kPer / 4][4];
+            unpack(i, y);
+            const int r = row(i);
+            if constexpr (kDigitsToo) {
+                float amax = 0.f;
+#pragma unroll
+                for (int q = 0; q < kPer / 4; ++q) amax = max_abs(y[q], amax);
+                const int e = max_exponent(over_row<MaximumOp>(amax));
+                const float scale = digit_scale(e);
+                uint32_t p[kPer / 4][K];
+#pragma unroll
+                for (int q = 0; q < kPer / 4; ++q) digits_of<K>(y[q], scale, p[q]);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    if constexpr (kPer == 4) *(uint32_t *)(digits + digit_offset<D, kTok>(k, r, piece() >> 2) + (piece() & 3) * 4) = p[0][k];
+                    else *(uint2 *)(digits + digit_offset<D, kTok>(k, r, piece() >> 1) + (piece() & 1) * 8) = make_uint2(p[0][k], p[1][k]);
+                }
+                if (piece() == 0) units[r] = row_unit(e);
+            }
+            if (kNorms) {
+                double s = 0.0;
+#pragma unroll
+                for (int q = 0; q < kPer / 4; ++q)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) s = fma((double)y[q][c], (double)y[q][c], s);
+                s = over_row<SumOp>(s);
+                if (piece() == 0) vv[r] = s;
+            }
+        }
+    }
+};
+
+// ------------------------------------------------------------------------------------
+// Rows of q as digits in memory: [row][K][D] bytes and a unit per row.  Four elements per lane.
+// ------------------------------------------------------------------------------------
+template <typename T, int D>
+__global__ __launch_bounds__(kThreads) void fixed_rows(const T *__restrict__ q, int W, int Hq, int Hkv, Piece w,
+                                                       int8_t *__restrict__ digits, double *__restrict__ units) {
+    constexpr int K = kDigits<T>, kLanes = D / 4;
+    const int row = ((int)blockIdx.x * kThreads + (int)threadIdx.x) / kLanes, c = threadIdx.x % kLanes, hl = blockIdx.z;
+    const int bg = w.bg0 + hl, M = Hq / Hkv * W;
+    const T *src = q + ((size_t)(bg / Hkv) * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D + c * 4;
+    float x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = load_as_float(src + i);
+    using Tile = TokenTile<float, D, 64>;                    // (four elements per lane: its lane layout)
+    const int e = max_exponent(Tile::template over_row<MaximumOp>(max_abs(x, 0.f)));
+    uint32_t p[K];
+    digits_of<K>(x, digit_scale(e), p);
+    if (row >= w.nr) return;
+    const size_t at = (size_t)hl * w.nr + row;
+#pragma unroll
+    for (int k = 0; k < K; ++k) *(uint32_t *)(digits + (at * K + k) * D + c * 4) = p[k];
+    if (c == 0) units[at] = row_unit(e);
+}
+
+// A wave's 32 rows of digits as a matrix operand: lane = row + 32 half holds bytes 16 half .. 16 half + 15 of every 32.
+template <int K, int D>
+struct RowDigits {
+    i32x4 x[K][D / 32];
+    __device__ __forceinline__ void load(const int8_t *__restrict__ digits, size_t at, bool live, int half) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int kk = 0; kk < D / 32; ++kk)
+                x[k][kk] = live ? *(const i32x4 *)(digits + (at * K + k) * D + kk * 32 + half * 16) : i32x4{0, 0, 0, 0};
+    }
+};
+
+// Buffers of a tile: two where two workgroups fit a CU with them, else one (and a barrier more per tile).
+constexpr int buffers_of(int bytes) { return bytes <= 36 * 1024 ? 2 : 1; }
+
+// Level sums of 32 rows against 32 tokens in LDS.  kRowsFirst: accumulator rows are window rows and lanes are tokens.
+template <int KR, int KT, int D, int kTok, bool kRowsFirst>
+__device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const char *digits, int tok, int half, i32x16 (&acc)[kLevels]) {
+#pragma unroll
+    for (int t = 0; t < kLevels; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0;
+#pragma unroll
+    for (int kk = 0; kk < D / 32; ++kk) {
+        i32x4 b[KT];
+#pragma unroll
+        for (int k = 0; k < KT; ++k) b[k] = *(const i32x4 *)(digits + digit_offset<D, kTok>(k, tok, 2 * kk + half));
+#pragma unroll
+        for (int k = 0; k < KT; ++k)
+#pragma unroll
+            for (int i = 0; i < KR && i + k < kLevels; ++i)
+                acc[i + k] = kRowsFirst ? __builtin_amdgcn_mfma_i32_32x32x32_i8(rows.x[i][kk], b[k], acc[i + k], 0, 0, 0)
+                                        : __builtin_amdgcn_mfma_i32_32x32x32_i8(b[k], rows.x[i][kk], acc[i + k], 0, 0, 0);
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// Logits.  Grid: x = token range of the piece, y = chunk of 32 kRb rows, z = KV head.  Wave w takes row block w % kRb and
+// token block w / kRb of every tile; lane = row (and half), registers = tokens.
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int kRb, typename Lens>
+__global__ __launch_bounds__(kThreads, 2) void fixed_logits(const int8_t *__restrict__ q_digits, const double *__restrict__ q_units,
+                                                            const T *__restrict__ k, int N, int W, int Hkv, int ragged, Lens lens,
+                                                            Piece w, int range_len, int n_ranges, float *__restrict__ z,
+                                                            float2 *__restrict__ range_best) {
+    constexpr int K = kDigits<T>, kTok = 32 * 4 / kRb, kBuf = buffers_of(K * kTok * D);
+    __shared__ __attribute__((aligned(16))) char digits[kBuf][K * kTok * D];
+    __shared__ __attribute__((aligned(16))) double units[2][kTok];
+    __shared__ float2 best_s[4][32];
+    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
+    const int len = seq_len_of(lens, ragged, b, N);
+    const int range = w.s0 / range_len + blockIdx.x;
+    const int t_begin = range * range_len, t_end = min(min(t_begin + range_len, w.s1), len);
+    if (t_begin >= t_end) return;                            // uniform
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
+    const int rb = wave % kRb, tb = wave / kRb;
+    const int row = ((int)blockIdx.y * kRb + rb) * 32 + (lane & 31);
+    const bool live = row < w.nr;
+    const __amdgpu_buffer_rsrc_t kg = span_of(k + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
+    TokenTile<T, D, kTok> next;
+    next.load(kg, 0);
+    RowDigits<K, D> rows;
+    rows.load(q_digits, (size_t)hl * w.nr + min(row, w.nr - 1), live, half);
+    const double qu = live ? q_units[(size_t)hl * w.nr + row] * (1.0 / sqrt((double)D)) : 0.0;
+    const int last = live ? len - W + (w.r0 + row) % W : -1;             // last token the row sees
+    float *zp = z + ((size_t)hl * w.nr + row) * w.z_stride - w.s0;
+    float m = -INFINITY;
+    int at = kNoToken;
+    next.template store_digits<false>(digits[0], units[0], nullptr);
+    if (t_begin + kTok < t_end) next.load(kg, kTok);
+    int slot = 0;
+    for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
+        __syncthreads();                                     // this tile is in LDS, the one before it has been read
+        i32x16 acc[kLevels];
+        level_sums<K, K, D, kTok, false>(rows, digits[slot % kBuf], tb * 32 + (lane & 31), half, acc);
+        if (kBuf == 1) __syncthreads();
+        if (t0 + kTok < t_end) next.template store_digits<false>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], nullptr);
+        if (t0 + 2 * kTok < t_end) next.load(kg, t0 - t_begin + 2 * kTok);
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int p0 = tb * 32 + 8 * r4 + 4 * half;      // in the tile
+            const double2 u01 = *(const double2 *)(units[slot] + p0), u23 = *(const double2 *)(units[slot] + p0 + 2);
+            const double ku[4] = {u01.x, u01.y, u23.x, u23.y};
+            float x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = 4 * r4 + i;
+                const double dot = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
+                x[i] = (float)(dot * ku[i] * qu);                // scaled logit
+                const int p = t0 + p0 + i;
+                if (p <= last && p < t_end && x[i] > m) { m = x[i]; at = p; }   // (tokens ascend: strict keeps the lowest)
+            }
+            if (live) *(float4 *)(zp + t0 + p0) = make_float4(x[0], x[1], x[2], x[3]);       // (rows of z have room for whole tiles)
+        }
+    }
+    {
+        float m0, m1;
+        uint32_t a0, a1;
+        both_of_pair<32>(m, m0, m1);
+        both_of_pair<32>((uint32_t)at, a0, a1);
+        const bool second = m1 > m0 || (m1 == m0 && a1 < a0);
+        if (half == 0) best_s[wave][lane] = make_float2(second ? m1 : m0, __int_as_float((int)(second ? a1 : a0)));
+    }
+    __syncthreads();
+    if (tb == 0 && half == 0 && live) {
+        float2 best = best_s[wave][lane];
+#pragma unroll
+        for (int c = 1; c < 4 / kRb; ++c) {
+            const float2 o = best_s[wave + c * kRb][lane];
+            if (o.x > best.x || (o.x == best.x && __float_as_int(o.y) < __float_as_int(best.y))) best = o;
+        }
+        range_best[((size_t)hl * w.nr + row) * n_ranges + range] = best;
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// Weights and P V.  Grid: x = split of the piece, y = chunk of 32 kRb rows, z = KV head.  Lane = row (and half);
+// O^T += V^T P^T.  The token blocks of a tile (4 / kRb of them) are splits of their own.
+// ------------------------------------------------------------------------------------
+// V pieces in LDS: kP planes of kTok rows of D bf16.  A row's 16-byte piece c sits where the transposing read (16 lanes fetch
+// 8 bytes each of four consecutive tokens, 32 lanes 64 contiguous bytes of them) meets every bank once.
+template <int D, int kTok>
+__device__ __forceinline__ int value_offset(int plane, int tok, int c) {
+    const int slot = D == 128 ? (c + 4 * (tok & 3)) & 15 : (c + 4 * (tok >> 1 & 1)) & 7;
+    return (plane * kTok + tok) * D * 2 + slot * 16;
+}
+
+// Two elements as three bf16 pieces each, rounded to nearest and each remainder exact (9 + 9 + 8 bits and more hold the 24).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void three_pieces(float a, float b, uint32_t (&p)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const bf16x2 r = __builtin_convertvector((f32x2{a, b}), bf16x2);     // v_cvt_pk_bf16_f32
+        p[i] = *(const uint32_t *)&r;
+        a -= __uint_as_float(p[i] << 16);
+        b -= __uint_as_float(p[i] & 0xffff0000u);
+    }
+}
+
+template <typename T, int D, int kRb, bool kNeedO, typename Lens>
+__global__ __launch_bounds__(kThreads, 2) void fixed_weights(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
+                                                             Piece w, int range_len, int n_ranges, int split_len, int n_splits,
+                                                             const float *__restrict__ z, const float2 *__restrict__ range_best,
+                                                             RowRecord *__restrict__ records, float *__restrict__ part_l,
+                                                             float *__restrict__ part_o) {
+    constexpr int kTb = 4 / kRb, kTok = 32 * kTb, kP = sizeof(T) == 4 ? 3 : 1, kRows = 32 * kRb,
+                  kBuf = buffers_of(kP * kTok * D * 2);
+    __shared__ __attribute__((aligned(16))) char values[kBuf][kNeedO ? kP * kTok * D * 2 : 16];
+    __shared__ float m_s[kRows];
+    __shared__ int top_s[kRows];
+    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
+    const int len = seq_len_of(lens, ragged, b, N);
+    const int split = w.s0 / split_len + blockIdx.x;
+    const int t_begin = split * split_len, t_end = min(min(t_begin + split_len, w.s1), len);
+    if (t_begin >= t_end) return;                            // uniform
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
+    const int rb = wave % kRb, tb = wave / kRb, row0 = blockIdx.y * kRows;
+    const __amdgpu_buffer_rsrc_t vg = span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
+    TokenTile<T, D, kTok> next;
+    if (kNeedO) next.load(vg, 0);
+    {
+        constexpr int kSub = kThreads / kRows;               // the row's maximum over its ranges: kSub lanes per row
+        const int row = threadIdx.x / kSub, live = (len + range_len - 1) / range_len;
+        float m = -INFINITY;
+        int at = kNoToken;
+        if (row0 + row < w.nr)
+#pragma unroll 8
+            for (int i = threadIdx.x % kSub; i < live; i += kSub) {
+                const float2 o = range_best[((size_t)hl * w.nr + row0 + row) * n_ranges + i];
+                if (o.x > m || (o.x == m && __float_as_int(o.y) < at)) { m = o.x; at = __float_as_int(o.y); }
+            }
+        lanes_best<kSub>(m, at);
+        if (threadIdx.x % kSub == 0) {
+            m_s[row] = m;
+            top_s[row] = at;
+            if (split == 0 && row0 + row < w.nr) {
+                RowRecord *rec = records + (size_t)hl * w.nr + row0 + row;
+                rec->m = m;
+                rec->top = at;
+            }
+        }
+    }
+    auto store_values = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < next.kCount; ++i) {
+            if constexpr (kP == 1) {
+                *(uint4 *)(values[slot % kBuf] + value_offset<D, kTok>(0, next.row(i), next.piece())) = next.x[i];
+            } else {
+                float y[1][4];
+                next.unpack(i, y);
+                uint32_t p[2][3];
+                three_pieces(y[0][0], y[0][1], p[0]);
+                three_pieces(y[0][2], y[0][3], p[1]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    *(uint2 *)(values[slot % kBuf] + value_offset<D, kTok>(k, next.row(i), next.piece() >> 1) + (next.piece() & 1) * 8) =
+                        make_uint2(p[0][k], p[1][k]);
+            }
+        }
+    };
+    if (kNeedO) store_values(0);
+    __syncthreads();
+    const int row_l = rb * 32 + (lane & 31), row = row0 + row_l;
+    const float m = row < w.nr ? m_s[row_l] : 0.f;
+    const int top = top_s[row_l];
+    const int last = row < w.nr ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;    // last token the row sees here
+    const float *zp = z + ((size_t)hl * w.nr + min(row, w.nr - 1)) * w.z_stride - w.s0;
+    // This lane's weights of a 16-token step: tokens 4 half + {0..3} and 8 + 4 half + {0..3}, the order of the transposing reads.
+    float4 x[4];
+    auto fetch = [&](int t0) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) x[g] = *(const float4 *)(zp + t0 + tb * 32 + 8 * g + 4 * half);    // (rows of z have room for whole tiles)
+    };
+    fetch(t_begin);
+    if (kNeedO && t_begin + kTok < t_end) next.load(vg, kTok);
+    f32x16 acc[D / 32];
+#pragma unroll
+    for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[d][r] = 0.f;
+    float sum = 0.f;
+    int slot = 0;
+    const int i16 = lane & 15, tok_in4 = i16 >> 2, sub = lane >> 4 & 1;
+    for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
+        if (kNeedO && t0 > t_begin) __syncthreads();         // this tile is in LDS, the one before it has been read
+        union Pieces { bf16x8 v; uint32_t u[4]; } p[2][3];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const float4 f = x[2 * s + g];
+                const float y[4] = {f.x, f.y, f.z, f.w};
+                float e4[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int t = t0 + tb * 32 + 16 * s + 8 * g + 4 * half + i;
+                    e4[i] = t <= last && t != top ? exp_nonpositive(y[i] - m) : 0.f;
+                    sum += e4[i];
+                }
+                uint32_t q[2][3];
+                three_pieces(e4[0], e4[1], q[0]);
+                three_pieces(e4[2], e4[3], q[1]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    p[s][k].u[2 * g] = q[0][k];
+                    p[s][k].u[2 * g + 1] = q[1][k];
+                }
+            }
+        if (t0 + kTok < t_end) fetch(t0 + kTok);
+        auto advance = [&]() {
+            if (t0 + kTok < t_end) store_values(slot ^ 1);
+            if (t0 + 2 * kTok < t_end) next.load(vg, t0 - t_begin + 2 * kTok);
+        };
+        if (!kNeedO) continue;
+        if (kBuf == 2) advance();
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+                for (int k = 0; k < kP; ++k) {
+                    union { bf16x8 v; i16x4 h[2]; } a;
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+                        const int tok = tb * 32 + 16 * s + 8 * g + 4 * half + tok_in4;
+                        const char *src = values[slot % kBuf] + value_offset<D, kTok>(k, tok, d * 4 + sub * 2 + (i16 >> 1 & 1)) + (i16 & 1) * 8;
+                        a.h[g] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(src));
+                    }
+#pragma unroll
+                    for (int j = 0; j + k < 3; ++j)
+                        acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, p[s][j].v, acc[d], 0, 0, 0);
+                }
+        if (kBuf == 1) {
+            __syncthreads();
+            advance();
+        }
+    }
+    const size_t out_row = ((size_t)hl * n_splits * kTb + split * kTb + tb) * w.nr + row;
+    sum = across_halves(sum);
+    if (row >= w.nr) return;
+    if (half == 0) part_l[out_row] = sum;
+    if (!kNeedO) return;
+#pragma unroll
+    for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+            *(float4 *)(part_o + out_row * D + d * 32 + 8 * r4 + 4 * half) =
+                make_float4(acc[d][4 * r4], acc[d][4 * r4 + 1], acc[d][4 * r4 + 2], acc[d][4 * r4 + 3]);
+}
+
+// ------------------------------------------------------------------------------------
+// Scores of Eq. 4, 5, 6.  Grid: x = `n_tiles` tiles of the piece, z = KV head.  Lane = token (and
+// half), registers = rows.  A workgroup takes its tokens against one chunk of rows after the other.
+// ------------------------------------------------------------------------------------
+constexpr int kScoreTokens = 512;              // most tokens of a workgroup
+template <typename T, int D, int kRb, int kVariant, typename Lens>
+__global__ __launch_bounds__(kThreads, 2) void fixed_score(const T *__restrict__ v, int N, int Hkv, int ragged, Lens lens, Piece w,
+                                                           int n_tiles, const float *__restrict__ z,
+                                                           const RowRecord *__restrict__ records,
+                                                           const float *__restrict__ o, const int8_t *__restrict__ o_digits,
+                                                           float *__restrict__ scores, size_t variant_stride, int add) {
+    constexpr int K = kDigits<T>, kTb = 4 / kRb, kTok = 32 * kTb, kRows = 32 * kRb, kBuf = buffers_of(K * kTok * D);
+    constexpr bool kDoV = kVariant == OBC_ALL || kVariant == OBC_VALUE, kDoK = kVariant == OBC_ALL || kVariant == OBC_KEY,
+                   kDoJ = kVariant == OBC_ALL || kVariant == OBC_JOINT, kNeedO = kDoK || kDoJ;
+    __shared__ __attribute__((aligned(16))) char digits[kBuf][kNeedO ? K * kTok * D : 16];
+    __shared__ __attribute__((aligned(16))) double units[2][kTok];
+    __shared__ double vv_s[2][kTok];
+    __shared__ __attribute__((aligned(16))) RowRecord rec_s[kRows];
+    __shared__ float sum_s[2][4][3][32];
+    __shared__ float run_s[kVariant == OBC_ALL ? 3 : 1][kScoreTokens];      // sums over the chunks so far
+    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
+    const int len = seq_len_of(lens, ragged, b, N);
+    const int t_begin = w.s0 + blockIdx.x * n_tiles * kTok, t_stop = min(t_begin + n_tiles * kTok, w.s1), t_end = min(t_stop, len);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
+    const int rb = wave % kRb, tb = wave / kRb;
+    float *out = scores + (size_t)bg * N;
+    if (!add)
+        for (int t = max(t_begin, len) + (int)threadIdx.x; t < t_stop; t += kThreads)        // the padding
+#pragma unroll
+            for (int c = 0; c < (kVariant == OBC_ALL ? 3 : 1); ++c) out[c * variant_stride + t] = 0.f;
+    if (t_begin >= t_end) return;                            // uniform
+    const __amdgpu_buffer_rsrc_t vg = span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
+    const __amdgpu_buffer_rsrc_t zg = span_of(z + (size_t)hl * w.nr * w.z_stride, (size_t)w.nr * w.z_stride * sizeof(float));
+    for (int row0 = 0; row0 < w.nr; row0 += kRows) {
+        TokenTile<T, D, kTok> next;
+        next.load(vg, 0);
+        const int arow = row0 + rb * 32 + (lane & 31);
+        RowDigits<kRowDigits, D> rows;
+        if (kNeedO) rows.load(o_digits, (size_t)hl * w.nr + min(arow, w.nr - 1), arow < w.nr, half);
+        __syncthreads();                                     // (the chunk before this one is done with)
+        for (int i = threadIdx.x; i < kRows; i += kThreads) {
+            RowRecord rec = records[(size_t)hl * w.nr + min(row0 + i, w.nr - 1)];
+            if (row0 + i >= w.nr) rec.last = -1;             // no such row: it sees nothing
+            rec_s[i] = rec;
+        }
+        next.template store_digits<true, kNeedO>(digits[0], units[0], vv_s[0]);
+        if (t_begin + kTok < t_end) next.load(vg, kTok);
+        int slot = 0;
+        for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
+            const int tok_l = tb * 32 + (lane & 31), p = t0 + tok_l;
+            float x[16];                                     // (rows of z have room for whole tiles)
+            const int at = ((row0 + rb * 32 + 4 * half) * w.z_stride + (p - w.s0)) * 4;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                x[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(zg, at + (8 * (r >> 2) + (r & 3)) * w.z_stride * 4, 0, 0));
+            __syncthreads();                                 // this tile is in LDS, the one before it has been read
+            i32x16 acc[kLevels];
+            if (kNeedO) {
+                level_sums<kRowDigits, K, D, kTok, true>(rows, digits[slot % kBuf], tok_l, half, acc);
+                if (kBuf == 1) __syncthreads();
+            }
+            __builtin_amdgcn_sched_barrier(0);               // (one thing at a time: registers)
+            const double vv = vv_s[slot][tok_l];
+            const double vu = kNeedO ? -2.0 * units[slot][tok_l] : 0.0;
+            if (t0 + kTok < t_end) next.template store_digits<true, kNeedO>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], vv_s[slot ^ 1]);
+            if (t0 + 2 * kTok < t_end) next.load(vg, t0 - t_begin + 2 * kTok);
+            float acc_v = 0.f, acc_k = 0.f, acc_j = 0.f;
+            bool close = false;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                __builtin_amdgcn_sched_barrier(0);
+                const RowRecord &rec = rec_s[rb * 32 + 8 * (r >> 2) + 4 * half + (r & 3)];
+                const float a = p <= rec.last ? exp_nonpositive(x[r] - rec.m) * rec.inv_l : 0.f;
+                const float a2 = a * a;
+                if (kDoV) acc_v = fmaf(a, a, acc_v);             // (the same rounding in every variant)
+                if (!kNeedO) continue;
+                const double vo = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
+                const double d2 = fma(vo * rec.unit, vu, vv + rec.oo);                   // ||v_p - o_i||^2
+                const bool is_top = p == rec.top;
+                close |= d2 < vv * 0x1p-22 && p <= rec.last && !is_top;
+                if (kDoK) acc_k = fmaf(a2 * x[r] * x[r], is_top ? rec.top_dk : fmaxf((float)d2, 0.f), acc_k);
+                if (kDoJ) {
+                    const double zd = x[r];                  // ||v_p + Z (v_p - o_i)||^2 with 2 (v_p - o_i).v_p = d2 + vv - oo
+                    const double dj = fma(zd, fma(zd, d2, d2 + (vv - rec.oo)), vv);
+                    acc_j = fmaf(a2, is_top ? rec.top_dj : fmaxf((float)dj, 0.f), acc_j);
+                }
+            }
+            // v_p within 2^-11 of o_i: the expanded square has lost too much, the direct one is formed from fp32 v and o
+            if (kNeedO && close && p < t_end) {
+                acc_k = acc_j = 0.f;
+                const T *vp = v + ((size_t)bg * N + p) * D;
+#pragma unroll 1
+                for (int r = 0; r < 16; ++r) {
+                    const int row = rb * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                    const RowRecord &rec = rec_s[row];
+                    if (p > rec.last) continue;
+                    const size_t at_row = (size_t)hl * w.nr + row0 + row;
+                    const float zr = z[at_row * w.z_stride + (p - w.s0)], a = exp_nonpositive(zr - rec.m) * rec.inv_l, a2 = a * a;
+                    float d2 = 0.f, dj = 0.f;
+#pragma unroll 4
+                    for (int c = 0; c < D; ++c) {
+                        const float x = load_as_float(vp + c), diff = x - o[at_row * D + c], comb = fmaf(zr, diff, x);
+                        d2 = fmaf(diff, diff, d2);
+                        dj = fmaf(comb, comb, dj);
+                    }
+                    acc_k = fmaf(a2 * zr * zr, p == rec.top ? rec.top_dk : d2, acc_k);
+                    acc_j = fmaf(a2, p == rec.top ? rec.top_dj : dj, acc_j);
+                }
+            }
+            // the other half of the wave and the other row blocks held other rows
+            auto put = [&](int c, float s) {
+                s = across_halves(s);
+                if (half == 0) sum_s[slot][wave][c][lane] = s;
+            };
+            if (kDoV) put(0, acc_v * (float)vv);
+            if (kDoK) put(1, acc_k);
+            if (kDoJ) put(2, acc_j);
+            __syncthreads();
+            if (rb == 0 && half == 0 && p < t_end) {
+                int n = 0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    if ((c == 0 && !kDoV) || (c == 1 && !kDoK) || (c == 2 && !kDoJ)) continue;
+                    float s = 0.f;
+#pragma unroll
+                    for (int q = 0; q < kRb; ++q) s += sum_s[slot][wave + q][c][lane];
+                    float *d = out + (n++) * variant_stride + p;
+                    if (row0 > 0) s += run_s[n - 1][p - t_begin];                // (same thread in every chunk)
+                    if (row0 + kRows < w.nr) run_s[n - 1][p - t_begin] = s;
+                    else *d = add ? *d + s : s;
+                }
+            }
+        }
+    }
+}

@@ -29,6 +29,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "wave_util.h"
 
 namespace obc {
 namespace {
@@ -58,6 +59,7 @@ struct RowRecord {
     float top_dk, top_dj;        // ||v - o||^2 and ||v + Z (v - o)||^2 of the top token
     int last;                    // last token the row sees
     double oo;                   // ||o_i||^2
+    double unit;                 // of o_i's digits (score_fixed.h)
 };
 
 template <typename T> __device__ __forceinline__ float load_as_float(const T *p);
@@ -398,54 +400,76 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
             }
 }
 
+#include "score_fixed.h"
+
 // ------------------------------------------------------------------------------------
-// Merge.  One wave per row, D / 64 elements per lane.  Grid: x = four rows of the piece, z = KV head.
+// Merge.  One wave per row, D / 64 consecutive elements per lane.  Grid: x = four rows of the piece, z = KV head.
+// The output is left in fp32, with kFixed also as digits.
 // ------------------------------------------------------------------------------------
-template <typename T, int D, bool kNeedO, typename Lens>
+template <typename T, int D, bool kNeedO, bool kFixed, typename Lens>
 __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
-                                                        Piece w, int split_len, int n_splits,
+                                                        Piece w, int split_len, int n_parts, int parts_per_split,
                                                         const float *__restrict__ part_l, const float *__restrict__ part_o,
-                                                        RowRecord *__restrict__ records, float *__restrict__ out) {
+                                                        RowRecord *__restrict__ records, float *__restrict__ out,
+                                                        int8_t *__restrict__ out_digits) {
     constexpr int kE = D / 64;
     const int hl = blockIdx.z, bg = w.bg0 + hl, row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= w.nr) return;                                 // uniform over the wave
     const int len = seq_len_of(lens, ragged, bg / Hkv, N);
-    const int live = (len + split_len - 1) / split_len;
+    const int live = (len + split_len - 1) / split_len * parts_per_split;
     RowRecord *rec = records + (size_t)hl * w.nr + row;
-    const int top = rec->top;
+    const int top = min(rec->top, len - 1);                  // (logits that are not numbers have no largest one)
     const float m = rec->m;
     float vt[kE], o[kE];
 #pragma unroll
     for (int e = 0; e < kE; ++e) {
-        vt[e] = kNeedO ? load_as_float(v + ((size_t)bg * N + top) * D + lane + 64 * e) : 0.f;
+        vt[e] = kNeedO ? load_as_float(v + ((size_t)bg * N + top) * D + lane * kE + e) : 0.f;
         o[e] = 0.f;
     }
     float l = 0.f;
 #pragma unroll 8
     for (int s = 0; s < live; ++s) {
-        const size_t at = ((size_t)hl * n_splits + s) * w.nr + row;
+        const size_t at = ((size_t)hl * n_parts + s) * w.nr + row;
         l += part_l[at];
 #pragma unroll
         for (int e = 0; e < kE; ++e)
-            if (kNeedO) o[e] += part_o[at * D + lane + 64 * e];
+            if (kNeedO) o[e] += part_o[at * D + lane * kE + e];
     }
     const float frac = l / (1.0f + l);                       // 1 - A_{i,top}; the top token's own weight is exp(0) = 1
     const float inv = l > 0.f ? 1.0f / l : 0.f;
     double oo = 0.0, dk = 0.0, dj = 0.0;
+    double unit = 0.0;
     if (kNeedO) {
+        float oi[kE], amax = 0.f;
 #pragma unroll
         for (int e = 0; e < kE; ++e) {
             const float diff = frac * (vt[e] - o[e] * inv);  // v_top - o_i
-            const float oi = vt[e] - diff;
+            oi[e] = vt[e] - diff;
             const float comb = fmaf(m, diff, vt[e]);         // (1+Z) v_top - Z o_i
-            out[((size_t)hl * w.nr + row) * D + lane + 64 * e] = oi;
-            oo += (double)oi * oi;
+            oo += (double)oi[e] * oi[e];
             dk += (double)diff * diff;
             dj += (double)comb * comb;
+            amax = MaximumOp()(amax, fabsf(oi[e]));
         }
-        oo = wave_sum(oo);
-        dk = wave_sum(dk);
-        dj = wave_sum(dj);
+        const size_t at = (size_t)hl * w.nr + row;
+        if constexpr (kFixed) {
+            const int oe = max_exponent(wave_reduce<MaximumOp>(amax));
+            unit = row_unit(oe);
+            const float x[4] = {oi[0], kE > 1 ? oi[kE - 1] : 0.f, 0.f, 0.f};
+            uint32_t p[kRowDigits];
+            digits_of<kRowDigits>(x, digit_scale(oe), p);
+#pragma unroll
+            for (int k = 0; k < kRowDigits; ++k) {
+                int8_t *dst = out_digits + (at * kRowDigits + k) * D + lane * kE;
+                if constexpr (kE == 2) *(uint16_t *)dst = (uint16_t)p[k];
+                else *dst = (int8_t)p[k];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < kE; ++e) out[at * D + lane * kE + e] = oi[e];
+        oo = wave_reduce<SumOp>(oo);
+        dk = wave_reduce<SumOp>(dk);
+        dj = wave_reduce<SumOp>(dj);
     }
     if (lane == 0) {
         rec->last = len - W + (w.r0 + row) % W;
@@ -453,6 +477,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
         rec->top_dk = (float)dk;
         rec->top_dj = (float)dj;
         rec->oo = oo;
+        rec->unit = unit;
     }
 }
 
@@ -578,6 +603,11 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     float *out = (float *)(base + ws.pl_out);
     float2 *best = (float2 *)(base + ws.pl_best);
     RowRecord *rec = (RowRecord *)(base + ws.pl_records);
+    int8_t *q_digits = (int8_t *)(base + ws.pl_q_digits), *o_digits = (int8_t *)(base + ws.pl_o_digits);
+    double *q_units = (double *)(base + ws.pl_q_units);
+    // More than 32 rows are taken apart into digits; 64 or 128 of them per workgroup.
+    constexpr bool fixed = kRt == 4 || kRt == 8;
+    constexpr int kRb = kRt == 8 ? 4 : 2;
     const bool need_o = a.variant == OBC_KEY || a.variant == OBC_JOINT || a.variant == OBC_ALL;
     const int BH = a.B * a.Hkv, M = a.G * a.W;
     const size_t variant_stride = (size_t)BH * a.N;
@@ -593,15 +623,27 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     for (int bg0 = 0; bg0 < BH; bg0 += ws.pl_heads)
         for (int r0 = 0; r0 < M; r0 += ws.pl_rows) {
             Piece w;
-            w.bg0 = bg0; w.r0 = r0; w.nr = std::min(ws.pl_rows, M - r0); w.z_stride = ws.pl_seg;
-            const unsigned heads = std::min(ws.pl_heads, BH - bg0), chunks = (w.nr + 16 * kRt - 1) / (16 * kRt);
+            w.bg0 = bg0; w.r0 = r0; w.nr = std::min(ws.pl_rows, M - r0); w.z_stride = ws.pl_z_stride;
+            const unsigned heads = std::min(ws.pl_heads, BH - bg0), chunks = (w.nr + 16 * kFewRt - 1) / (16 * kFewRt);
             auto segment = [&](int i) { w.s0 = i * ws.pl_seg; w.s1 = std::min(w.s0 + ws.pl_seg, a.N); };
+            const unsigned row_chunks = (w.nr + 32 * kRb - 1) / (32 * kRb);         // (score_fixed.h)
             auto logits = [&]() {
-                plain_logits<T, D, kFewRt><<<dim3((w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range, (w.nr + 16 * kFewRt - 1) / (16 * kFewRt), heads), dim3(kThreads), 0, stream>>>(
-                    q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
+                const unsigned ranges = (w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range;
+                if constexpr (fixed)
+                    fixed_logits<T, D, kRb><<<dim3(ranges, row_chunks, heads), dim3(kThreads), 0, stream>>>(
+                        q_digits, q_units, k, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
+                else
+                    plain_logits<T, D, kRt><<<dim3(ranges, chunks, heads), dim3(kThreads), 0, stream>>>(
+                        q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 e = hipGetLastError();
                 return e == hipSuccess;
             };
+            const bool again = mask & OBC_STAGE_SWEEP1 || segs > 1;
+            if (fixed && again) {
+                fixed_rows<T, D><<<dim3((w.nr * (D / 4) + kThreads - 1) / kThreads, 1, heads), dim3(kThreads), 0, stream>>>(
+                    q, a.W, a.Hq, a.Hkv, w, q_digits, q_units);
+                if ((e = hipGetLastError()) != hipSuccess) return e;
+            }
             if (mask & OBC_STAGE_SWEEP1) {
                 for (int i = 0; i < segs; ++i) {             // every range's maximum first
                     segment(i);
@@ -611,31 +653,55 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                     segment(i);
                     if (segs > 1 && !logits()) return e;
                     const dim3 grid((w.s1 - w.s0 + ws.pl_split - 1) / ws.pl_split, chunks, heads);
-                    if (need_o)
-                        plain_weights<T, D, kRt, true><<<grid, dim3(kThreads), 0, stream>>>(
-                            v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
-                            best, rec, part_l, part_o);
-                    else
-                        plain_weights<T, D, kRt, false><<<grid, dim3(kThreads), 0, stream>>>(
-                            v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
-                            best, rec, part_l, part_o);
+                    auto weights = [&](auto with_output) {
+                        constexpr bool kNeedO = decltype(with_output)::value;
+                        if constexpr (fixed)
+                            fixed_weights<T, D, kRb, kNeedO><<<dim3(grid.x, row_chunks, heads), dim3(kThreads), 0, stream>>>(
+                                v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
+                                best, rec, part_l, part_o);
+                        else
+                            plain_weights<T, D, kRt, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
+                                v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
+                                best, rec, part_l, part_o);
+                    };
+                    if (need_o) weights(std::true_type());
+                    else weights(std::false_type());
                     if ((e = hipGetLastError()) != hipSuccess) return e;
                 }
             }
             if (mask & OBC_STAGE_COMBINE) {
                 const dim3 grid((w.nr + 3) / 4, 1, heads);
-                if (need_o)
-                    plain_merge<T, D, true><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split,
-                                                                                 ws.pl_splits, part_l, part_o, rec, out);
-                else
-                    plain_merge<T, D, false><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split,
-                                                                                  ws.pl_splits, part_l, part_o, rec, out);
+                const int per_split = fixed ? 4 / kRb : 1;
+#define OBC_PLAIN_MERGE(need_o, fixed)                                                                                 \
+    plain_merge<T, D, need_o, fixed><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split,  \
+                                                                          ws.pl_splits * per_split, per_split, part_l, part_o, \
+                                                                          rec, out, o_digits)
+                if (need_o && fixed) OBC_PLAIN_MERGE(true, true);
+                else if (need_o) OBC_PLAIN_MERGE(true, false);
+                else OBC_PLAIN_MERGE(false, false);
+#undef OBC_PLAIN_MERGE
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
             if (!(mask & OBC_STAGE_SWEEP2)) continue;
             for (int i = 0; i < segs; ++i) {
                 segment(i);
                 if (segs > 1 && !logits()) return e;
+                if (fixed && a.variant != OBC_ATTN && a.variant != OBC_VATP) {
+                    constexpr int kTok = 128 / kRb;
+                    const int tiles = (w.s1 - w.s0 + kTok - 1) / kTok;
+                    const int n_tiles = (int)std::min((tiles * (long long)heads + kResident / 2 - 1) / (kResident / 2), kScoreTokens / kTok + 0ll);
+                    const dim3 grid((tiles + n_tiles - 1) / n_tiles, 1, heads);
+#define OBC_FIXED_SCORE(variant)                                                                                       \
+    fixed_score<T, D, kRb, variant><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_digits, \
+                                                                         a.scores, variant_stride, a.accumulate || r0 > 0)
+                    if (a.variant == OBC_VALUE) OBC_FIXED_SCORE(OBC_VALUE);
+                    else if (a.variant == OBC_KEY) OBC_FIXED_SCORE(OBC_KEY);
+                    else if (a.variant == OBC_JOINT) OBC_FIXED_SCORE(OBC_JOINT);
+                    else OBC_FIXED_SCORE(OBC_ALL);
+#undef OBC_FIXED_SCORE
+                    if ((e = hipGetLastError()) != hipSuccess) return e;
+                    continue;
+                }
                 const int tiles = (w.s1 - w.s0 + kTile - 1) / kTile, n_tiles = (int)((tiles * (long long)heads + kResident - 1) / kResident);
                 const dim3 grid((tiles + n_tiles - 1) / n_tiles, 1, heads);
                 const int add = a.accumulate || r0 > 0;
@@ -664,11 +730,12 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
 
 template <typename T, int D>
 hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
-    // 16-row tiles of a workgroup: four where the rows fill them (a workgroup reads its tokens once for all of them).
+    // 16-row tiles of a workgroup.
     const int rows = std::min(ws.pl_rows, a.G * a.W);
     if (rows <= 16) return run<T, D, 1>(a, ws, base, stream);
-    if ((rows + 31) / 32 % 2 != 0) return run<T, D, 2>(a, ws, base, stream);
-    return run<T, D, 4>(a, ws, base, stream);
+    if (rows <= 32) return run<T, D, 2>(a, ws, base, stream);
+    if ((rows + 63) / 64 % 2 != 0) return run<T, D, 4>(a, ws, base, stream);      // (the last 128 would be half empty)
+    return run<T, D, 8>(a, ws, base, stream);
 }
 
 }  // namespace
@@ -680,18 +747,21 @@ hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hi
 void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv, M = Hq / Hkv * W;
-    const long long chunks = (long long)BH * ((M + 63) / 64), tiles = (N + kTile - 1) / kTile;
-    const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, (2 * tiles * chunks + kResident - 1) / kResident);     // (chunks of 64 rows here, of 32 there)
+    const bool fixed = M > 32;
+    const long long chunks = (long long)BH * (fixed ? (M + 127) / 128 : (M + 31) / 32), tiles = (N + kTile - 1) / kTile;
+    const long long resident = fixed ? kResident / 2 : kResident;
+    const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, (tiles * chunks + resident - 1) / resident);
     ws->pl_range = (int)(std::min(range_tiles, tiles) * kTile);
     ws->pl_ranges = (N + ws->pl_range - 1) / ws->pl_range;
     const long long splits = std::max<long long>(1, std::min<long long>(std::min<long long>(kMaxSplits, tiles), (kResident / 2 + chunks - 1) / chunks));
     ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
     ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
+    const int parts = fixed ? 2 : 1;                         // (partial records per split, at most)
     auto row_bytes = [&]() {                                 // of one row, beside its logits
-        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * 4 + (size_t)ws->pl_splits * (d + 1) * 4;
+        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 14 : 4) + 8 + (size_t)ws->pl_splits * parts * (d + 1) * 4;
     };
-    const size_t per_row = row_bytes() + (size_t)N * 4;
-    cap -= 6 * 256;                                          // alignment of the buffers
+    const size_t per_row = row_bytes() + (size_t)align_up(N, kTile) * 4;
+    cap -= 9 * 256;                                          // alignment of the buffers
     ws->pl_seg = N;
     ws->pl_rows = M;
     ws->pl_heads = (int)std::min<size_t>(BH, cap / (per_row * M));
@@ -710,12 +780,18 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
     }
     const size_t rows = (size_t)ws->pl_heads * ws->pl_rows;
     auto take = [&](size_t *at, size_t bytes) { *at = *off; *off = align_up(*off + bytes, 256); };
-    take(&ws->pl_z, rows * ws->pl_seg * 4);
+    ws->pl_z_stride = (int)align_up(ws->pl_seg, kTile);       // (whole tiles are written)
+    take(&ws->pl_z, rows * ws->pl_z_stride * 4);
     take(&ws->pl_best, rows * ws->pl_ranges * sizeof(float2));
     take(&ws->pl_records, rows * sizeof(RowRecord));
     take(&ws->pl_out, rows * d * 4);
-    take(&ws->pl_part_l, rows * ws->pl_splits * 4);
-    take(&ws->pl_part_o, rows * ws->pl_splits * d * 4);
+    if (fixed) {
+        take(&ws->pl_o_digits, rows * d * 5);
+        take(&ws->pl_q_digits, rows * d * 5);
+        take(&ws->pl_q_units, rows * 8);
+    }
+    take(&ws->pl_part_l, rows * ws->pl_splits * parts * 4);
+    take(&ws->pl_part_o, rows * ws->pl_splits * parts * d * 4);
 }
 
 hipError_t launch_score_plain(const ScoreArgs &a, const ScoreWorkspace &ws, char *ws_base, hipStream_t stream) {

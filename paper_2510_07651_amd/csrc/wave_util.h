@@ -21,6 +21,9 @@ __device__ __forceinline__ unsigned long long dpp_pair(unsigned long long x) {
     return ((unsigned long long)dpp_pair<kCtrl>((uint32_t)(x >> 32)) << 32) | dpp_pair<kCtrl>((uint32_t)x);
 }
 
+template <int kCtrl>
+__device__ __forceinline__ double dpp_pair(double x) { return __longlong_as_double((long long)dpp_pair<kCtrl>((unsigned long long)__double_as_longlong(x))); }
+
 // The values of the two lanes that differ in bit 4 (16) or 5 (32) of their index, lower one first.
 template <int kBit>
 __device__ __forceinline__ void both_of_pair(uint32_t x, uint32_t &lower, uint32_t &upper) {
@@ -42,6 +45,14 @@ __device__ __forceinline__ void both_of_pair(unsigned long long x, unsigned long
     both_of_pair<kBit>((uint32_t)x, ll, ul);
     lower = ((unsigned long long)lh << 32) | ll;
     upper = ((unsigned long long)uh << 32) | ul;
+}
+
+template <int kBit>
+__device__ __forceinline__ void both_of_pair(double x, double &lower, double &upper) {
+    unsigned long long a, b;
+    both_of_pair<kBit>((unsigned long long)__double_as_longlong(x), a, b);
+    lower = __longlong_as_double((long long)a);
+    upper = __longlong_as_double((long long)b);
 }
 
 __device__ __forceinline__ unsigned long long min64(unsigned long long a, unsigned long long b) { return a < b ? a : b; }
@@ -69,6 +80,12 @@ __device__ __forceinline__ T across_rows(T x) {
     x = op(a, b);
     both_of_pair<32>(x, a, b);
     return op(a, b);
+}
+// Sum of a lane's value and that of the lane in the other half of the wave.
+__device__ __forceinline__ float across_halves(float x) {
+    float a, b;
+    both_of_pair<32>(x, a, b);
+    return a + b;
 }
 template <typename Op, typename T>
 __device__ __forceinline__ T wave_reduce(T x) { return across_rows<Op>(row16_reduce<Op>(x)); }
