@@ -9,7 +9,7 @@
 // integers; pairs of digits beyond the fifth level are left out, and the levels are put together in fp64.  A dot product
 // is off by a few parts in 2^36 of |x|max |y|max before it is rounded to fp32: far below that rounding unless the sum
 // cancels to less than 2^-10 of its terms.  Where it does, in ||v_p - o_i||^2 of a v_p that is nearly o_i, the squares are
-// formed directly.  Fifteen integer ops replace 128 fp64 ones.
+// formed directly (fixed_score's last part).  Fifteen integer ops replace 128 fp64 ones.
 //
 // P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each (exact), products of pieces down to 2^-18 of the
 // leading one (what is left out is below an fp32 rounding), fp32 accumulation: six bf16 ops (three for bf16 values, where
@@ -19,14 +19,18 @@
 // workgroup of up to 128 rows, and putting a dot product together about 12; below 33 rows the fp64 kernels are as fast.
 // fp32, 32/8 heads, d = 128, 8111 tokens, joint: FIXED_TIMES
 typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 template <typename T> constexpr int kDigits = sizeof(T) == 4 ? 5 : 4;
 constexpr int kRowDigits = 5;                  // of o_i, which is fp32 whatever the inputs are
 constexpr int kLevels = 5;
+
+// Shape of a workgroup: eight waves, each with 16 window rows; kRb = 8 takes 128 rows, kRb = 4 takes 64 and two halves of a
+// token tile.  Rows and sums of a wave fit 128 registers, so that four waves share a SIMD and hide each other's latencies
+// (with 32 rows per wave and two waves the three kernels took 30, 37 and 43 us at the shape above).
+constexpr int kFixedThreads = 512;
+template <int D, int kRb> constexpr int kFixedTile = D == 64 || kRb == 4 ? 64 : 32;      // tokens
 
 // Maximum that lets a NaN through.
 struct MaximumOp { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_elementwise_maximum(a, b); } };
@@ -93,17 +97,17 @@ template <typename T, int D, int kTok>
 struct TokenTile {
     static constexpr int kPer = 16 / (int)sizeof(T);                     // elements of a 16-byte piece
     static constexpr int kLanes = D / kPer;                              // lanes per row
-    static constexpr int kCount = kTok * kLanes / kThreads;
-    static_assert(kTok * kLanes % kThreads == 0, "whole pieces per thread");
+    static constexpr int kCount = kTok * kLanes / kFixedThreads;
+    static_assert(kTok * kLanes % kFixedThreads == 0, "whole pieces per thread");
     uint4 x[kCount];
 
-    __device__ __forceinline__ int row(int i) const { return ((int)threadIdx.x + i * kThreads) / kLanes; }
+    __device__ __forceinline__ int row(int i) const { return ((int)threadIdx.x + i * kFixedThreads) / kLanes; }
     __device__ __forceinline__ int piece() const { return (int)threadIdx.x % kLanes; }
     // Rows from row t of the span; rows beyond its end become zeros.
     __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t span, int t) {
 #pragma unroll
         for (int i = 0; i < kCount; ++i) {
-            const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(span, (t * kLanes + (int)threadIdx.x + i * kThreads) * 16, 0, 0);
+            const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(span, (t * kLanes + (int)threadIdx.x + i * kFixedThreads) * 16, 0, 0);
             x[i] = make_uint4(u.x, u.y, u.z, u.w);
         }
     }
@@ -195,72 +199,71 @@ __global__ __launch_bounds__(kThreads) void fixed_rows(const T *__restrict__ q, 
     if (c == 0) units[at] = row_unit(e);
 }
 
-// A wave's 32 rows of digits as a matrix operand: lane = row + 32 half holds bytes 16 half .. 16 half + 15 of every 32.
+// A wave's 16 rows of digits as a matrix operand: lane = row + 16 g holds bytes 16 g .. 16 g + 15 of every 64.
 template <int K, int D>
 struct RowDigits {
-    i32x4 x[K][D / 32];
-    __device__ __forceinline__ void load(const int8_t *__restrict__ digits, size_t at, bool live, int half) {
+    i32x4 x[K][D / 64];
+    __device__ __forceinline__ void load(const int8_t *__restrict__ digits, size_t at, bool live, int g) {
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int kk = 0; kk < D / 32; ++kk)
-                x[k][kk] = live ? *(const i32x4 *)(digits + (at * K + k) * D + kk * 32 + half * 16) : i32x4{0, 0, 0, 0};
+            for (int kk = 0; kk < D / 64; ++kk)
+                x[k][kk] = live ? *(const i32x4 *)(digits + (at * K + k) * D + kk * 64 + g * 16) : i32x4{0, 0, 0, 0};
     }
 };
 
 // Buffers of a tile: two where two workgroups fit a CU with them, else one (and a barrier more per tile).
-constexpr int buffers_of(int bytes) { return bytes <= 36 * 1024 ? 2 : 1; }
+constexpr int buffers_of(int bytes) { return bytes <= 32 * 1024 ? 2 : 1; }
 
-// Level sums of 32 rows against 32 tokens in LDS.  kRowsFirst: accumulator rows are window rows and lanes are tokens.
+// Level sums of 16 rows against 16 tokens in LDS.  kRowsFirst: accumulator rows are window rows and lanes are tokens.
 template <int KR, int KT, int D, int kTok, bool kRowsFirst>
-__device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const char *digits, int tok, int half, i32x16 (&acc)[kLevels]) {
+__device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const char *digits, int tok, int g, i32x4 (&acc)[kLevels]) {
 #pragma unroll
-    for (int t = 0; t < kLevels; ++t)
+    for (int t = 0; t < kLevels; ++t) acc[t] = i32x4{0, 0, 0, 0};
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0;
-#pragma unroll
-    for (int kk = 0; kk < D / 32; ++kk) {
+    for (int kk = 0; kk < D / 64; ++kk) {
+        if (kk > 0) __builtin_amdgcn_sched_barrier(0);       // (one piece at a time: registers)
         i32x4 b[KT];
 #pragma unroll
-        for (int k = 0; k < KT; ++k) b[k] = *(const i32x4 *)(digits + digit_offset<D, kTok>(k, tok, 2 * kk + half));
+        for (int k = 0; k < KT; ++k) b[k] = *(const i32x4 *)(digits + digit_offset<D, kTok>(k, tok, 4 * kk + g));
 #pragma unroll
         for (int k = 0; k < KT; ++k)
 #pragma unroll
             for (int i = 0; i < KR && i + k < kLevels; ++i)
-                acc[i + k] = kRowsFirst ? __builtin_amdgcn_mfma_i32_32x32x32_i8(rows.x[i][kk], b[k], acc[i + k], 0, 0, 0)
-                                        : __builtin_amdgcn_mfma_i32_32x32x32_i8(b[k], rows.x[i][kk], acc[i + k], 0, 0, 0);
+                acc[i + k] = kRowsFirst ? __builtin_amdgcn_mfma_i32_16x16x64_i8(rows.x[i][kk], b[k], acc[i + k], 0, 0, 0)
+                                        : __builtin_amdgcn_mfma_i32_16x16x64_i8(b[k], rows.x[i][kk], acc[i + k], 0, 0, 0);
     }
 }
 
 // ------------------------------------------------------------------------------------
-// Logits.  Grid: x = token range of the piece, y = chunk of 32 kRb rows, z = KV head.  Wave w takes row block w % kRb and
-// token block w / kRb of every tile; lane = row (and half), registers = tokens.
+// Logits.  Grid: x = token range of the piece, y = chunk of 16 kRb rows, z = KV head.  Wave w takes row block w % kRb and
+// part w / kRb of every tile, 16 tokens at a time; lane = row + 16 g, registers = tokens 4 g .. 4 g + 3.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int kRb, typename Lens>
-__global__ __launch_bounds__(kThreads, 2) void fixed_logits(const int8_t *__restrict__ q_digits, const double *__restrict__ q_units,
-                                                            const T *__restrict__ k, int N, int W, int Hkv, int ragged, Lens lens,
-                                                            Piece w, int range_len, int n_ranges, float *__restrict__ z,
-                                                            float2 *__restrict__ range_best) {
-    constexpr int K = kDigits<T>, kTok = 32 * 4 / kRb, kBuf = buffers_of(K * kTok * D);
+__global__ __launch_bounds__(kFixedThreads, 4) void fixed_logits(const int8_t *__restrict__ q_digits, const double *__restrict__ q_units,
+                                                                 const T *__restrict__ k, int N, int W, int Hkv, int ragged, Lens lens,
+                                                                 Piece w, int range_len, int n_ranges, float *__restrict__ z,
+                                                                 float2 *__restrict__ range_best) {
+    constexpr int K = kDigits<T>, kTok = kFixedTile<D, kRb>, kPart = kTok / (8 / kRb), kBuf = buffers_of(K * kTok * D);
     __shared__ __attribute__((aligned(16))) char digits[kBuf][K * kTok * D];
     __shared__ __attribute__((aligned(16))) double units[2][kTok];
-    __shared__ float2 best_s[4][32];
+    __shared__ float2 best_s[8][16];
     const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
     const int range = w.s0 / range_len + blockIdx.x;
     const int t_begin = range * range_len, t_end = min(min(t_begin + range_len, w.s1), len);
     if (t_begin >= t_end) return;                            // uniform
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
-    const int rb = wave % kRb, tb = wave / kRb;
-    const int row = ((int)blockIdx.y * kRb + rb) * 32 + (lane & 31);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
+    const int rb = wave % kRb, part = wave / kRb;
+    const int row = ((int)blockIdx.y * kRb + rb) * 16 + (lane & 15);
     const bool live = row < w.nr;
     const __amdgpu_buffer_rsrc_t kg = span_of(k + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
     TokenTile<T, D, kTok> next;
     next.load(kg, 0);
     RowDigits<K, D> rows;
-    rows.load(q_digits, (size_t)hl * w.nr + min(row, w.nr - 1), live, half);
+    rows.load(q_digits, (size_t)hl * w.nr + min(row, w.nr - 1), live, g);
     const double qu = live ? q_units[(size_t)hl * w.nr + row] * (1.0 / sqrt((double)D)) : 0.0;
-    const int last = live ? len - W + (w.r0 + row) % W : -1;             // last token the row sees
+    const int last = live ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;         // last token the row sees here
     float *zp = z + ((size_t)hl * w.nr + row) * w.z_stride - w.s0;
     float m = -INFINITY;
     int at = kNoToken;
@@ -269,41 +272,50 @@ __global__ __launch_bounds__(kThreads, 2) void fixed_logits(const int8_t *__rest
     int slot = 0;
     for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
         __syncthreads();                                     // this tile is in LDS, the one before it has been read
-        i32x16 acc[kLevels];
-        level_sums<K, K, D, kTok, false>(rows, digits[slot % kBuf], tb * 32 + (lane & 31), half, acc);
-        if (kBuf == 1) __syncthreads();
-        if (t0 + kTok < t_end) next.template store_digits<false>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], nullptr);
-        if (t0 + 2 * kTok < t_end) next.load(kg, t0 - t_begin + 2 * kTok);
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            const int p0 = tb * 32 + 8 * r4 + 4 * half;      // in the tile
-            const double2 u01 = *(const double2 *)(units[slot] + p0), u23 = *(const double2 *)(units[slot] + p0 + 2);
+        if (kBuf == 2) {
+            if (t0 + kTok < t_end) next.template store_digits<false>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], nullptr);
+            if (t0 + 2 * kTok < t_end) next.load(kg, t0 - t_begin + 2 * kTok);
+        }
+#pragma unroll 1
+        for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
+            i32x4 acc[kLevels];
+            level_sums<K, K, D, kTok, false>(rows, digits[slot % kBuf], p0 + (lane & 15), g, acc);
+            const double2 u01 = *(const double2 *)(units[slot] + p0 + 4 * g), u23 = *(const double2 *)(units[slot] + p0 + 4 * g + 2);
             const double ku[4] = {u01.x, u01.y, u23.x, u23.y};
             float x[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int r = 4 * r4 + i;
-                const double dot = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
-                x[i] = (float)(dot * ku[i] * qu);                // scaled logit
-                const int p = t0 + p0 + i;
-                if (p <= last && p < t_end && x[i] > m) { m = x[i]; at = p; }   // (tokens ascend: strict keeps the lowest)
+                const double dot = join_levels(acc[0][i], acc[1][i], acc[2][i], acc[3][i], acc[4][i]);
+                x[i] = (float)(dot * ku[i] * qu);            // scaled logit
+                const int p = t0 + p0 + 4 * g + i;
+                if (p <= last && x[i] > m) { m = x[i]; at = p; }         // (tokens ascend: strict keeps the lowest)
             }
-            if (live) *(float4 *)(zp + t0 + p0) = make_float4(x[0], x[1], x[2], x[3]);       // (rows of z have room for whole tiles)
+            if (live) *(float4 *)(zp + t0 + p0 + 4 * g) = make_float4(x[0], x[1], x[2], x[3]);   // (rows of z have room for whole tiles)
+        }
+        if (kBuf == 1) {
+            __syncthreads();
+            if (t0 + kTok < t_end) next.template store_digits<false>(digits[0], units[slot ^ 1], nullptr);
+            if (t0 + 2 * kTok < t_end) next.load(kg, t0 - t_begin + 2 * kTok);
         }
     }
-    {
+    auto best_of_pair = [&](auto bit) {
+        constexpr int kBit = decltype(bit)::value;
         float m0, m1;
         uint32_t a0, a1;
-        both_of_pair<32>(m, m0, m1);
-        both_of_pair<32>((uint32_t)at, a0, a1);
+        both_of_pair<kBit>(m, m0, m1);
+        both_of_pair<kBit>((uint32_t)at, a0, a1);
         const bool second = m1 > m0 || (m1 == m0 && a1 < a0);
-        if (half == 0) best_s[wave][lane] = make_float2(second ? m1 : m0, __int_as_float((int)(second ? a1 : a0)));
-    }
+        m = second ? m1 : m0;
+        at = (int)(second ? a1 : a0);
+    };
+    best_of_pair(std::integral_constant<int, 16>());
+    best_of_pair(std::integral_constant<int, 32>());
+    if (g == 0) best_s[wave][lane] = make_float2(m, __int_as_float(at));
     __syncthreads();
-    if (tb == 0 && half == 0 && live) {
+    if (part == 0 && g == 0 && live) {
         float2 best = best_s[wave][lane];
 #pragma unroll
-        for (int c = 1; c < 4 / kRb; ++c) {
+        for (int c = 1; c < 8 / kRb; ++c) {
             const float2 o = best_s[wave + c * kRb][lane];
             if (o.x > best.x || (o.x == best.x && __float_as_int(o.y) < __float_as_int(best.y))) best = o;
         }
@@ -312,14 +324,14 @@ __global__ __launch_bounds__(kThreads, 2) void fixed_logits(const int8_t *__rest
 }
 
 // ------------------------------------------------------------------------------------
-// Weights and P V.  Grid: x = split of the piece, y = chunk of 32 kRb rows, z = KV head.  Lane = row (and half);
-// O^T += V^T P^T.  The token blocks of a tile (4 / kRb of them) are splits of their own.
+// Weights and P V.  Grid: x = split of the piece, y = chunk of 16 kRb rows, z = KV head.  O^T += V^T P^T, 32 tokens at a
+// time; lane = row + 16 g.  The parts of a tile (8 / kRb of them) are splits of their own.
 // ------------------------------------------------------------------------------------
-// V pieces in LDS: kP planes of kTok rows of D bf16.  A row's 16-byte piece c sits where the transposing read (16 lanes fetch
-// 8 bytes each of four consecutive tokens, 32 lanes 64 contiguous bytes of them) meets every bank once.
+// V pieces in LDS: kP planes of kTok rows of D bf16.  A row's 16-byte piece c sits where the transposing read (32 lanes
+// fetch 32 bytes each of eight consecutive tokens) meets every bank once.
 template <int D, int kTok>
 __device__ __forceinline__ int value_offset(int plane, int tok, int c) {
-    const int slot = D == 128 ? (c + 4 * (tok & 3)) & 15 : (c + 4 * (tok >> 1 & 1)) & 7;
+    const int slot = D == 128 ? (c + 2 * (tok & 7)) & 15 : (c + 2 * (tok >> 1 & 3)) & 7;
     return (plane * kTok + tok) * D * 2 + slot * 16;
 }
 
@@ -337,12 +349,12 @@ __device__ __forceinline__ void three_pieces(float a, float b, uint32_t (&p)[3])
 }
 
 template <typename T, int D, int kRb, bool kNeedO, typename Lens>
-__global__ __launch_bounds__(kThreads, 2) void fixed_weights(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
-                                                             Piece w, int range_len, int n_ranges, int split_len, int n_splits,
-                                                             const float *__restrict__ z, const float2 *__restrict__ range_best,
-                                                             RowRecord *__restrict__ records, float *__restrict__ part_l,
-                                                             float *__restrict__ part_o) {
-    constexpr int kTb = 4 / kRb, kTok = 32 * kTb, kP = sizeof(T) == 4 ? 3 : 1, kRows = 32 * kRb,
+__global__ __launch_bounds__(kFixedThreads, 4) void fixed_weights(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
+                                                                  Piece w, int range_len, int n_ranges, int split_len, int n_splits,
+                                                                  const float *__restrict__ z, const float2 *__restrict__ range_best,
+                                                                  RowRecord *__restrict__ records, float *__restrict__ part_l,
+                                                                  float *__restrict__ part_o) {
+    constexpr int kTok = kFixedTile<D, kRb>, kParts = 8 / kRb, kPart = kTok / kParts, kP = sizeof(T) == 4 ? 3 : 1, kRows = 16 * kRb,
                   kBuf = buffers_of(kP * kTok * D * 2);
     __shared__ __attribute__((aligned(16))) char values[kBuf][kNeedO ? kP * kTok * D * 2 : 16];
     __shared__ float m_s[kRows];
@@ -352,13 +364,22 @@ __global__ __launch_bounds__(kThreads, 2) void fixed_weights(const T *__restrict
     const int split = w.s0 / split_len + blockIdx.x;
     const int t_begin = split * split_len, t_end = min(min(t_begin + split_len, w.s1), len);
     if (t_begin >= t_end) return;                            // uniform
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
-    const int rb = wave % kRb, tb = wave / kRb, row0 = blockIdx.y * kRows;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
+    const int rb = wave % kRb, part = wave / kRb, row0 = blockIdx.y * kRows;
     const __amdgpu_buffer_rsrc_t vg = span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
     TokenTile<T, D, kTok> next;
     if (kNeedO) next.load(vg, 0);
+    const int row_l = rb * 16 + (lane & 15), row = row0 + row_l;
+    const float *zp = z + ((size_t)hl * w.nr + min(row, w.nr - 1)) * w.z_stride - w.s0 + part * kPart + 4 * g;
+    // This lane's logits of a 32-token step: tokens 4 g + {0..3} and 16 + 4 g + {0..3}, the order of the transposing reads.
+    float4 x[2 * (kPart / 32)];
+    auto fetch = [&](int t0) {
+#pragma unroll
+        for (int i = 0; i < 2 * (kPart / 32); ++i) x[i] = *(const float4 *)(zp + t0 + 16 * i);     // (rows of z have room for whole tiles)
+    };
+    fetch(t_begin);
     {
-        constexpr int kSub = kThreads / kRows;               // the row's maximum over its ranges: kSub lanes per row
+        constexpr int kSub = kFixedThreads / kRows;          // the row's maximum over its ranges: kSub lanes per row
         const int row = threadIdx.x / kSub, live = (len + range_len - 1) / range_len;
         float m = -INFINITY;
         int at = kNoToken;
@@ -399,40 +420,30 @@ __global__ __launch_bounds__(kThreads, 2) void fixed_weights(const T *__restrict
     };
     if (kNeedO) store_values(0);
     __syncthreads();
-    const int row_l = rb * 32 + (lane & 31), row = row0 + row_l;
     const float m = row < w.nr ? m_s[row_l] : 0.f;
     const int top = top_s[row_l];
     const int last = row < w.nr ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;    // last token the row sees here
-    const float *zp = z + ((size_t)hl * w.nr + min(row, w.nr - 1)) * w.z_stride - w.s0;
-    // This lane's weights of a 16-token step: tokens 4 half + {0..3} and 8 + 4 half + {0..3}, the order of the transposing reads.
-    float4 x[4];
-    auto fetch = [&](int t0) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) x[g] = *(const float4 *)(zp + t0 + tb * 32 + 8 * g + 4 * half);    // (rows of z have room for whole tiles)
-    };
-    fetch(t_begin);
     if (kNeedO && t_begin + kTok < t_end) next.load(vg, kTok);
-    f32x16 acc[D / 32];
+    f32x4 acc[D / 16];
 #pragma unroll
-    for (int d = 0; d < D / 32; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[d][r] = 0.f;
+    for (int d = 0; d < D / 16; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
     float sum = 0.f;
     int slot = 0;
-    const int i16 = lane & 15, tok_in4 = i16 >> 2, sub = lane >> 4 & 1;
+    // Transposing read: in every 16 lanes four tokens' 16 elements of head_dim block d; two reads make a 32-token operand.
+    const int i16 = lane & 15, tok_l = part * kPart + 4 * g + (i16 >> 2), c_l = i16 >> 1 & 1, byte_l = (i16 & 1) * 8;
     for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
         if (kNeedO && t0 > t_begin) __syncthreads();         // this tile is in LDS, the one before it has been read
-        union Pieces { bf16x8 v; uint32_t u[4]; } p[2][3];
+        union Pieces { bf16x8 v; uint32_t u[4]; } p[kPart / 32][3];
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < kPart / 32; ++s)
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const float4 f = x[2 * s + g];
+            for (int h = 0; h < 2; ++h) {
+                const float4 f = x[2 * s + h];
                 const float y[4] = {f.x, f.y, f.z, f.w};
                 float e4[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int t = t0 + tb * 32 + 16 * s + 8 * g + 4 * half + i;
+                    const int t = t0 + part * kPart + 32 * s + 16 * h + 4 * g + i;
                     e4[i] = t <= last && t != top ? exp_nonpositive(y[i] - m) : 0.f;
                     sum += e4[i];
                 }
@@ -441,93 +452,92 @@ __global__ __launch_bounds__(kThreads, 2) void fixed_weights(const T *__restrict
                 three_pieces(e4[2], e4[3], q[1]);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
-                    p[s][k].u[2 * g] = q[0][k];
-                    p[s][k].u[2 * g + 1] = q[1][k];
+                    p[s][k].u[2 * h] = q[0][k];
+                    p[s][k].u[2 * h + 1] = q[1][k];
                 }
             }
         if (t0 + kTok < t_end) fetch(t0 + kTok);
+        if (!kNeedO) continue;
         auto advance = [&]() {
             if (t0 + kTok < t_end) store_values(slot ^ 1);
             if (t0 + 2 * kTok < t_end) next.load(vg, t0 - t_begin + 2 * kTok);
         };
-        if (!kNeedO) continue;
         if (kBuf == 2) advance();
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < kPart / 32; ++s)
 #pragma unroll
-            for (int d = 0; d < D / 32; ++d)
+            for (int d = 0; d < D / 16; ++d)
 #pragma unroll
                 for (int k = 0; k < kP; ++k) {
                     union { bf16x8 v; i16x4 h[2]; } a;
 #pragma unroll
-                    for (int g = 0; g < 2; ++g) {
-                        const int tok = tb * 32 + 16 * s + 8 * g + 4 * half + tok_in4;
-                        const char *src = values[slot % kBuf] + value_offset<D, kTok>(k, tok, d * 4 + sub * 2 + (i16 >> 1 & 1)) + (i16 & 1) * 8;
-                        a.h[g] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(src));
-                    }
+                    for (int h = 0; h < 2; ++h)
+                        a.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(
+                            values[slot % kBuf] + value_offset<D, kTok>(k, tok_l + 32 * s + 16 * h, 2 * d + c_l) + byte_l));
 #pragma unroll
                     for (int j = 0; j + k < 3; ++j)
-                        acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, p[s][j].v, acc[d], 0, 0, 0);
+                        acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, p[s][j].v, acc[d], 0, 0, 0);
                 }
         if (kBuf == 1) {
             __syncthreads();
             advance();
         }
     }
-    const size_t out_row = ((size_t)hl * n_splits * kTb + split * kTb + tb) * w.nr + row;
-    sum = across_halves(sum);
+    const size_t out_row = ((size_t)hl * n_splits * kParts + split * kParts + part) * w.nr + row;
+    sum = across_rows<SumOp>(sum);
     if (row >= w.nr) return;
-    if (half == 0) part_l[out_row] = sum;
+    if (g == 0) part_l[out_row] = sum;
     if (!kNeedO) return;
 #pragma unroll
-    for (int d = 0; d < D / 32; ++d)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-            *(float4 *)(part_o + out_row * D + d * 32 + 8 * r4 + 4 * half) =
-                make_float4(acc[d][4 * r4], acc[d][4 * r4 + 1], acc[d][4 * r4 + 2], acc[d][4 * r4 + 3]);
+    for (int d = 0; d < D / 16; ++d)
+        *(float4 *)(part_o + out_row * D + d * 16 + 4 * g) = make_float4(acc[d][0], acc[d][1], acc[d][2], acc[d][3]);
 }
 
 // ------------------------------------------------------------------------------------
-// Scores of Eq. 4, 5, 6.  Grid: x = `n_tiles` tiles of the piece, z = KV head.  Lane = token (and
-// half), registers = rows.  A workgroup takes its tokens against one chunk of rows after the other.
+// Scores of Eq. 4, 5, 6.  Grid: x = `n_tiles` tiles of the piece, z = KV head.  Lane = token + 16 g, registers = rows
+// 4 g .. 4 g + 3 of the wave's 16.  A workgroup takes its tokens against one chunk of rows after the other.
 // ------------------------------------------------------------------------------------
 constexpr int kScoreTokens = 512;              // most tokens of a workgroup
 template <typename T, int D, int kRb, int kVariant, typename Lens>
-__global__ __launch_bounds__(kThreads, 2) void fixed_score(const T *__restrict__ v, int N, int Hkv, int ragged, Lens lens, Piece w,
-                                                           int n_tiles, const float *__restrict__ z,
-                                                           const RowRecord *__restrict__ records,
-                                                           const float *__restrict__ o, const int8_t *__restrict__ o_digits,
-                                                           float *__restrict__ scores, size_t variant_stride, int add) {
-    constexpr int K = kDigits<T>, kTb = 4 / kRb, kTok = 32 * kTb, kRows = 32 * kRb, kBuf = buffers_of(K * kTok * D);
+__global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restrict__ v, int N, int Hkv, int ragged, Lens lens, Piece w,
+                                                                int n_tiles, const float *__restrict__ z,
+                                                                const RowRecord *__restrict__ records, const float *__restrict__ o,
+                                                                const int8_t *__restrict__ o_digits, float *__restrict__ scores,
+                                                                size_t variant_stride, int add) {
+    constexpr int K = kDigits<T>, kTok = kFixedTile<D, kRb>, kPart = kTok / (8 / kRb), kRows = 16 * kRb;
     constexpr bool kDoV = kVariant == OBC_ALL || kVariant == OBC_VALUE, kDoK = kVariant == OBC_ALL || kVariant == OBC_KEY,
                    kDoJ = kVariant == OBC_ALL || kVariant == OBC_JOINT, kNeedO = kDoK || kDoJ;
+    constexpr int kSums = kVariant == OBC_ALL ? 3 : 1, kBuf = buffers_of(K * kTok * D);
     __shared__ __attribute__((aligned(16))) char digits[kBuf][kNeedO ? K * kTok * D : 16];
     __shared__ __attribute__((aligned(16))) double units[2][kTok];
     __shared__ double vv_s[2][kTok];
     __shared__ __attribute__((aligned(16))) RowRecord rec_s[kRows];
-    __shared__ float sum_s[2][4][3][32];
-    __shared__ float run_s[kVariant == OBC_ALL ? 3 : 1][kScoreTokens];      // sums over the chunks so far
+    __shared__ float sum_s[kSums][kRb][kTok];
+    __shared__ float run_s[kSums][kScoreTokens];             // sums over the chunks so far
+    __shared__ uint32_t close_s[kScoreTokens / 32];          // tokens with a value next to an output, scored below
+    __shared__ float close_sum_s[2][8];
     const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
     const int t_begin = w.s0 + blockIdx.x * n_tiles * kTok, t_stop = min(t_begin + n_tiles * kTok, w.s1), t_end = min(t_stop, len);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
-    const int rb = wave % kRb, tb = wave / kRb;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
+    const int rb = wave % kRb, part = wave / kRb;
     float *out = scores + (size_t)bg * N;
     if (!add)
-        for (int t = max(t_begin, len) + (int)threadIdx.x; t < t_stop; t += kThreads)        // the padding
+        for (int t = max(t_begin, len) + (int)threadIdx.x; t < t_stop; t += kFixedThreads)       // the padding
 #pragma unroll
-            for (int c = 0; c < (kVariant == OBC_ALL ? 3 : 1); ++c) out[c * variant_stride + t] = 0.f;
+            for (int c = 0; c < kSums; ++c) out[c * variant_stride + t] = 0.f;
     if (t_begin >= t_end) return;                            // uniform
     const __amdgpu_buffer_rsrc_t vg = span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
     const __amdgpu_buffer_rsrc_t zg = span_of(z + (size_t)hl * w.nr * w.z_stride, (size_t)w.nr * w.z_stride * sizeof(float));
+    if ((int)threadIdx.x < kScoreTokens / 32) close_s[threadIdx.x] = 0u;         // (two barriers before the first use)
     for (int row0 = 0; row0 < w.nr; row0 += kRows) {
         TokenTile<T, D, kTok> next;
         next.load(vg, 0);
-        const int arow = row0 + rb * 32 + (lane & 31);
+        const int arow = row0 + rb * 16 + (lane & 15);
         RowDigits<kRowDigits, D> rows;
-        if (kNeedO) rows.load(o_digits, (size_t)hl * w.nr + min(arow, w.nr - 1), arow < w.nr, half);
+        if (kNeedO) rows.load(o_digits, (size_t)hl * w.nr + min(arow, w.nr - 1), arow < w.nr, g);
         __syncthreads();                                     // (the chunk before this one is done with)
-        for (int i = threadIdx.x; i < kRows; i += kThreads) {
+        for (int i = threadIdx.x; i < kRows; i += kFixedThreads) {
             RowRecord rec = records[(size_t)hl * w.nr + min(row0 + i, w.nr - 1)];
             if (row0 + i >= w.nr) rec.last = -1;             // no such row: it sees nothing
             rec_s[i] = rec;
@@ -536,89 +546,110 @@ __global__ __launch_bounds__(kThreads, 2) void fixed_score(const T *__restrict__
         if (t_begin + kTok < t_end) next.load(vg, kTok);
         int slot = 0;
         for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
-            const int tok_l = tb * 32 + (lane & 31), p = t0 + tok_l;
-            float x[16];                                     // (rows of z have room for whole tiles)
-            const int at = ((row0 + rb * 32 + 4 * half) * w.z_stride + (p - w.s0)) * 4;
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                x[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(zg, at + (8 * (r >> 2) + (r & 3)) * w.z_stride * 4, 0, 0));
             __syncthreads();                                 // this tile is in LDS, the one before it has been read
-            i32x16 acc[kLevels];
-            if (kNeedO) {
-                level_sums<kRowDigits, K, D, kTok, true>(rows, digits[slot % kBuf], tok_l, half, acc);
-                if (kBuf == 1) __syncthreads();
-            }
-            __builtin_amdgcn_sched_barrier(0);               // (one thing at a time: registers)
-            const double vv = vv_s[slot][tok_l];
-            const double vu = kNeedO ? -2.0 * units[slot][tok_l] : 0.0;
-            if (t0 + kTok < t_end) next.template store_digits<true, kNeedO>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], vv_s[slot ^ 1]);
-            if (t0 + 2 * kTok < t_end) next.load(vg, t0 - t_begin + 2 * kTok);
-            float acc_v = 0.f, acc_k = 0.f, acc_j = 0.f;
-            bool close = false;
+            auto advance = [&]() {
+                if (t0 + kTok < t_end) next.template store_digits<true, kNeedO>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], vv_s[slot ^ 1]);
+                if (t0 + 2 * kTok < t_end) next.load(vg, t0 - t_begin + 2 * kTok);
+            };
+            if (kBuf == 2) advance();
+#pragma unroll 1
+            for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
+                const int tok_l = p0 + (lane & 15), p = t0 + tok_l;
+                float x[4];                                  // (rows of z have room for whole tiles)
+                const int at = ((row0 + rb * 16 + 4 * g) * w.z_stride + (p - w.s0)) * 4;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                __builtin_amdgcn_sched_barrier(0);
-                const RowRecord &rec = rec_s[rb * 32 + 8 * (r >> 2) + 4 * half + (r & 3)];
-                const float a = p <= rec.last ? exp_nonpositive(x[r] - rec.m) * rec.inv_l : 0.f;
-                const float a2 = a * a;
-                if (kDoV) acc_v = fmaf(a, a, acc_v);             // (the same rounding in every variant)
-                if (!kNeedO) continue;
-                const double vo = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
-                const double d2 = fma(vo * rec.unit, vu, vv + rec.oo);                   // ||v_p - o_i||^2
-                const bool is_top = p == rec.top;
-                close |= d2 < vv * 0x1p-22 && p <= rec.last && !is_top;
-                if (kDoK) acc_k = fmaf(a2 * x[r] * x[r], is_top ? rec.top_dk : fmaxf((float)d2, 0.f), acc_k);
-                if (kDoJ) {
-                    const double zd = x[r];                  // ||v_p + Z (v_p - o_i)||^2 with 2 (v_p - o_i).v_p = d2 + vv - oo
-                    const double dj = fma(zd, fma(zd, d2, d2 + (vv - rec.oo)), vv);
-                    acc_j = fmaf(a2, is_top ? rec.top_dj : fmaxf((float)dj, 0.f), acc_j);
+                for (int r = 0; r < 4; ++r) x[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(zg, at + r * w.z_stride * 4, 0, 0));
+                i32x4 acc[kLevels];
+                if (kNeedO) level_sums<kRowDigits, K, D, kTok, true>(rows, digits[slot % kBuf], tok_l, g, acc);
+                const double vv = vv_s[slot][tok_l];
+                const double vu = kNeedO ? -2.0 * units[slot][tok_l] : 0.0;
+                float acc_v = 0.f, acc_k = 0.f, acc_j = 0.f, nearest = INFINITY;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    const RowRecord &rec = rec_s[rb * 16 + 4 * g + r];
+                    const float a = p <= rec.last ? exp_nonpositive(x[r] - rec.m) * rec.inv_l : 0.f;
+                    const float a2 = a * a;
+                    if (kDoV) acc_v = fmaf(a, a, acc_v);     // (the same rounding in every variant)
+                    if (!kNeedO) continue;
+                    const double vo = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
+                    const double d2 = fma(vo * rec.unit, vu, vv + rec.oo);               // ||v_p - o_i||^2
+                    const bool is_top = p == rec.top;
+                    nearest = fminf(nearest, is_top ? INFINITY : (float)d2);
+                    if (kDoK) acc_k = fmaf(a2 * x[r] * x[r], is_top ? rec.top_dk : fmaxf((float)d2, 0.f), acc_k);
+                    if (kDoJ) {
+                        const double zd = x[r];              // ||v_p + Z (v_p - o_i)||^2 with 2 (v_p - o_i).v_p = d2 + vv - oo
+                        const double dj = fma(zd, fma(zd, d2, d2 + (vv - rec.oo)), vv);
+                        acc_j = fmaf(a2, is_top ? rec.top_dj : fmaxf((float)dj, 0.f), acc_j);
+                    }
+                }
+                // v_p within 2^-11 of an o_i: the expanded square has lost too much
+                if (kNeedO && nearest < (float)vv * 0x1p-22f) atomicOr(close_s + ((p - t_begin) >> 5), 1u << ((p - t_begin) & 31));
+                // the other lanes of a token and the other row blocks held other rows
+                int n = 0;
+                auto put = [&](float s) {
+                    s = across_rows<SumOp>(s);
+                    if (g == 0) sum_s[n][rb][tok_l] = s;
+                    ++n;
+                };
+                if (kDoV) put(acc_v * (float)vv);
+                if (kDoK) put(acc_k);
+                if (kDoJ) put(acc_j);
+            }
+            __syncthreads();
+            if ((int)threadIdx.x < kSums * kTok) {           // (the same thread for a token in every chunk)
+                const int c = threadIdx.x / kTok, tok_l = threadIdx.x % kTok, p = t0 + tok_l;
+                float s = 0.f;
+#pragma unroll
+                for (int i = 0; i < kRb; ++i) s += sum_s[c][i][tok_l];
+                if (row0 > 0) s += run_s[c][p - t_begin];
+                if (row0 + kRows < w.nr) run_s[c][p - t_begin] = s;
+                else if (p < t_end && !((kDoV && c == 0) ? 0u : close_s[(p - t_begin) >> 5] >> ((p - t_begin) & 31) & 1u)) {
+                    float *d = out + c * variant_stride + p;
+                    *d = add ? *d + s : s;
                 }
             }
-            // v_p within 2^-11 of o_i: the expanded square has lost too much, the direct one is formed from fp32 v and o
-            if (kNeedO && close && p < t_end) {
-                acc_k = acc_j = 0.f;
-                const T *vp = v + ((size_t)bg * N + p) * D;
-#pragma unroll 1
-                for (int r = 0; r < 16; ++r) {
-                    const int row = rb * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                    const RowRecord &rec = rec_s[row];
-                    if (p > rec.last) continue;
-                    const size_t at_row = (size_t)hl * w.nr + row0 + row;
-                    const float zr = z[at_row * w.z_stride + (p - w.s0)], a = exp_nonpositive(zr - rec.m) * rec.inv_l, a2 = a * a;
+            if (kBuf == 1) advance();
+        }
+    }
+    if (!kNeedO) return;
+    // The squares of the tokens set aside, formed directly from fp32 v and o: a wave per row, elements over its lanes.
+    __syncthreads();
+    for (int i = 0; i < kScoreTokens / 32; ++i)
+        for (uint32_t bits = close_s[i]; bits != 0u; bits &= bits - 1u) {
+            const int p = t_begin + i * 32 + __builtin_ctz(bits);
+            if (p >= t_end) break;                           // uniform
+            constexpr int kE = D / 64;
+            float x[kE], acc_k = 0.f, acc_j = 0.f;
+#pragma unroll
+            for (int e = 0; e < kE; ++e) x[e] = load_as_float(v + ((size_t)bg * N + p) * D + lane * kE + e);
+            for (int row0 = wave; row0 < w.nr; row0 += 32)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {                // (four rows' loads in flight)
+                    const int row = row0 + 8 * u;
+                    const size_t at = (size_t)hl * w.nr + min(row, w.nr - 1);
+                    const RowRecord rec = records[at];
+                    const float zr = z[at * w.z_stride + (p - w.s0)];
+                    const float a = row < w.nr && p <= rec.last ? exp_nonpositive(zr - rec.m) * rec.inv_l : 0.f, a2 = a * a;
                     float d2 = 0.f, dj = 0.f;
-#pragma unroll 4
-                    for (int c = 0; c < D; ++c) {
-                        const float x = load_as_float(vp + c), diff = x - o[at_row * D + c], comb = fmaf(zr, diff, x);
+#pragma unroll
+                    for (int e = 0; e < kE; ++e) {
+                        const float diff = x[e] - o[at * D + lane * kE + e], comb = fmaf(zr, diff, x[e]);
                         d2 = fmaf(diff, diff, d2);
                         dj = fmaf(comb, comb, dj);
                     }
-                    acc_k = fmaf(a2 * zr * zr, p == rec.top ? rec.top_dk : d2, acc_k);
-                    acc_j = fmaf(a2, p == rec.top ? rec.top_dj : dj, acc_j);
+                    acc_k = fmaf(a2 * zr * zr, p == rec.top ? rec.top_dk : wave_reduce<SumOp>(d2), acc_k);
+                    acc_j = fmaf(a2, p == rec.top ? rec.top_dj : wave_reduce<SumOp>(dj), acc_j);
                 }
-            }
-            // the other half of the wave and the other row blocks held other rows
-            auto put = [&](int c, float s) {
-                s = across_halves(s);
-                if (half == 0) sum_s[slot][wave][c][lane] = s;
-            };
-            if (kDoV) put(0, acc_v * (float)vv);
-            if (kDoK) put(1, acc_k);
-            if (kDoJ) put(2, acc_j);
+            if (lane == 0) { close_sum_s[0][wave] = acc_k; close_sum_s[1][wave] = acc_j; }
             __syncthreads();
-            if (rb == 0 && half == 0 && p < t_end) {
-                int n = 0;
+            if ((int)threadIdx.x < 2 && (threadIdx.x == 0 ? kDoK : kDoJ)) {
+                float s = 0.f;
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    if ((c == 0 && !kDoV) || (c == 1 && !kDoK) || (c == 2 && !kDoJ)) continue;
-                    float s = 0.f;
-#pragma unroll
-                    for (int q = 0; q < kRb; ++q) s += sum_s[slot][wave + q][c][lane];
-                    float *d = out + (n++) * variant_stride + p;
-                    if (row0 > 0) s += run_s[n - 1][p - t_begin];                // (same thread in every chunk)
-                    if (row0 + kRows < w.nr) run_s[n - 1][p - t_begin] = s;
-                    else *d = add ? *d + s : s;
-                }
+                for (int c = 0; c < 8; ++c) s += close_sum_s[threadIdx.x][c];
+                float *d = out + (kVariant == OBC_ALL ? 1 + threadIdx.x : 0) * variant_stride + p;
+                *d = add ? *d + s : s;
             }
+            __syncthreads();
         }
-    }
 }

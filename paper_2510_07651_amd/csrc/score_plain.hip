@@ -607,7 +607,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     double *q_units = (double *)(base + ws.pl_q_units);
     // More than 32 rows are taken apart into digits; 64 or 128 of them per workgroup.
     constexpr bool fixed = kRt == 4 || kRt == 8;
-    constexpr int kRb = kRt == 8 ? 4 : 2;
+    constexpr int kRb = kRt == 8 ? 8 : 4;
     const bool need_o = a.variant == OBC_KEY || a.variant == OBC_JOINT || a.variant == OBC_ALL;
     const int BH = a.B * a.Hkv, M = a.G * a.W;
     const size_t variant_stride = (size_t)BH * a.N;
@@ -626,11 +626,11 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             w.bg0 = bg0; w.r0 = r0; w.nr = std::min(ws.pl_rows, M - r0); w.z_stride = ws.pl_z_stride;
             const unsigned heads = std::min(ws.pl_heads, BH - bg0), chunks = (w.nr + 16 * kFewRt - 1) / (16 * kFewRt);
             auto segment = [&](int i) { w.s0 = i * ws.pl_seg; w.s1 = std::min(w.s0 + ws.pl_seg, a.N); };
-            const unsigned row_chunks = (w.nr + 32 * kRb - 1) / (32 * kRb);         // (score_fixed.h)
+            const unsigned row_chunks = (w.nr + 16 * kRb - 1) / (16 * kRb);         // (score_fixed.h)
             auto logits = [&]() {
                 const unsigned ranges = (w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range;
                 if constexpr (fixed)
-                    fixed_logits<T, D, kRb><<<dim3(ranges, row_chunks, heads), dim3(kThreads), 0, stream>>>(
+                    fixed_logits<T, D, kRb><<<dim3(ranges, row_chunks, heads), dim3(kFixedThreads), 0, stream>>>(
                         q_digits, q_units, k, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 else
                     plain_logits<T, D, kRt><<<dim3(ranges, chunks, heads), dim3(kThreads), 0, stream>>>(
@@ -656,7 +656,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                     auto weights = [&](auto with_output) {
                         constexpr bool kNeedO = decltype(with_output)::value;
                         if constexpr (fixed)
-                            fixed_weights<T, D, kRb, kNeedO><<<dim3(grid.x, row_chunks, heads), dim3(kThreads), 0, stream>>>(
+                            fixed_weights<T, D, kRb, kNeedO><<<dim3(grid.x, row_chunks, heads), dim3(kFixedThreads), 0, stream>>>(
                                 v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
                                 best, rec, part_l, part_o);
                         else
@@ -671,7 +671,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             }
             if (mask & OBC_STAGE_COMBINE) {
                 const dim3 grid((w.nr + 3) / 4, 1, heads);
-                const int per_split = fixed ? 4 / kRb : 1;
+                const int per_split = fixed ? 8 / kRb : 1;
 #define OBC_PLAIN_MERGE(need_o, fixed)                                                                                 \
     plain_merge<T, D, need_o, fixed><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split,  \
                                                                           ws.pl_splits * per_split, per_split, part_l, part_o, \
@@ -687,12 +687,12 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                 segment(i);
                 if (segs > 1 && !logits()) return e;
                 if (fixed && a.variant != OBC_ATTN && a.variant != OBC_VATP) {
-                    constexpr int kTok = 128 / kRb;
+                    constexpr int kTok = kFixedTile<D, kRb>;
                     const int tiles = (w.s1 - w.s0 + kTok - 1) / kTok;
                     const int n_tiles = (int)std::min((tiles * (long long)heads + kResident / 2 - 1) / (kResident / 2), kScoreTokens / kTok + 0ll);
                     const dim3 grid((tiles + n_tiles - 1) / n_tiles, 1, heads);
 #define OBC_FIXED_SCORE(variant)                                                                                       \
-    fixed_score<T, D, kRb, variant><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_digits, \
+    fixed_score<T, D, kRb, variant><<<grid, dim3(kFixedThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_digits, \
                                                                          a.scores, variant_stride, a.accumulate || r0 > 0)
                     if (a.variant == OBC_VALUE) OBC_FIXED_SCORE(OBC_VALUE);
                     else if (a.variant == OBC_KEY) OBC_FIXED_SCORE(OBC_KEY);
