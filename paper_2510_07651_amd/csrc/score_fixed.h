@@ -26,47 +26,58 @@ template <typename T> constexpr int kDigits = sizeof(T) == 4 ? 5 : 4;
 constexpr int kRowDigits = 5;                  // of o_i, which is fp32 whatever the inputs are
 constexpr int kLevels = 5;
 
-// Shape of a workgroup: eight waves, each with 16 window rows; kRb = 8 takes 128 rows, kRb = 4 takes 64 and two halves of a
-// token tile.  Rows and sums of a wave fit 128 registers, so that four waves share a SIMD and hide each other's latencies
-// (with 32 rows per wave and two waves the three kernels took 30, 37 and 43 us at the shape above).
-constexpr int kFixedThreads = 512;
-template <int D, int kRb> constexpr int kFixedTile = D == 64 || kRb == 4 ? 64 : 32;      // tokens
+// A wave has 16 window rows: the rows' digits and a block's sums fit 128 registers, so that four waves share a SIMD and hide
+// each other's latencies (with 32 rows per wave and two waves the three kernels took 30, 37 and 43 us at the shape above).
+// kRb = 8 puts 128 rows into a workgroup; kRb = 4 puts 64 and gives its waves different parts of a token tile.
+constexpr int kFixedThreads = 512, kWeightThreads = 1024;
+template <int D> constexpr int kFixedTile = D == 64 ? 64 : 32;           // tokens
 
-// Maximum that lets a NaN through.
-struct MaximumOp { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_elementwise_maximum(a, b); } };
-__device__ __forceinline__ float max_abs(const float (&x)[4], float m) {
-    const MaximumOp op;
-    return op(op(op(op(m, fabsf(x[0])), fabsf(x[1])), fabsf(x[2])), fabsf(x[3]));
+// Layouts in memory, such that a wave reads and writes whole kilobytes (a lane has one row; rows side by side in memory would
+// make every lane's 16 bytes a line of their own: 64 cache accesses instead of 8).
+//   z       [head][row / 16][token / 16][token % 16 / 4][row % 16][token % 4]
+//   digits  [head][row / 16][digit][element / 64][element % 64 / 16][row % 16][element % 16]
+__device__ __forceinline__ size_t z_block(const Piece &w, int hl, int row_block, int token) {
+    return (((size_t)hl * ((w.nr + 15) / 16) + row_block) * (w.z_stride / 16) + (token - w.s0) / 16) * 256;
 }
-// Exponent e with |x|max < 2^e, kept where its scale is a normal number (a smaller maximum only loses bits no product shows).
-__device__ __forceinline__ int max_exponent(float amax) { return max((int)(__float_as_uint(amax) >> 23 & 255) - 126, -96); }
-// 2^(30 - e), which turns an element into its fixed-point integer ...
-__device__ __forceinline__ float digit_scale(int e) { return __uint_as_float((uint32_t)(157 - e) << 23); }
-// ... and 2^(e - 18), a row's share of the unit of a dot product; NaN where an element was infinite or not a number.
+template <int K, int D>
+__device__ __forceinline__ size_t digit_address(size_t block, int k, int row, int c) {
+    return ((block * K + k) * (D / 64) + c / 64) * 1024 + (c % 64 / 16 * 16 + row % 16) * 16 + c % 16;
+}
+
+// Largest |x|, as bits: integers order them like the numbers and put what is not a number on top.
+struct MaxBitsOp { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; } };
+__device__ __forceinline__ uint32_t max_abs(const float (&x)[4]) {
+    const float m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x[0]), fabsf(x[1])),
+                                                  __builtin_elementwise_maximum(fabsf(x[2]), fabsf(x[3])));
+    return __float_as_uint(m) & 0x7fffffffu;
+}
+// Exponent e with |x|max < 2^e.
+__device__ __forceinline__ int max_exponent(uint32_t amax) { return (int)(amax >> 23) - 126; }
+// A row's share of the unit of a dot product, 2^(e - 18); NaN where an element was infinite or not a number.
 __device__ __forceinline__ double row_unit(int e) { return e > 128 ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, e - 18); }
 
-// The digits of four elements, most significant first, one byte per element: 128 added to every digit of the fixed-point
-// integer makes its bytes the digits plus 128, carries included.
+// The digits of four elements, most significant first, one byte per element.  The sum with 1.5 * 2^52 rounds to the
+// fixed-point integer and leaves it in the low bits; 128 added to every digit makes its bytes the digits plus 128.
 template <int K>
-__device__ __forceinline__ void digits_of(const float (&x)[4], float scale, uint32_t (&plane)[K]) {
-    uint32_t w[4], low[4];
+__device__ __forceinline__ void digits_of(const double (&x)[4], int e, uint32_t (&plane)[K]) {
+    const double scale = __hiloint2double((1023 + (K == 5 ? 38 : 30) - e) << 20, 0);
+    const double bias = 6755399441055744.0 + (K == 5 ? (double)0x8080808080ll : (double)0x80808080ll);
+    uint32_t w[4], top[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float y = x[i] * scale, h = rintf(y);           // |y| <= 2^30; both exact
-        w[i] = (uint32_t)(int)h + 0x80808080u;
-        if (K == 5) {
-            const uint32_t l = __float_as_uint(fmaf(y - h, 256.f, 12582912.f + 128.f)) & 511u;     // 0 .. 256
-            w[i] += l >> 8;
-            low[i] = l & 255u;
-        }
+        const double t = fma(x[i], scale, bias);
+        w[i] = (uint32_t)__double2loint(t);
+        top[i] = (uint32_t)__double2hiint(t);
     }
     const uint32_t t0 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602), t1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602);
     const uint32_t u0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400), u1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400);
-    plane[0] = __builtin_amdgcn_perm(t1, t0, 0x07060302) ^ 0x80808080u;
-    plane[1] = __builtin_amdgcn_perm(t1, t0, 0x05040100) ^ 0x80808080u;
-    plane[2] = __builtin_amdgcn_perm(u1, u0, 0x07060302) ^ 0x80808080u;
-    plane[3] = __builtin_amdgcn_perm(u1, u0, 0x05040100) ^ 0x80808080u;
-    if (K == 5) plane[K - 1] = (low[0] | low[1] << 8 | low[2] << 16 | low[3] << 24) ^ 0x80808080u;
+    plane[K - 4] = __builtin_amdgcn_perm(t1, t0, 0x07060302) ^ 0x80808080u;
+    plane[K - 3] = __builtin_amdgcn_perm(t1, t0, 0x05040100) ^ 0x80808080u;
+    plane[K - 2] = __builtin_amdgcn_perm(u1, u0, 0x07060302) ^ 0x80808080u;
+    plane[K - 1] = __builtin_amdgcn_perm(u1, u0, 0x05040100) ^ 0x80808080u;
+    if (K == 5)
+        plane[0] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(top[3], top[2], 0x0c0c0400),
+                                         __builtin_amdgcn_perm(top[1], top[0], 0x0c0c0400), 0x05040100) ^ 0x80808080u;
 }
 
 // x . y of the two fixed-point vectors from the level sums, in units of row_unit(ex) row_unit(ey).
@@ -93,21 +104,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_of(const void *p, size_t 
 // ------------------------------------------------------------------------------------
 // Token tiles: kTok rows of k or v on their way from memory into LDS.
 // ------------------------------------------------------------------------------------
-template <typename T, int D, int kTok>
+template <typename T, int D, int kTok, int kTileThreads>
 struct TokenTile {
     static constexpr int kPer = 16 / (int)sizeof(T);                     // elements of a 16-byte piece
     static constexpr int kLanes = D / kPer;                              // lanes per row
-    static constexpr int kCount = kTok * kLanes / kFixedThreads;
-    static_assert(kTok * kLanes % kFixedThreads == 0, "whole pieces per thread");
+    static constexpr int kCount = kTok * kLanes / kTileThreads;
+    static_assert(kTok * kLanes % kTileThreads == 0, "whole pieces per thread");
+    static constexpr int kStep = kTileThreads / kLanes;                  // rows from one piece of a thread to its next
+    static_assert(kStep % 16 == 0, "the swizzles repeat every 16 rows");
     uint4 x[kCount];
 
-    __device__ __forceinline__ int row(int i) const { return ((int)threadIdx.x + i * kFixedThreads) / kLanes; }
-    __device__ __forceinline__ int piece() const { return (int)threadIdx.x % kLanes; }
     // Rows from row t of the span; rows beyond its end become zeros.
     __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t span, int t) {
+        int thread = threadIdx.x;
+        asm volatile("" : "+v"(thread));                     // (addresses anew for every tile: registers)
 #pragma unroll
         for (int i = 0; i < kCount; ++i) {
-            const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(span, (t * kLanes + (int)threadIdx.x + i * kFixedThreads) * 16, 0, 0);
+            const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(span, (t * kLanes + thread + i * kTileThreads) * 16, 0, 0);
             x[i] = make_uint4(u.x, u.y, u.z, u.w);
         }
     }
@@ -137,86 +150,96 @@ struct TokenTile {
         }
         return v;
     }
-    // Digits and units into LDS, with kNorms also the rows' squared norms.
-    template <bool kNorms, bool kDigitsToo = true>
-    __device__ __forceinline__ void store_digits(char *digits, double *units, double *vv) const {
+    // Digits and units into LDS and, where asked for, the rows' norms: ||v||^2 (2) or ||v||_1 (1).
+    template <bool kWithDigits, int kNorm>
+    __device__ __forceinline__ void store_digits(char *digits, double *units, double *norms) const {
         constexpr int K = kDigits<T>;
+        int thread = threadIdx.x;
+        asm volatile("" : "+v"(thread));                     // (addresses anew for every tile: registers)
+        const int r0 = thread / kLanes, c = thread % kLanes;
+        char *dst = digits + digit_offset<D, kTok>(0, r0, c * kPer / 16) + c * kPer % 16;
 #pragma unroll
         for (int i = 0; i < kCount; ++i) {
+            __builtin_amdgcn_sched_barrier(0);               // (one piece at a time: registers)
             float y[kPer / 4][4];
             unpack(i, y);
-            const int r = row(i);
-            if constexpr (kDigitsToo) {
-                float amax = 0.f;
+            double yd[kPer / 4][4];
 #pragma unroll
-                for (int q = 0; q < kPer / 4; ++q) amax = max_abs(y[q], amax);
-                const int e = max_exponent(over_row<MaximumOp>(amax));
-                const float scale = digit_scale(e);
+            for (int q = 0; q < kPer / 4; ++q)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) yd[q][k] = y[q][k];
+            if constexpr (kWithDigits) {
+                uint32_t amax = max_abs(y[0]);
+                if (kPer == 8) amax = MaxBitsOp()(amax, max_abs(y[kPer / 4 - 1]));
+                const int e = max_exponent(over_row<MaxBitsOp>(amax));
                 uint32_t p[kPer / 4][K];
 #pragma unroll
-                for (int q = 0; q < kPer / 4; ++q) digits_of<K>(y[q], scale, p[q]);
+                for (int q = 0; q < kPer / 4; ++q) digits_of<K>(yd[q], e, p[q]);
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    if constexpr (kPer == 4) *(uint32_t *)(digits + digit_offset<D, kTok>(k, r, piece() >> 2) + (piece() & 3) * 4) = p[0][k];
-                    else *(uint2 *)(digits + digit_offset<D, kTok>(k, r, piece() >> 1) + (piece() & 1) * 8) = make_uint2(p[0][k], p[1][k]);
+                    char *at = dst + (k * kTok + i * kStep) * D;
+                    if constexpr (kPer == 4) *(uint32_t *)at = p[0][k];
+                    else *(uint2 *)at = make_uint2(p[0][k], p[1][k]);
                 }
-                if (piece() == 0) units[r] = row_unit(e);
+                if (c == 0) units[r0 + i * kStep] = row_unit(e);
             }
-            if (kNorms) {
+            if (kNorm != 0) {
                 double s = 0.0;
 #pragma unroll
                 for (int q = 0; q < kPer / 4; ++q)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) s = fma((double)y[q][c], (double)y[q][c], s);
+                    for (int k = 0; k < 4; ++k) s = kNorm == 2 ? fma(yd[q][k], yd[q][k], s) : s + fabs(yd[q][k]);
                 s = over_row<SumOp>(s);
-                if (piece() == 0) vv[r] = s;
+                if (c == 0) norms[r0 + i * kStep] = s;
             }
         }
     }
 };
 
 // ------------------------------------------------------------------------------------
-// Rows of q as digits in memory: [row][K][D] bytes and a unit per row.  Four elements per lane.
+// Rows of q as digits in memory, and a unit per row.  Four elements per lane; the last block of rows is filled up.
 // ------------------------------------------------------------------------------------
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void fixed_rows(const T *__restrict__ q, int W, int Hq, int Hkv, Piece w,
                                                        int8_t *__restrict__ digits, double *__restrict__ units) {
     constexpr int K = kDigits<T>, kLanes = D / 4;
-    const int row = ((int)blockIdx.x * kThreads + (int)threadIdx.x) / kLanes, c = threadIdx.x % kLanes, hl = blockIdx.z;
-    const int bg = w.bg0 + hl, M = Hq / Hkv * W;
-    const T *src = q + ((size_t)(bg / Hkv) * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D + c * 4;
+    const int row = ((int)blockIdx.x * kThreads + (int)threadIdx.x) / kLanes, c = threadIdx.x % kLanes * 4, hl = blockIdx.z;
+    const int bg = w.bg0 + hl, M = Hq / Hkv * W, blocks = (w.nr + 15) / 16;
+    const T *src = q + ((size_t)(bg / Hkv) * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D + c;
     float x[4];
+    double xd[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = load_as_float(src + i);
-    using Tile = TokenTile<float, D, 64>;                    // (four elements per lane: its lane layout)
-    const int e = max_exponent(Tile::template over_row<MaximumOp>(max_abs(x, 0.f)));
+    for (int i = 0; i < 4; ++i) xd[i] = x[i] = load_as_float(src + i);
+    using Tile = TokenTile<float, D, 64, kFixedThreads>;     // (four elements per lane: its lane layout)
+    const int e = max_exponent(Tile::template over_row<MaxBitsOp>(max_abs(x)));
     uint32_t p[K];
-    digits_of<K>(x, digit_scale(e), p);
-    if (row >= w.nr) return;
-    const size_t at = (size_t)hl * w.nr + row;
+    digits_of<K>(xd, e, p);
+    if (row >= blocks * 16) return;
 #pragma unroll
-    for (int k = 0; k < K; ++k) *(uint32_t *)(digits + (at * K + k) * D + c * 4) = p[k];
-    if (c == 0) units[at] = row_unit(e);
+    for (int k = 0; k < K; ++k) *(uint32_t *)(digits + digit_address<K, D>((size_t)hl * blocks + row / 16, k, row, c)) = p[k];
+    if (c == 0 && row < w.nr) units[(size_t)hl * w.nr + row] = row_unit(e);
 }
 
 // A wave's 16 rows of digits as a matrix operand: lane = row + 16 g holds bytes 16 g .. 16 g + 15 of every 64.
 template <int K, int D>
 struct RowDigits {
     i32x4 x[K][D / 64];
-    __device__ __forceinline__ void load(const int8_t *__restrict__ digits, size_t at, bool live, int g) {
+    __device__ __forceinline__ void load(const int8_t *__restrict__ digits, int hl, int block, int blocks, int lane) {
+        const __amdgpu_buffer_rsrc_t span = span_of(digits + digit_address<K, D>((size_t)hl * blocks, 0, 0, 0), (size_t)blocks * 16 * K * D);
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
             for (int kk = 0; kk < D / 64; ++kk)
-                x[k][kk] = live ? *(const i32x4 *)(digits + (at * K + k) * D + kk * 64 + g * 16) : i32x4{0, 0, 0, 0};
+                x[k][kk] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                         span, (int)digit_address<K, D>(block, k, 0, kk * 64) + lane * 16, 0, 0));
     }
 };
 
 // Buffers of a tile: two where two workgroups fit a CU with them, else one (and a barrier more per tile).
 constexpr int buffers_of(int bytes) { return bytes <= 32 * 1024 ? 2 : 1; }
 
-// Level sums of 16 rows against 16 tokens in LDS.  kRowsFirst: accumulator rows are window rows and lanes are tokens.
-template <int KR, int KT, int D, int kTok, bool kRowsFirst>
+// Level sums of 16 tokens in LDS (accumulator rows) and 16 window rows (lanes).
+template <int KR, int KT, int D, int kTok>
 __device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const char *digits, int tok, int g, i32x4 (&acc)[kLevels]) {
 #pragma unroll
     for (int t = 0; t < kLevels; ++t) acc[t] = i32x4{0, 0, 0, 0};
@@ -230,13 +253,13 @@ __device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const c
         for (int k = 0; k < KT; ++k)
 #pragma unroll
             for (int i = 0; i < KR && i + k < kLevels; ++i)
-                acc[i + k] = kRowsFirst ? __builtin_amdgcn_mfma_i32_16x16x64_i8(rows.x[i][kk], b[k], acc[i + k], 0, 0, 0)
-                                        : __builtin_amdgcn_mfma_i32_16x16x64_i8(b[k], rows.x[i][kk], acc[i + k], 0, 0, 0);
+                acc[i + k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b[k], rows.x[i][kk], acc[i + k], 0, 0, 0);
     }
 }
 
 // ------------------------------------------------------------------------------------
-// Logits.  Grid: x = token range of the piece, y = chunk of 16 kRb rows, z = KV head.  Wave w takes row block w % kRb and
+// Logits.  Grid: x = KV head (neighbours run on different XCDs, whose L2 caches then hold the rows, values and logits of
+// few heads), y = token range of the piece, z = chunk of 16 kRb rows.  Wave w takes row block w % kRb and
 // part w / kRb of every tile, 16 tokens at a time; lane = row + 16 g, registers = tokens 4 g .. 4 g + 3.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int kRb, typename Lens>
@@ -244,42 +267,42 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_logits(const int8_t *_
                                                                  const T *__restrict__ k, int N, int W, int Hkv, int ragged, Lens lens,
                                                                  Piece w, int range_len, int n_ranges, float *__restrict__ z,
                                                                  float2 *__restrict__ range_best) {
-    constexpr int K = kDigits<T>, kTok = kFixedTile<D, kRb>, kPart = kTok / (8 / kRb), kBuf = buffers_of(K * kTok * D);
+    constexpr int K = kDigits<T>, kTok = kFixedTile<D>, kPart = kTok / (8 / kRb), kBuf = buffers_of(K * kTok * D);
     __shared__ __attribute__((aligned(16))) char digits[kBuf][K * kTok * D];
     __shared__ __attribute__((aligned(16))) double units[2][kTok];
     __shared__ float2 best_s[8][16];
-    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
+    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int range = w.s0 / range_len + blockIdx.x;
+    const int range = w.s0 / range_len + blockIdx.y;
     const int t_begin = range * range_len, t_end = min(min(t_begin + range_len, w.s1), len);
     if (t_begin >= t_end) return;                            // uniform
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
     const int rb = wave % kRb, part = wave / kRb;
-    const int row = ((int)blockIdx.y * kRb + rb) * 16 + (lane & 15);
+    const int block = (int)blockIdx.z * kRb + rb, blocks = (w.nr + 15) / 16, row = block * 16 + (lane & 15);
     const bool live = row < w.nr;
     const __amdgpu_buffer_rsrc_t kg = span_of(k + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
-    TokenTile<T, D, kTok> next;
+    TokenTile<T, D, kTok, kFixedThreads> next;
     next.load(kg, 0);
     RowDigits<K, D> rows;
-    rows.load(q_digits, (size_t)hl * w.nr + min(row, w.nr - 1), live, g);
+    rows.load(q_digits, hl, block, blocks, lane);
     const double qu = live ? q_units[(size_t)hl * w.nr + row] * (1.0 / sqrt((double)D)) : 0.0;
     const int last = live ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;         // last token the row sees here
-    float *zp = z + ((size_t)hl * w.nr + row) * w.z_stride - w.s0;
+    float *zp = z + z_block(w, hl, block, t_begin) + lane * 4;
     float m = -INFINITY;
     int at = kNoToken;
-    next.template store_digits<false>(digits[0], units[0], nullptr);
+    next.template store_digits<true, 0>(digits[0], units[0], nullptr);
     if (t_begin + kTok < t_end) next.load(kg, kTok);
     int slot = 0;
     for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
         __syncthreads();                                     // this tile is in LDS, the one before it has been read
         if (kBuf == 2) {
-            if (t0 + kTok < t_end) next.template store_digits<false>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], nullptr);
+            if (t0 + kTok < t_end) next.template store_digits<true, 0>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], nullptr);
             if (t0 + 2 * kTok < t_end) next.load(kg, t0 - t_begin + 2 * kTok);
         }
 #pragma unroll 1
         for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
             i32x4 acc[kLevels];
-            level_sums<K, K, D, kTok, false>(rows, digits[slot % kBuf], p0 + (lane & 15), g, acc);
+            level_sums<K, K, D, kTok>(rows, digits[slot % kBuf], p0 + (lane & 15), g, acc);
             const double2 u01 = *(const double2 *)(units[slot] + p0 + 4 * g), u23 = *(const double2 *)(units[slot] + p0 + 4 * g + 2);
             const double ku[4] = {u01.x, u01.y, u23.x, u23.y};
             float x[4];
@@ -290,11 +313,11 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_logits(const int8_t *_
                 const int p = t0 + p0 + 4 * g + i;
                 if (p <= last && x[i] > m) { m = x[i]; at = p; }         // (tokens ascend: strict keeps the lowest)
             }
-            if (live) *(float4 *)(zp + t0 + p0 + 4 * g) = make_float4(x[0], x[1], x[2], x[3]);   // (rows of z have room for whole tiles)
+            if (block < blocks) *(float4 *)(zp + (t0 - t_begin + p0) * 16) = make_float4(x[0], x[1], x[2], x[3]);   // (room for whole tiles)
         }
         if (kBuf == 1) {
             __syncthreads();
-            if (t0 + kTok < t_end) next.template store_digits<false>(digits[0], units[slot ^ 1], nullptr);
+            if (t0 + kTok < t_end) next.template store_digits<true, 0>(digits[0], units[slot ^ 1], nullptr);
             if (t0 + 2 * kTok < t_end) next.load(kg, t0 - t_begin + 2 * kTok);
         }
     }
@@ -324,8 +347,9 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_logits(const int8_t *_
 }
 
 // ------------------------------------------------------------------------------------
-// Weights and P V.  Grid: x = split of the piece, y = chunk of 16 kRb rows, z = KV head.  O^T += V^T P^T, 32 tokens at a
-// time; lane = row + 16 g.  The parts of a tile (8 / kRb of them) are splits of their own.
+// Weights and P V.  Grid: x = KV head, y = split of the piece, z = chunk of 16 kRb rows.  O^T += V^T P^T, 32 tokens
+// at a time; lane = row + 16 g.  The parts of a tile (16 / kRb of them) meet in LDS at the
+// end: two waves per SIMD are too few to hide the chain logit, weight, product, and more splits would be more traffic.
 // ------------------------------------------------------------------------------------
 // V pieces in LDS: kP planes of kTok rows of D bf16.  A row's 16-byte piece c sits where the transposing read (32 lanes
 // fetch 32 bytes each of eight consecutive tokens) meets every bank once.
@@ -348,38 +372,50 @@ __device__ __forceinline__ void three_pieces(float a, float b, uint32_t (&p)[3])
     }
 }
 
+// Tokens of a tile: 32 for every part, or 64 where a tile would have fewer 16-byte pieces than threads.
+template <typename T, int D, int kRb>
+constexpr int kWeightTile = 16 / kRb * 32 * D * (int)sizeof(T) >= kWeightThreads * 16 ? 16 / kRb * 32 : 16 / kRb * 64;
 template <typename T, int D, int kRb, bool kNeedO, typename Lens>
-__global__ __launch_bounds__(kFixedThreads, 4) void fixed_weights(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
+__global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
                                                                   Piece w, int range_len, int n_ranges, int split_len, int n_splits,
                                                                   const float *__restrict__ z, const float2 *__restrict__ range_best,
                                                                   RowRecord *__restrict__ records, float *__restrict__ part_l,
                                                                   float *__restrict__ part_o) {
-    constexpr int kTok = kFixedTile<D, kRb>, kParts = 8 / kRb, kPart = kTok / kParts, kP = sizeof(T) == 4 ? 3 : 1, kRows = 16 * kRb,
-                  kBuf = buffers_of(kP * kTok * D * 2);
-    __shared__ __attribute__((aligned(16))) char values[kBuf][kNeedO ? kP * kTok * D * 2 : 16];
+    constexpr int kTok = kWeightTile<T, D, kRb>, kParts = 16 / kRb, kPart = kTok / kParts, kP = sizeof(T) == 4 ? 3 : 1,
+                  kRows = 16 * kRb, kTileBytes = kP * kTok * D * 2, kBuf = kTileBytes <= 64 * 1024 ? 2 : 1;
+    constexpr int kMergeBytes = (kParts - 1) * kRows * D * 4;
+    __shared__ __attribute__((aligned(16))) char values[kNeedO ? (kBuf * kTileBytes > kMergeBytes ? kBuf * kTileBytes : kMergeBytes) : 16];
+    __shared__ float sum_s[kParts][kRows];
     __shared__ float m_s[kRows];
     __shared__ int top_s[kRows];
-    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
+    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int split = w.s0 / split_len + blockIdx.x;
+    const int split = w.s0 / split_len + blockIdx.y;
     const int t_begin = split * split_len, t_end = min(min(t_begin + split_len, w.s1), len);
     if (t_begin >= t_end) return;                            // uniform
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
-    const int rb = wave % kRb, part = wave / kRb, row0 = blockIdx.y * kRows;
+    const int rb = wave % kRb, part = wave / kRb, row0 = blockIdx.z * kRows;
     const __amdgpu_buffer_rsrc_t vg = span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
-    TokenTile<T, D, kTok> next;
+    TokenTile<T, D, kTok, kWeightThreads> next;
     if (kNeedO) next.load(vg, 0);
     const int row_l = rb * 16 + (lane & 15), row = row0 + row_l;
-    const float *zp = z + ((size_t)hl * w.nr + min(row, w.nr - 1)) * w.z_stride - w.s0 + part * kPart + 4 * g;
+    const int block = min(row0 / 16 + rb, (w.nr + 15) / 16 - 1);
+    const size_t z_head = z_block(w, hl, 0, w.s0);
+    const __amdgpu_buffer_rsrc_t zg = span_of(z + z_head, z_block(w, 1, 0, w.s0) * 4);
+    const int z_at = (int)(z_block(w, hl, block, t_begin) - z_head) * 4 + lane * 16;
     // This lane's logits of a 32-token step: tokens 4 g + {0..3} and 16 + 4 g + {0..3}, the order of the transposing reads.
+    // (What lies beyond the last token's tile is anything, and not used.)
     float4 x[2 * (kPart / 32)];
     auto fetch = [&](int t0) {
 #pragma unroll
-        for (int i = 0; i < 2 * (kPart / 32); ++i) x[i] = *(const float4 *)(zp + t0 + 16 * i);     // (rows of z have room for whole tiles)
+        for (int i = 0; i < 2 * (kPart / 32); ++i) {
+            const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(zg, z_at + (t0 - t_begin + part * kPart + 16 * i) * 64, 0, 0);
+            x[i] = make_float4(__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w));
+        }
     };
     fetch(t_begin);
     {
-        constexpr int kSub = kFixedThreads / kRows;          // the row's maximum over its ranges: kSub lanes per row
+        constexpr int kSub = kWeightThreads / kRows;          // the row's maximum over its ranges: kSub lanes per row
         const int row = threadIdx.x / kSub, live = (len + range_len - 1) / range_len;
         float m = -INFINITY;
         int at = kNoToken;
@@ -401,10 +437,15 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_weights(const T *__res
         }
     }
     auto store_values = [&](int slot) {
+        int thread = threadIdx.x;
+        asm volatile("" : "+v"(thread));                     // (addresses anew for every tile: registers)
+        const int c = thread % next.kLanes;
+        char *dst = values + slot % kBuf * kTileBytes + value_offset<D, kTok>(0, thread / next.kLanes, c * next.kPer / 8) + c * next.kPer % 8 * 2;
 #pragma unroll
         for (int i = 0; i < next.kCount; ++i) {
+            char *at = dst + i * next.kStep * D * 2;
             if constexpr (kP == 1) {
-                *(uint4 *)(values[slot % kBuf] + value_offset<D, kTok>(0, next.row(i), next.piece())) = next.x[i];
+                *(uint4 *)at = next.x[i];
             } else {
                 float y[1][4];
                 next.unpack(i, y);
@@ -412,9 +453,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_weights(const T *__res
                 three_pieces(y[0][0], y[0][1], p[0]);
                 three_pieces(y[0][2], y[0][3], p[1]);
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
-                    *(uint2 *)(values[slot % kBuf] + value_offset<D, kTok>(k, next.row(i), next.piece() >> 1) + (next.piece() & 1) * 8) =
-                        make_uint2(p[0][k], p[1][k]);
+                for (int k = 0; k < 3; ++k) *(uint2 *)(at + k * kTok * D * 2) = make_uint2(p[0][k], p[1][k]);
             }
         }
     };
@@ -473,7 +512,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_weights(const T *__res
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
                         a.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(
-                            values[slot % kBuf] + value_offset<D, kTok>(k, tok_l + 32 * s + 16 * h, 2 * d + c_l) + byte_l));
+                            values + slot % kBuf * kTileBytes + value_offset<D, kTok>(k, tok_l + 32 * s + 16 * h, 2 * d + c_l) + byte_l));
 #pragma unroll
                     for (int j = 0; j + k < 3; ++j)
                         acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, p[s][j].v, acc[d], 0, 0, 0);
@@ -483,19 +522,38 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_weights(const T *__res
             advance();
         }
     }
-    const size_t out_row = ((size_t)hl * n_splits * kParts + split * kParts + part) * w.nr + row;
     sum = across_rows<SumOp>(sum);
-    if (row >= w.nr) return;
-    if (g == 0) part_l[out_row] = sum;
+    if (g == 0) sum_s[part][row_l] = sum;
+    __syncthreads();                                         // (also: the last tile has been read)
+    float4 *merge = (float4 *)values + (rb * (D / 16)) * 64 + lane;      // [part - 1][row block][element / 16][lane]
+    if (kNeedO && part > 0)
+#pragma unroll
+        for (int d = 0; d < D / 16; ++d)
+            merge[((part - 1) * kRb * (D / 16) + d) * 64] = make_float4(acc[d][0], acc[d][1], acc[d][2], acc[d][3]);
+    __syncthreads();
+    if (part > 0 || row >= w.nr) return;
+    const size_t out_row = ((size_t)hl * n_splits + split) * w.nr + row;
+    if (g == 0) {
+#pragma unroll
+        for (int c = 1; c < kParts; ++c) sum += sum_s[c][row_l];
+        part_l[out_row] = sum;
+    }
     if (!kNeedO) return;
 #pragma unroll
-    for (int d = 0; d < D / 16; ++d)
-        *(float4 *)(part_o + out_row * D + d * 16 + 4 * g) = make_float4(acc[d][0], acc[d][1], acc[d][2], acc[d][3]);
+    for (int d = 0; d < D / 16; ++d) {
+        float4 o = make_float4(acc[d][0], acc[d][1], acc[d][2], acc[d][3]);
+#pragma unroll
+        for (int c = 0; c < kParts - 1; ++c) {
+            const float4 x = merge[(c * kRb * (D / 16) + d) * 64];
+            o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
+        }
+        *(float4 *)(part_o + out_row * D + d * 16 + 4 * g) = o;
+    }
 }
 
 // ------------------------------------------------------------------------------------
-// Scores of Eq. 4, 5, 6.  Grid: x = `n_tiles` tiles of the piece, z = KV head.  Lane = token + 16 g, registers = rows
-// 4 g .. 4 g + 3 of the wave's 16.  A workgroup takes its tokens against one chunk of rows after the other.
+// Scores of every variant.  Grid: x = KV head, y = `n_tiles` tiles of the piece.  Lane = row + 16 g, registers =
+// tokens 4 g .. 4 g + 3 of the 16 at hand.  A workgroup takes its tokens against one chunk of rows after the other.
 // ------------------------------------------------------------------------------------
 constexpr int kScoreTokens = 512;              // most tokens of a workgroup
 template <typename T, int D, int kRb, int kVariant, typename Lens>
@@ -504,21 +562,22 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
                                                                 const RowRecord *__restrict__ records, const float *__restrict__ o,
                                                                 const int8_t *__restrict__ o_digits, float *__restrict__ scores,
                                                                 size_t variant_stride, int add) {
-    constexpr int K = kDigits<T>, kTok = kFixedTile<D, kRb>, kPart = kTok / (8 / kRb), kRows = 16 * kRb;
-    constexpr bool kDoV = kVariant == OBC_ALL || kVariant == OBC_VALUE, kDoK = kVariant == OBC_ALL || kVariant == OBC_KEY,
-                   kDoJ = kVariant == OBC_ALL || kVariant == OBC_JOINT, kNeedO = kDoK || kDoJ;
-    constexpr int kSums = kVariant == OBC_ALL ? 3 : 1, kBuf = buffers_of(K * kTok * D);
+    constexpr int K = kDigits<T>, kTok = kFixedTile<D>, kPart = kTok / (8 / kRb), kRows = 16 * kRb;
+    constexpr bool kAttnLike = kVariant == OBC_ATTN || kVariant == OBC_VATP;
+    constexpr bool kDoV = kVariant == OBC_ALL || kVariant == OBC_VALUE || kAttnLike, kDoK = kVariant == OBC_ALL || kVariant == OBC_KEY,
+                   kDoJ = kVariant == OBC_ALL || kVariant == OBC_JOINT, kNeedO = kDoK || kDoJ, kNeedV = kVariant != OBC_ATTN;
+    constexpr int kSums = kVariant == OBC_ALL ? 3 : 1, kBuf = buffers_of(K * kTok * D), kNorm = kVariant == OBC_VATP ? 1 : 2;
     __shared__ __attribute__((aligned(16))) char digits[kBuf][kNeedO ? K * kTok * D : 16];
     __shared__ __attribute__((aligned(16))) double units[2][kTok];
-    __shared__ double vv_s[2][kTok];
+    __shared__ __attribute__((aligned(16))) double norm_s[2][kTok];
     __shared__ __attribute__((aligned(16))) RowRecord rec_s[kRows];
-    __shared__ float sum_s[kSums][kRb][kTok];
+    __shared__ __attribute__((aligned(16))) float sum_s[kSums][kRb][kTok];
     __shared__ float run_s[kSums][kScoreTokens];             // sums over the chunks so far
     __shared__ uint32_t close_s[kScoreTokens / 32];          // tokens with a value next to an output, scored below
     __shared__ float close_sum_s[2][8];
-    const int hl = blockIdx.z, bg = w.bg0 + hl, b = bg / Hkv;
+    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int t_begin = w.s0 + blockIdx.x * n_tiles * kTok, t_stop = min(t_begin + n_tiles * kTok, w.s1), t_end = min(t_stop, len);
+    const int t_begin = w.s0 + blockIdx.y * n_tiles * kTok, t_stop = min(t_begin + n_tiles * kTok, w.s1), t_end = min(t_stop, len);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
     const int rb = wave % kRb, part = wave / kRb;
     float *out = scores + (size_t)bg * N;
@@ -528,80 +587,89 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
             for (int c = 0; c < kSums; ++c) out[c * variant_stride + t] = 0.f;
     if (t_begin >= t_end) return;                            // uniform
     const __amdgpu_buffer_rsrc_t vg = span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
-    const __amdgpu_buffer_rsrc_t zg = span_of(z + (size_t)hl * w.nr * w.z_stride, (size_t)w.nr * w.z_stride * sizeof(float));
     if ((int)threadIdx.x < kScoreTokens / 32) close_s[threadIdx.x] = 0u;         // (two barriers before the first use)
+    const int blocks = (w.nr + 15) / 16;
     for (int row0 = 0; row0 < w.nr; row0 += kRows) {
-        TokenTile<T, D, kTok> next;
-        next.load(vg, 0);
-        const int arow = row0 + rb * 16 + (lane & 15);
+        TokenTile<T, D, kTok, kFixedThreads> next;
+        if (kNeedV) next.load(vg, 0);
+        const int block = min(row0 / 16 + rb, blocks - 1);
         RowDigits<kRowDigits, D> rows;
-        if (kNeedO) rows.load(o_digits, (size_t)hl * w.nr + min(arow, w.nr - 1), arow < w.nr, g);
+        if (kNeedO) rows.load(o_digits, hl, block, blocks, lane);
+        const __amdgpu_buffer_rsrc_t zg = span_of(z + z_block(w, hl, 0, t_begin), z_block(w, 1, 0, w.s0) * 4);
+        const int z_at = (int)(z_block(w, 0, block, w.s0) * 4) + lane * 16;
         __syncthreads();                                     // (the chunk before this one is done with)
-        for (int i = threadIdx.x; i < kRows; i += kFixedThreads) {
-            RowRecord rec = records[(size_t)hl * w.nr + min(row0 + i, w.nr - 1)];
-            if (row0 + i >= w.nr) rec.last = -1;             // no such row: it sees nothing
-            rec_s[i] = rec;
+        int i = threadIdx.x;
+        asm volatile("" : "+v"(i));                          // (addresses anew for every chunk: registers)
+        if (i < kRows) {
+            rec_s[i] = records[(size_t)hl * w.nr + min(row0 + i, w.nr - 1)];
+            if (row0 + i >= w.nr) rec_s[i].last = -1;        // no such row: it sees nothing
         }
-        next.template store_digits<true, kNeedO>(digits[0], units[0], vv_s[0]);
-        if (t_begin + kTok < t_end) next.load(vg, kTok);
+        if (kNeedV) next.template store_digits<kNeedO, kNorm>(digits[0], units[0], norm_s[0]);
+        if (kNeedV && t_begin + kTok < t_end) next.load(vg, kTok);
         int slot = 0;
         for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
             __syncthreads();                                 // this tile is in LDS, the one before it has been read
             auto advance = [&]() {
-                if (t0 + kTok < t_end) next.template store_digits<true, kNeedO>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], vv_s[slot ^ 1]);
+                if (!kNeedV) return;
+                if (t0 + kTok < t_end)
+                    next.template store_digits<kNeedO, kNorm>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], norm_s[slot ^ 1]);
                 if (t0 + 2 * kTok < t_end) next.load(vg, t0 - t_begin + 2 * kTok);
             };
             if (kBuf == 2) advance();
 #pragma unroll 1
             for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
-                const int tok_l = p0 + (lane & 15), p = t0 + tok_l;
-                float x[4];                                  // (rows of z have room for whole tiles)
-                const int at = ((row0 + rb * 16 + 4 * g) * w.z_stride + (p - w.s0)) * 4;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) x[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(zg, at + r * w.z_stride * 4, 0, 0));
+                const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(zg, z_at, (t0 - t_begin + p0) * 64, 0);    // (room for whole tiles)
+                const float x[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
                 i32x4 acc[kLevels];
-                if (kNeedO) level_sums<kRowDigits, K, D, kTok, true>(rows, digits[slot % kBuf], tok_l, g, acc);
-                const double vv = vv_s[slot][tok_l];
-                const double vu = kNeedO ? -2.0 * units[slot][tok_l] : 0.0;
-                float acc_v = 0.f, acc_k = 0.f, acc_j = 0.f, nearest = INFINITY;
+                if (kNeedO) level_sums<kRowDigits, K, D, kTok>(rows, digits[slot % kBuf], p0 + (lane & 15), g, acc);
+                __builtin_amdgcn_sched_barrier(0);           // (the row's record only now: registers)
+                const RowRecord rec = rec_s[rb * 16 + (lane & 15)];
+                const float near_oo = (float)rec.oo * 0x1p-22f;
+                const double row_unit2 = -2.0 * rec.unit;
+                float acc_v[4], acc_k[4], acc_j[4];
+                uint32_t close = 0u;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     __builtin_amdgcn_sched_barrier(0);
-                    const RowRecord &rec = rec_s[rb * 16 + 4 * g + r];
+                    const int tok = p0 + 4 * g + r, p = t0 + tok;
                     const float a = p <= rec.last ? exp_nonpositive(x[r] - rec.m) * rec.inv_l : 0.f;
                     const float a2 = a * a;
-                    if (kDoV) acc_v = fmaf(a, a, acc_v);     // (the same rounding in every variant)
+                    acc_v[r] = kAttnLike ? a : a2;
                     if (!kNeedO) continue;
-                    const double vo = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
-                    const double d2 = fma(vo * rec.unit, vu, vv + rec.oo);               // ||v_p - o_i||^2
+                    const double vv = norm_s[slot][tok], vo2 = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
+                    const double d2 = fma(vo2 * row_unit2, units[slot][tok], vv + rec.oo);          // ||v_p - o_i||^2
                     const bool is_top = p == rec.top;
-                    nearest = fminf(nearest, is_top ? INFINITY : (float)d2);
-                    if (kDoK) acc_k = fmaf(a2 * x[r] * x[r], is_top ? rec.top_dk : fmaxf((float)d2, 0.f), acc_k);
+                    close |= (float)d2 < near_oo && !is_top ? 1u << r : 0u;
+                    if (kDoK) acc_k[r] = a2 * x[r] * x[r] * (is_top ? rec.top_dk : fmaxf((float)d2, 0.f));
                     if (kDoJ) {
                         const double zd = x[r];              // ||v_p + Z (v_p - o_i)||^2 with 2 (v_p - o_i).v_p = d2 + vv - oo
                         const double dj = fma(zd, fma(zd, d2, d2 + (vv - rec.oo)), vv);
-                        acc_j = fmaf(a2, is_top ? rec.top_dj : fmaxf((float)dj, 0.f), acc_j);
+                        acc_j[r] = a2 * (is_top ? rec.top_dj : fmaxf((float)dj, 0.f));
                     }
                 }
                 // v_p within 2^-11 of an o_i: the expanded square has lost too much
-                if (kNeedO && nearest < (float)vv * 0x1p-22f) atomicOr(close_s + ((p - t_begin) >> 5), 1u << ((p - t_begin) & 31));
-                // the other lanes of a token and the other row blocks held other rows
+                if (kNeedO && close != 0u) atomicOr(close_s + ((t0 + p0 - t_begin) >> 5), close << (((t0 + p0 - t_begin) & 31) + 4 * g));
+                // over the 16 rows; the other row blocks held others
                 int n = 0;
-                auto put = [&](float s) {
-                    s = across_rows<SumOp>(s);
-                    if (g == 0) sum_s[n][rb][tok_l] = s;
+                auto put = [&](float (&s)[4]) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) s[r] = row16_reduce<SumOp>(s[r]);
+                    if ((lane & 15) == 0) *(float4 *)(&sum_s[n][rb][p0 + 4 * g]) = make_float4(s[0], s[1], s[2], s[3]);
                     ++n;
                 };
-                if (kDoV) put(acc_v * (float)vv);
+                if (kDoV) put(acc_v);
                 if (kDoK) put(acc_k);
                 if (kDoJ) put(acc_j);
             }
             __syncthreads();
-            if ((int)threadIdx.x < kSums * kTok) {           // (the same thread for a token in every chunk)
-                const int c = threadIdx.x / kTok, tok_l = threadIdx.x % kTok, p = t0 + tok_l;
+            int thread = threadIdx.x;
+            asm volatile("" : "+v"(thread));                 // (addresses anew for every tile: registers)
+            if (thread < kSums * kTok) {                     // (the same thread for a token in every chunk)
+                const int c = thread / kTok, tok_l = thread % kTok, p = t0 + tok_l;
                 float s = 0.f;
 #pragma unroll
                 for (int i = 0; i < kRb; ++i) s += sum_s[c][i][tok_l];
+                if (kDoV && kNeedV && c == 0) s *= (float)norm_s[slot][tok_l];
                 if (row0 > 0) s += run_s[c][p - t_begin];
                 if (row0 + kRows < w.nr) run_s[c][p - t_begin] = s;
                 else if (p < t_end && !((kDoV && c == 0) ? 0u : close_s[(p - t_begin) >> 5] >> ((p - t_begin) & 31) & 1u)) {
@@ -629,7 +697,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
                     const int row = row0 + 8 * u;
                     const size_t at = (size_t)hl * w.nr + min(row, w.nr - 1);
                     const RowRecord rec = records[at];
-                    const float zr = z[at * w.z_stride + (p - w.s0)];
+                    const float zr = z[z_block(w, hl, min(row, w.nr - 1) / 16, p) + ((p - w.s0) % 16 / 4 * 16 + min(row, w.nr - 1) % 16) * 4 + p % 4];
                     const float a = row < w.nr && p <= rec.last ? exp_nonpositive(zr - rec.m) * rec.inv_l : 0.f, a2 = a * a;
                     float d2 = 0.f, dj = 0.f;
 #pragma unroll

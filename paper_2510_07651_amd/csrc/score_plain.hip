@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
 // ------------------------------------------------------------------------------------
 template <typename T, int D, bool kNeedO, bool kFixed, typename Lens>
 __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
-                                                        Piece w, int split_len, int n_parts, int parts_per_split,
+                                                        Piece w, int split_len, int n_splits,
                                                         const float *__restrict__ part_l, const float *__restrict__ part_o,
                                                         RowRecord *__restrict__ records, float *__restrict__ out,
                                                         int8_t *__restrict__ out_digits) {
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
     const int hl = blockIdx.z, bg = w.bg0 + hl, row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= w.nr) return;                                 // uniform over the wave
     const int len = seq_len_of(lens, ragged, bg / Hkv, N);
-    const int live = (len + split_len - 1) / split_len * parts_per_split;
+    const int live = (len + split_len - 1) / split_len;
     RowRecord *rec = records + (size_t)hl * w.nr + row;
     const int top = min(rec->top, len - 1);                  // (logits that are not numbers have no largest one)
     const float m = rec->m;
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
     float l = 0.f;
 #pragma unroll 8
     for (int s = 0; s < live; ++s) {
-        const size_t at = ((size_t)hl * n_parts + s) * w.nr + row;
+        const size_t at = ((size_t)hl * n_splits + s) * w.nr + row;
         l += part_l[at];
 #pragma unroll
         for (int e = 0; e < kE; ++e)
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
     double oo = 0.0, dk = 0.0, dj = 0.0;
     double unit = 0.0;
     if (kNeedO) {
-        float oi[kE], amax = 0.f;
+        float oi[kE];
 #pragma unroll
         for (int e = 0; e < kE; ++e) {
             const float diff = frac * (vt[e] - o[e] * inv);  // v_top - o_i
@@ -449,18 +449,18 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
             oo += (double)oi[e] * oi[e];
             dk += (double)diff * diff;
             dj += (double)comb * comb;
-            amax = MaximumOp()(amax, fabsf(oi[e]));
         }
         const size_t at = (size_t)hl * w.nr + row;
         if constexpr (kFixed) {
-            const int oe = max_exponent(wave_reduce<MaximumOp>(amax));
+            const float f[4] = {oi[0], kE > 1 ? oi[kE - 1] : 0.f, 0.f, 0.f};
+            const double x[4] = {f[0], f[1], 0.0, 0.0};
+            const int oe = max_exponent(wave_reduce<MaxBitsOp>(max_abs(f)));
             unit = row_unit(oe);
-            const float x[4] = {oi[0], kE > 1 ? oi[kE - 1] : 0.f, 0.f, 0.f};
             uint32_t p[kRowDigits];
-            digits_of<kRowDigits>(x, digit_scale(oe), p);
+            digits_of<kRowDigits>(x, oe, p);
 #pragma unroll
             for (int k = 0; k < kRowDigits; ++k) {
-                int8_t *dst = out_digits + (at * kRowDigits + k) * D + lane * kE;
+                int8_t *dst = out_digits + digit_address<kRowDigits, D>((size_t)hl * ((w.nr + 15) / 16) + row / 16, k, row, lane * kE);
                 if constexpr (kE == 2) *(uint16_t *)dst = (uint16_t)p[k];
                 else *dst = (int8_t)p[k];
             }
@@ -616,21 +616,18 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     const int mask = one_piece ? a.stage_mask : a.stage_mask & OBC_STAGE_SWEEP2 ? (int)OBC_STAGE_ALL
                      : a.stage_mask & OBC_STAGE_COMBINE ? OBC_STAGE_SWEEP1 | OBC_STAGE_COMBINE : a.stage_mask;
     const int segs = (a.N + ws.pl_seg - 1) / ws.pl_seg;
-    // Row tiles of the fp64 kernels: not more than two, which leaves registers for four waves per SIMD.  (With four and
-    // two the kernels keep more of each tile in flight and come out 0-10 % behind.)
-    constexpr int kFewRt = kRt < 2 ? kRt : 2;
     hipError_t e = hipSuccess;
     for (int bg0 = 0; bg0 < BH; bg0 += ws.pl_heads)
         for (int r0 = 0; r0 < M; r0 += ws.pl_rows) {
             Piece w;
             w.bg0 = bg0; w.r0 = r0; w.nr = std::min(ws.pl_rows, M - r0); w.z_stride = ws.pl_z_stride;
-            const unsigned heads = std::min(ws.pl_heads, BH - bg0), chunks = (w.nr + 16 * kFewRt - 1) / (16 * kFewRt);
+            const unsigned heads = std::min(ws.pl_heads, BH - bg0), chunks = (w.nr + 16 * kRt - 1) / (16 * kRt);
             auto segment = [&](int i) { w.s0 = i * ws.pl_seg; w.s1 = std::min(w.s0 + ws.pl_seg, a.N); };
             const unsigned row_chunks = (w.nr + 16 * kRb - 1) / (16 * kRb);         // (score_fixed.h)
             auto logits = [&]() {
                 const unsigned ranges = (w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range;
                 if constexpr (fixed)
-                    fixed_logits<T, D, kRb><<<dim3(ranges, row_chunks, heads), dim3(kFixedThreads), 0, stream>>>(
+                    fixed_logits<T, D, kRb><<<dim3(heads, ranges, row_chunks), dim3(kFixedThreads), 0, stream>>>(
                         q_digits, q_units, k, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 else
                     plain_logits<T, D, kRt><<<dim3(ranges, chunks, heads), dim3(kThreads), 0, stream>>>(
@@ -640,7 +637,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             };
             const bool again = mask & OBC_STAGE_SWEEP1 || segs > 1;
             if (fixed && again) {
-                fixed_rows<T, D><<<dim3((w.nr * (D / 4) + kThreads - 1) / kThreads, 1, heads), dim3(kThreads), 0, stream>>>(
+                fixed_rows<T, D><<<dim3(((w.nr + 15) / 16 * 16 * (D / 4) + kThreads - 1) / kThreads, 1, heads), dim3(kThreads), 0, stream>>>(
                     q, a.W, a.Hq, a.Hkv, w, q_digits, q_units);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
@@ -656,7 +653,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                     auto weights = [&](auto with_output) {
                         constexpr bool kNeedO = decltype(with_output)::value;
                         if constexpr (fixed)
-                            fixed_weights<T, D, kRb, kNeedO><<<dim3(grid.x, row_chunks, heads), dim3(kFixedThreads), 0, stream>>>(
+                            fixed_weights<T, D, kRb, kNeedO><<<dim3(heads, grid.x, row_chunks), dim3(kWeightThreads), 0, stream>>>(
                                 v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
                                 best, rec, part_l, part_o);
                         else
@@ -671,13 +668,10 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             }
             if (mask & OBC_STAGE_COMBINE) {
                 const dim3 grid((w.nr + 3) / 4, 1, heads);
-                const int per_split = fixed ? 8 / kRb : 1;
 #define OBC_PLAIN_MERGE(need_o, fixed)                                                                                 \
     plain_merge<T, D, need_o, fixed><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split,  \
-                                                                          ws.pl_splits * per_split, per_split, part_l, part_o, \
-                                                                          rec, out, o_digits)
-                if (need_o && fixed) OBC_PLAIN_MERGE(true, true);
-                else if (need_o) OBC_PLAIN_MERGE(true, false);
+                                                                          ws.pl_splits, part_l, part_o, rec, out, o_digits)
+                if (need_o) OBC_PLAIN_MERGE(true, fixed);
                 else OBC_PLAIN_MERGE(false, false);
 #undef OBC_PLAIN_MERGE
                 if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -686,37 +680,30 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             for (int i = 0; i < segs; ++i) {
                 segment(i);
                 if (segs > 1 && !logits()) return e;
-                if (fixed && a.variant != OBC_ATTN && a.variant != OBC_VATP) {
-                    constexpr int kTok = kFixedTile<D, kRb>;
-                    const int tiles = (w.s1 - w.s0 + kTok - 1) / kTok;
-                    const int n_tiles = (int)std::min((tiles * (long long)heads + kResident / 2 - 1) / (kResident / 2), kScoreTokens / kTok + 0ll);
-                    const dim3 grid((tiles + n_tiles - 1) / n_tiles, 1, heads);
-#define OBC_FIXED_SCORE(variant)                                                                                       \
-    fixed_score<T, D, kRb, variant><<<grid, dim3(kFixedThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_digits, \
-                                                                         a.scores, variant_stride, a.accumulate || r0 > 0)
-                    if (a.variant == OBC_VALUE) OBC_FIXED_SCORE(OBC_VALUE);
-                    else if (a.variant == OBC_KEY) OBC_FIXED_SCORE(OBC_KEY);
-                    else if (a.variant == OBC_JOINT) OBC_FIXED_SCORE(OBC_JOINT);
-                    else OBC_FIXED_SCORE(OBC_ALL);
-#undef OBC_FIXED_SCORE
-                    if ((e = hipGetLastError()) != hipSuccess) return e;
-                    continue;
-                }
-                const int tiles = (w.s1 - w.s0 + kTile - 1) / kTile, n_tiles = (int)((tiles * (long long)heads + kResident - 1) / kResident);
-                const dim3 grid((tiles + n_tiles - 1) / n_tiles, 1, heads);
                 const int add = a.accumulate || r0 > 0;
-#define OBC_PLAIN_SCORE(variant)                                                                                       \
-    plain_score<T, D, kFewRt, variant><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, \
-                                                                         out, a.scores, variant_stride, add)
+                auto score = [&](auto which) {
+                    constexpr int kVariant = decltype(which)::value;
+                    if constexpr (fixed) {
+                        constexpr int kTok = kFixedTile<D>;
+                        const int tiles = (w.s1 - w.s0 + kTok - 1) / kTok;
+                        const int n_tiles = (int)std::min((tiles * (long long)heads + kResident / 2 - 1) / (kResident / 2), kScoreTokens / kTok + 0ll);
+                        fixed_score<T, D, kRb, kVariant><<<dim3(heads, (tiles + n_tiles - 1) / n_tiles), dim3(kFixedThreads), 0, stream>>>(
+                            v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_digits, a.scores, variant_stride, add);
+                    } else {
+                        const int tiles = (w.s1 - w.s0 + kTile - 1) / kTile;
+                        const int n_tiles = (int)((tiles * (long long)heads + kResident - 1) / kResident);
+                        plain_score<T, D, kRt, kVariant><<<dim3((tiles + n_tiles - 1) / n_tiles, 1, heads), dim3(kThreads), 0, stream>>>(
+                            v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, a.scores, variant_stride, add);
+                    }
+                };
                 switch (a.variant) {
-                    case OBC_VALUE: OBC_PLAIN_SCORE(OBC_VALUE); break;
-                    case OBC_KEY: OBC_PLAIN_SCORE(OBC_KEY); break;
-                    case OBC_JOINT: OBC_PLAIN_SCORE(OBC_JOINT); break;
-                    case OBC_ATTN: OBC_PLAIN_SCORE(OBC_ATTN); break;
-                    case OBC_VATP: OBC_PLAIN_SCORE(OBC_VATP); break;
-                    default: OBC_PLAIN_SCORE(OBC_ALL); break;
+                    case OBC_VALUE: score(std::integral_constant<int, OBC_VALUE>()); break;
+                    case OBC_KEY: score(std::integral_constant<int, OBC_KEY>()); break;
+                    case OBC_JOINT: score(std::integral_constant<int, OBC_JOINT>()); break;
+                    case OBC_ATTN: score(std::integral_constant<int, OBC_ATTN>()); break;
+                    case OBC_VATP: score(std::integral_constant<int, OBC_VATP>()); break;
+                    default: score(std::integral_constant<int, OBC_ALL>()); break;
                 }
-#undef OBC_PLAIN_SCORE
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
         }
@@ -753,18 +740,17 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
     const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, (tiles * chunks + resident - 1) / resident);
     ws->pl_range = (int)(std::min(range_tiles, tiles) * kTile);
     ws->pl_ranges = (N + ws->pl_range - 1) / ws->pl_range;
-    const long long splits = std::max<long long>(1, std::min<long long>(std::min<long long>(kMaxSplits, tiles), (kResident / 2 + chunks - 1) / chunks));
+    const long long splits = std::max<long long>(1, std::min<long long>(std::min<long long>(kMaxSplits, tiles), (resident / 2 + chunks - 1) / chunks));
     ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
     ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
-    const int parts = fixed ? 2 : 1;                         // (partial records per split, at most)
     auto row_bytes = [&]() {                                 // of one row, beside its logits
-        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 14 : 4) + 8 + (size_t)ws->pl_splits * parts * (d + 1) * 4;
+        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 14 : 4) + 8 + (size_t)ws->pl_splits * (d + 1) * 4;
     };
     const size_t per_row = row_bytes() + (size_t)align_up(N, kTile) * 4;
     cap -= 9 * 256;                                          // alignment of the buffers
     ws->pl_seg = N;
     ws->pl_rows = M;
-    ws->pl_heads = (int)std::min<size_t>(BH, cap / (per_row * M));
+    ws->pl_heads = (int)std::min<size_t>(BH, cap / (per_row * align_up(M, 16)));
     if (ws->pl_heads < 1) {
         ws->pl_heads = 1;
         ws->pl_rows = (int)std::min<size_t>(M, cap / per_row / 16 * 16);
@@ -778,7 +764,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
             ws->pl_seg = (int)std::min<size_t>(align_up(N, ws->pl_split), std::max<size_t>(seg, ws->pl_split));
         }
     }
-    const size_t rows = (size_t)ws->pl_heads * ws->pl_rows;
+    const size_t rows = ws->pl_heads * align_up(ws->pl_rows, 16);        // (whole blocks are written)
     auto take = [&](size_t *at, size_t bytes) { *at = *off; *off = align_up(*off + bytes, 256); };
     ws->pl_z_stride = (int)align_up(ws->pl_seg, kTile);       // (whole tiles are written)
     take(&ws->pl_z, rows * ws->pl_z_stride * 4);
@@ -790,8 +776,8 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
         take(&ws->pl_q_digits, rows * d * 5);
         take(&ws->pl_q_units, rows * 8);
     }
-    take(&ws->pl_part_l, rows * ws->pl_splits * parts * 4);
-    take(&ws->pl_part_o, rows * ws->pl_splits * parts * d * 4);
+    take(&ws->pl_part_l, rows * ws->pl_splits * 4);
+    take(&ws->pl_part_o, rows * ws->pl_splits * d * 4);
 }
 
 hipError_t launch_score_plain(const ScoreArgs &a, const ScoreWorkspace &ws, char *ws_base, hipStream_t stream) {
