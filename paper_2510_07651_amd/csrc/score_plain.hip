@@ -87,14 +87,16 @@ __device__ __forceinline__ F wave_sum(F x) {
 // (max, lowest token attaining it) merged across the lanes whose index differs in the bits of `below`.
 template <int kLanes>
 __device__ __forceinline__ void lanes_best(float &m, int &at) {
-#pragma unroll
-    for (int off = kLanes / 2; off > 0; off >>= 1) {
-        const float om = __shfl_xor(m, off);
-        const int oat = __shfl_xor(at, off);
-        const bool take = om > m || (om == m && oat < at);
+    static_assert(kLanes == 4 || kLanes == 8 || kLanes == 16, "inside a row of 16 lanes");
+    auto step = [&](float om, uint32_t oat) {
+        const bool take = om > m || (om == m && (int)oat < at);
         m = take ? om : m;
-        at = take ? oat : at;
-    }
+        at = take ? (int)oat : at;
+    };
+    step(dpp_pair<0xB1>(m), dpp_pair<0xB1>((uint32_t)at));
+    step(dpp_pair<0x4E>(m), dpp_pair<0x4E>((uint32_t)at));
+    if (kLanes >= 8) step(dpp_pair<0x141>(m), dpp_pair<0x141>((uint32_t)at));
+    if (kLanes == 16) step(dpp_pair<0x140>(m), dpp_pair<0x140>((uint32_t)at));
 }
 
 // ------------------------------------------------------------------------------------
@@ -482,15 +484,217 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
 }
 
 // ------------------------------------------------------------------------------------
+// Short sequences in two launches.  short_partial: logits, weights and P V of one tile of 64 tokens, relative to the tile's
+// own maximum and without its top token (and once more with it: the merge wants only the row's top token left out).
+// plain_score<.., kShort> merges the tiles' records itself before it scores.  Grid: x = tile, z = KV head.
+// What bounds a call this small is launches and the latency of dependent loads: fp32, one head, d = 64, 512 tokens, all
+// three scores took 17 us in four launches (logits 5.6, weights 4.8, merge 2.8, scores 5.0).
+// ------------------------------------------------------------------------------------
+constexpr int kShortTiles = 16;      // most tiles of a short sequence
+
+template <typename T, int D, int kRt, bool kNeedO, typename Lens>
+__global__ __launch_bounds__(kThreads) void short_partial(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
+                                                          int N, int W, int Hq, int Hkv, int ragged, Lens lens, Piece w,
+                                                          float *__restrict__ z, float4 *__restrict__ heads, float *__restrict__ part_o) {
+    constexpr int kRows = 16 * kRt, kPs = kTile + 4, kCt = D / 64;
+    __shared__ __attribute__((aligned(16))) float rows_s[kRows * kStride<D>], v_s[kNeedO ? kTile * kStride<D> : 4], p_s[kRows * kPs];
+    __shared__ float2 best_s[4][kRows];
+    __shared__ float l_s[4][kRows];
+    const int hl = blockIdx.z, b = hl / Hkv, M = w.nr, n_tiles = gridDim.x;
+    const int len = seq_len_of(lens, ragged, b, N), t0 = blockIdx.x * kTile;
+    if (t0 >= len) return;                                   // uniform
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, p = t0 + wave * 16 + (lane & 15);
+    RowRegs<T, D> tok;
+    tok.load(k + (size_t)hl * N * D, p, len, lane >> 4);
+    {
+        TileRegs<T, D, kRows> qr;
+        qr.load(q + (size_t)hl * M * D, 0, M);
+        TileRegs<T, D, kTile> vr;
+        if (kNeedO) vr.load(v + (size_t)hl * N * D, t0, len);
+        qr.store(rows_s);
+        if (kNeedO) vr.store(v_s);
+    }
+    __syncthreads();
+    f64x4 acc[kRt];
+#pragma unroll
+    for (int rt = 0; rt < kRt; ++rt) acc[rt] = f64x4{0.0, 0.0, 0.0, 0.0};
+    tile_dots<T, D, kRt>(rows_s, tok, lane, acc);
+    float x[kRt * 4];
+#pragma unroll
+    for (int i = 0; i < kRt * 4; ++i) {
+        const int row = 4 * i + (lane >> 4);
+        x[i] = (float)(acc[i >> 2][i & 3] * (1.0 / sqrt((double)D)));            // scaled logit: the only rounding
+        const bool seen = row < M && p < len && p <= len - W + row % W;
+        if (seen) z[((size_t)hl * M + row) * w.z_stride + p] = x[i];
+        float m = seen && x[i] > -INFINITY ? x[i] : -INFINITY;
+        int at = seen && x[i] > -INFINITY ? p : kNoToken;
+        lanes_best<16>(m, at);
+        if ((lane & 15) == 0) best_s[wave][row] = make_float2(m, __int_as_float(at));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kRt * 4; ++i) {
+        const int row = 4 * i + (lane >> 4);
+        float m = best_s[0][row].x;
+        int top = __float_as_int(best_s[0][row].y);
+#pragma unroll
+        for (int c = 1; c < 4; ++c)                          // (tokens ascend with the wave: strict keeps the lowest)
+            if (best_s[c][row].x > m) { m = best_s[c][row].x; top = __float_as_int(best_s[c][row].y); }
+        const bool seen = row < M && p < len && p <= len - W + row % W;
+        const float e = seen && p != top ? exp_nonpositive(x[i] - m) : 0.f;
+        p_s[row * kPs + wave * 16 + (lane & 15)] = e;
+        const float l = row16_reduce<SumOp>(e);
+        if ((lane & 15) == 0) l_s[wave][row] = l;
+        if (wave == 0 && (lane & 15) == 0) best_s[0][row] = make_float2(m, __int_as_float(top));     // (read by this wave alone so far)
+    }
+    __syncthreads();
+    const size_t record = ((size_t)hl * n_tiles + blockIdx.x) * M;
+    if ((int)threadIdx.x < M) {
+        const int row = threadIdx.x;
+        heads[record + row] = make_float4(best_s[0][row].x, (l_s[0][row] + l_s[1][row]) + (l_s[2][row] + l_s[3][row]), best_s[0][row].y, 0.f);
+    }
+    if (!kNeedO) return;
+    f32x4 o[kRt][kCt];
+#pragma unroll
+    for (int rt = 0; rt < kRt; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < kCt; ++ct) o[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < kTile / 16; ++s) {
+        f32x4 a[kRt];
+#pragma unroll
+        for (int rt = 0; rt < kRt; ++rt) a[rt] = *(const f32x4 *)(p_s + (16 * rt + (lane & 15)) * kPs + 16 * s + 4 * (lane >> 4));
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int ct = 0; ct < kCt; ++ct) {
+                const float vv = v_s[(16 * s + 4 * (lane >> 4) + c) * kStride<D> + (wave * kCt + ct) * 16 + (lane & 15)];
+#pragma unroll
+                for (int rt = 0; rt < kRt; ++rt) o[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rt][c], vv, o[rt][ct], 0, 0, 0);
+            }
+    }
+#pragma unroll
+    for (int rt = 0; rt < kRt; ++rt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * rt + 4 * (lane >> 4) + r;
+            if (row >= M) continue;
+            const int top = __float_as_int(best_s[0][row].y);
+#pragma unroll
+            for (int ct = 0; ct < kCt; ++ct) {
+                const int col = (wave * kCt + ct) * 16 + (lane & 15);
+                float *dst = part_o + (record + row) * 2 * D + col;
+                dst[0] = o[rt][ct][r];
+                dst[D] = o[rt][ct][r] + (top != kNoToken ? v_s[(top - t0) * kStride<D> + col] : 0.f);
+            }
+        }
+}
+
+// The rows' outputs (into LDS as fp32) and records from the tiles' partial ones; the barrier after it is the caller's.
+template <typename T, int D, int kRt, bool kNeedO>
+__device__ __forceinline__ void merge_short(const T *__restrict__ vg, int len, int W, int M, int hl, int n_tiles,
+                                            const float4 *__restrict__ heads, const float *__restrict__ part_o, float *rows_s,
+                                            RowRecord *rec_s) {
+    constexpr int kRows = 16 * kRt, kSub = kThreads / kRows, kOwn = kShortTiles / kSub, kE = D / 64;
+    __shared__ float w_s[kRows][kShortTiles];
+    const int live = (len + kTile - 1) / kTile;
+    {
+        const int row = threadIdx.x / kSub, sub = threadIdx.x % kSub;
+        float hm[kOwn], hl_[kOwn];
+        float m = -INFINITY;
+        int top = kNoToken;
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) {
+            const int s = sub + i * kSub;
+            const float4 h = row < M && s < live ? heads[((size_t)hl * n_tiles + s) * M + row] : make_float4(-INFINITY, 0.f, __int_as_float(kNoToken), 0.f);
+            hm[i] = h.x;
+            hl_[i] = h.y;
+            if (h.x > m || (h.x == m && __float_as_int(h.z) < top)) { m = h.x; top = __float_as_int(h.z); }
+        }
+        lanes_best<kSub>(m, top);
+        top = min(top, len - 1);                             // (logits that are not numbers have no largest one)
+        float l = 0.f;
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) {
+            const int s = sub + i * kSub;
+            const float wt = hm[i] > -INFINITY ? exp_nonpositive(hm[i] - m) : 0.f;
+            w_s[row][s] = wt;
+            l += fmaf(wt, hl_[i], s != top / kTile ? wt : 0.f);          // (other tiles count their top token)
+        }
+#pragma unroll
+        for (int off = kSub / 2; off > 0; off >>= 1) l += __shfl_xor(l, off);
+        if (sub == 0) {
+            RowRecord &rec = rec_s[row];
+            rec.m = m;
+            rec.top = top;
+            rec.inv_l = 1.0f / (1.0f + l);
+            rec.last = len - W + row % W;
+            rec.unit = l;                                    // (for the vectors below)
+        }
+    }
+    __syncthreads();
+    if (!kNeedO) return;
+    // Sixteen lanes per row, 16-byte pieces: short code matters where every instruction is fetched for the first time.
+    const int sub = threadIdx.x & 15;
+#pragma unroll 1
+    for (int row = threadIdx.x >> 4; row < kRows; row += 16) {
+        const int rc = min(row, M - 1), top = rec_s[rc].top;
+        f32x4 vt[kE], o[kE];
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+            const T *src = vg + (size_t)top * D + (sub + 16 * e) * 4;
+            vt[e] = f32x4{load_as_float(src), load_as_float(src + 1), load_as_float(src + 2), load_as_float(src + 3)};
+            o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int s0 = 0; s0 < live; s0 += 8)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int s = min(s0 + u, live - 1);
+                const float wt = s0 + u < live ? w_s[rc][s] : 0.f;
+                const float *src = part_o + ((((size_t)hl * n_tiles + s) * M + rc) * 2 + (s != top / kTile ? 1 : 0)) * D + sub * 4;
+#pragma unroll
+                for (int e = 0; e < kE; ++e) o[e] += wt * *(const f32x4 *)(src + 64 * e);
+            }
+        const float l = (float)rec_s[rc].unit, m = rec_s[rc].m;
+        const float frac = l / (1.0f + l);                   // 1 - A_{i,top}; the top token's own weight is exp(0) = 1
+        const float inv = l > 0.f ? 1.0f / l : 0.f;
+        double oo = 0.0, dk = 0.0, dj = 0.0;
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+            f32x4 oi;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float diff = frac * (vt[e][c] - o[e][c] * inv);    // v_top - o_i
+                oi[c] = vt[e][c] - diff;
+                const float comb = fmaf(m, diff, vt[e][c]);  // (1+Z) v_top - Z o_i
+                oo += (double)oi[c] * oi[c];
+                dk += (double)diff * diff;
+                dj += (double)comb * comb;
+            }
+            *(f32x4 *)(rows_s + row * kStride<D> + (sub + 16 * e) * 4) = oi;
+        }
+        oo = row16_reduce<SumOp>(oo);
+        dk = row16_reduce<SumOp>(dk);
+        dj = row16_reduce<SumOp>(dj);
+        if (sub == 0) {
+            rec_s[row].oo = oo;
+            rec_s[row].top_dk = (float)dk;
+            rec_s[row].top_dj = (float)dj;
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------
 // Scores.  Grid: x = `n_tiles` tiles of 64 tokens of the piece, z = KV head.  `add`: on top of what `scores` holds (the
 // caller's running scores, or the rows of an earlier piece).
 // ------------------------------------------------------------------------------------
-template <typename T, int D, int kRt, int kVariant, typename Lens>
-__global__ __launch_bounds__(kThreads, 4) void plain_score(const T *__restrict__ v, int N, int Hkv,
+template <typename T, int D, int kRt, int kVariant, bool kShort, typename Lens>
+__global__ __launch_bounds__(kThreads, kShort ? 2 : 4) void plain_score(const T *__restrict__ v, int N, int W, int Hkv,
                                                            int ragged, Lens lens, Piece w, int n_tiles,
                                                            const float *__restrict__ z,
                                                            const RowRecord *__restrict__ records,
-                                                           const float *__restrict__ out, float *__restrict__ scores,
+                                                           const float *__restrict__ out, const float4 *__restrict__ heads,
+                                                           const float *__restrict__ part_o, float *__restrict__ scores,
                                                            size_t variant_stride, int add) {
     constexpr int kRows = 16 * kRt;
     constexpr bool kAttnLike = kVariant == OBC_ATTN || kVariant == OBC_VATP;
@@ -529,7 +733,7 @@ __global__ __launch_bounds__(kThreads, 4) void plain_score(const T *__restrict__
             }
             for (int row0 = 0; row0 < w.nr; row0 += kRows) {
                 TileRegs<float, D, kRows> orow;
-                if (kNeedO) orow.load(out + (size_t)hl * w.nr * D, row0, w.nr);
+                if (kNeedO && !kShort) orow.load(out + (size_t)hl * w.nr * D, row0, w.nr);
                 float x[kRt * 4];
 #pragma unroll
                 for (int i = 0; i < kRt * 4; ++i) {
@@ -537,8 +741,9 @@ __global__ __launch_bounds__(kThreads, 4) void plain_score(const T *__restrict__
                     x[i] = p < t_live && row < w.nr ? z[((size_t)hl * w.nr + row) * w.z_stride + (p - w.s0)] : 0.f;
                 }
                 __syncthreads();                             // the rows before these have been read
-                if (kNeedO) orow.store(rows_s);
-                if ((int)threadIdx.x < kRows && row0 + (int)threadIdx.x < w.nr)
+                if (kShort) merge_short<T, D, kRt, kNeedO>(vg, len, W, w.nr, hl, gridDim.x, heads, part_o, rows_s, rec_s);
+                if (kNeedO && !kShort) orow.store(rows_s);
+                if (!kShort && (int)threadIdx.x < kRows && row0 + (int)threadIdx.x < w.nr)
                     rec_s[threadIdx.x] = records[(size_t)hl * w.nr + row0 + threadIdx.x];
                 __syncthreads();
                 f64x4 acc[kRt];
@@ -596,6 +801,44 @@ __global__ __launch_bounds__(kThreads, 4) void plain_score(const T *__restrict__
 // ------------------------------------------------------------------------------------
 // Host
 // ------------------------------------------------------------------------------------
+// f with the variant as a constant.
+template <typename F>
+void with_variant(int variant, F &&f) {
+    switch (variant) {
+        case OBC_VALUE: return f(std::integral_constant<int, OBC_VALUE>());
+        case OBC_KEY: return f(std::integral_constant<int, OBC_KEY>());
+        case OBC_JOINT: return f(std::integral_constant<int, OBC_JOINT>());
+        case OBC_ATTN: return f(std::integral_constant<int, OBC_ATTN>());
+        case OBC_VATP: return f(std::integral_constant<int, OBC_VATP>());
+        default: return f(std::integral_constant<int, OBC_ALL>());
+    }
+}
+
+// Short sequences: see short_partial.
+template <typename T, int D, int kRt, typename Lens>
+hipError_t run_short(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+    const T *q = (const T *)a.q, *k = (const T *)a.k, *v = (const T *)a.v;
+    float *z = (float *)(base + ws.pl_z), *part_o = (float *)(base + ws.pl_part_o);
+    float4 *heads = (float4 *)(base + ws.pl_part_l);
+    const bool need_o = a.variant == OBC_KEY || a.variant == OBC_JOINT || a.variant == OBC_ALL;
+    Piece w;
+    w.bg0 = w.r0 = w.s0 = 0; w.nr = a.G * a.W; w.s1 = a.N; w.z_stride = ws.pl_z_stride;
+    const dim3 grid(ws.pl_splits, 1, a.B * a.Hkv);
+    if (a.stage_mask & OBC_STAGE_SWEEP1) {
+        if (need_o)
+            short_partial<T, D, kRt, true><<<grid, dim3(kThreads), 0, stream>>>(q, k, v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, z, heads, part_o);
+        else
+            short_partial<T, D, kRt, false><<<grid, dim3(kThreads), 0, stream>>>(q, k, v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, z, heads, part_o);
+        if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    if (!(a.stage_mask & OBC_STAGE_SWEEP2)) return hipSuccess;
+    with_variant(a.variant, [&](auto which) {
+        plain_score<T, D, kRt, decltype(which)::value, true><<<grid, dim3(kThreads), 0, stream>>>(
+            v, a.N, a.W, a.Hkv, a.ragged, lens, w, 1, z, nullptr, nullptr, heads, part_o, a.scores, (size_t)a.B * a.Hkv * a.N, a.accumulate);
+    });
+    return hipGetLastError();
+}
+
 template <typename T, int D, int kRt, typename Lens>
 hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
     const T *q = (const T *)a.q, *k = (const T *)a.k, *v = (const T *)a.v;
@@ -692,18 +935,11 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                     } else {
                         const int tiles = (w.s1 - w.s0 + kTile - 1) / kTile;
                         const int n_tiles = (int)((tiles * (long long)heads + kResident - 1) / kResident);
-                        plain_score<T, D, kRt, kVariant><<<dim3((tiles + n_tiles - 1) / n_tiles, 1, heads), dim3(kThreads), 0, stream>>>(
-                            v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, a.scores, variant_stride, add);
+                        plain_score<T, D, kRt, kVariant, false><<<dim3((tiles + n_tiles - 1) / n_tiles, 1, heads), dim3(kThreads), 0, stream>>>(
+                            v, a.N, a.W, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, nullptr, nullptr, a.scores, variant_stride, add);
                     }
                 };
-                switch (a.variant) {
-                    case OBC_VALUE: score(std::integral_constant<int, OBC_VALUE>()); break;
-                    case OBC_KEY: score(std::integral_constant<int, OBC_KEY>()); break;
-                    case OBC_JOINT: score(std::integral_constant<int, OBC_JOINT>()); break;
-                    case OBC_ATTN: score(std::integral_constant<int, OBC_ATTN>()); break;
-                    case OBC_VATP: score(std::integral_constant<int, OBC_VATP>()); break;
-                    default: score(std::integral_constant<int, OBC_ALL>()); break;
-                }
+                with_variant(a.variant, score);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
         }
@@ -712,7 +948,11 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
 
 template <typename T, int D, int kRt>
 hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
-    return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) { return run_with<T, D, kRt>(a, lens, ws, base, stream); });
+    return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) {
+        if constexpr (kRt <= 2)
+            if (ws.pl_short) return run_short<T, D, kRt>(a, lens, ws, base, stream);
+        return run_with<T, D, kRt>(a, lens, ws, base, stream);
+    });
 }
 
 template <typename T, int D>
@@ -764,8 +1004,21 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
             ws->pl_seg = (int)std::min<size_t>(align_up(N, ws->pl_split), std::max<size_t>(seg, ws->pl_split));
         }
     }
-    const size_t rows = ws->pl_heads * align_up(ws->pl_rows, 16);        // (whole blocks are written)
     auto take = [&](size_t *at, size_t bytes) { *at = *off; *off = align_up(*off + bytes, 256); };
+    const size_t rows = ws->pl_heads * align_up(ws->pl_rows, 16);        // (whole blocks are written)
+    // Two launches instead of four where every tile of a head may merge all of the head's records (short_partial): as long
+    // as that reads less than 32 MB, some 5 us.
+    ws->pl_short = !fixed && tiles <= kShortTiles && ws->pl_heads == BH && ws->pl_rows == M &&
+                   (size_t)BH * tiles * tiles * M * d * 4 <= (size_t)32 << 20 && rows * (tiles * (kTile * 4 + 8 * d + 16)) <= cap;
+    if (ws->pl_short) {
+        ws->pl_split = ws->pl_range = kTile;
+        ws->pl_splits = (int)tiles;
+        ws->pl_z_stride = (int)tiles * kTile;
+        take(&ws->pl_z, rows * ws->pl_z_stride * 4);
+        take(&ws->pl_part_l, rows * tiles * sizeof(float4));
+        take(&ws->pl_part_o, rows * tiles * 2 * d * 4);
+        return;
+    }
     ws->pl_z_stride = (int)align_up(ws->pl_seg, kTile);       // (whole tiles are written)
     take(&ws->pl_z, rows * ws->pl_z_stride * 4);
     take(&ws->pl_best, rows * ws->pl_ranges * sizeof(float2));
