@@ -59,6 +59,8 @@ struct ScoreWorkspace {
     size_t z;          // float [B*Hkv*rows*z_stride]  raw q.k, kept by the first sweep when keep_z
     int keep_z, z_stride;
     int use_wide;      // 1: the second sweep runs in its register-blocked form (score_mfma_wide.hip)
+    int solo;          // 1: there the last chunk has at most 64 rows and goes to mfma_sweep2_solo, in ranges of range_solo
+    int range_solo;
     // General path: see score_plain.hip.  One piece of the work is `pl_heads` KV heads x `pl_rows` window rows x
     // `pl_seg` tokens; its buffers are reused by the next one.
     size_t pl_z;       // float [heads*rows*seg]     scaled logits
@@ -111,7 +113,7 @@ hipError_t launch_score_plain(const ScoreArgs &a, const ScoreWorkspace &ws, char
 hipError_t launch_score_mfma(const ScoreArgs &a, const ScoreWorkspace &ws, char *ws_base, hipStream_t stream);
 // Register-blocked second sweep: whether it serves the variant and row count, and its launcher (same arguments
 // and outputs as the 32-rows-per-wave kernel it stands in for).
-bool sweep2_wide_covers(int variant, int m_pad, int M);
+bool sweep2_wide_covers(int variant);
 hipError_t launch_sweep2_wide(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, float *dst, size_t plane_elems,
                               size_t chunk_stride, hipStream_t stream);
 hipError_t launch_select(const float *scores, int budget, int32_t *keep_idx, int B, int Hkv, int N, int ragged,

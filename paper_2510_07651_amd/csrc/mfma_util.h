@@ -252,5 +252,93 @@ __device__ __forceinline__ float sumabs8(const bf16x8 x, float acc) {
     return acc;
 }
 
+// What a workgroup of a sweep works on: token range `part` of `parts` of KV head g of sequence b, row chunk `chunk`.
+// With equal lengths the grid is (parts, chunks, B * Hkv).  A ragged batch's grid is one line of the live workgroups only
+// (workgroups are dealt out to the dies in turn before anyone knows that one has nothing to do, and a die with more live
+// ones than it has room for takes twice as long), in the same order.
+struct SweepPart { int part, parts, chunk, b, g, len; };
+template <typename Lens>
+__device__ __forceinline__ SweepPart sweep_part(const Lens &lens, int ragged, int N, int Hkv, int n_chunks, int share) {
+    SweepPart s;
+    if (!ragged) {
+        s.part = blockIdx.x; s.parts = gridDim.x; s.chunk = blockIdx.y;
+        s.b = blockIdx.z / Hkv; s.g = blockIdx.z % Hkv; s.len = N;
+        return s;
+    }
+    int at = blockIdx.x;
+    for (s.b = 0;; ++s.b) {                                    // (ends: the grid has exactly the live workgroups)
+        s.len = lens.len[s.b];
+        s.parts = (s.len + share - 1) / share;
+        const int here = s.parts * n_chunks * Hkv;
+        if (at < here) break;
+        at -= here;
+    }
+    s.part = at % s.parts;
+    s.chunk = at / s.parts % n_chunks;
+    s.g = at / (s.parts * n_chunks);
+    return s;
+}
+template <typename Lens>
+inline dim3 sweep_grid(const ScoreArgs &a, const Lens &lens, int n_chunks, int share) {
+    if (!a.ragged) return dim3((a.N + share - 1) / share, n_chunks, a.B * a.Hkv);
+    unsigned n = 0;
+    for (int b = 0; b < a.B; ++b) n += (lens.len[b] + share - 1) / share;
+    return dim3(n * n_chunks * a.Hkv);
+}
+// Zeros for the positions past the sequence's end, each of its workgroups an equal piece.
+template <int kNv>
+__device__ __forceinline__ void zero_padding(const SweepPart &s, int N, float *out, size_t variant_stride) {
+    const int piece = (N - s.len + s.parts - 1) / s.parts, from = s.len + s.part * piece, to = min(from + piece, N);
+    for (int t = from + (int)threadIdx.x; t < to; t += kThreads)
+#pragma unroll
+        for (int c = 0; c < kNv; ++c) out[c * variant_stride + t] = 0.f;
+}
+
+// Adds the separately scored pairs of at most 128 rows to a workgroup's finished sums (`special`: token or -1 and the
+// pair's three terms per row).  Call with every thread and at least 2 KB of `scratch` that nobody uses any more.  The first
+// wave collects the pairs of this token range; each pair's lane goes through them, and the first row of a token adds up
+// that token's terms in row order.  (One thread walking all rows took up to 11 us, and the workgroup that holds the sinks
+// is the one the launch then waits for.)
+template <int kVariant>
+__device__ __forceinline__ void add_special_pairs(char *scratch, const float *special, int rows, int t_begin, int t_end,
+                                                  float *out, size_t variant_stride) {
+    const int lane = threadIdx.x & 63;
+    float4 sp[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int i = 64 * h + lane;
+        sp[h] = threadIdx.x < 64 && i < rows ? ((const float4 *)special)[i] : make_float4(__int_as_float(-1), 0.f, 0.f, 0.f);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // (this wave's part of the sums is written)
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    float4 *list = (float4 *)scratch;
+    int n = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int tok = __float_as_int(sp[h].x);
+        const unsigned long long mine = __ballot(tok >= t_begin && tok < t_end);
+        if (mine >> lane & 1) list[n + __popcll(mine & ((1ull << lane) - 1))] = sp[h];
+        n += __popcll(mine);
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane; i < n; i += 64) {
+        const int tok = __float_as_int(list[i].x);
+        float acc[3] = {0.f, 0.f, 0.f};
+        bool first = true;
+        for (int j = 0; j < n; ++j) {
+            const float4 x = list[j];
+            if (__float_as_int(x.x) != tok) continue;
+            first = first && j >= i;
+            acc[0] += x.y; acc[1] += x.z; acc[2] += x.w;
+        }
+        if (!first) continue;
+        float *o = out + tok;
+        if (kVariant == OBC_VALUE || kVariant == OBC_ALL) { *o += acc[0]; o += variant_stride; }
+        if (kVariant == OBC_KEY || kVariant == OBC_ALL) { *o += acc[1]; o += variant_stride; }
+        if (kVariant == OBC_JOINT || kVariant == OBC_ALL) *o += acc[2];
+    }
+}
+
 }  // namespace mfma
 }  // namespace obc

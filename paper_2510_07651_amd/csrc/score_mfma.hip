@@ -23,9 +23,9 @@
 // interleaves them.  Sweep 2 exists in two forms.  The one in this file gives a wave 32 rows, runs
 // a block's matrix phase and vector phase back to back and leaves the overlap to the second wave
 // on the SIMD (its stationary operands and row constants leave no registers for a second set of
-// accumulators).  The register-blocked form (score_mfma_wide.hip: 64 rows per wave, stationary
-// operands in the accumulator file, the wave pipelined against itself) serves the key, joint and
-// all-three variants whenever every 128-row chunk is at least three quarters full.  K and V travel
+// accumulators).  The register-blocked forms (score_mfma_wide.hip: 64 rows per wave, stationary
+// operands in the accumulator file, the wave pipelined against itself) serve the key, joint and
+// all-three variants.  K and V travel
 // HBM -> LDS with direct-to-LDS loads: in sweep 1 as 32-token blocks through four-slot rings, three
 // batches in flight; in sweep 2 as 64-token tiles, double-buffered here, a four-slot ring there.
 //
@@ -59,6 +59,19 @@ namespace {
 // ------------------------------------------------------------------------------------
 // Sweep 1
 // ------------------------------------------------------------------------------------
+// Where a head's partial records start: every sequence has as many slots per head as it has live splits.
+template <typename Lens>
+__device__ __forceinline__ int split_slot(const Lens &lens, int ragged, int b, int g, int N, int Hkv, int split_len) {
+    int before = 0, own = (N + split_len - 1) / split_len;
+    if (ragged) {
+        for (int i = 0; i < b; ++i) before += (lens.len[i] + split_len - 1) / split_len;
+        own = (lens.len[b] + split_len - 1) / split_len;
+    } else {
+        before = b * own;
+    }
+    return before * Hkv + g * own;
+}
+
 struct Sweep1Regs {
     bf16x8 q[8];          // stationary B operand: this lane's query row, pieces 2 kk + half
     f32x16 oacc[4];       // O^T accumulators: head_dim block x 16 registers
@@ -319,7 +332,7 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
     }
 }
 
-// Grid: x = sequence split, y = 128-row chunk, z = (b, KV head).
+// Grid: see sweep_part (a part is a sequence split).
 // With kNeedO every row keeps its candidate for a dominant key (see kCandMargin) out of its sums and
 // reports it with the partial record; the combine step then forms v_cand - o_i without
 // cancellation for every row, and no row ever needs a second pass.
@@ -328,17 +341,15 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
                                                            const uint16_t *__restrict__ k,
                                                            const uint16_t *__restrict__ v, int N, int W, int Hq,
                                                            int Hkv, int ragged, Lens lens, int split_len,
-                                                           int n_splits, int m_pad, float *__restrict__ part_ml,
+                                                           int n_chunks, int m_pad, float *__restrict__ part_ml,
                                                            float *__restrict__ part_o, float *__restrict__ z, int z_stride) {
     __shared__ __attribute__((aligned(1024))) char smem[kLdsTiles];
     __shared__ int2 ev_list[kNeedO ? kThreads * kEvents : 1];   // per lane: parked former candidates (token, logit bits)
     int2 *events = ev_list + (kNeedO ? threadIdx.x * kEvents : 0);
 
-    const int split = blockIdx.x, chunk = blockIdx.y, bg = blockIdx.z;
-    const int b = bg / Hkv, g = bg % Hkv, G = Hq / Hkv, M = G * W;
-    const int len = seq_len_of(lens, ragged, b, N);
+    const SweepPart part = sweep_part(lens, ragged, N, Hkv, n_chunks, split_len);
+    const int b = part.b, g = part.g, bg = b * Hkv + g, chunk = part.chunk, split = part.part, G = Hq / Hkv, M = G * W, len = part.len;
     const int t_begin = split * split_len;
-    if (t_begin >= len) return;                                  // uniform: nothing of this split is live
     const int t_end = min(t_begin + split_len, len);
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -488,7 +499,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     if (kNeedO) __syncthreads();      // every wave is done with the rings: their space now stages the output rows
     if (!wave_active) return;
     const float lrow = halves_sum(R.lsum);
-    const size_t prow0 = ((size_t)bg * n_splits + split) * m_pad + rb * 32;     // the wave's first row
+    const size_t prow0 = (size_t)(split_slot(lens, ragged, b, g, N, Hkv, split_len) + split) * m_pad + rb * 32;     // the wave's first row
     if (half == 0)                    // reference in raw q.k units (-inf when the split holds no visible key), sum, candidate
         *(float4 *)(part_ml + (prow0 + (lane & 31)) * 4) =
             make_float4(R.m_ref, lrow, kNeedO ? R.cand_val : R.m_true, __int_as_float(kNeedO ? R.cand_tok : 0));
@@ -526,7 +537,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
 // one constant per row the second sweep turns logits into weights with.
 template <typename Lens>
 __global__ __launch_bounds__(128) void mfma_combine(const float *__restrict__ part_ml, int N, int W, int Hq, int Hkv,
-                                                    int ragged, Lens lens, int split_len, int n_splits,
+                                                    int ragged, Lens lens, int split_len,
                                                     int m_pad, uint16_t *__restrict__ out_bf16,
                                                     float *__restrict__ row_const, float *__restrict__ special) {
     const int row = blockIdx.x, bg = blockIdx.y;
@@ -534,6 +545,7 @@ __global__ __launch_bounds__(128) void mfma_combine(const float *__restrict__ pa
     const int len = seq_len_of(lens, ragged, b, N);
     const int dd = threadIdx.x;
     const size_t crow = (size_t)bg * m_pad + row;
+    const int slot0 = split_slot(lens, ragged, b, bg % Hkv, N, Hkv, split_len);
     const size_t lo_plane = (size_t)gridDim.y * m_pad * kD;   // residual pieces follow the high pieces
     out_bf16[crow * kD + dd] = 0;                     // (no cross term: the operand is never read, and stays defined)
     out_bf16[lo_plane + crow * kD + dd] = 0;
@@ -555,7 +567,7 @@ __global__ __launch_bounds__(128) void mfma_combine(const float *__restrict__ pa
         float4 ml[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j)      // (clamped slots are ignored below)
-            ml[j] = ((const float4 *)part_ml)[((size_t)bg * n_splits + min(s0 + j, live_splits - 1)) * m_pad + row];
+            ml[j] = ((const float4 *)part_ml)[(size_t)(slot0 + min(s0 + j, live_splits - 1)) * m_pad + row];
         float m_new = m_raw;
 #pragma unroll
         for (int j = 0; j < 16; ++j)
@@ -580,20 +592,24 @@ __global__ __launch_bounds__(128) void mfma_combine(const float *__restrict__ pa
 //     v_cand - o_i = l' / (w + l') * (v_cand - O' / l'),      o_i = v_cand - (v_cand - o_i)
 // without cancellation however much of the row's attention the candidate holds.  A candidate that
 // holds a large share is scored here from these (`special`) and skipped by the second sweep.
-// Grid: x = group of four padded rows, y = (b, KV head); 32 lanes per row, four head_dim elements per lane.
-template <typename Lens>
-__global__ __launch_bounds__(128) void mfma_combine_hold(const uint16_t *__restrict__ v,
-                                                         const float *__restrict__ part_ml,
-                                                         const float *__restrict__ part_o, int N, int W, int Hq,
-                                                         int Hkv, int ragged, Lens lens, int split_len,
-                                                         int n_splits, int m_pad, uint16_t *__restrict__ out_bf16,
-                                                         float *__restrict__ row_const,
-                                                         float *__restrict__ special) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 5), bg = blockIdx.y;
+//
+// Grid: y = (b, KV head).  32 lanes take a row's elements, four each, and kBatch splits in one memory round trip.  With
+// kGroups == 1 a workgroup has four rows.  With more, it has one row, and its kGroups groups of 32 lanes take kBatch
+// splits each: a long head alone on the chip is cut into up to 128 splits, which one group would fetch in eight round
+// trips (4 heads x 128K, 112 rows: 47 us, 14 us in eight groups).
+template <int kGroups, int kBatch, typename Lens>
+__global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combine_hold(
+    const uint16_t *__restrict__ v, const float *__restrict__ part_ml, const float *__restrict__ part_o, int N, int W, int Hq,
+    int Hkv, int ragged, Lens lens, int split_len, int m_pad, uint16_t *__restrict__ out_bf16, float *__restrict__ row_const,
+    float *__restrict__ special) {
+    const int group = threadIdx.x >> 5, row = kGroups == 1 ? blockIdx.x * 4 + group : blockIdx.x, bg = blockIdx.y;
+    const int first = kGroups == 1 ? 0 : group * kBatch;  // this group's first split
+    constexpr int kStride = kBatch * kGroups;
     const int b = bg / Hkv, G = Hq / Hkv, M = G * W;
     const int len = seq_len_of(lens, ragged, b, N);
     const int sub = threadIdx.x & 31, dd = sub * 4;   // this lane's elements dd .. dd + 3
     const size_t crow = (size_t)bg * m_pad + row;
+    const int slot0 = split_slot(lens, ragged, b, bg % Hkv, N, Hkv, split_len);
     const size_t lo_plane = (size_t)gridDim.y * m_pad * kD;
     const bool live = row < M;                        // the same for the 32 lanes of a row
     const int live_splits = (len + split_len - 1) / split_len;
@@ -601,57 +617,71 @@ __global__ __launch_bounds__(128) void mfma_combine_hold(const uint16_t *__restr
     const uint16_t *vg = v + (size_t)bg * N * kD;
     // First the common reference T (no sum lies more than the lazy-rescale slack above its own
     // reference, so the largest reference or candidate logit will do) and the winning candidate.
-    // The first 16 splits' records and sums are fetched in one go and stay in registers.
+    // The first splits' records and sums are fetched in one go and stay in registers.
     float T = -INFINITY, c_val = -INFINITY;
     int c_tok = -1, s_star = -1;
-    float4 ml[16], po[16];
+    float4 ml[kBatch], po[kBatch];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const size_t prow = ((size_t)bg * n_splits + min(j, live_splits - 1)) * m_pad + row;
+    for (int j = 0; j < kBatch; ++j) {
+        const size_t prow = (size_t)(slot0 + min(first + j, live_splits - 1)) * m_pad + row;
         ml[j] = ((const float4 *)part_ml)[prow];
         po[j] = *(const float4 *)(part_o + prow * kD + dd);
     }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        if (j >= live_splits) continue;
+    for (int j = 0; j < kBatch; ++j) {
+        if (first + j >= live_splits) continue;
         T = fmaxf(T, fmaxf(ml[j].x, ml[j].z));
         const int tok = __float_as_int(ml[j].w);
-        if (tok >= 0 && ml[j].z > c_val) { c_val = ml[j].z; c_tok = tok; s_star = j; }
+        if (tok >= 0 && ml[j].z > c_val) { c_val = ml[j].z; c_tok = tok; s_star = first + j; }
     }
-    for (int s0 = 16; s0 < live_splits; s0 += 16) {
-        float4 mm[16];
+    for (int s0 = first + kStride; s0 < live_splits; s0 += kStride) {
+        float4 mm[kBatch];
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-            mm[j] = ((const float4 *)part_ml)[((size_t)bg * n_splits + min(s0 + j, live_splits - 1)) * m_pad + row];
+        for (int j = 0; j < kBatch; ++j)
+            mm[j] = ((const float4 *)part_ml)[(size_t)(slot0 + min(s0 + j, live_splits - 1)) * m_pad + row];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+        for (int j = 0; j < kBatch; ++j) {
             if (s0 + j >= live_splits) continue;
             T = fmaxf(T, fmaxf(mm[j].x, mm[j].z));
             const int tok = __float_as_int(mm[j].w);
             if (tok >= 0 && mm[j].z > c_val) { c_val = mm[j].z; c_tok = tok; s_star = s0 + j; }
         }
     }
+    if constexpr (kGroups > 1) {                      // the groups agree (equal logits: the lowest split)
+        __shared__ float4 found[kGroups];
+        if (sub == 0) found[group] = make_float4(T, c_val, __int_as_float(c_tok), __int_as_float(s_star));
+        __syncthreads();
+        T = c_val = -INFINITY;
+        c_tok = s_star = -1;
+#pragma unroll
+        for (int i = 0; i < kGroups; ++i) {
+            const float4 f = found[i];
+            T = fmaxf(T, f.x);
+            const int tok = __float_as_int(f.z), star = __float_as_int(f.w);
+            if (tok >= 0 && (f.y > c_val || (f.y == c_val && star < s_star))) { c_val = f.y; c_tok = tok; s_star = star; }
+        }
+    }
     if (!live) { c_tok = -1; s_star = -1; }           // padded rows: zero queries, nothing of theirs is used
     const uint2 vt_bits = c_tok >= 0 ? *(const uint2 *)(vg + (size_t)c_tok * kD + dd) : make_uint2(0u, 0u);
     float l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < live_splits; s0 += 16) {
-        uint2 vo[16];
-        if (s0 > 0) {
+    for (int s0 = first; s0 < live_splits; s0 += kStride) {
+        uint2 vo[kBatch];
+        if (s0 > first) {
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {         // (the records are in cache from the pass above)
-                const size_t prow = ((size_t)bg * n_splits + min(s0 + j, live_splits - 1)) * m_pad + row;
+            for (int j = 0; j < kBatch; ++j) {         // (the records are in cache from the pass above)
+                const size_t prow = (size_t)(slot0 + min(s0 + j, live_splits - 1)) * m_pad + row;
                 ml[j] = ((const float4 *)part_ml)[prow];
                 po[j] = *(const float4 *)(part_o + prow * kD + dd);
             }
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+        for (int j = 0; j < kBatch; ++j) {
             const int tok = __float_as_int(ml[j].w);
             const bool back = live && s0 + j < live_splits && s0 + j != s_star && tok >= 0;
             vo[j] = back ? *(const uint2 *)(vg + (size_t)tok * kD + dd) : make_uint2(0u, 0u);
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+        for (int j = 0; j < kBatch; ++j) {
             if (s0 + j >= live_splits) continue;
             const float w = ml[j].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml[j].x - T) * c2);
             l = fmaf(w, ml[j].y, l);
@@ -667,6 +697,19 @@ __global__ __launch_bounds__(128) void mfma_combine_hold(const uint16_t *__restr
                 o[2] = fmaf(wc, __uint_as_float(vo[j].y << 16), o[2]);
                 o[3] = fmaf(wc, __uint_as_float(vo[j].y & 0xffff0000u), o[3]);
             }
+        }
+    }
+    if constexpr (kGroups > 1) {                      // the groups' sums meet in group order
+        __shared__ float sum_l[kGroups];
+        __shared__ float4 sum_o[kGroups][32];
+        if (sub == 0) sum_l[group] = l;
+        sum_o[group][sub] = make_float4(o[0], o[1], o[2], o[3]);
+        __syncthreads();
+        if (group != 0) return;
+        for (int i = 1; i < kGroups; ++i) {
+            const float4 x = sum_o[i][sub];
+            l += sum_l[i];
+            o[0] += x.x; o[1] += x.y; o[2] += x.z; o[3] += x.w;
         }
     }
     // (no split may have kept a candidate: then w = 0 and o_i = O' / l' as usual)
@@ -860,15 +903,15 @@ __device__ __forceinline__ void sweep2_step(Sweep2Regs &R, const char *smem, uin
     }
 }
 
-// kVariant: OBC_VALUE / OBC_KEY / OBC_JOINT / OBC_ALL / OBC_ATTN / OBC_VATP.  Grid: x = token range, y = chunk, z = (b, KV head).
+// kVariant: OBC_VALUE / OBC_KEY / OBC_JOINT / OBC_ALL / OBC_ATTN / OBC_VATP.  Grid: see sweep_part.
 // With one chunk the scores go straight to `scores`; with several, each chunk writes its
 // own plane and mfma_sum_planes adds them in chunk order.
 template <int kVariant, typename Lens>
 __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__restrict__ q,
                                                            const uint16_t *__restrict__ k,
                                                            const uint16_t *__restrict__ v, int N, int W, int Hq,
-                                                           int Hkv, int ragged, Lens lens, int range_len, int m_pad,
-                                                           const uint16_t *__restrict__ out_bf16,
+                                                           int Hkv, int heads, int ragged, Lens lens, int range_len,
+                                                           int n_chunks, int m_pad, const uint16_t *__restrict__ out_bf16,
                                                            const float *__restrict__ row_const,
                                                            const float *__restrict__ special,
                                                            float *__restrict__ dst, size_t variant_stride,
@@ -882,20 +925,10 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__res
     float *excl_s = vis_s + 128;                               // [128] key of the row that is scored separately, or -1
     float *part = excl_s + 128;                                // [2 tiles][4 waves][kNv][64] partial scores
 
-    const int range = blockIdx.x, chunk = blockIdx.y, bg = blockIdx.z;
-    const int b = bg / Hkv, g = bg % Hkv, G = Hq / Hkv, M = G * W;
-    const int len = seq_len_of(lens, ragged, b, N);
-    const int t_begin = range * range_len;
-    const int t_stop = min(t_begin + range_len, N);            // scores are written for [t_begin, t_stop)
+    const SweepPart where = sweep_part(lens, ragged, N, Hkv, n_chunks, range_len);
+    const int b = where.b, g = where.g, bg = b * Hkv + g, chunk = where.chunk, G = Hq / Hkv, M = G * W, len = where.len;
+    const int t_begin = where.part * range_len;
     float *out = dst + (size_t)chunk * chunk_stride + (size_t)bg * N;
-
-    if (t_begin >= len) {                                      // uniform: only padded positions here
-        if (accumulate) return;
-        for (int t = t_begin + threadIdx.x; t < t_stop; t += kThreads)
-#pragma unroll
-            for (int c = 0; c < kNv; ++c) out[c * variant_stride + t] = 0.f;
-        return;
-    }
     const int t_end = min(t_begin + range_len, len);
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -938,7 +971,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__res
         const bool ok = arow < M;
         const char *qrow = (const char *)q + (((size_t)b * Hq + (size_t)g * G) * W + arow) * kRowBytes;
         const char *orow = (const char *)out_bf16 + (cbase + arow) * kRowBytes;
-        const size_t lo_plane = (size_t)gridDim.z * m_pad * kRowBytes;
+        const size_t lo_plane = (size_t)heads * m_pad * kRowBytes;
         // One array after the other: the four loads that share a 128-byte line of a row follow each other closely.
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk)
@@ -1017,42 +1050,10 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__res
     __syncthreads();
     // The last tile's partial sums (second staging slot: n_total is a multiple of 4), then zeros for the padding.
     sweep2_flush<kNv>(part + 4 * kNv * 64, out, variant_stride, t_begin + (n_total - 2) * 32, t_end, wave, lane, accumulate);
-    if (!accumulate)
-        for (int t = t_end + threadIdx.x; t < t_stop; t += kThreads)
-#pragma unroll
-            for (int c = 0; c < kNv; ++c) out[c * variant_stride + t] = 0.f;
+    if (!accumulate) zero_padding<kNv>(where, N, out, variant_stride);
     if (has_special) {
-        // Add the separately scored pairs: staged in LDS (the tiles are done with), then summed by one
-        // thread in row order; consecutive rows that share their key (a sink, typically) cost one update.
         wait_async_loads();
-        __syncthreads();
-        float4 *staged = (float4 *)smem;
-        if (threadIdx.x < 128) {
-            const int i = chunk * 128 + threadIdx.x;
-            staged[threadIdx.x] = i < m_pad ? ((const float4 *)special)[cbase + i] : make_float4(__int_as_float(-1), 0.f, 0.f, 0.f);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int cur = -1;
-            float acc[3] = {0.f, 0.f, 0.f};
-            for (int i = 0; i <= 128; ++i) {
-                const float4 sp = i < 128 ? staged[i] : make_float4(__int_as_float(-2), 0.f, 0.f, 0.f);
-                const int ex = __float_as_int(sp.x);
-                const bool mine = ex >= t_begin && ex < t_end;
-                if (i < 128 && !mine) continue;
-                if (ex != cur) {
-                    if (cur >= 0) {
-                        int c = 0;
-                        if (kVariant == OBC_VALUE || kVariant == OBC_ALL) out[(c++) * variant_stride + cur] += acc[0];
-                        if (kVariant == OBC_KEY || kVariant == OBC_ALL) out[(c++) * variant_stride + cur] += acc[1];
-                        if (kVariant == OBC_JOINT || kVariant == OBC_ALL) out[(c++) * variant_stride + cur] += acc[2];
-                    }
-                    cur = i < 128 ? ex : -1;
-                    acc[0] = acc[1] = acc[2] = 0.f;
-                }
-                acc[0] += sp.y; acc[1] += sp.z; acc[2] += sp.w;
-            }
-        }
+        add_special_pairs<kVariant>(smem, special + (cbase + chunk * 128) * 4, min(128, m_pad - chunk * 128), t_begin, t_end, out, variant_stride);
     }
 }
 
@@ -1063,7 +1064,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__res
 // One 16x16x32 matrix op takes 16 tokens and all rows at once: rows 0-7 of its A operand are the high pieces of the
 // (scaled) o^_i, rows 8-15 the low ones, so their products meet in lanes l and l ^ 32.  V goes from memory straight into
 // the B operand (a tile's instruction reads 64 bytes of each of 16 rows), no LDS.  Bound by the read of V: 4 x 8 x 32768
-// tokens, G = 4, joint: 109 us for the second sweep over K and V, FEW_US for this.
+// tokens, G = 4, joint: 109 us for the second sweep over K and V, 57 us for this.
 constexpr int kFewRows = 8;
 constexpr int kFewTiles = 4;
 
@@ -1229,9 +1230,8 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
     const size_t plane_elems = (size_t)a.B * a.Hkv * a.N;
     float *dst = ws.n_chunks > 1 ? (float *)(base + ws.planes) : a.scores;
     const size_t chunk_stride = ws.n_chunks > 1 ? plane_elems * nv : 0;
-    const dim3 grid((a.N + ws.range_len - 1) / ws.range_len, ws.n_chunks, a.B * a.Hkv);
     if (ws.keep_z) {
-        score_few_rows<kVariant><<<dim3(grid.x, a.B * a.Hkv), dim3(kThreads), 0, stream>>>(
+        score_few_rows<kVariant><<<dim3((a.N + ws.range_len - 1) / ws.range_len, a.B * a.Hkv), dim3(kThreads), 0, stream>>>(
             (const uint16_t *)a.v, a.N, a.G * a.W, a.Hkv, a.ragged, lens, ws.range_len, ws.m_pad, (const float *)(base + ws.z),
             ws.z_stride, (const uint16_t *)(base + ws.out_bf16), (size_t)a.B * a.Hkv * ws.m_pad * kD, (const float *)(base + ws.row_const),
             (const float *)(base + ws.special), dst, plane_elems, a.accumulate);
@@ -1239,9 +1239,9 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
     } else if (ws.use_wide) {
         e = launch_sweep2_wide(a, ws, base, dst, plane_elems, chunk_stride, stream);
     } else {
-        mfma_sweep2<kVariant><<<grid, dim3(kThreads), 0, stream>>>(
-            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens,
-            ws.range_len, ws.m_pad, (const uint16_t *)(base + ws.out_bf16), (const float *)(base + ws.row_const),
+        mfma_sweep2<kVariant><<<sweep_grid(a, lens, ws.n_chunks, ws.range_len), dim3(kThreads), 0, stream>>>(
+            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.B * a.Hkv, a.ragged, lens,
+            ws.range_len, ws.n_chunks, ws.m_pad, (const uint16_t *)(base + ws.out_bf16), (const float *)(base + ws.row_const),
             (const float *)(base + ws.special), dst, plane_elems, chunk_stride,
             ws.n_chunks == 1 ? a.accumulate : 0);
         e = hipGetLastError();
@@ -1255,28 +1255,49 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
 
 }  // namespace
 
+// Tokens one workgroup should take of every KV head's sequence, so that the launch keeps the chip evenly busy.  `slots`
+// workgroups run at a time and `heads` of them walk each sequence side by side; a launch of a few workgroups more than
+// the slots would take twice as long, and sequences shorter than N leave slots idle.  Among the lengths that fill one to
+// eight rounds of the slots, the one with the least rounds x (length + kStart) is taken; kStart stands for what a
+// workgroup does before its first and after its last token.
+static int even_share(const int *len, int B, int N, int heads, int slots, int min_len) {
+    constexpr int kUnit = kTileTok, kStart = 256;
+    auto workgroups = [&](int share) {
+        long long n = 0;
+        if (!len) return (long long)heads * B * ((N + share - 1) / share);
+        for (int b = 0; b < B; ++b) n += (len[b] + share - 1) / share;
+        return n * heads;
+    };
+    const int lo_unit = min_len / kUnit, hi_unit = (N + kUnit - 1) / kUnit;
+    int best = 0;
+    long long best_cost = 0;
+    for (int rounds = 1; rounds <= 8; ++rounds) {
+        int lo = lo_unit, hi = hi_unit > lo_unit ? hi_unit : lo_unit;          // the shortest share that fits, if any does
+        if (workgroups(hi * kUnit) > (long long)rounds * slots) continue;
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (workgroups(mid * kUnit) <= (long long)rounds * slots) hi = mid; else lo = mid + 1;
+        }
+        const long long cost = (long long)rounds * (lo * kUnit + kStart);
+        if (best == 0 || cost < best_cost) { best = lo * kUnit; best_cost = cost; }
+        if (lo == lo_unit) break;
+    }
+    if (best == 0) best = (hi_unit > lo_unit ? hi_unit : lo_unit) * kUnit;      // more sequences than eight rounds: one workgroup each
+    return best;
+}
+
 void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv;
     const int nv = variant == OBC_ALL ? 3 : 1;
+    const int M = Hq / Hkv * W, form = tuned_sweep2_form();
     ws->n_chunks = (ws->m_pad + 127) / 128;
-    int splits = (512 + BH * ws->n_chunks - 1) / (BH * ws->n_chunks);
-    const int max_splits = (N + 511) / 512;
-    splits = splits < 1 ? 1 : (splits > max_splits ? max_splits : splits);
-    if (const int v = tuned_splits(); v >= 1 && v <= max_splits) splits = v;    // obc_set_score_tuning
-    ws->split_len = ((N + splits - 1) / splits + kTileTok - 1) / kTileTok * kTileTok;
+    ws->split_len = even_share(nullptr, B, N, Hkv * ws->n_chunks, 512, 512);
+    if (const int v = tuned_splits(); v >= 1 && v <= (N + 511) / 512)           // obc_set_score_tuning
+        ws->split_len = ((N + v - 1) / v + kTileTok - 1) / kTileTok * kTileTok;
     ws->splits = (N + ws->split_len - 1) / ws->split_len;
-    // Token range of one sweep-2 block: about two blocks per compute unit over the whole launch; the
-    // register-blocked form runs one workgroup per compute unit and gets one block each.
-    const int form = tuned_sweep2_form();
-    ws->use_wide = (form != 1 && sweep2_wide_covers(variant, ws->m_pad, (Hq / Hkv) * W)) ? 1 : 0;
-    {
-        const long long units = (long long)N * BH * ws->n_chunks;
-        const long long blocks = ws->use_wide ? 256 : 512;
-        long long r = ((units + blocks - 1) / blocks + 63) / 64 * 64;
-        ws->range_len = (int)(r < 128 ? 128 : (r > 8192 ? 8192 : r));
-    }
-    if (const int v = tuned_range(); v >= 64 && v <= 65536 && v % 64 == 0) ws->range_len = v;
+    ws->use_wide = form != 1 && sweep2_wide_covers(variant) ? 1 : 0;
+    ws->solo = ws->use_wide && (M - 1) % 128 < 64 ? 1 : 0;
     const size_t rows = (size_t)BH * ws->m_pad;
     ws->out_bf16 = *off;  *off = align_up(*off + 2 * rows * d * 2, 256);   // high pieces, then residual pieces
     ws->row_const = *off; *off = align_up(*off + rows * 4 * sizeof(float), 256);
@@ -1287,17 +1308,37 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, size_t 
     if (ws->n_chunks > 1) *off = align_up(*off + (size_t)ws->n_chunks * nv * BH * N * sizeof(float), 256);
     // With few rows the first sweep keeps their logits (4 bytes per pair) and the second reads them instead of K (256 bytes
     // per token): beyond eight rows the gain fades.
-    const int M = Hq / Hkv * W;
     ws->z_stride = (N + 31) / 32 * 32;
     const size_t z_bytes = (size_t)BH * M * ws->z_stride * sizeof(float);
     ws->keep_z = M <= kFewRows && *off + z_bytes <= cap && (long long)M * ws->z_stride < (1LL << 29) ? 1 : 0;    // (32-bit offsets)
     if (ws->keep_z) {
         ws->z = *off;
         *off = align_up(*off + z_bytes, 256);
-        ws->use_wide = 0;
-        // The first sweep's splits, in whole workgroup steps of 256 tokens (see score_few_rows for the order inside).
-        ws->range_len = (int)align_up(ws->split_len, 256);
+        ws->use_wide = ws->solo = 0;
     }
+}
+
+// The shares of this call's true lengths (the plan knows only N): shorter splits where they still fit the workspace, whose
+// records lie one sequence after the other (see split_slot), and the second sweep's ranges.
+static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
+    const int *len = a.ragged ? a.lens.len : nullptr;
+    if (len && tuned_splits() == 0) {
+        const int share = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, 512, 512);
+        int records = 0, most = 1;
+        for (int b = 0; b < a.B; ++b) {
+            const int n = (len[b] + share - 1) / share;
+            records += n;
+            most = n > most ? n : most;
+        }
+        if (records <= a.B * ws.splits) { ws.split_len = share; ws.splits = most; }
+    }
+    const int full = ws.n_chunks - ws.solo;
+    ws.range_len = even_share(len, a.B, a.N, a.Hkv * (full > 0 ? full : 1), ws.use_wide ? 256 : 512, 128);
+    ws.range_solo = even_share(len, a.B, a.N, a.Hkv, 256, 128);
+    // (kept logits: the first sweep's splits, in whole workgroup steps of 256 tokens; score_few_rows says in which order)
+    if (ws.keep_z) ws.range_len = (ws.split_len + 255) / 256 * 256;
+    else if (const int v = tuned_range(); v >= 64 && v <= 65536 && v % 64 == 0) ws.range_len = ws.range_solo = v;
+    return ws;
 }
 
 template <typename Lens>
@@ -1306,11 +1347,11 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
     float *part_ml = (float *)(base + ws.part_ml), *part_o = (float *)(base + ws.part_o);
     hipError_t e = hipSuccess;
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
-        const dim3 grid(ws.splits, ws.n_chunks, a.B * a.Hkv);
+        const dim3 grid = sweep_grid(a, lens, ws.n_chunks, ws.split_len);
 #define OBC_SWEEP1(need_o, store_z)                                                                                    \
     mfma_sweep1<need_o, store_z><<<grid, dim3(kThreads), 0, stream>>>(                                                 \
         (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens,      \
-        ws.split_len, ws.splits, ws.m_pad, part_ml, part_o, (float *)(base + ws.z), ws.z_stride)
+        ws.split_len, ws.n_chunks, ws.m_pad, part_ml, part_o, (float *)(base + ws.z), ws.z_stride)
         if (need_o && ws.keep_z) OBC_SWEEP1(true, true);
         else if (need_o) OBC_SWEEP1(true, false);
         else if (ws.keep_z) OBC_SWEEP1(false, true);
@@ -1321,14 +1362,18 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
     }
     if (a.stage_mask & OBC_STAGE_COMBINE) {
         const dim3 grid(ws.m_pad, a.B * a.Hkv);
-        if (need_o)
-            mfma_combine_hold<<<dim3(ws.m_pad / 4, a.B * a.Hkv), dim3(128), 0, stream>>>(      // (m_pad: a multiple of 32)
-                (const uint16_t *)a.v, part_ml, part_o, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len,
-                ws.splits, ws.m_pad, (uint16_t *)(base + ws.out_bf16), (float *)(base + ws.row_const),
-                (float *)(base + ws.special));
+#define OBC_COMBINE(groups, batch, rows)                                                                               \
+    mfma_combine_hold<groups, batch><<<dim3(ws.m_pad / rows, a.B * a.Hkv), dim3(32 * groups * rows), 0, stream>>>(            \
+        (const uint16_t *)a.v, part_ml, part_o, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.m_pad,         \
+        (uint16_t *)(base + ws.out_bf16), (float *)(base + ws.row_const), (float *)(base + ws.special))
+        if (need_o && ws.splits <= 16) OBC_COMBINE(1, 16, 4);      // (m_pad: a multiple of 32)
+        else if (need_o && ws.splits <= 32) OBC_COMBINE(4, 8, 1);
+        else if (need_o && ws.splits <= 64) OBC_COMBINE(8, 8, 1);
+        else if (need_o) OBC_COMBINE(8, 16, 1);
+#undef OBC_COMBINE
         else
             mfma_combine<<<grid, dim3(128), 0, stream>>>(
-                part_ml, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.splits, ws.m_pad,
+                part_ml, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.m_pad,
                 (uint16_t *)(base + ws.out_bf16), (float *)(base + ws.row_const), (float *)(base + ws.special));
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1344,7 +1389,8 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
     }
 }
 
-hipError_t launch_score_mfma(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
+hipError_t launch_score_mfma(const ScoreArgs &a, const ScoreWorkspace &plan, char *base, hipStream_t stream) {
+    const ScoreWorkspace ws = mfma_balance(a, plan);
     return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) { return launch_with(a, lens, ws, base, stream); });
 }
 

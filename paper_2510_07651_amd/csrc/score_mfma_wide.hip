@@ -29,6 +29,8 @@
 #include "internal.h"
 #include "mfma_util.h"
 
+#include <type_traits>
+
 namespace obc {
 using namespace mfma;
 namespace {
@@ -218,6 +220,15 @@ __device__ __forceinline__ void hide_pairs(f32x16 &z, int S, int tok, int t_end,
     }
 }
 
+// Blocks of 32 tokens (counted from the workgroup's first) that hold a separately scored pair, one bit each, folded at
+// kSpecialWords * 32 blocks: a block that is taken for one of them without need only costs its masks.  (With needles all
+// over a long context nearly every block lies between the first and the last such pair of a range.)
+constexpr int kSpecialWords = 32;
+__device__ __forceinline__ int special_word(int blk) { return blk >> 5 & (kSpecialWords - 1); }
+__device__ __forceinline__ bool special_bit(uint32_t word, int blk) {
+    return __builtin_amdgcn_readfirstlane((int)word) >> (blk & 31) & 1;
+}
+
 // Sum of squares of dwords 2 q and 2 q + 1 (four bf16 values) of a 16-byte operand piece.
 __device__ __forceinline__ float sumsq_quarter(const bf16x8 x, int q, float acc) {
     union { bf16x8 v; bf16x2 h[4]; } u;
@@ -244,11 +255,12 @@ __device__ __forceinline__ void fetch_one(const TileFetch &f, int n, int wave) {
 // 2 j and 2 j + 1.  Phase 1 also forms ||v_p||^2 of this block (two dot-product ops in each of the first 16 slots) and
 // starts the wave's eight transfers of the tile three steps ahead (one in each of the last eight slots).
 // The row constants of four accumulator registers are fetched from LDS six slots before their first use.
-// `masks`: some (row, key) pair of this block is causally hidden, past the sequence's end or scored separately.
+// `hidden`: some (row, key) pair of this block is causally hidden or past the sequence's end; `special`: the bits of its
+// group of 32 blocks (see special_word).
 template <int kVariant>
 __device__ __forceinline__ void pipelined_block(WideState &R, const Stationary &A, const TileFetch &fetch, float *stage_prev,
-                                                int tok, int t_end, int rh, int th, int wave, int lane, bool masks,
-                                                const int *vis_i, const int *excl_i) {
+                                                int tok, int t_end, int rh, int th, int wave, int lane, int blk, bool hidden,
+                                                uint32_t special, const int *vis_i, const int *excl_i) {
     const int half = lane >> 5;
     float vvn = 0.f, bv = 0.f, bk = 0.f, bj = 0.f;
     const TokenConsts tp = token_consts(R.vv_prev);
@@ -268,6 +280,7 @@ __device__ __forceinline__ void pipelined_block(WideState &R, const Stationary &
     });
     // (unconditional, so that the vector work above stays where it is: with no block before, `stage_prev` is a spare slot)
     park_block<kVariant>(stage_prev, rh, th, lane, tp.vv, R.sv, R.sk, R.sj, bv, bk, bj);
+    const bool masks = hidden || special_bit(special, blk);
     if (masks) {                                               // uniform for the wave, rare
         matrix_results_land();
         hide_pairs(R.zA, 0, tok, t_end, rh, half, vis_i, excl_i);
@@ -312,7 +325,7 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
                                           int tile_fetch, int tile_flush, int t_begin,
                                           int t_end, int last_row, const int *vis_i, const int *excl_i, const char *kh,
                                           const char *vh, const uint32_t (&kdoff)[4], int wave, int lane, int vis_min,
-                                          int m_lo, int m_hi, float *stage, float *out, size_t variant_stride,
+                                          const uint32_t *special_s, float *stage, float *out, size_t variant_stride,
                                           bool accumulate) {
     constexpr int kNv = kVariant == OBC_ALL ? 3 : 1;
     const int rh = wave & 1, th = wave >> 1;
@@ -344,21 +357,21 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
     const int tok0 = t_begin + tile * kTileTok + th * 32;                // this wave's block
     const int blk = 2 * tile + th;
     // Blocks every row of the wave sees in full and that hold no separately scored pair need no masks.
-    const bool masks = !(tok0 + 31 <= vis_min) || (blk >= m_lo && blk <= m_hi);      // uniform for the wave
+    const bool hidden = !(tok0 + 31 <= vis_min);                         // uniform for the wave
     float *stage_prev = stage + (R.pend ? (s - 1) & 3 : kSlots) * 2 * kNv * 64;      // (slot 4: never flushed)
-    pipelined_block<kVariant>(R, A, fetch, stage_prev, tok0 + (lane & 31), t_end, rh, th, wave, lane, masks, vis_i, excl_i);
+    pipelined_block<kVariant>(R, A, fetch, stage_prev, tok0 + (lane & 31), t_end, rh, th, wave, lane, blk, hidden, special_s[special_word(blk)], vis_i, excl_i);
     // On to the slot of tile s+2 (the ring wraps after slot 3).
     const int hop = ((s + 1) & 3) == 0 ? -(kSlots - 1) * kSlotBytes : kSlotBytes;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) R.kp[kk] += hop;
 }
 
-// kVariant: OBC_KEY / OBC_JOINT / OBC_ALL.  Grid: x = token range, y = 128-row chunk, z = (b, KV head).
+// kVariant: OBC_KEY / OBC_JOINT / OBC_ALL.  Grid: see sweep_part.
 template <int kVariant, typename Lens>
 __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *__restrict__ q,
                                                                 const uint16_t *__restrict__ k,
                                                                 const uint16_t *__restrict__ v, int N, int W, int Hq,
-                                                                int Hkv, int ragged, Lens lens, int range_len, int m_pad,
+                                                                int Hkv, int heads, int ragged, Lens lens, int range_len, int n_chunks, int m_pad,
                                                                 const uint16_t *__restrict__ out_bf16,
                                                                 const float *__restrict__ row_const,
                                                                 const float *__restrict__ special,
@@ -373,20 +386,10 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     float *excl_s = vis_s + 128;                               // [128] key of the row that is scored separately, or -1
     float *stage = excl_s + 128;                               // [4 tiles + 1][2 row halves][kNv][64]
 
-    const int range = blockIdx.x, chunk = blockIdx.y, bg = blockIdx.z;
-    const int b = bg / Hkv, g = bg % Hkv, G = Hq / Hkv, M = G * W;
-    const int len = seq_len_of(lens, ragged, b, N);
-    const int t_begin = range * range_len;
-    const int t_stop = min(t_begin + range_len, N);            // scores are written for [t_begin, t_stop)
+    const SweepPart part = sweep_part(lens, ragged, N, Hkv, n_chunks, range_len);
+    const int b = part.b, g = part.g, bg = b * Hkv + g, chunk = part.chunk, G = Hq / Hkv, M = G * W, len = part.len;
+    const int t_begin = part.part * range_len;
     float *out = dst + (size_t)chunk * chunk_stride + (size_t)bg * N;
-
-    if (t_begin >= len) {                                      // uniform: only padded positions here
-        if (accumulate) return;
-        for (int t = t_begin + threadIdx.x; t < t_stop; t += kThreads)
-#pragma unroll
-            for (int c = 0; c < kNv; ++c) out[c * variant_stride + t] = 0.f;
-        return;
-    }
     const int t_end = min(t_begin + range_len, len);
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -413,7 +416,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
         tile_load_async<kXor16>(kh, tt, len - 1, lds0 + 3 * kSlotBytes, wave, lane, kdoff);
         tile_load_async<kXor16>(vh, tt, len - 1, lds0 + 3 * kSlotBytes + kTileBytes, wave, lane, kdoff);
     }
-    const size_t lo_plane = (size_t)gridDim.z * m_pad * kRowBytes;
+    const size_t lo_plane = (size_t)heads * m_pad * kRowBytes;
     {
         const char *q_rows = (const char *)q + ((size_t)b * Hq + (size_t)g * G) * W * kRowBytes;      // the KV head's M rows
         const char *o_rows = (const char *)out_bf16 + cbase * kRowBytes;                             // its m_pad rows
@@ -453,9 +456,8 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
         vis_min = __builtin_amdgcn_readfirstlane(min(vis_min, t_end - 1));
     }
 
-    // First and last block (of 32 tokens, counted from t_begin) that hold a separately scored (row, key) pair.
-    __shared__ int spec_lo, spec_hi;
-    if (threadIdx.x == 0) { spec_lo = 0x7fffffff; spec_hi = -1; }
+    __shared__ uint32_t special_s[kSpecialWords];
+    if (threadIdx.x < kSpecialWords) special_s[threadIdx.x] = 0;
     wait_async_loads();                                        // the first tile and the staged operands have landed
     __syncthreads();
     // Stationary operands: rows row0 + 32 S + (lane % 32), pieces 2 kk + half, parked in the accumulator file.
@@ -481,15 +483,10 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
         vis_s[threadIdx.x] = my_rc.z;
         excl_s[threadIdx.x] = __int_as_float(ex);
         mine_special = ex >= t_begin && ex < t_end;
-        if (mine_special) {
-            atomicMin(&spec_lo, (ex - t_begin) >> 5);
-            atomicMax(&spec_hi, (ex - t_begin) >> 5);
-        }
+        if (mine_special) atomicOr(&special_s[special_word((ex - t_begin) >> 5)], 1u << ((ex - t_begin) >> 5 & 31));
     }
     const int *vis_i = (const int *)vis_s, *excl_i = (const int *)excl_s;
     const bool has_special = __syncthreads_or(mine_special) != 0;
-    const int m_lo = has_special ? __builtin_amdgcn_readfirstlane(spec_lo) : 1;
-    const int m_hi = has_special ? __builtin_amdgcn_readfirstlane(spec_hi) : 0;
 
     // Every wave has its stationary operands (the barrier above): the staging slots take the next three tiles.
 #pragma unroll
@@ -514,8 +511,8 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     // Positions of the walk: the tile worked on, the one fetched during the step (four ahead), the one flushed (two back).
     int tile = first, tile_fetch = tile_at(4, first, n_tiles), tile_flush = tile_at(2 * n_tiles - 2, first, n_tiles);
     for (int s = 0; s < n_tiles; ++s, tile = next_tile(tile, n_tiles), tile_fetch = next_tile(tile_fetch, n_tiles), tile_flush = next_tile(tile_flush, n_tiles))
-        wide_step<kVariant>(R, A, lds0, s, tile, tile_fetch, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, kdoff, wave, lane, vis_min, m_lo,
-                            m_hi, stage, out, variant_stride, accumulate);
+        wide_step<kVariant>(R, A, lds0, s, tile, tile_fetch, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, kdoff, wave, lane, vis_min,
+                            special_s, stage, out, variant_stride, accumulate);
     if (R.pend) {                                              // set B of the last block
         matrix_results_land();
         float bv = 0.f, bk = 0.f, bj = 0.f;
@@ -526,60 +523,292 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     __syncthreads();
     if (n_tiles >= 2) flush_tile<kNv>(stage + ((n_tiles - 2) & 3) * 2 * kNv * 64, out, variant_stride, t_begin + tile_at(n_tiles - 2, first, n_tiles) * kTileTok, t_end, wave, lane, accumulate);
     flush_tile<kNv>(stage + ((n_tiles - 1) & 3) * 2 * kNv * 64, out, variant_stride, t_begin + tile_at(n_tiles - 1, first, n_tiles) * kTileTok, t_end, wave, lane, accumulate);
-    if (!accumulate)
-        for (int t = t_end + threadIdx.x; t < t_stop; t += kThreads)
+    if (!accumulate) zero_padding<kNv>(part, N, out, variant_stride);
+    if (has_special) add_special_pairs<kVariant>(smem, special + (cbase + chunk * 128) * 4, min(128, m_pad - chunk * 128), t_begin, t_end, out, variant_stride);
+}
+
+// ------------------------------------------------------------------------------------
+// The last 64 window rows or fewer of a KV head: every wave by itself
+// ------------------------------------------------------------------------------------
+// With at most 64 rows one wave holds all of them, and the four waves of a workgroup share nothing but the rows: each
+// takes its own 32-token blocks (block 4 g + wave of the range), brings them in with its own transfers through its own
+// ring of two 16 KB slots, and writes finished sums.  No barrier, no staging of partial sums; a block's transfers have a
+// whole step to land.  Bound by the read of K and V: 4 x 8 heads x 32K, 64 rows, joint: 153 us with 32 rows per wave, 98 us
+// here (32 rows: 105 and 97).
+constexpr int kSoloTok = 32;
+constexpr int kSoloSlot = 2 * kBlkBytes;          // 16 KB: a block's K rows, then its V rows
+constexpr int kSoloTransfers = 16;                // direct-to-LDS transfers a wave issues per block (8 K + 8 V)
+
+struct SoloFetch {
+    const char *k_base, *v_base;     // first row of the block in K and in V (uniform)
+    uint32_t voff[8];                // per-lane byte offset of transfer n inside the block (rows past the end clamped)
+    uint32_t lds;                    // LDS byte address of the slot
+};
+__device__ __forceinline__ void solo_fetch_one(const SoloFetch &f, int n) {       // n = 0..7: K, 8..15: V
+    dma16_based(n < 8 ? f.k_base : f.v_base, f.voff[n & 7], f.lds + (n < 8 ? 0 : kBlkBytes) + (n & 7) * 1024);
+}
+__device__ __forceinline__ SoloFetch solo_fetch(const char *kh, const char *vh, int t0, int last_row, uint32_t lds, const uint32_t (&doff)[8], int lane) {
+    SoloFetch f;
+    const int row = min(t0, last_row), rmax = last_row - row;
+    f.k_base = kh + (size_t)row * kRowBytes;
+    f.v_base = vh + (size_t)row * kRowBytes;
+    f.lds = lds;
 #pragma unroll
-            for (int c = 0; c < kNv; ++c) out[c * variant_stride + t] = 0.f;
-    if (has_special) {
-        // Add the separately scored pairs: staged in LDS (the tiles are done with), then summed by one
-        // thread in row order; consecutive rows that share their key (a sink, typically) cost one update.
-        __syncthreads();
-        float4 *staged = (float4 *)smem;
-        if (threadIdx.x < 128) {
-            const int i = chunk * 128 + threadIdx.x;
-            staged[threadIdx.x] = i < m_pad ? ((const float4 *)special)[cbase + i] : make_float4(__int_as_float(-1), 0.f, 0.f, 0.f);
+    for (int n = 0; n < 8; ++n) f.voff[n] = doff[n];
+    if (rmax < kSoloTok - 1) {                                             // uniform, rare: rows past the end re-read the last one
+#pragma unroll
+        for (int n = 0; n < 8; ++n) f.voff[n] -= (uint32_t)(max(4 * n + (lane >> 4) - rmax, 0) * kRowBytes);
+    }
+    return f;
+}
+
+// One block of a wave, in the two phases of pipelined_block: its operands are in registers, the previous block's set B is
+// still due, and the next block lies in slot kNext of the wave's ring from the end of phase 1 on.
+template <int kVariant, int kNext>
+__device__ __forceinline__ void solo_block(WideState &R, const Stationary &A, const SoloFetch &fetch, float *out,
+                                           size_t variant_stride, int tok, int tok_prev, int t_end, int lane, int blk, bool hidden,
+                                           uint32_t special, const int *vis_i, const int *excl_i, bool accumulate) {
+    constexpr bool kDoV = kVariant == OBC_ALL;
+    constexpr bool kDoK = kVariant == OBC_KEY || kVariant == OBC_ALL;
+    constexpr bool kDoJ = kVariant == OBC_JOINT || kVariant == OBC_ALL;
+    const int half = lane >> 5;
+    float vvn = 0.f, bv = 0.f, bk = 0.f, bj = 0.f;
+    const TokenConsts tp = token_consts(R.vv_prev);
+    RowConsts cB[4], cA[4];
+    PairWork pw[16];
+    cB[0] = R.c0;
+    matrix_phase<0>(A, R.zA, R.voA, R.kreg, R.vreg, [&](int j) __attribute__((always_inline)) {
+        if (j % 6 == 0 && j < 18) cB[j / 6 + 1] = row_consts(R.cp, 1, j / 6 + 1);
+        if (j == 18) cA[0] = row_consts(R.cp, 0, 0);
+        if (j < 16) { vvn = sumsq_quarter(R.vreg[j >> 1], j & 1, vvn); stay(vvn); }
+        if (j >= 8) solo_fetch_one(fetch, j - 8);
+#pragma unroll
+        for (int t = 2 * j; t < 2 * j + 2; ++t) {
+            const int r = t / 3;
+            pair_task<kVariant>(t % 3, pw[r], R.zB[r], R.voB[r], m2_of(cB[r >> 2], r & 3), oo_of(cB[r >> 2], r & 3), tp, bv, bk, bj);
         }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int cur = -1;
-            float acc[3] = {0.f, 0.f, 0.f};
-            for (int i = 0; i <= 128; ++i) {
-                const float4 sp = i < 128 ? staged[i] : make_float4(__int_as_float(-2), 0.f, 0.f, 0.f);
-                const int ex = __float_as_int(sp.x);
-                const bool mine = ex >= t_begin && ex < t_end;
-                if (i < 128 && !mine) continue;
-                if (ex != cur) {
-                    if (cur >= 0) {
-                        int c = 0;
-                        if (kVariant == OBC_ALL) out[(c++) * variant_stride + cur] += acc[0];
-                        if (kVariant == OBC_KEY || kVariant == OBC_ALL) out[(c++) * variant_stride + cur] += acc[1];
-                        if (kVariant == OBC_JOINT || kVariant == OBC_ALL) out[(c++) * variant_stride + cur] += acc[2];
-                    }
-                    cur = i < 128 ? ex : -1;
-                    acc[0] = acc[1] = acc[2] = 0.f;
-                }
-                acc[0] += sp.y; acc[1] += sp.z; acc[2] += sp.w;
-            }
+    });
+    // Everything older than the transfers just started: the next block has landed.
+    wait_async_loads_keep<kSoloTransfers>();
+    {
+        float sv = 0.f, sk = 0.f, sj = 0.f;
+        if (kDoV) sv = halves_sum((R.sv + bv) * tp.vv);
+        if (kDoK) sk = fmaxf(halves_sum(R.sk + bk), 0.f);      // (rounding can leave a sum a hair below zero)
+        if (kDoJ) sj = fmaxf(halves_sum(R.sj + bj), 0.f);
+        if (half == 0 && tok_prev < t_end) {
+            float *o = out + tok_prev;
+            auto put = [&](float x) { *o = accumulate ? *o + x : x; o += variant_stride; };
+            if (kDoV) put(sv);
+            if (kDoK) put(sk);
+            if (kDoJ) put(sj);
         }
     }
+    const bool masks = hidden || special_bit(special, blk);
+    if (masks) {                                               // uniform for the wave, rare
+        matrix_results_land();
+        hide_pairs(R.zA, 0, tok, t_end, 0, half, vis_i, excl_i);
+    }
+    const TokenConsts tc = token_consts(halves_sum(vvn));
+    float av = 0.f, ak = 0.f, aj = 0.f;
+    matrix_phase<1>(A, R.zB, R.voB, R.kreg, R.vreg, [&](int j) __attribute__((always_inline)) {
+        if (j % 6 == 0 && j < 18) cA[j / 6 + 1] = row_consts(R.cp, 0, j / 6 + 1);
+        if (j == 18) R.c0 = row_consts(R.cp, 1, 0);
+        if (j < 8) R.kreg[j] = lds_piece(R.kp[j], kNext * kSoloSlot);
+        else if (j & 1) R.vreg[(j - 8) >> 1] = lds_piece(R.kp[(j - 8) >> 1], kNext * kSoloSlot + kBlkBytes);
+#pragma unroll
+        for (int t = 2 * j; t < 2 * j + 2; ++t) {
+            const int r = t / 3;
+            pair_task<kVariant>(t % 3, pw[r], R.zA[r], R.voA[r], m2_of(cA[r >> 2], r & 3), oo_of(cA[r >> 2], r & 3), tc, av, ak, aj);
+        }
+    });
+    if (masks) {
+        matrix_results_land();
+        hide_pairs(R.zB, 1, tok, t_end, 0, half, vis_i, excl_i);
+    }
+    R.sv = av; R.sk = ak; R.sj = aj;
+    R.vv_prev = tc.vv;
+    // The operand reads above have arrived: the next step's transfers may overwrite the slot they came from.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// kVariant: OBC_KEY / OBC_JOINT / OBC_ALL.  Grid: see sweep_part; rows row0 .. row0 + 63 of the head.
+template <int kVariant, typename Lens>
+__global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *__restrict__ q,
+                                                                const uint16_t *__restrict__ k,
+                                                                const uint16_t *__restrict__ v, int N, int W, int Hq,
+                                                                int Hkv, int heads, int ragged, Lens lens, int range_len,
+                                                                int m_pad, int row0, const uint16_t *__restrict__ out_bf16,
+                                                                const float *__restrict__ row_const,
+                                                                const float *__restrict__ special,
+                                                                float *__restrict__ dst, size_t variant_stride,
+                                                                int accumulate_flag) {
+    const bool accumulate = accumulate_flag != 0;
+    constexpr int kNv = kVariant == OBC_ALL ? 3 : 1;
+    // the four waves' rings, then four constants per row
+    __shared__ __attribute__((aligned(1024))) char smem[4 * 2 * kSoloSlot + 256 * sizeof(float)];
+    float *rc_s = (float *)(smem + 4 * 2 * kSoloSlot);         // [64][2] 2 (max + log2 sum) and ||o^||^2 of each row
+    float *vis_s = rc_s + 128;                                 // [64] last visible key of each row
+    float *excl_s = vis_s + 64;                                // [64] key of the row that is scored separately, or -1
+
+    const SweepPart part = sweep_part(lens, ragged, N, Hkv, 1, range_len);
+    const int b = part.b, g = part.g, bg = b * Hkv + g, G = Hq / Hkv, M = G * W, len = part.len;
+    const int t_begin = part.part * range_len;
+    float *out = dst + (size_t)bg * N;
+    const int t_end = min(t_begin + range_len, len);
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const size_t cbase = (size_t)bg * m_pad + row0;
+    const char *kh = (const char *)k + (size_t)bg * N * kRowBytes;
+    const char *vh = (const char *)v + (size_t)bg * N * kRowBytes;
+    const uint32_t lds0 = lds_offset_of(smem), ring = lds0 + wave * 2 * kSoloSlot;
+
+    // The walk: groups of 128 tokens, from this workgroup's own first group around (see tile_at).
+    const int n_groups = (t_end - t_begin + 4 * kSoloTok - 1) / (4 * kSoloTok);
+    int group = (int)((13u * (blockIdx.x + gridDim.x * blockIdx.z)) % (unsigned)n_groups);
+    auto block_of = [&](int grp) { return t_begin + (4 * grp + wave) * kSoloTok; };       // first token of the wave's block
+    uint32_t doff[8];
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+        const int Rn = 4 * n + (lane >> 4);
+        doff[n] = (uint32_t)(Rn * kRowBytes + piece_of(kXor16, Rn, lane & 15) * 16);
+    }
+    // The wave's first block goes to slot 0; the second slots of waves 0, 1 and 2 first stage the stationary operands:
+    // Q, the high and the residual pieces of o_i, one 64-row tile each, brought in by all four waves.
+    {
+        const SoloFetch f = solo_fetch(kh, vh, block_of(group), len - 1, ring, doff, lane);
+#pragma unroll
+        for (int n = 0; n < kSoloTransfers; ++n) solo_fetch_one(f, n);
+    }
+    {
+        uint32_t toff[4];
+        tile_lane_offsets<kXor16>(toff, wave, lane);
+        const char *q_rows = (const char *)q + (((size_t)b * Hq + (size_t)g * G) * W + row0) * kRowBytes;
+        const char *o_rows = (const char *)out_bf16 + cbase * kRowBytes;
+        const size_t lo_plane = (size_t)heads * m_pad * kRowBytes;
+        // (rows past the last one re-read it, and are zeroed below)
+        tile_load_async<kXor16>(q_rows, 0, M - row0 - 1, lds0 + kSoloSlot, wave, lane, toff);
+        tile_load_async<kXor16>(o_rows, 0, M - row0 - 1, lds0 + 3 * kSoloSlot, wave, lane, toff);
+        tile_load_async<kXor16>(o_rows + lo_plane, 0, M - row0 - 1, lds0 + 5 * kSoloSlot, wave, lane, toff);
+    }
+    float4 my_rc = make_float4(1e30f, 0.f, __int_as_float(-1), 0.f);   // rows past the last one (1e30) weigh nothing
+    int my_excl = -1;
+    if (row0 + lane < M) {                                     // (every wave looks at row `lane`, the first one stores)
+        my_rc = ((const float4 *)row_const)[cbase + lane];
+        my_excl = __float_as_int(special[(cbase + lane) * 4]);
+    }
+    int vis_min = row0 + lane < M ? __float_as_int(my_rc.z) : 0x7fffffff;
+    const bool mine_special = my_excl >= t_begin && my_excl < t_end;
+    const bool has_special = __any(mine_special);              // (the same in every wave)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        vis_min = min(vis_min, __shfl_xor(vis_min, off));
+    }
+    vis_min = __builtin_amdgcn_readfirstlane(min(vis_min, t_end - 1));
+    __shared__ uint32_t special_s[kSpecialWords];
+    if (threadIdx.x < 64) {
+        if (lane < kSpecialWords) special_s[lane] = 0;
+        if (mine_special) atomicOr(&special_s[special_word((my_excl - t_begin) >> 5)], 1u << ((my_excl - t_begin) >> 5 & 31));
+        rc_s[2 * lane] = my_rc.x;
+        rc_s[2 * lane + 1] = my_rc.y;
+        vis_s[lane] = my_rc.z;
+        excl_s[lane] = __int_as_float(my_excl);
+    }
+    const int *vis_i = (const int *)vis_s, *excl_i = (const int *)excl_s;
+
+    WideState R;
+    lds_ptr base = (lds_ptr)smem;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) R.kp[kk] = base + wave * 2 * kSoloSlot + row_piece_offset(lane, kk);
+    R.cp = base + 4 * 2 * kSoloSlot + 4 * half * 8;
+    wait_async_loads();
+    __syncthreads();
+    Stationary A;
+#pragma unroll
+    for (int S = 0; S < 2; ++S) {
+        const bool ok = row0 + 32 * S + (lane & 31) < M;
+        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            lds_ptr piece = base + kSoloSlot + S * 32 * kRowBytes + row_piece_offset(lane, kk);
+            const bf16x8 tq = lds_piece(piece, 0), th = lds_piece(piece, 2 * kSoloSlot), tl = lds_piece(piece + 4 * kSoloSlot, 0);
+            A.q[S][kk] = park(ok ? tq : zero);
+            A.hi[S][kk] = park(ok ? th : zero);
+            A.lo[S][kk] = park(ok ? tl : zero);
+        }
+    }
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+        R.kreg[kk] = lds_piece(R.kp[kk], 0);
+        R.vreg[kk] = lds_piece(R.kp[kk], kBlkBytes);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();                                           // every wave has its stationary operands: the slots are free
+    group = next_tile(group, n_groups);
+    {
+        const SoloFetch f = solo_fetch(kh, vh, block_of(group), len - 1, ring + kSoloSlot, doff, lane);
+#pragma unroll
+        for (int n = 0; n < kSoloTransfers; ++n) solo_fetch_one(f, n);
+    }
+    R.zA = zero16(); R.voA = zero16(); R.zB = zero16(); R.voB = zero16();
+    R.sv = R.sk = R.sj = 0.f;
+    R.vv_prev = 0.f;
+    R.c0 = row_consts(R.cp, 1, 0);
+
+    int here = group == 0 ? n_groups - 1 : group - 1;          // the group worked on; `group` is the one after it
+    int tok_prev = 0x7fffffff;
+    auto step = [&](auto slot) __attribute__((always_inline)) {        // slot: of the block worked on
+        const int after = next_tile(group, n_groups), tok0 = block_of(here), blk = 4 * here + wave;
+        const SoloFetch f = solo_fetch(kh, vh, block_of(after), len - 1, ring + slot.value * kSoloSlot, doff, lane);
+        const bool hidden = !(tok0 + 31 <= vis_min);
+        const int tok = tok0 + (lane & 31);
+        solo_block<kVariant, 1 - slot.value>(R, A, f, out, variant_stride, tok, tok_prev, t_end, lane, blk, hidden, special_s[special_word(blk)], vis_i, excl_i, accumulate);
+        tok_prev = tok;
+        here = group;
+        group = after;
+    };
+    for (int s = 0; s < n_groups; s += 2) {
+        step(std::integral_constant<int, 0>{});
+        if (s + 1 == n_groups) break;
+        step(std::integral_constant<int, 1>{});
+    }
+    matrix_results_land();                                     // set B of the last block
+    {
+        float bv = 0.f, bk = 0.f, bj = 0.f;
+        score_set<kVariant>(R.zB, R.voB, R.cp, 1, R.vv_prev, bv, bk, bj);
+        const float sv = halves_sum((R.sv + bv) * R.vv_prev), sk = fmaxf(halves_sum(R.sk + bk), 0.f), sj = fmaxf(halves_sum(R.sj + bj), 0.f);
+        if (half == 0 && tok_prev < t_end) {
+            float *o = out + tok_prev;
+            auto put = [&](float x) { *o = accumulate ? *o + x : x; o += variant_stride; };
+            if (kVariant == OBC_ALL) put(sv);
+            if (kVariant == OBC_KEY || kVariant == OBC_ALL) put(sk);
+            if (kVariant == OBC_JOINT || kVariant == OBC_ALL) put(sj);
+        }
+    }
+    wait_async_loads();        // the blocks fetched past the end must have landed before the LDS is given back
+    if (!accumulate) zero_padding<kNv>(part, N, out, variant_stride);
+    if (has_special) add_special_pairs<kVariant>(smem, special + cbase * 4, min(64, M - row0), t_begin, t_end, out, variant_stride);     // uniform
 }
 
 }  // namespace
 
-bool sweep2_wide_covers(int variant, int m_pad, int M) {
-    if (variant != OBC_KEY && variant != OBC_JOINT && variant != OBC_ALL) return false;
-    return M % 128 == 0 || M % 128 > 64;        // every 128-row chunk at least three quarters full
-}
+bool sweep2_wide_covers(int variant) { return variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL; }
 
 template <int kVariant>
 static hipError_t launch_wide(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, float *dst, size_t plane_elems,
                               size_t chunk_stride, hipStream_t stream) {
-    const dim3 grid((a.N + ws.range_len - 1) / ws.range_len, ws.n_chunks, a.B * a.Hkv);
+    const uint16_t *q = (const uint16_t *)a.q, *k = (const uint16_t *)a.k, *v = (const uint16_t *)a.v, *o = (const uint16_t *)(base + ws.out_bf16);
+    const float *row_const = (const float *)(base + ws.row_const), *special = (const float *)(base + ws.special);
+    const int accumulate = ws.n_chunks == 1 ? a.accumulate : 0, BH = a.B * a.Hkv, full = ws.n_chunks - ws.solo;
     return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) {
-        mfma_sweep2_wide<kVariant><<<grid, dim3(kThreads), 0, stream>>>(
-            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens,
-            ws.range_len, ws.m_pad, (const uint16_t *)(base + ws.out_bf16), (const float *)(base + ws.row_const),
-            (const float *)(base + ws.special), dst, plane_elems, chunk_stride, ws.n_chunks == 1 ? a.accumulate : 0);
+        if (full > 0)
+            mfma_sweep2_wide<kVariant><<<sweep_grid(a, lens, full, ws.range_len), dim3(kThreads), 0, stream>>>(
+                q, k, v, a.N, a.W, a.Hq, a.Hkv, BH, a.ragged, lens, ws.range_len, full, ws.m_pad, o, row_const, special, dst, plane_elems,
+                chunk_stride, accumulate);
+        if (ws.solo)
+            mfma_sweep2_solo<kVariant><<<sweep_grid(a, lens, 1, ws.range_solo), dim3(kThreads), 0, stream>>>(
+                q, k, v, a.N, a.W, a.Hq, a.Hkv, BH, a.ragged, lens, ws.range_solo, ws.m_pad, full * 128, o, row_const, special,
+                dst + full * chunk_stride, plane_elems, accumulate);
         return hipGetLastError();
     });
 }

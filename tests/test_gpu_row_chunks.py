@@ -1,0 +1,59 @@
+"""The matrix-core path where its shares of the work can go wrong, against the oracle.
+
+Row counts that leave the last 128-row chunk with at most 64 rows (its own second sweep) or with more; token counts around
+the 32-token blocks, the 128-token groups and the splits; ragged batches, whose grid holds live workgroups only; heads long
+enough for every form of the combine step; pairs that are scored separately in many blocks.
+"""
+import pytest
+import torch
+
+import oracle
+from paper_2510_07651_amd import binding as obc
+from paper_2510_07651_amd import synth
+
+from parity_util import TOL, run_case, score_error
+
+pytestmark = pytest.mark.gpu
+
+# (G, W, Hkv, N, lens)
+SHAPES = [(1, 9, 2, 127, None), (1, 33, 2, 129, [129, 33]), (1, 64, 1, 4097, None), (5, 13, 2, 1000, [1000, 999, 65]),
+          (3, 43, 1, 2111, [65, 2111]), (4, 40, 2, 3000, None), (3, 64, 1, 8200, None), (7, 64, 1, 1500, [700, 1500]),
+          (1, 48, 1, 12345, None), (1, 20, 1, 25001, [25001, 64]), (2, 64, 1, 40000, None)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "%dx%dx%d_%d" % s[:4])
+@pytest.mark.parametrize("range_len", [0, 64])
+def test_rows_and_shares_match_oracle(shape, range_len, score_path):
+    G, W, Hkv, N, lens = shape
+    score_path("mfma")
+    obc.obc_set_score_tuning(0, range_len)
+    gen = torch.Generator().manual_seed(17)
+    B = len(lens or [N])
+    q, k, v = (torch.randn(B, H, n, 128, generator=gen).to(torch.bfloat16) for H, n in ((G * Hkv, W), (Hkv, N), (Hkv, N)))
+    rows = q.view(B, Hkv, G * W, 128)
+    short = min(lens or [N])
+    k[:, :, 0] = (3 * rows.float().mean(dim=2)).to(torch.bfloat16)
+    for i in range(min(6, short - W)):                     # keys that single rows give nearly all their attention to
+        k[:, :, 1 + i * (short - W) // 7] = 2 * rows[:, :, (11 * i) % (G * W)]
+    ref = oracle.score(q, k, v, seq_lens=lens)
+    for b, n in enumerate(lens or [N]):
+        k[b, :, n:] = float("nan")
+        v[b, :, n:] = float("nan")
+    q, k, v = q.cuda(), k.cuda(), v.cuda()
+    got = obc.obc_score(q, k, v, "all", seq_lens=lens)
+    for i, name in enumerate(("value", "key", "joint")):
+        one = obc.obc_score(q, k, v, name, seq_lens=lens)
+        for s in (got[i], one):
+            err, where = score_error(s.cpu().numpy(), ref[i], max(1, short // 8), lens, TOL["bf16"])
+            assert err <= TOL["bf16"], (name, err, where)
+    run = torch.full_like(got[2], 2.0)
+    obc.obc_score(q, k, v, "joint", seq_lens=lens, scores=run, accumulate=True)
+    joint = obc.obc_score(q, k, v, "joint", seq_lens=lens)
+    for b, n in enumerate(lens or [N]):
+        assert torch.allclose(run[b, :, :n], joint[b, :, :n] + 2.0, rtol=1e-6) and bool((run[b, :, n:] == 2.0).all())
+
+
+@pytest.mark.parametrize("W", [16, 32])
+def test_sinks_and_needles_all_over_a_ragged_batch(W, score_path):
+    run_case(synth.Workload("needles", B=3, Hq=6, Hkv=2, d=128, N=9000, W=W, dtype="bf16", budget=256, seed=77, sinks=4,
+                            outlier_channels=4, needles=64, ragged=(3000, 9000), pad_nan=True))
