@@ -1,22 +1,25 @@
 // Part of score_plain.hip: its logits, weights and scores for more than 32 window rows per KV head.
 //
-// The fp64 matrix cores do 79 TFLOP/s and the fp32 ones 157, the 8-bit integer ones 5000 and the bf16 ones 2500, so the
-// contractions are taken apart into pieces the fast ones multiply exactly.
+// The fp64 matrix cores do 79 TFLOP/s and the fp32 ones 157, the 8-bit integer ones 5000 and the bf16 ones 2500, so
+// contractions whose accuracy allows it are taken apart into pieces the fast ones multiply exactly.
 //
-// Dot products (fixed_logits, fixed_score).  Each row of q, k, v and o is scaled by a power of two to fixed point, 38 bits
-// and a sign relative to the row's largest element (30 for bf16 inputs, whose elements have 8 significant bits), and
-// written as five (four) balanced base-256 digits, |digit| <= 128.  Products of digits are summed exactly in 32-bit
-// integers; pairs of digits beyond the fifth level are left out, and the levels are put together in fp64.  A dot product
-// is off by a few parts in 2^36 of |x|max |y|max before it is rounded to fp32: far below that rounding unless the sum
-// cancels to less than 2^-10 of its terms.  Where it does, in ||v_p - o_i||^2 of a v_p that is nearly o_i, the squares are
-// formed directly (fixed_score's last part).  Fifteen integer ops replace 128 fp64 ones.
+// Logits (blocked_logits) stay in fp64.  Fixed point relative to a row's largest element cannot stand in for it: where a key
+// has a large element that meets a small one of the query, the digits that are left out are those the logit is made of.
+//
+// v_p . o_i (fixed_score).  Each row of v and o is scaled by a power of two to fixed point, 38 bits and a sign relative to
+// the row's largest element (30 for bf16 values, whose elements have 8 significant bits), and written as five (four)
+// balanced base-256 digits, |digit| <= 128.  Products of digits are summed exactly in 32-bit integers; pairs of digits
+// beyond the fifth level are left out, and the levels are put together in fp64.  A dot product is off by a few parts in
+// 2^36 of |v|max |o|max, which is far below the fp32 of the norms it goes into unless those cancel.  Where they do, in
+// ||v_p - o_i||^2 of a v_p that is nearly o_i, the squares are formed directly (fixed_score's last part).
 //
 // P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each (exact), products of pieces down to 2^-18 of the
 // leading one (what is left out is below an fp32 rounding), fp32 accumulation: six bf16 ops (three for bf16 values, where
 // nothing is left out) replace sixteen fp32 ones.
 //
-// What bounds them: the vector ALUs.  Taking an element apart costs about 15 instructions (7 for bf16), paid once per
-// workgroup of up to 128 rows, and putting a dot product together about 12; below 33 rows the fp64 kernels are as fast.
+// What bounds them: the logits the fp64 matrix cores, the rest the vector ALUs.  Taking an element apart costs about 15
+// instructions (7 for bf16), paid once per workgroup of up to 128 rows, and putting a dot product together about 12; below
+// 33 rows the fp64 kernels are as fast.
 // fp32, 32/8 heads, d = 128, 8111 tokens, joint: FIXED_TIMES
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -196,30 +199,6 @@ struct TokenTile {
     }
 };
 
-// ------------------------------------------------------------------------------------
-// Rows of q as digits in memory, and a unit per row.  Four elements per lane; the last block of rows is filled up.
-// ------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void fixed_rows(const T *__restrict__ q, int W, int Hq, int Hkv, Piece w,
-                                                       int8_t *__restrict__ digits, double *__restrict__ units) {
-    constexpr int K = kDigits<T>, kLanes = D / 4;
-    const int row = ((int)blockIdx.x * kThreads + (int)threadIdx.x) / kLanes, c = threadIdx.x % kLanes * 4, hl = blockIdx.z;
-    const int bg = w.bg0 + hl, M = Hq / Hkv * W, blocks = (w.nr + 15) / 16;
-    const T *src = q + ((size_t)(bg / Hkv) * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D + c;
-    float x[4];
-    double xd[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) xd[i] = x[i] = load_as_float(src + i);
-    using Tile = TokenTile<float, D, 64, kFixedThreads>;     // (four elements per lane: its lane layout)
-    const int e = max_exponent(Tile::template over_row<MaxBitsOp>(max_abs(x)));
-    uint32_t p[K];
-    digits_of<K>(xd, e, p);
-    if (row >= blocks * 16) return;
-#pragma unroll
-    for (int k = 0; k < K; ++k) *(uint32_t *)(digits + digit_address<K, D>((size_t)hl * blocks + row / 16, k, row, c)) = p[k];
-    if (c == 0 && row < w.nr) units[(size_t)hl * w.nr + row] = row_unit(e);
-}
-
 // A wave's 16 rows of digits as a matrix operand: lane = row + 16 g holds bytes 16 g .. 16 g + 15 of every 64.
 template <int K, int D>
 struct RowDigits {
@@ -258,70 +237,66 @@ __device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const c
 }
 
 // ------------------------------------------------------------------------------------
-// Logits.  Grid: x = KV head (neighbours run on different XCDs, whose L2 caches then hold the rows, values and logits of
-// few heads), y = token range of the piece, z = chunk of 16 kRb rows.  Wave w takes row block w % kRb and
-// part w / kRb of every tile, 16 tokens at a time; lane = row + 16 g, registers = tokens 4 g .. 4 g + 3.
+// Logits, as plain_logits forms them (fp64 dot products, rounded once), into the blocked layout.  Grid: x = KV head
+// (neighbours run on different XCDs, whose L2 caches then hold the rows, values and logits of few heads), y = token range
+// of the piece, z = chunk of kLogitRows rows.  A wave has 16 tokens of every tile of 64; lane = row + 16 g of every 16 rows,
+// with tokens 4 g .. 4 g + 3, which the lanes' order of loading puts there.
 // ------------------------------------------------------------------------------------
-template <typename T, int D, int kRb, typename Lens>
-__global__ __launch_bounds__(kFixedThreads, 4) void fixed_logits(const int8_t *__restrict__ q_digits, const double *__restrict__ q_units,
-                                                                 const T *__restrict__ k, int N, int W, int Hkv, int ragged, Lens lens,
-                                                                 Piece w, int range_len, int n_ranges, float *__restrict__ z,
-                                                                 float2 *__restrict__ range_best) {
-    constexpr int K = kDigits<T>, kTok = kFixedTile<D>, kPart = kTok / (8 / kRb), kBuf = buffers_of(K * kTok * D);
-    __shared__ __attribute__((aligned(16))) char digits[kBuf][K * kTok * D];
-    __shared__ __attribute__((aligned(16))) double units[2][kTok];
-    __shared__ float2 best_s[8][16];
-    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
+constexpr int kLogitRows = 32;
+template <typename T, int D, typename Lens>
+__global__ __launch_bounds__(kThreads, 4) void blocked_logits(const T *__restrict__ q, const T *__restrict__ k, int N, int W, int Hq,
+                                                              int Hkv, int ragged, Lens lens, Piece w, int range_len, int n_ranges,
+                                                              float *__restrict__ z, float2 *__restrict__ range_best) {
+    constexpr int kRt = kLogitRows / 16;
+    __shared__ __attribute__((aligned(16))) float rows_s[kLogitRows * kStride<D>];
+    __shared__ float2 best_s[4][kLogitRows];
+    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv, M = Hq / Hkv * W;
     const int len = seq_len_of(lens, ragged, b, N);
     const int range = w.s0 / range_len + blockIdx.y;
     const int t_begin = range * range_len, t_end = min(min(t_begin + range_len, w.s1), len);
     if (t_begin >= t_end) return;                            // uniform
+    const int row0 = blockIdx.z * kLogitRows, blocks = (w.nr + 15) / 16;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
-    const int rb = wave % kRb, part = wave / kRb;
-    const int block = (int)blockIdx.z * kRb + rb, blocks = (w.nr + 15) / 16, row = block * 16 + (lane & 15);
-    const bool live = row < w.nr;
-    const __amdgpu_buffer_rsrc_t kg = span_of(k + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
-    TokenTile<T, D, kTok, kFixedThreads> next;
-    next.load(kg, 0);
-    RowDigits<K, D> rows;
-    rows.load(q_digits, hl, block, blocks, lane);
-    const double qu = live ? q_units[(size_t)hl * w.nr + row] * (1.0 / sqrt((double)D)) : 0.0;
-    const int last = live ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;         // last token the row sees here
-    float *zp = z + z_block(w, hl, block, t_begin) + lane * 4;
-    float m = -INFINITY;
-    int at = kNoToken;
-    next.template store_digits<true, 0>(digits[0], units[0], nullptr);
-    if (t_begin + kTok < t_end) next.load(kg, kTok);
-    int slot = 0;
-    for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
-        __syncthreads();                                     // this tile is in LDS, the one before it has been read
-        if (kBuf == 2) {
-            if (t0 + kTok < t_end) next.template store_digits<true, 0>(digits[(slot ^ 1) % kBuf], units[slot ^ 1], nullptr);
-            if (t0 + 2 * kTok < t_end) next.load(kg, t0 - t_begin + 2 * kTok);
-        }
-#pragma unroll 1
-        for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
-            i32x4 acc[kLevels];
-            level_sums<K, K, D, kTok>(rows, digits[slot % kBuf], p0 + (lane & 15), g, acc);
-            const double2 u01 = *(const double2 *)(units[slot] + p0 + 4 * g), u23 = *(const double2 *)(units[slot] + p0 + 4 * g + 2);
-            const double ku[4] = {u01.x, u01.y, u23.x, u23.y};
+    const T *kg = k + (size_t)bg * N * D;
+    const int mine = wave * 16 + 4 * (lane & 3) + (lane >> 2 & 3);       // operand row 4 r + g is token 4 g + r
+    RowRegs<T, D> tok;
+    tok.load(kg, t_begin + mine, t_end, g);
+    {
+        TileRegs<T, D, kLogitRows> qr;
+        qr.load(q + ((size_t)b * Hq * W + (size_t)(bg % Hkv) * M + w.r0) * D, row0, w.nr);
+        qr.store(rows_s);
+    }
+    int last[kRt], at[kRt];
+    float m[kRt];
+    float *zp[kRt];
+#pragma unroll
+    for (int rt = 0; rt < kRt; ++rt) {
+        const int row = row0 + 16 * rt + (lane & 15);
+        last[rt] = row < w.nr ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;     // last token the row sees here
+        m[rt] = -INFINITY;
+        at[rt] = kNoToken;
+        zp[rt] = z + z_block(w, hl, row0 / 16 + rt, t_begin + wave * 16) + lane * 4;
+    }
+    __syncthreads();
+    for (int t0 = t_begin; t0 < t_end; t0 += kTile) {
+        f64x4 acc[kRt];
+#pragma unroll
+        for (int rt = 0; rt < kRt; ++rt) acc[rt] = f64x4{0.0, 0.0, 0.0, 0.0};
+        tile_dots<T, D, kRt, true>(rows_s, tok, lane, acc);
+        if (t0 + kTile < t_end) tok.load(kg, t0 + kTile + mine, t_end, g);
+#pragma unroll
+        for (int rt = 0; rt < kRt; ++rt) {
             float x[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const double dot = join_levels(acc[0][i], acc[1][i], acc[2][i], acc[3][i], acc[4][i]);
-                x[i] = (float)(dot * ku[i] * qu);            // scaled logit
-                const int p = t0 + p0 + 4 * g + i;
-                if (p <= last && x[i] > m) { m = x[i]; at = p; }         // (tokens ascend: strict keeps the lowest)
+            for (int r = 0; r < 4; ++r) {
+                x[r] = (float)(acc[rt][r] * (1.0 / sqrt((double)D)));    // scaled logit: the only rounding
+                const int p = t0 + wave * 16 + 4 * g + r;
+                if (p <= last[rt] && x[r] > m[rt]) { m[rt] = x[r]; at[rt] = p; }     // (tokens ascend: strict keeps the lowest)
             }
-            if (block < blocks) *(float4 *)(zp + (t0 - t_begin + p0) * 16) = make_float4(x[0], x[1], x[2], x[3]);   // (room for whole tiles)
-        }
-        if (kBuf == 1) {
-            __syncthreads();
-            if (t0 + kTok < t_end) next.template store_digits<true, 0>(digits[0], units[slot ^ 1], nullptr);
-            if (t0 + 2 * kTok < t_end) next.load(kg, t0 - t_begin + 2 * kTok);
+            if (row0 / 16 + rt < blocks) *(float4 *)(zp[rt] + (t0 - t_begin) * 16) = make_float4(x[0], x[1], x[2], x[3]);   // (room for whole tiles)
         }
     }
-    auto best_of_pair = [&](auto bit) {
+    auto best_of_pair = [&](float &m, int &at, auto bit) {
         constexpr int kBit = decltype(bit)::value;
         float m0, m1;
         uint32_t a0, a1;
@@ -331,18 +306,22 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_logits(const int8_t *_
         m = second ? m1 : m0;
         at = (int)(second ? a1 : a0);
     };
-    best_of_pair(std::integral_constant<int, 16>());
-    best_of_pair(std::integral_constant<int, 32>());
-    if (g == 0) best_s[wave][lane] = make_float2(m, __int_as_float(at));
-    __syncthreads();
-    if (part == 0 && g == 0 && live) {
-        float2 best = best_s[wave][lane];
 #pragma unroll
-        for (int c = 1; c < 8 / kRb; ++c) {
-            const float2 o = best_s[wave + c * kRb][lane];
+    for (int rt = 0; rt < kRt; ++rt) {
+        best_of_pair(m[rt], at[rt], std::integral_constant<int, 16>());
+        best_of_pair(m[rt], at[rt], std::integral_constant<int, 32>());
+        if (g == 0) best_s[wave][16 * rt + lane] = make_float2(m[rt], __int_as_float(at[rt]));
+    }
+    __syncthreads();
+    const int row = threadIdx.x;
+    if (row < kLogitRows && row0 + row < w.nr) {
+        float2 best = best_s[0][row];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) {
+            const float2 o = best_s[c][row];
             if (o.x > best.x || (o.x == best.x && __float_as_int(o.y) < __float_as_int(best.y))) best = o;
         }
-        range_best[((size_t)hl * w.nr + row) * n_ranges + range] = best;
+        range_best[((size_t)hl * w.nr + row0 + row) * n_ranges + range] = best;
     }
 }
 

@@ -161,7 +161,8 @@ struct RowRegs {
 // fp64 dot products of 16 kRt rows in LDS and this wave's 16 tokens: acc[rt][r] is row 16 rt + 4 r + lane / 16, token
 // lane % 16.  The four k values of a matrix op are components c of the four lane groups' 16-byte pieces: any assignment
 // of elements to k will do as long as both operands use the same, and this one reads 16 bytes at a time.
-template <typename T, int D, int kRt>
+// kTokensDown: the transpose, acc[rt][r] is the token of lane 4 r + lane / 16 (among 16) and row 16 rt + lane % 16.
+template <typename T, int D, int kRt, bool kTokensDown = false>
 __device__ __forceinline__ void tile_dots(const float *rows, const RowRegs<T, D> &tok, int lane, f64x4 (&acc)[kRt]) {
     const float *rp = rows + (lane & 15) * kStride<D> + 4 * (lane >> 4);
     asm volatile("" ::: "memory");                           // (the row operands are not to be kept across calls)
@@ -179,8 +180,11 @@ __device__ __forceinline__ void tile_dots(const float *rows, const RowRegs<T, D>
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int rt = 0; rt < kRt; ++rt)
-                acc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s & 1][rt][c], (double)t[c], acc[rt], 0, 0, 0);
+            for (int rt = 0; rt < kRt; ++rt) {
+                const double x = a[s & 1][rt][c], y = t[c];
+                acc[rt] = kTokensDown ? __builtin_amdgcn_mfma_f64_16x16x4f64(y, x, acc[rt], 0, 0, 0)
+                                      : __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, acc[rt], 0, 0, 0);
+            }
     }
 }
 
@@ -846,9 +850,8 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     float *out = (float *)(base + ws.pl_out);
     float2 *best = (float2 *)(base + ws.pl_best);
     RowRecord *rec = (RowRecord *)(base + ws.pl_records);
-    int8_t *q_digits = (int8_t *)(base + ws.pl_q_digits), *o_digits = (int8_t *)(base + ws.pl_o_digits);
-    double *q_units = (double *)(base + ws.pl_q_units);
-    // More than 32 rows are taken apart into digits; 64 or 128 of them per workgroup.
+    int8_t *o_digits = (int8_t *)(base + ws.pl_o_digits);
+    // More than 32 rows: score_fixed.h, 64 or 128 of them per workgroup.
     constexpr bool fixed = kRt == 4 || kRt == 8;
     constexpr int kRb = kRt == 8 ? 8 : 4;
     const bool need_o = a.variant == OBC_KEY || a.variant == OBC_JOINT || a.variant == OBC_ALL;
@@ -870,20 +873,14 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             auto logits = [&]() {
                 const unsigned ranges = (w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range;
                 if constexpr (fixed)
-                    fixed_logits<T, D, kRb><<<dim3(heads, ranges, row_chunks), dim3(kFixedThreads), 0, stream>>>(
-                        q_digits, q_units, k, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
+                    blocked_logits<T, D><<<dim3(heads, ranges, (w.nr + kLogitRows - 1) / kLogitRows), dim3(kThreads), 0, stream>>>(
+                        q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 else
                     plain_logits<T, D, kRt><<<dim3(ranges, chunks, heads), dim3(kThreads), 0, stream>>>(
                         q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 e = hipGetLastError();
                 return e == hipSuccess;
             };
-            const bool again = mask & OBC_STAGE_SWEEP1 || segs > 1;
-            if (fixed && again) {
-                fixed_rows<T, D><<<dim3(((w.nr + 15) / 16 * 16 * (D / 4) + kThreads - 1) / kThreads, 1, heads), dim3(kThreads), 0, stream>>>(
-                    q, a.W, a.Hq, a.Hkv, w, q_digits, q_units);
-                if ((e = hipGetLastError()) != hipSuccess) return e;
-            }
             if (mask & OBC_STAGE_SWEEP1) {
                 for (int i = 0; i < segs; ++i) {             // every range's maximum first
                     segment(i);
@@ -975,19 +972,19 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv, M = Hq / Hkv * W;
     const bool fixed = M > 32;
-    const long long chunks = (long long)BH * (fixed ? (M + 127) / 128 : (M + 31) / 32), tiles = (N + kTile - 1) / kTile;
-    const long long resident = fixed ? kResident / 2 : kResident;
-    const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, (tiles * chunks + resident - 1) / resident);
+    const long long tiles = (N + kTile - 1) / kTile, logit_chunks = (long long)BH * ((M + 31) / 32);
+    const long long chunks = fixed ? (long long)BH * ((M + 127) / 128) : logit_chunks, resident = fixed ? kResident / 2 : kResident;
+    const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, (tiles * logit_chunks + kResident - 1) / kResident);
     ws->pl_range = (int)(std::min(range_tiles, tiles) * kTile);
     ws->pl_ranges = (N + ws->pl_range - 1) / ws->pl_range;
     const long long splits = std::max<long long>(1, std::min<long long>(std::min<long long>(kMaxSplits, tiles), (resident / 2 + chunks - 1) / chunks));
     ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
     ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
     auto row_bytes = [&]() {                                 // of one row, beside its logits
-        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 14 : 4) + 8 + (size_t)ws->pl_splits * (d + 1) * 4;
+        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 9 : 4) + (size_t)ws->pl_splits * (d + 1) * 4;
     };
     const size_t per_row = row_bytes() + (size_t)align_up(N, kTile) * 4;
-    cap -= 9 * 256;                                          // alignment of the buffers
+    cap -= 7 * 256;                                          // alignment of the buffers
     ws->pl_seg = N;
     ws->pl_rows = M;
     ws->pl_heads = (int)std::min<size_t>(BH, cap / (per_row * align_up(M, 16)));
@@ -1024,11 +1021,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
     take(&ws->pl_best, rows * ws->pl_ranges * sizeof(float2));
     take(&ws->pl_records, rows * sizeof(RowRecord));
     take(&ws->pl_out, rows * d * 4);
-    if (fixed) {
-        take(&ws->pl_o_digits, rows * d * 5);
-        take(&ws->pl_q_digits, rows * d * 5);
-        take(&ws->pl_q_units, rows * 8);
-    }
+    if (fixed) take(&ws->pl_o_digits, rows * d * 5);
     take(&ws->pl_part_l, rows * ws->pl_splits * 4);
     take(&ws->pl_part_o, rows * ws->pl_splits * d * 4);
 }
