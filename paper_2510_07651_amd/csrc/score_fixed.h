@@ -9,9 +9,12 @@
 // v_p . o_i (fixed_score).  Each row of v and o is scaled by a power of two to fixed point, 38 bits and a sign relative to
 // the row's largest element (30 for bf16 values, whose elements have 8 significant bits), and written as five (four)
 // balanced base-256 digits, |digit| <= 128.  Products of digits are summed exactly in 32-bit integers; pairs of digits
-// beyond the fifth level are left out, and the levels are put together in fp64.  A dot product is off by a few parts in
-// 2^36 of |v|max |o|max, which is far below the fp32 of the norms it goes into unless those cancel.  Where they do, in
-// ||v_p - o_i||^2 of a v_p that is nearly o_i, the squares are formed directly (fixed_score's last part).
+// beyond the fifth level are left out, and the levels are put together in fp64.  With 2^E for the product of the powers of
+// two just above the rows' largest elements, the arithmetic in a CPU model is off by 2^-35 2^E (rms, 2^-33 at most over
+// millions of pairs: normal elements, channels larger than the others by up to 2^26, elements over 20 binades; there bf16
+// values, which keep fewer bits, reach 2^-30).  The norms it goes into are as good as an fp32 rounding where they are above
+// 2^-4 2^E; where a pair that counts has a smaller one (a v_p that is nearly o_i), the wave forms its 16 x 16 dot products
+// again in fp64 (fixed_score's loop), from where on they are what plain_score computes.
 //
 // P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each (exact), products of pieces down to 2^-18 of the
 // leading one (what is left out is below an fp32 rounding), fp32 accumulation: six bf16 ops (three for bf16 values, where
@@ -530,6 +533,29 @@ __global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__re
     }
 }
 
+// fp64 dot products of 16 tokens and 16 rows from memory: lane = row + 16 g, dot[r] that of token 4 g + r.  `tok`: the
+// lane's token, 4 (lane % 4) + lane / 4 % 4 of the 16; `row`: row lane % 16.
+template <typename T, int D>
+__device__ __forceinline__ void block_dots(const T *__restrict__ tok, const float *__restrict__ row, int g, double (&dot)[4]) {
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int s = 0; s < D / 16; ++s) {
+        const T *t = tok + 16 * s + 4 * g;
+        f32x4 x;
+        if constexpr (sizeof(T) == 4) {
+            x = *(const f32x4 *)t;
+        } else {
+            const uint2 h = *(const uint2 *)t;
+            x = f32x4{__uint_as_float(h.x << 16), __uint_as_float(h.x & 0xffff0000u), __uint_as_float(h.y << 16), __uint_as_float(h.y & 0xffff0000u)};
+        }
+        const f32x4 y = *(const f32x4 *)(row + 16 * s + 4 * g);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[c], (double)y[c], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) dot[r] = acc[r];
+}
+
 // ------------------------------------------------------------------------------------
 // Scores of every variant.  Grid: x = KV head, y = `n_tiles` tiles of the piece.  Lane = row + 16 g, registers =
 // tokens 4 g .. 4 g + 3 of the 16 at hand.  A workgroup takes its tokens against one chunk of rows after the other.
@@ -541,6 +567,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
                                                                 const RowRecord *__restrict__ records, const float *__restrict__ o,
                                                                 const int8_t *__restrict__ o_digits, float *__restrict__ scores,
                                                                 size_t variant_stride, int add) {
+#pragma clang fp contract(off)                               // (a score has the same bits alone and among all three)
     constexpr int K = kDigits<T>, kTok = kFixedTile<D>, kPart = kTok / (8 / kRb), kRows = 16 * kRb;
     constexpr bool kAttnLike = kVariant == OBC_ATTN || kVariant == OBC_VATP;
     constexpr bool kDoV = kVariant == OBC_ALL || kVariant == OBC_VALUE || kAttnLike, kDoK = kVariant == OBC_ALL || kVariant == OBC_KEY,
@@ -552,12 +579,10 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
     __shared__ __attribute__((aligned(16))) RowRecord rec_s[kRows];
     __shared__ __attribute__((aligned(16))) float sum_s[kSums][kRb][kTok];
     __shared__ float run_s[kSums][kScoreTokens];             // sums over the chunks so far
-    __shared__ uint32_t close_s[kScoreTokens / 32];          // tokens with a value next to an output, scored below
-    __shared__ float close_sum_s[2][8];
     const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
     const int t_begin = w.s0 + blockIdx.y * n_tiles * kTok, t_stop = min(t_begin + n_tiles * kTok, w.s1), t_end = min(t_stop, len);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;   // (a scalar: registers)
     const int rb = wave % kRb, part = wave / kRb;
     float *out = scores + (size_t)bg * N;
     if (!add)
@@ -566,7 +591,6 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
             for (int c = 0; c < kSums; ++c) out[c * variant_stride + t] = 0.f;
     if (t_begin >= t_end) return;                            // uniform
     const __amdgpu_buffer_rsrc_t vg = span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
-    if ((int)threadIdx.x < kScoreTokens / 32) close_s[threadIdx.x] = 0u;         // (two barriers before the first use)
     const int blocks = (w.nr + 15) / 16;
     for (int row0 = 0; row0 < w.nr; row0 += kRows) {
         TokenTile<T, D, kTok, kFixedThreads> next;
@@ -575,7 +599,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
         RowDigits<kRowDigits, D> rows;
         if (kNeedO) rows.load(o_digits, hl, block, blocks, lane);
         const __amdgpu_buffer_rsrc_t zg = span_of(z + z_block(w, hl, 0, t_begin), z_block(w, 1, 0, w.s0) * 4);
-        const int z_at = (int)(z_block(w, 0, block, w.s0) * 4) + lane * 16;
+        const int z_at = (int)(z_block(w, 0, block, w.s0) * 4);
         __syncthreads();                                     // (the chunk before this one is done with)
         int i = threadIdx.x;
         asm volatile("" : "+v"(i));                          // (addresses anew for every chunk: registers)
@@ -597,43 +621,57 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
             if (kBuf == 2) advance();
 #pragma unroll 1
             for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
-                const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(zg, z_at, (t0 - t_begin + p0) * 64, 0);    // (room for whole tiles)
+                int l = lane;
+                asm volatile("" : "+v"(l));                  // (addresses anew: registers)
+                const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(zg, l * 16, z_at + (t0 - t_begin + p0) * 64, 0);    // (room for whole tiles)
                 const float x[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
-                i32x4 acc[kLevels];
-                if (kNeedO) level_sums<kRowDigits, K, D, kTok>(rows, digits[slot % kBuf], p0 + (lane & 15), g, acc);
-                __builtin_amdgcn_sched_barrier(0);           // (the row's record only now: registers)
-                const RowRecord rec = rec_s[rb * 16 + (lane & 15)];
-                const float near_oo = (float)rec.oo * 0x1p-22f;
-                const double row_unit2 = -2.0 * rec.unit;
-                float acc_v[4], acc_k[4], acc_j[4];
-                uint32_t close = 0u;
+                double vo[4];                                // v_p . o_i
+                if (kNeedO) {
+                    i32x4 acc[kLevels];
+                    level_sums<kRowDigits, K, D, kTok>(rows, digits[slot % kBuf], p0 + (l & 15), l >> 4, acc);
+                    __builtin_amdgcn_sched_barrier(0);       // (the row's record only now: registers)
+                    const double unit = rec_s[rb * 16 + (l & 15)].unit;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    const int tok = p0 + 4 * g + r, p = t0 + tok;
-                    const float a = p <= rec.last ? exp_nonpositive(x[r] - rec.m) * rec.inv_l : 0.f;
-                    const float a2 = a * a;
-                    acc_v[r] = kAttnLike ? a : a2;
-                    if (!kNeedO) continue;
-                    const double vv = norm_s[slot][tok], vo2 = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
-                    const double d2 = fma(vo2 * row_unit2, units[slot][tok], vv + rec.oo);          // ||v_p - o_i||^2
-                    const bool is_top = p == rec.top;
-                    close |= (float)d2 < near_oo && !is_top ? 1u << r : 0u;
-                    if (kDoK) acc_k[r] = a2 * x[r] * x[r] * (is_top ? rec.top_dk : fmaxf((float)d2, 0.f));
-                    if (kDoJ) {
-                        const double zd = x[r];              // ||v_p + Z (v_p - o_i)||^2 with 2 (v_p - o_i).v_p = d2 + vv - oo
-                        const double dj = fma(zd, fma(zd, d2, d2 + (vv - rec.oo)), vv);
-                        acc_j[r] = a2 * (is_top ? rec.top_dj : fmaxf((float)dj, 0.f));
-                    }
+                    for (int r = 0; r < 4; ++r)
+                        vo[r] = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]) * (units[slot][p0 + 4 * (l >> 4) + r] * unit);
                 }
-                // v_p within 2^-11 of an o_i: the expanded square has lost too much
-                if (kNeedO && close != 0u) atomicOr(close_s + ((t0 + p0 - t_begin) >> 5), close << (((t0 + p0 - t_begin) & 31) + 4 * g));
+                float acc_v[4], acc_k[4], acc_j[4];
+                for (bool again = false;; again = true) {
+                    bool close = false;                      // a norm is too small for the digits' error
+                    const RowRecord rec = rec_s[rb * 16 + (l & 15)];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        const int tok = p0 + 4 * (l >> 4) + r, p = t0 + tok;
+                        const float a = p <= rec.last ? exp_nonpositive(x[r] - rec.m) * rec.inv_l : 0.f;
+                        const float a2 = a * a;
+                        acc_v[r] = kAttnLike ? a : a2;
+                        if (!kNeedO) continue;
+                        const bool is_top = p == rec.top, counts = a2 != 0.f && !is_top;
+                        const double vv = norm_s[slot][tok], d2 = fma(-2.0, vo[r], vv + rec.oo);    // ||v_p - o_i||^2
+                        const float least = (float)(units[slot][tok] * rec.unit) * 0x1p32f;         // 2^-4 2^E
+                        if (kDoK) {
+                            acc_k[r] = a2 * x[r] * x[r] * (is_top ? rec.top_dk : fmaxf((float)d2, 0.f));
+                            close |= counts && (float)d2 < least;
+                        }
+                        if (kDoJ) {
+                            const double zd = x[r];          // ||v_p + Z (v_p - o_i)||^2 with 2 (v_p - o_i).v_p = d2 + vv - oo
+                            const double dj = fma(zd, fma(zd, d2, d2 + (vv - rec.oo)), vv);
+                            acc_j[r] = a2 * (is_top ? rec.top_dj : fmaxf((float)dj, 0.f));
+                            close |= counts && (float)dj < least * fabsf(fmaf(x[r], x[r], x[r]));   // (its share of d2's error)
+                        }
+                    }
+                    if (!kNeedO || again || __ballot(close) == 0ull) break;      // uniform
+                    asm volatile("" : "+v"(l));              // (and here)
+                    block_dots<T, D>(v + ((size_t)bg * N + min(t0 + p0 + 4 * (l & 3) + (l >> 2 & 3), t_end - 1)) * D,
+                                     o + ((size_t)hl * w.nr + min(block * 16 + (l & 15), w.nr - 1)) * D, l >> 4, vo);
+                }
                 // over the 16 rows; the other row blocks held others
                 int n = 0;
                 auto put = [&](float (&s)[4]) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) s[r] = row16_reduce<SumOp>(s[r]);
-                    if ((lane & 15) == 0) *(float4 *)(&sum_s[n][rb][p0 + 4 * g]) = make_float4(s[0], s[1], s[2], s[3]);
+                    if ((l & 15) == 0) *(float4 *)(&sum_s[n][rb][p0 + 4 * (l >> 4)]) = make_float4(s[0], s[1], s[2], s[3]);
                     ++n;
                 };
                 if (kDoV) put(acc_v);
@@ -651,7 +689,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
                 if (kDoV && kNeedV && c == 0) s *= (float)norm_s[slot][tok_l];
                 if (row0 > 0) s += run_s[c][p - t_begin];
                 if (row0 + kRows < w.nr) run_s[c][p - t_begin] = s;
-                else if (p < t_end && !((kDoV && c == 0) ? 0u : close_s[(p - t_begin) >> 5] >> ((p - t_begin) & 31) & 1u)) {
+                else if (p < t_end) {
                     float *d = out + c * variant_stride + p;
                     *d = add ? *d + s : s;
                 }
@@ -659,44 +697,4 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
             if (kBuf == 1) advance();
         }
     }
-    if (!kNeedO) return;
-    // The squares of the tokens set aside, formed directly from fp32 v and o: a wave per row, elements over its lanes.
-    __syncthreads();
-    for (int i = 0; i < kScoreTokens / 32; ++i)
-        for (uint32_t bits = close_s[i]; bits != 0u; bits &= bits - 1u) {
-            const int p = t_begin + i * 32 + __builtin_ctz(bits);
-            if (p >= t_end) break;                           // uniform
-            constexpr int kE = D / 64;
-            float x[kE], acc_k = 0.f, acc_j = 0.f;
-#pragma unroll
-            for (int e = 0; e < kE; ++e) x[e] = load_as_float(v + ((size_t)bg * N + p) * D + lane * kE + e);
-            for (int row0 = wave; row0 < w.nr; row0 += 32)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {                // (four rows' loads in flight)
-                    const int row = row0 + 8 * u;
-                    const size_t at = (size_t)hl * w.nr + min(row, w.nr - 1);
-                    const RowRecord rec = records[at];
-                    const float zr = z[z_block(w, hl, min(row, w.nr - 1) / 16, p) + ((p - w.s0) % 16 / 4 * 16 + min(row, w.nr - 1) % 16) * 4 + p % 4];
-                    const float a = row < w.nr && p <= rec.last ? exp_nonpositive(zr - rec.m) * rec.inv_l : 0.f, a2 = a * a;
-                    float d2 = 0.f, dj = 0.f;
-#pragma unroll
-                    for (int e = 0; e < kE; ++e) {
-                        const float diff = x[e] - o[at * D + lane * kE + e], comb = fmaf(zr, diff, x[e]);
-                        d2 = fmaf(diff, diff, d2);
-                        dj = fmaf(comb, comb, dj);
-                    }
-                    acc_k = fmaf(a2 * zr * zr, p == rec.top ? rec.top_dk : wave_reduce<SumOp>(d2), acc_k);
-                    acc_j = fmaf(a2, p == rec.top ? rec.top_dj : wave_reduce<SumOp>(dj), acc_j);
-                }
-            if (lane == 0) { close_sum_s[0][wave] = acc_k; close_sum_s[1][wave] = acc_j; }
-            __syncthreads();
-            if ((int)threadIdx.x < 2 && (threadIdx.x == 0 ? kDoK : kDoJ)) {
-                float s = 0.f;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) s += close_sum_s[threadIdx.x][c];
-                float *d = out + (kVariant == OBC_ALL ? 1 + threadIdx.x : 0) * variant_stride + p;
-                *d = add ? *d + s : s;
-            }
-            __syncthreads();
-        }
 }

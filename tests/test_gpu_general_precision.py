@@ -1,6 +1,7 @@
 """The general scoring path on inputs whose elements span many binades, against the oracle.
 
-A logit is a sum of products; nothing may be lost of it that its terms hold, whatever else the rows contain.
+A logit is a sum of products; nothing may be lost of it that its terms hold, whatever else the rows contain.  The same
+goes for the squared distance of a value from a row's output, also where most of both is common to them.
 """
 import pytest
 import torch
@@ -47,3 +48,32 @@ def test_large_key_channel_meets_small_query_channel(shape, binades):
     k[..., 3:5] *= 2.0 ** binades
     q[..., 3:5] *= 2.0 ** -binades
     _check(shape, q, k, v)
+
+
+# How the values of a head resemble each other, and with them the outputs.  Distances stay above 2^-6 of the norm: an output
+# is a sum in fp32 (some 4 roundings of 2^-24), which moves a squared distance by 2 * 4 * 2^-24 / (2^-6 sqrt(d)), 4e-6.
+VALUES = {
+    # one channel is the same for all: the distance lies in the others
+    "common_channel_2^8": lambda v: _set_channel(v, 2.0 ** 8),
+    "common_channel_2^14": lambda v: _set_channel(v, 2.0 ** 14),
+    "common_channel_2^16": lambda v: _set_channel(v, 2.0 ** 16),
+    # nearly the same row everywhere
+    "nearly_repeated": lambda v: v[:, :, :1] + v * 2.0 ** -4,
+    # the same row exactly, but for every eighth token
+    "repeated": lambda v: torch.where((torch.arange(v.shape[2]) % 8 == 5)[:, None], v, v[:, :, :1]),
+    # multiples of one row: (1 + Z) v cancels Z o for some pairs
+    "parallel": lambda v: v[:, :, :1] * (1 + v[..., :1]) + v * 2.0 ** -4,
+}
+
+
+def _set_channel(v, x):
+    v = v.clone()
+    v[..., 7] = x
+    return v
+
+
+@pytest.mark.parametrize("values", VALUES)
+@pytest.mark.parametrize("shape", SHAPES, ids=IDS)
+def test_values_close_to_the_outputs(shape, values):
+    q, k, v = _random(shape, 72)
+    _check(shape, q, k, VALUES[values](v))
