@@ -16,9 +16,8 @@
 // 2^-4 2^E; where a pair that counts has a smaller one (a v_p that is nearly o_i), the wave forms its 16 x 16 dot products
 // again in fp64 (fixed_score's loop), from where on they are what plain_score computes.
 //
-// P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each (exact), products of pieces down to 2^-18 of the
-// leading one (what is left out is below an fp32 rounding), fp32 accumulation: six bf16 ops (three for bf16 values, where
-// nothing is left out) replace sixteen fp32 ones.
+// P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each (exact), all nine products (each exact), fp32
+// accumulation: per 32 tokens nine bf16 ops (three for bf16 values) of 16 cycles replace eight fp32 ones of 32.
 //
 // What bounds them: the logits the fp64 matrix cores, the rest the vector ALUs.  Taking an element apart costs about 15
 // instructions (7 for bf16), paid once per workgroup of up to 128 rows, and putting a dot product together about 12; below
@@ -496,7 +495,7 @@ __global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__re
                         a.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(
                             values + slot % kBuf * kTileBytes + value_offset<D, kTok>(k, tok_l + 32 * s + 16 * h, 2 * d + c_l) + byte_l));
 #pragma unroll
-                    for (int j = 0; j + k < 3; ++j)
+                    for (int j = 0; j < 3; ++j)
                         acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, p[s][j].v, acc[d], 0, 0, 0);
                 }
         if (kBuf == 1) {
