@@ -581,7 +581,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
     const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
     const int len = seq_len_of(lens, ragged, b, N);
     const int t_begin = w.s0 + blockIdx.y * n_tiles * kTok, t_stop = min(t_begin + n_tiles * kTok, w.s1), t_end = min(t_stop, len);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4;   // (a scalar: registers)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;    // (a scalar: registers)
     const int rb = wave % kRb, part = wave / kRb;
     float *out = scores + (size_t)bg * N;
     if (!add)

@@ -67,8 +67,10 @@ template <> __device__ __forceinline__ float load_as_float<float>(const float *p
 template <> __device__ __forceinline__ float load_as_float<uint16_t>(const uint16_t *p) { return bf16_bits_to_float(*p); }
 
 // exp(x) for x <= 0.  The product x log2(e) is carried as a pair, so that the argument of exp2 keeps full fp32 accuracy
-// however large |x| is: exp(x) = 2^t (1 + ln2 r) with t + r = x log2(e).  Results below 2^-126 become 0.
+// however large |x| is: exp(x) = 2^t (1 + ln2 r) with t + r = x log2(e).  Results below 2^-126 become 0, also that of
+// -inf and of an x whose pair would not be finite; not a number stays that.
 __device__ __forceinline__ float exp_nonpositive(float x) {
+    x = __builtin_elementwise_maximum(x, -200.f);
     const float log2e = 1.44269504f, log2e_rest = 1.925963033500e-8f;      // log2(e) = 1.44269504 (as fp32) + the rest
     const float t = x * log2e;
     const float r = fmaf(x, log2e_rest, fmaf(x, log2e, -t));

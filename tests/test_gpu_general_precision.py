@@ -77,3 +77,20 @@ def _set_channel(v, x):
 def test_values_close_to_the_outputs(shape, values):
     q, k, v = _random(shape, 72)
     _check(shape, q, k, VALUES[values](v))
+
+
+@pytest.mark.parametrize("shape", SHAPES + [("fp32", 64, 1, 4, 3000)], ids=IDS + ["fp32_d64_1x4_3000"])
+def test_logits_at_the_end_of_fp32_have_weight_zero(shape):
+    """One key's logit is -3.1e38, another's overflows to -infinity: both have weight 0, and nothing else changes."""
+    q, k, v = _random(shape, 73)
+    dt = torch.float32 if shape[0] == "fp32" else torch.bfloat16
+    q[..., 0], k[..., 0] = 2.0 ** 63, 0.0
+    k[:, :, 5, 0] = -3.1e38 * shape[1] ** 0.5 / 2.0 ** 63
+    k[:, :, 11, 0] = -1e39 * shape[1] ** 0.5 / 2.0 ** 63
+    q, k, v = (x.to(dt) for x in (q, k, v))
+    want = {"value": oracle.score(q, k, v)[0], "attn": oracle.attn_score(q, k, v), "vatp": oracle.vatp_score(q, k, v)}
+    for variant, ref in want.items():
+        got = obc.obc_score(q.cuda(), k.cuda(), v.cuda(), variant).cpu().numpy()
+        assert (got[:, :, [5, 11]] == 0).all(), variant
+        err, where = score_error(got, ref, shape[4] // 8, None, TOL["fp32"])
+        assert err <= TOL["fp32"], (variant, err, where)
