@@ -650,13 +650,13 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
                         const double vv = norm_s[slot][tok], d2 = fma(-2.0, vo[r], vv + rec.oo);    // ||v_p - o_i||^2
                         const float least = (float)(units[slot][tok] * rec.unit) * 0x1p32f;         // 2^-4 2^E
                         if (kDoK) {
-                            acc_k[r] = a2 * x[r] * x[r] * (is_top ? rec.top_dk : fmaxf((float)d2, 0.f));
+                            acc_k[r] = a2 * x[r] * x[r] * (is_top ? rec.top_dk : at_least_0((float)d2));
                             close |= counts && (float)d2 < least;
                         }
                         if (kDoJ) {
                             const double zd = x[r];          // ||v_p + Z (v_p - o_i)||^2 with 2 (v_p - o_i).v_p = d2 + vv - oo
                             const double dj = fma(zd, fma(zd, d2, d2 + (vv - rec.oo)), vv);
-                            acc_j[r] = a2 * (is_top ? rec.top_dj : fmaxf((float)dj, 0.f));
+                            acc_j[r] = a2 * (is_top ? rec.top_dj : at_least_0((float)dj));
                             close |= counts && (float)dj < least * fabsf(fmaf(x[r], x[r], x[r]));   // (its share of d2's error)
                         }
                     }

@@ -78,13 +78,8 @@ __device__ __forceinline__ float exp_nonpositive(float x) {
     return fmaf(e, r * 0.693147181f, e);
 }
 
-// Fixed-order tree sum over the 64 lanes.
-template <typename F>
-__device__ __forceinline__ F wave_sum(F x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
+// A norm that rounding has taken below 0 is 0; not a number stays that (fmaxf would make a 0 of it).
+__device__ __forceinline__ float at_least_0(float x) { return __builtin_elementwise_maximum(x, 0.f); }
 
 // (max, lowest token attaining it) merged across the lanes whose index differs in the bits of `below`.
 template <int kLanes>
@@ -774,10 +769,10 @@ __global__ __launch_bounds__(kThreads, kShort ? 2 : 4) void plain_score(const T 
                         const double d2 = (vv + r.oo) - 2.0 * vo;                        // ||v_p - o_i||^2
                         const bool is_top = p == r.top;
                         if (kVariant != OBC_JOINT)
-                            acc_k = fmaf(a2 * x[i] * x[i], is_top ? r.top_dk : fmaxf((float)d2, 0.f), acc_k);
+                            acc_k = fmaf(a2 * x[i] * x[i], is_top ? r.top_dk : at_least_0((float)d2), acc_k);
                         if (kVariant != OBC_KEY) {
                             const double dj = vv + zd * (2.0 * (vv - vo) + zd * d2);     // ||v_p + Z (v_p - o_i)||^2
-                            acc_j = fmaf(a2, is_top ? r.top_dj : fmaxf((float)dj, 0.f), acc_j);
+                            acc_j = fmaf(a2, is_top ? r.top_dj : at_least_0((float)dj), acc_j);
                         }
                     }
                 }

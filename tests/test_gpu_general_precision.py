@@ -94,3 +94,14 @@ def test_logits_at_the_end_of_fp32_have_weight_zero(shape):
         assert (got[:, :, [5, 11]] == 0).all(), variant
         err, where = score_error(got, ref, shape[4] // 8, None, TOL["fp32"])
         assert err <= TOL["fp32"], (variant, err, where)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=IDS)
+def test_a_value_that_is_not_a_number_shows(shape):
+    """It is part of every row's output, and with that of every key and joint score of its head; other heads are left alone."""
+    q, k, v = _random(shape, 74)
+    dt = torch.float32 if shape[0] == "fp32" else torch.bfloat16
+    v[:, 1, 17, 3] = float("nan")
+    for variant in ("key", "joint"):
+        got = obc.obc_score(*(x.to(dt).cuda() for x in (q, k, v)), variant)
+        assert bool(got[:, 1].isnan().all()) and bool(got[:, 0].isfinite().all()), variant
