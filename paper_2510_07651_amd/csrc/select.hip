@@ -571,21 +571,24 @@ struct Slices {
 
 constexpr int kMaxGroupSlices = 1024;    // of a group whose bookkeeping fits LDS; larger ones (that many heads) read it where it lies
 
-// Where a workgroup of the sliced kernels works: blockIdx.x = slice of the group, blockIdx.y = group.
+// Where a workgroup of the sliced kernels works: the groups' slices one after the other along the grid's x (either count may
+// exceed what y takes).
 struct SlicePlace {
+    int slices;                              // of a group
     int slice, group, head, in_head;         // head: of all groups
     int c0, c1, len;                         // chunks of the head, its true length
     template <typename Lens>
     __device__ __forceinline__ SlicePlace(const Slices &S, int N, int Hkv, int ragged, const Lens &lens) {
-        slice = blockIdx.x;
-        group = blockIdx.y;
+        slices = S.heads * S.per_head;
+        group = (int)(blockIdx.x / (uint32_t)slices);
+        slice = (int)(blockIdx.x % (uint32_t)slices);
         head = group * S.heads + slice / S.per_head;
         in_head = slice % S.per_head;
         len = seq_len_of(lens, ragged, head / Hkv, N);
         c0 = in_head * S.chunks;
         c1 = min(c0 + S.chunks, (len + kChunk - 1) / kChunk);
     }
-    __device__ __forceinline__ size_t flat() const { return (size_t)group * gridDim.x + slice; }
+    __device__ __forceinline__ size_t flat() const { return blockIdx.x; }
 };
 
 // The slice's keys, kBatch chunks at a time: f(keys, first chunk).  From the scores, or from S.keys once those hold them.
@@ -650,7 +653,7 @@ __global__ __launch_bounds__(kSelThreads) void slices_collect(const float *__res
     if (tid == 0) { n_list = 0; n_above = 0; }
     // Sum of the group's histograms: four counters per thread, even slices by one half of the workgroup, odd ones by the other.
     constexpr int kAhead = 16;                               // slices of a half in flight at once
-    const int half = tid / (kSliceBins / 4), bin = tid % (kSliceBins / 4) * 4, n = gridDim.x;
+    const int half = tid / (kSliceBins / 4), bin = tid % (kSliceBins / 4) * 4, n = at.slices;
     const int *src = S.hist + (size_t)at.group * n * kSliceBins + bin;
     int4 h[kAhead];
     auto fetch = [&](int s0) {
@@ -731,13 +734,13 @@ struct SliceAhead {
     int count;               // of the slice with this thread's index
     __device__ __forceinline__ SliceAhead(const Slices &S, const SlicePlace &at) {
         state = S.state[at.group];
-        count = (int)gridDim.x <= kMaxGroupSlices && threadIdx.x < gridDim.x ? S.count[(size_t)at.group * gridDim.x + threadIdx.x] : 0;
+        count = at.slices <= kMaxGroupSlices && (int)threadIdx.x < at.slices ? S.count[(size_t)at.group * at.slices + threadIdx.x] : 0;
     }
 };
 
 __device__ __forceinline__ SliceThreshold slice_threshold(SliceShared &sh, const Slices &S, const SlicePlace &at, const SliceAhead &ahead) {
     using D = Digits<kSliceBits>;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = gridDim.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = at.slices;
     const int head0 = at.slice - at.in_head, head1 = head0 + S.per_head;       // the head's slices
     const SliceState st = ahead.state;
     clear_counters<D::kBins1>(sh.hist1);
@@ -972,7 +975,7 @@ static hipError_t launch_select_sliced(const float *scores, int budget, int32_t 
     Slices S;
     plan_slices(&S, (char *)workspace, B * Hkv, 1, N, true);
     if (radius == 0) S.keys = nullptr;       // (scores are as quick to turn into keys as keys are to read)
-    const dim3 grid(S.per_head, B * Hkv), block(kSelThreads);
+    const dim3 grid((unsigned)S.per_head * B * Hkv), block(kSelThreads);
     return with_lens(ragged, B, lens, [&](const auto &few) {
         return with_batch(S, [&](auto batch) {
             constexpr int kBatch = decltype(batch)::value;
@@ -1010,17 +1013,17 @@ hipError_t launch_select_adaptive(const float *scores, int budget, int n_safe, i
                                   void *workspace, hipStream_t stream) {
     Slices safe, all;
     plan_adaptive(&safe, &all, (char *)workspace, B, Hkv, N);
-    const dim3 by_head(all.per_head, B * Hkv), by_sequence(all.per_head * Hkv, B), block(kSelThreads);
+    const dim3 grid((unsigned)all.per_head * B * Hkv), block(kSelThreads);
     return with_lens(ragged, B, lens, [&](const auto &few) {
         return with_batch(all, [&](auto batch) {
             constexpr int kBatch = decltype(batch)::value;
             if (n_safe > 0) {
-                slices_count<kBatch><<<by_head, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, safe);
-                slices_collect<kBatch><<<by_head, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, 0, 0, 0, safe);
+                slices_count<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, safe);
+                slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, 0, 0, 0, safe);
             }
-            slices_safeguard<kBatch><<<by_head, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, safe, all.keys, all.hist);
-            slices_collect<kBatch><<<by_sequence, block, 0, stream>>>(scores, N, Hkv * budget, Hkv, ragged, few, 0, 0, 0, all);
-            slices_emit<kBatch><<<by_sequence, block, 0, stream>>>(scores, N, cap, Hkv, ragged, few, 0, 0, 0, all, keep_idx, counts);
+            slices_safeguard<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, safe, all.keys, all.hist);
+            slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv * budget, Hkv, ragged, few, 0, 0, 0, all);
+            slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, cap, Hkv, ragged, few, 0, 0, 0, all, keep_idx, counts);
             return hipGetLastError();
         });
     });

@@ -120,3 +120,15 @@ def test_random_select_adaptive(seed):
     np.testing.assert_array_equal(got_idx.cpu().numpy(), want_idx, err_msg=label)
     if N <= 9000:
         _check_inplace(rng, want_idx, N)
+
+
+@pytest.mark.parametrize("B, Hkv", [(4400, 15), (65540, 1), (1, 65540)])
+def test_adaptive_over_more_heads_than_a_grid_dimension_takes(B, Hkv):
+    """Beyond 65535 heads in all, sequences, or heads of one sequence."""
+    rng = np.random.default_rng(5)
+    N, budget, n_safe = 9, 3, 1
+    s = rng.standard_normal((B, Hkv, N)).astype(np.float32)
+    want_idx, want_cnt = oracle.select_adaptive(s, budget, n_safe)
+    got_idx, got_cnt = obc.obc_select_adaptive(torch.from_numpy(s).cuda(), budget, n_safe)
+    np.testing.assert_array_equal(got_cnt.cpu().numpy(), want_cnt)
+    np.testing.assert_array_equal(got_idx.cpu().numpy(), want_idx)
