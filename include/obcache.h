@@ -40,7 +40,9 @@
  *   - obc_score picks its kernels from the shapes: bf16 with head_dim 128 runs on the matrix
  *     cores; a one-row window (W = 1, the decoding case) over a bf16 cache of up to ~1e5
  *     head-tokens runs on kernels shaped for memory round trips; everything else (fp32,
- *     bf16 with head_dim 64 and W > 1) on general kernels (fp64 logits and cross terms).  The routing depends
+ *     bf16 with head_dim 64 and W > 1) on general kernels: logits are fp64 sums rounded once to
+ *     fp32, attention outputs and scores fp32 sums, ||v_p - o_i||^2 and what goes with it as good
+ *     as an fp32 rounding of the fp64 value of the fp32 o_i.  The routing depends
  *     on the arguments only (and on obc_set_score_path, a test hook declared at the end of
  *     this file); the process environment is never read.
  */
@@ -126,11 +128,17 @@ int obc_score_accumulate(const void *q, const void *k, const void *v,
  * serving loops, harnesses that forbid device allocation.  obc_score (accumulate = 0) or
  * obc_score_accumulate (accumulate = 1) with the library's own scratch in place of the
  * `workspace` argument: a device array of OBC_STATIC_SCRATCH_BYTES that is part of the loaded
- * library (one copy per GPU, held until the process ends).  Same inputs, outputs, checks and
- * results as those calls; nothing is allocated, freed, copied or synchronised.
- *   - Shapes whose obc_score_workspace_bytes exceeds OBC_STATIC_SCRATCH_BYTES are rejected with
- *     OBC_EWORKSPACE before anything is launched (the metric's workload, 4 x 32768 tokens of a
- *     32/8-head layer, needs ~35 MiB and fits; decode steps need well under 1 MiB).
+ * library (one copy per GPU, held until the process ends).  Same inputs, outputs and checks as
+ * those calls; nothing is allocated, freed, copied or synchronised.
+ *   - Same bits as those calls, with one exception: where the logits of ONE KV head (4 bytes per
+ *     window row of its group and token) outgrow the array on the general path (fp32, or bf16 with
+ *     head_dim 64), the head's rows or tokens are taken in smaller pieces than with a workspace,
+ *     and the sums over the pieces can differ in their low bits.
+ *   - The general path works in pieces, so the array serves any shape of it up to millions of tokens
+ *     (OBC_EWORKSPACE beyond).  On the matrix cores (bf16, head_dim 128) shapes whose
+ *     obc_score_workspace_bytes exceeds OBC_STATIC_SCRATCH_BYTES are rejected with OBC_EWORKSPACE
+ *     before anything is launched (4 x 32768 tokens of a 32/8-head layer need ~35 MiB and fit;
+ *     decode steps need well under 1 MiB).
  *   - Every call on one GPU shares that GPU's array.  The scratch carries no state between
  *     calls (each call overwrites what it reads), but two calls in flight on the same GPU at
  *     the same time (different streams, or graphs replayed concurrently) race on it: keep calls

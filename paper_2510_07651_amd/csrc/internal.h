@@ -100,7 +100,7 @@ int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype,
 // Adds the general path's buffers to the plan, advancing *off (bytes).
 void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWorkspace *ws, size_t *off);
 // Adds the matrix-core path's buffers to the plan, advancing *off (bytes).
-void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, size_t cap, ScoreWorkspace *ws, size_t *off);
+void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWorkspace *ws, size_t *off);
 
 // Decode path: whether it covers the shape, its buffers (advancing *off), its launcher.
 bool decode_path_covers(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, bool any_size);

@@ -74,7 +74,7 @@ int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype,
     if (ws->use_decode) {
         decode_plan(B, N, Hq, Hkv, d, ws, &off);
     } else if (ws->use_mfma) {
-        mfma_plan(B, N, W, Hq, Hkv, d, variant, cap ? cap : SIZE_MAX, ws, &off);
+        mfma_plan(B, N, W, Hq, Hkv, d, variant, ws, &off);
     } else {
         plain_plan(B, N, W, Hq, Hkv, d, cap ? cap : kPlainWorkspace, ws, &off);
     }

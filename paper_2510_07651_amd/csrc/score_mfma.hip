@@ -1286,7 +1286,7 @@ static int even_share(const int *len, int B, int N, int heads, int slots, int mi
     return best;
 }
 
-void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, size_t cap, ScoreWorkspace *ws, size_t *off) {
+void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv;
     const int nv = variant == OBC_ALL ? 3 : 1;
@@ -1307,10 +1307,11 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, size_t 
     ws->planes = *off;
     if (ws->n_chunks > 1) *off = align_up(*off + (size_t)ws->n_chunks * nv * BH * N * sizeof(float), 256);
     // With few rows the first sweep keeps their logits (4 bytes per pair) and the second reads them instead of K (256 bytes
-    // per token): beyond eight rows the gain fades.
+    // per token): beyond eight rows the gain fades.  Only within the static scratch, so that a call has the same plan, and
+    // with it the same bits, on either scratch.
     ws->z_stride = (N + 31) / 32 * 32;
     const size_t z_bytes = (size_t)BH * M * ws->z_stride * sizeof(float);
-    ws->keep_z = M <= kFewRows && *off + z_bytes <= cap && (long long)M * ws->z_stride < (1LL << 29) ? 1 : 0;    // (32-bit offsets)
+    ws->keep_z = M <= kFewRows && *off + z_bytes <= OBC_STATIC_SCRATCH_BYTES && (long long)M * ws->z_stride < (1LL << 29) ? 1 : 0;    // (32-bit offsets)
     if (ws->keep_z) {
         ws->z = *off;
         *off = align_up(*off + z_bytes, 256);

@@ -961,10 +961,10 @@ hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hi
 
 }  // namespace
 
-// Pieces.  `cap` bounds the workspace: as many KV heads at a time as fit, then as many rows of one head, then as many
-// tokens.  Within it a launch should fill the chip once (kResident), so that no workgroup pays a prologue more than
-// needed and no last wave of workgroups is nearly empty; a row has at most kMaxRanges maxima, which every workgroup of the
-// weight kernel reads.
+// Pieces.  `cap` bounds the workspace: as many KV heads at a time as fit (which leaves every sum as it is), then as many
+// rows of one head, then as many tokens (which does not).  Within it a launch should fill the chip once (kResident), so that
+// no workgroup pays a prologue more than needed and no last wave of workgroups is nearly empty; a row has at most kMaxRanges
+// maxima, which every workgroup of the weight kernel reads.
 void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv, M = Hq / Hkv * W;
@@ -999,12 +999,14 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
         }
     }
     auto take = [&](size_t *at, size_t bytes) { *at = *off; *off = align_up(*off + bytes, 256); };
-    const size_t rows = ws->pl_heads * align_up(ws->pl_rows, 16);        // (whole blocks are written)
+    size_t rows = BH * align_up(M, 16);                      // (whole blocks are written)
     // Two launches instead of four where every tile of a head may merge all of the head's records (short_partial): as long
-    // as that reads less than 32 MB, some 5 us.
-    ws->pl_short = !fixed && tiles <= kShortTiles && ws->pl_heads == BH && ws->pl_rows == M &&
-                   (size_t)BH * tiles * tiles * M * d * 4 <= (size_t)32 << 20 && rows * (tiles * (kTile * 4 + 8 * d + 16)) <= cap;
+    // as that reads less than 32 MB, some 5 us, and the buffers fit the static scratch (on either scratch the same kernels).
+    ws->pl_short = !fixed && tiles <= kShortTiles && (size_t)BH * tiles * tiles * M * d * 4 <= (size_t)32 << 20 &&
+                   rows * (tiles * (kTile * 4 + 8 * d + 16)) <= (size_t)OBC_STATIC_SCRATCH_BYTES - 7 * 256;
     if (ws->pl_short) {
+        ws->pl_heads = BH;
+        ws->pl_rows = M;
         ws->pl_split = ws->pl_range = kTile;
         ws->pl_splits = (int)tiles;
         ws->pl_z_stride = (int)tiles * kTile;
@@ -1013,6 +1015,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
         take(&ws->pl_part_o, rows * tiles * 2 * d * 4);
         return;
     }
+    rows = ws->pl_heads * align_up(ws->pl_rows, 16);
     ws->pl_z_stride = (int)align_up(ws->pl_seg, kTile);       // (whole tiles are written)
     take(&ws->pl_z, rows * ws->pl_z_stride * 4);
     take(&ws->pl_best, rows * ws->pl_ranges * sizeof(float2));

@@ -78,3 +78,20 @@ def test_static_scratch_refuses_shapes_beyond_its_size():
     lib = obc.load_library()
     assert lib.obc_score_static(q.data_ptr(), k.data_ptr(), k.data_ptr(), N, W, Hq, Hkv, d, obc.OBC_ALL,
                                 scores.data_ptr(), B, obc.OBC_BF16, None, 2, None) == obc.OBC_EINVAL   # accumulate flag
+
+
+# (dtype, d, G, W, N, Hkv) that would profit from more than the static scratch: logits of a few heads at a time, short
+# sequences, eight rows whose kept logits would not fit
+BEYOND = [("fp32", 64, 4, 32, 13001, 12), ("fp32", 64, 1, 4, 256, 1200), ("bf16", 128, 8, 1, 200000, 8)]
+
+
+@pytest.mark.parametrize("case", BEYOND, ids=["heads", "short", "few_rows"])
+def test_static_scratch_has_the_bits_of_the_workspace_call(case):
+    dtype, d, G, W, N, Hkv = case
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    q, k, v = (torch.randn(1, H, n, d, generator=gen, device="cuda", dtype=dt) for H, n in ((G * Hkv, W), (Hkv, N), (Hkv, N)))
+    want = obc.obc_score(q, k, v, "joint")
+    got = torch.empty_like(want)
+    obc.obc_score_static(q, k, v, "joint", got)
+    assert torch.equal(got, want)
