@@ -155,10 +155,12 @@ int obc_score_static(const void *q, const void *k, const void *v,
 
 /*
  * Optional workspace of the three selection calls below.  Heads longer than 32768 tokens
- * do not fit one block's registers; given *bytes_out bytes of 256-byte aligned device
- * scratch their selection is cut into slices of 8192 tokens that run on separate blocks.
- * *bytes_out is 0 for shapes that do not profit.  The results do not depend on whether the
- * workspace is given.
+ * do not fit one block's registers; given device scratch, 256-byte aligned, their selection
+ * is cut into slices (4096 tokens, more for very long heads) that run on separate blocks.
+ * *bytes_out is 0 for shapes that do not profit; otherwise about 8 bytes per score and 8 KB
+ * per slice, of which plain scores (pool = 1) need only the first half: without the last
+ * B * Hkv * 4 * N bytes (N rounded up to 4, the whole to 256) the same kernels run.  The results
+ * do not depend on whether the workspace is given.
  */
 int obc_select_workspace_bytes(int B, int Hkv, int N, size_t *bytes_out);
 
@@ -223,7 +225,8 @@ int obc_select_pooled(const float *scores, int num_hh, int num_sinks, int num_re
  * `cap` must hold the most one head can receive, min(len_b, Hkv*budget - (Hkv-1)*n_safe).
  * obc_compact turns the -1 entries into all-zero rows.  n_safe = budget is obc_select.
  * Requires 0 <= n_safe <= budget <= len_b and a workspace of
- * obc_select_adaptive_workspace_bytes(...) bytes, 256-byte aligned.
+ * obc_select_adaptive_workspace_bytes(...) bytes, 256-byte aligned (about 8 bytes per score and
+ * 16 KB per slice; `budget` and `n_safe` are checked there but do not change the size).
  */
 int obc_select_adaptive_workspace_bytes(int B, int Hkv, int N, int budget, int n_safe, size_t *bytes_out);
 int obc_select_adaptive(const float *scores, int budget, int n_safe, int32_t *keep_idx, int32_t *counts, int cap,

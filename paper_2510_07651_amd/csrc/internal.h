@@ -122,7 +122,7 @@ size_t select_adaptive_workspace_bytes(int B, int Hkv, int N, int budget, int n_
 hipError_t launch_select_adaptive(const float *scores, int budget, int n_safe, int cap, int32_t *keep_idx,
                                   int32_t *counts, int B, int Hkv, int N, int ragged, const SeqLens &lens,
                                   void *workspace, hipStream_t stream);
-size_t select_workspace_bytes(int B, int Hkv, int N);
+size_t select_workspace_bytes(int B, int Hkv, int N, bool pooled);
 bool select_prefers_slices(int B, int Hkv, int N);
 hipError_t launch_compact(const void *k, const void *v, const int32_t *keep_idx, void *k_out, void *v_out, int B,
                           int Hkv, int N, int budget, int row_bytes, hipStream_t stream);

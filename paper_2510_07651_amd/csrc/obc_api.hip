@@ -224,7 +224,7 @@ static int score_impl(const void *q, const void *k, const void *v, int N, int W,
 int obc_select_workspace_bytes(int B, int Hkv, int N, size_t *bytes_out) {
     if (!bytes_out || B < 1 || Hkv < 1 || N < 1) return OBC_EINVAL;
     if ((long long)B * Hkv > 0x7fffffffLL / 2 || (long long)N > (1LL << 30)) return OBC_EUNSUPPORTED;
-    *bytes_out = select_prefers_slices(B, Hkv, N) ? select_workspace_bytes(B, Hkv, N) : 0;
+    *bytes_out = select_prefers_slices(B, Hkv, N) ? select_workspace_bytes(B, Hkv, N, true) : 0;
     return OBC_OK;
 }
 

@@ -562,8 +562,9 @@ struct SliceState {      // of a group, written by slices_collect
 struct Slices {
     int heads, per_head, chunks;     // heads per group, slices per head, chunks of 4096 scores per slice
     int key_stride;                  // keys between the heads of `keys`: N rounded up to 4
+    int list_stride;                 // keys between the slices of `list`: the most a slice has
     int *hist;                       // [groups][slices][kSliceBins]
-    uint32_t *list;                  // [groups][slices][chunks * kChunk]
+    uint32_t *list;                  // [groups][slices][list_stride]
     int *above, *count;              // [groups][slices] keys above the class, keys in the list
     SliceState *state;               // [groups]
     uint32_t *keys;                  // [heads of all groups][key_stride]; NULL: the keys are formed from the scores each time
@@ -681,7 +682,7 @@ __global__ __launch_bounds__(kSelThreads) void slices_collect(const float *__res
         if (at.slice == 0 && tid == 0) S.state[at.group] = SliceState{digit, remaining};
     };
     fetch(0);
-    uint32_t *list = S.list + at.flat() * S.chunks * kChunk;
+    uint32_t *list = S.list + at.flat() * S.list_stride;
     for_batches<kBatch>(S, at, scores, N, first, tail, radius, S.keys != nullptr, pick_class, [&](uint32_t (&keys)[kBatch][kItems], int c) {
         int mine = 0;                                        // low 16 bits: in the class, high 16 bits: above it
 #pragma unroll
@@ -773,11 +774,11 @@ __device__ __forceinline__ SliceThreshold slice_threshold(SliceShared &sh, const
     __syncthreads();
     const int n_list = few ? sh.offset[n] : 0;
     const bool in_lds = few && n_list <= kList;              // uniform
-    const uint32_t *lists = S.list + (size_t)at.group * n * S.chunks * kChunk;
+    const uint32_t *lists = S.list + (size_t)at.group * n * S.list_stride;
     // f(key, slice) over the lists where they lie: a wave per slice
     auto visit_global = [&](auto &&f) {
         for (int sl = wave; sl < n; sl += kSelWaves) {
-            const uint32_t *src = lists + (size_t)sl * S.chunks * kChunk;
+            const uint32_t *src = lists + (size_t)sl * S.list_stride;
             const int c = few ? sh.count[sl] : counts[sl];
             for (int i = lane; i < c; i += 64) f(src[i], sl, i);
         }
@@ -942,11 +943,12 @@ static size_t plan_slices(Slices *S, char *base, int groups, int heads, int N, b
     S->chunks = slice_chunks(heads, N);
     S->per_head = (int)((N + (long long)S->chunks * kChunk - 1) / ((long long)S->chunks * kChunk));
     S->key_stride = (N + 3) / 4 * 4;
+    S->list_stride = S->per_head == 1 ? S->key_stride : S->chunks * kChunk;
     const size_t slices = (size_t)groups * heads * S->per_head;
     size_t off = 0;
     auto take = [&](size_t bytes) { char *p = base + off; off += up256(bytes); return p; };
     S->hist = (int *)take(slices * kSliceBins * sizeof(int));
-    S->list = (uint32_t *)take(slices * S->chunks * kChunk * sizeof(uint32_t));
+    S->list = (uint32_t *)take(slices * S->list_stride * sizeof(uint32_t));
     S->above = (int *)take(slices * sizeof(int));
     S->count = (int *)take(slices * sizeof(int));
     S->state = (SliceState *)take((size_t)groups * sizeof(SliceState));
@@ -959,9 +961,10 @@ static hipError_t with_batch(const Slices &S, F &&f) {
     return S.chunks == 1 ? f(std::integral_constant<int, 1>()) : f(std::integral_constant<int, 4>());
 }
 
-size_t select_workspace_bytes(int B, int Hkv, int N) {
+// Only the pooled ranking reads keys; scores are turned into them as quickly as keys are read.
+size_t select_workspace_bytes(int B, int Hkv, int N, bool pooled) {
     Slices S;
-    return plan_slices(&S, nullptr, B * Hkv, 1, N, true);
+    return plan_slices(&S, nullptr, B * Hkv, 1, N, pooled);
 }
 
 // Long heads take the sliced path: one workgroup per head keeps a 32K-token head in registers, but beyond that it
@@ -973,8 +976,7 @@ bool select_prefers_slices(int B, int Hkv, int N) {
 static hipError_t launch_select_sliced(const float *scores, int budget, int32_t *keep_idx, int B, int Hkv, int N, int ragged,
                                        const SeqLens &lens, int first, int tail, int radius, void *workspace, hipStream_t stream) {
     Slices S;
-    plan_slices(&S, (char *)workspace, B * Hkv, 1, N, true);
-    if (radius == 0) S.keys = nullptr;       // (scores are as quick to turn into keys as keys are to read)
+    plan_slices(&S, (char *)workspace, B * Hkv, 1, N, radius > 0);
     const dim3 grid((unsigned)S.per_head * B * Hkv), block(kSelThreads);
     return with_lens(ragged, B, lens, [&](const auto &few) {
         return with_batch(S, [&](auto batch) {
@@ -1032,7 +1034,7 @@ hipError_t launch_select_adaptive(const float *scores, int budget, int n_safe, i
 hipError_t launch_select(const float *scores, int budget, int32_t *keep_idx, int B, int Hkv, int N, int ragged,
                          const SeqLens &lens, int first, int tail, int radius, void *workspace,
                          size_t workspace_bytes, hipStream_t stream) {
-    if (workspace && select_prefers_slices(B, Hkv, N) && workspace_bytes >= select_workspace_bytes(B, Hkv, N))
+    if (workspace && select_prefers_slices(B, Hkv, N) && workspace_bytes >= select_workspace_bytes(B, Hkv, N, radius > 0))
         return launch_select_sliced(scores, budget, keep_idx, B, Hkv, N, ragged, lens, first, tail, radius, workspace, stream);
     const dim3 grid(B * Hkv), block(kSelThreads);
     return with_lens(ragged, B, lens, [&](const auto &few) {

@@ -132,3 +132,17 @@ def test_adaptive_over_more_heads_than_a_grid_dimension_takes(B, Hkv):
     got_idx, got_cnt = obc.obc_select_adaptive(torch.from_numpy(s).cuda(), budget, n_safe)
     np.testing.assert_array_equal(got_cnt.cpu().numpy(), want_cnt)
     np.testing.assert_array_equal(got_idx.cpu().numpy(), want_idx)
+
+
+@pytest.mark.parametrize("pool", [1, 5])
+def test_long_heads_with_the_least_scratch_that_is_taken(pool):
+    """Plain scores need no room for keys; a scratch one byte short, or none, gives the same through select_topk."""
+    rng = np.random.default_rng(6)
+    B, Hkv, N, hh = 1, 3, 70001, 500
+    s = torch.from_numpy(_scores(rng, (B, Hkv, N))).cuda()
+    need = obc.obc_select_workspace_bytes(B, Hkv, N)
+    keys = (4 * B * Hkv * ((N + 3) // 4 * 4) + 255) // 256 * 256
+    want = obc.obc_select_pooled(s, hh, pool=pool, workspace=False)
+    for size in (need, need - keys, need - keys - 1):
+        got = obc.obc_select_pooled(s, hh, pool=pool, workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        assert torch.equal(got, want), size
