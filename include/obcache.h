@@ -359,10 +359,13 @@ int obc_set_score_path(int path);
 int obc_set_score_tuning(int splits, int range_len);
 
 /*
- * Test hook: form of the matrix-core path's second sweep for the variants with a cross term (key, joint, all),
- * process-wide.  0: chosen by shape; 1: 32 window rows per wave, two workgroups per compute unit; 2: as 0,
- * 64 rows per wave with the stationary operands in the accumulator registers, one workgroup per compute unit.  Both forms meet the same tolerance; their
- * sums run in different orders, so their low bits differ.
+ * Test hook: form of the matrix-core path's second sweep, process-wide.
+ *   0: chosen by shape
+ *   1: 32 window rows per wave, two workgroups per compute unit
+ *   2: 64 rows per wave with the stationary operands in the accumulator registers, one workgroup per compute
+ *      unit, for the variants with a cross term (key, joint, all)
+ * 1 and 2 also keep windows of at most eight rows from the kernel that scores them from kept logits.  All forms meet the
+ * same tolerance; their sums run in different orders, so their low bits differ.
  */
 int obc_set_sweep2_form(int form);
 

@@ -158,7 +158,8 @@ def obc_set_score_path(path="auto") -> None:
 
 
 def obc_set_sweep2_form(form: int = 0) -> None:
-    """Test hook: 0 = second sweep chosen by shape, 1 = 32 rows per wave, 2 = 64 rows per wave where possible."""
+    """Test hook: 0 = second sweep chosen by shape, 1 = 32 rows per wave, 2 = 64 rows per wave where the variant has a
+    cross term; 1 and 2 also where the few-row kernel would run."""
     rc = load_library().obc_set_sweep2_form(int(form))
     if rc != OBC_OK:
         raise ObcError(rc, "obc_set_sweep2_form")

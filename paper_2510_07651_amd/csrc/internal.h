@@ -92,7 +92,7 @@ constexpr int kDecodeMaxGroup = 8;   // query heads per KV head the decode path 
 // Sweep-1 split count and sweep-2 token range forced through obc_set_score_tuning (0: automatic).
 int tuned_splits();
 int tuned_range();
-int tuned_sweep2_form();     // 0: by shape, 1: 32 rows per wave, 2: 64 rows per wave where the shape allows
+int tuned_sweep2_form();     // 0: by shape, 1: 32 rows per wave, 2: 64 rows per wave where the variant has a cross term
 
 // `cap`: bytes the plan should stay within where it has a choice (0: what is best).
 constexpr size_t kPlainWorkspace = (size_t)96 << 20;      // of the general path, which works in pieces

@@ -1308,10 +1308,10 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     if (ws->n_chunks > 1) *off = align_up(*off + (size_t)ws->n_chunks * nv * BH * N * sizeof(float), 256);
     // With few rows the first sweep keeps their logits (4 bytes per pair) and the second reads them instead of K (256 bytes
     // per token): beyond eight rows the gain fades.  Only within the static scratch, so that a call has the same plan, and
-    // with it the same bits, on either scratch.
+    // with it the same bits, on either scratch; and not where a form of the second sweep is asked for (obc_set_sweep2_form).
     ws->z_stride = (N + 31) / 32 * 32;
     const size_t z_bytes = (size_t)BH * M * ws->z_stride * sizeof(float);
-    ws->keep_z = M <= kFewRows && *off + z_bytes <= OBC_STATIC_SCRATCH_BYTES && (long long)M * ws->z_stride < (1LL << 29) ? 1 : 0;    // (32-bit offsets)
+    ws->keep_z = form == 0 && M <= kFewRows && *off + z_bytes <= OBC_STATIC_SCRATCH_BYTES && (long long)M * ws->z_stride < (1LL << 29) ? 1 : 0;    // (32-bit offsets)
     if (ws->keep_z) {
         ws->z = *off;
         *off = align_up(*off + z_bytes, 256);

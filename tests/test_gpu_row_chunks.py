@@ -57,3 +57,17 @@ def test_rows_and_shares_match_oracle(shape, range_len, score_path):
 def test_sinks_and_needles_all_over_a_ragged_batch(W, score_path):
     run_case(synth.Workload("needles", B=3, Hq=6, Hkv=2, d=128, N=9000, W=W, dtype="bf16", budget=256, seed=77, sinks=4,
                             outlier_channels=4, needles=64, ragged=(3000, 9000), pad_nan=True))
+
+
+@pytest.mark.parametrize("form", [0, 1, 2])
+def test_few_rows_on_every_form_of_the_second_sweep(form, score_path):
+    """Eight rows or fewer keep their logits for a kernel of their own, unless a form is asked for."""
+    B, G, Hkv, N = 1, 4, 2, 12001
+    score_path("mfma")
+    size = []
+    for f in (1, form):
+        obc.obc_set_sweep2_form(f)
+        size.append(obc.obc_score_workspace_bytes(B, N, 1, G * Hkv, Hkv, 128, obc.OBC_BF16, obc.OBC_JOINT))
+    assert (size[1] - size[0] >= 4 * G * Hkv * N) == (form == 0)
+    run_case(synth.Workload("few_rows", B=B, Hq=G * Hkv, Hkv=Hkv, d=128, N=N, W=1, dtype="bf16", budget=256, seed=78, sinks=2,
+                            outlier_channels=4))
