@@ -283,7 +283,7 @@ static int adaptive_checks(int budget, int n_safe, int cap, int B, int Hkv, int 
 int obc_select_adaptive_workspace_bytes(int B, int Hkv, int N, int budget, int n_safe, size_t *bytes_out) {
     if (!bytes_out || B < 1 || Hkv < 1 || N < 1 || budget < 1 || n_safe < 0 || n_safe > budget || budget > N) return OBC_EINVAL;
     if ((long long)B * Hkv > 0x7fffffffLL / 2 || (long long)Hkv * N > (1LL << 30)) return OBC_EUNSUPPORTED;
-    *bytes_out = select_adaptive_workspace_bytes(B, Hkv, N, budget, n_safe);
+    *bytes_out = select_adaptive_workspace_bytes(B, Hkv, N);
     return OBC_OK;
 }
 
@@ -297,7 +297,7 @@ int obc_select_adaptive(const float *scores, int budget, int n_safe, int32_t *ke
     const int rc = adaptive_checks(budget, n_safe, cap, B, Hkv, N, seq_lens_host, &ragged, &lens);
     if (rc != OBC_OK) return rc;
     if (!workspace || ((uintptr_t)workspace & 255) != 0 ||
-        workspace_bytes < select_adaptive_workspace_bytes(B, Hkv, N, budget, n_safe))
+        workspace_bytes < select_adaptive_workspace_bytes(B, Hkv, N))
         return OBC_EWORKSPACE;
     const hipError_t e = launch_select_adaptive(scores, budget, n_safe, cap, keep_idx, counts, B, Hkv, N, ragged, lens,
                                                 workspace, (hipStream_t)hip_stream);

@@ -800,7 +800,7 @@ __device__ __forceinline__ void sweep2_flush(const float *stage, float *out, siz
 // (on this hardware a 32x32x16 matrix op blocks most vector-ALU issue anyway).
 // Even steps first wait for the tile issued two steps earlier and start the next one.
 template <int PH, bool kMasked, int kVariant>
-__device__ __forceinline__ void sweep2_step(Sweep2Regs &R, const char *smem, uint32_t lds0, int n, int n_blk,
+__device__ __forceinline__ void sweep2_step(Sweep2Regs &R, uint32_t lds0, int n, int n_blk,
                                             int t_begin, int t_end, int last_row, const int *vis_i,
                                             const int *excl_i, const char *kh, const char *vh,
                                             const char *const (&kp)[8], const uint32_t (&kdoff)[4], int wave, int lane,
@@ -1032,7 +1032,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__res
     // Blocks m_lo .. m_hi span the separately scored pairs of this range (none: an empty span).
     const int m_lo = has_special ? __builtin_amdgcn_readfirstlane(spec_lo) : 1;
     const int m_hi = has_special ? __builtin_amdgcn_readfirstlane(spec_hi) : 0;
-#define OBC_S2_ARGS smem, lds0, n, n_blk, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, kp, kdoff, wave, lane, wave_active, part, out, variant_stride, accumulate, m_lo, m_hi
+#define OBC_S2_ARGS lds0, n, n_blk, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, kp, kdoff, wave, lane, wave_active, part, out, variant_stride, accumulate, m_lo, m_hi
     int n = 0;
     for (; n < n_plain; n += 4) {
         sweep2_step<0, false, kVariant>(R, OBC_S2_ARGS); ++n;

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kThreads, 4) void plain_logits(const T *__restrict_
 // l1 form) only the sums are formed.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int kRt, bool kNeedO, typename Lens>
-__global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict__ v, int N, int W, int Hq, int Hkv,
+__global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict__ v, int N, int W, int Hkv,
                                                              int ragged, Lens lens, Piece w, int range_len, int n_ranges,
                                                              int split_len, int n_splits, const float *__restrict__ z,
                                                              const float2 *__restrict__ range_best,
@@ -495,7 +495,7 @@ constexpr int kShortTiles = 16;      // most tiles of a short sequence
 
 template <typename T, int D, int kRt, bool kNeedO, typename Lens>
 __global__ __launch_bounds__(kThreads) void short_partial(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
-                                                          int N, int W, int Hq, int Hkv, int ragged, Lens lens, Piece w,
+                                                          int N, int W, int Hkv, int ragged, Lens lens, Piece w,
                                                           float *__restrict__ z, float4 *__restrict__ heads, float *__restrict__ part_o) {
     constexpr int kRows = 16 * kRt, kPs = kTile + 4, kCt = D / 64;
     __shared__ __attribute__((aligned(16))) float rows_s[kRows * kStride<D>], v_s[kNeedO ? kTile * kStride<D> : 4], p_s[kRows * kPs];
@@ -827,9 +827,9 @@ hipError_t run_short(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace 
     const dim3 grid(ws.pl_splits, 1, a.B * a.Hkv);
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
         if (need_o)
-            short_partial<T, D, kRt, true><<<grid, dim3(kThreads), 0, stream>>>(q, k, v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, z, heads, part_o);
+            short_partial<T, D, kRt, true><<<grid, dim3(kThreads), 0, stream>>>(q, k, v, a.N, a.W, a.Hkv, a.ragged, lens, w, z, heads, part_o);
         else
-            short_partial<T, D, kRt, false><<<grid, dim3(kThreads), 0, stream>>>(q, k, v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, z, heads, part_o);
+            short_partial<T, D, kRt, false><<<grid, dim3(kThreads), 0, stream>>>(q, k, v, a.N, a.W, a.Hkv, a.ragged, lens, w, z, heads, part_o);
         if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     if (!(a.stage_mask & OBC_STAGE_SWEEP2)) return hipSuccess;
@@ -895,7 +895,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                                 best, rec, part_l, part_o);
                         else
                             plain_weights<T, D, kRt, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
-                                v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
+                                v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
                                 best, rec, part_l, part_o);
                     };
                     if (need_o) weights(std::true_type());

@@ -211,7 +211,7 @@ __device__ __forceinline__ void emit_chunk(int *wave_tot, const uint32_t (&key)[
 // scans the (chunk, wave) totals in emission order; every thread places its keys.
 template <int kRegChunks, typename Shared>
 __device__ __forceinline__ void emit_resident(Shared &sh, const uint32_t (&keys)[kRegChunks][kItems], int n_chunks,
-                                              int len, uint32_t thr, int need_eq, int budget, int32_t *out) {
+                                              uint32_t thr, int need_eq, int budget, int32_t *out) {
     static_assert(kRegChunks <= kMaxRegChunks, "cw_tot is sized for kMaxRegChunks chunks");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int before[kRegChunks];                     // packed counts: low 16 bits #equal, high 16 bits #greater (<= 256 per wave)
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const float *__restri
     // ---- ordered sweep ----
     if constexpr (kResident) {
         if (need_eq == n_equal) emit_resident_uncut<kRegChunks>(sh, keys, n_chunks, thr, budget, out);
-        else emit_resident<kRegChunks>(sh, keys, n_chunks, len, thr, need_eq, budget, out);
+        else emit_resident<kRegChunks>(sh, keys, n_chunks, thr, need_eq, budget, out);
     } else {
         int gt_base = 0, eq_base = 0;
         for (int c0 = 0; c0 < n_chunks; c0 += kRegChunks) {
@@ -1004,8 +1004,7 @@ static size_t plan_adaptive(Slices *safe, Slices *all, char *base, int B, int Hk
     return off;
 }
 
-size_t select_adaptive_workspace_bytes(int B, int Hkv, int N, int budget, int n_safe) {
-    (void)budget; (void)n_safe;
+size_t select_adaptive_workspace_bytes(int B, int Hkv, int N) {
     Slices a, b;
     return plan_adaptive(&a, &b, nullptr, B, Hkv, N);
 }

@@ -81,12 +81,6 @@ __device__ __forceinline__ T across_rows(T x) {
     both_of_pair<32>(x, a, b);
     return op(a, b);
 }
-// Sum of a lane's value and that of the lane in the other half of the wave.
-__device__ __forceinline__ float across_halves(float x) {
-    float a, b;
-    both_of_pair<32>(x, a, b);
-    return a + b;
-}
 template <typename Op, typename T>
 __device__ __forceinline__ T wave_reduce(T x) { return across_rows<Op>(row16_reduce<Op>(x)); }
 
