@@ -560,7 +560,8 @@ struct SliceState {      // of a group, written by slices_collect
 
 // Shape of a sliced selection and its buffers in the workspace.
 struct Slices {
-    int heads, per_head, chunks;     // heads per group, slices per head, chunks of 4096 scores per slice
+    int groups, group0, heads;       // in all, first of the launch; heads per group
+    int per_head, chunks;            // slices per head, chunks of 4096 scores per slice
     int key_stride;                  // keys between the heads of `keys`: N rounded up to 4
     int list_stride;                 // keys between the slices of `list`: the most a slice has
     int *hist;                       // [groups][slices][kSliceBins]
@@ -572,24 +573,21 @@ struct Slices {
 
 constexpr int kMaxGroupSlices = 1024;    // of a group whose bookkeeping fits LDS; larger ones (that many heads) read it where it lies
 
-// Where a workgroup of the sliced kernels works: the groups' slices one after the other along the grid's x (either count may
-// exceed what y takes).
+// Where a workgroup of the sliced kernels works: blockIdx.x = slice of the group, blockIdx.y = group of the launch's.
 struct SlicePlace {
-    int slices;                              // of a group
     int slice, group, head, in_head;         // head: of all groups
     int c0, c1, len;                         // chunks of the head, its true length
     template <typename Lens>
     __device__ __forceinline__ SlicePlace(const Slices &S, int N, int Hkv, int ragged, const Lens &lens) {
-        slices = S.heads * S.per_head;
-        group = (int)(blockIdx.x / (uint32_t)slices);
-        slice = (int)(blockIdx.x % (uint32_t)slices);
+        slice = blockIdx.x;
+        group = S.group0 + blockIdx.y;
         head = group * S.heads + slice / S.per_head;
         in_head = slice % S.per_head;
         len = seq_len_of(lens, ragged, head / Hkv, N);
         c0 = in_head * S.chunks;
         c1 = min(c0 + S.chunks, (len + kChunk - 1) / kChunk);
     }
-    __device__ __forceinline__ size_t flat() const { return blockIdx.x; }
+    __device__ __forceinline__ size_t flat() const { return (size_t)group * gridDim.x + slice; }
 };
 
 // The slice's keys, kBatch chunks at a time: f(keys, first chunk).  From the scores, or from S.keys once those hold them.
@@ -654,7 +652,7 @@ __global__ __launch_bounds__(kSelThreads) void slices_collect(const float *__res
     if (tid == 0) { n_list = 0; n_above = 0; }
     // Sum of the group's histograms: four counters per thread, even slices by one half of the workgroup, odd ones by the other.
     constexpr int kAhead = 16;                               // slices of a half in flight at once
-    const int half = tid / (kSliceBins / 4), bin = tid % (kSliceBins / 4) * 4, n = at.slices;
+    const int half = tid / (kSliceBins / 4), bin = tid % (kSliceBins / 4) * 4, n = gridDim.x;
     const int *src = S.hist + (size_t)at.group * n * kSliceBins + bin;
     int4 h[kAhead];
     auto fetch = [&](int s0) {
@@ -735,13 +733,13 @@ struct SliceAhead {
     int count;               // of the slice with this thread's index
     __device__ __forceinline__ SliceAhead(const Slices &S, const SlicePlace &at) {
         state = S.state[at.group];
-        count = at.slices <= kMaxGroupSlices && (int)threadIdx.x < at.slices ? S.count[(size_t)at.group * at.slices + threadIdx.x] : 0;
+        count = (int)gridDim.x <= kMaxGroupSlices && threadIdx.x < gridDim.x ? S.count[(size_t)at.group * gridDim.x + threadIdx.x] : 0;
     }
 };
 
 __device__ __forceinline__ SliceThreshold slice_threshold(SliceShared &sh, const Slices &S, const SlicePlace &at, const SliceAhead &ahead) {
     using D = Digits<kSliceBits>;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = at.slices;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = gridDim.x;
     const int head0 = at.slice - at.in_head, head1 = head0 + S.per_head;       // the head's slices
     const SliceState st = ahead.state;
     clear_counters<D::kBins1>(sh.hist1);
@@ -939,6 +937,8 @@ static int slice_chunks(int heads, int N) {
 
 // Carves the buffers of a sliced selection out of `base` (nullptr: sizes only); returns the bytes.
 static size_t plan_slices(Slices *S, char *base, int groups, int heads, int N, bool own_keys) {
+    S->groups = groups;
+    S->group0 = 0;
     S->heads = heads;
     S->chunks = slice_chunks(heads, N);
     S->per_head = (int)((N + (long long)S->chunks * kChunk - 1) / ((long long)S->chunks * kChunk));
@@ -954,6 +954,18 @@ static size_t plan_slices(Slices *S, char *base, int groups, int heads, int N, b
     S->state = (SliceState *)take((size_t)groups * sizeof(SliceState));
     S->keys = own_keys ? (uint32_t *)take((size_t)groups * heads * S->key_stride * sizeof(uint32_t)) : nullptr;
     return off;
+}
+
+// f(shape, grid) for launches of as many groups as the grid's y takes: one, but for tens of thousands of heads.  (One launch
+// with all slices along x cost a division ahead of the first loads, with the groups along y and z another round trip for the
+// grid's size: 0.1 us per kernel.)
+template <typename F>
+static void over_groups(Slices S, F &&f) {
+    constexpr int kMost = 65535;
+    for (S.group0 = 0; S.group0 < S.groups; S.group0 += kMost) {
+        const int left = S.groups - S.group0;
+        f(S, dim3((unsigned)S.heads * S.per_head, left < kMost ? left : kMost));
+    }
 }
 
 template <typename F>
@@ -977,14 +989,16 @@ static hipError_t launch_select_sliced(const float *scores, int budget, int32_t 
                                        const SeqLens &lens, int first, int tail, int radius, void *workspace, hipStream_t stream) {
     Slices S;
     plan_slices(&S, (char *)workspace, B * Hkv, 1, N, radius > 0);
-    const dim3 grid((unsigned)S.per_head * B * Hkv), block(kSelThreads);
+    const dim3 block(kSelThreads);
     return with_lens(ragged, B, lens, [&](const auto &few) {
         return with_batch(S, [&](auto batch) {
             constexpr int kBatch = decltype(batch)::value;
-            slices_count<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, radius, S);
-            slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S);
-            slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S, keep_idx,
-                                                            (int32_t *)nullptr);
+            over_groups(S, [&](const Slices &S, dim3 grid) {
+                slices_count<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, radius, S);
+                slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S);
+                slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S, keep_idx,
+                                                                (int32_t *)nullptr);
+            });
             return hipGetLastError();
         });
     });
@@ -994,6 +1008,7 @@ static hipError_t launch_select_sliced(const float *scores, int budget, int32_t 
 static size_t plan_adaptive(Slices *safe, Slices *all, char *base, int B, int Hkv, int N) {
     size_t off = plan_slices(all, base, B, Hkv, N, true);
     *safe = *all;
+    safe->groups = B * Hkv;
     safe->heads = 1;
     safe->keys = nullptr;                    // (formed from the scores; the second selection's keys are written beside)
     const size_t slices = (size_t)B * Hkv * all->per_head;
@@ -1014,17 +1029,21 @@ hipError_t launch_select_adaptive(const float *scores, int budget, int n_safe, i
                                   void *workspace, hipStream_t stream) {
     Slices safe, all;
     plan_adaptive(&safe, &all, (char *)workspace, B, Hkv, N);
-    const dim3 grid((unsigned)all.per_head * B * Hkv), block(kSelThreads);
+    const dim3 block(kSelThreads);
     return with_lens(ragged, B, lens, [&](const auto &few) {
         return with_batch(all, [&](auto batch) {
             constexpr int kBatch = decltype(batch)::value;
-            if (n_safe > 0) {
-                slices_count<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, safe);
-                slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, 0, 0, 0, safe);
-            }
-            slices_safeguard<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, safe, all.keys, all.hist);
-            slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv * budget, Hkv, ragged, few, 0, 0, 0, all);
-            slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, cap, Hkv, ragged, few, 0, 0, 0, all, keep_idx, counts);
+            over_groups(safe, [&](const Slices &S, dim3 grid) {
+                if (n_safe > 0) {
+                    slices_count<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, S);
+                    slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, 0, 0, 0, S);
+                }
+                slices_safeguard<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, S, all.keys, all.hist);
+            });
+            over_groups(all, [&](const Slices &S, dim3 grid) {
+                slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv * budget, Hkv, ragged, few, 0, 0, 0, S);
+                slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, cap, Hkv, ragged, few, 0, 0, 0, S, keep_idx, counts);
+            });
             return hipGetLastError();
         });
     });
