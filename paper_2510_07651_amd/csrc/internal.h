@@ -110,8 +110,8 @@ hipError_t launch_score_decode(const ScoreArgs &a, const ScoreWorkspace &ws, cha
 // Launchers.  Each enqueues on `stream` and returns hipSuccess or the launch error.
 hipError_t launch_score_plain(const ScoreArgs &a, const ScoreWorkspace &ws, char *ws_base, hipStream_t stream);
 hipError_t launch_score_mfma(const ScoreArgs &a, const ScoreWorkspace &ws, char *ws_base, hipStream_t stream);
-// Register-blocked second sweep: whether it serves the variant and row count, and its launcher (same arguments
-// and outputs as the 32-rows-per-wave kernel it stands in for).
+// Register-blocked second sweep: whether it serves the variant, and its launcher (same arguments and outputs as the
+// 32-rows-per-wave kernel it stands in for).
 bool sweep2_wide_covers(int variant);
 hipError_t launch_sweep2_wide(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, float *dst, size_t plane_elems,
                               size_t chunk_stride, hipStream_t stream);

@@ -1,4 +1,4 @@
-// Part of score_plain.hip: its logits, weights and scores for more than 32 window rows per KV head.
+// Part of score_plain.hip: its kernels for more than 32 window rows per KV head.
 //
 // The fp64 matrix cores do 79 TFLOP/s and the fp32 ones 157, the 8-bit integer ones 5000 and the bf16 ones 2500, so
 // contractions whose accuracy allows it are taken apart into pieces the fast ones multiply exactly.
@@ -16,13 +16,21 @@
 // 2^-4 2^E; where a pair that counts has a smaller one (a v_p that is nearly o_i), the wave forms its 16 x 16 dot products
 // again in fp64 (fixed_score's loop), from where on they are what plain_score computes.
 //
-// P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each (exact), all nine products (each exact), fp32
+// P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each, all nine products (exact, normal numbers), fp32
 // accumulation: per 32 tokens nine bf16 ops (three for bf16 values) of 16 cycles replace eight fp32 ones of 32.
 //
-// What bounds them: the logits the fp64 matrix cores, the rest the vector ALUs.  Taking an element apart costs about 15
-// instructions (7 for bf16), paid once per workgroup of up to 128 rows, and putting a dot product together about 12; below
-// 33 rows the fp64 kernels are as fast.
-// fp32, 32/8 heads, d = 128, 8111 tokens, joint: FIXED_TIMES
+// What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  fixed_score: the vector ALUs, 83
+// instructions per 64 pairs (63 for bf16 values): putting a dot product together about 12, the norms and the closeness test
+// in fp64, and taking an element apart about 15 (7 for bf16), paid once per workgroup of up to 128 rows; matrix cores busy
+// 26 %.  fixed_weights: vector ALUs and matrix cores in turn (exponentials and pieces; busy 37 %).
+// Kernel times, 32/8 heads, joint, in us: logits / weights / merge / scores
+//   fp32, d = 128,  8111 tokens   48.5 / 27.3 / 5.5 / 29.6
+//   bf16, d = 64,  16384 tokens   47.5 / 21.4 / 5.0 / 36.0
+// Against the kernels for up to 32 rows, whole calls, 8 heads, us here / there:
+//   33 rows: fp32 d 128 8K 64 / 81, 4 x 8K 189 / 250; d 64 8K 42 / 56; bf16 d 64 8K 40 / 57, 2K 22 / 29
+//   32 rows: fp32 d 128 8K 54 / 59, 4 x 8K 154 / 154; d 64 8K 37 / 44; bf16 d 64 8K 33 / 43, 2K 20 / 24
+//   17 rows: fp32 d 128 8K 54 / 56, 4 x 8K 153 / 148; d 64 4 x 8K 98 / 89; bf16 d 64 8K 33 / 41
+// so the line lies at 32 rows, where fp32 batches break even; for bf16 it could lie lower.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -32,7 +40,8 @@ constexpr int kRowDigits = 5;                  // of o_i, which is fp32 whatever
 constexpr int kLevels = 5;
 
 // A wave has 16 window rows: the rows' digits and a block's sums fit 128 registers, so that four waves share a SIMD and hide
-// each other's latencies (with 32 rows per wave and two waves the three kernels took 30, 37 and 43 us at the shape above).
+// each other's latencies (with 32 rows per wave and two waves weights and scores took 37 and 43 us where 29 and 36 then were
+// left: fp32, d = 128, 8111 tokens).
 // kRb = 8 puts 128 rows into a workgroup; kRb = 4 puts 64 and gives its waves different parts of a token tile.
 constexpr int kFixedThreads = 512, kWeightThreads = 1024;
 template <int D> constexpr int kFixedTile = D == 64 ? 64 : 32;           // tokens

@@ -1,5 +1,6 @@
 // General scoring path: fp32 inputs, bf16 with head_dim 64, and anything pinned to it (obc_set_score_path).
-// Logits and cross terms are accumulated in fp64 on the matrix cores, attention outputs in fp32 there.
+// Logits are accumulated in fp64 on the matrix cores, attention outputs in fp32 there, cross terms in fp64 or, beyond 32
+// window rows per KV head, in fixed point where that is as good (score_fixed.h).
 //
 // Four kernels over a group of KV heads (Section 3 of the paper, then Eq. 4-6 summed over the window, Eq. 9, and the
 // query heads of the KV head, Appendix A.5):
@@ -21,10 +22,11 @@
 // and ||v_p + Z (v_p - o_i)||^2 are formed from ||v_p||^2, ||o_i||^2 and v_p.o_i in fp64: their cancellation costs bits
 // far below the fp32 of o_i itself.
 //
-// What bounds it: the two fp64 contractions, 2 * 2 d flop per (row, token) pair at the 79 TFLOP/s of the fp64 matrix
-// cores (a wave's 16 x 16 x 4 op occupies its SIMD's matrix core for 64 cycles, so operands from LDS, the conversion
-// of fp32 to fp64 and the exponentials ride in its shadow), then P V on the fp32 matrix cores (twice that rate).
+// What bounds it, up to 32 rows: the two fp64 contractions, 2 * 2 d flop per (row, token) pair at the 79 TFLOP/s of the
+// fp64 matrix cores (a wave's 16 x 16 x 4 op occupies its SIMD's matrix core for 64 cycles, so operands from LDS, the
+// conversion of fp32 to fp64 and the exponentials ride in its shadow), then P V on the fp32 matrix cores (twice that rate).
 // The vector-ALU kernels this replaced took one fp64 multiply-add per element and lane with a block per query head.
+// Beyond 32 rows: see score_fixed.h.  Short sequences: launches, see short_partial.
 // Sums run in a fixed order, so results are bit-reproducible.
 #include <algorithm>
 
@@ -51,7 +53,7 @@ struct Piece {
     int z_stride;                // floats between the logits of consecutive rows
 };
 
-// Constants of one row, written by plain_weights (m, top) and plain_merge (the rest).
+// Constants of one row, written by plain_weights or fixed_weights (m, top) and plain_merge (the rest).
 struct RowRecord {
     float m;                     // largest visible logit
     int top;                     // lowest token that attains it
