@@ -18,6 +18,9 @@
 //
 // P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each, all nine products (exact, normal numbers), fp32
 // accumulation: per 32 tokens nine bf16 ops (three for bf16 values) of 16 cycles replace eight fp32 ones of 32.
+// The outputs are as good as those of the fp32 ops: key scores of values that differ by 2^-6 (2^-9) of their norm, where the
+// outputs' error is what shows, are off by 1.0e-6 (8.6e-6) in the 2-norm, with plain_weights by 1.1e-6 (8.7e-6); fp32,
+// d = 128, 8111 tokens.
 //
 // What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  fixed_score: the vector ALUs, 83
 // instructions per 64 pairs (63 for bf16 values): putting a dot product together about 12, the norms and the closeness test
