@@ -371,7 +371,7 @@ def main():
         "valu": {"pairs": pairs, "lane_ops_per_pair": lane_ops_per_pair, "peak_lane_ops_per_s": valu_rate,
                  "ms_at_peak": round(valu_ms, 4), "frac": round(valu_ms / ms["obc_score"], 4)},
         "kernel_ms": {k: round(v, 4) for k, v in ms.items()},
-        # plain streaming read of the same K and V buffers on this machine: the practical ceiling
+        # plain streaming read of the same K and V buffers on this GPU: the practical ceiling
         "stream_read_GBps": round(2 * sets[0]["k"].numel() * esize / (ms_stream * 1e-3) / 1e9, 1),
         # the four dense contractions of the path (Q K^T twice, P V, O V^T) against the dense bf16 matrix-core peak
         "mfma": {"flops": mfma_flops, "achieved_TFLOPs": round(mfma_flops / (ms["obc_score"] * 1e-3) / 1e12, 1),
