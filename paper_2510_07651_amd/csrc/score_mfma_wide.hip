@@ -28,6 +28,7 @@
 // All sums have a fixed order: results are bit-reproducible.
 #include "internal.h"
 #include "mfma_util.h"
+#include "wave_util.h"
 
 #include <type_traits>
 
@@ -50,19 +51,15 @@ __device__ __forceinline__ void mma_first(f32x16 &acc, const f32x4 &a, const bf1
 __device__ __forceinline__ void mma_next(f32x16 &acc, const f32x4 &a, const bf16x8 &b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "a"(a), "v"(b));
 }
-// Moves a 16-byte operand into the accumulator file, where it stays.
-__device__ __forceinline__ f32x4 park(const bf16x8 &x) {
-    union { bf16x8 v; float f[4]; } u;
-    u.v = x;
-    f32x4 r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        float t;
-        asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(t) : "v"(u.f[e]));
-        r[e] = t;
-    }
-    return r;
+// Reads a 16-byte operand from LDS into the accumulator file, where it stays; parked() waits for the reads before it.
+// (One instruction each: through architectural registers it were five, in a part of the kernel where every instruction is
+// fetched for the first time.)
+template <int kOffset>
+__device__ __forceinline__ void park(f32x4 &x, uint32_t lds) {
+    static_assert(kOffset >= 0 && kOffset < 65536, "16 bits of offset");
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=a"(x) : "v"(lds), "n"(kOffset) : "memory");
 }
+__device__ __forceinline__ void parked() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 // The matrix ops above are opaque to the compiler, which therefore cannot count the cycles a
 // vector instruction must keep away from a matrix op's result (the last pass of a 32x32x16 op
 // lands ten issue slots after the op).  Wherever vector code may follow a matrix op closely,
@@ -70,25 +67,33 @@ __device__ __forceinline__ f32x4 park(const bf16x8 &x) {
 __device__ __forceinline__ void matrix_results_land() { asm volatile("s_nop 7\n\ts_nop 4" ::: "memory"); }
 
 // Ties a value to this point of the instruction stream (no instruction is emitted): the compiler's passes would
-// otherwise gather the vector work that is spread between the matrix ops next to its first use.
-__device__ __forceinline__ void stay(float &x) { asm volatile("" : "+v"(x)); }
+// otherwise gather the vector work that is spread between the matrix ops next to its first use.  The value only goes in:
+// were it also an output, the compiler would put a wait slot in front of an instruction that reads it next (it cannot see
+// what kind of write the assembly is), 45 of them per block.
+__device__ __forceinline__ void stay(float x) { asm volatile("" ::"v"(x)); }
 
 __device__ __forceinline__ bf16x8 lds_piece(lds_ptr p, int imm) {
     return *(const __attribute__((address_space(3))) bf16x8 *)(p + imm);
 }
 
-// Row constants live in LDS as [128 rows][2] = {2 (max + log2 sum), ||o^||^2}.  Accumulator registers 4 g .. 4 g + 3
-// of row set S hold four consecutive rows: their constants are two 16-byte reads, the same address for the 32 lanes
-// of a half-wave.
-struct RowConsts { f32x4 a, b; };      // {m2_0, oo_0, m2_1, oo_1}, {m2_2, oo_2, m2_3, oo_3}
-__device__ __forceinline__ RowConsts row_consts(lds_ptr cp, int S, int g) {
+// Constants of a row set S, one pair per accumulator register: 2 (max + log2 sum) and ||o^||^2 / 128 of register r's row.
+// They stay in registers: read from LDS as they are needed they took 16 reads and as many waits of the block's 660
+// instructions, and a lone wave pays for each the same.
+struct RowConsts { float m2[2][16], oo[2][16]; };
+// From the rows' row_const in LDS; `p`: the lane's first row.
+__device__ __forceinline__ RowConsts row_consts(lds_ptr p) {
+    typedef const __attribute__((address_space(3))) float *lds_float_ptr;
     RowConsts c;
-    c.a = *(const __attribute__((address_space(3))) f32x4 *)(cp + (32 * S + 8 * g) * 8);
-    c.b = *(const __attribute__((address_space(3))) f32x4 *)(cp + (32 * S + 8 * g) * 8 + 16);
+#pragma unroll
+    for (int S = 0; S < 2; ++S)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const lds_float_ptr x = (lds_float_ptr)(p + (32 * S + 8 * (r >> 2) + (r & 3)) * 16);
+            c.m2[S][r] = x[0];
+            c.oo[S][r] = x[1];
+        }
     return c;
 }
-__device__ __forceinline__ float m2_of(const RowConsts &c, int e) { return e == 0 ? c.a[0] : e == 1 ? c.a[2] : e == 2 ? c.b[0] : c.b[2]; }
-__device__ __forceinline__ float oo_of(const RowConsts &c, int e) { return e == 0 ? c.a[1] : e == 1 ? c.a[3] : e == 2 ? c.b[1] : c.b[3]; }
 
 struct Stationary {          // per 32-row set S: Q, high and residual pieces of -2 o^ (accumulator file)
     f32x4 q[2][8], hi[2][8], lo[2][8];
@@ -98,8 +103,7 @@ struct WideState {
     f32x16 zA, voA, zB, voB;             // logits and cross terms of the two row sets
     bf16x8 kreg[8], vreg[8];             // this lane's operand pieces of the current block
     lds_ptr kp[8];                       // LDS address of operand piece kk of this lane's block in the tile read next
-    lds_ptr cp;                          // LDS address of this lane's first row constants
-    RowConsts c0;                        // row constants of the first four registers of the set that is scored next
+    RowConsts rc;
     float sv, sk, sj;                    // set A's sums of the block whose set B is still due
     float vv_prev;                       // ||v_p||^2 (or ||v_p||_1) of that block's token
     bool pend;                           // uniform: set B of the previous block is still due
@@ -172,19 +176,14 @@ __device__ __forceinline__ void flush_tile(const float *stage_slot, float *out, 
 
 // Vector work of one row set of one block outside the pipeline (the last block's second set).
 template <int kVariant>
-__device__ __forceinline__ void score_set(const f32x16 &z, const f32x16 &vo, lds_ptr cp, int S, float vv, float &av,
+__device__ __forceinline__ void score_set(const f32x16 &z, const f32x16 &vo, const RowConsts &c, int S, float vv, float &av,
                                           float &ak, float &aj) {
     const TokenConsts t = token_consts(vv);
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const RowConsts c = row_consts(cp, S, g);
+    for (int r = 0; r < 16; ++r) {
+        PairWork p;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            PairWork p;
-#pragma unroll
-            for (int task = 0; task < 3; ++task)
-                pair_task<kVariant>(task, p, z[4 * g + e], vo[4 * g + e], m2_of(c, e), oo_of(c, e), t, av, ak, aj);
-        }
+        for (int task = 0; task < 3; ++task) pair_task<kVariant>(task, p, z[r], vo[r], c.m2[S][r], c.oo[S][r], t, av, ak, aj);
     }
 }
 
@@ -237,14 +236,48 @@ __device__ __forceinline__ float sumsq_quarter(const bf16x8 x, int q, float acc)
     return __builtin_amdgcn_fdot2_f32_bf16(u.h[2 * q + 1], u.h[2 * q + 1], acc, false);
 }
 
-// What a wave needs to start one of its eight transfers of the tile that is fetched during a step.
+// What a wave needs to start one of its eight transfers of the tile that is fetched during a step.  Transfers of one
+// tensor lie 1 KB apart in LDS: the instruction's offset moves their memory address along, which the lane's offset takes
+// back, so that the LDS address register is written once per tensor (a write, its wait slot and the addition that makes the
+// address, for every transfer, were 24 instructions per block).  kBias keeps the lane offsets from falling below zero.
+constexpr int kBias = 4096;
 struct TileFetch {
-    const char *k_base, *v_base;     // first byte of the tile's first row in K and in V (uniform)
-    uint32_t voff[4];                // per-lane byte offset of transfer n inside the tile (rows past the end clamped)
-    uint32_t lds;                    // LDS byte address of the ring slot (K tile; the V tile follows)
+    const char *k_base, *v_base;     // kBias bytes ahead of the tile's first row in K and in V (uniform)
+    uint32_t voff[4];                // per-lane byte offset of transfer n inside the tile + kBias - 1024 n (rows past the end clamped)
+    uint32_t lds;                    // LDS byte address of the ring slot (K tile; the V tile follows), this wave's first transfer
 };
-__device__ __forceinline__ void fetch_one(const TileFetch &f, int n, int wave) {       // n = 0..3: K, 4..7: V
-    dma16_based(n < 4 ? f.k_base : f.v_base, f.voff[n & 3], f.lds + (n < 4 ? 0 : kTileBytes) + (wave * 4 + (n & 3)) * 1024);
+template <int kSlot>
+__device__ __forceinline__ void transfer_at(const char *sbase, uint32_t voff, uint32_t lds) {
+    if constexpr (kSlot == 0)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(sbase) : "memory");
+    else
+        asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2 nt" ::"v"(voff), "s"(sbase), "n"(kSlot * 1024) : "memory");
+}
+__device__ __forceinline__ void fetch_one(const TileFetch &f, int n) {       // n = 0..3: K, 4..7: V, in this order
+    const char *base = n < 4 ? f.k_base : f.v_base;
+    switch (n & 3) {
+        case 0: return transfer_at<0>(base, f.voff[0], f.lds + (n < 4 ? 0 : kTileBytes));
+        case 1: return transfer_at<1>(base, f.voff[1], 0);
+        case 2: return transfer_at<2>(base, f.voff[2], 0);
+        default: return transfer_at<3>(base, f.voff[3], 0);
+    }
+}
+// All four transfers a wave issues for 64 rows from row `row0` of `rows`; rows past `last` (>= row0) re-read it.  `lds`: this
+// wave's first one.  Short code: what a kernel runs once costs its instructions' way from memory (see mfma_sweep2_wide).
+__device__ __forceinline__ void load_64_rows(const char *rows, int row0, int last, uint32_t lds, const uint32_t (&moff)[4], int wave, int lane) {
+    const char *base = rows + (size_t)row0 * kRowBytes - kBias;
+    uint32_t voff[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) voff[n] = moff[n] - (uint32_t)(max((wave * 4 + n) * 4 + (lane >> 4) - (last - row0), 0) * kRowBytes);
+    transfer_at<0>(base, voff[0], lds);
+    transfer_at<1>(base, voff[1], 0);
+    transfer_at<2>(base, voff[2], 0);
+    transfer_at<3>(base, voff[3], 0);
+}
+// Zeros for rows `from` .. 63 of a 64-row tile in LDS, whatever its swizzle (256 threads).
+__device__ __forceinline__ void zero_rows(char *tile, int from) {
+#pragma unroll 1
+    for (int e = max(from, 0) * (kRowBytes / 16) + (int)threadIdx.x; e < kTileBytes / 16; e += kThreads) ((uint4 *)tile)[e] = make_uint4(0, 0, 0, 0);
 }
 
 // The pipelined work of one wave on one block (32 tokens, lane's token `tok`), operands already in registers:
@@ -254,7 +287,6 @@ __device__ __forceinline__ void fetch_one(const TileFetch &f, int n, int wave) {
 // A phase has 24 slots (one matrix op each) and 48 vector tasks (three per accumulator register): slot j runs tasks
 // 2 j and 2 j + 1.  Phase 1 also forms ||v_p||^2 of this block (two dot-product ops in each of the first 16 slots) and
 // starts the wave's eight transfers of the tile three steps ahead (one in each of the last eight slots).
-// The row constants of four accumulator registers are fetched from LDS six slots before their first use.
 // `hidden`: some (row, key) pair of this block is causally hidden or past the sequence's end; `special`: the bits of its
 // group of 32 blocks (see special_word).
 template <int kVariant>
@@ -264,18 +296,14 @@ __device__ __forceinline__ void pipelined_block(WideState &R, const Stationary &
     const int half = lane >> 5;
     float vvn = 0.f, bv = 0.f, bk = 0.f, bj = 0.f;
     const TokenConsts tp = token_consts(R.vv_prev);
-    RowConsts cB[4], cA[4];
     PairWork pw[16];
-    cB[0] = R.c0;
     matrix_phase<0>(A, R.zA, R.voA, R.kreg, R.vreg, [&](int j) __attribute__((always_inline)) {
-        if (j % 6 == 0 && j < 18) cB[j / 6 + 1] = row_consts(R.cp, 1, j / 6 + 1);
-        if (j == 18) cA[0] = row_consts(R.cp, 0, 0);
         if (j < 16) { vvn = sumsq_quarter(R.vreg[j >> 1], j & 1, vvn); stay(vvn); }
-        else fetch_one(fetch, j - 16, wave);
+        else fetch_one(fetch, j - 16);
 #pragma unroll
         for (int t = 2 * j; t < 2 * j + 2; ++t) {
             const int r = t / 3;
-            pair_task<kVariant>(t % 3, pw[r], R.zB[r], R.voB[r], m2_of(cB[r >> 2], r & 3), oo_of(cB[r >> 2], r & 3), tp, bv, bk, bj);
+            pair_task<kVariant>(t % 3, pw[r], R.zB[r], R.voB[r], R.rc.m2[1][r], R.rc.oo[1][r], tp, bv, bk, bj);
         }
     });
     // (unconditional, so that the vector work above stays where it is: with no block before, `stage_prev` is a spare slot)
@@ -288,14 +316,12 @@ __device__ __forceinline__ void pipelined_block(WideState &R, const Stationary &
     const TokenConsts tc = token_consts(halves_sum(vvn));
     float av = 0.f, ak = 0.f, aj = 0.f;
     matrix_phase<1>(A, R.zB, R.voB, R.kreg, R.vreg, [&](int j) __attribute__((always_inline)) {
-        if (j % 6 == 0 && j < 18) cA[j / 6 + 1] = row_consts(R.cp, 0, j / 6 + 1);
-        if (j == 18) R.c0 = row_consts(R.cp, 1, 0);
         if (j < 8) R.kreg[j] = lds_piece(R.kp[j], 0);
         else if (j & 1) R.vreg[(j - 8) >> 1] = lds_piece(R.kp[(j - 8) >> 1], kTileBytes);
 #pragma unroll
         for (int t = 2 * j; t < 2 * j + 2; ++t) {
             const int r = t / 3;
-            pair_task<kVariant>(t % 3, pw[r], R.zA[r], R.voA[r], m2_of(cA[r >> 2], r & 3), oo_of(cA[r >> 2], r & 3), tc, av, ak, aj);
+            pair_task<kVariant>(t % 3, pw[r], R.zA[r], R.voA[r], R.rc.m2[0][r], R.rc.oo[0][r], tc, av, ak, aj);
         }
     });
     if (masks) {
@@ -324,7 +350,7 @@ template <int kVariant>
 __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, const uint32_t lds0, int s, int tile,
                                           int tile_fetch, int tile_flush, int t_begin,
                                           int t_end, int last_row, const int *vis_i, const int *excl_i, const char *kh,
-                                          const char *vh, const uint32_t (&kdoff)[4], int wave, int lane, int vis_min,
+                                          const char *vh, const uint32_t (&moff)[4], int wave, int lane, int vis_min,
                                           const uint32_t *special_s, float *stage, float *out, size_t variant_stride,
                                           bool accumulate) {
     constexpr int kNv = kVariant == OBC_ALL ? 3 : 1;
@@ -338,12 +364,12 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
     TileFetch fetch;
     {
         const int tn = t_begin + tile_fetch * kTileTok;                          // (<= last_row: the tile exists)
-        fetch.k_base = kh + (size_t)tn * kRowBytes;
-        fetch.v_base = vh + (size_t)tn * kRowBytes;
-        fetch.lds = lds0 + ((s + 3) & 3) * kSlotBytes;                        // (the slot of tile s)
+        fetch.k_base = kh + (size_t)tn * kRowBytes - kBias;
+        fetch.v_base = vh + (size_t)tn * kRowBytes - kBias;
+        fetch.lds = lds0 + ((s + 3) & 3) * kSlotBytes + wave * 4096;          // (the slot of tile s)
         const int rmax = last_row - tn;                                    // last row of the tile that exists
 #pragma unroll
-        for (int n = 0; n < 4; ++n) fetch.voff[n] = kdoff[n];
+        for (int n = 0; n < 4; ++n) fetch.voff[n] = moff[n];
         if (rmax < kTileTok - 1) {                                         // uniform, rare: rows past the end re-read the last one
 #pragma unroll
             for (int n = 0; n < 4; ++n) {
@@ -379,12 +405,14 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
                                                                 size_t chunk_stride, int accumulate_flag) {
     const bool accumulate = accumulate_flag != 0;
     constexpr int kNv = kVariant == OBC_ALL ? 3 : 1;
-    // the ring of K/V tiles, four constants per row of the chunk, the staged partial scores of four tiles (+ a spare slot)
-    __shared__ __attribute__((aligned(1024))) char smem[kRing + 512 * sizeof(float) + 5 * 2 * kNv * 64 * sizeof(float)];
-    float *rc_s = (float *)(smem + kRing);                     // [128][2] 2 (max + log2 sum) and ||o^||^2 of each row
-    float *vis_s = rc_s + 256;                                 // [128] last visible key of each row of the chunk
-    float *excl_s = vis_s + 128;                               // [128] key of the row that is scored separately, or -1
-    float *stage = excl_s + 128;                               // [4 tiles + 1][2 row halves][kNv][64]
+    // the ring of K/V tiles, the records of the chunk's rows, the staged partial scores of four tiles (+ a spare slot)
+    constexpr int kStageBytes = 5 * 2 * kNv * 64 * sizeof(float);
+    __shared__ __attribute__((aligned(1024))) char smem[kRing + 4096 + 256 * sizeof(int) + kStageBytes];
+    float4 *rc_s = (float4 *)(smem + kRing);                   // [128] row_const of each row of the chunk
+    const float4 *sp_s = rc_s + 128;                           // [128] its `special`
+    int *vis_i = (int *)(rc_s + 256);                          // [128] last visible key
+    int *excl_i = vis_i + 128;                                 // [128] key of the row that is scored separately, or -1
+    float *stage = (float *)(excl_i + 128);                    // [4 tiles + 1][2 row halves][kNv][64]
 
     const SweepPart part = sweep_part(lens, ragged, N, Hkv, n_chunks, range_len);
     const int b = part.b, g = part.g, bg = b * Hkv + g, chunk = part.chunk, G = Hq / Hkv, M = G * W, len = part.len;
@@ -402,38 +430,36 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     const char *vh = (const char *)v + (size_t)bg * N * kRowBytes;
     const uint32_t lds0 = lds_offset_of(smem);
 
-    // Tile t of the walk lives in ring slot (t + 3) mod 4.  The first tile goes out before anything else (slot 3); the
-    // other three slots first serve as a staging area for the stationary operands of the chunk's 128 rows: Q, then the
-    // high and the residual pieces of o_i, each as two 64-row tiles in the K tiles' layout, brought in by the same
-    // coalesced direct-to-LDS transfers (per-lane loads of 16-byte pieces from 32 rows each would take ten times as long).
-    uint32_t kdoff[4];
-    tile_lane_offsets<kXor16>(kdoff, wave, lane);
+    // Everything from here to the loop runs once, and what it costs is its instructions' way into the instruction cache, from
+    // memory after a sweep that has filled the L2: written out (two forms of every tile load, operands parked through
+    // architectural registers, a lane exchange per step of a minimum) it was 1700 instructions and took 9.5 to 13.5 us of a
+    // launch; in loops and with loads into the accumulator file, 7 to 10, most of that the transfers themselves.  Kernel, us,
+    // before and after: 8 heads x 8K, joint 19.2 / 16.2, all 20.3 / 17.4; 4 x 8 x 32K, joint 135 / 132; 4 x 128K, 448 rows,
+    // all (both kernels) 274 / 269.
+    // (workgroups start their walks all over the range: see tile_at)
     const int n_tiles = (t_end - t_begin + kTileTok - 1) / kTileTok;
-    // (consecutive workgroups start 13 tiles apart: coprime to the power-of-two tile counts of the usual shapes)
-    const int first = (int)((13u * (blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z))) % (unsigned)n_tiles);
-    {
-        const int tt = t_begin + first * kTileTok;
-        tile_load_async<kXor16>(kh, tt, len - 1, lds0 + 3 * kSlotBytes, wave, lane, kdoff);
-        tile_load_async<kXor16>(vh, tt, len - 1, lds0 + 3 * kSlotBytes + kTileBytes, wave, lane, kdoff);
-    }
-    const size_t lo_plane = (size_t)heads * m_pad * kRowBytes;
+    const int first = (int)__umulhi((blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) * 0x9e3779b1u, (unsigned)n_tiles);
+    uint32_t moff[4];
+    tile_lane_offsets<kXor16>(moff, wave, lane);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) moff[n] += kBias - 1024 * n;
+    // Tile t of the walk lives in ring slot (t + 3) mod 4.  Slots 0 to 2 first serve as a staging area for the stationary
+    // operands of the chunk's 128 rows: Q, then the high and the residual pieces of o_i, each as two 64-row tiles in the K
+    // tiles' layout, brought in by the same coalesced direct-to-LDS transfers (per-lane loads of 16-byte pieces from 32 rows
+    // each would take ten times as long).  The first tile follows them to slot 3.  The rows' records come the same way,
+    // one transfer per wave: ordinary loads of theirs, ahead of the transfers or behind them, are waited for with all of them.
     {
         const char *q_rows = (const char *)q + ((size_t)b * Hq + (size_t)g * G) * W * kRowBytes;      // the KV head's M rows
         const char *o_rows = (const char *)out_bf16 + cbase * kRowBytes;                             // its m_pad rows
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {              // rows past the last one re-read it (and are zeroed below, for Q)
-            tile_load_async<kXor16>(q_rows, chunk * 128 + 64 * t, M - 1, lds0 + t * kTileBytes, wave, lane, kdoff);
-            tile_load_async<kXor16>(o_rows, chunk * 128 + 64 * t, m_pad - 1, lds0 + kSlotBytes + t * kTileBytes, wave, lane, kdoff);
-            tile_load_async<kXor16>(o_rows + lo_plane, chunk * 128 + 64 * t, m_pad - 1, lds0 + 2 * kSlotBytes + t * kTileBytes, wave, lane, kdoff);
+        const char *o_low = o_rows + (size_t)heads * m_pad * kRowBytes;
+        const char *records = (const char *)((wave < 2 ? row_const : special) + cbase * 4);
+        transfer_at<0>(records, (uint32_t)min(chunk * 128 + rh * 64 + lane, m_pad - 1) * 16, lds0 + kRing + wave * 1024);
+#pragma unroll 1
+        for (int t = 0; t < 8; ++t) {              // (rows past the last one re-read it)
+            const char *rows = t < 2 ? q_rows : t < 4 ? o_rows : t < 6 ? o_low : t < 7 ? kh : vh;
+            const int from = t < 6 ? chunk * 128 + (t & 1) * 64 : t_begin + first * kTileTok, last = t < 2 ? M - 1 : t < 6 ? m_pad - 1 : len - 1;
+            load_64_rows(rows, min(from, last), last, lds0 + t * kTileBytes + wave * 4096, moff, wave, lane);
         }
-    }
-
-    float4 my_rc = make_float4(1e30f, 0.f, __int_as_float(-1), 0.f);   // padded rows (1e30) weigh nothing
-    int my_excl = -1;
-    if (threadIdx.x < 128) {
-        const int i = chunk * 128 + threadIdx.x;
-        if (i < m_pad) my_rc = ((const float4 *)row_const)[cbase + i];
-        if (i < m_pad) my_excl = __float_as_int(special[(cbase + i) * 4 + 0]);
     }
 
     WideState R;
@@ -443,58 +469,50 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     lds_ptr base = (lds_ptr)smem;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) R.kp[kk] = base + 3 * kSlotBytes + th * 32 * kRowBytes + row_piece_offset(lane, kk);
-    R.cp = base + kRing + (rh * 64 + 4 * half) * 8;
-
-    // First key some valid row of this wave cannot see (rows row0 .. row0 + 63; lane l looks at row l).
-    int vis_min = 0x7fffffff;
-    {
-        const int i = row0 + lane;
-        const int vi = i < m_pad ? __float_as_int(row_const[(cbase + i) * 4 + 2]) : -1;
-        if (vi >= 0) vis_min = vi;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) vis_min = min(vis_min, __shfl_xor(vis_min, off));
-        vis_min = __builtin_amdgcn_readfirstlane(min(vis_min, t_end - 1));
-    }
-
     __shared__ uint32_t special_s[kSpecialWords];
     if (threadIdx.x < kSpecialWords) special_s[threadIdx.x] = 0;
-    wait_async_loads();                                        // the first tile and the staged operands have landed
+    wait_async_loads_keep<kTilePerWave>();                     // the staged operands and the records have landed
     __syncthreads();
+    if (chunk * 128 + 128 > M) {                               // uniform: rows past the last one have a Q of zeros
+        zero_rows(smem, M - chunk * 128);
+        zero_rows(smem + kTileBytes, M - chunk * 128 - 64);
+        __syncthreads();
+    }
     // Stationary operands: rows row0 + 32 S + (lane % 32), pieces 2 kk + half, parked in the accumulator file.
     Stationary A;
 #pragma unroll
-    for (int S = 0; S < 2; ++S) {
-        const bool ok = row0 + 32 * S + (lane & 31) < M;       // (o_i of a padded row is stored as zeros; Q has no such row)
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) {
-            lds_ptr piece = base + rh * kTileBytes + S * 32 * kRowBytes + row_piece_offset(lane, kk);
-            const bf16x8 tq = lds_piece(piece, 0);
-            A.q[S][kk] = park(ok ? tq : zero);
-            A.hi[S][kk] = park(lds_piece(piece, kSlotBytes));
-            A.lo[S][kk] = park(lds_piece(piece + 2 * kSlotBytes, 0));
-        }
+    for (int kk = 0; kk < 8; ++kk) {
+        const uint32_t piece = lds0 + rh * kTileBytes + row_piece_offset(lane, kk);
+        park<0>(A.q[0][kk], piece);
+        park<32 * kRowBytes>(A.q[1][kk], piece);
+        park<kSlotBytes>(A.hi[0][kk], piece);
+        park<kSlotBytes + 32 * kRowBytes>(A.hi[1][kk], piece);
+        park<0>(A.lo[0][kk], piece + 2 * kSlotBytes);
+        park<32 * kRowBytes>(A.lo[1][kk], piece + 2 * kSlotBytes);
     }
+    // First key some valid row of this wave cannot see (lane l looks at row l of its 64; -1, a padded row, is above every key).
+    const bool wave_row = row0 + lane < m_pad;
+    const uint32_t vis_least = wave_reduce<MinOp>(wave_row ? (uint32_t)__float_as_int(rc_s[rh * 64 + lane].z) : 0xffffffffu);
+    const int vis_min = __builtin_amdgcn_readfirstlane((int)min(vis_least, (uint32_t)(t_end - 1)));
     int mine_special = 0;
     if (threadIdx.x < 128) {
-        const int ex = my_excl;
-        rc_s[2 * threadIdx.x] = my_rc.x;
-        rc_s[2 * threadIdx.x + 1] = my_rc.y;
-        vis_s[threadIdx.x] = my_rc.z;
-        excl_s[threadIdx.x] = __int_as_float(ex);
+        const bool row = chunk * 128 + (int)threadIdx.x < m_pad;
+        const int ex = row ? __float_as_int(sp_s[threadIdx.x].x) : -1;
+        vis_i[threadIdx.x] = row ? __float_as_int(rc_s[threadIdx.x].z) : -1;
+        excl_i[threadIdx.x] = ex;
+        if (!row) rc_s[threadIdx.x] = make_float4(1e30f, 0.f, 0.f, 0.f);      // (weighs nothing)
         mine_special = ex >= t_begin && ex < t_end;
         if (mine_special) atomicOr(&special_s[special_word((ex - t_begin) >> 5)], 1u << ((ex - t_begin) >> 5 & 31));
     }
-    const int *vis_i = (const int *)vis_s, *excl_i = (const int *)excl_s;
+    parked();
     const bool has_special = __syncthreads_or(mine_special) != 0;
 
     // Every wave has its stationary operands (the barrier above): the staging slots take the next three tiles.
-#pragma unroll
-    for (int t = 1; t < kSlots; ++t) {
-        const int tt = t_begin + tile_at(t, first, n_tiles) * kTileTok;
-        tile_load_async<kXor16>(kh, tt, len - 1, lds0 + (t - 1) * kSlotBytes, wave, lane, kdoff);
-        tile_load_async<kXor16>(vh, tt, len - 1, lds0 + (t - 1) * kSlotBytes + kTileBytes, wave, lane, kdoff);
-    }
+#pragma unroll 1
+    for (int t = 0; t < 6; ++t)
+        load_64_rows(t & 1 ? vh : kh, t_begin + tile_at((t >> 1) + 1, first, n_tiles) * kTileTok, len - 1, lds0 + t * kTileBytes + wave * 4096, moff, wave, lane);
+    wait_async_loads_keep<3 * kTilePerWave>();                 // the first tile has landed
+    __syncthreads();
     // The first block's operand pieces (slot 3).
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
@@ -506,17 +524,17 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     R.sv = R.sk = R.sj = 0.f;
     R.vv_prev = 0.f;
     R.pend = false;
-    R.c0 = row_consts(R.cp, 1, 0);
+    R.rc = row_consts(base + kRing + (rh * 64 + 4 * half) * 16);
 
     // Positions of the walk: the tile worked on, the one fetched during the step (four ahead), the one flushed (two back).
     int tile = first, tile_fetch = tile_at(4, first, n_tiles), tile_flush = tile_at(2 * n_tiles - 2, first, n_tiles);
     for (int s = 0; s < n_tiles; ++s, tile = next_tile(tile, n_tiles), tile_fetch = next_tile(tile_fetch, n_tiles), tile_flush = next_tile(tile_flush, n_tiles))
-        wide_step<kVariant>(R, A, lds0, s, tile, tile_fetch, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, kdoff, wave, lane, vis_min,
+        wide_step<kVariant>(R, A, lds0, s, tile, tile_fetch, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, moff, wave, lane, vis_min,
                             special_s, stage, out, variant_stride, accumulate);
     if (R.pend) {                                              // set B of the last block
         matrix_results_land();
         float bv = 0.f, bk = 0.f, bj = 0.f;
-        score_set<kVariant>(R.zB, R.voB, R.cp, 1, R.vv_prev, bv, bk, bj);
+        score_set<kVariant>(R.zB, R.voB, R.rc, 1, R.vv_prev, bv, bk, bj);
         park_block<kVariant>(stage + ((n_tiles - 1) & 3) * 2 * kNv * 64, rh, th, lane, R.vv_prev, R.sv, R.sk, R.sj, bv, bk, bj);
     }
     wait_async_loads();        // the tiles fetched past the end must have landed before the LDS is given back
@@ -562,6 +580,19 @@ __device__ __forceinline__ SoloFetch solo_fetch(const char *kh, const char *vh, 
     return f;
 }
 
+// A whole block at once, in short code (for the prologue); rows past the end re-read the last one.
+__device__ __forceinline__ void load_block(const char *kh, const char *vh, int t0, int last_row, uint32_t lds, int lane) {
+    const int row = min(t0, last_row);
+    const char *k_base = kh + (size_t)row * kRowBytes, *v_base = vh + (size_t)row * kRowBytes;
+#pragma unroll 1
+    for (int n = 0; n < 8; ++n) {
+        const int Rn = 4 * n + (lane >> 4);
+        const uint32_t voff = (uint32_t)(min(Rn, last_row - row) * kRowBytes + piece_of(kXor16, Rn, lane & 15) * 16);
+        transfer_at<0>(k_base, voff, lds + n * 1024);
+        transfer_at<0>(v_base, voff, lds + kBlkBytes + n * 1024);
+    }
+}
+
 // One block of a wave, in the two phases of pipelined_block: its operands are in registers, the previous block's set B is
 // still due, and the next block lies in slot kNext of the wave's ring from the end of phase 1 on.
 template <int kVariant, int kNext>
@@ -574,18 +605,14 @@ __device__ __forceinline__ void solo_block(WideState &R, const Stationary &A, co
     const int half = lane >> 5;
     float vvn = 0.f, bv = 0.f, bk = 0.f, bj = 0.f;
     const TokenConsts tp = token_consts(R.vv_prev);
-    RowConsts cB[4], cA[4];
     PairWork pw[16];
-    cB[0] = R.c0;
     matrix_phase<0>(A, R.zA, R.voA, R.kreg, R.vreg, [&](int j) __attribute__((always_inline)) {
-        if (j % 6 == 0 && j < 18) cB[j / 6 + 1] = row_consts(R.cp, 1, j / 6 + 1);
-        if (j == 18) cA[0] = row_consts(R.cp, 0, 0);
         if (j < 16) { vvn = sumsq_quarter(R.vreg[j >> 1], j & 1, vvn); stay(vvn); }
         if (j >= 8) solo_fetch_one(fetch, j - 8);
 #pragma unroll
         for (int t = 2 * j; t < 2 * j + 2; ++t) {
             const int r = t / 3;
-            pair_task<kVariant>(t % 3, pw[r], R.zB[r], R.voB[r], m2_of(cB[r >> 2], r & 3), oo_of(cB[r >> 2], r & 3), tp, bv, bk, bj);
+            pair_task<kVariant>(t % 3, pw[r], R.zB[r], R.voB[r], R.rc.m2[1][r], R.rc.oo[1][r], tp, bv, bk, bj);
         }
     });
     // Everything older than the transfers just started: the next block has landed.
@@ -611,14 +638,12 @@ __device__ __forceinline__ void solo_block(WideState &R, const Stationary &A, co
     const TokenConsts tc = token_consts(halves_sum(vvn));
     float av = 0.f, ak = 0.f, aj = 0.f;
     matrix_phase<1>(A, R.zB, R.voB, R.kreg, R.vreg, [&](int j) __attribute__((always_inline)) {
-        if (j % 6 == 0 && j < 18) cA[j / 6 + 1] = row_consts(R.cp, 0, j / 6 + 1);
-        if (j == 18) R.c0 = row_consts(R.cp, 1, 0);
         if (j < 8) R.kreg[j] = lds_piece(R.kp[j], kNext * kSoloSlot);
         else if (j & 1) R.vreg[(j - 8) >> 1] = lds_piece(R.kp[(j - 8) >> 1], kNext * kSoloSlot + kBlkBytes);
 #pragma unroll
         for (int t = 2 * j; t < 2 * j + 2; ++t) {
             const int r = t / 3;
-            pair_task<kVariant>(t % 3, pw[r], R.zA[r], R.voA[r], m2_of(cA[r >> 2], r & 3), oo_of(cA[r >> 2], r & 3), tc, av, ak, aj);
+            pair_task<kVariant>(t % 3, pw[r], R.zA[r], R.voA[r], R.rc.m2[0][r], R.rc.oo[0][r], tc, av, ak, aj);
         }
     });
     if (masks) {
@@ -644,11 +669,11 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
                                                                 int accumulate_flag) {
     const bool accumulate = accumulate_flag != 0;
     constexpr int kNv = kVariant == OBC_ALL ? 3 : 1;
-    // the four waves' rings, then four constants per row
-    __shared__ __attribute__((aligned(1024))) char smem[4 * 2 * kSoloSlot + 256 * sizeof(float)];
-    float *rc_s = (float *)(smem + 4 * 2 * kSoloSlot);         // [64][2] 2 (max + log2 sum) and ||o^||^2 of each row
-    float *vis_s = rc_s + 128;                                 // [64] last visible key of each row
-    float *excl_s = vis_s + 64;                                // [64] key of the row that is scored separately, or -1
+    // the four waves' rings, then the rows' records
+    __shared__ __attribute__((aligned(1024))) char smem[4 * 2 * kSoloSlot + 64 * sizeof(float4) + 128 * sizeof(int)];
+    float4 *rc_s = (float4 *)(smem + 4 * 2 * kSoloSlot);       // [64] row_const of each row
+    int *vis_i = (int *)(rc_s + 64);                           // [64] last visible key of each row
+    int *excl_i = vis_i + 64;                                  // [64] key of the row that is scored separately, or -1
 
     const SweepPart part = sweep_part(lens, ragged, N, Hkv, 1, range_len);
     const int b = part.b, g = part.g, bg = b * Hkv + g, G = Hq / Hkv, M = G * W, len = part.len;
@@ -675,21 +700,18 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
     }
     // The wave's first block goes to slot 0; the second slots of waves 0, 1 and 2 first stage the stationary operands:
     // Q, the high and the residual pieces of o_i, one 64-row tile each, brought in by all four waves.
+    load_block(kh, vh, block_of(group), len - 1, ring, lane);
     {
-        const SoloFetch f = solo_fetch(kh, vh, block_of(group), len - 1, ring, doff, lane);
+        uint32_t moff[4];
+        tile_lane_offsets<kXor16>(moff, wave, lane);
 #pragma unroll
-        for (int n = 0; n < kSoloTransfers; ++n) solo_fetch_one(f, n);
-    }
-    {
-        uint32_t toff[4];
-        tile_lane_offsets<kXor16>(toff, wave, lane);
+        for (int n = 0; n < 4; ++n) moff[n] += kBias - 1024 * n;
         const char *q_rows = (const char *)q + (((size_t)b * Hq + (size_t)g * G) * W + row0) * kRowBytes;
         const char *o_rows = (const char *)out_bf16 + cbase * kRowBytes;
         const size_t lo_plane = (size_t)heads * m_pad * kRowBytes;
-        // (rows past the last one re-read it, and are zeroed below)
-        tile_load_async<kXor16>(q_rows, 0, M - row0 - 1, lds0 + kSoloSlot, wave, lane, toff);
-        tile_load_async<kXor16>(o_rows, 0, M - row0 - 1, lds0 + 3 * kSoloSlot, wave, lane, toff);
-        tile_load_async<kXor16>(o_rows + lo_plane, 0, M - row0 - 1, lds0 + 5 * kSoloSlot, wave, lane, toff);
+#pragma unroll 1
+        for (int t = 0; t < 3; ++t)                            // (rows past the last one re-read it, and are zeroed below)
+            load_64_rows(t == 0 ? q_rows : t == 1 ? o_rows : o_rows + lo_plane, 0, M - row0 - 1, lds0 + (2 * t + 1) * kSoloSlot + wave * 4096, moff, wave, lane);
     }
     float4 my_rc = make_float4(1e30f, 0.f, __int_as_float(-1), 0.f);   // rows past the last one (1e30) weigh nothing
     int my_excl = -1;
@@ -697,45 +719,40 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
         my_rc = ((const float4 *)row_const)[cbase + lane];
         my_excl = __float_as_int(special[(cbase + lane) * 4]);
     }
-    int vis_min = row0 + lane < M ? __float_as_int(my_rc.z) : 0x7fffffff;
     const bool mine_special = my_excl >= t_begin && my_excl < t_end;
     const bool has_special = __any(mine_special);              // (the same in every wave)
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        vis_min = min(vis_min, __shfl_xor(vis_min, off));
-    }
-    vis_min = __builtin_amdgcn_readfirstlane(min(vis_min, t_end - 1));
+    uint32_t vis_least = wave_reduce<MinOp>((uint32_t)__float_as_int(my_rc.z));     // (-1, no such row, is above every key)
+    const int vis_min = __builtin_amdgcn_readfirstlane((int)min(vis_least, (uint32_t)(t_end - 1)));
     __shared__ uint32_t special_s[kSpecialWords];
     if (threadIdx.x < 64) {
         if (lane < kSpecialWords) special_s[lane] = 0;
         if (mine_special) atomicOr(&special_s[special_word((my_excl - t_begin) >> 5)], 1u << ((my_excl - t_begin) >> 5 & 31));
-        rc_s[2 * lane] = my_rc.x;
-        rc_s[2 * lane + 1] = my_rc.y;
-        vis_s[lane] = my_rc.z;
-        excl_s[lane] = __int_as_float(my_excl);
+        rc_s[lane] = my_rc;
+        vis_i[lane] = __float_as_int(my_rc.z);
+        excl_i[lane] = my_excl;
     }
-    const int *vis_i = (const int *)vis_s, *excl_i = (const int *)excl_s;
 
     WideState R;
     lds_ptr base = (lds_ptr)smem;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) R.kp[kk] = base + wave * 2 * kSoloSlot + row_piece_offset(lane, kk);
-    R.cp = base + 4 * 2 * kSoloSlot + 4 * half * 8;
     wait_async_loads();
     __syncthreads();
+    if (row0 + 64 > M) {                                       // uniform: rows past the last one are zeros
+#pragma unroll
+        for (int t = 0; t < 3; ++t) zero_rows(smem + (2 * t + 1) * kSoloSlot, M - row0);
+        __syncthreads();
+    }
     Stationary A;
 #pragma unroll
-    for (int S = 0; S < 2; ++S) {
-        const bool ok = row0 + 32 * S + (lane & 31) < M;
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) {
-            lds_ptr piece = base + kSoloSlot + S * 32 * kRowBytes + row_piece_offset(lane, kk);
-            const bf16x8 tq = lds_piece(piece, 0), th = lds_piece(piece, 2 * kSoloSlot), tl = lds_piece(piece + 4 * kSoloSlot, 0);
-            A.q[S][kk] = park(ok ? tq : zero);
-            A.hi[S][kk] = park(ok ? th : zero);
-            A.lo[S][kk] = park(ok ? tl : zero);
-        }
+    for (int kk = 0; kk < 8; ++kk) {
+        const uint32_t piece = lds0 + kSoloSlot + row_piece_offset(lane, kk);
+        park<0>(A.q[0][kk], piece);
+        park<32 * kRowBytes>(A.q[1][kk], piece);
+        park<2 * kSoloSlot>(A.hi[0][kk], piece);
+        park<2 * kSoloSlot + 32 * kRowBytes>(A.hi[1][kk], piece);
+        park<0>(A.lo[0][kk], piece + 4 * kSoloSlot);
+        park<32 * kRowBytes>(A.lo[1][kk], piece + 4 * kSoloSlot);
     }
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
@@ -745,15 +762,11 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();                                           // every wave has its stationary operands: the slots are free
     group = next_tile(group, n_groups);
-    {
-        const SoloFetch f = solo_fetch(kh, vh, block_of(group), len - 1, ring + kSoloSlot, doff, lane);
-#pragma unroll
-        for (int n = 0; n < kSoloTransfers; ++n) solo_fetch_one(f, n);
-    }
+    load_block(kh, vh, block_of(group), len - 1, ring + kSoloSlot, lane);
     R.zA = zero16(); R.voA = zero16(); R.zB = zero16(); R.voB = zero16();
     R.sv = R.sk = R.sj = 0.f;
     R.vv_prev = 0.f;
-    R.c0 = row_consts(R.cp, 1, 0);
+    R.rc = row_consts(base + 4 * 2 * kSoloSlot + 4 * half * 16);
 
     int here = group == 0 ? n_groups - 1 : group - 1;          // the group worked on; `group` is the one after it
     int tok_prev = 0x7fffffff;
@@ -775,7 +788,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
     matrix_results_land();                                     // set B of the last block
     {
         float bv = 0.f, bk = 0.f, bj = 0.f;
-        score_set<kVariant>(R.zB, R.voB, R.cp, 1, R.vv_prev, bv, bk, bj);
+        score_set<kVariant>(R.zB, R.voB, R.rc, 1, R.vv_prev, bv, bk, bj);
         const float sv = halves_sum((R.sv + bv) * R.vv_prev), sk = fmaxf(halves_sum(R.sk + bk), 0.f), sj = fmaxf(halves_sum(R.sj + bj), 0.f);
         if (half == 0 && tok_prev < t_end) {
             float *o = out + tok_prev;

@@ -53,6 +53,15 @@ def test_rows_and_shares_match_oracle(shape, range_len, score_path):
         assert torch.allclose(run[b, :, :n], joint[b, :, :n] + 2.0, rtol=1e-6) and bool((run[b, :, n:] == 2.0).all())
 
 
+@pytest.mark.parametrize("G,W,N", [(3, 32, 300), (2, 50, 129), (3, 42, 64), (7, 10, 4097), (1, 1, 40), (1, 63, 63)])
+def test_rows_past_the_last_one_weigh_nothing(G, W, N, score_path):
+    """96, 100, 126 and 70 rows of a 128-row chunk, 1 and 63 of a 64-row one: on either side of the padded row count."""
+    obc.obc_set_sweep2_form(2)
+    score_path("mfma")
+    run_case(synth.Workload("pad", B=2, Hq=2 * G, Hkv=2, d=128, N=N, W=W, dtype="bf16", budget=max(1, N // 8), seed=79, sinks=1,
+                            outlier_channels=4))
+
+
 @pytest.mark.parametrize("W", [16, 32])
 def test_sinks_and_needles_all_over_a_ragged_batch(W, score_path):
     run_case(synth.Workload("needles", B=3, Hq=6, Hkv=2, d=128, N=9000, W=W, dtype="bf16", budget=256, seed=77, sinks=4,
