@@ -48,6 +48,8 @@
 // skips it.  One pass serves every input: nothing is rescanned for rows that turn out dominated.
 //
 // A and Z never touch HBM.  All sums have a fixed order: results are bit-reproducible.
+#include <cfloat>
+
 #include "internal.h"
 #include "mfma_util.h"
 #include "wave_util.h"
@@ -155,9 +157,9 @@ __device__ __forceinline__ void pack_weights(Sweep1Regs &R) {
 // its sums.  The step is then cut in two: K Q^T and the block's row maxima first; a vote whether
 // some row of the wave meets a new candidate in block n, and (rarely) the branch that deals with
 // it; then V^T P^T and the weights.  Without kNeedO the step is one basic block.
-template <int PH, bool kMasked, bool kNeedO, bool kStoreZ>
+template <int PH, bool kNeedO, bool kStoreZ>
 __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uint32_t lds0, int n, int t_begin,
-                                            int t_end, int last_row, int vis, const char *kh, const char *vh,
+                                            int t_end, int last_row, int vis, int n_plain, const char *kh, const char *vh,
                                             const int (&koff)[8], const int (&voff)[4], const uint32_t (&kdoff)[2],
                                             const uint32_t (&vdoff)[2], int wave, int lane, bool wave_active,
                                             int2 *events, char *z_split, uint32_t z_off) {
@@ -186,6 +188,16 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
 #pragma unroll
         for (int r = 0; r < 16; r += 4)
             *(float4 *)(z_split + n * 128 + 8 * r + z_off) = make_float4(R.s_cur[r], R.s_cur[r + 1], R.s_cur[r + 2], R.s_cur[r + 3]);
+    }
+
+    // Blocks that not every row of the wave sees in full.  (A branch in the step, not steps of their own: those were 2000
+    // instructions that only the last split of a sequence ran, fetched for the first time at its very end: 3 us of 24 at 8 heads
+    // x 8K.)
+    if (n >= n_plain) {                                                // uniform
+        const int tok0 = t_begin + n * 32 + 4 * half;  // register r holds token tok0 + 8 (r / 4) + r % 4
+        const int past = min(vis, t_end - 1) - tok0;   // what lies past it is hidden
+#pragma unroll
+        for (int r = 0; r < 16; ++r) R.s_cur[r] = 8 * (r >> 2) + (r & 3) > past ? -INFINITY : R.s_cur[r];
     }
 
     // ---- matrix cores: block n+1 ----
@@ -224,14 +236,6 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
     }
     // ---- vector ALUs: block n ----
     f32x16 s = R.s_cur;
-    if (kMasked) {
-        const int tok0 = t_begin + n * 32;      // register r holds token tok0 + 8 (r / 4) + 4 half + r % 4
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int tok = tok0 + 8 * (r >> 2) + 4 * half + (r & 3);
-            if (tok > vis || tok >= t_end) s[r] = -INFINITY;
-        }
-    }
     float mx = max3(s[0], s[1], s[2]);
 #pragma unroll
     for (int r = 3; r < 15; r += 2) mx = max3(mx, s[r], s[r + 1]);
@@ -300,12 +304,8 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
     R.m_true = fmaxf(R.m_true, mx);
     const bool moved = mx > R.m_ref + kLazyRescale;                    // also true for the first visible key
     const float m_new = moved ? mx : R.m_ref;
-    float alpha = __builtin_amdgcn_exp2f((R.m_ref - m_new) * c2);      // 1 when the reference stays; exp2(-inf) = 0
-    float mref = m_new * c2;
-    if (kMasked) {                                                     // rows with nothing visible yet
-        alpha = moved ? alpha : 1.0f;
-        mref = m_new == -INFINITY ? 0.f : mref;
-    }
+    const float alpha = __builtin_amdgcn_exp2f((R.m_ref - m_new) * c2);      // 1 when the reference stays, 0 with the first visible key
+    const float mref = m_new * c2;
     R.m_ref = m_new;
     float psum = 0.f;
 #pragma unroll
@@ -361,10 +361,9 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     // Last key the row may see (Eq. 9 window rows are causal).  Padded rows carry a zero
     // query and see everything: they stay finite and are discarded later.
     const int vis = row_valid ? len - W + (row % W) : len - 1;
-    int vis_min = vis;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) vis_min = min(vis_min, __shfl_xor(vis_min, off));
-    vis_min = __builtin_amdgcn_readfirstlane(min(vis_min, t_end - 1));
+    // What the wave's first row sees, or with a multiple of W among its rows the least any row sees.
+    const int phase = rb * 32 % W;
+    const int vis_min = min(len - W + (phase + min(M - 1 - rb * 32, 31) >= W ? 0 : phase), t_end - 1);
 
     const char *kh = (const char *)k + (size_t)bg * N * kRowBytes;
     const char *vh = (const char *)v + (size_t)bg * N * kRowBytes;
@@ -393,7 +392,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
         for (int e = 0; e < 4; ++e) { R.phi[sx].u[e] = 0; R.plo[sx].u[e] = 0; }
 #pragma unroll
     for (int r = 0; r < 16; ++r) R.p[r] = 0.f;
-    R.m_ref = -INFINITY;
+    R.m_ref = -FLT_MAX;              // (finite: a row may meet nothing visible in its first blocks)
     R.m_true = -INFINITY;
     R.lsum = 0.f;
     R.alpha = 1.0f;
@@ -430,24 +429,16 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
 
     const int n_blk = (t_end - t_begin + 31) / 32;
     const int n_total = (n_blk + 3) & ~3;
-    int n_plain = (vis_min + 1 - t_begin) / 32;       // leading blocks every row of this wave sees in full
-    n_plain = max(0, min(n_plain, n_blk)) & ~3;
+    const int n_plain = max(vis_min + 1 - t_begin, 0) / 32;   // leading blocks every row of this wave sees in full
     // (kStoreZ: at most 32 rows, so they are the first wave's)
     char *z_split = (char *)(z + (size_t)bg * M * z_stride + t_begin);
     const uint32_t z_off = kStoreZ && row_valid ? (uint32_t)row * z_stride * 4 + 16 * half : ~0u;
-#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, len - 1, vis, kh, vh, koff, voff, kdoff, vdoff, wave, lane, wave_active, events, z_split, z_off
-    int n = 0;
-    for (; n < n_plain; n += 4) {
-        sweep1_step<0, false, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<1, false, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<2, false, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<3, false, kNeedO, kStoreZ>(R, OBC_S1_ARGS); n -= 3;
-    }
-    for (; n < n_total; n += 4) {
-        sweep1_step<0, true, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<1, true, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<2, true, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<3, true, kNeedO, kStoreZ>(R, OBC_S1_ARGS); n -= 3;
+#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, len - 1, vis, n_plain, kh, vh, koff, voff, kdoff, vdoff, wave, lane, wave_active, events, z_split, z_off
+    for (int n = 0; n < n_total; n += 4) {
+        sweep1_step<0, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<1, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<2, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<3, kNeedO, kStoreZ>(R, OBC_S1_ARGS); n -= 3;
     }
 #undef OBC_S1_ARGS
     // A final candidate that holds less than half of its own split's weight cannot dominate the
@@ -499,6 +490,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     if (kNeedO) __syncthreads();      // every wave is done with the rings: their space now stages the output rows
     if (!wave_active) return;
     const float lrow = halves_sum(R.lsum);
+    if (R.m_ref == -FLT_MAX && lrow == 0.f) R.m_ref = -INFINITY;
     const size_t prow0 = (size_t)(split_slot(lens, ragged, b, g, N, Hkv, split_len) + split) * m_pad + rb * 32;     // the wave's first row
     if (half == 0)                    // reference in raw q.k units (-inf when the split holds no visible key), sum, candidate
         *(float4 *)(part_ml + (prow0 + (lane & 31)) * 4) =
@@ -531,60 +523,50 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
 }
 
 // ------------------------------------------------------------------------------------
-// Combine: one 128-thread block per (KV head, padded row); thread = head_dim element.
+// Combine
 // ------------------------------------------------------------------------------------
 // Variants that need no o_i (Eq. 4, Eq. 8 and its l1-weighted form): the splits' row sums are merged into the
-// one constant per row the second sweep turns logits into weights with.
+// one constant per row the second sweep turns logits into weights with.  Grid: y = (b, KV head); 16 lanes per row, one split
+// each (with one lane per row that took sixteen splits at a time, 64 splits of 8 heads x 32K took 18.2 us; now 5.2).
 template <typename Lens>
-__global__ __launch_bounds__(128) void mfma_combine(const float *__restrict__ part_ml, int N, int W, int Hq, int Hkv,
-                                                    int ragged, Lens lens, int split_len,
-                                                    int m_pad, uint16_t *__restrict__ out_bf16,
+__global__ __launch_bounds__(256) void mfma_combine(const float *__restrict__ part_ml, int N, int W, int Hq, int Hkv,
+                                                    int ragged, Lens lens, int split_len, int m_pad,
                                                     float *__restrict__ row_const, float *__restrict__ special) {
-    const int row = blockIdx.x, bg = blockIdx.y;
+    const int row = blockIdx.x * 16 + (threadIdx.x >> 4), sub = threadIdx.x & 15, bg = blockIdx.y;      // (m_pad: a multiple of 32)
     const int b = bg / Hkv, G = Hq / Hkv, M = G * W;
     const int len = seq_len_of(lens, ragged, b, N);
-    const int dd = threadIdx.x;
-    const size_t crow = (size_t)bg * m_pad + row;
-    const int slot0 = split_slot(lens, ragged, b, bg % Hkv, N, Hkv, split_len);
-    const size_t lo_plane = (size_t)gridDim.y * m_pad * kD;   // residual pieces follow the high pieces
-    out_bf16[crow * kD + dd] = 0;                     // (no cross term: the operand is never read, and stays defined)
-    out_bf16[lo_plane + crow * kD + dd] = 0;
-    if (dd != 0) return;
-    special[crow * 4 + 0] = __int_as_float(-1);       // no separately scored (row, token) pair
-    row_const[crow * 4 + 1] = 0.f;
-    row_const[crow * 4 + 3] = 0.f;
-    if (row >= M) {                                   // padded row: weightless in the second sweep
-        row_const[crow * 4 + 0] = 1e30f;
-        row_const[crow * 4 + 2] = __int_as_float(-1);
-        return;
-    }
+    const float4 *ml = (const float4 *)part_ml + (size_t)split_slot(lens, ragged, b, bg % Hkv, N, Hkv, split_len) * m_pad + row;
     const int live_splits = (len + split_len - 1) / split_len;
     const float c2 = kLog2e * kInvSqrtD;
-    // Splits are merged sixteen at a time, every load of a batch issued before the first use.  The running sum
-    // follows the running max of the raw dot products; a split's sum is relative to its own reference.
+    constexpr int kOwn = 4;                           // splits a lane holds at a time
+    // The running sum follows the running max of the raw dot products; a split's sum is relative to its own reference.
     float m_raw = -INFINITY, l = 0.f;
-    for (int s0 = 0; s0 < live_splits; s0 += 16) {
-        float4 ml[16];
+    for (int s0 = 0; s0 < live_splits; s0 += 16 * kOwn) {
+        float4 x[kOwn];
 #pragma unroll
-        for (int j = 0; j < 16; ++j)      // (clamped slots are ignored below)
-            ml[j] = ((const float4 *)part_ml)[(size_t)(slot0 + min(s0 + j, live_splits - 1)) * m_pad + row];
+        for (int j = 0; j < kOwn; ++j) {
+            const int s = s0 + 16 * j + sub;
+            x[j] = s < live_splits ? ml[(size_t)s * m_pad] : make_float4(-INFINITY, 0.f, -INFINITY, 0.f);
+        }
         float m_new = m_raw;
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (s0 + j < live_splits) m_new = fmaxf(m_new, ml[j].z);
+        for (int j = 0; j < kOwn; ++j) m_new = fmaxf(m_new, x[j].z);
+        m_new = row16_reduce<MaxOp>(m_new);
         l *= m_raw == -INFINITY ? 0.f : exp2f((m_raw - m_new) * c2);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if (s0 + j >= live_splits) continue;
-            l = fmaf(ml[j].x == -INFINITY ? 0.f : exp2f((ml[j].x - m_new) * c2), ml[j].y, l);
-        }
+        for (int j = 0; j < kOwn; ++j) l = fmaf(x[j].x == -INFINITY ? 0.f : exp2f((x[j].x - m_new) * c2), x[j].y, l);
         m_raw = m_new;
     }
-    row_const[crow * 4 + 0] = 2.0f * (m_raw * c2 + log2f(l));   // A_ip^2 = exp2(2 log2e Z_ip - this)
-    row_const[crow * 4 + 2] = __int_as_float(len - W + (row % W));
+    l = row16_reduce<SumOp>(l);
+    if (sub != 0) return;
+    const size_t crow = (size_t)bg * m_pad + row;
+    special[crow * 4 + 0] = __int_as_float(-1);       // no separately scored (row, token) pair
+    // A_ip^2 = exp2(2 log2e Z_ip - the first); padded rows are weightless in the second sweep
+    ((float4 *)row_const)[crow] = row < M ? make_float4(2.0f * (m_raw * c2 + log2f(l)), 0.f, __int_as_float(len - W + (row % W)), 0.f)
+                                          : make_float4(1e30f, 0.f, __int_as_float(-1), 0.f);
 }
 
-// Variants that need o_i (Eq. 5, 6): the same grid.  Every split reports, per row, its sums without its
+// Variants that need o_i (Eq. 5, 6).  Every split reports, per row, its sums without its
 // candidate key and the candidate itself.  The candidate with the largest logit (the first split on
 // ties) stays held out; the others are ordinary keys and are added back from the value cache.  With
 // l' and O' the sums over every key but that one, relative to a common reference T,
@@ -1254,35 +1236,59 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
 
 }  // namespace
 
-// Tokens one workgroup should take of every KV head's sequence, so that the launch keeps the chip evenly busy.  `slots`
-// workgroups run at a time and `heads` of them walk each sequence side by side; a launch of a few workgroups more than
-// the slots would take twice as long, and sequences shorter than N leave slots idle.  Among the lengths that fill one to
-// eight rounds of the slots, the one with the least rounds x (length + kStart) is taken; kStart stands for what a
-// workgroup does before its first and after its last token.
-static int even_share(const int *len, int B, int N, int heads, int slots, int min_len) {
-    constexpr int kUnit = kTileTok, kStart = 256;
+// Tokens one workgroup should take of every KV head's sequence.  `heads` workgroups walk each sequence side by side.  Among
+// the shortest shares whose workgroups fit one to sixteen times the compute units, the one with the least estimated time is
+// taken, counted in the time a workgroup alone on its compute unit spends on a token:
+//   start   what it does before its first and after its last token
+//   pairs   two workgroups share a compute unit where there are that many; each then takes `crowd` times as long for a token
+//           and `crowd_start` for its start
+//   record  what the combine step spends on the partial records of every further 256 workgroups
+// First sweep, us, workgroups x tokens: 256 x 128 11.0, 256 x 256 15.6, 256 x 512 22.5, 256 x 1024 38.8, 256 x 2048 69.5,
+// 256 x 4096 130; 512 x 256 25.7, 512 x 512 38.7, 512 x 1024 65.7, 512 x 2048 121, and 3 us more in the combine step: one
+// round of 256 up to some 1800 tokens, from where on the bytes in flight of a second workgroup pay.  Without output sums 256 x 256
+// 8.9, 256 x 512 12.9, 256 x 1024 21.9, 256 x 4096 75; 512 x 512 19.0, 512 x 2048 58.
+// (With shares of at least 512 tokens, and else all 512 places filled whatever the length, whole calls took: 8 heads x 8K, all
+// 47.7 us, now 44.2; 8 x 2K 40.2, now 31.9; 8 x 1000 38.8, now 28.2; 4 heads x 20000, 224 rows, 64.8, now 60.4.)
+struct ShareCost { int unit, start; bool pairs; float crowd; int crowd_start, record; };
+constexpr ShareCost kSweep1Cost = {128, 230, true, 1.79f, 330, 85}, kSweep1SumsCost = {128, 310, true, 1.51f, 320, 20},
+                    kSweep2Cost = {64, 500, true, 1.85f, 500, 0}, kSweep2WideCost = {64, 400, false, 0.f, 0, 0},
+                    kSweep2SoloCost = {128, 400, false, 0.f, 0, 0};
+static bool needs_output(int variant) { return variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL; }
+static size_t record_bytes(int m_pad, int variant) { return (size_t)(m_pad < 128 ? m_pad : 128) * (16 + (needs_output(variant) ? kD * 4 : 0)); }
+static const ShareCost &sweep1_cost(int variant) { return needs_output(variant) ? kSweep1Cost : kSweep1SumsCost; }
+// `record_bytes`: of a workgroup's partial records; with more than the fewest workgroups they take at most kMostRecords, so
+// that plans that fit the static scratch go on doing so.
+constexpr size_t kMostRecords = (size_t)36 << 20;
+static int even_share(const int *len, int B, int N, int heads, const ShareCost &c, size_t record_bytes = 0) {
+    constexpr int kUnits = 256;                                                // compute units
     auto workgroups = [&](int share) {
         long long n = 0;
         if (!len) return (long long)heads * B * ((N + share - 1) / share);
         for (int b = 0; b < B; ++b) n += (len[b] + share - 1) / share;
         return n * heads;
     };
-    const int lo_unit = min_len / kUnit, hi_unit = (N + kUnit - 1) / kUnit;
+    auto cost = [&](int share) {
+        const long long n = workgroups(share);
+        const float records = (float)c.record * (float)((n + kUnits - 1) / kUnits);
+        if (c.pairs && n > kUnits) return (float)((n + 2 * kUnits - 1) / (2 * kUnits)) * (c.crowd * share + c.crowd_start) + records;
+        return (float)((n + kUnits - 1) / kUnits) * (float)(share + c.start) + records;
+    };
+    const int most = (N + c.unit - 1) / c.unit;
     int best = 0;
-    long long best_cost = 0;
-    for (int rounds = 1; rounds <= 8; ++rounds) {
-        int lo = lo_unit, hi = hi_unit > lo_unit ? hi_unit : lo_unit;          // the shortest share that fits, if any does
-        if (workgroups(hi * kUnit) > (long long)rounds * slots) continue;
+    float best_cost = 0.f;
+    for (int rounds = 1; rounds <= 16; ++rounds) {
+        int lo = 1, hi = most;                                                 // the shortest share that fits, if any does
+        if (workgroups(hi * c.unit) > (long long)rounds * kUnits) continue;
         while (lo < hi) {
             const int mid = (lo + hi) / 2;
-            if (workgroups(mid * kUnit) <= (long long)rounds * slots) hi = mid; else lo = mid + 1;
+            if (workgroups(mid * c.unit) <= (long long)rounds * kUnits) hi = mid; else lo = mid + 1;
         }
-        const long long cost = (long long)rounds * (lo * kUnit + kStart);
-        if (best == 0 || cost < best_cost) { best = lo * kUnit; best_cost = cost; }
-        if (lo == lo_unit) break;
+        if (best != 0 && workgroups(lo * c.unit) * record_bytes > kMostRecords) break;
+        const float t = cost(lo * c.unit);
+        if (best == 0 || t < best_cost) { best = lo * c.unit; best_cost = t; }
+        if (lo == 1) break;
     }
-    if (best == 0) best = (hi_unit > lo_unit ? hi_unit : lo_unit) * kUnit;      // more sequences than eight rounds: one workgroup each
-    return best;
+    return best ? best : most * c.unit;                                        // more sequences than sixteen rounds: one workgroup each
 }
 
 void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWorkspace *ws, size_t *off) {
@@ -1291,7 +1297,7 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     const int nv = variant == OBC_ALL ? 3 : 1;
     const int M = Hq / Hkv * W, form = tuned_sweep2_form();
     ws->n_chunks = (ws->m_pad + 127) / 128;
-    ws->split_len = even_share(nullptr, B, N, Hkv * ws->n_chunks, 512, 512);
+    ws->split_len = even_share(nullptr, B, N, Hkv * ws->n_chunks, sweep1_cost(variant), record_bytes(ws->m_pad, variant));
     if (const int v = tuned_splits(); v >= 1 && v <= (N + 511) / 512)           // obc_set_score_tuning
         ws->split_len = ((N + v - 1) / v + kTileTok - 1) / kTileTok * kTileTok;
     ws->splits = (N + ws->split_len - 1) / ws->split_len;
@@ -1302,7 +1308,8 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     ws->row_const = *off; *off = align_up(*off + rows * 4 * sizeof(float), 256);
     ws->part_ml = *off;   *off = align_up(*off + rows * ws->splits * 4 * sizeof(float), 256);
     ws->special = *off;   *off = align_up(*off + rows * 4 * sizeof(float), 256);
-    ws->part_o = *off;    *off = align_up(*off + rows * ws->splits * d * sizeof(float), 256);
+    ws->part_o = *off;
+    if (needs_output(variant)) *off = align_up(*off + rows * ws->splits * d * sizeof(float), 256);
     ws->planes = *off;
     if (ws->n_chunks > 1) *off = align_up(*off + (size_t)ws->n_chunks * nv * BH * N * sizeof(float), 256);
     // With few rows the first sweep keeps their logits (4 bytes per pair) and the second reads them instead of K (256 bytes
@@ -1323,7 +1330,7 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
 static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
     const int *len = a.ragged ? a.lens.len : nullptr;
     if (len && tuned_splits() == 0) {
-        const int share = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, 512, 512);
+        const int share = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, sweep1_cost(a.variant), record_bytes(ws.m_pad, a.variant));
         int records = 0, most = 1;
         for (int b = 0; b < a.B; ++b) {
             const int n = (len[b] + share - 1) / share;
@@ -1333,8 +1340,8 @@ static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
         if (records <= a.B * ws.splits) { ws.split_len = share; ws.splits = most; }
     }
     const int full = ws.n_chunks - ws.solo;
-    ws.range_len = even_share(len, a.B, a.N, a.Hkv * (full > 0 ? full : 1), ws.use_wide ? 256 : 512, 128);
-    ws.range_solo = even_share(len, a.B, a.N, a.Hkv, 256, 128);
+    ws.range_len = even_share(len, a.B, a.N, a.Hkv * (full > 0 ? full : 1), ws.use_wide ? kSweep2WideCost : kSweep2Cost);
+    ws.range_solo = even_share(len, a.B, a.N, a.Hkv, kSweep2SoloCost);
     // (kept logits: the first sweep's splits, in whole workgroup steps of 256 tokens)
     if (ws.keep_z) ws.range_len = (ws.split_len + 255) / 256 * 256;
     else if (const int v = tuned_range(); v >= 64 && v <= 65536 && v % 64 == 0) ws.range_len = ws.range_solo = v;
@@ -1343,7 +1350,7 @@ static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
 
 template <typename Lens>
 static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
-    const bool need_o = a.variant == OBC_KEY || a.variant == OBC_JOINT || a.variant == OBC_ALL;
+    const bool need_o = needs_output(a.variant);
     float *part_ml = (float *)(base + ws.part_ml), *part_o = (float *)(base + ws.part_o);
     hipError_t e = hipSuccess;
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
@@ -1361,7 +1368,6 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
         if (e != hipSuccess) return e;
     }
     if (a.stage_mask & OBC_STAGE_COMBINE) {
-        const dim3 grid(ws.m_pad, a.B * a.Hkv);
 #define OBC_COMBINE(groups, batch, rows)                                                                               \
     mfma_combine_hold<groups, batch><<<dim3(ws.m_pad / rows, a.B * a.Hkv), dim3(32 * groups * rows), 0, stream>>>(            \
         (const uint16_t *)a.v, part_ml, part_o, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.m_pad,         \
@@ -1372,9 +1378,9 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
         else if (need_o) OBC_COMBINE(8, 16, 1);
 #undef OBC_COMBINE
         else
-            mfma_combine<<<grid, dim3(128), 0, stream>>>(
-                part_ml, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.m_pad,
-                (uint16_t *)(base + ws.out_bf16), (float *)(base + ws.row_const), (float *)(base + ws.special));
+            mfma_combine<<<dim3(ws.m_pad / 16, a.B * a.Hkv), dim3(256), 0, stream>>>(
+                part_ml, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.m_pad, (float *)(base + ws.row_const),
+                (float *)(base + ws.special));
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
