@@ -1250,16 +1250,23 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
 // (With shares of at least 512 tokens, and else all 512 places filled whatever the length, whole calls took: 8 heads x 8K, all
 // 47.7 us, now 44.2; 8 x 2K 40.2, now 31.9; 8 x 1000 38.8, now 28.2; 4 heads x 20000, 224 rows, 64.8, now 60.4.)
 struct ShareCost { int unit, start; bool pairs; float crowd; int crowd_start, record; };
+// Windows of at most eight rows keep one wave of a workgroup busy, and a second workgroup costs the first less: 8 heads, G = 1,
+// 4 x 7429 ragged 25.4 us on 224 workgroups, 21.4 on 448; x 60000, G = 4 52.6 on 240, 44.2 on 472.  The kernel after it always
+// wants both places: 18.3 us on 240 workgroups and 14.0 on 352.
 constexpr ShareCost kSweep1Cost = {128, 230, true, 1.79f, 330, 85}, kSweep1SumsCost = {128, 310, true, 1.51f, 320, 20},
+                    kSweep1FewCost = {128, 330, true, 1.55f, 400, 10}, kFewRowsCost = {256, 300, true, 1.f, 300, 0},
                     kSweep2Cost = {64, 500, true, 1.85f, 500, 0}, kSweep2WideCost = {64, 400, false, 0.f, 0, 0},
                     kSweep2SoloCost = {128, 400, false, 0.f, 0, 0};
+constexpr float kLaunchCost = 80.f;            // of a launch behind another one, 2 us
 static bool needs_output(int variant) { return variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL; }
 static size_t record_bytes(int m_pad, int variant) { return (size_t)(m_pad < 128 ? m_pad : 128) * (16 + (needs_output(variant) ? kD * 4 : 0)); }
-static const ShareCost &sweep1_cost(int variant) { return needs_output(variant) ? kSweep1Cost : kSweep1SumsCost; }
+static const ShareCost &sweep1_cost(int variant, int rows) {
+    return rows <= kFewRows ? kSweep1FewCost : needs_output(variant) ? kSweep1Cost : kSweep1SumsCost;
+}
 // `record_bytes`: of a workgroup's partial records; with more than the fewest workgroups they take at most kMostRecords, so
 // that plans that fit the static scratch go on doing so.
 constexpr size_t kMostRecords = (size_t)36 << 20;
-static int even_share(const int *len, int B, int N, int heads, const ShareCost &c, size_t record_bytes = 0) {
+static int even_share(const int *len, int B, int N, int heads, const ShareCost &c, size_t record_bytes = 0, float *least_cost = nullptr) {
     constexpr int kUnits = 256;                                                // compute units
     auto workgroups = [&](int share) {
         long long n = 0;
@@ -1288,7 +1295,9 @@ static int even_share(const int *len, int B, int N, int heads, const ShareCost &
         if (best == 0 || t < best_cost) { best = lo * c.unit; best_cost = t; }
         if (lo == 1) break;
     }
-    return best ? best : most * c.unit;                                        // more sequences than sixteen rounds: one workgroup each
+    if (!best) { best = most * c.unit; best_cost = cost(best); }               // more sequences than sixteen rounds: one workgroup each
+    if (least_cost) *least_cost = best_cost;
+    return best;
 }
 
 void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWorkspace *ws, size_t *off) {
@@ -1297,7 +1306,7 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     const int nv = variant == OBC_ALL ? 3 : 1;
     const int M = Hq / Hkv * W, form = tuned_sweep2_form();
     ws->n_chunks = (ws->m_pad + 127) / 128;
-    ws->split_len = even_share(nullptr, B, N, Hkv * ws->n_chunks, sweep1_cost(variant), record_bytes(ws->m_pad, variant));
+    ws->split_len = even_share(nullptr, B, N, Hkv * ws->n_chunks, sweep1_cost(variant, M), record_bytes(ws->m_pad, variant));
     if (const int v = tuned_splits(); v >= 1 && v <= (N + 511) / 512)           // obc_set_score_tuning
         ws->split_len = ((N + v - 1) / v + kTileTok - 1) / kTileTok * kTileTok;
     ws->splits = (N + ws->split_len - 1) / ws->split_len;
@@ -1330,7 +1339,7 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
 static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
     const int *len = a.ragged ? a.lens.len : nullptr;
     if (len && tuned_splits() == 0) {
-        const int share = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, sweep1_cost(a.variant), record_bytes(ws.m_pad, a.variant));
+        const int share = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, sweep1_cost(a.variant, a.G * a.W), record_bytes(ws.m_pad, a.variant));
         int records = 0, most = 1;
         for (int b = 0; b < a.B; ++b) {
             const int n = (len[b] + share - 1) / share;
@@ -1339,11 +1348,20 @@ static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
         }
         if (records <= a.B * ws.splits) { ws.split_len = share; ws.splits = most; }
     }
-    const int full = ws.n_chunks - ws.solo;
-    ws.range_len = even_share(len, a.B, a.N, a.Hkv * (full > 0 ? full : 1), ws.use_wide ? kSweep2WideCost : kSweep2Cost);
-    ws.range_solo = even_share(len, a.B, a.N, a.Hkv, kSweep2SoloCost);
-    // (kept logits: the first sweep's splits, in whole workgroup steps of 256 tokens)
-    if (ws.keep_z) ws.range_len = (ws.split_len + 255) / 256 * 256;
+    int full = ws.n_chunks - ws.solo;
+    float wide = 0.f, solo = 0.f, padded = 0.f;
+    const ShareCost &cost = ws.use_wide ? kSweep2WideCost : kSweep2Cost;
+    ws.range_len = even_share(len, a.B, a.N, a.Hkv * (full > 0 ? full : 1), cost, 0, &wide);
+    ws.range_solo = even_share(len, a.B, a.N, a.Hkv, kSweep2SoloCost, 0, &solo);
+    // A last chunk of at most 64 rows behind full ones: a launch of its own spends 0.7 of the time on a token and a start of its
+    // own; on short prompts that start costs more than the empty half of a 128-row chunk.  408 rows, 4 x 4 heads x 3507 ragged,
+    // key: 27.9 + 12.7 us, as four chunks 32.1; 168 rows, 4 heads x 20000, all: 21.0 + 16.0, as two 29.8; x 60000, joint: 39.9 +
+    // 29.0, as two 66.5.
+    if (ws.solo && full > 0) {
+        const int range = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, cost, 0, &padded);
+        if (padded < wide + 0.7f * solo + kLaunchCost) { ws.solo = 0; ws.range_len = range; }
+    }
+    if (ws.keep_z) ws.range_len = even_share(len, a.B, a.N, a.Hkv, kFewRowsCost);        // (whole steps of its workgroups)
     else if (const int v = tuned_range(); v >= 64 && v <= 65536 && v % 64 == 0) ws.range_len = ws.range_solo = v;
     return ws;
 }
