@@ -551,7 +551,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const float *__restri
 //                   slices before it keep
 // No global atomics and nothing to clear; every workgroup of a group repeats the integer sums.  Bound by the launches
 // and their memory round trips (a 4 x 128K selection reads 2 MB): five kernels with a histogram of the whole slice per
-// digit took 52 us there, these three take 21.
+// digit took 52 us there, these three take 20.
 // ------------------------------------------------------------------------------------
 struct SliceState {      // of a group, written by slices_collect
     uint32_t digit;      // first digit of the threshold
@@ -619,7 +619,8 @@ __device__ __forceinline__ void store_keys(const Slices &S, const SlicePlace &at
         *(uint4 *)(S.keys + (size_t)at.head * S.key_stride + i0) = make_uint4(key[0], key[1], key[2], key[3]);
 }
 
-template <int kBatch, typename Lens>
+// kPacked: counters of 16 bits, two neighbours to a word (slices of at most kPackedChunks chunks).
+template <int kBatch, bool kPacked, typename Lens>
 __global__ __launch_bounds__(kSelThreads) void slices_count(const float *__restrict__ scores, int N, int Hkv, int ragged, Lens lens,
                                                             int first, int tail, int radius, Slices S) {
     __shared__ __attribute__((aligned(16))) int hist[kSliceBins];
@@ -637,8 +638,9 @@ __global__ __launch_bounds__(kSelThreads) void slices_count(const float *__restr
         }
     });
     __syncthreads();
-    int *dst = S.hist + at.flat() * kSliceBins;
-    *(int2 *)(dst + 2 * threadIdx.x) = *(const int2 *)(hist + 2 * threadIdx.x);
+    const int2 two = *(const int2 *)(hist + 2 * threadIdx.x);
+    if constexpr (kPacked) ((uint32_t *)S.hist)[at.flat() * (kSliceBins / 2) + threadIdx.x] = (uint32_t)two.x | (uint32_t)two.y << 16;
+    else *(int2 *)(S.hist + at.flat() * kSliceBins + 2 * threadIdx.x) = two;
 }
 
 template <int kBatch, typename Lens>
@@ -796,14 +798,13 @@ __device__ __forceinline__ SliceThreshold slice_threshold(SliceShared &sh, const
     int gt_before = 0, gt_head = 0, eq_first = 0, eq_before = 0, eq_head = 0;
     const int p_head0 = few ? sh.offset[head0] : 0, p_slice = few ? sh.offset[at.slice] : 0, p_head1 = few ? sh.offset[head1] : 0;
     auto tally = [&](uint32_t key, bool before_head, bool before_slice, bool in_head) {
-        if (key > t.thr) {
-            gt_head += in_head ? 1 : 0;
-            gt_before += in_head && before_slice ? 1 : 0;
-        } else if (key == t.thr) {
-            eq_first += before_head ? 1 : 0;
-            eq_before += before_slice ? 1 : 0;
-            eq_head += in_head ? 1 : 0;
-        }
+        // (branches here became sums through selected addresses, in scratch memory)
+        const int gt = key > t.thr ? 1 : 0, eq = key == t.thr ? 1 : 0;
+        gt_head += in_head ? gt : 0;
+        gt_before += in_head & before_slice ? gt : 0;
+        eq_first += before_head ? eq : 0;
+        eq_before += before_slice ? eq : 0;
+        eq_head += in_head ? eq : 0;
     };
     if (in_lds) for (int j = tid; j < n_list; j += kSelThreads) tally(sh.list[j], j < p_head0, j < p_slice, j >= p_head0 && j < p_head1);
     else visit_global([&](uint32_t key, int sl, int) { tally(key, sl < head0, sl < at.slice, sl >= head0 && sl < head1); });
@@ -864,7 +865,8 @@ __global__ __launch_bounds__(kSelThreads) void slices_emit(const float *__restri
 // slices_collect find every head's class for n_safe; the kernel below finishes that selection and
 // turns the slice's scores into the keys of the second one (live tokens >= 1, 0 for positions
 // beyond the true length, 0xffffffff for the safeguard), with their histogram; then
-// slices_collect and slices_emit run over all heads of a sequence as one group.
+// slices_collect and slices_emit run over all heads of a sequence as one group.  For many heads or long ones, and where the
+// safeguard is the whole budget; the others take the three kernels after these.
 // ------------------------------------------------------------------------------------
 template <int kBatch, typename Lens>
 __global__ __launch_bounds__(kSelThreads) void slices_safeguard(const float *__restrict__ scores, int N, int n_safe, int Hkv, int ragged,
@@ -920,6 +922,407 @@ __global__ __launch_bounds__(kSelThreads) void slices_safeguard(const float *__r
     __syncthreads();
     int *dst = hist_out + at.flat() * kSliceBins;
     *(int2 *)(dst + 2 * threadIdx.x) = *(const int2 *)(hist + 2 * threadIdx.x);
+}
+
+// ------------------------------------------------------------------------------------
+// The same for few heads, without a first selection.  A head keeps max(n_safe, its keys above the common threshold T), so T
+// is the largest value at which the sum of those maxima over the heads reaches the budget, and the histograms of
+// slices_count give T's class.  By the class, a head
+//   has its safeguard above it: it keeps its keys above T;
+//   falls short of its safeguard even with the whole class: it keeps its own top n_safe and stands apart;
+//   holds the end of its safeguard in the class: the safeguard's keys there are kept in any case and do not compete.
+// adaptive_collect leaves one class of every head, the common one or, apart, the one its own n_safe-th key is in;
+// adaptive_emit finishes both kinds from the lists.  Three kernels where the selection of the safeguard first takes five;
+// bound, as they are, by launches and round trips: 2 x 8 heads of up to 24001 scores, budget 1024, 38.4 -> 24.3 us on the device
+// (count 4.7, collect 10.1, emit 9.5), and with the copying of the rows 48.6 -> 33.8; 8 heads of 90K, budget 4096, 77.8 ->
+// 51.7; 4 x 32 heads of 4000, budget 400, 103 -> 101.
+// ------------------------------------------------------------------------------------
+// Most heads (a workgroup finishes a safeguard per wave, the bookkeeping is a lane per head); the gain has shrunk to a
+// few percent there, as every workgroup goes through all heads' histograms one by one.
+constexpr int kFewHeads = 32;
+constexpr int kPackedChunks = 8;         // chunks of a slice whose counters stay below 2^16
+
+struct HeadState {       // written by adaptive_collect
+    uint32_t digit;      // class of the head's list
+    int above;           // keys of the head above it
+    int safe_rank;       // rank of the safeguard's last key inside it (0: the safeguard lies above)
+    int apart;
+};
+
+// Sums of the heads' histograms, two counters per thread, and how many of their keys lie in the counters of higher threads,
+// for kHeads heads at a time.
+template <int kHeads>
+struct HeadSuffix {
+    static constexpr int kAhead = 6;                         // slices of each head in flight at once
+    int2 c[kHeads];
+    int above[kHeads];
+    uint32_t x[kAhead][kHeads];
+    // hist: of the first head.  (A head too many reads the last one's: no branch between the loads.)
+    __device__ __forceinline__ void fetch(const uint32_t *__restrict__ hist, int heads, int per_head, int s0) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+            for (int h = 0; h < kHeads; ++h) {
+                const int sl = min(h, heads - 1) * per_head + min(s0 + i, per_head - 1);
+                x[i][h] = hist[(size_t)sl * (kSliceBins / 2) + threadIdx.x];
+            }
+    }
+    // The first slices have been fetched.
+    __device__ __forceinline__ void sum(const uint32_t *__restrict__ hist, int heads, int per_head) {
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) c[h] = make_int2(0, 0);
+        for (int s0 = 0; s0 < per_head; s0 += kAhead) {
+            if (s0 > 0) fetch(hist, heads, per_head, s0);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                if (s0 + i >= per_head) continue;            // uniform
+#pragma unroll
+                for (int h = 0; h < kHeads; ++h) { c[h].x += x[i][h] & 0xffff; c[h].y += x[i][h] >> 16; }
+            }
+        }
+    }
+    __device__ __forceinline__ void scan(int (&tot)[kHeads][kSelWaves]) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        __syncthreads();                                     // (the totals of the heads before these have been read)
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) {
+            const int mine = c[h].x + c[h].y, incl = wave_scan<true>(mine, lane);
+            above[h] = incl - mine;
+            if (lane == 0) tot[h][wave] = incl;
+        }
+        __syncthreads();
+        static_assert(kHeads <= kSelWaves && kSelWaves == 16, "a wave per head, its totals in one row of lanes");
+        if (wave < kHeads) {                                 // totals -> totals of the higher waves
+            const int x = lane < kSelWaves ? tot[wave][lane] : 0, incl = wave_scan<true>(x, lane);
+            if (lane < kSelWaves) tot[wave][lane] = incl - x;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) above[h] += tot[h][wave];
+    }
+};
+
+// Grid: x = slice of the sequence's heads, y = sequence.
+template <int kBatch, typename Lens>
+__global__ __launch_bounds__(kSelThreads) void adaptive_collect(const float *__restrict__ scores, int N, int budget, int n_safe,
+                                                                int Hkv, int ragged, Lens lens, Slices S,
+                                                                HeadState *__restrict__ states) {
+    constexpr int kHeads = 8;
+    __shared__ int tot[kHeads][kSelWaves];
+    __shared__ uint32_t common, own_class;
+    __shared__ int safe_rank_s;
+    __shared__ HeadState own;
+    __shared__ int n_list, n_above;
+    const SlicePlace at(S, N, Hkv, ragged, lens);
+    const int tid = threadIdx.x, lane = tid & 63, own_head = at.slice / S.per_head;
+    if (tid == 0) { n_list = 0; n_above = 0; }
+    const uint32_t *hist = (const uint32_t *)S.hist + (size_t)at.group * gridDim.x * (kSliceBins / 2);
+    HeadSuffix<kHeads> hs;
+    hs.fetch(hist, S.heads, S.per_head, 0);
+    auto classes = [&]() {
+        // F(d) = sum over the heads of max(n_safe, keys with a first digit >= d), at the thread's two digits and past them
+        long long f0 = 0, f1 = 0, f2 = 0;
+        int own_above = 0;
+        int2 own_c = make_int2(0, 0);
+        for (int h0 = 0; h0 < S.heads; h0 += kHeads) {
+            const uint32_t *first = hist + (size_t)h0 * S.per_head * (kSliceBins / 2);
+            if (h0 > 0) hs.fetch(first, S.heads - h0, S.per_head, 0);
+            hs.sum(first, S.heads - h0, S.per_head);
+            hs.scan(tot);
+#pragma unroll
+            for (int h = 0; h < kHeads; ++h) {
+                if (h0 + h >= S.heads) continue;             // uniform
+                const int a2 = hs.above[h], a1 = a2 + hs.c[h].y, a0 = a1 + hs.c[h].x;
+                f2 += max(n_safe, a2);
+                f1 += max(n_safe, a1);
+                f0 += max(n_safe, a0);
+                if (h0 + h == own_head) { own_above = a2; own_c = hs.c[h]; }
+            }
+        }
+        const long long total = (long long)S.heads * budget;
+        if (f2 < total && f0 >= total) common = 2 * tid + (f1 >= total ? 1 : 0);         // exactly one thread
+        if (own_above < n_safe && n_safe <= own_above + own_c.y + own_c.x) {              // likewise, with a safeguard
+            const bool upper = n_safe <= own_above + own_c.y;
+            own_class = 2 * tid + (upper ? 1 : 0);
+            safe_rank_s = n_safe - own_above - (upper ? 0 : own_c.y);
+        }
+        __syncthreads();
+        const uint32_t cls = common;
+        if ((int)(cls >> 1) == tid) {
+            const int above = own_above + ((cls & 1) ? 0 : own_c.y), in_class = (cls & 1) ? own_c.y : own_c.x;
+            if (above + in_class < n_safe) own = HeadState{own_class, n_safe - safe_rank_s, safe_rank_s, 1};
+            else own = HeadState{cls, above, max(n_safe - above, 0), 0};
+            if (at.in_head == 0) states[at.head] = own;
+        }
+        __syncthreads();
+    };
+    uint32_t *list = S.list + at.flat() * S.list_stride;
+    for_batches<kBatch>(S, at, scores, N, 0, 0, 0, false, classes, [&](uint32_t (&keys)[kBatch][kItems], int c) {
+        const uint32_t digit = own.digit;
+        int mine = 0;                                        // low 16 bits: in the class, high 16 bits: above it
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+#pragma unroll
+            for (int e = 0; e < kItems; ++e) {
+                const bool in = c + i < at.c1 && (c + i) * kChunk + tid * kItems + e < at.len;
+                const uint32_t d = keys[i][e] >> (32 - kSliceBits);
+                mine += in && d == digit ? 1 : in && d > digit ? 0x10000 : 0;
+            }
+        const int incl = wave_scan<false>(mine, lane);
+        int base = 0;
+        if (lane == 63 && incl != 0) {
+            base = atomicAdd(&n_list, incl & 0xffff);
+            atomicAdd(&n_above, incl >> 16);
+        }
+        int pos = __builtin_amdgcn_readlane(base, 63) + ((incl - mine) & 0xffff);
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+#pragma unroll
+            for (int e = 0; e < kItems; ++e) {
+                const bool in = c + i < at.c1 && (c + i) * kChunk + tid * kItems + e < at.len;
+                if (in && (keys[i][e] >> (32 - kSliceBits)) == digit) list[pos++] = keys[i][e];
+            }
+    });
+    __syncthreads();
+    if (tid == 0) { S.count[at.flat()] = n_list; S.above[at.flat()] = n_above; }
+}
+
+constexpr int kAdaptiveList = 14336;     // keys of all heads' lists that fit LDS beside the counters, two workgroups to a compute unit
+
+struct AdaptiveShared {
+    using D = Digits<kSliceBits>;
+    int hist1[D::kBins1], hist2[D::kBins2];
+    uint32_t list[kAdaptiveList];
+    int count[kMaxGroupSlices], offset[kMaxGroupSlices + 1];
+    HeadState head[kFewHeads];
+    uint32_t safe_thr[kFewHeads];        // of the heads whose safeguard ends inside the common class: its last key
+    int safe_eq[kFewHeads];              // and how many keys equal to that belong to it
+    PickShared pick;
+    int above_before, gt_before, gt_head, eq_before_heads, eq_before, eq_head;
+};
+
+// The key of rank *rank among the keys of a class, by one wave: three digits of 7 bits over what is left of a key below its
+// first digit.  visit(f) calls f(key) for the lane's share.  hist: 128 counters of the wave's own.  Leaves in *rank how many
+// keys equal to it there are down to that rank.
+template <typename Visit>
+__device__ __forceinline__ uint32_t wave_select(int *hist, uint32_t key, int *rank, Visit &&visit) {
+    constexpr int kBits = 7;
+    static_assert(3 * kBits == 32 - kSliceBits, "three digits below the first one");
+    const int lane = threadIdx.x & 63;
+    auto ordered = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); };
+#pragma unroll
+    for (int shift = 2 * kBits; shift >= 0; shift -= kBits) {
+        *(int2 *)(hist + 2 * lane) = make_int2(0, 0);
+        ordered();
+        visit([&](uint32_t k) { if ((k ^ key) >> (shift + kBits) == 0) atomicAdd(&hist[(k >> shift) & 127], 1); });
+        ordered();
+        const int2 c = *(const int2 *)(hist + 2 * lane);
+        const int incl = wave_scan<true>(c.x + c.y, lane), above = incl - c.x - c.y;
+        const unsigned long long at = __ballot(above < *rank && *rank <= incl);      // one lane
+        const bool upper = *rank <= above + c.y;
+        const int from = at ? __ffsll(at) - 1 : 0;
+        const int digit = __shfl(2 * lane + (upper ? 1 : 0), from), less = __shfl(above + (upper ? 0 : c.y), from);
+        key |= (uint32_t)digit << shift;
+        *rank -= less;
+    }
+    return key;
+}
+
+// What adaptive_emit needs of a slice: the threshold its head's keys are kept by, how many equal to it, and what lies before.
+struct HeadThreshold { uint32_t thr; int need_eq, gt_before, eq_before, kept; };
+
+__device__ __forceinline__ HeadThreshold head_threshold(AdaptiveShared &sh, const Slices &S, const SlicePlace &at, int n_safe, int budget) {
+    using D = Digits<kSliceBits>;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = gridDim.x, own_head = at.slice / S.per_head;
+    const int head0 = own_head * S.per_head, head1 = head0 + S.per_head;
+    clear_counters<D::kBins1>(sh.hist1);
+    clear_counters<D::kBins2>(sh.hist2);
+    if (tid == 0) sh.above_before = sh.gt_before = sh.gt_head = sh.eq_before_heads = sh.eq_before = sh.eq_head = 0;
+    __syncthreads();
+    const HeadState own = sh.head[own_head];
+    // The lists that count: of the head alone where it stands apart, else of all heads that do not.
+    if (wave == 0) {
+        int base = 0;
+        for (int s0 = 0; s0 < n; s0 += 64) {
+            const int sl = s0 + lane;
+            int c = 0;
+            if (sl < n && (own.apart ? sl >= head0 && sl < head1 : sh.head[sl / S.per_head].apart == 0)) c = sh.count[sl];
+            if (sl < n) sh.count[sl] = c;
+            const int incl = wave_scan<false>(c, lane);
+            if (sl < n) sh.offset[sl] = base + incl - c;
+            base += __builtin_amdgcn_readlane(incl, 63);
+        }
+        if (lane == 0) sh.offset[n] = base;
+    } else if (wave == 1) {                                  // keys above the class in the head's earlier slices
+        int before = 0;
+        for (int sl = head0 + lane; sl < at.slice; sl += 64) before += S.above[(size_t)at.group * n + sl];
+        before = (int)wave_reduce<SumOp>((uint32_t)before);
+        if (lane == 0) sh.above_before = before;
+    }
+    // What the lists decide between themselves (the budget less what the heads keep in any case), and whether a safeguard
+    // ends inside the common class.
+    int remaining = own.safe_rank, n_equal;
+    bool any_safe = false;
+    if (!own.apart) {
+        const bool head = lane < S.heads;
+        const HeadState st = sh.head[head ? lane : 0];
+        static_assert(kFewHeads <= 64, "a lane per head");
+        any_safe = __ballot(head && !st.apart && st.safe_rank > 0) != 0ull;
+        const int sure = !head ? 0 : st.apart ? n_safe : st.above + st.safe_rank;       // (at most heads * budget in all)
+        remaining = (int)((uint32_t)S.heads * budget - wave_reduce<SumOp>((uint32_t)sure));
+    }
+    auto safe_of = [&](int h) { return any_safe && sh.head[h].apart == 0 && sh.head[h].safe_rank > 0; };
+    __syncthreads();
+    const int n_list = sh.offset[n], p_head0 = sh.offset[head0], p_slice = sh.offset[at.slice], p_head1 = sh.offset[head1];
+    const bool in_lds = n_list <= kAdaptiveList;             // uniform
+    const uint32_t *lists = S.list + (size_t)at.group * n * S.list_stride;
+    if (in_lds) {
+        constexpr int kAhead = 4;                            // slices of a wave in flight at once
+        for (int s0 = wave; s0 < n; s0 += kAhead * kSelWaves) {
+            uint32_t key[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int sl = s0 + u * kSelWaves;
+                key[u] = sl < n && lane < sh.count[sl] ? lists[(size_t)sl * S.list_stride + lane] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int sl = s0 + u * kSelWaves;
+                if (sl >= n) continue;                       // uniform
+                const int c = sh.count[sl], o = sh.offset[sl];
+                if (lane < c) sh.list[o + lane] = key[u];
+                for (int i = 64 + lane; i < c; i += 64) sh.list[o + i] = lists[(size_t)sl * S.list_stride + i];
+            }
+        }
+        __syncthreads();
+    }
+    // Safeguards that end inside the common class, a wave per head; their keys leave the competition: as 0, which no key
+    // is, but for those equal to the last one.
+    if (any_safe) {                                          // uniform
+        static_assert(D::kBins1 == kSelWaves * 128, "counters of wave_select");
+        for (int h = wave; h < S.heads; h += kSelWaves) {
+            if (!safe_of(h)) continue;                       // uniform in the wave
+            const int j0 = sh.offset[h * S.per_head], j1 = sh.offset[(h + 1) * S.per_head];
+            int rank = sh.head[h].safe_rank;
+            const uint32_t thr = wave_select(sh.hist1 + 128 * wave, sh.head[h].digit << (32 - kSliceBits), &rank, [&](auto &&f) {
+                if (in_lds) {
+#pragma unroll 4
+                    for (int j = j0 + lane; j < j1; j += 64) f(sh.list[j]);
+                } else {
+                    for (int sl = h * S.per_head; sl < (h + 1) * S.per_head; ++sl) {
+                        const uint32_t *src = lists + (size_t)sl * S.list_stride;
+                        const int c = sh.count[sl];
+#pragma unroll 8
+                        for (int i = lane; i < c; i += 64) f(src[i]);
+                    }
+                }
+            });
+            if (lane == 0) { sh.safe_thr[h] = thr; sh.safe_eq[h] = rank; }
+            if (in_lds)
+                for (int j = j0 + lane; j < j1; j += 64)
+                    if (sh.list[j] > thr) sh.list[j] = 0u;
+        }
+        __syncthreads();
+        clear_counters<D::kBins1>(sh.hist1);
+        __syncthreads();
+    }
+    // f(key, place) over the lists; key 0: of a safeguard
+    auto visit = [&](auto &&f) {
+        if (in_lds) {
+            for (int j = tid; j < n_list; j += kSelThreads) f(sh.list[j], j);
+        } else {
+            for (int sl = wave; sl < n; sl += kSelWaves) {
+                const uint32_t *src = lists + (size_t)sl * S.list_stride;
+                const int c = sh.count[sl], o = sh.offset[sl], h = sl / S.per_head;
+                const uint32_t most = safe_of(h) ? sh.safe_thr[h] : 0xffffffffu;
+                for (int i = lane; i < c; i += 64) {
+                    const uint32_t key = src[i];
+                    f(key > most ? 0u : key, o + i);
+                }
+            }
+        }
+    };
+    // keys equal to a safeguard's last one that belong to it, taken off a digit's counters
+    auto take_off = [&](int *hist, int shift, uint32_t bins, auto &&counted) {
+        if (!any_safe) return;                               // uniform
+        __syncthreads();
+        if (tid < S.heads && safe_of(tid) && counted(sh.safe_thr[tid])) atomicSub(&hist[(sh.safe_thr[tid] >> shift) & (bins - 1)], sh.safe_eq[tid]);
+    };
+    uint32_t digit;
+    visit([&](uint32_t key, int) { if (key) atomicAdd(&sh.hist1[(key >> D::kShift1) & (D::kBins1 - 1)], 1); });
+    take_off(sh.hist1, D::kShift1, D::kBins1, [](uint32_t) { return true; });
+    pick_digit<D::kBins1>(sh.hist1, sh.pick, &digit, &remaining, &n_equal);
+    const uint32_t middle = digit;
+    auto in_middle = [&](uint32_t key) { return ((key >> D::kShift1) & (D::kBins1 - 1)) == middle; };
+    visit([&](uint32_t key, int) { if (key && in_middle(key)) atomicAdd(&sh.hist2[key & (D::kBins2 - 1)], 1); });
+    take_off(sh.hist2, 0, D::kBins2, in_middle);
+    pick_digit<D::kBins2>(sh.hist2, sh.pick, &digit, &remaining, &n_equal);
+    const uint32_t common = (own.digit << (32 - kSliceBits)) | (middle << D::kShift1) | digit;
+    // The head keeps its safeguard alone where that ends below the threshold.
+    const bool safe_only = safe_of(own_head) && sh.safe_thr[own_head] < common;
+    HeadThreshold t;
+    t.thr = safe_only ? sh.safe_thr[own_head] : common;
+    int gt_before = 0, gt_head = 0, eq_heads = 0, eq_before = 0, eq_head = 0;
+    visit([&](uint32_t key, int j) {
+        const bool in_head = j >= p_head0 && j < p_head1;    // (no branches: as in slice_threshold)
+        const int gt = in_head & (key == 0u || key > t.thr) ? 1 : 0, eq = in_head & (key == t.thr) ? 1 : 0;
+        gt_head += gt;
+        eq_head += eq;
+        gt_before += j < p_slice ? gt : 0;
+        eq_before += j < p_slice ? eq : 0;
+        eq_heads += (j < p_head0) & (key == common) ? 1 : 0;
+    });
+    auto add = [&](int *to, int x) {
+        if (__ballot(x != 0) == 0ull) return;                // uniform
+        x = (int)wave_reduce<SumOp>((uint32_t)x);
+        if (lane == 0) atomicAdd(to, x);
+    };
+    add(&sh.gt_before, gt_before);
+    add(&sh.gt_head, gt_head);
+    add(&sh.eq_before_heads, eq_heads);
+    add(&sh.eq_before, eq_before);
+    add(&sh.eq_head, eq_head);
+    if (any_safe && tid < own_head && safe_of(tid) && sh.safe_thr[tid] == common) atomicSub(&sh.eq_before_heads, sh.safe_eq[tid]);
+    __syncthreads();
+    if (safe_only) {
+        t.need_eq = sh.safe_eq[own_head];
+    } else {                                                 // the safeguard's first, then as many as earlier heads leave
+        const int safe = safe_of(own_head) && sh.safe_thr[own_head] == common ? sh.safe_eq[own_head] : 0;
+        t.need_eq = safe + min(max(remaining - sh.eq_before_heads, 0), sh.eq_head - safe);
+    }
+    t.gt_before = sh.above_before + sh.gt_before;
+    t.eq_before = sh.eq_before;
+    t.kept = own.above + sh.gt_head + t.need_eq;
+    return t;
+}
+
+template <int kBatch, typename Lens>
+__global__ __launch_bounds__(kSelThreads) void adaptive_emit(const float *__restrict__ scores, int N, int budget, int n_safe, int room,
+                                                             int Hkv, int ragged, Lens lens, Slices S,
+                                                             const HeadState *__restrict__ states, int32_t *__restrict__ keep_idx,
+                                                             int32_t *__restrict__ counts) {
+    __shared__ __attribute__((aligned(16))) AdaptiveShared sh;
+    const SlicePlace at(S, N, Hkv, ragged, lens);
+    const int tid = threadIdx.x, n = gridDim.x;
+    const int count = tid < n ? S.count[(size_t)at.group * n + tid] : 0;      // (n <= kMaxGroupSlices: the host's choice)
+    if (tid < S.heads) sh.head[tid] = states[(size_t)at.group * S.heads + tid];
+    HeadThreshold t;
+    int32_t *out = keep_idx + (size_t)at.head * room;
+    int gt_base, eq_base;
+    for_batches<kBatch>(S, at, scores, N, 0, 0, 0, false, [&]() {
+        if (tid < n) sh.count[tid] = count;
+        t = head_threshold(sh, S, at, n_safe, budget);
+        gt_base = t.gt_before;
+        eq_base = t.eq_before;
+    }, [&](uint32_t (&keys)[kBatch][kItems], int c) {
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+            if (c + i < at.c1)
+                emit_chunk(sh.pick.wave_tot, keys[i], (c + i) * kChunk + tid * kItems, at.len, t.thr, t.need_eq, room, gt_base, eq_base, out);
+    });
+    const int kept = min(t.kept, room);
+    if (at.in_head == 0 && tid == 0) counts[at.head] = kept;
+    for (int j = kept + at.in_head * kSelThreads + tid; j < room; j += S.per_head * kSelThreads) out[j] = -1;
 }
 
 }  // namespace
@@ -994,7 +1397,7 @@ static hipError_t launch_select_sliced(const float *scores, int budget, int32_t 
         return with_batch(S, [&](auto batch) {
             constexpr int kBatch = decltype(batch)::value;
             over_groups(S, [&](const Slices &S, dim3 grid) {
-                slices_count<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, radius, S);
+                slices_count<kBatch, false><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, radius, S);
                 slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S);
                 slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S, keep_idx,
                                                                 (int32_t *)nullptr);
@@ -1033,9 +1436,21 @@ hipError_t launch_select_adaptive(const float *scores, int budget, int n_safe, i
     return with_lens(ragged, B, lens, [&](const auto &few) {
         return with_batch(all, [&](auto batch) {
             constexpr int kBatch = decltype(batch)::value;
+            if (Hkv <= kFewHeads && Hkv * all.per_head <= kMaxGroupSlices && all.chunks <= kPackedChunks && n_safe < budget) {
+                HeadState *states = (HeadState *)safe.hist;              // (a second set of histograms is not needed)
+                safe.hist = all.hist;
+                over_groups(safe, [&](const Slices &S, dim3 grid) {
+                    slices_count<kBatch, true><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, S);
+                });
+                over_groups(all, [&](const Slices &S, dim3 grid) {
+                    adaptive_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, n_safe, Hkv, ragged, few, S, states);
+                    adaptive_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, n_safe, cap, Hkv, ragged, few, S, states, keep_idx, counts);
+                });
+                return hipGetLastError();
+            }
             over_groups(safe, [&](const Slices &S, dim3 grid) {
                 if (n_safe > 0) {
-                    slices_count<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, S);
+                    slices_count<kBatch, false><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, S);
                     slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, 0, 0, 0, S);
                 }
                 slices_safeguard<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, S, all.keys, all.hist);

@@ -146,3 +146,26 @@ def test_long_heads_with_the_least_scratch_that_is_taken(pool):
     for size in (need, need - keys, need - keys - 1):
         got = obc.obc_select_pooled(s, hh, pool=pool, workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
         assert torch.equal(got, want), size
+
+
+@pytest.mark.parametrize("N", [41, 4096, 4097, 20011])
+@pytest.mark.parametrize("Hkv", [1, 8, 9, 32, 33])
+def test_adaptive_safeguards_about_the_common_threshold(Hkv, N):
+    """Scores of few values in few classes of the first digit, heads on scales of their own: safeguards that end above,
+    at and below the common threshold, inside its class and outside, with ties cut at either; and classes too large for
+    LDS.  33 heads are past what the three kernels take."""
+    rng = np.random.default_rng(100 * Hkv + N)
+    B = 2
+    for levels in (3, 40, 100000):
+        s = 1 + np.floor(rng.random((B, Hkv, N)) * levels) / (4 * levels)               # one class: 1 .. 1.25
+        s *= rng.choice([1, 1, 1, 1.1, 0.98, 0.25, 16], size=(B, Hkv, 1))
+        s = s.astype(np.float32)
+        lens = [N, N - N // 3]
+        budget = min(lens) // 4
+        dev = torch.from_numpy(s).cuda()
+        for n_safe in (0, 1, budget // 5, budget - 1, budget):
+            label = "levels %d budget %d n_safe %d" % (levels, budget, n_safe)
+            want_idx, want_cnt = oracle.select_adaptive(s, budget, n_safe, seq_lens=lens)
+            got_idx, got_cnt = obc.obc_select_adaptive(dev, budget, n_safe, seq_lens=lens)
+            np.testing.assert_array_equal(got_cnt.cpu().numpy(), want_cnt, err_msg=label)
+            np.testing.assert_array_equal(got_idx.cpu().numpy(), want_idx, err_msg=label)
