@@ -70,7 +70,7 @@ struct ScoreWorkspace {
     size_t pl_o_digits;  // int8 [heads*rows][5][d]  o_i in fixed point (score_fixed.h)
     size_t pl_part_l;  // float [heads*splits*rows]  sum of exp(z - max) of a split, without the row's top token
     size_t pl_part_o;  // float [heads*splits*rows*d]  unnormalised output of a split, likewise
-    int pl_heads, pl_rows, pl_seg, pl_z_stride, pl_short;
+    int pl_heads, pl_rows, pl_seg, pl_z_stride, pl_short, pl_digit_logits;
     int pl_range, pl_ranges;   // tokens per range, ranges
     int pl_split, pl_splits;   // tokens per split (a multiple of 64), splits
     // Decode path (one window row per query head): see score_decode.hip.

@@ -3,8 +3,21 @@
 // The fp64 matrix cores do 79 TFLOP/s and the fp32 ones 157, the 8-bit integer ones 5000 and the bf16 ones 2500, so
 // contractions whose accuracy allows it are taken apart into pieces the fast ones multiply exactly.
 //
-// Logits (blocked_logits) stay in fp64.  Fixed point relative to a row's largest element cannot stand in for it: where a key
-// has a large element that meets a small one of the query, the digits that are left out are those the logit is made of.
+// Logits (digit_logits).  Rows of q and k as fixed point relative to their largest element, fp32 values 46 bits and a sign in
+// six balanced base-256 digits, bf16 values 30 bits in four, which hold their elements exactly down to 2^-23 of the row's
+// largest.  Products of digits are summed exactly in 32-bit integers, for the seven highest of the levels (all of four by
+// four digits).  Fixed point alone cannot stand in for fp64: where a key has a large element that meets a small one of the
+// query, the digits that are left out are those the logit is made of.  With 2^E for the product of the powers of two just
+// above the rows' largest elements, a CPU model of the arithmetic is off by 2^-46 2^E at most over millions of pairs (2^-54
+// rms: normal elements, 2^-53: channels larger than the others by 8, 2^-50: elements over 20 binades) and by 2^-43.8 where
+// channels 2^24 larger on one side are as much smaller on the other.  So a wave whose 16 x 16 pairs have one below 2^-17 2^E,
+// where that could be more than 2^-26.8 of the dot product (its rounding to fp32 is 2^-25), or a row that the digits do not
+// hold (bf16 elements cut off, infinities, NaN), forms its dot products in fp64 as blocked_logits does: 0.5 % of them for
+// normal keys with channels larger by 8.  The scores of the benchmark shapes are the same bit for bit.
+// Whole calls with one and with the other, by 64-token tiles times 128-row chunks over all heads, us:
+//   80 - 300: 20.0 / 24.7, 21.0 / 26.9, 30.3 / 36.1, 33.3 / 38.0; 384: 29.9 / 32.1; 432: 28.3 / 29.1; 456: 32.8 / 30.2;
+//   480: 53.7 / 53.3; 700 - 800: 27.7 / 27.8, 82.4 / 82.2; 1056: 84.7 / 77.7; 1344: 118.9 / 108.4; 3456: 93.5 / 77.0
+// as the digits of a workgroup's 128 rows cost as much as some tiles: digits from kDigitTiles = 512 on.
 //
 // v_p . o_i (fixed_score).  Each row of v and o is scaled by a power of two to fixed point, 38 bits and a sign relative to
 // the row's largest element (30 for bf16 values, whose elements have 8 significant bits), and written as five (four)
@@ -22,13 +35,15 @@
 // outputs' error is what shows, are off by 1.0e-6 (8.6e-6) in the 2-norm, with plain_weights by 1.1e-6 (8.7e-6); fp32,
 // d = 128, 8111 tokens.
 //
-// What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  fixed_score: the vector ALUs, 83
+// What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  digit_logits: the vector ALUs (73 % of the
+// kernel for bf16 values, 51 % for fp32: 20 instructions put four levels' pairs together, check and scale them, 8 take an
+// element apart) and the integer matrix cores (29 % and 40 %), a wave doing one after the other.  fixed_score: the vector ALUs, 83
 // instructions per 64 pairs (63 for bf16 values): putting a dot product together about 12, the norms and the closeness test
 // in fp64, and taking an element apart about 15 (7 for bf16), paid once per workgroup of up to 128 rows; matrix cores busy
 // 26 %.  fixed_weights: vector ALUs and matrix cores in turn (exponentials and pieces; busy 37 %).
-// Kernel times, 32/8 heads, joint, in us: logits / weights / merge / scores
-//   fp32, d = 128,  8111 tokens   48.5 / 27.3 / 5.5 / 29.6
-//   bf16, d = 64,  16384 tokens   47.5 / 21.4 / 5.0 / 36.0
+// Kernel times, 32/8 heads, joint, in us: logits (blocked_logits) / weights / merge / scores
+//   fp32, d = 128,  8111 tokens   36.0 (48.5) / 27.3 / 5.5 / 29.6
+//   bf16, d = 64,  16384 tokens   28.7 (47.5) / 21.4 / 5.0 / 36.0
 // Against the kernels for up to 32 rows, whole calls, 8 heads, us here / there:
 //   33 rows: fp32 d 128 8K 64 / 81, 4 x 8K 189 / 250; d 64 8K 42 / 56; bf16 d 64 8K 40 / 57, 2K 22 / 29
 //   32 rows: fp32 d 128 8K 54 / 59, 4 x 8K 154 / 154; d 64 8K 37 / 44; bf16 d 64 8K 33 / 43, 2K 20 / 24
@@ -41,6 +56,9 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 template <typename T> constexpr int kDigits = sizeof(T) == 4 ? 5 : 4;
 constexpr int kRowDigits = 5;                  // of o_i, which is fp32 whatever the inputs are
 constexpr int kLevels = 5;
+template <typename T> constexpr int kLogitDigits = sizeof(T) == 4 ? 6 : 4;
+constexpr int kLogitLevels = 7;
+template <typename T> constexpr double kLeastDot = sizeof(T) == 4 ? 0x1p34 : 0x1p29;       // units of join_seven
 
 // A wave has 16 window rows: the rows' digits and a block's sums fit 128 registers, so that four waves share a SIMD and hide
 // each other's latencies (with 32 rows per wave and two waves weights and scores took 37 and 43 us where 29 and 36 then were
@@ -73,12 +91,22 @@ __device__ __forceinline__ int max_exponent(uint32_t amax) { return (int)(amax >
 // A row's share of the unit of a dot product, 2^(e - 18); NaN where an element was infinite or not a number.
 __device__ __forceinline__ double row_unit(int e) { return e > 128 ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, e - 18); }
 
+// The last four planes of digits from four words whose bytes are digits plus 128.
+template <int K>
+__device__ __forceinline__ void byte_planes(const uint32_t (&w)[4], uint32_t (&plane)[K]) {
+    const uint32_t t0 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602), t1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602);
+    const uint32_t u0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400), u1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400);
+    plane[K - 4] = __builtin_amdgcn_perm(t1, t0, 0x07060302) ^ 0x80808080u;
+    plane[K - 3] = __builtin_amdgcn_perm(t1, t0, 0x05040100) ^ 0x80808080u;
+    plane[K - 2] = __builtin_amdgcn_perm(u1, u0, 0x07060302) ^ 0x80808080u;
+    plane[K - 1] = __builtin_amdgcn_perm(u1, u0, 0x05040100) ^ 0x80808080u;
+}
 // The digits of four elements, most significant first, one byte per element.  The sum with 1.5 * 2^52 rounds to the
 // fixed-point integer and leaves it in the low bits; 128 added to every digit makes its bytes the digits plus 128.
-template <int K>
+template <int K>          // 4, 5 or 6
 __device__ __forceinline__ void digits_of(const double (&x)[4], int e, uint32_t (&plane)[K]) {
-    const double scale = __hiloint2double((1023 + (K == 5 ? 38 : 30) - e) << 20, 0);
-    const double bias = 6755399441055744.0 + (K == 5 ? (double)0x8080808080ll : (double)0x80808080ll);
+    const double scale = __hiloint2double((1023 + 8 * K - 2 - e) << 20, 0);
+    const double bias = 6755399441055744.0 + (K == 6 ? (double)0x808080808080ll : K == 5 ? (double)0x8080808080ll : (double)0x80808080ll);
     uint32_t w[4], top[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -86,21 +114,48 @@ __device__ __forceinline__ void digits_of(const double (&x)[4], int e, uint32_t 
         w[i] = (uint32_t)__double2loint(t);
         top[i] = (uint32_t)__double2hiint(t);
     }
-    const uint32_t t0 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602), t1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602);
-    const uint32_t u0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400), u1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400);
-    plane[K - 4] = __builtin_amdgcn_perm(t1, t0, 0x07060302) ^ 0x80808080u;
-    plane[K - 3] = __builtin_amdgcn_perm(t1, t0, 0x05040100) ^ 0x80808080u;
-    plane[K - 2] = __builtin_amdgcn_perm(u1, u0, 0x07060302) ^ 0x80808080u;
-    plane[K - 1] = __builtin_amdgcn_perm(u1, u0, 0x05040100) ^ 0x80808080u;
-    if (K == 5)
-        plane[0] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(top[3], top[2], 0x0c0c0400),
-                                         __builtin_amdgcn_perm(top[1], top[0], 0x0c0c0400), 0x05040100) ^ 0x80808080u;
+    byte_planes<K>(w, plane);
+    if (K >= 5)
+        plane[K - 5] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(top[3], top[2], 0x0c0c0400),
+                                             __builtin_amdgcn_perm(top[1], top[0], 0x0c0c0400), 0x05040100) ^ 0x80808080u;
+    if (K == 6)
+        plane[0] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(top[3], top[2], 0x0c0c0501),
+                                         __builtin_amdgcn_perm(top[1], top[0], 0x0c0c0501), 0x05040100) ^ 0x80808080u;
 }
 
 // x . y of the two fixed-point vectors from the level sums, in units of row_unit(ex) row_unit(ey).
 __device__ __forceinline__ double join_levels(int l0, int l1, int l2, int l3, int l4) {
     const int hi = (l0 << 8) + l1, lo = (l2 << 8) + l3 + (l4 >> 8);      // (at most 2^27 and 2^31: |digit| <= 128, the first one <= 64)
     return fma((double)hi, 65536.0, (double)lo);
+}
+
+// The same from the seven levels of a logit, in units of 2^(E - 51); what is cut off is less than two of them.
+template <int K>
+__device__ __forceinline__ double join_seven(int l0, int l1, int l2, int l3, int l4, int l5, int l6) {
+    const int hi = (l0 << 8) + l1, mid = (l2 << 8) + l3;                 // (at most 2^27 and 2^30, as is lo)
+    const int lo = (l4 << 7) + (K == 4 ? ((l5 << 8) + l6) >> 9 : (l5 + (l6 >> 8)) >> 1);
+    return fma(fma((double)hi, 65536.0, (double)mid), 32768.0, (double)lo);
+}
+// Exponent of a row whose elements the digits of a logit cannot hold.
+constexpr int kNoExponent = 1 << 20;
+__device__ __forceinline__ int logit_exponent(uint32_t amax) { return amax >= 0x7f800000u ? kNoExponent : max_exponent(amax); }
+// Digits of elements below 2^e.  bf16 values: as integers of 30 bits, and `cut` is above zero where one has bits below those.
+template <typename T, int K>
+__device__ __forceinline__ void logit_digits(const float (&y)[4], int e, uint32_t (&plane)[K], float &cut) {
+    if constexpr (sizeof(T) == 4) {
+        const double yd[4] = {y[0], y[1], y[2], y[3]};
+        digits_of<K>(yd, e, plane);
+    } else {
+        static_assert(K == 4, "30 bits and a sign");
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float t = __builtin_amdgcn_ldexpf(y[i], 30 - e);
+            cut = fmaxf(cut, __builtin_amdgcn_fractf(t));
+            w[i] = (uint32_t)(int)t + 0x80808080u;
+        }
+        byte_planes<K>(w, plane);
+    }
 }
 
 // Rows of digits in LDS, kTok rows x K planes of D bytes.  A row's 16-byte piece c sits at slot c ^ f(row), so that the 16
@@ -167,6 +222,36 @@ struct TokenTile {
         }
         return v;
     }
+    // The digits of digit_logits and the rows' exponents into LDS.
+    template <int K>
+    __device__ __forceinline__ void store_logit_digits(char *digits, int *exponents) const {
+        int thread = threadIdx.x;
+        asm volatile("" : "+v"(thread));                     // (addresses anew for every tile: registers)
+        const int r0 = thread / kLanes, c = thread % kLanes;
+        char *dst = digits + digit_offset<D, kTok>(0, r0, c * kPer / 16) + c * kPer % 16;
+#pragma unroll
+        for (int i = 0; i < kCount; ++i) {
+            __builtin_amdgcn_sched_barrier(0);               // (one piece at a time: registers)
+            float y[kPer / 4][4];
+            unpack(i, y);
+            uint32_t amax = max_abs(y[0]);
+            if (kPer == 8) amax = MaxBitsOp()(amax, max_abs(y[kPer / 4 - 1]));
+            amax = over_row<MaxBitsOp>(amax);
+            uint32_t p[kPer / 4][K];
+            float cut = 0.f;
+#pragma unroll
+            for (int q = 0; q < kPer / 4; ++q) logit_digits<T>(y[q], max_exponent(amax), p[q], cut);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                char *at = dst + (k * kTok + i * kStep) * D;
+                if constexpr (kPer == 4) *(uint32_t *)at = p[0][k];
+                else *(uint2 *)at = make_uint2(p[0][k], p[1][k]);
+            }
+            if (c == 0) exponents[r0 + i * kStep] = logit_exponent(amax);
+            if (sizeof(T) == 2 && __builtin_amdgcn_ballot_w64(cut > 0.f) != 0ull)      // uniform, rare; a row's lanes are in one wave
+                if (cut > 0.f) *(volatile int *)(exponents + r0 + i * kStep) = kNoExponent;
+        }
+    }
     // Digits and units into LDS and, where asked for, the rows' norms: ||v||^2 (2) or ||v||_1 (1).
     template <bool kWithDigits, int kNorm>
     __device__ __forceinline__ void store_digits(char *digits, double *units, double *norms) const {
@@ -226,16 +311,61 @@ struct RowDigits {
                 x[k][kk] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(
                                                          span, (int)digit_address<K, D>(block, k, 0, kk * 64) + lane * 16, 0, 0));
     }
+    // Digits of a row itself, for digit_logits; returns the row's exponent.
+    template <typename T>
+    __device__ __forceinline__ int take(const T *__restrict__ row, int g) {
+        float y[D / 64][4][4];
+#pragma unroll
+        for (int kk = 0; kk < D / 64; ++kk) {
+            const T *src = row + kk * 64 + 16 * g;
+            if constexpr (sizeof(T) == 4) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float4 f = *(const float4 *)(src + 4 * c);
+                    y[kk][c][0] = f.x; y[kk][c][1] = f.y; y[kk][c][2] = f.z; y[kk][c][3] = f.w;
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; c += 2) {
+                    const uint4 h = *(const uint4 *)(src + 4 * c);
+                    const uint32_t u[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        y[kk][c + i / 2][i % 2 * 2] = __uint_as_float(u[i] << 16);
+                        y[kk][c + i / 2][i % 2 * 2 + 1] = __uint_as_float(u[i] & 0xffff0000u);
+                    }
+                }
+            }
+        }
+        uint32_t amax = 0u;
+#pragma unroll
+        for (int kk = 0; kk < D / 64; ++kk)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) amax = MaxBitsOp()(amax, max_abs(y[kk][c]));
+        amax = across_rows<MaxBitsOp>(amax);
+        float cut = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < D / 64; ++kk)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                uint32_t p[K];
+                logit_digits<T>(y[kk][c], max_exponent(amax), p, cut);
+#pragma unroll
+                for (int k = 0; k < K; ++k) x[k][kk][c] = (int)p[k];
+            }
+        if (sizeof(T) == 2) cut = across_rows<MaxOp>(cut);
+        return cut > 0.f ? kNoExponent : logit_exponent(amax);
+    }
 };
 
 // Buffers of a tile: two where two workgroups fit a CU with them, else one (and a barrier more per tile).
 constexpr int buffers_of(int bytes) { return bytes <= 32 * 1024 ? 2 : 1; }
 
 // Level sums of 16 tokens in LDS (accumulator rows) and 16 window rows (lanes).
-template <int KR, int KT, int D, int kTok>
-__device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const char *digits, int tok, int g, i32x4 (&acc)[kLevels]) {
+template <int KR, int KT, int D, int kTok, int L>
+__device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const char *digits, int tok, int g, i32x4 (&acc)[L]) {
 #pragma unroll
-    for (int t = 0; t < kLevels; ++t) acc[t] = i32x4{0, 0, 0, 0};
+    for (int t = 0; t < L; ++t) acc[t] = i32x4{0, 0, 0, 0};
 #pragma unroll
     for (int kk = 0; kk < D / 64; ++kk) {
         if (kk > 0) __builtin_amdgcn_sched_barrier(0);       // (one piece at a time: registers)
@@ -245,13 +375,49 @@ __device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const c
 #pragma unroll
         for (int k = 0; k < KT; ++k)
 #pragma unroll
-            for (int i = 0; i < KR && i + k < kLevels; ++i)
+            for (int i = 0; i < KR && i + k < L; ++i)
                 acc[i + k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b[k], rows.x[i][kk], acc[i + k], 0, 0, 0);
     }
 }
 
+// fp64 dot products of 16 tokens and 16 rows from memory: lane = row + 16 g, dot[r] that of token 4 g + r.  `tok`: the
+// lane's token, 4 (lane % 4) + lane / 4 % 4 of the 16; `row`: row lane % 16.
+template <typename T>
+__device__ __forceinline__ f32x4 four_elements(const T *x) {
+    if constexpr (sizeof(T) == 4) {
+        return *(const f32x4 *)x;
+    } else {
+        const uint2 h = *(const uint2 *)x;
+        return f32x4{__uint_as_float(h.x << 16), __uint_as_float(h.x & 0xffff0000u), __uint_as_float(h.y << 16), __uint_as_float(h.y & 0xffff0000u)};
+    }
+}
+template <typename T, int D, typename R>
+__device__ __forceinline__ void block_dots(const T *__restrict__ tok, const R *__restrict__ row, int g, double (&dot)[4]) {
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int s = 0; s < D / 16; ++s) {
+        const f32x4 x = four_elements(tok + 16 * s + 4 * g), y = four_elements(row + 16 * s + 4 * g);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[c], (double)y[c], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) dot[r] = acc[r];
+}
+
+// The larger maximum, or the lower token that has it, of the lanes whose numbers differ in kBit.
+template <int kBit>
+__device__ __forceinline__ void best_of_pair(float &m, int &at) {
+    float m0, m1;
+    uint32_t a0, a1;
+    both_of_pair<kBit>(m, m0, m1);
+    both_of_pair<kBit>((uint32_t)at, a0, a1);
+    const bool second = m1 > m0 || (m1 == m0 && a1 < a0);
+    m = second ? m1 : m0;
+    at = (int)(second ? a1 : a0);
+}
+
 // ------------------------------------------------------------------------------------
-// Logits, as plain_logits forms them (fp64 dot products, rounded once), into the blocked layout.  Grid: x = KV head
+// Logits, as plain_logits forms them (fp64 dot products, rounded once), into the blocked layout.  For short calls.  Grid: x = KV head
 // (neighbours run on different XCDs, whose L2 caches then hold the rows, values and logits of few heads), y = token range
 // of the piece, z = chunk of kLogitRows rows.  A wave has 16 tokens of every tile of 64; lane = row + 16 g of every 16 rows,
 // with tokens 4 g .. 4 g + 3, which the lanes' order of loading puts there.
@@ -310,20 +476,10 @@ __global__ __launch_bounds__(kThreads, 4) void blocked_logits(const T *__restric
             if (row0 / 16 + rt < blocks) *(float4 *)(zp[rt] + (t0 - t_begin) * 16) = make_float4(x[0], x[1], x[2], x[3]);   // (room for whole tiles)
         }
     }
-    auto best_of_pair = [&](float &m, int &at, auto bit) {
-        constexpr int kBit = decltype(bit)::value;
-        float m0, m1;
-        uint32_t a0, a1;
-        both_of_pair<kBit>(m, m0, m1);
-        both_of_pair<kBit>((uint32_t)at, a0, a1);
-        const bool second = m1 > m0 || (m1 == m0 && a1 < a0);
-        m = second ? m1 : m0;
-        at = (int)(second ? a1 : a0);
-    };
 #pragma unroll
     for (int rt = 0; rt < kRt; ++rt) {
-        best_of_pair(m[rt], at[rt], std::integral_constant<int, 16>());
-        best_of_pair(m[rt], at[rt], std::integral_constant<int, 32>());
+        best_of_pair<16>(m[rt], at[rt]);
+        best_of_pair<32>(m[rt], at[rt]);
         if (g == 0) best_s[wave][16 * rt + lane] = make_float2(m[rt], __int_as_float(at[rt]));
     }
     __syncthreads();
@@ -336,6 +492,105 @@ __global__ __launch_bounds__(kThreads, 4) void blocked_logits(const T *__restric
             if (o.x > best.x || (o.x == best.x && __float_as_int(o.y) < __float_as_int(best.y))) best = o;
         }
         range_best[((size_t)hl * w.nr + row0 + row) * n_ranges + range] = best;
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// The same from digits, where the call is long enough.  Grid: x = KV head, y = token range of the piece, z = chunk of 16 kRb
+// rows.  Lane = row + 16 g, registers = tokens 4 g .. 4 g + 3 of the 16 at hand.
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int kRb, typename Lens>
+__global__ __launch_bounds__(kFixedThreads, 4) void digit_logits(const T *__restrict__ q, const T *__restrict__ k, int N, int W, int Hq,
+                                                                 int Hkv, int ragged, Lens lens, Piece w, int range_len, int n_ranges,
+                                                                 float *__restrict__ z, float2 *__restrict__ range_best) {
+    constexpr int K = kLogitDigits<T>, kTok = kFixedTile<D>, kParts = 8 / kRb, kPart = kTok / kParts, kRows = 16 * kRb,
+                  kBuf = buffers_of(K * kTok * D);
+    static_assert(kBuf == 2, "one barrier per tile");
+    __shared__ __attribute__((aligned(16))) char digits[kBuf][K * kTok * D];
+    __shared__ __attribute__((aligned(16))) int exponents[2][kTok];
+    __shared__ float2 best_s[kParts][kRows];
+    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv, M = Hq / Hkv * W;
+    const int len = seq_len_of(lens, ragged, b, N);
+    const int range = w.s0 / range_len + blockIdx.y;
+    const int t_begin = range * range_len, t_end = min(min(t_begin + range_len, w.s1), len);
+    if (t_begin >= t_end) return;                            // uniform
+    const int row0 = blockIdx.z * kRows, blocks = (w.nr + 15) / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int rb = wave % kRb, part = wave / kRb, row = row0 + rb * 16 + (lane & 15);
+    const bool live = row0 / 16 + rb < blocks;               // uniform in the wave
+    const T *kg = k + (size_t)bg * N * D;
+    const __amdgpu_buffer_rsrc_t span = span_of(kg + (size_t)t_begin * D, (size_t)(t_end - t_begin) * D * sizeof(T));
+    TokenTile<T, D, kTok, kFixedThreads> next;
+    next.load(span, 0);
+    const T *q_row = q + ((size_t)b * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D;
+    RowDigits<K, D> rows;
+    const int exponent = rows.template take<T>(q_row, lane >> 4) - 51 - 3;
+    const int last = min(len - W + (w.r0 + min(row, w.nr - 1)) % W, t_end - 1);                // last token the row sees here
+    const int least = __builtin_amdgcn_readfirstlane((int)row16_reduce<MinOp>((uint32_t)last));      // of the 16 rows
+    float *zp = z + z_block(w, hl, min(row0 / 16 + rb, blocks - 1), t_begin) + lane * 4;
+    float m = -INFINITY;
+    int at = kNoToken;
+    next.template store_logit_digits<K>(digits[0], exponents[0]);
+    if (t_begin + kTok < t_end) next.load(span, kTok);
+    int slot = 0;
+    for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
+        __syncthreads();                                     // this tile is in LDS, the one before it has been read
+        if (t0 + kTok < t_end) next.template store_logit_digits<K>(digits[slot ^ 1], exponents[slot ^ 1]);
+        if (t0 + 2 * kTok < t_end) next.load(span, t0 - t_begin + 2 * kTok);
+        if (!live) continue;
+#pragma unroll 1
+        for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
+            i32x4 acc[kLogitLevels];
+            level_sums<K, K, D, kTok>(rows, digits[slot], p0 + (lane & 15), lane >> 4, acc);
+            __builtin_amdgcn_sched_barrier(0);
+            const int first = t0 + p0 + 4 * (lane >> 4);     // register r has token first + r
+            const i32x4 ex = *(const i32x4 *)&exponents[slot][p0 + 4 * (lane >> 4)];
+            float x[4];
+            bool again = max(max(max(ex[0], ex[1]), ex[2]), ex[3]) + exponent >= kNoExponent / 2;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                double dot = join_seven<K>(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r], acc[5][r], acc[6][r]);
+                again |= fabs(dot) < kLeastDot<T>;           // (also of the zeros past the end)
+                if (D == 128) dot *= 0.088388347648318440550 * 8.0;
+                x[r] = __builtin_amdgcn_ldexpf((float)dot, ex[r] + exponent);
+            }
+            if (__builtin_amdgcn_ballot_w64(again) != 0ull) {            // uniform
+                double dot[4];
+                block_dots<T, D>(kg + (size_t)min(t0 + p0 + 4 * (lane & 3) + (lane >> 2 & 3), t_end - 1) * D, q_row, lane >> 4, dot);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[r] = (float)(dot[r] * (1.0 / sqrt((double)D)));
+            }
+            auto improve = [&](const float (&y)[4]) {
+                const float best = fmaxf(fmaxf(fmaxf(y[0], y[1]), y[2]), y[3]);
+                if (__builtin_amdgcn_ballot_w64(best > m) == 0ull) return;       // uniform, usual once the maxima have settled
+#pragma unroll
+                for (int r = 0; r < 4; ++r)                  // (tokens ascend: strict keeps the lowest)
+                    if (y[r] > m) { m = y[r]; at = first + r; }
+            };
+            if (t0 + p0 + 15 > least) {                      // uniform: not every row sees every token
+                float y[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[r] = first + r <= last ? x[r] : -INFINITY;
+                improve(y);
+            } else {
+                improve(x);
+            }
+            *(float4 *)(zp + (t0 - t_begin + p0) * 16) = make_float4(x[0], x[1], x[2], x[3]);      // (room for whole tiles)
+        }
+    }
+    best_of_pair<16>(m, at);
+    best_of_pair<32>(m, at);
+    if (lane < 16) best_s[part][rb * 16 + lane] = make_float2(m, __int_as_float(at));
+    __syncthreads();
+    const int r = threadIdx.x;
+    if (r < kRows && row0 + r < w.nr) {
+        float2 best = best_s[0][r];
+#pragma unroll
+        for (int c = 1; c < kParts; ++c) {
+            const float2 o = best_s[c][r];
+            if (o.x > best.x || (o.x == best.x && __float_as_int(o.y) < __float_as_int(best.y))) best = o;
+        }
+        range_best[((size_t)hl * w.nr + row0 + r) * n_ranges + range] = best;
     }
 }
 
@@ -542,29 +797,6 @@ __global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__re
         }
         *(float4 *)(part_o + out_row * D + d * 16 + 4 * g) = o;
     }
-}
-
-// fp64 dot products of 16 tokens and 16 rows from memory: lane = row + 16 g, dot[r] that of token 4 g + r.  `tok`: the
-// lane's token, 4 (lane % 4) + lane / 4 % 4 of the 16; `row`: row lane % 16.
-template <typename T, int D>
-__device__ __forceinline__ void block_dots(const T *__restrict__ tok, const float *__restrict__ row, int g, double (&dot)[4]) {
-    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-    for (int s = 0; s < D / 16; ++s) {
-        const T *t = tok + 16 * s + 4 * g;
-        f32x4 x;
-        if constexpr (sizeof(T) == 4) {
-            x = *(const f32x4 *)t;
-        } else {
-            const uint2 h = *(const uint2 *)t;
-            x = f32x4{__uint_as_float(h.x << 16), __uint_as_float(h.x & 0xffff0000u), __uint_as_float(h.y << 16), __uint_as_float(h.y & 0xffff0000u)};
-        }
-        const f32x4 y = *(const f32x4 *)(row + 16 * s + 4 * g);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[c], (double)y[c], acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) dot[r] = acc[r];
 }
 
 // ------------------------------------------------------------------------------------

@@ -41,6 +41,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 64;        // tokens per tile; each of the four waves owns 16 of them
 constexpr int kThreads = 256;    // 4 waves
+constexpr int kDigitTiles = 512; // least tiles times 128-row chunks for digit_logits
 constexpr int kMaxRanges = 64;   // token ranges with a row maximum of their own, at most
 constexpr int kMaxSplits = 32;   // sequence splits of P V, at most
 constexpr int kResident = 1024;  // workgroups the chip holds at four per CU: a launch is cut into about this many
@@ -871,10 +872,14 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             const unsigned row_chunks = (w.nr + 16 * kRb - 1) / (16 * kRb);         // (score_fixed.h)
             auto logits = [&]() {
                 const unsigned ranges = (w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range;
-                if constexpr (fixed)
-                    blocked_logits<T, D><<<dim3(heads, ranges, (w.nr + kLogitRows - 1) / kLogitRows), dim3(kThreads), 0, stream>>>(
-                        q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
-                else
+                if constexpr (fixed) {
+                    if (ws.pl_digit_logits)
+                        digit_logits<T, D, kRb><<<dim3(heads, ranges, row_chunks), dim3(kFixedThreads), 0, stream>>>(
+                            q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
+                    else
+                        blocked_logits<T, D><<<dim3(heads, ranges, (w.nr + kLogitRows - 1) / kLogitRows), dim3(kThreads), 0, stream>>>(
+                            q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
+                } else
                     plain_logits<T, D, kRt><<<dim3(ranges, chunks, heads), dim3(kThreads), 0, stream>>>(
                         q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 e = hipGetLastError();
@@ -973,7 +978,9 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWo
     const bool fixed = M > 32;
     const long long tiles = (N + kTile - 1) / kTile, logit_chunks = (long long)BH * ((M + 31) / 32);
     const long long chunks = fixed ? (long long)BH * ((M + 127) / 128) : logit_chunks, resident = fixed ? kResident / 2 : kResident;
-    const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, (tiles * logit_chunks + kResident - 1) / kResident);
+    ws->pl_digit_logits = fixed && tiles * chunks >= kDigitTiles ? 1 : 0;
+    const long long logit_tiles = ws->pl_digit_logits ? (tiles * chunks + resident - 1) / resident : (tiles * logit_chunks + kResident - 1) / kResident;
+    const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, logit_tiles);
     ws->pl_range = (int)(std::min(range_tiles, tiles) * kTile);
     ws->pl_ranges = (N + ws->pl_range - 1) / ws->pl_range;
     const long long splits = std::max<long long>(1, std::min<long long>(std::min<long long>(kMaxSplits, tiles), (resident / 2 + chunks - 1) / chunks));

@@ -105,3 +105,54 @@ def test_a_value_that_is_not_a_number_shows(shape):
     for variant in ("key", "joint"):
         got = obc.obc_score(*(x.to(dt).cuda() for x in (q, k, v)), variant)
         assert bool(got[:, 1].isnan().all()) and bool(got[:, 0].isfinite().all()), variant
+
+
+# What the digits of a logit cannot hold, or hold only in part.
+LOGITS = {
+    # the query's large element meets the keys' small one, and the other way round: the digits' error next to the logit's size
+    "apart_2^7": lambda q, k: _apart(q, k, 7),
+    "apart_2^12": lambda q, k: _apart(q, k, 12),
+    "apart_2^20": lambda q, k: _apart(q, k, 20),
+    "channels_2^12": lambda q, k: (_scaled(q, slice(3, 5), -12), _scaled(k, slice(3, 5), 12)),
+    "channels_2^26": lambda q, k: (_scaled(q, slice(3, 5), -26), _scaled(k, slice(3, 5), 26)),
+    # elements far below their rows' largest, in every 16th key and one query row
+    "small_elements": lambda q, k: (_put(q, slice(3, 4), 2.0 ** -29), _put(k, slice(5, None, 16), 2.0 ** -27)),
+    # keys that are zero; keys at a right angle to every query
+    "zero_keys": lambda q, k: (q, _put(k, slice(9, None, 50), 0.0, slice(None))),
+    "right_angles": lambda q, k: (_put(q, slice(None), 0.0, slice(0, 32)), _put(k, slice(2, None, 7), 0.0, slice(32, None))),
+}
+
+
+def _put(x, rows, value, channels=slice(1, 4)):
+    x = x.clone()
+    x[:, :, rows, channels] = value
+    return x
+
+
+def _scaled(x, channels, binades):
+    x = x.clone()
+    x[..., channels] *= 2.0 ** binades
+    return x
+
+
+def _apart(q, k, binades):
+    return _scaled(q, slice(0, 1), binades), _scaled(k, slice(0, 1), -binades)
+
+
+# Long enough for digits (512 tiles of 64 tokens times chunks of 128 rows over both heads), and one that is not.
+DIGIT_SHAPES = [("fp32", 128, 3, 43, 8131), ("fp32", 64, 1, 64, 16332), ("bf16", 64, 5, 40, 8145), ("bf16", 64, 1, 33, 16321),
+                ("bf16", 128, 1, 40, 16323), ("fp32", 128, 3, 43, 129)]
+
+
+@pytest.mark.parametrize("logits", LOGITS)
+@pytest.mark.parametrize("shape", DIGIT_SHAPES, ids=lambda s: "%s_d%d_%dx%d_%d" % s)
+def test_logits_beyond_their_digits(shape, logits, score_path):
+    score_path("plain")
+    q, k, v = _random(shape, 75)
+    q, k = LOGITS[logits](q, k)
+    _check(shape, q, k, v)
+
+
+@pytest.mark.parametrize("shape", DIGIT_SHAPES[:4], ids=lambda s: "%s_d%d_%dx%d_%d" % s)
+def test_digit_logits_at_the_end_of_fp32(shape):
+    test_logits_at_the_end_of_fp32_have_weight_zero(shape)
