@@ -43,8 +43,17 @@ constexpr int kChunk = kSelThreads * kItems;           // 4096 scores per chunk
 // Monotone map float -> uint32: larger float <=> larger key.  -0.0 is folded onto +0.0,
 // every NaN maps to 1 (below -inf, whose key is 0x007fffff).  No score maps to 0: that key marks
 // positions that do not exist (past a sequence's length), which therefore rank below every token
-// and never reach a threshold as long as the budget does not exceed the length.
+// and never reach a threshold as long as the budget does not exceed the length.  (Six instructions; eight with the sign
+// and the zero tested apart.  A select_topk of 32K tokens forms 32 keys per thread and is bound by its instructions, four waves
+// to a SIMD: with the kept keys counted per chunk before they are packed, 15.8 -> 15.3 us, 4 x 8 heads.)
 __device__ __forceinline__ uint32_t order_key(float f) {
+    const uint32_t u = __float_as_uint(f + 0.0f);           // (-0.0 + 0.0 is +0.0)
+    const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+    return f != f ? 1u : key;
+}
+
+// The same for a pooled sum.  (The shorter form above made select_topk 0.4 us slower there, 32 heads x 14.7K.)
+__device__ __forceinline__ uint32_t pooled_key(float f) {
     uint32_t u = __float_as_uint(f);
     if (f != f) return 1u;
     if (u == 0x80000000u) u = 0u;
@@ -288,9 +297,12 @@ __device__ __forceinline__ void emit_resident_uncut(Shared &sh, const uint32_t (
     for (int g = 0; g < kPacks; ++g) {
         int mine = 0;
 #pragma unroll
-        for (int c = 3 * g; c < 3 * g + 3 && c < kRegChunks; ++c)
+        for (int c = 3 * g; c < 3 * g + 3 && c < kRegChunks; ++c) {
+            int of_chunk = 0;
 #pragma unroll
-            for (int e = 0; e < kItems; ++e) mine += keys[c][e] >= thr ? 1 << (10 * (c - 3 * g)) : 0;
+            for (int e = 0; e < kItems; ++e) of_chunk += keys[c][e] >= thr ? 1 : 0;
+            mine += of_chunk << (10 * (c - 3 * g));
+        }
         const int incl = wave_scan<false>(mine, lane);
         before[g] = incl - mine;
         if (lane == 63) {
@@ -350,7 +362,7 @@ __device__ __forceinline__ void pooled_four(const float *__restrict__ s, int i0,
         float sum = w[kSide * kItems + e - R];
 #pragma unroll
         for (int j = 1; j <= 2 * R; ++j) sum = __fadd_rn(sum, w[kSide * kItems + e - R + j]);
-        keys[e] = order_key(sum);
+        keys[e] = pooled_key(sum);
     }
 }
 
@@ -424,7 +436,7 @@ __device__ __forceinline__ void load_batch(uint32_t (&keys)[kRegChunks][kItems],
 #pragma unroll
                     for (int j = 1; j <= 2 * kMaxRadius; ++j)
                         if (j <= 2 * radius) sum = __fadd_rn(sum, w[e + j]);
-                    keys[c][e] = i0 + e < len ? order_key(sum) : 0u;
+                    keys[c][e] = i0 + e < len ? pooled_key(sum) : 0u;
                 }
             } else if (keys_in) {                         // uniform: the input already holds order-preserving keys
                 const uint32_t *kin = (const uint32_t *)s;
