@@ -35,9 +35,9 @@
 // outputs' error is what shows, are off by 1.0e-6 (8.6e-6) in the 2-norm, with plain_weights by 1.1e-6 (8.7e-6); fp32,
 // d = 128, 8111 tokens.
 //
-// What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  digit_logits: the vector ALUs (73 % of the
-// kernel for bf16 values, 51 % for fp32: 20 instructions put four levels' pairs together, check and scale them, 8 take an
-// element apart) and the integer matrix cores (29 % and 40 %), a wave doing one after the other.  fixed_score: the vector ALUs, 83
+// What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  digit_logits: the vector ALUs (71 % of the
+// kernel for bf16 values, 53 % for fp32: some 18 instructions put a pair's levels together, check and scale them, some 9 take an
+// element apart) and the integer matrix cores (30 % and 43 %), a wave doing one after the other.  fixed_score: the vector ALUs, 83
 // instructions per 64 pairs (63 for bf16 values): putting a dot product together about 12, the norms and the closeness test
 // in fp64, and taking an element apart about 15 (7 for bf16), paid once per workgroup of up to 128 rows; matrix cores busy
 // 26 %.  fixed_weights: vector ALUs and matrix cores in turn (exponentials and pieces; busy 37 %).
