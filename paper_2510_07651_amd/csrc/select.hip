@@ -563,7 +563,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const float *__restri
 //                   slices before it keep
 // No global atomics and nothing to clear; every workgroup of a group repeats the integer sums.  Bound by the launches
 // and their memory round trips (a 4 x 128K selection reads 2 MB): five kernels with a histogram of the whole slice per
-// digit took 52 us there, these three take 20.
+// digit took 52 us there, these three take 21, of which 6.6 to collect (7.3 with counters of 32 bits).
 // ------------------------------------------------------------------------------------
 struct SliceState {      // of a group, written by slices_collect
     uint32_t digit;      // first digit of the threshold
@@ -583,6 +583,7 @@ struct Slices {
     uint32_t *keys;                  // [heads of all groups][key_stride]; NULL: the keys are formed from the scores each time
 };
 
+constexpr int kPackedChunks = 8;         // chunks of a slice whose counters stay below 2^16
 constexpr int kMaxGroupSlices = 1024;    // of a group whose bookkeeping fits LDS; larger ones (that many heads) read it where it lies
 
 // Where a workgroup of the sliced kernels works: blockIdx.x = slice of the group, blockIdx.y = group of the launch's.
@@ -655,45 +656,73 @@ __global__ __launch_bounds__(kSelThreads) void slices_count(const float *__restr
     else *(int2 *)(S.hist + at.flat() * kSliceBins + 2 * threadIdx.x) = two;
 }
 
-template <int kBatch, typename Lens>
+// Sum of a group's `n` histograms in LDS, fetched ahead of what follows and added up later; the whole workgroup.
+template <bool kPacked>
+struct HistogramSum {
+    // A thread has 16 bytes of a histogram, so kParts slices are read side by side.
+    static constexpr int kOwn = kPacked ? 8 : 4, kParts = kSelThreads * kOwn / kSliceBins;
+    static constexpr int kAhead = 32 / kParts;               // slices of a part in flight at once
+    uint4 h[kAhead];
+    __device__ __forceinline__ void fetch(const int *__restrict__ hist, int n, int s0) {      // hist: of the group
+        const int part = threadIdx.x / (kSliceBins / kOwn), piece = threadIdx.x % (kSliceBins / kOwn);
+        const uint4 *src = (const uint4 *)hist + piece;
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const int sl = s0 + kParts * i + part;
+            h[i] = make_uint4(0u, 0u, 0u, 0u);
+            if (sl < n) h[i] = src[(size_t)sl * (kSliceBins / kOwn)];
+        }
+    }
+    // The first slices have been fetched.  Leaves the sums in parts[0]; a barrier has to follow.
+    __device__ __forceinline__ void sum(const int *__restrict__ hist, int n, int (&parts)[kParts][kSliceBins]) {
+        const int part = threadIdx.x / (kSliceBins / kOwn), piece = threadIdx.x % (kSliceBins / kOwn);
+        int c[kOwn] = {};
+        for (int s0 = 0; s0 < n; s0 += kParts * kAhead) {
+            if (s0 > 0) fetch(hist, n, s0);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const uint32_t w[4] = {h[i].x, h[i].y, h[i].z, h[i].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if constexpr (kPacked) { c[2 * j] += w[j] & 0xffff; c[2 * j + 1] += w[j] >> 16; }
+                    else c[j] += w[j];
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kOwn; j += 4) *(int4 *)(&parts[part][piece * kOwn + j]) = make_int4(c[j], c[j + 1], c[j + 2], c[j + 3]);
+        __syncthreads();
+        int2 t = make_int2(0, 0);
+#pragma unroll
+        for (int i = 0; i < kParts; ++i) {
+            const int2 x = *(const int2 *)(&parts[i][2 * threadIdx.x]);
+            t.x += x.x;
+            t.y += x.y;
+        }
+        *(int2 *)(&parts[0][2 * threadIdx.x]) = t;           // (read by this thread alone so far)
+    }
+};
+
+template <int kBatch, bool kPacked, typename Lens>
 __global__ __launch_bounds__(kSelThreads) void slices_collect(const float *__restrict__ scores, int N, int budget, int Hkv, int ragged,
                                                               Lens lens, int first, int tail, int radius, Slices S) {
-    __shared__ __attribute__((aligned(16))) int hist[kSliceBins];
+    using Sum = HistogramSum<kPacked>;
+    __shared__ __attribute__((aligned(16))) int hist[Sum::kParts][kSliceBins];
     __shared__ PickShared pick;
     __shared__ int n_list, n_above;
     const SlicePlace at(S, N, Hkv, ragged, lens);
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, n = gridDim.x;
     if (tid == 0) { n_list = 0; n_above = 0; }
-    // Sum of the group's histograms: four counters per thread, even slices by one half of the workgroup, odd ones by the other.
-    constexpr int kAhead = 16;                               // slices of a half in flight at once
-    const int half = tid / (kSliceBins / 4), bin = tid % (kSliceBins / 4) * 4, n = gridDim.x;
-    const int *src = S.hist + (size_t)at.group * n * kSliceBins + bin;
-    int4 h[kAhead];
-    auto fetch = [&](int s0) {
-#pragma unroll
-        for (int i = 0; i < kAhead; ++i) {
-            const int sl = s0 + 2 * i + half;
-            h[i] = make_int4(0, 0, 0, 0);
-            if (sl < n) h[i] = *(const int4 *)(src + (size_t)sl * kSliceBins);
-        }
-    };
+    const int *src = S.hist + (size_t)at.group * n * (kPacked ? kSliceBins / 2 : kSliceBins);
+    Sum histograms;
     uint32_t digit;
     auto pick_class = [&]() {
-        int4 sum = make_int4(0, 0, 0, 0);
-        for (int s0 = 0; s0 < n; s0 += 2 * kAhead) {
-            if (s0 > 0) fetch(s0);
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i) { sum.x += h[i].x; sum.y += h[i].y; sum.z += h[i].z; sum.w += h[i].w; }
-        }
-        int4 *dst = (int4 *)(hist + bin);
-        if (half == 0) *dst = sum;
-        __syncthreads();
-        if (half == 1) *dst = make_int4(dst->x + sum.x, dst->y + sum.y, dst->z + sum.z, dst->w + sum.w);
+        histograms.sum(src, n, hist);
         int remaining = budget, in_digit;
-        pick_digit<kSliceBins>(hist, pick, &digit, &remaining, &in_digit);
+        pick_digit<kSliceBins>(hist[0], pick, &digit, &remaining, &in_digit);
         if (at.slice == 0 && tid == 0) S.state[at.group] = SliceState{digit, remaining};
     };
-    fetch(0);
+    histograms.fetch(src, n, 0);
     uint32_t *list = S.list + at.flat() * S.list_stride;
     for_batches<kBatch>(S, at, scores, N, first, tail, radius, S.keys != nullptr, pick_class, [&](uint32_t (&keys)[kBatch][kItems], int c) {
         int mine = 0;                                        // low 16 bits: in the class, high 16 bits: above it
@@ -952,7 +981,6 @@ __global__ __launch_bounds__(kSelThreads) void slices_safeguard(const float *__r
 // Most heads (a workgroup finishes a safeguard per wave, the bookkeeping is a lane per head); the gain has shrunk to a
 // few percent there, as every workgroup goes through all heads' histograms one by one.
 constexpr int kFewHeads = 32;
-constexpr int kPackedChunks = 8;         // chunks of a slice whose counters stay below 2^16
 
 struct HeadState {       // written by adaptive_collect
     uint32_t digit;      // class of the head's list
@@ -1409,8 +1437,13 @@ static hipError_t launch_select_sliced(const float *scores, int budget, int32_t 
         return with_batch(S, [&](auto batch) {
             constexpr int kBatch = decltype(batch)::value;
             over_groups(S, [&](const Slices &S, dim3 grid) {
-                slices_count<kBatch, false><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, radius, S);
-                slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S);
+                if (S.chunks <= kPackedChunks) {
+                    slices_count<kBatch, true><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, radius, S);
+                    slices_collect<kBatch, true><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S);
+                } else {
+                    slices_count<kBatch, false><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, radius, S);
+                    slices_collect<kBatch, false><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S);
+                }
                 slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, budget, Hkv, ragged, few, first, tail, radius, S, keep_idx,
                                                                 (int32_t *)nullptr);
             });
@@ -1463,12 +1496,12 @@ hipError_t launch_select_adaptive(const float *scores, int budget, int n_safe, i
             over_groups(safe, [&](const Slices &S, dim3 grid) {
                 if (n_safe > 0) {
                     slices_count<kBatch, false><<<grid, block, 0, stream>>>(scores, N, Hkv, ragged, few, 0, 0, 0, S);
-                    slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, 0, 0, 0, S);
+                    slices_collect<kBatch, false><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, 0, 0, 0, S);
                 }
                 slices_safeguard<kBatch><<<grid, block, 0, stream>>>(scores, N, n_safe, Hkv, ragged, few, S, all.keys, all.hist);
             });
             over_groups(all, [&](const Slices &S, dim3 grid) {
-                slices_collect<kBatch><<<grid, block, 0, stream>>>(scores, N, Hkv * budget, Hkv, ragged, few, 0, 0, 0, S);
+                slices_collect<kBatch, false><<<grid, block, 0, stream>>>(scores, N, Hkv * budget, Hkv, ragged, few, 0, 0, 0, S);
                 slices_emit<kBatch><<<grid, block, 0, stream>>>(scores, N, cap, Hkv, ragged, few, 0, 0, 0, S, keep_idx, counts);
             });
             return hipGetLastError();

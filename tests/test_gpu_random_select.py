@@ -169,3 +169,13 @@ def test_adaptive_safeguards_about_the_common_threshold(Hkv, N):
             got_idx, got_cnt = obc.obc_select_adaptive(dev, budget, n_safe, seq_lens=lens)
             np.testing.assert_array_equal(got_cnt.cpu().numpy(), want_cnt, err_msg=label)
             np.testing.assert_array_equal(got_idx.cpu().numpy(), want_idx, err_msg=label)
+
+
+@pytest.mark.parametrize("N", [262144, 262145, 4300001, 8400001])
+def test_counters_of_long_slices(N):
+    """Slices of one, four, eight and sixteen chunks; every key of a slice in one counter, and keys all over."""
+    rng = np.random.default_rng(8)
+    for s in (np.ones((1, 1, N), np.float32), rng.standard_normal((1, 1, N), dtype=np.float32)):
+        want = oracle.select(s, 700)
+        got = obc.obc_select(torch.from_numpy(s).cuda(), 700)
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
