@@ -7,13 +7,17 @@
 // six balanced base-256 digits, bf16 values 30 bits in four, which hold their elements exactly down to 2^-23 of the row's
 // largest.  Products of digits are summed exactly in 32-bit integers, for the seven highest of the levels (all of four by
 // four digits).  Fixed point alone cannot stand in for fp64: where a key has a large element that meets a small one of the
-// query, the digits that are left out are those the logit is made of.  With 2^E for the product of the powers of two just
-// above the rows' largest elements, a CPU model of the arithmetic is off by 2^-46 2^E at most over millions of pairs (2^-54
-// rms: normal elements, 2^-53: channels larger than the others by 8, 2^-50: elements over 20 binades) and by 2^-43.8 where
-// channels 2^24 larger on one side are as much smaller on the other.  So a wave whose 16 x 16 pairs have one below 2^-17 2^E,
-// where that could be more than 2^-26.8 of the dot product (its rounding to fp32 is 2^-25), or a row that the digits do not
-// hold (bf16 elements cut off, infinities, NaN), forms its dot products in fp64 as blocked_logits does: 0.5 % of them for
-// normal keys with channels larger by 8.  The scores of the benchmark shapes are the same bit for bit.
+// query, the digits that are left out are those the logit is made of.  So a wave whose 16 x 16 pairs have a dot product that
+// the digits may miss by more than 2^-27 of it (its rounding to fp32 is 2^-25 to 2^-24) forms them in fp64 as blocked_logits
+// does.  With 2^E for the product of the powers of two just above the rows' largest elements and d <= 128:
+//   the levels left out are at most d (4 * 2^14 * 2^24 + 3 * 2^14 * 2^16 + ..) 2^-92 = 2^-45 (fp32 only), what join_seven cuts
+//   off is 2^-50: 2^-27.9 of an fp32 dot product from 2^-17 2^E up, 2^-28 of a bf16 one from 2^-22 2^E up (kLeastDot);
+//   an fp32 row with an element below 2^-23 of its largest may have it cut off: by up to 2^-47 of the row's power of two per
+//   element, 2^-40 2^E per dot product and side, 2^-27 of it from 2^-12 2^E up (kLeastDotCut, for the blocks with such a row
+//   in their tile or their window rows).  Normal rows: one in 30000;
+//   bf16 rows with such elements, infinities, NaN: fp64 always.
+// Of normal keys with channels larger by 8, 0.5 % of the blocks go to fp64.  The scores of the benchmark shapes are the same
+// bit for bit.
 // Whole calls with one and with the other, by 64-token tiles times 128-row chunks over all heads, us:
 //   80 - 300: 20.0 / 24.7, 21.0 / 26.9, 30.3 / 36.1, 33.3 / 38.0; 384: 29.9 / 32.1; 432: 28.3 / 29.1; 456: 32.8 / 30.2;
 //   480: 53.7 / 53.3; 700 - 800: 27.7 / 27.8, 82.4 / 82.2; 1056: 84.7 / 77.7; 1344: 118.9 / 108.4; 3456: 93.5 / 77.0
@@ -58,7 +62,9 @@ constexpr int kRowDigits = 5;                  // of o_i, which is fp32 whatever
 constexpr int kLevels = 5;
 template <typename T> constexpr int kLogitDigits = sizeof(T) == 4 ? 6 : 4;
 constexpr int kLogitLevels = 7;
-template <typename T> constexpr double kLeastDot = sizeof(T) == 4 ? 0x1p34 : 0x1p29;       // units of join_seven
+// Least dot products that the digits give, in units of join_seven: of rows that they hold, and of fp32 rows that they cut.
+template <typename T> constexpr double kLeastDot = sizeof(T) == 4 ? 0x1p34 : 0x1p29;
+constexpr double kLeastDotCut = 0x1p39;
 
 // A wave has 16 window rows: the rows' digits and a block's sums fit 128 registers, so that four waves share a SIMD and hide
 // each other's latencies (with 32 rows per wave and two waves weights and scores took 37 and 43 us where 29 and 36 then were
@@ -139,6 +145,14 @@ __device__ __forceinline__ double join_seven(int l0, int l1, int l2, int l3, int
 // Exponent of a row whose elements the digits of a logit cannot hold.
 constexpr int kNoExponent = 1 << 20;
 __device__ __forceinline__ int logit_exponent(uint32_t amax) { return amax >= 0x7f800000u ? kNoExponent : max_exponent(amax); }
+// What four elements below 2^e have below the digits' bits, above zero if anything (but for what falls below fp32's range here:
+// 2^-149 of a unit and less).
+template <int K>
+__device__ __forceinline__ float below_digits(const float (&y)[4], int e, float cut) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cut = fmaxf(cut, __builtin_amdgcn_fractf(__builtin_amdgcn_ldexpf(y[i], 8 * K - 2 - e)));
+    return cut;
+}
 // Digits of elements below 2^e.  bf16 values: as integers of 30 bits, and `cut` is above zero where one has bits below those.
 template <typename T, int K>
 __device__ __forceinline__ void logit_digits(const float (&y)[4], int e, uint32_t (&plane)[K], float &cut) {
@@ -222,13 +236,14 @@ struct TokenTile {
         }
         return v;
     }
-    // The digits of digit_logits and the rows' exponents into LDS.
+    // The digits of digit_logits and the rows' exponents into LDS; fp32: also whether elements of the wave's rows were cut.
     template <int K>
-    __device__ __forceinline__ void store_logit_digits(char *digits, int *exponents) const {
+    __device__ __forceinline__ void store_logit_digits(char *digits, int *exponents, uint8_t *cut_s) const {
         int thread = threadIdx.x;
         asm volatile("" : "+v"(thread));                     // (addresses anew for every tile: registers)
         const int r0 = thread / kLanes, c = thread % kLanes;
         char *dst = digits + digit_offset<D, kTok>(0, r0, c * kPer / 16) + c * kPer % 16;
+        bool any_cut = false;                                // uniform
 #pragma unroll
         for (int i = 0; i < kCount; ++i) {
             __builtin_amdgcn_sched_barrier(0);               // (one piece at a time: registers)
@@ -248,9 +263,18 @@ struct TokenTile {
                 else *(uint2 *)at = make_uint2(p[0][k], p[1][k]);
             }
             if (c == 0) exponents[r0 + i * kStep] = logit_exponent(amax);
-            if (sizeof(T) == 2 && __builtin_amdgcn_ballot_w64(cut > 0.f) != 0ull)      // uniform, rare; a row's lanes are in one wave
+            if constexpr (sizeof(T) == 4) {
+                // (elements from 2^(e - 23) up are held; one below that, or a zero, is rare: in 1 of 10000 waves for normal ones)
+                const float least = __builtin_elementwise_minimum(__builtin_elementwise_minimum(fabsf(y[0][0]), fabsf(y[0][1])),
+                                                                  __builtin_elementwise_minimum(fabsf(y[0][2]), fabsf(y[0][3])));
+                const int e = max_exponent(amax);
+                if (__builtin_amdgcn_ballot_w64(least < __builtin_amdgcn_ldexpf(1.f, e - 23)) != 0ull)
+                    any_cut |= __builtin_amdgcn_ballot_w64(below_digits<K>(y[0], e, 0.f) > 0.f) != 0ull;
+            } else if (__builtin_amdgcn_ballot_w64(cut > 0.f) != 0ull) {     // uniform, rare; a row's lanes are in one wave
                 if (cut > 0.f) *(volatile int *)(exponents + r0 + i * kStep) = kNoExponent;
+            }
         }
+        if (sizeof(T) == 4 && threadIdx.x % 64 == 0) cut_s[threadIdx.x / 64] = any_cut;
     }
     // Digits and units into LDS and, where asked for, the rows' norms: ||v||^2 (2) or ||v||_1 (1).
     template <bool kWithDigits, int kNorm>
@@ -311,9 +335,10 @@ struct RowDigits {
                 x[k][kk] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(
                                                          span, (int)digit_address<K, D>(block, k, 0, kk * 64) + lane * 16, 0, 0));
     }
-    // Digits of a row itself, for digit_logits; returns the row's exponent.
+    // Digits of a row itself, for digit_logits; returns the row's exponent.  fp32: `any_cut`, whether elements of the wave's
+    // rows were cut.
     template <typename T>
-    __device__ __forceinline__ int take(const T *__restrict__ row, int g) {
+    __device__ __forceinline__ int take(const T *__restrict__ row, int g, bool &any_cut) {
         float y[D / 64][4][4];
 #pragma unroll
         for (int kk = 0; kk < D / 64; ++kk) {
@@ -349,12 +374,14 @@ struct RowDigits {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 uint32_t p[K];
+                if (sizeof(T) == 4) cut = below_digits<K>(y[kk][c], max_exponent(amax), cut);
                 logit_digits<T>(y[kk][c], max_exponent(amax), p, cut);
 #pragma unroll
                 for (int k = 0; k < K; ++k) x[k][kk][c] = (int)p[k];
             }
+        any_cut = sizeof(T) == 4 && __builtin_amdgcn_ballot_w64(cut > 0.f) != 0ull;
         if (sizeof(T) == 2) cut = across_rows<MaxOp>(cut);
-        return cut > 0.f ? kNoExponent : logit_exponent(amax);
+        return sizeof(T) == 2 && cut > 0.f ? kNoExponent : logit_exponent(amax);
     }
 };
 
@@ -508,6 +535,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void digit_logits(const T *__rest
     static_assert(kBuf == 2, "one barrier per tile");
     __shared__ __attribute__((aligned(16))) char digits[kBuf][K * kTok * D];
     __shared__ __attribute__((aligned(16))) int exponents[2][kTok];
+    __shared__ __attribute__((aligned(8))) uint8_t cut_s[2][kFixedThreads / 64];
     __shared__ float2 best_s[kParts][kRows];
     const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv, M = Hq / Hkv * W;
     const int len = seq_len_of(lens, ragged, b, N);
@@ -524,20 +552,26 @@ __global__ __launch_bounds__(kFixedThreads, 4) void digit_logits(const T *__rest
     next.load(span, 0);
     const T *q_row = q + ((size_t)b * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D;
     RowDigits<K, D> rows;
-    const int exponent = rows.template take<T>(q_row, lane >> 4) - 51 - 3;
+    bool rows_cut;
+    const int exponent = rows.template take<T>(q_row, lane >> 4, rows_cut) - 51 - 3;
     const int last = min(len - W + (w.r0 + min(row, w.nr - 1)) % W, t_end - 1);                // last token the row sees here
     const int least = __builtin_amdgcn_readfirstlane((int)row16_reduce<MinOp>((uint32_t)last));      // of the 16 rows
     float *zp = z + z_block(w, hl, min(row0 / 16 + rb, blocks - 1), t_begin) + lane * 4;
     float m = -INFINITY;
     int at = kNoToken;
-    next.template store_logit_digits<K>(digits[0], exponents[0]);
+    next.template store_logit_digits<K>(digits[0], exponents[0], cut_s[0]);
     if (t_begin + kTok < t_end) next.load(span, kTok);
     int slot = 0;
     for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
         __syncthreads();                                     // this tile is in LDS, the one before it has been read
-        if (t0 + kTok < t_end) next.template store_logit_digits<K>(digits[slot ^ 1], exponents[slot ^ 1]);
+        if (t0 + kTok < t_end) next.template store_logit_digits<K>(digits[slot ^ 1], exponents[slot ^ 1], cut_s[slot ^ 1]);
         if (t0 + 2 * kTok < t_end) next.load(span, t0 - t_begin + 2 * kTok);
         if (!live) continue;
+        double least_dot = kLeastDot<T>;
+        if (sizeof(T) == 4) {
+            const uint2 cut = *(const uint2 *)cut_s[slot];
+            if (rows_cut || __builtin_amdgcn_readfirstlane((int)(cut.x | cut.y)) != 0) least_dot = kLeastDotCut;     // uniform
+        }
 #pragma unroll 1
         for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
             i32x4 acc[kLogitLevels];
@@ -550,7 +584,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void digit_logits(const T *__rest
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 double dot = join_seven<K>(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r], acc[5][r], acc[6][r]);
-                again |= fabs(dot) < kLeastDot<T>;           // (also of the zeros past the end)
+                again |= fabs(dot) < least_dot;              // (also of the zeros past the end)
                 if (D == 128) dot *= 0.088388347648318440550 * 8.0;
                 x[r] = __builtin_amdgcn_ldexpf((float)dot, ex[r] + exponent);
             }

@@ -153,6 +153,37 @@ def test_logits_beyond_their_digits(shape, logits, score_path):
     _check(shape, q, k, v)
 
 
+@pytest.mark.parametrize("big", ["query", "key", "half"])
+@pytest.mark.parametrize("shape", DIGIT_SHAPES[:2], ids=lambda s: "%s_d%d_%dx%d_%d" % s)
+def test_rows_that_the_digits_cut(shape, big):
+    """Rows with elements half a unit of their digits above a whole one, all of them where the other side has its large ones:
+    the dot products stand out above 2^-17 2^E and what is cut off is 2^-23.3 of them, three roundings to fp32.  Logits of
+    some 2^12 make that 2^-11 in a weight, next to those of 16 keys whose rows are held.  Against weights of exact dot
+    products rounded once, which is what the logits are defined as."""
+    _, d, G, W, N = shape
+    below_one, tiny = 1 - 2.0 ** -24, 2.0 ** -24 * (1.25 + 2.0 ** -23)
+    n = {"query": 1, "half": d // 2, "key": d - 1}[big]      # elements of the key that are large
+    key, query = torch.full((d,), tiny), torch.full((d,), tiny)
+    key[:n], query[n:] = below_one, below_one
+    held = torch.zeros(d)
+    held[n:] = float(key.double() @ query.double()) / (d - n)
+    query *= 2.0 ** 32
+    k = key.repeat(1, HKV, N, 1)
+    k[:, :, :16] = held
+    q, v = query.repeat(1, G * HKV, W, 1), _random(shape, 76)[2]
+    z64 = (torch.stack((held, key)).double() @ query.double()) / d ** 0.5
+    z = z64.float()
+    ulp = 2.0 ** (torch.frexp(z)[1] - 24).double()
+    assert bool((((z64 - z.double()).abs() / ulp) < 0.49).all()) and 2.0 ** 11 < float(z.min())     # no matter of rounding
+    row = torch.full((N,), float(z[1]), dtype=torch.float64)
+    row[:16] = float(z[0])
+    want = sum(G * torch.nn.functional.pad(torch.softmax(row[:N - W + 1 + r], 0), (0, W - 1 - r)) for r in range(W))
+    got = obc.obc_score(q.cuda(), k.cuda(), v.cuda(), "attn").cpu().double()
+    err = float(((got - want) / want).abs().max())
+    print(err)
+    assert err <= TOL["fp32"], err
+
+
 @pytest.mark.parametrize("shape", DIGIT_SHAPES[:4], ids=lambda s: "%s_d%d_%dx%d_%d" % s)
 def test_digit_logits_at_the_end_of_fp32(shape):
     test_logits_at_the_end_of_fp32_have_weight_zero(shape)
