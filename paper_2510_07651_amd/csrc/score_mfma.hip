@@ -1263,39 +1263,59 @@ static size_t record_bytes(int m_pad, int variant) { return (size_t)(m_pad < 128
 static const ShareCost &sweep1_cost(int variant, int rows) {
     return rows <= kFewRows ? kSweep1FewCost : needs_output(variant) ? kSweep1Cost : kSweep1SumsCost;
 }
+// A call with lengths searches anew, for every layer and token, so shares that cannot fit or cannot win are not counted out: a
+// sequence takes at least its tokens over the share and less than one workgroup more, and the estimate grows with the share.
+// Host time of an accumulating call through the binding, 8 heads, one window row, us: 8 x 64K 17 (25 with every round searched
+// from end to end), 32 x 4K 20 (37), 128 x 4K 35 (69); the shares are the same (1.7 million random batches).
 // `record_bytes`: of a workgroup's partial records; with more than the fewest workgroups they take at most kMostRecords, so
 // that plans that fit the static scratch go on doing so.
 constexpr size_t kMostRecords = (size_t)36 << 20;
 static int even_share(const int *len, int B, int N, int heads, const ShareCost &c, size_t record_bytes = 0, float *least_cost = nullptr) {
     constexpr int kUnits = 256;                                                // compute units
+    long long tokens = (long long)B * N;
+    if (len) {
+        tokens = 0;
+        for (int b = 0; b < B; ++b) tokens += len[b];
+    }
     auto workgroups = [&](int share) {
         long long n = 0;
         if (!len) return (long long)heads * B * ((N + share - 1) / share);
-        for (int b = 0; b < B; ++b) n += (len[b] + share - 1) / share;
+        for (int b = 0; b < B; ++b) n += (unsigned)(len[b] + share - 1) / (unsigned)share;
         return n * heads;
     };
-    auto cost = [&](int share) {
-        const long long n = workgroups(share);
-        const float records = (float)c.record * (float)((n + kUnits - 1) / kUnits);
-        if (c.pairs && n > kUnits) return (float)((n + 2 * kUnits - 1) / (2 * kUnits)) * (c.crowd * share + c.crowd_start) + records;
-        return (float)((n + kUnits - 1) / kUnits) * (float)(share + c.start) + records;
+    auto cost = [&](int share, int rounds) {                                   // on (rounds - 1) * kUnits + 1 .. rounds * kUnits workgroups
+        const float records = (float)c.record * (float)rounds;
+        if (c.pairs && rounds > 1) return (float)((rounds + 1) / 2) * (c.crowd * share + c.crowd_start) + records;
+        return (float)rounds * (float)(share + c.start) + records;
     };
-    const int most = (N + c.unit - 1) / c.unit;
-    int best = 0;
+    auto rounds_of = [&](int share) { return (int)((workgroups(share) + kUnits - 1) / kUnits); };
+    const int most = (N + c.unit - 1) / c.unit, fewest = rounds_of(most * c.unit);
+    int best = 0, hi = most;                                                   // (hi: fits)
     float best_cost = 0.f;
-    for (int rounds = 1; rounds <= 16; ++rounds) {
-        int lo = 1, hi = most;                                                 // the shortest share that fits, if any does
-        if (workgroups(hi * c.unit) > (long long)rounds * kUnits) continue;
-        while (lo < hi) {
-            const int mid = (lo + hi) / 2;
-            if (workgroups(mid * c.unit) <= (long long)rounds * kUnits) hi = mid; else lo = mid + 1;
+    for (int rounds = fewest < 1 ? 1 : fewest; rounds <= 16; ++rounds) {
+        // The shortest share that fits; one that fits fewer rounds, too, has been looked at with them.
+        const long long fit = (long long)rounds * kUnits / heads;              // workgroups per KV head and chunk, at most
+        int lo = (int)((tokens + fit * c.unit - 1) / (fit * c.unit));
+        if (lo < 1) lo = 1;
+        if (fit > B) {                                                         // (a sequence takes less than one more than its tokens over the share)
+            const long long enough = (tokens + (fit - B) * c.unit - 1) / ((fit - B) * c.unit);
+            if (enough < hi) hi = (int)(enough < lo ? lo : enough);
         }
-        if (best != 0 && workgroups(lo * c.unit) * record_bytes > kMostRecords) break;
-        const float t = cost(lo * c.unit);
-        if (best == 0 || t < best_cost) { best = lo * c.unit; best_cost = t; }
+        auto wins = [&](int units) { return best == 0 || cost(units * c.unit, rounds) < best_cost; };
+        int top = hi;
+        while (lo < top && wins(lo)) {
+            const int mid = (lo + top) / 2;
+            if (workgroups(mid * c.unit) <= (long long)rounds * kUnits) top = mid; else lo = mid + 1;
+        }
+        if (lo < top || !wins(lo)) continue;
+        const int share = lo * c.unit;
+        if (best != 0 && workgroups(share) * record_bytes > kMostRecords) break;
+        const float t = cost(share, rounds_of(share));
+        if (best == 0 || t < best_cost) { best = share; best_cost = t; }
         if (lo == 1) break;
+        hi = lo;
     }
-    if (!best) { best = most * c.unit; best_cost = cost(best); }               // more sequences than sixteen rounds: one workgroup each
+    if (!best) { best = most * c.unit; best_cost = cost(best, fewest); }       // more sequences than sixteen rounds: one workgroup each
     if (least_cost) *least_cost = best_cost;
     return best;
 }
@@ -1350,9 +1370,9 @@ static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
     }
     int full = ws.n_chunks - ws.solo;
     float wide = 0.f, solo = 0.f, padded = 0.f;
-    const ShareCost &cost = ws.use_wide ? kSweep2WideCost : kSweep2Cost;
-    ws.range_len = even_share(len, a.B, a.N, a.Hkv * (full > 0 ? full : 1), cost, 0, &wide);
-    ws.range_solo = even_share(len, a.B, a.N, a.Hkv, kSweep2SoloCost, 0, &solo);
+    const ShareCost &cost = ws.keep_z ? kFewRowsCost : ws.use_wide ? kSweep2WideCost : kSweep2Cost;
+    if (full > 0) ws.range_len = even_share(len, a.B, a.N, a.Hkv * full, cost, 0, &wide);        // (kFewRowsCost: whole steps of its workgroups)
+    if (ws.solo) ws.range_solo = even_share(len, a.B, a.N, a.Hkv, kSweep2SoloCost, 0, &solo);
     // A last chunk of at most 64 rows behind full ones: a launch of its own spends 0.7 of the time on a token and a start of its
     // own; on short prompts that start costs more than the empty half of a 128-row chunk.  408 rows, 4 x 4 heads x 3507 ragged,
     // key: 27.9 + 12.7 us, as four chunks 32.1; 168 rows, 4 heads x 20000, all: 21.0 + 16.0, as two 29.8; x 60000, joint: 39.9 +
@@ -1361,8 +1381,8 @@ static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
         const int range = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, cost, 0, &padded);
         if (padded < wide + 0.7f * solo + kLaunchCost) { ws.solo = 0; ws.range_len = range; }
     }
-    if (ws.keep_z) ws.range_len = even_share(len, a.B, a.N, a.Hkv, kFewRowsCost);        // (whole steps of its workgroups)
-    else if (const int v = tuned_range(); v >= 64 && v <= 65536 && v % 64 == 0) ws.range_len = ws.range_solo = v;
+    if (ws.keep_z) return ws;
+    if (const int v = tuned_range(); v >= 64 && v <= 65536 && v % 64 == 0) ws.range_len = ws.range_solo = v;
     return ws;
 }
 
