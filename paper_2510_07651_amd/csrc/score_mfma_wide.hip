@@ -51,15 +51,15 @@ __device__ __forceinline__ void mma_first(f32x16 &acc, const f32x4 &a, const bf1
 __device__ __forceinline__ void mma_next(f32x16 &acc, const f32x4 &a, const bf16x8 &b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "a"(a), "v"(b));
 }
-// Reads a 16-byte operand from LDS into the accumulator file, where it stays; parked() waits for the reads before it.
-// (One instruction each: through architectural registers it were five, in a part of the kernel where every instruction is
-// fetched for the first time.)
+// Reads a 16-byte operand from LDS into the accumulator file, where it stays: parked() ties it there, which lets the compiler
+// load it in place and makes it wait for the load.  (One instruction each: through architectural registers it were five, in a
+// part of the kernel where every instruction is fetched for the first time.)
 template <int kOffset>
-__device__ __forceinline__ void park(f32x4 &x, uint32_t lds) {
+__device__ __forceinline__ void park(f32x4 &x, lds_ptr p) {
     static_assert(kOffset >= 0 && kOffset < 65536, "16 bits of offset");
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=a"(x) : "v"(lds), "n"(kOffset) : "memory");
+    x = *(const __attribute__((address_space(3))) f32x4 *)(p + kOffset);
 }
-__device__ __forceinline__ void parked() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void parked(f32x4 &x) { asm volatile("" : "+a"(x)); }
 // The matrix ops above are opaque to the compiler, which therefore cannot count the cycles a
 // vector instruction must keep away from a matrix op's result (the last pass of a 32x32x16 op
 // lands ten issue slots after the op).  Wherever vector code may follow a matrix op closely,
@@ -97,6 +97,12 @@ __device__ __forceinline__ RowConsts row_consts(lds_ptr p) {
 
 struct Stationary {          // per 32-row set S: Q, high and residual pieces of -2 o^ (accumulator file)
     f32x4 q[2][8], hi[2][8], lo[2][8];
+    __device__ __forceinline__ void tie() {
+#pragma unroll
+        for (int S = 0; S < 2; ++S)
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk) { parked(q[S][kk]); parked(hi[S][kk]); parked(lo[S][kk]); }
+    }
 };
 
 struct WideState {
@@ -238,8 +244,10 @@ __device__ __forceinline__ float sumsq_quarter(const bf16x8 x, int q, float acc)
 
 // What a wave needs to start one of its eight transfers of the tile that is fetched during a step.  Transfers of one
 // tensor lie 1 KB apart in LDS: the instruction's offset moves their memory address along, which the lane's offset takes
-// back, so that the LDS address register is written once per tensor (a write, its wait slot and the addition that makes the
-// address, for every transfer, were 24 instructions per block).  kBias keeps the lane offsets from falling below zero.
+// back, so that the LDS address register m0 is written once per tensor (a write, its wait slot and the addition that makes the
+// address, for every transfer, were 24 instructions per block).  Every transfer names m0 as its operand and brings the wait
+// slot that a write just before it would need; the compiler leaves out the writes that change nothing.  kBias keeps the lane
+// offsets from falling below zero.
 constexpr int kBias = 4096;
 struct TileFetch {
     const char *k_base, *v_base;     // kBias bytes ahead of the tile's first row in K and in V (uniform)
@@ -248,18 +256,16 @@ struct TileFetch {
 };
 template <int kSlot>
 __device__ __forceinline__ void transfer_at(const char *sbase, uint32_t voff, uint32_t lds) {
-    if constexpr (kSlot == 0)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(sbase) : "memory");
-    else
-        asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2 nt" ::"v"(voff), "s"(sbase), "n"(kSlot * 1024) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt" ::"{m0}"(lds), "v"(voff), "s"(sbase), "n"(kSlot * 1024) : "memory");
 }
 __device__ __forceinline__ void fetch_one(const TileFetch &f, int n) {       // n = 0..3: K, 4..7: V, in this order
     const char *base = n < 4 ? f.k_base : f.v_base;
+    const uint32_t lds = f.lds + (n < 4 ? 0 : kTileBytes);
     switch (n & 3) {
-        case 0: return transfer_at<0>(base, f.voff[0], f.lds + (n < 4 ? 0 : kTileBytes));
-        case 1: return transfer_at<1>(base, f.voff[1], 0);
-        case 2: return transfer_at<2>(base, f.voff[2], 0);
-        default: return transfer_at<3>(base, f.voff[3], 0);
+        case 0: return transfer_at<0>(base, f.voff[0], lds);
+        case 1: return transfer_at<1>(base, f.voff[1], lds);
+        case 2: return transfer_at<2>(base, f.voff[2], lds);
+        default: return transfer_at<3>(base, f.voff[3], lds);
     }
 }
 // All four transfers a wave issues for 64 rows from row `row0` of `rows`; rows past `last` (>= row0) re-read it.  `lds`: this
@@ -270,9 +276,9 @@ __device__ __forceinline__ void load_64_rows(const char *rows, int row0, int las
 #pragma unroll
     for (int n = 0; n < 4; ++n) voff[n] = moff[n] - (uint32_t)(max((wave * 4 + n) * 4 + (lane >> 4) - (last - row0), 0) * kRowBytes);
     transfer_at<0>(base, voff[0], lds);
-    transfer_at<1>(base, voff[1], 0);
-    transfer_at<2>(base, voff[2], 0);
-    transfer_at<3>(base, voff[3], 0);
+    transfer_at<1>(base, voff[1], lds);
+    transfer_at<2>(base, voff[2], lds);
+    transfer_at<3>(base, voff[3], lds);
 }
 // Zeros for rows `from` .. 63 of a 64-row tile in LDS, whatever its swizzle (256 threads).
 __device__ __forceinline__ void zero_rows(char *tile, int from) {
@@ -482,7 +488,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     Stationary A;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-        const uint32_t piece = lds0 + rh * kTileBytes + row_piece_offset(lane, kk);
+        const lds_ptr piece = base + rh * kTileBytes + row_piece_offset(lane, kk);
         park<0>(A.q[0][kk], piece);
         park<32 * kRowBytes>(A.q[1][kk], piece);
         park<kSlotBytes>(A.hi[0][kk], piece);
@@ -504,7 +510,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
         mine_special = ex >= t_begin && ex < t_end;
         if (mine_special) atomicOr(&special_s[special_word((ex - t_begin) >> 5)], 1u << ((ex - t_begin) >> 5 & 31));
     }
-    parked();
+    A.tie();
     const bool has_special = __syncthreads_or(mine_special) != 0;
 
     // Every wave has its stationary operands (the barrier above): the staging slots take the next three tiles.
@@ -746,7 +752,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
     Stationary A;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-        const uint32_t piece = lds0 + kSoloSlot + row_piece_offset(lane, kk);
+        const lds_ptr piece = base + kSoloSlot + row_piece_offset(lane, kk);
         park<0>(A.q[0][kk], piece);
         park<32 * kRowBytes>(A.q[1][kk], piece);
         park<2 * kSoloSlot>(A.hi[0][kk], piece);
@@ -759,7 +765,8 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
         R.kreg[kk] = lds_piece(R.kp[kk], 0);
         R.vreg[kk] = lds_piece(R.kp[kk], kBlkBytes);
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    A.tie();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // (the first block's operands, too)
     __syncthreads();                                           // every wave has its stationary operands: the slots are free
     group = next_tile(group, n_groups);
     load_block(kh, vh, block_of(group), len - 1, ring + kSoloSlot, lane);
