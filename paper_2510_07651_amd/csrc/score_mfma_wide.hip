@@ -13,8 +13,9 @@
 //   * The wave's 192 registers of stationary operands (Q and the two bf16 pieces of o_i for
 //     its 64 rows) live in the accumulator half of the register file.  The matrix ops read
 //     them from there directly (inline assembly: the compiler would otherwise copy each
-//     operand into the other half before every matrix op), leaving the architectural
-//     registers to accumulators, row constants and the streamed K/V pieces.
+//     operand into the other half before every matrix op), and so they do with the streamed
+//     K pieces, leaving the architectural registers to accumulators, row constants and the
+//     streamed V pieces.
 //   * With one wave per SIMD the overlap of matrix cores and vector ALUs comes from a
 //     software pipeline inside the wave: while the matrix cores form set A's logits and
 //     cross terms of block n, the vector ALUs score set B of block n-1; then the roles swap.
@@ -43,12 +44,21 @@ constexpr int kSlotBytes = 2 * kTileBytes;      // 32 KB: a K tile, then the V t
 constexpr int kRing = kSlots * kSlotBytes;      // 128 KB
 constexpr int kTilePerWave = 8;                 // direct-to-LDS transfers a wave issues per tile (4 K + 4 V)
 
-// acc = A * B (first op of a chain) and acc += A * B, with the 16-byte A operand in four accumulator-file
-// registers and B in four architectural ones.
-__device__ __forceinline__ void mma_first(f32x16 &acc, const f32x4 &a, const bf16x8 &b) {
+// acc = A * B (first op of a chain) and acc += A * B, with the 16-byte A operand in four accumulator-file registers.  B is
+// there, too, where it is a piece of K, which only matrix ops read; a piece of V is in architectural ones, as its norm is formed
+// from it.  (With K in those as well mfma_sweep2_solo ran out of them and fetched 7 to 8 values per block back from the
+// accumulator file for the joint score and all three, which no time showed: 4 x 8 heads x 32K, 64 rows, joint, 90.8 us then and
+// 91.2 now, all 99.)
+__device__ __forceinline__ void mma_k_first(f32x16 &acc, const f32x4 &a, const bf16x8 &b) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "a"(a), "a"(b));
+}
+__device__ __forceinline__ void mma_k_next(f32x16 &acc, const f32x4 &a, const bf16x8 &b) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "a"(a), "a"(b));
+}
+__device__ __forceinline__ void mma_v_first(f32x16 &acc, const f32x4 &a, const bf16x8 &b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "a"(a), "v"(b));
 }
-__device__ __forceinline__ void mma_next(f32x16 &acc, const f32x4 &a, const bf16x8 &b) {
+__device__ __forceinline__ void mma_v_next(f32x16 &acc, const f32x4 &a, const bf16x8 &b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "a"(a), "v"(b));
 }
 // Reads a 16-byte operand from LDS into the accumulator file, where it stays: parked() ties it there, which lets the compiler
@@ -107,7 +117,7 @@ struct Stationary {          // per 32-row set S: Q, high and residual pieces of
 
 struct WideState {
     f32x16 zA, voA, zB, voB;             // logits and cross terms of the two row sets
-    bf16x8 kreg[8], vreg[8];             // this lane's operand pieces of the current block
+    bf16x8 kreg[8], vreg[8];             // this lane's operand pieces of the current block (K: accumulator file)
     lds_ptr kp[8];                       // LDS address of operand piece kk of this lane's block in the tile read next
     RowConsts rc;
     float sv, sk, sj;                    // set A's sums of the block whose set B is still due
@@ -199,11 +209,11 @@ __device__ __forceinline__ void matrix_phase(const Stationary &A, f32x16 &z, f32
                                              const bf16x8 (&vreg)[8], Work &&work) {
 #pragma unroll
     for (int j = 0; j < 24; ++j) {
-        if (j == 0) mma_first(z, A.q[S][0], kreg[0]);
-        else if (j < 8) mma_next(z, A.q[S][j], kreg[j]);
-        else if (j == 8) mma_first(vo, A.hi[S][0], vreg[0]);
-        else if (j & 1) mma_next(vo, A.lo[S][(j - 8) >> 1], vreg[(j - 8) >> 1]);
-        else mma_next(vo, A.hi[S][(j - 8) >> 1], vreg[(j - 8) >> 1]);
+        if (j == 0) mma_k_first(z, A.q[S][0], kreg[0]);
+        else if (j < 8) mma_k_next(z, A.q[S][j], kreg[j]);
+        else if (j == 8) mma_v_first(vo, A.hi[S][0], vreg[0]);
+        else if (j & 1) mma_v_next(vo, A.lo[S][(j - 8) >> 1], vreg[(j - 8) >> 1]);
+        else mma_v_next(vo, A.hi[S][(j - 8) >> 1], vreg[(j - 8) >> 1]);
         work(j);
         __builtin_amdgcn_sched_barrier(0);
     }
