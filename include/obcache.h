@@ -35,7 +35,8 @@
  *   - Query head h reads KV head h / (Hq/Hkv).
  *   - Return value: OBC_OK or a negative obc_status_t.  Argument errors are
  *     detected on the host before anything is launched.
- *   - Same inputs give bit-identical outputs (no floating-point atomics).
+ *   - The same call gives bit-identical outputs (no floating-point atomics).  How its sums are split depends on the shapes and
+ *     lengths of the whole batch, so the low bits of a sequence's scores can differ between batches.
  *   - The library targets gfx950 only and has no CPU fallback.
  *   - obc_score picks its kernels from the shapes: bf16 with head_dim 128 runs on the matrix
  *     cores; a one-row window (W = 1, the decoding case) over a bf16 cache of up to ~1e5

@@ -17,11 +17,21 @@
 //   in their tile or their window rows).  Normal rows: one in 30000;
 //   bf16 rows with such elements, infinities, NaN: fp64 always.
 // Of normal keys with channels larger by 8, 0.5 % of the blocks go to fp64.  The scores of the benchmark shapes are the same
-// bit for bit.
+// bit for bit.  A block that goes that way does both, and fetches its operands from memory again: whole calls, joint, us,
+// ordinary inputs / every block in fp64 (key channels 2^26 larger that meet query channels as much smaller, or a key of zeros
+// among every sixteen) / fp64 throughout (blocked_logits) / fp32 keys that are all cut:
+//   fp32, d = 128,  8 heads x 128 rows x  8111 tokens    97 /  144 /  111 /  106     (the logits alone 35 / 86 / 49)
+//   fp32, d = 128, 32 heads x 256 rows x  8111 tokens  1071 / 1943 / 1256 / 1315     (426 / 1281 / 565)
+//   fp32, d =  64, 16 heads x 160 rows x 16000 tokens   343 /  519 /  364 /  388
+//   bf16, d =  64,  8 heads x 128 rows x 16384 tokens    95 /  133 /  107            (29 / 79 / 51)
+// So inputs of that kind take 1.25 to 1.55 times what they would in fp64, and ordinary ones are 1.06 to 1.17 times faster.  (Without
+// the digits while a wave's blocks go to fp64 one after the other, and with four of their loads in flight, such calls took 2 to
+// 8 % less: what they cost is the fp64 products themselves, at a wave's own pace from memory.)
 // Whole calls with one and with the other, by 64-token tiles times 128-row chunks over all heads, us:
 //   80 - 300: 20.0 / 24.7, 21.0 / 26.9, 30.3 / 36.1, 33.3 / 38.0; 384: 29.9 / 32.1; 432: 28.3 / 29.1; 456: 32.8 / 30.2;
 //   480: 53.7 / 53.3; 700 - 800: 27.7 / 27.8, 82.4 / 82.2; 1056: 84.7 / 77.7; 1344: 118.9 / 108.4; 3456: 93.5 / 77.0
-// as the digits of a workgroup's 128 rows cost as much as some tiles: digits from kDigitTiles = 512 on.
+// as the digits of a workgroup's 128 rows cost as much as some tiles: digits from kDigitTiles = 512 on.  (The line counts every
+// head of the call, so which kernel forms a sequence's logits, and with it their last bit now and then, depends on the batch.)
 //
 // v_p . o_i (fixed_score).  Each row of v and o is scaled by a power of two to fixed point, 38 bits and a sign relative to
 // the row's largest element (30 for bf16 values, whose elements have 8 significant bits), and written as five (four)
