@@ -1141,29 +1141,36 @@ struct AdaptiveShared {
     int above_before, gt_before, gt_head, eq_before_heads, eq_before, eq_head;
 };
 
-// The key of rank *rank among the keys of a class, by one wave: three digits of 7 bits over what is left of a key below its
-// first digit.  visit(f) calls f(key) for the lane's share.  hist: 128 counters of the wave's own.  Leaves in *rank how many
-// keys equal to it there are down to that rank.
+// The key of rank *rank among the keys of a class: three digits of 7 bits over what is left of a key below its first digit.
+constexpr int kRankBits = 7;
+static_assert(3 * kRankBits == 32 - kSliceBits, "three digits below the first one");
+
+// One digit, by one wave, from its 128 counters: into *key, and into *rank what is left of it among the keys with that digit.
+__device__ __forceinline__ void wave_digit(const int *hist, int shift, uint32_t *key, int *rank) {
+    const int lane = threadIdx.x & 63;
+    const int2 c = *(const int2 *)(hist + 2 * lane);
+    const int incl = wave_scan<true>(c.x + c.y, lane), above = incl - c.x - c.y;
+    const unsigned long long at = __ballot(above < *rank && *rank <= incl);      // one lane
+    const bool upper = *rank <= above + c.y;
+    const int from = at ? __ffsll(at) - 1 : 0;
+    const int digit = __shfl(2 * lane + (upper ? 1 : 0), from), less = __shfl(above + (upper ? 0 : c.y), from);
+    *key |= (uint32_t)digit << shift;
+    *rank -= less;
+}
+
+// All three by one wave.  visit(f) calls f(key) for the lane's share.  hist: 128 counters of the wave's own.  Leaves in *rank
+// how many keys equal to it there are down to that rank.
 template <typename Visit>
 __device__ __forceinline__ uint32_t wave_select(int *hist, uint32_t key, int *rank, Visit &&visit) {
-    constexpr int kBits = 7;
-    static_assert(3 * kBits == 32 - kSliceBits, "three digits below the first one");
     const int lane = threadIdx.x & 63;
     auto ordered = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); };
 #pragma unroll
-    for (int shift = 2 * kBits; shift >= 0; shift -= kBits) {
+    for (int shift = 2 * kRankBits; shift >= 0; shift -= kRankBits) {
         *(int2 *)(hist + 2 * lane) = make_int2(0, 0);
         ordered();
-        visit([&](uint32_t k) { if ((k ^ key) >> (shift + kBits) == 0) atomicAdd(&hist[(k >> shift) & 127], 1); });
+        visit([&](uint32_t k) { if ((k ^ key) >> (shift + kRankBits) == 0) atomicAdd(&hist[(k >> shift) & 127], 1); });
         ordered();
-        const int2 c = *(const int2 *)(hist + 2 * lane);
-        const int incl = wave_scan<true>(c.x + c.y, lane), above = incl - c.x - c.y;
-        const unsigned long long at = __ballot(above < *rank && *rank <= incl);      // one lane
-        const bool upper = *rank <= above + c.y;
-        const int from = at ? __ffsll(at) - 1 : 0;
-        const int digit = __shfl(2 * lane + (upper ? 1 : 0), from), less = __shfl(above + (upper ? 0 : c.y), from);
-        key |= (uint32_t)digit << shift;
-        *rank -= less;
+        wave_digit(hist, shift, &key, rank);
     }
     return key;
 }
@@ -1236,82 +1243,126 @@ __device__ __forceinline__ HeadThreshold head_threshold(AdaptiveShared &sh, cons
         }
         __syncthreads();
     }
-    // Safeguards that end inside the common class, a wave per head; their keys leave the competition: as 0, which no key
-    // is, but for those equal to the last one.
-    if (any_safe) {                                          // uniform
+    // f(key, place) over the lists of slices with want(head) where they lie: a wave takes 1024 keys of a slice at a time, several
+    // waves the same slice where there are fewer than sixteen.  (With one load in flight, and a wave per head for the safeguards,
+    // crowded classes made the selection slower than the five kernels are.  2 x 8 heads x 24001 scores, budget 1024, us, five
+    // kernels / so / now: uniform 57 / 82 / 47, all in one class 221 / 308 / 135; 8 x 90000 141 / 191 / 88 and 808 / 1133 / 464;
+    // 4 x 32 x 4000, uniform 45 / 62 / 51.)
+    const int by = 31 - __builtin_clz(max(kSelWaves / n, 1));                    // 2^by waves per slice
+    auto visit_global = [&](auto &&want, auto &&f) {
+        constexpr int kLoads = 4;                            // (of four keys per lane, in flight together)
+        const int uwave = __builtin_amdgcn_readfirstlane(wave);
+        for (int sl = uwave >> by; sl < n; sl += kSelWaves >> by) {
+            const int c = __builtin_amdgcn_readfirstlane(sh.count[sl]);
+            if (c == 0 || !want(sl / S.per_head)) continue;  // uniform in the wave
+            const uint32_t *src = lists + (size_t)sl * S.list_stride;            // (lists start at multiples of four keys)
+            const int last = (c - 1) / 4 * 4, o = __builtin_amdgcn_readfirstlane(sh.offset[sl]);
+            for (int i0 = (uwave & ((1 << by) - 1)) * 256 * kLoads; i0 < c; i0 += 256 * kLoads << by) {
+                uint4 key[kLoads];
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) key[u] = *(const uint4 *)(src + min(i0 + 256 * u + 4 * lane, last));
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    const int i = i0 + 256 * u + 4 * lane;
+                    if (i0 + 256 * u >= c) break;            // uniform
+                    const uint32_t k[4] = {key[u].x, key[u].y, key[u].z, key[u].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (i + e < c) f(k[e], o + i + e);
+                }
+            }
+        }
+    };
+    // Safeguards that end inside the common class; their keys leave the competition: as 0, which no key is, but for those
+    // equal to the last one.  A wave per head; where the lists do not fit LDS, whose space is free then, all heads at a time.
+    if (any_safe && in_lds) {                                // uniform
         static_assert(D::kBins1 == kSelWaves * 128, "counters of wave_select");
         for (int h = wave; h < S.heads; h += kSelWaves) {
             if (!safe_of(h)) continue;                       // uniform in the wave
             const int j0 = sh.offset[h * S.per_head], j1 = sh.offset[(h + 1) * S.per_head];
             int rank = sh.head[h].safe_rank;
             const uint32_t thr = wave_select(sh.hist1 + 128 * wave, sh.head[h].digit << (32 - kSliceBits), &rank, [&](auto &&f) {
-                if (in_lds) {
 #pragma unroll 4
-                    for (int j = j0 + lane; j < j1; j += 64) f(sh.list[j]);
-                } else {
-                    for (int sl = h * S.per_head; sl < (h + 1) * S.per_head; ++sl) {
-                        const uint32_t *src = lists + (size_t)sl * S.list_stride;
-                        const int c = sh.count[sl];
-#pragma unroll 8
-                        for (int i = lane; i < c; i += 64) f(src[i]);
-                    }
-                }
+                for (int j = j0 + lane; j < j1; j += 64) f(sh.list[j]);
             });
             if (lane == 0) { sh.safe_thr[h] = thr; sh.safe_eq[h] = rank; }
-            if (in_lds)
-                for (int j = j0 + lane; j < j1; j += 64)
-                    if (sh.list[j] > thr) sh.list[j] = 0u;
+            for (int j = j0 + lane; j < j1; j += 64)
+                if (sh.list[j] > thr) sh.list[j] = 0u;
         }
         __syncthreads();
         clear_counters<D::kBins1>(sh.hist1);
         __syncthreads();
-    }
-    // f(key, place) over the lists; key 0: of a safeguard
-    auto visit = [&](auto &&f) {
-        if (in_lds) {
-            for (int j = tid; j < n_list; j += kSelThreads) f(sh.list[j], j);
-        } else {
-            for (int sl = wave; sl < n; sl += kSelWaves) {
-                const uint32_t *src = lists + (size_t)sl * S.list_stride;
-                const int c = sh.count[sl], o = sh.offset[sl], h = sl / S.per_head;
-                const uint32_t most = safe_of(h) ? sh.safe_thr[h] : 0xffffffffu;
-                for (int i = lane; i < c; i += 64) {
-                    const uint32_t key = src[i];
-                    f(key > most ? 0u : key, o + i);
-                }
+    } else if (__builtin_expect(any_safe, false)) {
+        static_assert(kFewHeads * 128 <= kAdaptiveList, "counters of a digit for every head");
+        int *const counters = (int *)sh.list;
+        if (tid < S.heads && safe_of(tid)) { sh.safe_thr[tid] = sh.head[tid].digit << (32 - kSliceBits); sh.safe_eq[tid] = sh.head[tid].safe_rank; }
+#pragma unroll 1
+        for (int shift = 2 * kRankBits; shift >= 0; shift -= kRankBits) {
+            for (int i = tid; i < S.heads * 128; i += kSelThreads) counters[i] = 0;
+            __syncthreads();
+            uint32_t prefix;
+            int *of_head;
+            visit_global([&](int h) {
+                if (!safe_of(h)) return false;
+                prefix = sh.safe_thr[h];
+                of_head = counters + 128 * h;
+                return true;
+            }, [&](uint32_t key, int) { if ((key ^ prefix) >> (shift + kRankBits) == 0) atomicAdd(&of_head[(key >> shift) & 127], 1); });
+            __syncthreads();
+            for (int h = wave; h < S.heads; h += kSelWaves) {
+                if (!safe_of(h)) continue;                   // uniform in the wave
+                uint32_t thr = sh.safe_thr[h];
+                int rank = sh.safe_eq[h];
+                wave_digit(counters + 128 * h, shift, &thr, &rank);
+                if (lane == 0) { sh.safe_thr[h] = thr; sh.safe_eq[h] = rank; }
             }
+            __syncthreads();
         }
-    };
+    }
     // keys equal to a safeguard's last one that belong to it, taken off a digit's counters
     auto take_off = [&](int *hist, int shift, uint32_t bins, auto &&counted) {
         if (!any_safe) return;                               // uniform
         __syncthreads();
         if (tid < S.heads && safe_of(tid) && counted(sh.safe_thr[tid])) atomicSub(&hist[(sh.safe_thr[tid] >> shift) & (bins - 1)], sh.safe_eq[tid]);
     };
-    uint32_t digit;
-    visit([&](uint32_t key, int) { if (key) atomicAdd(&sh.hist1[(key >> D::kShift1) & (D::kBins1 - 1)], 1); });
-    take_off(sh.hist1, D::kShift1, D::kBins1, [](uint32_t) { return true; });
-    pick_digit<D::kBins1>(sh.hist1, sh.pick, &digit, &remaining, &n_equal);
-    const uint32_t middle = digit;
-    auto in_middle = [&](uint32_t key) { return ((key >> D::kShift1) & (D::kBins1 - 1)) == middle; };
-    visit([&](uint32_t key, int) { if (key && in_middle(key)) atomicAdd(&sh.hist2[key & (D::kBins2 - 1)], 1); });
-    take_off(sh.hist2, 0, D::kBins2, in_middle);
-    pick_digit<D::kBins2>(sh.hist2, sh.pick, &digit, &remaining, &n_equal);
-    const uint32_t common = (own.digit << (32 - kSliceBits)) | (middle << D::kShift1) | digit;
-    // The head keeps its safeguard alone where that ends below the threshold.
-    const bool safe_only = safe_of(own_head) && sh.safe_thr[own_head] < common;
+    // visit(f): f(key, place) over the lists; key 0: of a safeguard
     HeadThreshold t;
-    t.thr = safe_only ? sh.safe_thr[own_head] : common;
+    uint32_t common;
+    bool safe_only;
     int gt_before = 0, gt_head = 0, eq_heads = 0, eq_before = 0, eq_head = 0;
-    visit([&](uint32_t key, int j) {
-        const bool in_head = j >= p_head0 && j < p_head1;    // (no branches: as in slice_threshold)
-        const int gt = in_head & (key == 0u || key > t.thr) ? 1 : 0, eq = in_head & (key == t.thr) ? 1 : 0;
-        gt_head += gt;
-        eq_head += eq;
-        gt_before += j < p_slice ? gt : 0;
-        eq_before += j < p_slice ? eq : 0;
-        eq_heads += (j < p_head0) & (key == common) ? 1 : 0;
-    });
+    auto settle = [&](auto &&visit) {
+        uint32_t digit;
+        visit([&](uint32_t key, int) { if (key) atomicAdd(&sh.hist1[(key >> D::kShift1) & (D::kBins1 - 1)], 1); });
+        take_off(sh.hist1, D::kShift1, D::kBins1, [](uint32_t) { return true; });
+        pick_digit<D::kBins1>(sh.hist1, sh.pick, &digit, &remaining, &n_equal);
+        const uint32_t middle = digit;
+        auto in_middle = [&](uint32_t key) { return ((key >> D::kShift1) & (D::kBins1 - 1)) == middle; };
+        visit([&](uint32_t key, int) { if (key && in_middle(key)) atomicAdd(&sh.hist2[key & (D::kBins2 - 1)], 1); });
+        take_off(sh.hist2, 0, D::kBins2, in_middle);
+        pick_digit<D::kBins2>(sh.hist2, sh.pick, &digit, &remaining, &n_equal);
+        common = (own.digit << (32 - kSliceBits)) | (middle << D::kShift1) | digit;
+        // The head keeps its safeguard alone where that ends below the threshold.
+        safe_only = safe_of(own_head) && sh.safe_thr[own_head] < common;
+        t.thr = safe_only ? sh.safe_thr[own_head] : common;
+        visit([&](uint32_t key, int j) {
+            const bool in_head = j >= p_head0 && j < p_head1;    // (no branches: as in slice_threshold)
+            const int gt = in_head & (key == 0u || key > t.thr) ? 1 : 0, eq = in_head & (key == t.thr) ? 1 : 0;
+            gt_head += gt;
+            eq_head += eq;
+            gt_before += j < p_slice ? gt : 0;
+            eq_before += j < p_slice ? eq : 0;
+            eq_heads += (j < p_head0) & (key == common) ? 1 : 0;
+        });
+    };
+    if (__builtin_expect(in_lds, true)) {
+        settle([&](auto &&f) { for (int j = tid; j < n_list; j += kSelThreads) f(sh.list[j], j); });
+    } else {
+        settle([&](auto &&f) {
+            uint32_t most;
+            visit_global([&](int h) { most = safe_of(h) ? sh.safe_thr[h] : 0xffffffffu; return true; },
+                         [&](uint32_t key, int j) { f(key > most ? 0u : key, j); });
+        });
+    }
     auto add = [&](int *to, int x) {
         if (__ballot(x != 0) == 0ull) return;                // uniform
         x = (int)wave_reduce<SumOp>((uint32_t)x);

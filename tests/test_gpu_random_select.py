@@ -171,6 +171,25 @@ def test_adaptive_safeguards_about_the_common_threshold(Hkv, N):
             np.testing.assert_array_equal(got_idx.cpu().numpy(), want_idx, err_msg=label)
 
 
+@pytest.mark.parametrize("Hkv,N", [(1, 32768), (2, 8191), (1, 20001), (3, 20001), (8, 70001), (32, 9001), (31, 3001)])
+def test_adaptive_classes_beyond_lds(Hkv, N):
+    """All scores of a sequence in one class of the first digit: lists of 16 K to 560 K keys, read where they lie, on four slices
+    and more, of one chunk and of four, full and empty; safeguards that end at, above and below the threshold."""
+    rng = np.random.default_rng(1000 * Hkv + N)
+    shift = rng.random((2, Hkv, 1))
+    lens = [N, N - min(4097, N // 2)]
+    budget = min(lens) // 5
+    for levels in (5, 1 << 20):
+        s = (1 + (np.floor(rng.random((2, Hkv, N)) * levels) / levels + shift) / 17).astype(np.float32)      # 1 .. 1.118
+        dev = torch.from_numpy(s).cuda()
+        for n_safe in (0, 1, budget // 3, budget - 1):
+            label = "levels %d n_safe %d" % (levels, n_safe)
+            want_idx, want_cnt = oracle.select_adaptive(s, budget, n_safe, seq_lens=lens)
+            got_idx, got_cnt = obc.obc_select_adaptive(dev, budget, n_safe, seq_lens=lens)
+            np.testing.assert_array_equal(got_cnt.cpu().numpy(), want_cnt, err_msg=label)
+            np.testing.assert_array_equal(got_idx.cpu().numpy(), want_idx, err_msg=label)
+
+
 @pytest.mark.parametrize("N", [262144, 262145, 4300001, 8400001])
 def test_counters_of_long_slices(N):
     """Slices of one, four, eight and sixteen chunks; every key of a slice in one counter, and keys all over."""
