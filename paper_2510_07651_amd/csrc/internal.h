@@ -45,14 +45,15 @@ struct ScoreArgs {
 struct ScoreWorkspace {
     size_t out_bf16;   // bf16  [2][B*Hkv*m_pad*d]  o_i as two bf16 pieces (high, residual); rows of a KV head padded to a multiple of 32
     size_t row_const;  // float [B*Hkv*m_pad*4]  per padded row: 2*(max + log2 sum) in log2 units, ||o||^2, last visible key, spare
-    size_t part_ml;    // float [B*Hkv*splits*m_pad*4]  per sequence split: row max (raw q.k), row sum, spare x2
+    size_t part_ml;    // float [Hkv*records*m_pad*4]  per sequence split: row max (raw q.k), row sum, spare x2
     size_t special;    // float [B*Hkv*m_pad*4]  per padded row: separately scored top key (token or -1) and its value/key/joint terms
-    size_t part_o;     // float [B*Hkv*splits*m_pad*d]  per sequence split: unnormalised output
+    size_t part_o;     // float [Hkv*records*m_pad*d]  per sequence split: unnormalised output
     size_t planes;     // float [n_chunks*nv*B*Hkv*N]   per row-chunk partial scores (only when n_chunks > 1)
     size_t total;
     int m_pad;         // padded rows per KV head (multiple of 32)
     int n_chunks;      // row chunks of 128 rows per KV head
     int splits;        // sequence splits in the first sweep
+    int records;       // splits of all sequences together there is room for
     int split_len;     // tokens per split (multiple of 64)
     int range_len;     // tokens per workgroup in the second sweep (multiple of 64)
     int use_mfma;      // 1: bf16 matrix-core path, 0: general path

@@ -48,6 +48,7 @@
 // skips it.  One pass serves every input: nothing is rescanned for rows that turn out dominated.
 //
 // A and Z never touch HBM.  All sums have a fixed order: results are bit-reproducible.
+#include <algorithm>
 #include <cfloat>
 
 #include "internal.h"
@@ -1270,7 +1271,9 @@ static const ShareCost &sweep1_cost(int variant, int rows) {
 // `record_bytes`: of a workgroup's partial records; with more than the fewest workgroups they take at most kMostRecords, so
 // that plans that fit the static scratch go on doing so.
 constexpr size_t kMostRecords = (size_t)36 << 20;
-static int even_share(const int *len, int B, int N, int heads, const ShareCost &c, size_t record_bytes = 0, float *least_cost = nullptr) {
+// `most_records`: workgroups per KV head and chunk there is room for (at least what the plan's own share takes).
+static int even_share(const int *len, int B, int N, int heads, const ShareCost &c, size_t record_bytes = 0, float *least_cost = nullptr,
+                      int most_records = 0x7fffffff) {
     constexpr int kUnits = 256;                                                // compute units
     long long tokens = (long long)B * N;
     if (len) {
@@ -1294,7 +1297,7 @@ static int even_share(const int *len, int B, int N, int heads, const ShareCost &
     float best_cost = 0.f;
     for (int rounds = fewest < 1 ? 1 : fewest; rounds <= 16; ++rounds) {
         // The shortest share that fits; one that fits fewer rounds, too, has been looked at with them.
-        const long long fit = (long long)rounds * kUnits / heads;              // workgroups per KV head and chunk, at most
+        const long long fit = std::min((long long)rounds * kUnits / heads, (long long)most_records);     // workgroups per KV head and chunk, at most
         int lo = (int)((tokens + fit * c.unit - 1) / (fit * c.unit));
         if (lo < 1) lo = 1;
         if (fit > B) {                                                         // (a sequence takes less than one more than its tokens over the share)
@@ -1305,14 +1308,14 @@ static int even_share(const int *len, int B, int N, int heads, const ShareCost &
         int top = hi;
         while (lo < top && wins(lo)) {
             const int mid = (lo + top) / 2;
-            if (workgroups(mid * c.unit) <= (long long)rounds * kUnits) top = mid; else lo = mid + 1;
+            if (workgroups(mid * c.unit) <= fit * heads) top = mid; else lo = mid + 1;
         }
         if (lo < top || !wins(lo)) continue;
         const int share = lo * c.unit;
         if (best != 0 && workgroups(share) * record_bytes > kMostRecords) break;
         const float t = cost(share, rounds_of(share));
         if (best == 0 || t < best_cost) { best = share; best_cost = t; }
-        if (lo == 1) break;
+        if (lo == 1 || fit == most_records) break;
         hi = lo;
     }
     if (!best) { best = most * c.unit; best_cost = cost(best, fewest); }       // more sequences than sixteen rounds: one workgroup each
@@ -1332,41 +1335,55 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     ws->splits = (N + ws->split_len - 1) / ws->split_len;
     ws->use_wide = form != 1 && sweep2_wide_covers(variant) ? 1 : 0;
     ws->solo = ws->use_wide && (M - 1) % 128 < 64 ? 1 : 0;
-    const size_t rows = (size_t)BH * ws->m_pad;
-    ws->out_bf16 = *off;  *off = align_up(*off + 2 * rows * d * 2, 256);   // high pieces, then residual pieces
-    ws->row_const = *off; *off = align_up(*off + rows * 4 * sizeof(float), 256);
-    ws->part_ml = *off;   *off = align_up(*off + rows * ws->splits * 4 * sizeof(float), 256);
-    ws->special = *off;   *off = align_up(*off + rows * 4 * sizeof(float), 256);
-    ws->part_o = *off;
-    if (needs_output(variant)) *off = align_up(*off + rows * ws->splits * d * sizeof(float), 256);
-    ws->planes = *off;
-    if (ws->n_chunks > 1) *off = align_up(*off + (size_t)ws->n_chunks * nv * BH * N * sizeof(float), 256);
+    ws->z_stride = (N + 31) / 32 * 32;
+    const size_t rows = (size_t)BH * ws->m_pad, first = *off, z_bytes = (size_t)BH * M * ws->z_stride * sizeof(float);
+    ws->keep_z = 0;
+    auto lay_out = [&](int records) {
+        size_t at = first;
+        const size_t record_rows = (size_t)Hkv * records * ws->m_pad;
+        ws->records = records;
+        ws->out_bf16 = at;  at = align_up(at + 2 * rows * d * 2, 256);      // high pieces, then residual pieces
+        ws->row_const = at; at = align_up(at + rows * 4 * sizeof(float), 256);
+        ws->part_ml = at;   at = align_up(at + record_rows * 4 * sizeof(float), 256);
+        ws->special = at;   at = align_up(at + rows * 4 * sizeof(float), 256);
+        ws->part_o = at;
+        if (needs_output(variant)) at = align_up(at + record_rows * d * sizeof(float), 256);
+        ws->planes = at;
+        if (ws->n_chunks > 1) at = align_up(at + (size_t)ws->n_chunks * nv * BH * N * sizeof(float), 256);
+        ws->z = at;
+        if (ws->keep_z) at = align_up(at + z_bytes, 256);
+        return at;
+    };
+    *off = lay_out(B * ws->splits);
     // With few rows the first sweep keeps their logits (4 bytes per pair) and the second reads them instead of K (256 bytes
     // per token): beyond eight rows the gain fades.  Only within the static scratch, so that a call has the same plan, and
     // with it the same bits, on either scratch; and not where a form of the second sweep is asked for (obc_set_sweep2_form).
-    ws->z_stride = (N + 31) / 32 * 32;
-    const size_t z_bytes = (size_t)BH * M * ws->z_stride * sizeof(float);
     ws->keep_z = form == 0 && M <= kFewRows && *off + z_bytes <= OBC_STATIC_SCRATCH_BYTES && (long long)M * ws->z_stride < (1LL << 29) ? 1 : 0;    // (32-bit offsets)
     if (ws->keep_z) {
-        ws->z = *off;
-        *off = align_up(*off + z_bytes, 256);
+        *off = lay_out(B * ws->splits);
         ws->use_wide = ws->solo = 0;
+    }
+    // A call's lengths may want two workgroups per compute unit where full ones want one.  Room for those, unless the plan would
+    // no longer fit the static scratch.  (With B * splits records: 2 x 8 heads of 42588 and 26618 tokens, 30 rows, all, took
+    // splits of 2688 tokens instead of 1152, 59.9 us instead of 50.7 in the first sweep; 3 x 4 of 27688 to 55376, 98 rows, key,
+    // 77 and 59; 4 x 8 of 7324 to 16739, 30 rows, l1, 23 and 18.)
+    const int unit = sweep1_cost(variant, M).unit, two_rounds = (int)std::min(512ll / (Hkv * ws->n_chunks), (long long)B * ((N + unit - 1) / unit));
+    if (two_rounds > ws->records && tuned_splits() == 0) {
+        const size_t fewest = *off;
+        *off = lay_out(two_rounds);
+        if (*off > OBC_STATIC_SCRATCH_BYTES && fewest <= OBC_STATIC_SCRATCH_BYTES) *off = lay_out(B * ws->splits);
     }
 }
 
-// The shares of this call's true lengths (the plan knows only N): shorter splits where they still fit the workspace, whose
+// The shares of this call's true lengths (the plan knows only N): shorter splits as far as they fit the workspace, whose
 // records lie one sequence after the other (see split_slot), and the second sweep's ranges.
 static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
     const int *len = a.ragged ? a.lens.len : nullptr;
     if (len && tuned_splits() == 0) {
-        const int share = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, sweep1_cost(a.variant, a.G * a.W), record_bytes(ws.m_pad, a.variant));
-        int records = 0, most = 1;
-        for (int b = 0; b < a.B; ++b) {
-            const int n = (len[b] + share - 1) / share;
-            records += n;
-            most = n > most ? n : most;
-        }
-        if (records <= a.B * ws.splits) { ws.split_len = share; ws.splits = most; }
+        ws.split_len = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, sweep1_cost(a.variant, a.G * a.W), record_bytes(ws.m_pad, a.variant),
+                                  nullptr, ws.records);
+        ws.splits = 1;
+        for (int b = 0; b < a.B; ++b) ws.splits = std::max(ws.splits, (len[b] + ws.split_len - 1) / ws.split_len);
     }
     int full = ws.n_chunks - ws.solo;
     float wide = 0.f, solo = 0.f, padded = 0.f;

@@ -63,6 +63,20 @@ def test_workspace_query_validation():
         assert e.value.status == expect, args
 
 
+@pytest.mark.parametrize("B,Hkv,G,N,W,variant", [(2, 8, 2, 42588, 15, "all"), (3, 4, 7, 55376, 14, "key"), (4, 8, 1, 16739, 30, "vatp"),
+                                                  (3, 8, 2, 8701, 15, "joint"), (1, 4, 7, 131072, 64, "joint"), (2, 1, 1, 700, 9, "key")])
+def test_lengths_find_room_for_their_shares(B, Hkv, G, N, W, variant):
+    """The plan knows the longest length only; lengths may want their first sweep in as many workgroups as the chip holds two by
+    two, 512, if they are long enough for shares of 128 tokens, and each leaves a record of 128 padded rows at most."""
+    need = obc.obc_score_workspace_bytes(B, N, W, G * Hkv, Hkv, 128, obc.OBC_BF16, obc.VARIANT_CODES[variant])
+    rows = (G * W + 31) // 32 * 32
+    chunks = (rows + 127) // 128
+    record = 16 + (512 if variant in ("key", "joint", "all") else 0)
+    records = min(512 // (Hkv * chunks), B * ((N + 127) // 128)) * Hkv * rows * record
+    assert records <= need <= records + (1 << 20) + 4 * Hkv * B * N * chunks + 1100 * B * Hkv * rows
+
+
+
 def test_entry_points_reject_bad_arguments_before_launch(lib):
     """Null pointers, bad lengths and missing workspace return error codes on a box with no GPU."""
     fake = ctypes.c_void_p(4096)          # never dereferenced: validation fails first
