@@ -1241,8 +1241,9 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
 // the shortest shares whose workgroups fit one to sixteen times the compute units, the one with the least estimated time is
 // taken, counted in the time a workgroup alone on its compute unit spends on a token:
 //   start   what it does before its first and after its last token
-//   pairs   two workgroups share a compute unit where there are that many; each then takes `crowd` times as long for a token
-//           and `crowd_start` for its start
+//   pairs   two workgroups share a compute unit where there are that many.  Each then takes `shared` times as long for a token,
+//           but all together at least what the chip takes to read the tokens: `crowd` times as long where 512 are busy.  (Where
+//           the compute unit itself is the limit both are the same.)  `crowd_start` is their start
 //   record  what the combine step spends on the partial records of every further 256 workgroups
 // First sweep, us, workgroups x tokens: 256 x 128 11.0, 256 x 256 15.6, 256 x 512 22.5, 256 x 1024 38.8, 256 x 2048 69.5,
 // 256 x 4096 130; 512 x 256 25.7, 512 x 512 38.7, 512 x 1024 65.7, 512 x 2048 121, and 3 us more in the combine step: one
@@ -1250,14 +1251,20 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
 // 8.9, 256 x 512 12.9, 256 x 1024 21.9, 256 x 4096 75; 512 x 512 19.0, 512 x 2048 58.
 // (With shares of at least 512 tokens, and else all 512 places filled whatever the length, whole calls took: 8 heads x 8K, all
 // 47.7 us, now 44.2; 8 x 2K 40.2, now 31.9; 8 x 1000 38.8, now 28.2; 4 heads x 20000, 224 rows, 64.8, now 60.4.)
-struct ShareCost { int unit, start; bool pairs; float crowd; int crowd_start, record; };
+struct ShareCost { int unit, start; bool pairs; float shared, crowd; int crowd_start, record; };
 // Windows of at most eight rows keep one wave of a workgroup busy, and a second workgroup costs the first less: 8 heads, G = 1,
 // 4 x 7429 ragged 25.4 us on 224 workgroups, 21.4 on 448; x 60000, G = 4 52.6 on 240, 44.2 on 472.  The kernel after it always
 // wants both places: 18.3 us on 240 workgroups and 14.0 on 352.
-constexpr ShareCost kSweep1Cost = {128, 230, true, 1.79f, 330, 85}, kSweep1SumsCost = {128, 310, true, 1.51f, 320, 20},
-                    kSweep1FewCost = {128, 330, true, 1.55f, 400, 10}, kFewRowsCost = {256, 300, true, 1.f, 300, 0},
-                    kSweep2Cost = {64, 500, true, 1.85f, 500, 0}, kSweep2WideCost = {64, 400, false, 0.f, 0, 0},
-                    kSweep2SoloCost = {128, 400, false, 0.f, 0, 0};
+// Without output sums, and in the second sweep with 32 rows per wave, the memory is the limit of a second workgroup.  8 heads,
+// 30 and 128 rows, us on 256 x 1024 / 512 x 512 / 256 x 1920 / 512 x 1024 tokens: first sweep 18.7 / 12.8 / 32.0 / 22.7 and 25.2 /
+// 17.5 / 42.8 / 31.5; second sweep, value 29.8 / 26.3 / 48.2 / 45.4 and 32.8 / 28.8 / 52.6 / 49.7, attention 22.6 / 17.3 / 34.7 /
+// 26.4 and 24.7 / 21.5 / 39.1 / 32.7, l1 33.3 / 26.9 / 53.9 / 46.3 and 35.9 / 31.7 / 58.8 / 54.1.  (Estimated as if it were
+// the compute unit, 32 heads x 5580, 17 rows, value took 256 workgroups of 704 tokens for the second, 23.3 us, now 480 of 384, 16.6.)
+constexpr ShareCost kSweep1Cost = {128, 230, true, 1.79f, 1.79f, 330, 85}, kSweep1SumsCost = {128, 240, true, 1.1f, 1.27f, 260, 10},
+                    kSweep1FewCost = {128, 330, true, 1.55f, 1.55f, 400, 10}, kFewRowsCost = {256, 300, true, 1.f, 1.f, 300, 0},
+                    kSweep2Cost = {64, 470, true, 1.45f, 1.8f, 430, 0}, kSweep2AttnCost = {64, 680, true, 1.2f, 1.4f, 700, 0},
+                    kSweep2VatpCost = {64, 410, true, 1.35f, 1.57f, 430, 0}, kSweep2WideCost = {64, 400, false, 0.f, 0.f, 0, 0},
+                    kSweep2SoloCost = {128, 400, false, 0.f, 0.f, 0, 0};
 constexpr float kLaunchCost = 80.f;            // of a launch behind another one, 2 us
 static bool needs_output(int variant) { return variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL; }
 static size_t record_bytes(int m_pad, int variant) { return (size_t)(m_pad < 128 ? m_pad : 128) * (16 + (needs_output(variant) ? kD * 4 : 0)); }
@@ -1288,7 +1295,10 @@ static int even_share(const int *len, int B, int N, int heads, const ShareCost &
     };
     auto cost = [&](int share, int rounds) {                                   // on (rounds - 1) * kUnits + 1 .. rounds * kUnits workgroups
         const float records = (float)c.record * (float)rounds;
-        if (c.pairs && rounds > 1) return (float)((rounds + 1) / 2) * (c.crowd * share + c.crowd_start) + records;
+        if (c.pairs && rounds > 1) {
+            const float turns = (float)((rounds + 1) / 2);
+            return std::max(turns * c.shared * share, c.crowd * heads * tokens / (2 * kUnits)) + turns * c.crowd_start + records;
+        }
         return (float)rounds * (float)(share + c.start) + records;
     };
     auto rounds_of = [&](int share) { return (int)((workgroups(share) + kUnits - 1) / kUnits); };
@@ -1387,7 +1397,8 @@ static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
     }
     int full = ws.n_chunks - ws.solo;
     float wide = 0.f, solo = 0.f, padded = 0.f;
-    const ShareCost &cost = ws.keep_z ? kFewRowsCost : ws.use_wide ? kSweep2WideCost : kSweep2Cost;
+    const ShareCost &cost = ws.keep_z ? kFewRowsCost : ws.use_wide ? kSweep2WideCost
+                            : a.variant == OBC_ATTN ? kSweep2AttnCost : a.variant == OBC_VATP ? kSweep2VatpCost : kSweep2Cost;
     if (full > 0) ws.range_len = even_share(len, a.B, a.N, a.Hkv * full, cost, 0, &wide);        // (kFewRowsCost: whole steps of its workgroups)
     if (ws.solo) ws.range_solo = even_share(len, a.B, a.N, a.Hkv, kSweep2SoloCost, 0, &solo);
     // A last chunk of at most 64 rows behind full ones: a launch of its own spends 0.7 of the time on a token and a start of its
