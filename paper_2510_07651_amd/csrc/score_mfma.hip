@@ -1268,8 +1268,13 @@ constexpr ShareCost kSweep1Cost = {128, 230, true, 1.79f, 1.79f, 330, 85}, kSwee
 constexpr float kLaunchCost = 80.f;            // of a launch behind another one, 2 us
 static bool needs_output(int variant) { return variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL; }
 static size_t record_bytes(int m_pad, int variant) { return (size_t)(m_pad < 128 ? m_pad : 128) * (16 + (needs_output(variant) ? kD * 4 : 0)); }
-static const ShareCost &sweep1_cost(int variant, int rows) {
-    return rows <= kFewRows ? kSweep1FewCost : needs_output(variant) ? kSweep1Cost : kSweep1SumsCost;
+// Row chunks of the same split share K and V in a die's L2 if the splits are a multiple of the eight dies, as 512 or 256
+// workgroups over the heads' chunks are wherever the split can be cut finely enough.  (4 heads x 63094, 406 rows, joint: 31 splits
+// of 2048 tokens 106.6 us, 32 of 1984, half a step of each for nothing, 101.3.)
+static ShareCost sweep1_cost(int variant, int rows) {
+    ShareCost c = rows <= kFewRows ? kSweep1FewCost : needs_output(variant) ? kSweep1Cost : kSweep1SumsCost;
+    if (rows > 128) c.unit = 64;
+    return c;
 }
 // A call with lengths searches anew, for every layer and token, so shares that cannot fit or cannot win are not counted out: a
 // sequence takes at least its tokens over the share and less than one workgroup more, and the estimate grows with the share.
