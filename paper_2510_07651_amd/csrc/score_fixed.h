@@ -27,11 +27,17 @@
 // So inputs of that kind take 1.25 to 1.55 times what they would in fp64, and ordinary ones are 1.06 to 1.17 times faster.  (Without
 // the digits while a wave's blocks go to fp64 one after the other, and with four of their loads in flight, such calls took 2 to
 // 8 % less: what they cost is the fp64 products themselves, at a wave's own pace from memory.)
-// Whole calls with one and with the other, by 64-token tiles times 128-row chunks over all heads, us:
-//   80 - 300: 20.0 / 24.7, 21.0 / 26.9, 30.3 / 36.1, 33.3 / 38.0; 384: 29.9 / 32.1; 432: 28.3 / 29.1; 456: 32.8 / 30.2;
-//   480: 53.7 / 53.3; 700 - 800: 27.7 / 27.8, 82.4 / 82.2; 1056: 84.7 / 77.7; 1344: 118.9 / 108.4; 3456: 93.5 / 77.0
-// as the digits of a workgroup's 128 rows cost as much as some tiles: digits from kDigitTiles = 512 on.  (The line counts every
-// head of the call, so which kernel forms a sequence's logits, and with it their last bit now and then, depends on the batch.)
+// A workgroup takes its 128 rows apart, which costs as much as some tiles, so short calls stay with blocked_logits.  Attention
+// scores of 7700 random shapes (4 to 128 heads, 33 to 512 rows), time with fp64 over time with digits, geometric means by 64-token
+// tiles times 128-row chunks over all heads:
+//   tiles             128    256    512    724   1024   1217   2048
+//   fp32, d = 128    0.89   0.96   1.01   1.07   1.10   1.19   1.21
+//   bf16, d =  64    0.93   0.95   1.02   1.09   1.11   1.18   1.24
+//   fp32, d =  64    0.86   0.89   0.94   0.97   1.00   1.06   1.10
+// Shapes of one size differ by 10 % either way, as a launch's last turn is full or not.  digit_tiles, 768 and for fp32, d = 64
+// 1280: less than 1 % of the shapes lose 3 % or more (with 512 for all it was 11.6 % of the last kind, up to a fifth of a call), and all
+// of them gain 2.7 to 8 % in the mean.  (The line counts every head of the call, so which kernel forms a sequence's logits, and
+// with it their last bit now and then, depends on the batch.)
 //
 // v_p . o_i (fixed_score).  Each row of v and o is scaled by a power of two to fixed point, 38 bits and a sign relative to
 // the row's largest element (30 for bf16 values, whose elements have 8 significant bits), and written as five (four)

@@ -41,7 +41,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 64;        // tokens per tile; each of the four waves owns 16 of them
 constexpr int kThreads = 256;    // 4 waves
-constexpr int kDigitTiles = 512; // least tiles times 128-row chunks for digit_logits
+// Least tiles times 128-row chunks for digit_logits (score_fixed.h).
+constexpr int digit_tiles(int dtype, int d) { return dtype == OBC_F32 && d == 64 ? 1280 : 768; }
 constexpr int kMaxRanges = 64;   // token ranges with a row maximum of their own, at most
 constexpr int kMaxSplits = 32;   // sequence splits of P V, at most
 constexpr int kResident = 1024;  // workgroups the chip holds at four per CU: a launch is cut into about this many
@@ -972,13 +973,13 @@ hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hi
 // rows of one head, then as many tokens (which does not).  Within it a launch should fill the chip once (kResident), so that
 // no workgroup pays a prologue more than needed and no last wave of workgroups is nearly empty; a row has at most kMaxRanges
 // maxima, which every workgroup of the weight kernel reads.
-void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, size_t cap, ScoreWorkspace *ws, size_t *off) {
+void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv, M = Hq / Hkv * W;
     const bool fixed = M > 32;
     const long long tiles = (N + kTile - 1) / kTile, logit_chunks = (long long)BH * ((M + 31) / 32);
     const long long chunks = fixed ? (long long)BH * ((M + 127) / 128) : logit_chunks, resident = fixed ? kResident / 2 : kResident;
-    ws->pl_digit_logits = fixed && tiles * chunks >= kDigitTiles ? 1 : 0;
+    ws->pl_digit_logits = fixed && tiles * chunks >= digit_tiles(dtype, d) ? 1 : 0;
     const long long logit_tiles = ws->pl_digit_logits ? (tiles * chunks + resident - 1) / resident : (tiles * logit_chunks + kResident - 1) / kResident;
     const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, logit_tiles);
     ws->pl_range = (int)(std::min(range_tiles, tiles) * kTile);

@@ -139,9 +139,11 @@ def _apart(q, k, binades):
     return _scaled(q, slice(0, 1), binades), _scaled(k, slice(0, 1), -binades)
 
 
-# Long enough for digits (512 tiles of 64 tokens times chunks of 128 rows over both heads), and one that is not.
-DIGIT_SHAPES = [("fp32", 128, 3, 43, 8131), ("fp32", 64, 1, 64, 16332), ("bf16", 64, 5, 40, 8145), ("bf16", 64, 1, 33, 16321),
-                ("bf16", 128, 1, 40, 16323), ("fp32", 128, 3, 43, 129)]
+# Long enough for digits (768 tiles of 64 tokens times chunks of 128 rows over both heads, 1280 for fp32 with d = 64), each
+# followed by shapes that are not.
+DIGIT_SHAPES = [("fp32", 128, 3, 43, 12301), ("fp32", 64, 1, 64, 40991), ("fp32", 128, 3, 43, 8131), ("fp32", 64, 1, 64, 16332),
+                ("bf16", 64, 5, 40, 12303), ("bf16", 64, 1, 33, 24595), ("bf16", 64, 5, 40, 8145), ("bf16", 64, 1, 33, 16321),
+                ("bf16", 128, 1, 40, 24597), ("bf16", 128, 1, 40, 16323), ("fp32", 128, 3, 43, 129)]
 
 
 @pytest.mark.parametrize("logits", LOGITS)
@@ -154,7 +156,7 @@ def test_logits_beyond_their_digits(shape, logits, score_path):
 
 
 @pytest.mark.parametrize("big", ["query", "key", "half"])
-@pytest.mark.parametrize("shape", DIGIT_SHAPES[:2], ids=lambda s: "%s_d%d_%dx%d_%d" % s)
+@pytest.mark.parametrize("shape", DIGIT_SHAPES[:4], ids=lambda s: "%s_d%d_%dx%d_%d" % s)
 def test_rows_that_the_digits_cut(shape, big):
     """Rows with elements half a unit of their digits above a whole one, all of them where the other side has its large ones:
     the dot products stand out above 2^-17 2^E and what is cut off is 2^-23.3 of them, three roundings to fp32.  Logits of
@@ -184,6 +186,6 @@ def test_rows_that_the_digits_cut(shape, big):
     assert err <= TOL["fp32"], err
 
 
-@pytest.mark.parametrize("shape", DIGIT_SHAPES[:4], ids=lambda s: "%s_d%d_%dx%d_%d" % s)
+@pytest.mark.parametrize("shape", DIGIT_SHAPES[:8], ids=lambda s: "%s_d%d_%dx%d_%d" % s)
 def test_digit_logits_at_the_end_of_fp32(shape):
     test_logits_at_the_end_of_fp32_have_weight_zero(shape)
