@@ -19,9 +19,9 @@
 // Both sweeps walk their tokens in blocks of 32.  Sweep 1 is software-pipelined inside a
 // wave: while the vector ALUs turn block n's accumulators into softmax weights, the matrix
 // cores already work on block n+1's K Q^T and on block n-1's P V product; the streams of
-// one step are independent, sit in one basic block, and the instruction scheduler
-// interleaves them.  Sweep 2 exists in two forms.  The one in this file gives a wave 32 rows, runs
-// a block's matrix phase and vector phase back to back and leaves the overlap to the second wave
+// one step are independent, and the instruction scheduler interleaves them.  Sweep 2 exists in
+// two forms.  The one in this file gives a wave 32 rows, runs a block's matrix phase and vector
+// phase back to back and leaves the overlap to the second wave
 // on the SIMD (its stationary operands and row constants leave no registers for a second set of
 // accumulators).  The register-blocked forms (score_mfma_wide.hip: 64 rows per wave, stationary
 // operands in the accumulator file, the wave pipelined against itself) serve the key, joint and
@@ -157,7 +157,7 @@ __device__ __forceinline__ void pack_weights(Sweep1Regs &R) {
 // With kNeedO (Eq. 5, 6) every row keeps its candidate for a dominant key (see kCandMargin) out of
 // its sums.  The step is then cut in two: K Q^T and the block's row maxima first; a vote whether
 // some row of the wave meets a new candidate in block n, and (rarely) the branch that deals with
-// it; then V^T P^T and the weights.  Without kNeedO the step is one basic block.
+// it; then V^T P^T and the weights.  Without kNeedO only the branch of the masks divides it.
 template <int PH, bool kNeedO, bool kStoreZ>
 __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uint32_t lds0, int n, int t_begin,
                                             int t_end, int last_row, int vis, int n_plain, const char *kh, const char *vh,
@@ -1312,7 +1312,8 @@ static int even_share(const int *len, int B, int N, int heads, const ShareCost &
     float best_cost = 0.f;
     for (int rounds = fewest < 1 ? 1 : fewest; rounds <= 16; ++rounds) {
         // The shortest share that fits; one that fits fewer rounds, too, has been looked at with them.
-        const long long fit = std::min((long long)rounds * kUnits / heads, (long long)most_records);     // workgroups per KV head and chunk, at most
+        // (workgroups per KV head and chunk)
+        const long long fit = std::min((long long)rounds * kUnits / heads, (long long)most_records);
         int lo = (int)((tokens + fit * c.unit - 1) / (fit * c.unit));
         if (lo < 1) lo = 1;
         if (fit > B) {                                                         // (a sequence takes less than one more than its tokens over the share)
@@ -1380,9 +1381,10 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     }
     // A call's lengths may want two workgroups per compute unit where full ones want one.  Room for those, unless the plan would
     // no longer fit the static scratch.  (With B * splits records: 2 x 8 heads of 42588 and 26618 tokens, 30 rows, all, took
-    // splits of 2688 tokens instead of 1152, 59.9 us instead of 50.7 in the first sweep; 3 x 4 of 27688 to 55376, 98 rows, key,
-    // 77 and 59; 4 x 8 of 7324 to 16739, 30 rows, l1, 23 and 18.)
-    const int unit = sweep1_cost(variant, M).unit, two_rounds = (int)std::min(512ll / (Hkv * ws->n_chunks), (long long)B * ((N + unit - 1) / unit));
+    // splits of 2688 tokens instead of 1152, 59.9 us instead of 49.9 in the first sweep; 3 x 4 of 27688 to 55376, 98 rows, key,
+    // 77 and 62; 4 x 8 of 7324 to 16739, 30 rows, l1, 23 and 18.)
+    const int unit = sweep1_cost(variant, M).unit;
+    const int two_rounds = (int)std::min(512ll / (Hkv * ws->n_chunks), (long long)B * ((N + unit - 1) / unit));
     if (two_rounds > ws->records && tuned_splits() == 0) {
         const size_t fewest = *off;
         *off = lay_out(two_rounds);

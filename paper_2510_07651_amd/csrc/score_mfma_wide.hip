@@ -24,6 +24,12 @@
 //   * K and V tiles travel HBM -> LDS through a ring of four 32 KB slots, three tiles in
 //     flight per compute unit.
 //
+// What bounds it: no one thing.  4 x 8 heads x 32K, 128 rows, joint, us, leaving parts out: as it is 131.7; transfers served
+// from the L2 130.0; no transfers 113.1; no matrix ops 91.2; no vector tasks 115.3; neither 91.8, what the ring takes to read
+// the cache.  Cycles of a wave per block, of 3608: phase 1 1496, phase 2 1001 (768 of each are matrix ops), between them 327,
+// bookkeeping and flush 334, tail 283, barrier 115, wait for the ring 44.  The eight transfers cost their issue in phase 1, and
+// the matrix cores idle outside the phases.
+//
 // Blocks that hold a causally hidden (row, key) pair, the ragged end of a sequence or a
 // separately scored pair run the same pipeline with the masks applied to every pair.
 // All sums have a fixed order: results are bit-reproducible.
