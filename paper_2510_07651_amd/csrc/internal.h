@@ -59,6 +59,7 @@ struct ScoreWorkspace {
     int use_mfma;      // 1: bf16 matrix-core path, 0: general path
     size_t z;          // float [B*Hkv*rows*z_stride]  raw q.k, kept by the first sweep when keep_z
     int keep_z, z_stride;
+    int once1, once2;  // 1: the first, the second sweep marks K and V as read once (see reads_once)
     int use_wide;      // 1: the second sweep runs in its register-blocked form (score_mfma_wide.hip)
     int solo;          // 1: there the last chunk has at most 64 rows and goes to mfma_sweep2_solo, in ranges of range_solo
     int range_solo;

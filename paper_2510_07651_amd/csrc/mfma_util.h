@@ -49,18 +49,22 @@ __device__ __forceinline__ uint32_t lds_offset_of(const void *p) {
 
 // One direct-to-LDS transfer: every lane supplies the address of 16 bytes in global
 // memory; the wave's 1 KB lands contiguously at LDS byte `lds_off` (lane l at +16 l).
-// Marked non-temporal: every sweep reads K and V once, and they are far larger than the L2.
+// kOnce marks it non-temporal (see reads_once in score_mfma.hip).
 // The LDS address goes through m0, an operand of the statement; a write of it needs one wait slot.
 // Issued from inline assembly so that the compiler's wait-count bookkeeping does not tie
 // later LDS reads of OTHER tiles to these transfers; the kernels wait for them
 // explicitly (wait_async_loads + barrier) before the tile is read.
+template <bool kOnce>
 __device__ __forceinline__ void dma16(const void *gptr, uint32_t lds_off) {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"{m0}"(lds_off), "v"(gptr) : "memory");
+    if constexpr (kOnce) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"{m0}"(lds_off), "v"(gptr) : "memory");
+    else asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(lds_off), "v"(gptr) : "memory");
 }
 // Same transfer with the address split into a wave-uniform 64-bit base (scalar registers)
 // and a per-lane 32-bit byte offset: no vector-ALU address arithmetic per transfer.
+template <bool kOnce>
 __device__ __forceinline__ void dma16_based(const void *sbase, uint32_t voff, uint32_t lds_off) {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"{m0}"(lds_off), "v"(voff), "s"(sbase) : "memory");
+    if constexpr (kOnce) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"{m0}"(lds_off), "v"(voff), "s"(sbase) : "memory");
+    else asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds_off), "v"(voff), "s"(sbase) : "memory");
 }
 __device__ __forceinline__ void wait_async_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // Asynchronous copy of one 64-row tile.  Each wave issues four transfers; lane l of
@@ -77,13 +81,13 @@ __device__ __forceinline__ void tile_lane_offsets(uint32_t (&doff)[4], int wave,
     }
 }
 
-template <int SWZ>
+template <int SWZ, bool kOnce>
 __device__ __forceinline__ void tile_load_async(const char *__restrict__ head_base, int t0, int last_row,
                                                 uint32_t lds_tile, int wave, int lane, const uint32_t (&doff)[4]) {
     if (t0 + kTileTok - 1 <= last_row) {            // uniform: the common case, every row of the tile exists
         const char *sbase = head_base + (size_t)t0 * kRowBytes;
 #pragma unroll
-        for (int n = 0; n < 4; ++n) dma16_based(sbase, doff[n], lds_tile + (wave * 4 + n) * 1024);
+        for (int n = 0; n < 4; ++n) dma16_based<kOnce>(sbase, doff[n], lds_tile + (wave * 4 + n) * 1024);
         return;
     }
 #pragma unroll
@@ -92,7 +96,7 @@ __device__ __forceinline__ void tile_load_async(const char *__restrict__ head_ba
         const int c = piece_of(SWZ, R, lane & 15);
         int row = t0 + R;
         row = row > last_row ? last_row : row;
-        dma16(head_base + (size_t)row * kRowBytes + c * 16, lds_tile + (wave * 4 + n) * 1024);
+        dma16<kOnce>(head_base + (size_t)row * kRowBytes + c * 16, lds_tile + (wave * 4 + n) * 1024);
     }
 }
 
@@ -106,13 +110,13 @@ __device__ __forceinline__ void block_lane_offsets(uint32_t (&doff)[2], int wave
         doff[n] = (uint32_t)(R * kRowBytes + piece_of(SWZ, R, lane & 15) * 16);
     }
 }
-template <int SWZ>
+template <int SWZ, bool kOnce>
 __device__ __forceinline__ void block_load_async(const char *__restrict__ head_base, int t0, int last_row,
                                                  uint32_t lds_block, int wave, int lane, const uint32_t (&doff)[2]) {
     if (t0 + 31 <= last_row) {                      // uniform: every row of the block exists
         const char *sbase = head_base + (size_t)t0 * kRowBytes;
 #pragma unroll
-        for (int n = 0; n < 2; ++n) dma16_based(sbase, doff[n], lds_block + (wave * 2 + n) * 1024);
+        for (int n = 0; n < 2; ++n) dma16_based<kOnce>(sbase, doff[n], lds_block + (wave * 2 + n) * 1024);
         return;
     }
 #pragma unroll
@@ -121,7 +125,7 @@ __device__ __forceinline__ void block_load_async(const char *__restrict__ head_b
         const int c = piece_of(SWZ, R, lane & 15);
         int row = t0 + R;
         row = row > last_row ? last_row : row;
-        dma16(head_base + (size_t)row * kRowBytes + c * 16, lds_block + (wave * 2 + n) * 1024);
+        dma16<kOnce>(head_base + (size_t)row * kRowBytes + c * 16, lds_block + (wave * 2 + n) * 1024);
     }
 }
 // Waits until at most kKeep of this wave's most recent transfers are still in flight

@@ -55,6 +55,8 @@
 #include "mfma_util.h"
 #include "wave_util.h"
 
+#include <type_traits>
+
 namespace obc {
 using namespace mfma;
 namespace {
@@ -158,7 +160,7 @@ __device__ __forceinline__ void pack_weights(Sweep1Regs &R) {
 // its sums.  The step is then cut in two: K Q^T and the block's row maxima first; a vote whether
 // some row of the wave meets a new candidate in block n, and (rarely) the branch that deals with
 // it; then V^T P^T and the weights.  Without kNeedO only the branch of the masks divides it.
-template <int PH, bool kNeedO, bool kStoreZ>
+template <int PH, bool kNeedO, bool kStoreZ, bool kOnce>
 __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uint32_t lds0, int n, int t_begin,
                                             int t_end, int last_row, int vis, int n_plain, const char *kh, const char *vh,
                                             const int (&koff)[8], const int (&voff)[4], const uint32_t (&kdoff)[2],
@@ -181,9 +183,9 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
     else if (kStoreZ && wave_active && n == 1 && 32 < t_end - t_begin) wait_async_loads_keep<2 * kBatch + 4>();
     else wait_async_loads_keep<2 * kBatch>();
     __syncthreads();
-    block_load_async<kXor16>(kh, t_begin + (n + 4) * 32, last_row, lds0 + PH * kBlkBytes, wave, lane, kdoff);
+    block_load_async<kXor16, kOnce>(kh, t_begin + (n + 4) * 32, last_row, lds0 + PH * kBlkBytes, wave, lane, kdoff);
     if (kNeedO)
-        block_load_async<kRot4>(vh, t_begin + (n + 2) * 32, last_row, lds0 + (4 + ((PH + 2) & 3)) * kBlkBytes, wave, lane, vdoff);
+        block_load_async<kRot4, kOnce>(vh, t_begin + (n + 2) * 32, last_row, lds0 + (4 + ((PH + 2) & 3)) * kBlkBytes, wave, lane, vdoff);
     if (!wave_active) return;
     if (kStoreZ && n * 32 < t_end - t_begin && z_off != ~0u) {      // raw q.k of block n for score_few_rows
 #pragma unroll
@@ -337,7 +339,7 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
 // With kNeedO every row keeps its candidate for a dominant key (see kCandMargin) out of its sums and
 // reports it with the partial record; the combine step then forms v_cand - o_i without
 // cancellation for every row, and no row ever needs a second pass.
-template <bool kNeedO, bool kStoreZ, typename Lens>
+template <bool kNeedO, bool kStoreZ, bool kOnce, typename Lens>
 __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__restrict__ q,
                                                            const uint16_t *__restrict__ k,
                                                            const uint16_t *__restrict__ v, int N, int W, int Hq,
@@ -411,12 +413,12 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     block_lane_offsets<kXor16>(kdoff, wave, lane);
     block_lane_offsets<kRot4>(vdoff, wave, lane);
     for (int e = threadIdx.x; e < kBlkBytes / 16; e += kThreads) ((uint4 *)(smem + 7 * kBlkBytes))[e] = make_uint4(0, 0, 0, 0);
-    block_load_async<kXor16>(kh, t_begin, len - 1, lds0, wave, lane, kdoff);
-    block_load_async<kXor16>(kh, t_begin + 32, len - 1, lds0 + kBlkBytes, wave, lane, kdoff);
-    block_load_async<kXor16>(kh, t_begin + 64, len - 1, lds0 + 2 * kBlkBytes, wave, lane, kdoff);
-    if (kNeedO) block_load_async<kRot4>(vh, t_begin, len - 1, lds0 + 4 * kBlkBytes, wave, lane, vdoff);
-    block_load_async<kXor16>(kh, t_begin + 96, len - 1, lds0 + 3 * kBlkBytes, wave, lane, kdoff);
-    if (kNeedO) block_load_async<kRot4>(vh, t_begin + 32, len - 1, lds0 + 5 * kBlkBytes, wave, lane, vdoff);
+    block_load_async<kXor16, kOnce>(kh, t_begin, len - 1, lds0, wave, lane, kdoff);
+    block_load_async<kXor16, kOnce>(kh, t_begin + 32, len - 1, lds0 + kBlkBytes, wave, lane, kdoff);
+    block_load_async<kXor16, kOnce>(kh, t_begin + 64, len - 1, lds0 + 2 * kBlkBytes, wave, lane, kdoff);
+    if (kNeedO) block_load_async<kRot4, kOnce>(vh, t_begin, len - 1, lds0 + 4 * kBlkBytes, wave, lane, vdoff);
+    block_load_async<kXor16, kOnce>(kh, t_begin + 96, len - 1, lds0 + 3 * kBlkBytes, wave, lane, kdoff);
+    if (kNeedO) block_load_async<kRot4, kOnce>(vh, t_begin + 32, len - 1, lds0 + 5 * kBlkBytes, wave, lane, vdoff);
     wait_async_loads_keep<kNeedO ? 10 : 6>();         // everything after K block 0 may still be in flight
     __syncthreads();
     R.s_cur = zero16();
@@ -436,10 +438,10 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     const uint32_t z_off = kStoreZ && row_valid ? (uint32_t)row * z_stride * 4 + 16 * half : ~0u;
 #define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, len - 1, vis, n_plain, kh, vh, koff, voff, kdoff, vdoff, wave, lane, wave_active, events, z_split, z_off
     for (int n = 0; n < n_total; n += 4) {
-        sweep1_step<0, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<1, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<2, kNeedO, kStoreZ>(R, OBC_S1_ARGS); ++n;
-        sweep1_step<3, kNeedO, kStoreZ>(R, OBC_S1_ARGS); n -= 3;
+        sweep1_step<0, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<1, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<2, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;
+        sweep1_step<3, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); n -= 3;
     }
 #undef OBC_S1_ARGS
     // A final candidate that holds less than half of its own split's weight cannot dominate the
@@ -782,7 +784,7 @@ __device__ __forceinline__ void sweep2_flush(const float *stage, float *out, siz
 // The two phases of one wave do not overlap; the second wave on the SIMD runs in the gaps
 // (on this hardware a 32x32x16 matrix op blocks most vector-ALU issue anyway).
 // Even steps first wait for the tile issued two steps earlier and start the next one.
-template <int PH, bool kMasked, int kVariant>
+template <int PH, bool kMasked, int kVariant, bool kOnce>
 __device__ __forceinline__ void sweep2_step(Sweep2Regs &R, uint32_t lds0, int n, int n_blk,
                                             int t_begin, int t_end, int last_row, const int *vis_i,
                                             const int *excl_i, const char *kh, const char *vh,
@@ -806,9 +808,9 @@ __device__ __forceinline__ void sweep2_step(Sweep2Regs &R, uint32_t lds0, int n,
         __syncthreads();
         const int tn = t_begin + ((n >> 1) + 1) * kTileTok;           // first token of the tile to start now
         if (tn < t_end) {
-            tile_load_async<kXor16>(kh, tn, last_row, lds0 + (PH == 0 ? kLdsK1 : kLdsK0), wave, lane, kdoff);
+            tile_load_async<kXor16, kOnce>(kh, tn, last_row, lds0 + (PH == 0 ? kLdsK1 : kLdsK0), wave, lane, kdoff);
             if (kVariant != OBC_ATTN)
-                tile_load_async<kXor16>(vh, tn, last_row, lds0 + (PH == 0 ? kLdsV1 : kLdsV0), wave, lane, kdoff);
+                tile_load_async<kXor16, kOnce>(vh, tn, last_row, lds0 + (PH == 0 ? kLdsV1 : kLdsV0), wave, lane, kdoff);
         }
         if (n >= 2) sweep2_flush<kNv>(part + (kSlot ^ 1) * 4 * kNv * 64, out, variant_stride, t_begin + (n - 2) * 32, t_end, wave, lane, accumulate);
     }
@@ -889,7 +891,7 @@ __device__ __forceinline__ void sweep2_step(Sweep2Regs &R, uint32_t lds0, int n,
 // kVariant: OBC_VALUE / OBC_KEY / OBC_JOINT / OBC_ALL / OBC_ATTN / OBC_VATP.  Grid: see sweep_part.
 // With one chunk the scores go straight to `scores`; with several, each chunk writes its
 // own plane and mfma_sum_planes adds them in chunk order.
-template <int kVariant, typename Lens>
+template <int kVariant, bool kOnce, typename Lens>
 __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__restrict__ q,
                                                            const uint16_t *__restrict__ k,
                                                            const uint16_t *__restrict__ v, int N, int W, int Hq,
@@ -929,8 +931,8 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__res
     // this wave's stationary operands; step 0 waits for it.
     uint32_t kdoff[4];
     tile_lane_offsets<kXor16>(kdoff, wave, lane);
-    tile_load_async<kXor16>(kh, t_begin, len - 1, lds0 + kLdsK0, wave, lane, kdoff);
-    if (kVariant != OBC_ATTN) tile_load_async<kXor16>(vh, t_begin, len - 1, lds0 + kLdsV0, wave, lane, kdoff);
+    tile_load_async<kXor16, kOnce>(kh, t_begin, len - 1, lds0 + kLdsK0, wave, lane, kdoff);
+    if (kVariant != OBC_ATTN) tile_load_async<kXor16, kOnce>(vh, t_begin, len - 1, lds0 + kLdsV0, wave, lane, kdoff);
 
     // (fetched with the stationary operands below, in one memory round trip; used after them)
     float my_vis = __int_as_float(-1);
@@ -1018,16 +1020,16 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep2(const uint16_t *__res
 #define OBC_S2_ARGS lds0, n, n_blk, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, kp, kdoff, wave, lane, wave_active, part, out, variant_stride, accumulate, m_lo, m_hi
     int n = 0;
     for (; n < n_plain; n += 4) {
-        sweep2_step<0, false, kVariant>(R, OBC_S2_ARGS); ++n;
-        sweep2_step<1, false, kVariant>(R, OBC_S2_ARGS); ++n;
-        sweep2_step<2, false, kVariant>(R, OBC_S2_ARGS); ++n;
-        sweep2_step<3, false, kVariant>(R, OBC_S2_ARGS); n -= 3;
+        sweep2_step<0, false, kVariant, kOnce>(R, OBC_S2_ARGS); ++n;
+        sweep2_step<1, false, kVariant, kOnce>(R, OBC_S2_ARGS); ++n;
+        sweep2_step<2, false, kVariant, kOnce>(R, OBC_S2_ARGS); ++n;
+        sweep2_step<3, false, kVariant, kOnce>(R, OBC_S2_ARGS); n -= 3;
     }
     for (; n < n_total; n += 4) {
-        sweep2_step<0, true, kVariant>(R, OBC_S2_ARGS); ++n;
-        sweep2_step<1, true, kVariant>(R, OBC_S2_ARGS); ++n;
-        sweep2_step<2, true, kVariant>(R, OBC_S2_ARGS); ++n;
-        sweep2_step<3, true, kVariant>(R, OBC_S2_ARGS); n -= 3;
+        sweep2_step<0, true, kVariant, kOnce>(R, OBC_S2_ARGS); ++n;
+        sweep2_step<1, true, kVariant, kOnce>(R, OBC_S2_ARGS); ++n;
+        sweep2_step<2, true, kVariant, kOnce>(R, OBC_S2_ARGS); ++n;
+        sweep2_step<3, true, kVariant, kOnce>(R, OBC_S2_ARGS); n -= 3;
     }
 #undef OBC_S2_ARGS
     __syncthreads();
@@ -1221,11 +1223,14 @@ hipError_t launch_sweep2(const ScoreArgs &a, const Lens &lens, const ScoreWorksp
     } else if (ws.use_wide) {
         e = launch_sweep2_wide(a, ws, base, dst, plane_elems, chunk_stride, stream);
     } else {
-        mfma_sweep2<kVariant><<<sweep_grid(a, lens, ws.n_chunks, ws.range_len), dim3(kThreads), 0, stream>>>(
-            (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.B * a.Hkv, a.ragged, lens,
-            ws.range_len, ws.n_chunks, ws.m_pad, (const uint16_t *)(base + ws.out_bf16), (const float *)(base + ws.row_const),
-            (const float *)(base + ws.special), dst, plane_elems, chunk_stride,
-            ws.n_chunks == 1 ? a.accumulate : 0);
+        auto launch = [&](auto once) {
+            mfma_sweep2<kVariant, once.value><<<sweep_grid(a, lens, ws.n_chunks, ws.range_len), dim3(kThreads), 0, stream>>>(
+                (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.B * a.Hkv, a.ragged, lens,
+                ws.range_len, ws.n_chunks, ws.m_pad, (const uint16_t *)(base + ws.out_bf16), (const float *)(base + ws.row_const),
+                (const float *)(base + ws.special), dst, plane_elems, chunk_stride,
+                ws.n_chunks == 1 ? a.accumulate : 0);
+        };
+        if (ws.once2) launch(std::true_type{}); else launch(std::false_type{});
         e = hipGetLastError();
     }
     if (e != hipSuccess || ws.n_chunks == 1) return e;
@@ -1392,6 +1397,30 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
     }
 }
 
+// Whether a sweep marks its reads of K and V (of K alone without `with_v`) as non-temporal.  It does where nobody reads them
+// again soon: not with several row chunks, whose workgroups meet in a die's L2, and not where the memory-side cache of 256 MB
+// holds what the next sweep, or the next call, reads again.  Calls, us, marked / not (K and V of the call, MB):
+//   128 rows, joint     17: 39.3 / 31.2    34: 46.6 / 40.4    67: 60.9 / 53.6   134: 88.9 / 82.6   201: 120.7 / 115.6   268: 150.7 / 150.0   537: 273 / 272
+//   128 rows, value     34: 29.3 / 26.8    67: 38.7 / 35.3   134: 56.4 / 50.5   201: 69.6 / 67.3   268: 85.2 / 85.3     537: 155 / 164
+//   32 rows, attention 134: 35.9 / 34.6   268: 54.4 / 54.1   403: 74.9 / 77.3   537: 91.2 / 97.1 (reads K, half of them)
+//   256 rows, joint     34: 61.2 / 55.9   134: 150 / 138     268: 260 / 252     537: 502 / 495    1074: 971 / 961
+//   448 rows, joint     67: 143 / 130     134: 252 / 235     268: 471 / 438     537: 938 / 890    1074: 1825 / 1725
+// Up to 64 rows with output sums the kernels are bound by the reads themselves, and the mark pays always: 32 rows, joint, 67: 40.9 /
+// 41.3, 134: 62.7 / 64.1, 537: 193 / 202; so it does for windows of few rows, the same cache again for every token (4 rows,
+// joint, 268: 82 / 89; value, 201: 44 / 48).
+constexpr long long kCachedBytes = 200ll << 20;
+static int reads_once(const ScoreArgs &a, const ScoreWorkspace &ws, bool with_v) {
+    const int rows = a.G * a.W;
+    if (ws.n_chunks > 1) return 0;
+    if (ws.keep_z || rows <= kFewRows || (rows <= 64 && needs_output(a.variant))) return 1;
+    long long tokens = (long long)a.B * a.N;
+    if (a.ragged) {
+        tokens = 0;
+        for (int b = 0; b < a.B; ++b) tokens += a.lens.len[b];
+    }
+    return tokens * a.Hkv * kRowBytes * (with_v ? 2 : 1) > kCachedBytes;
+}
+
 // The shares of this call's true lengths (the plan knows only N): shorter splits as far as they fit the workspace, whose
 // records lie one sequence after the other (see split_slot), and the second sweep's ranges.
 static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
@@ -1416,6 +1445,8 @@ static ScoreWorkspace mfma_balance(const ScoreArgs &a, ScoreWorkspace ws) {
         const int range = even_share(len, a.B, a.N, a.Hkv * ws.n_chunks, cost, 0, &padded);
         if (padded < wide + 0.7f * solo + kLaunchCost) { ws.solo = 0; ws.range_len = range; }
     }
+    ws.once1 = reads_once(a, ws, needs_output(a.variant));
+    ws.once2 = reads_once(a, ws, a.variant != OBC_ATTN);
     if (ws.keep_z) return ws;
     if (const int v = tuned_range(); v >= 64 && v <= 65536 && v % 64 == 0) ws.range_len = ws.range_solo = v;
     return ws;
@@ -1428,14 +1459,16 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
     hipError_t e = hipSuccess;
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
         const dim3 grid = sweep_grid(a, lens, ws.n_chunks, ws.split_len);
-#define OBC_SWEEP1(need_o, store_z)                                                                                    \
-    mfma_sweep1<need_o, store_z><<<grid, dim3(kThreads), 0, stream>>>(                                                 \
+#define OBC_SWEEP1(need_o, store_z, once)                                                                              \
+    mfma_sweep1<need_o, store_z, once><<<grid, dim3(kThreads), 0, stream>>>(                                                 \
         (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens,      \
         ws.split_len, ws.n_chunks, ws.m_pad, part_ml, part_o, (float *)(base + ws.z), ws.z_stride)
-        if (need_o && ws.keep_z) OBC_SWEEP1(true, true);
-        else if (need_o) OBC_SWEEP1(true, false);
-        else if (ws.keep_z) OBC_SWEEP1(false, true);
-        else OBC_SWEEP1(false, false);
+        if (need_o && ws.keep_z) OBC_SWEEP1(true, true, true);
+        else if (need_o && ws.once1) OBC_SWEEP1(true, false, true);
+        else if (need_o) OBC_SWEEP1(true, false, false);
+        else if (ws.keep_z) OBC_SWEEP1(false, true, true);
+        else if (ws.once1) OBC_SWEEP1(false, false, true);
+        else OBC_SWEEP1(false, false, false);
 #undef OBC_SWEEP1
         e = hipGetLastError();
         if (e != hipSuccess) return e;

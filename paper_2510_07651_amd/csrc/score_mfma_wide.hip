@@ -270,31 +270,34 @@ struct TileFetch {
     uint32_t voff[4];                // per-lane byte offset of transfer n inside the tile + kBias - 1024 n (rows past the end clamped)
     uint32_t lds;                    // LDS byte address of the ring slot (K tile; the V tile follows), this wave's first transfer
 };
-template <int kSlot>
+template <int kSlot, bool kOnce>
 __device__ __forceinline__ void transfer_at(const char *sbase, uint32_t voff, uint32_t lds) {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt" ::"{m0}"(lds), "v"(voff), "s"(sbase), "n"(kSlot * 1024) : "memory");
+    if constexpr (kOnce) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt" ::"{m0}"(lds), "v"(voff), "s"(sbase), "n"(kSlot * 1024) : "memory");
+    else asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"{m0}"(lds), "v"(voff), "s"(sbase), "n"(kSlot * 1024) : "memory");
 }
+template <bool kOnce>
 __device__ __forceinline__ void fetch_one(const TileFetch &f, int n) {       // n = 0..3: K, 4..7: V, in this order
     const char *base = n < 4 ? f.k_base : f.v_base;
     const uint32_t lds = f.lds + (n < 4 ? 0 : kTileBytes);
     switch (n & 3) {
-        case 0: return transfer_at<0>(base, f.voff[0], lds);
-        case 1: return transfer_at<1>(base, f.voff[1], lds);
-        case 2: return transfer_at<2>(base, f.voff[2], lds);
-        default: return transfer_at<3>(base, f.voff[3], lds);
+        case 0: return transfer_at<0, kOnce>(base, f.voff[0], lds);
+        case 1: return transfer_at<1, kOnce>(base, f.voff[1], lds);
+        case 2: return transfer_at<2, kOnce>(base, f.voff[2], lds);
+        default: return transfer_at<3, kOnce>(base, f.voff[3], lds);
     }
 }
 // All four transfers a wave issues for 64 rows from row `row0` of `rows`; rows past `last` (>= row0) re-read it.  `lds`: this
 // wave's first one.  Short code: what a kernel runs once costs its instructions' way from memory (see mfma_sweep2_wide).
+template <bool kOnce>
 __device__ __forceinline__ void load_64_rows(const char *rows, int row0, int last, uint32_t lds, const uint32_t (&moff)[4], int wave, int lane) {
     const char *base = rows + (size_t)row0 * kRowBytes - kBias;
     uint32_t voff[4];
 #pragma unroll
     for (int n = 0; n < 4; ++n) voff[n] = moff[n] - (uint32_t)(max((wave * 4 + n) * 4 + (lane >> 4) - (last - row0), 0) * kRowBytes);
-    transfer_at<0>(base, voff[0], lds);
-    transfer_at<1>(base, voff[1], lds);
-    transfer_at<2>(base, voff[2], lds);
-    transfer_at<3>(base, voff[3], lds);
+    transfer_at<0, kOnce>(base, voff[0], lds);
+    transfer_at<1, kOnce>(base, voff[1], lds);
+    transfer_at<2, kOnce>(base, voff[2], lds);
+    transfer_at<3, kOnce>(base, voff[3], lds);
 }
 // Zeros for rows `from` .. 63 of a 64-row tile in LDS, whatever its swizzle (256 threads).
 __device__ __forceinline__ void zero_rows(char *tile, int from) {
@@ -311,7 +314,7 @@ __device__ __forceinline__ void zero_rows(char *tile, int from) {
 // starts the wave's eight transfers of the tile three steps ahead (one in each of the last eight slots).
 // `hidden`: some (row, key) pair of this block is causally hidden or past the sequence's end; `special`: the bits of its
 // group of 32 blocks (see special_word).
-template <int kVariant>
+template <int kVariant, bool kOnce>
 __device__ __forceinline__ void pipelined_block(WideState &R, const Stationary &A, const TileFetch &fetch, float *stage_prev,
                                                 int tok, int t_end, int rh, int th, int wave, int lane, int blk, bool hidden,
                                                 uint32_t special, const int *vis_i, const int *excl_i) {
@@ -321,7 +324,7 @@ __device__ __forceinline__ void pipelined_block(WideState &R, const Stationary &
     PairWork pw[16];
     matrix_phase<0>(A, R.zA, R.voA, R.kreg, R.vreg, [&](int j) __attribute__((always_inline)) {
         if (j < 16) { vvn = sumsq_quarter(R.vreg[j >> 1], j & 1, vvn); stay(vvn); }
-        else fetch_one(fetch, j - 16);
+        else fetch_one<kOnce>(fetch, j - 16);
 #pragma unroll
         for (int t = 2 * j; t < 2 * j + 2; ++t) {
             const int r = t / 3;
@@ -368,7 +371,7 @@ __device__ __forceinline__ int next_tile(int a, int n_tiles) { return a + 1 == n
 
 // One tile step of a wave: this block's operands are in registers already; the next tile (ring slot (s+1) mod 4,
 // where R.kp points) is read during the step.
-template <int kVariant>
+template <int kVariant, bool kOnce>
 __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, const uint32_t lds0, int s, int tile,
                                           int tile_fetch, int tile_flush, int t_begin,
                                           int t_end, int last_row, const int *vis_i, const int *excl_i, const char *kh,
@@ -407,7 +410,7 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
     // Blocks every row of the wave sees in full and that hold no separately scored pair need no masks.
     const bool hidden = !(tok0 + 31 <= vis_min);                         // uniform for the wave
     float *stage_prev = stage + (R.pend ? (s - 1) & 3 : kSlots) * 2 * kNv * 64;      // (slot 4: never flushed)
-    pipelined_block<kVariant>(R, A, fetch, stage_prev, tok0 + (lane & 31), t_end, rh, th, wave, lane, blk, hidden, special_s[special_word(blk)], vis_i, excl_i);
+    pipelined_block<kVariant, kOnce>(R, A, fetch, stage_prev, tok0 + (lane & 31), t_end, rh, th, wave, lane, blk, hidden, special_s[special_word(blk)], vis_i, excl_i);
     // On to the slot of tile s+2 (the ring wraps after slot 3).
     const int hop = ((s + 1) & 3) == 0 ? -(kSlots - 1) * kSlotBytes : kSlotBytes;
 #pragma unroll
@@ -415,7 +418,7 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
 }
 
 // kVariant: OBC_KEY / OBC_JOINT / OBC_ALL.  Grid: see sweep_part.
-template <int kVariant, typename Lens>
+template <int kVariant, bool kOnce, typename Lens>
 __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *__restrict__ q,
                                                                 const uint16_t *__restrict__ k,
                                                                 const uint16_t *__restrict__ v, int N, int W, int Hq,
@@ -475,12 +478,17 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
         const char *o_rows = (const char *)out_bf16 + cbase * kRowBytes;                             // its m_pad rows
         const char *o_low = o_rows + (size_t)heads * m_pad * kRowBytes;
         const char *records = (const char *)((wave < 2 ? row_const : special) + cbase * 4);
-        transfer_at<0>(records, (uint32_t)min(chunk * 128 + rh * 64 + lane, m_pad - 1) * 16, lds0 + kRing + wave * 1024);
+        transfer_at<0, false>(records, (uint32_t)min(chunk * 128 + rh * 64 + lane, m_pad - 1) * 16, lds0 + kRing + wave * 1024);
 #pragma unroll 1
-        for (int t = 0; t < 8; ++t) {              // (rows past the last one re-read it)
-            const char *rows = t < 2 ? q_rows : t < 4 ? o_rows : t < 6 ? o_low : t < 7 ? kh : vh;
-            const int from = t < 6 ? chunk * 128 + (t & 1) * 64 : t_begin + first * kTileTok, last = t < 2 ? M - 1 : t < 6 ? m_pad - 1 : len - 1;
-            load_64_rows(rows, min(from, last), last, lds0 + t * kTileBytes + wave * 4096, moff, wave, lane);
+        for (int t = 0; t < 6; ++t) {              // (rows past the last one re-read it)
+            const char *rows = t < 2 ? q_rows : t < 4 ? o_rows : o_low;
+            const int from = chunk * 128 + (t & 1) * 64, last = t < 2 ? M - 1 : m_pad - 1;
+            load_64_rows<false>(rows, min(from, last), last, lds0 + t * kTileBytes + wave * 4096, moff, wave, lane);
+        }
+#pragma unroll 1
+        for (int t = 6; t < 8; ++t) {
+            const int from = t_begin + first * kTileTok;
+            load_64_rows<kOnce>(t < 7 ? kh : vh, min(from, len - 1), len - 1, lds0 + t * kTileBytes + wave * 4096, moff, wave, lane);
         }
     }
 
@@ -532,7 +540,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     // Every wave has its stationary operands (the barrier above): the staging slots take the next three tiles.
 #pragma unroll 1
     for (int t = 0; t < 6; ++t)
-        load_64_rows(t & 1 ? vh : kh, t_begin + tile_at((t >> 1) + 1, first, n_tiles) * kTileTok, len - 1, lds0 + t * kTileBytes + wave * 4096, moff, wave, lane);
+        load_64_rows<kOnce>(t & 1 ? vh : kh, t_begin + tile_at((t >> 1) + 1, first, n_tiles) * kTileTok, len - 1, lds0 + t * kTileBytes + wave * 4096, moff, wave, lane);
     wait_async_loads_keep<3 * kTilePerWave>();                 // the first tile has landed
     __syncthreads();
     // The first block's operand pieces (slot 3).
@@ -551,7 +559,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     // Positions of the walk: the tile worked on, the one fetched during the step (four ahead), the one flushed (two back).
     int tile = first, tile_fetch = tile_at(4, first, n_tiles), tile_flush = tile_at(2 * n_tiles - 2, first, n_tiles);
     for (int s = 0; s < n_tiles; ++s, tile = next_tile(tile, n_tiles), tile_fetch = next_tile(tile_fetch, n_tiles), tile_flush = next_tile(tile_flush, n_tiles))
-        wide_step<kVariant>(R, A, lds0, s, tile, tile_fetch, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, moff, wave, lane, vis_min,
+        wide_step<kVariant, kOnce>(R, A, lds0, s, tile, tile_fetch, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, moff, wave, lane, vis_min,
                             special_s, stage, out, variant_stride, accumulate);
     if (R.pend) {                                              // set B of the last block
         matrix_results_land();
@@ -584,8 +592,9 @@ struct SoloFetch {
     uint32_t voff[8];                // per-lane byte offset of transfer n inside the block (rows past the end clamped)
     uint32_t lds;                    // LDS byte address of the slot
 };
+template <bool kOnce>
 __device__ __forceinline__ void solo_fetch_one(const SoloFetch &f, int n) {       // n = 0..7: K, 8..15: V
-    dma16_based(n < 8 ? f.k_base : f.v_base, f.voff[n & 7], f.lds + (n < 8 ? 0 : kBlkBytes) + (n & 7) * 1024);
+    dma16_based<kOnce>(n < 8 ? f.k_base : f.v_base, f.voff[n & 7], f.lds + (n < 8 ? 0 : kBlkBytes) + (n & 7) * 1024);
 }
 __device__ __forceinline__ SoloFetch solo_fetch(const char *kh, const char *vh, int t0, int last_row, uint32_t lds, const uint32_t (&doff)[8], int lane) {
     SoloFetch f;
@@ -603,6 +612,7 @@ __device__ __forceinline__ SoloFetch solo_fetch(const char *kh, const char *vh, 
 }
 
 // A whole block at once, in short code (for the prologue); rows past the end re-read the last one.
+template <bool kOnce>
 __device__ __forceinline__ void load_block(const char *kh, const char *vh, int t0, int last_row, uint32_t lds, int lane) {
     const int row = min(t0, last_row);
     const char *k_base = kh + (size_t)row * kRowBytes, *v_base = vh + (size_t)row * kRowBytes;
@@ -610,14 +620,14 @@ __device__ __forceinline__ void load_block(const char *kh, const char *vh, int t
     for (int n = 0; n < 8; ++n) {
         const int Rn = 4 * n + (lane >> 4);
         const uint32_t voff = (uint32_t)(min(Rn, last_row - row) * kRowBytes + piece_of(kXor16, Rn, lane & 15) * 16);
-        transfer_at<0>(k_base, voff, lds + n * 1024);
-        transfer_at<0>(v_base, voff, lds + kBlkBytes + n * 1024);
+        transfer_at<0, kOnce>(k_base, voff, lds + n * 1024);
+        transfer_at<0, kOnce>(v_base, voff, lds + kBlkBytes + n * 1024);
     }
 }
 
 // One block of a wave, in the two phases of pipelined_block: its operands are in registers, the previous block's set B is
 // still due, and the next block lies in slot kNext of the wave's ring from the end of phase 1 on.
-template <int kVariant, int kNext>
+template <int kVariant, int kNext, bool kOnce>
 __device__ __forceinline__ void solo_block(WideState &R, const Stationary &A, const SoloFetch &fetch, float *out,
                                            size_t variant_stride, int tok, int tok_prev, int t_end, int lane, int blk, bool hidden,
                                            uint32_t special, const int *vis_i, const int *excl_i, bool accumulate) {
@@ -630,7 +640,7 @@ __device__ __forceinline__ void solo_block(WideState &R, const Stationary &A, co
     PairWork pw[16];
     matrix_phase<0>(A, R.zA, R.voA, R.kreg, R.vreg, [&](int j) __attribute__((always_inline)) {
         if (j < 16) { vvn = sumsq_quarter(R.vreg[j >> 1], j & 1, vvn); stay(vvn); }
-        if (j >= 8) solo_fetch_one(fetch, j - 8);
+        if (j >= 8) solo_fetch_one<kOnce>(fetch, j - 8);
 #pragma unroll
         for (int t = 2 * j; t < 2 * j + 2; ++t) {
             const int r = t / 3;
@@ -679,7 +689,7 @@ __device__ __forceinline__ void solo_block(WideState &R, const Stationary &A, co
 }
 
 // kVariant: OBC_KEY / OBC_JOINT / OBC_ALL.  Grid: see sweep_part; rows row0 .. row0 + 63 of the head.
-template <int kVariant, typename Lens>
+template <int kVariant, bool kOnce, typename Lens>
 __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *__restrict__ q,
                                                                 const uint16_t *__restrict__ k,
                                                                 const uint16_t *__restrict__ v, int N, int W, int Hq,
@@ -722,7 +732,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
     }
     // The wave's first block goes to slot 0; the second slots of waves 0, 1 and 2 first stage the stationary operands:
     // Q, the high and the residual pieces of o_i, one 64-row tile each, brought in by all four waves.
-    load_block(kh, vh, block_of(group), len - 1, ring, lane);
+    load_block<kOnce>(kh, vh, block_of(group), len - 1, ring, lane);
     {
         uint32_t moff[4];
         tile_lane_offsets<kXor16>(moff, wave, lane);
@@ -733,7 +743,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
         const size_t lo_plane = (size_t)heads * m_pad * kRowBytes;
 #pragma unroll 1
         for (int t = 0; t < 3; ++t)                            // (rows past the last one re-read it, and are zeroed below)
-            load_64_rows(t == 0 ? q_rows : t == 1 ? o_rows : o_rows + lo_plane, 0, M - row0 - 1, lds0 + (2 * t + 1) * kSoloSlot + wave * 4096, moff, wave, lane);
+            load_64_rows<false>(t == 0 ? q_rows : t == 1 ? o_rows : o_rows + lo_plane, 0, M - row0 - 1, lds0 + (2 * t + 1) * kSoloSlot + wave * 4096, moff, wave, lane);
     }
     float4 my_rc = make_float4(1e30f, 0.f, __int_as_float(-1), 0.f);   // rows past the last one (1e30) weigh nothing
     int my_excl = -1;
@@ -785,7 +795,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // (the first block's operands, too)
     __syncthreads();                                           // every wave has its stationary operands: the slots are free
     group = next_tile(group, n_groups);
-    load_block(kh, vh, block_of(group), len - 1, ring + kSoloSlot, lane);
+    load_block<kOnce>(kh, vh, block_of(group), len - 1, ring + kSoloSlot, lane);
     R.zA = zero16(); R.voA = zero16(); R.zB = zero16(); R.voB = zero16();
     R.sv = R.sk = R.sj = 0.f;
     R.vv_prev = 0.f;
@@ -798,7 +808,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
         const SoloFetch f = solo_fetch(kh, vh, block_of(after), len - 1, ring + slot.value * kSoloSlot, doff, lane);
         const bool hidden = !(tok0 + 31 <= vis_min);
         const int tok = tok0 + (lane & 31);
-        solo_block<kVariant, 1 - slot.value>(R, A, f, out, variant_stride, tok, tok_prev, t_end, lane, blk, hidden, special_s[special_word(blk)], vis_i, excl_i, accumulate);
+        solo_block<kVariant, 1 - slot.value, kOnce>(R, A, f, out, variant_stride, tok, tok_prev, t_end, lane, blk, hidden, special_s[special_word(blk)], vis_i, excl_i, accumulate);
         tok_prev = tok;
         here = group;
         group = after;
@@ -837,14 +847,17 @@ static hipError_t launch_wide(const ScoreArgs &a, const ScoreWorkspace &ws, char
     const float *row_const = (const float *)(base + ws.row_const), *special = (const float *)(base + ws.special);
     const int accumulate = ws.n_chunks == 1 ? a.accumulate : 0, BH = a.B * a.Hkv, full = ws.n_chunks - ws.solo;
     return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) {
-        if (full > 0)
-            mfma_sweep2_wide<kVariant><<<sweep_grid(a, lens, full, ws.range_len), dim3(kThreads), 0, stream>>>(
-                q, k, v, a.N, a.W, a.Hq, a.Hkv, BH, a.ragged, lens, ws.range_len, full, ws.m_pad, o, row_const, special, dst, plane_elems,
-                chunk_stride, accumulate);
-        if (ws.solo)
-            mfma_sweep2_solo<kVariant><<<sweep_grid(a, lens, 1, ws.range_solo), dim3(kThreads), 0, stream>>>(
-                q, k, v, a.N, a.W, a.Hq, a.Hkv, BH, a.ragged, lens, ws.range_solo, ws.m_pad, full * 128, o, row_const, special,
-                dst + full * chunk_stride, plane_elems, accumulate);
+        auto launch = [&](auto once) {
+            if (full > 0)
+                mfma_sweep2_wide<kVariant, once.value><<<sweep_grid(a, lens, full, ws.range_len), dim3(kThreads), 0, stream>>>(
+                    q, k, v, a.N, a.W, a.Hq, a.Hkv, BH, a.ragged, lens, ws.range_len, full, ws.m_pad, o, row_const, special, dst, plane_elems,
+                    chunk_stride, accumulate);
+            if (ws.solo)
+                mfma_sweep2_solo<kVariant, once.value><<<sweep_grid(a, lens, 1, ws.range_solo), dim3(kThreads), 0, stream>>>(
+                    q, k, v, a.N, a.W, a.Hq, a.Hkv, BH, a.ragged, lens, ws.range_solo, ws.m_pad, full * 128, o, row_const, special,
+                    dst + full * chunk_stride, plane_elems, accumulate);
+        };
+        if (ws.once2) launch(std::true_type{}); else launch(std::false_type{});
         return hipGetLastError();
     });
 }
