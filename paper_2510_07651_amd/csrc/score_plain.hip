@@ -63,7 +63,7 @@ struct RowRecord {
     float top_dk, top_dj;        // ||v - o||^2 and ||v + Z (v - o)||^2 of the top token
     int last;                    // last token the row sees
     double oo;                   // ||o_i||^2
-    double unit;                 // of o_i's digits (score_fixed.h)
+    float root;                  // sqrt(oo) / 16 (score_fixed.h); short_partial's merge: the sum of exp(z - m) without the top token
 };
 
 template <typename T> __device__ __forceinline__ float load_as_float(const T *p);
@@ -411,14 +411,14 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
 
 // ------------------------------------------------------------------------------------
 // Merge.  One wave per row, D / 64 consecutive elements per lane.  Grid: x = four rows of the piece, z = KV head.
-// The output is left in fp32, with kFixed also as digits.
+// The output is left in fp32, with kFixed also as bf16 pieces.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, bool kNeedO, bool kFixed, typename Lens>
 __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
                                                         Piece w, int split_len, int n_splits,
                                                         const float *__restrict__ part_l, const float *__restrict__ part_o,
                                                         RowRecord *__restrict__ records, float *__restrict__ out,
-                                                        int8_t *__restrict__ out_digits) {
+                                                        uint16_t *__restrict__ out_pieces) {
     constexpr int kE = D / 64;
     const int hl = blockIdx.z, bg = w.bg0 + hl, row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= w.nr) return;                                 // uniform over the wave
@@ -445,7 +445,6 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
     const float frac = l / (1.0f + l);                       // 1 - A_{i,top}; the top token's own weight is exp(0) = 1
     const float inv = l > 0.f ? 1.0f / l : 0.f;
     double oo = 0.0, dk = 0.0, dj = 0.0;
-    double unit = 0.0;
     if (kNeedO) {
         float oi[kE];
 #pragma unroll
@@ -459,17 +458,13 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
         }
         const size_t at = (size_t)hl * w.nr + row;
         if constexpr (kFixed) {
-            const float f[4] = {oi[0], kE > 1 ? oi[kE - 1] : 0.f, 0.f, 0.f};
-            const double x[4] = {f[0], f[1], 0.0, 0.0};
-            const int oe = max_exponent(wave_reduce<MaxBitsOp>(max_abs(f)));
-            unit = row_unit(oe);
-            uint32_t p[kRowDigits];
-            digits_of<kRowDigits>(x, oe, p);
+            uint32_t p[3];
+            three_pieces(oi[0], oi[kE - 1], p);
 #pragma unroll
-            for (int k = 0; k < kRowDigits; ++k) {
-                int8_t *dst = out_digits + digit_address<kRowDigits, D>((size_t)hl * ((w.nr + 15) / 16) + row / 16, k, row, lane * kE);
-                if constexpr (kE == 2) *(uint16_t *)dst = (uint16_t)p[k];
-                else *dst = (int8_t)p[k];
+            for (int k = 0; k < 3; ++k) {
+                uint16_t *dst = out_pieces + row_piece_address<D>((size_t)hl * ((w.nr + 15) / 16) + row / 16, k, row, lane * kE);
+                if constexpr (kE == 2) *(uint32_t *)dst = p[k];
+                else *dst = (uint16_t)p[k];
             }
         }
 #pragma unroll
@@ -484,7 +479,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
         rec->top_dk = (float)dk;
         rec->top_dj = (float)dj;
         rec->oo = oo;
-        rec->unit = unit;
+        rec->root = 0.0625f * __builtin_sqrtf((float)oo);
     }
 }
 
@@ -634,7 +629,7 @@ __device__ __forceinline__ void merge_short(const T *__restrict__ vg, int len, i
             rec.top = top;
             rec.inv_l = 1.0f / (1.0f + l);
             rec.last = len - W + row % W;
-            rec.unit = l;                                    // (for the vectors below)
+            rec.root = l;                                    // (for the vectors below)
         }
     }
     __syncthreads();
@@ -660,7 +655,7 @@ __device__ __forceinline__ void merge_short(const T *__restrict__ vg, int len, i
 #pragma unroll
                 for (int e = 0; e < kE; ++e) o[e] += wt * *(const f32x4 *)(src + 64 * e);
             }
-        const float l = (float)rec_s[rc].unit, m = rec_s[rc].m;
+        const float l = rec_s[rc].root, m = rec_s[rc].m;
         const float frac = l / (1.0f + l);                   // 1 - A_{i,top}; the top token's own weight is exp(0) = 1
         const float inv = l > 0.f ? 1.0f / l : 0.f;
         double oo = 0.0, dk = 0.0, dj = 0.0;
@@ -851,7 +846,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     float *out = (float *)(base + ws.pl_out);
     float2 *best = (float2 *)(base + ws.pl_best);
     RowRecord *rec = (RowRecord *)(base + ws.pl_records);
-    int8_t *o_digits = (int8_t *)(base + ws.pl_o_digits);
+    uint16_t *o_pieces = (uint16_t *)(base + ws.pl_o_pieces);
     // More than 32 rows: score_fixed.h, 64 or 128 of them per workgroup.
     constexpr bool fixed = kRt == 4 || kRt == 8;
     constexpr int kRb = kRt == 8 ? 8 : 4;
@@ -913,12 +908,13 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             }
             if (mask & OBC_STAGE_COMBINE) {
                 const dim3 grid((w.nr + 3) / 4, 1, heads);
-#define OBC_PLAIN_MERGE(need_o, fixed)                                                                                 \
-    plain_merge<T, D, need_o, fixed><<<grid, dim3(kThreads), 0, stream>>>(v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split,  \
-                                                                          ws.pl_splits, part_l, part_o, rec, out, o_digits)
-                if (need_o) OBC_PLAIN_MERGE(true, fixed);
-                else OBC_PLAIN_MERGE(false, false);
-#undef OBC_PLAIN_MERGE
+                auto merge = [&](auto with_output) {
+                    constexpr bool kNeedO = decltype(with_output)::value;
+                    plain_merge<T, D, kNeedO, kNeedO && fixed><<<grid, dim3(kThreads), 0, stream>>>(
+                        v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split, ws.pl_splits, part_l, part_o, rec, out, o_pieces);
+                };
+                if (need_o) merge(std::true_type());
+                else merge(std::false_type());
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
             if (!(mask & OBC_STAGE_SWEEP2)) continue;
@@ -932,8 +928,8 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                         constexpr int kTok = kFixedTile<D>;
                         const int tiles = (w.s1 - w.s0 + kTok - 1) / kTok;
                         const int n_tiles = (int)std::min((tiles * (long long)heads + kResident / 2 - 1) / (kResident / 2), kScoreTokens / kTok + 0ll);
-                        fixed_score<T, D, kRb, kVariant><<<dim3(heads, (tiles + n_tiles - 1) / n_tiles), dim3(kFixedThreads), 0, stream>>>(
-                            v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_digits, a.scores, variant_stride, add);
+                        pieces_score<T, D, kRb, kVariant><<<dim3(heads, (tiles + n_tiles - 1) / n_tiles), dim3(kFixedThreads), 0, stream>>>(
+                            v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_pieces, a.scores, variant_stride, add);
                     } else {
                         const int tiles = (w.s1 - w.s0 + kTile - 1) / kTile;
                         const int n_tiles = (int)((tiles * (long long)heads + kResident - 1) / kResident);
@@ -988,7 +984,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t c
     ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
     ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
     auto row_bytes = [&]() {                                 // of one row, beside its logits
-        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 9 : 4) + (size_t)ws->pl_splits * (d + 1) * 4;
+        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 10 : 4) + (size_t)ws->pl_splits * (d + 1) * 4;
     };
     const size_t per_row = row_bytes() + (size_t)align_up(N, kTile) * 4;
     cap -= 7 * 256;                                          // alignment of the buffers
@@ -1031,7 +1027,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t c
     take(&ws->pl_best, rows * ws->pl_ranges * sizeof(float2));
     take(&ws->pl_records, rows * sizeof(RowRecord));
     take(&ws->pl_out, rows * d * 4);
-    if (fixed) take(&ws->pl_o_digits, rows * d * 5);
+    if (fixed) take(&ws->pl_o_pieces, rows * d * 6);
     take(&ws->pl_part_l, rows * ws->pl_splits * 4);
     take(&ws->pl_part_o, rows * ws->pl_splits * d * 4);
 }

@@ -61,6 +61,9 @@ VALUES = {
     "nearly_repeated": lambda v: v[:, :, :1] + v * 2.0 ** -4,
     # the same row exactly, but for every eighth token
     "repeated": lambda v: torch.where((torch.arange(v.shape[2]) % 8 == 5)[:, None], v, v[:, :, :1]),
+    # a common part of two and three times the rest: distances on either side of ||v|| ||o|| / 16, where fp64 takes over
+    "common_part_2": lambda v: v + 2 * v[:, :, :1],
+    "common_part_3": lambda v: v + 3 * v[:, :, :1],
     # multiples of one row: (1 + Z) v cancels Z o for some pairs
     "parallel": lambda v: v[:, :, :1] * (1 + v[..., :1]) + v * 2.0 ** -4,
 }
