@@ -70,9 +70,10 @@ struct ScoreWorkspace {
     size_t pl_records; // RowRecord [heads*rows]
     size_t pl_out;     // float [heads*rows*d]       o_i = sum_p A_ip v_p
     size_t pl_o_pieces;  // bf16 [heads*rows][3][d]  o_i as three pieces (score_fixed.h)
-    size_t pl_part_l;  // float [heads*splits*rows]  sum of exp(z - max) of a split, without the row's top token
+    size_t pl_part_l;  // float [heads*splits*rows]  sum of exp(z - max) of a split, without the row's top token; with pl_digits float4: the
+                       // split's own largest logit, the sum without its own top token, that token
     size_t pl_part_o;  // float [heads*splits*rows*d]  unnormalised output of a split, likewise
-    int pl_heads, pl_rows, pl_seg, pl_z_stride, pl_short, pl_digit_logits;
+    int pl_heads, pl_rows, pl_seg, pl_z_stride, pl_short, pl_digits;
     int pl_range, pl_ranges;   // tokens per range, ranges
     int pl_split, pl_splits;   // tokens per split (a multiple of 64), splits
     // Decode path (one window row per query head): see score_decode.hip.

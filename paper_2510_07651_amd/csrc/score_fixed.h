@@ -3,7 +3,7 @@
 // The fp64 matrix cores do 79 TFLOP/s and the fp32 ones 157, the 8-bit integer ones 5000 and the bf16 ones 2500, so
 // contractions whose accuracy allows it are taken apart into pieces the fast ones multiply exactly.
 //
-// Logits (digit_logits).  Rows of q and k as fixed point relative to their largest element, fp32 values 46 bits and a sign in
+// Logits (digit_sweep).  Rows of q and k as fixed point relative to their largest element, fp32 values 46 bits and a sign in
 // six balanced base-256 digits, bf16 values 30 bits in four, which hold their elements exactly down to 2^-23 of the row's
 // largest.  Products of digits are summed exactly in 32-bit integers, for the seven highest of the levels (all of four by
 // four digits).  Fixed point alone cannot stand in for fp64: where a key has a large element that meets a small one of the
@@ -16,28 +16,16 @@
 //   element, 2^-40 2^E per dot product and side, 2^-27 of it from 2^-12 2^E up (kLeastDotCut, for the blocks with such a row
 //   in their tile or their window rows).  Normal rows: one in 30000;
 //   bf16 rows with such elements, infinities, NaN: fp64 always.
-// Of normal keys with channels larger by 8, 0.5 % of the blocks go to fp64.  The scores of the benchmark shapes are the same
-// bit for bit.  A block that goes that way does both, and fetches its operands from memory again: whole calls, joint, us,
-// ordinary inputs / every block in fp64 (key channels 2^26 larger that meet query channels as much smaller, or a key of zeros
-// among every sixteen) / fp64 throughout (blocked_logits) / fp32 keys that are all cut:
-//   fp32, d = 128,  8 heads x 128 rows x  8111 tokens    97 /  144 /  111 /  106     (the logits alone 35 / 86 / 49)
-//   fp32, d = 128, 32 heads x 256 rows x  8111 tokens  1071 / 1943 / 1256 / 1315     (426 / 1281 / 565)
-//   fp32, d =  64, 16 heads x 160 rows x 16000 tokens   343 /  519 /  364 /  388
-//   bf16, d =  64,  8 heads x 128 rows x 16384 tokens    95 /  133 /  107            (29 / 79 / 51)
-// So inputs of that kind take 1.25 to 1.55 times what they would in fp64, and ordinary ones are 1.06 to 1.17 times faster.  (Without
-// the digits while a wave's blocks go to fp64 one after the other, and with four of their loads in flight, such calls took 2 to
-// 8 % less: what they cost is the fp64 products themselves, at a wave's own pace from memory.)
-// A workgroup takes its 128 rows apart, which costs as much as some tiles, so short calls stay with blocked_logits.  Attention
-// scores of 7700 random shapes (4 to 128 heads, 33 to 512 rows), time with fp64 over time with digits, geometric means by 64-token
-// tiles times 128-row chunks over all heads:
-//   tiles             128    256    512    724   1024   1217   2048
-//   fp32, d = 128    0.89   0.96   1.01   1.07   1.10   1.19   1.21
-//   bf16, d =  64    0.93   0.95   1.02   1.09   1.11   1.18   1.24
-//   fp32, d =  64    0.86   0.89   0.94   0.97   1.00   1.06   1.10
-// Shapes of one size differ by 10 % either way, as a launch's last turn is full or not.  digit_tiles, 768 and for fp32, d = 64
-// 1280: less than 1 % of the shapes lose 3 % or more (with 512 for all it was 11.6 % of the last kind, up to a fifth of a call), and all
-// of them gain 2.7 to 8 % in the mean.  (The line counts every head of the call, so which kernel forms a sequence's logits, and
-// with it their last bit now and then, depends on the batch.)
+// Of normal keys with channels larger by 8, 0.5 % of the blocks go to fp64.  A block that goes that way does both, and fetches its
+// operands from memory again: whole calls, joint, us, ordinary inputs / every block in fp64 (key channels 2^26 larger that meet query
+// channels as much smaller, or a key of zeros among every sixteen) / fp32 keys that are all cut, and with blocked_logits:
+//   fp32, d = 128,  8 heads x 128 rows x  8111 tokens    93 / 133 /  97    111      1500 tokens    38.5 / 48.5 / 40.9    41.1
+//   fp32, d = 128, 32 heads x 256 rows x  8111 tokens   585 / 960 / 636   1256
+//   fp32, d =  64, 16 heads x 160 rows x 16000 tokens   299 / 441 / 338    364
+//   bf16, d =  64,  8 heads x 128 rows x 16384 tokens    81 / 123          107      1500 tokens    27.8 / 34.2           29.7
+// (Without the digits while a wave's blocks go to fp64 one after the other, and with four of their loads in flight, such calls took 2
+// to 8 % less: what they cost is the fp64 products themselves, at a wave's own pace from memory.)
+// Which calls digit_sweep takes: sweeps_digits (score_plain.hip).
 //
 // v_p . o_i (pieces_score).  v and o as three bf16 pieces each (bf16 values as they are), the six products down to 2^-18 of the
 // largest on the bf16 matrix cores, fp32 accumulation: the highest pieces' products in two halves, everything else apart, put
@@ -52,25 +40,25 @@
 // quicker; with a line of 1/4 they go to fp64, 97 us instead of 68; with one of 1/64 a common part of four times the rest is off by
 // 1.1e-6.)
 //
-// P V (fixed_weights).  Weights and fp32 values as three bf16 pieces each, all nine products (exact, normal numbers), fp32
+// P V (weights_pv).  Weights and fp32 values as three bf16 pieces each, all nine products (exact, normal numbers), fp32
 // accumulation: per 32 tokens nine bf16 ops (three for bf16 values) of 16 cycles replace eight fp32 ones of 32.
 // The outputs are as good as those of the fp32 ops: key scores of values that differ by 2^-6 (2^-9) of their norm, where the
 // outputs' error is what shows, are off by 1.0e-6 (8.6e-6) in the 2-norm, with plain_weights by 1.1e-6 (8.7e-6); fp32,
 // d = 128, 8111 tokens.
 //
-// What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  digit_logits: the vector ALUs (71 % of the
-// kernel for bf16 values, 53 % for fp32: some 18 instructions put a pair's levels together, check and scale them, some 9 take an
-// element apart) and the integer matrix cores (30 % and 43 %), a wave doing one after the other.  pieces_score: chains of a
-// wave's dependent instructions (exponential, norms in fp64, closeness test: some 40 per 64 pairs) and the logits' way from memory, 67 MB
-// for the second shape below; fixed_weights: vector ALUs and matrix cores in turn (exponentials and pieces; busy 37 %).
-// Kernel times, 32/8 heads, joint, in us: logits (blocked_logits) / weights / merge / scores
-//   fp32, d = 128,  8111 tokens   36.0 (48.5) / 27.3 / 5.5 / 26.1 (from digits 27.6)
-//   bf16, d = 64,  16384 tokens   28.7 (47.5) / 21.4 / 5.0 / 28.2 (from digits 34.5)
-// Against the kernels for up to 32 rows, whole calls, 8 heads, us here / there:
-//   33 rows: fp32 d 128 8K 64 / 81, 4 x 8K 189 / 250; d 64 8K 42 / 56; bf16 d 64 8K 40 / 57, 2K 22 / 29
-//   32 rows: fp32 d 128 8K 54 / 59, 4 x 8K 154 / 154; d 64 8K 37 / 44; bf16 d 64 8K 33 / 43, 2K 20 / 24
-//   17 rows: fp32 d 128 8K 54 / 56, 4 x 8K 153 / 148; d 64 4 x 8K 98 / 89; bf16 d 64 8K 33 / 41
-// so the line lies at 32 rows, where fp32 batches break even; for bf16 it could lie lower.
+// What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  digit_sweep: vector ALUs and matrix cores, a wave
+// using one after the other (some 18 instructions put a pair's levels together, check and scale them, some 9 take an element apart, some
+// 20 make its weight and the weight's pieces), all four waves of a SIMD at the same stage.  pieces_score: chains of a wave's dependent
+// instructions (exponential, norms in fp64, closeness test: some 40 per 64 pairs) and the logits' way from memory, 67 MB for the second
+// shape below.
+// Kernel times, 32/8 heads, joint, in us: digit_sweep (as two kernels, logits / weights) / merge / scores
+//   fp32, d = 128,  8111 tokens   53.9 (36.0 / 27.3) / 5.5 / 24.5 (from digits 27.6)
+//   bf16, d = 64,  16384 tokens   43.0 (28.7 / 21.4) / 5.0 / 28.2 (from digits 34.5)
+// Two kernels met between them: the maxima of all ranges first.  Whole calls, two kernels / one (with as many splits as fill the chip
+// where the calls' heads pass in several launches), joint, us:
+//   fp32, d = 128, 4 x 8 heads x 128 rows x 8000   375 / 302     bf16, d = 64, 8 x 8 heads x 128 rows x 3000   168 / 128
+//   fp32, d = 128, 1 head x 128 rows x 60000       238 / 165     bf16, d = 64, 8 heads x 48 rows x 16384      51.7 / 47.7
+//   fp32, d =  64, 8 heads x 512 rows x 6000       232 / 168     fp32, d = 128, 8 heads x 128 rows x 8111      91.6 / 87
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -262,7 +250,7 @@ struct TokenTile {
         }
         return v;
     }
-    // The digits of digit_logits and the rows' exponents into LDS; fp32: also whether elements of the wave's rows were cut.
+    // The digits of digit_sweep and the rows' exponents into LDS; fp32: also whether elements of the wave's rows were cut.
     template <int K>
     __device__ __forceinline__ void store_logit_digits(char *digits, int *exponents, uint8_t *cut_s) const {
         int thread = threadIdx.x;
@@ -350,7 +338,7 @@ struct TokenTile {
 template <int K, int D>
 struct RowDigits {
     i32x4 x[K][D / 64];
-    // Digits of a row itself, for digit_logits; returns the row's exponent.  fp32: `any_cut`, whether elements of the wave's
+    // Digits of a row itself, for digit_sweep; returns the row's exponent.  fp32: `any_cut`, whether elements of the wave's
     // rows were cut.
     template <typename T>
     __device__ __forceinline__ int take(const T *__restrict__ row, int g, bool &any_cut) {
@@ -582,112 +570,6 @@ __global__ __launch_bounds__(kThreads, 4) void blocked_logits(const T *__restric
 }
 
 // ------------------------------------------------------------------------------------
-// The same from digits, where the call is long enough.  Grid: x = KV head, y = token range of the piece, z = chunk of 16 kRb
-// rows.  Lane = row + 16 g, registers = tokens 4 g .. 4 g + 3 of the 16 at hand.
-// ------------------------------------------------------------------------------------
-template <typename T, int D, int kRb, typename Lens>
-__global__ __launch_bounds__(kFixedThreads, 4) void digit_logits(const T *__restrict__ q, const T *__restrict__ k, int N, int W, int Hq,
-                                                                 int Hkv, int ragged, Lens lens, Piece w, int range_len, int n_ranges,
-                                                                 float *__restrict__ z, float2 *__restrict__ range_best) {
-    constexpr int K = kLogitDigits<T>, kTok = kFixedTile<D>, kParts = 8 / kRb, kPart = kTok / kParts, kRows = 16 * kRb,
-                  kBuf = buffers_of(K * kTok * D);
-    static_assert(kBuf == 2, "one barrier per tile");
-    __shared__ __attribute__((aligned(16))) char digits[kBuf][K * kTok * D];
-    __shared__ __attribute__((aligned(16))) int exponents[2][kTok];
-    __shared__ __attribute__((aligned(8))) uint8_t cut_s[2][kFixedThreads / 64];
-    __shared__ float2 best_s[kParts][kRows];
-    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv, M = Hq / Hkv * W;
-    const int len = seq_len_of(lens, ragged, b, N);
-    const int range = w.s0 / range_len + blockIdx.y;
-    const int t_begin = range * range_len, t_end = min(min(t_begin + range_len, w.s1), len);
-    if (t_begin >= t_end) return;                            // uniform
-    const int row0 = blockIdx.z * kRows, blocks = (w.nr + 15) / 16;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int rb = wave % kRb, part = wave / kRb, row = row0 + rb * 16 + (lane & 15);
-    const bool live = row0 / 16 + rb < blocks;               // uniform in the wave
-    const T *kg = k + (size_t)bg * N * D;
-    const __amdgpu_buffer_rsrc_t span = span_of(kg + (size_t)t_begin * D, (size_t)(t_end - t_begin) * D * sizeof(T));
-    TokenTile<T, D, kTok, kFixedThreads> next;
-    next.load(span, 0);
-    const T *q_row = q + ((size_t)b * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D;
-    RowDigits<K, D> rows;
-    bool rows_cut;
-    const int exponent = rows.template take<T>(q_row, lane >> 4, rows_cut) - 51 - 3;
-    const int last = min(len - W + (w.r0 + min(row, w.nr - 1)) % W, t_end - 1);                // last token the row sees here
-    const int least = __builtin_amdgcn_readfirstlane((int)row16_reduce<MinOp>((uint32_t)last));      // of the 16 rows
-    float *zp = z + z_block(w, hl, min(row0 / 16 + rb, blocks - 1), t_begin) + lane * 4;
-    float m = -INFINITY;
-    int at = kNoToken;
-    next.template store_logit_digits<K>(digits[0], exponents[0], cut_s[0]);
-    if (t_begin + kTok < t_end) next.load(span, kTok);
-    int slot = 0;
-    for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
-        __syncthreads();                                     // this tile is in LDS, the one before it has been read
-        if (t0 + kTok < t_end) next.template store_logit_digits<K>(digits[slot ^ 1], exponents[slot ^ 1], cut_s[slot ^ 1]);
-        if (t0 + 2 * kTok < t_end) next.load(span, t0 - t_begin + 2 * kTok);
-        if (!live) continue;
-        double least_dot = kLeastDot<T>;
-        if (sizeof(T) == 4) {
-            const uint2 cut = *(const uint2 *)cut_s[slot];
-            if (rows_cut || __builtin_amdgcn_readfirstlane((int)(cut.x | cut.y)) != 0) least_dot = kLeastDotCut;     // uniform
-        }
-#pragma unroll 1
-        for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
-            i32x4 acc[kLogitLevels];
-            level_sums<K, K, D, kTok>(rows, digits[slot], p0 + (lane & 15), lane >> 4, acc);
-            __builtin_amdgcn_sched_barrier(0);
-            const int first = t0 + p0 + 4 * (lane >> 4);     // register r has token first + r
-            const i32x4 ex = *(const i32x4 *)&exponents[slot][p0 + 4 * (lane >> 4)];
-            float x[4];
-            bool again = max(max(max(ex[0], ex[1]), ex[2]), ex[3]) + exponent >= kNoExponent / 2;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                double dot = join_seven<K>(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r], acc[5][r], acc[6][r]);
-                again |= fabs(dot) < least_dot;              // (also of the zeros past the end)
-                if (D == 128) dot *= 0.088388347648318440550 * 8.0;
-                x[r] = __builtin_amdgcn_ldexpf((float)dot, ex[r] + exponent);
-            }
-            if (__builtin_amdgcn_ballot_w64(again) != 0ull) {            // uniform
-                double dot[4];
-                block_dots<T, D>(kg + (size_t)min(t0 + p0 + 4 * (lane & 3) + (lane >> 2 & 3), t_end - 1) * D, q_row, lane >> 4, dot);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) x[r] = (float)(dot[r] * (1.0 / sqrt((double)D)));
-            }
-            auto improve = [&](const float (&y)[4]) {
-                const float best = fmaxf(fmaxf(fmaxf(y[0], y[1]), y[2]), y[3]);
-                if (__builtin_amdgcn_ballot_w64(best > m) == 0ull) return;       // uniform, usual once the maxima have settled
-#pragma unroll
-                for (int r = 0; r < 4; ++r)                  // (tokens ascend: strict keeps the lowest)
-                    if (y[r] > m) { m = y[r]; at = first + r; }
-            };
-            if (t0 + p0 + 15 > least) {                      // uniform: not every row sees every token
-                float y[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) y[r] = first + r <= last ? x[r] : -INFINITY;
-                improve(y);
-            } else {
-                improve(x);
-            }
-            *(float4 *)(zp + (t0 - t_begin + p0) * 16) = make_float4(x[0], x[1], x[2], x[3]);      // (room for whole tiles)
-        }
-    }
-    best_of_pair<16>(m, at);
-    best_of_pair<32>(m, at);
-    if (lane < 16) best_s[part][rb * 16 + lane] = make_float2(m, __int_as_float(at));
-    __syncthreads();
-    const int r = threadIdx.x;
-    if (r < kRows && row0 + r < w.nr) {
-        float2 best = best_s[0][r];
-#pragma unroll
-        for (int c = 1; c < kParts; ++c) {
-            const float2 o = best_s[c][r];
-            if (o.x > best.x || (o.x == best.x && __float_as_int(o.y) < __float_as_int(best.y))) best = o;
-        }
-        range_best[((size_t)hl * w.nr + row0 + r) * n_ranges + range] = best;
-    }
-}
-
-// ------------------------------------------------------------------------------------
 // Weights and P V.  Grid: x = KV head, y = split of the piece, z = chunk of 16 kRb rows.  O^T += V^T P^T, 32 tokens
 // at a time; lane = row + 16 g.  The parts of a tile (16 / kRb of them) meet in LDS at the
 // end: two waves per SIMD are too few to hide the chain logit, weight, product, and more splits would be more traffic.
@@ -700,37 +582,28 @@ __device__ __forceinline__ int value_offset(int plane, int tok, int c) {
     return (plane * kTok + tok) * D * 2 + slot * 16;
 }
 
-// Tokens of a tile: 32 for every part, or 64 where a tile would have fewer 16-byte pieces than threads.
+// Tokens of a tile of values: 32 for every part, or 64 where a tile would have fewer 16-byte pieces than threads.
 template <typename T, int D, int kRb>
 constexpr int kWeightTile = 16 / kRb * 32 * D * (int)sizeof(T) >= kWeightThreads * 16 ? 16 / kRb * 32 : 16 / kRb * 64;
-template <typename T, int D, int kRb, bool kNeedO, typename Lens>
-__global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
-                                                                  Piece w, int range_len, int n_ranges, int split_len, int n_splits,
-                                                                  const float *__restrict__ z, const float2 *__restrict__ range_best,
-                                                                  RowRecord *__restrict__ records, float *__restrict__ part_l,
-                                                                  float *__restrict__ part_o) {
-    constexpr int kTok = kWeightTile<T, D, kRb>, kParts = 16 / kRb, kPart = kTok / kParts, kP = sizeof(T) == 4 ? 3 : 1,
-                  kRows = 16 * kRb, kTileBytes = kP * kTok * D * 2, kBuf = kTileBytes <= 64 * 1024 ? 2 : 1;
-    constexpr int kMergeBytes = (kParts - 1) * kRows * D * 4;
-    __shared__ __attribute__((aligned(16))) char values[kNeedO ? (kBuf * kTileBytes > kMergeBytes ? kBuf * kTileBytes : kMergeBytes) : 16];
-    __shared__ float sum_s[kParts][kRows];
-    __shared__ float m_s[kRows];
-    __shared__ int top_s[kRows];
-    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
-    const int len = seq_len_of(lens, ragged, b, N);
-    const int split = w.s0 / split_len + blockIdx.y;
-    const int t_begin = split * split_len, t_end = min(min(t_begin + split_len, w.s1), len);
-    if (t_begin >= t_end) return;                            // uniform
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4;
-    const int rb = wave % kRb, part = wave / kRb, row0 = blockIdx.z * kRows;
-    const __amdgpu_buffer_rsrc_t vg = span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T));
+template <typename T> constexpr int kValuePieces = sizeof(T) == 4 ? 3 : 1;
+template <typename T, int D, int kRb> constexpr int kValueBytes = kValuePieces<T> * kWeightTile<T, D, kRb> * D * 2;
+template <typename T, int D, int kRb> constexpr int kValueBuffers = kValueBytes<T, D, kRb> <= 64 * 1024 ? 2 : 1;
+template <typename T, int D, int kRb>                                    // of LDS: tiles of values, later the parts' sums
+constexpr int kWeightBytes = std::max(kValueBuffers<T, D, kRb> * kValueBytes<T, D, kRb>, (16 / kRb - 1) * 16 * kRb * D * 4);
+
+// Weights and P V of tokens t_begin .. t_end - 1 for the wave's 16 rows: O^T += V^T P^T, 32 tokens at a time; lane = row + 16 g.  The
+// parts of a tile (16 / kRb of them) meet in LDS at the end: two waves per SIMD are too few to hide the chain logit, weight, product,
+// and more splits would be more traffic.  `zg`, `z_at`: where the lane's logits of t_begin lie; `vg`: the values from t_begin on.
+// `before` runs while the first loads are on their way, `rows(m, top, last)` gives the lane's row once all waves are through that: the
+// reference, the token left out, the last token it sees.  Returns the row's sum, and the sums of P V in `acc`, for the first part.
+template <typename T, int D, int kRb, bool kNeedO, typename Before, typename Rows>
+__device__ __forceinline__ float weights_pv(char *values, float (*sum_s)[16 * kRb], __amdgpu_buffer_rsrc_t zg, int z_at, __amdgpu_buffer_rsrc_t vg,
+                                            int t_begin, int t_end, int rb, int part, int lane, Before &&before, Rows &&rows, f32x4 (&acc)[D / 16]) {
+    constexpr int kTok = kWeightTile<T, D, kRb>, kParts = 16 / kRb, kPart = kTok / kParts, kP = kValuePieces<T>,
+                  kTileBytes = kValueBytes<T, D, kRb>, kBuf = kValueBuffers<T, D, kRb>;
+    const int g = lane >> 4, row_l = rb * 16 + (lane & 15);
     TokenTile<T, D, kTok, kWeightThreads> next;
     if (kNeedO) next.load(vg, 0);
-    const int row_l = rb * 16 + (lane & 15), row = row0 + row_l;
-    const int block = min(row0 / 16 + rb, (w.nr + 15) / 16 - 1);
-    const size_t z_head = z_block(w, hl, 0, w.s0);
-    const __amdgpu_buffer_rsrc_t zg = span_of(z + z_head, z_block(w, 1, 0, w.s0) * 4);
-    const int z_at = (int)(z_block(w, hl, block, t_begin) - z_head) * 4 + lane * 16;
     // This lane's logits of a 32-token step: tokens 4 g + {0..3} and 16 + 4 g + {0..3}, the order of the transposing reads.
     // (What lies beyond the last token's tile is anything, and not used.)
     float4 x[2 * (kPart / 32)];
@@ -742,28 +615,7 @@ __global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__re
         }
     };
     fetch(t_begin);
-    {
-        constexpr int kSub = kWeightThreads / kRows;          // the row's maximum over its ranges: kSub lanes per row
-        const int row = threadIdx.x / kSub, live = (len + range_len - 1) / range_len;
-        float m = -INFINITY;
-        int at = kNoToken;
-        if (row0 + row < w.nr)
-#pragma unroll 8
-            for (int i = threadIdx.x % kSub; i < live; i += kSub) {
-                const float2 o = range_best[((size_t)hl * w.nr + row0 + row) * n_ranges + i];
-                if (o.x > m || (o.x == m && __float_as_int(o.y) < at)) { m = o.x; at = __float_as_int(o.y); }
-            }
-        lanes_best<kSub>(m, at);
-        if (threadIdx.x % kSub == 0) {
-            m_s[row] = m;
-            top_s[row] = at;
-            if (split == 0 && row0 + row < w.nr) {
-                RowRecord *rec = records + (size_t)hl * w.nr + row0 + row;
-                rec->m = m;
-                rec->top = at;
-            }
-        }
-    }
+    before();
     auto store_values = [&](int slot) {
         int thread = threadIdx.x;
         asm volatile("" : "+v"(thread));                     // (addresses anew for every tile: registers)
@@ -787,11 +639,10 @@ __global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__re
     };
     if (kNeedO) store_values(0);
     __syncthreads();
-    const float m = row < w.nr ? m_s[row_l] : 0.f;
-    const int top = top_s[row_l];
-    const int last = row < w.nr ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;    // last token the row sees here
+    float m;
+    int top, last;
+    rows(m, top, last);
     if (kNeedO && t_begin + kTok < t_end) next.load(vg, kTok);
-    f32x4 acc[D / 16];
 #pragma unroll
     for (int d = 0; d < D / 16; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
     float sum = 0.f;
@@ -859,24 +710,217 @@ __global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__re
         for (int d = 0; d < D / 16; ++d)
             merge[((part - 1) * kRb * (D / 16) + d) * 64] = make_float4(acc[d][0], acc[d][1], acc[d][2], acc[d][3]);
     __syncthreads();
+    if (part > 0) return sum;
+#pragma unroll
+    for (int c = 1; c < kParts; ++c) sum += sum_s[c][row_l];
+    if (kNeedO)
+#pragma unroll
+        for (int d = 0; d < D / 16; ++d)
+#pragma unroll
+            for (int c = 0; c < kParts - 1; ++c) {
+                const float4 x = merge[(c * kRb * (D / 16) + d) * 64];
+                acc[d][0] += x.x; acc[d][1] += x.y; acc[d][2] += x.z; acc[d][3] += x.w;
+            }
+    return sum;
+}
+// The row's sums of P V to memory.
+template <int D>
+__device__ __forceinline__ void write_output(float *__restrict__ to, const f32x4 (&acc)[D / 16], int g) {
+#pragma unroll
+    for (int d = 0; d < D / 16; ++d) *(float4 *)(to + d * 16 + 4 * g) = make_float4(acc[d][0], acc[d][1], acc[d][2], acc[d][3]);
+}
+
+// ------------------------------------------------------------------------------------
+// Weights and P V behind blocked_logits, relative to the row's maximum over all its ranges.  Grid: x = KV head, y = split of the piece,
+// z = chunk of 16 kRb rows.
+// ------------------------------------------------------------------------------------
+template <typename T, int D, int kRb, bool kNeedO, typename Lens>
+__global__ __launch_bounds__(kWeightThreads, 4) void fixed_weights(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
+                                                                  Piece w, int range_len, int n_ranges, int split_len, int n_splits,
+                                                                  const float *__restrict__ z, const float2 *__restrict__ range_best,
+                                                                  RowRecord *__restrict__ records, float *__restrict__ part_l,
+                                                                  float *__restrict__ part_o) {
+    constexpr int kRows = 16 * kRb;
+    __shared__ __attribute__((aligned(16))) char values[kNeedO ? kWeightBytes<T, D, kRb> : 16];
+    __shared__ float sum_s[16 / kRb][kRows];
+    __shared__ float m_s[kRows];
+    __shared__ int top_s[kRows];
+    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
+    const int len = seq_len_of(lens, ragged, b, N);
+    const int split = w.s0 / split_len + blockIdx.y;
+    const int t_begin = split * split_len, t_end = min(min(t_begin + split_len, w.s1), len);
+    if (t_begin >= t_end) return;                            // uniform
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int rb = wave % kRb, part = wave / kRb, row0 = blockIdx.z * kRows, row_l = rb * 16 + (lane & 15), row = row0 + row_l;
+    const int block = min(row0 / 16 + rb, (w.nr + 15) / 16 - 1);
+    const size_t z_head = z_block(w, hl, 0, w.s0);
+    f32x4 acc[D / 16];
+    const float sum = weights_pv<T, D, kRb, kNeedO>(
+        values, sum_s, span_of(z + z_head, z_block(w, 1, 0, w.s0) * 4), (int)(z_block(w, hl, block, t_begin) - z_head) * 4 + lane * 16,
+        span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T)), t_begin, t_end, rb, part, lane,
+        [&]() {
+            constexpr int kSub = kWeightThreads / kRows;          // the row's maximum over its ranges: kSub lanes per row
+            const int row = threadIdx.x / kSub, live = (len + range_len - 1) / range_len;
+            float m = -INFINITY;
+            int at = kNoToken;
+            if (row0 + row < w.nr)
+#pragma unroll 8
+                for (int i = threadIdx.x % kSub; i < live; i += kSub) {
+                    const float2 o = range_best[((size_t)hl * w.nr + row0 + row) * n_ranges + i];
+                    if (o.x > m || (o.x == m && __float_as_int(o.y) < at)) { m = o.x; at = __float_as_int(o.y); }
+                }
+            lanes_best<kSub>(m, at);
+            if (threadIdx.x % kSub == 0) {
+                m_s[row] = m;
+                top_s[row] = at;
+                if (split == 0 && row0 + row < w.nr) {
+                    RowRecord *rec = records + (size_t)hl * w.nr + row0 + row;
+                    rec->m = m;
+                    rec->top = at;
+                }
+            }
+        },
+        [&](float &m, int &top, int &last) {
+            m = row < w.nr ? m_s[row_l] : 0.f;
+            top = top_s[row_l];
+            last = row < w.nr ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;       // last token the row sees here
+        },
+        acc);
     if (part > 0 || row >= w.nr) return;
     const size_t out_row = ((size_t)hl * n_splits + split) * w.nr + row;
-    if (g == 0) {
+    if (lane < 16) part_l[out_row] = sum;
+    if (kNeedO) write_output<D>(part_o + out_row * D, acc, lane >> 4);
+}
+
+// ------------------------------------------------------------------------------------
+// Logits from digits, weights and P V in one kernel, where the call is long enough.  Grid: x = KV head, y = split of the piece, z = chunk
+// of 16 kRb rows.  A workgroup first forms the logits of its split (kept, for the scores), then, with the split's own largest logit as
+// reference and without the token that has it, their weights: the logits come back from the die's L2, nobody waits for the other
+// splits' maxima, and a launch is saved.  plain_merge brings the splits to one reference and puts their tokens back.
+// Lane = row + 16 g, registers = tokens 4 g .. 4 g + 3 of the 16 at hand.
+// ------------------------------------------------------------------------------------
+template <typename T, int D> constexpr int kSweepTile = sizeof(T) == 2 && D == 64 ? 128 : 64;      // tokens of a tile of keys: a piece per thread
+template <typename T, int D, int kRb>
+constexpr int kSweepBytes = std::max(2 * kLogitDigits<T> * kSweepTile<T, D> * D, kWeightBytes<T, D, kRb>);
+template <typename T, int D, int kRb, bool kNeedO, typename Lens>
+__global__ __launch_bounds__(kWeightThreads, 4) void digit_sweep(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, int N,
+                                                                 int W, int Hq, int Hkv, int ragged, Lens lens, Piece w, int split_len,
+                                                                 int n_splits, float *z, float4 *__restrict__ part_head,
+                                                                 float *__restrict__ part_o) {
+    constexpr int K = kLogitDigits<T>, kTok = kSweepTile<T, D>, kParts = 16 / kRb, kPart = kTok / kParts, kRows = 16 * kRb;
+    static_assert(kPart % 16 == 0, "whole blocks of 16 tokens");
+    __shared__ __attribute__((aligned(16))) char smem[kSweepBytes<T, D, kRb>];       // digits of two tiles, then tiles of values
+    __shared__ __attribute__((aligned(16))) int exponents[2][kTok];
+    __shared__ __attribute__((aligned(16))) uint8_t cut_s[2][kWeightThreads / 64];
+    __shared__ float2 best_s[kParts][kRows];
+    __shared__ float sum_s[kParts][kRows];
+    const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv, M = Hq / Hkv * W;
+    const int len = seq_len_of(lens, ragged, b, N);
+    const int split = blockIdx.y, t_begin = split * split_len, t_end = min(t_begin + split_len, len);
+    if (t_begin >= t_end) return;                            // uniform
+    const int row0 = blockIdx.z * kRows, blocks = (w.nr + 15) / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int rb = wave % kRb, part = wave / kRb, row = row0 + rb * 16 + (lane & 15);
+    float m = -INFINITY;
+    int at = kNoToken;
+    {
+        char (&digits)[2][K * kTok * D] = *(char (*)[2][K * kTok * D])smem;
+        const bool live = row0 / 16 + rb < blocks;           // uniform in the wave
+        const T *kg = k + (size_t)bg * N * D;
+        const __amdgpu_buffer_rsrc_t span = span_of(kg + (size_t)t_begin * D, (size_t)(t_end - t_begin) * D * sizeof(T));
+        TokenTile<T, D, kTok, kWeightThreads> next;
+        next.load(span, 0);
+        const T *q_row = q + ((size_t)b * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D;
+        RowDigits<K, D> rows;
+        bool rows_cut;
+        const int exponent = rows.template take<T>(q_row, lane >> 4, rows_cut) - 51 - 3;
+        const int last = min(len - W + (w.r0 + min(row, w.nr - 1)) % W, t_end - 1);                // last token the row sees here
+        const int least = __builtin_amdgcn_readfirstlane((int)row16_reduce<MinOp>((uint32_t)last));      // of the 16 rows
+        float *zp = z + z_block(w, hl, min(row0 / 16 + rb, blocks - 1), t_begin) + lane * 4;
+        next.template store_logit_digits<K>(digits[0], exponents[0], cut_s[0]);
+        if (t_begin + kTok < t_end) next.load(span, kTok);
+        int slot = 0;
+        for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
+            __syncthreads();                                 // this tile is in LDS, the one before it has been read
+            if (t0 + kTok < t_end) next.template store_logit_digits<K>(digits[slot ^ 1], exponents[slot ^ 1], cut_s[slot ^ 1]);
+            if (t0 + 2 * kTok < t_end) next.load(span, t0 - t_begin + 2 * kTok);
+            if (!live) continue;
+            double least_dot = kLeastDot<T>;
+            if (sizeof(T) == 4) {
+                const uint4 cut = *(const uint4 *)cut_s[slot];
+                if (rows_cut || __builtin_amdgcn_readfirstlane((int)(cut.x | cut.y | cut.z | cut.w)) != 0) least_dot = kLeastDotCut;     // uniform
+            }
+#pragma unroll 1
+            for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
+                if (t0 + p0 >= t_end) break;                 // uniform (what follows is another split's)
+                i32x4 acc[kLogitLevels];
+                level_sums<K, K, D, kTok>(rows, digits[slot], p0 + (lane & 15), lane >> 4, acc);
+                __builtin_amdgcn_sched_barrier(0);
+                const int first = t0 + p0 + 4 * (lane >> 4);     // register r has token first + r
+                const i32x4 ex = *(const i32x4 *)&exponents[slot][p0 + 4 * (lane >> 4)];
+                float x[4];
+                bool again = max(max(max(ex[0], ex[1]), ex[2]), ex[3]) + exponent >= kNoExponent / 2;
 #pragma unroll
-        for (int c = 1; c < kParts; ++c) sum += sum_s[c][row_l];
-        part_l[out_row] = sum;
-    }
-    if (!kNeedO) return;
+                for (int r = 0; r < 4; ++r) {
+                    double dot = join_seven<K>(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r], acc[5][r], acc[6][r]);
+                    again |= fabs(dot) < least_dot;              // (also of the zeros past the end)
+                    if (D == 128) dot *= 0.088388347648318440550 * 8.0;
+                    x[r] = __builtin_amdgcn_ldexpf((float)dot, ex[r] + exponent);
+                }
+                if (__builtin_amdgcn_ballot_w64(again) != 0ull) {            // uniform
+                    double dot[4];
+                    block_dots<T, D>(kg + (size_t)min(t0 + p0 + 4 * (lane & 3) + (lane >> 2 & 3), t_end - 1) * D, q_row, lane >> 4, dot);
 #pragma unroll
-    for (int d = 0; d < D / 16; ++d) {
-        float4 o = make_float4(acc[d][0], acc[d][1], acc[d][2], acc[d][3]);
+                    for (int r = 0; r < 4; ++r) x[r] = (float)(dot[r] * (1.0 / sqrt((double)D)));
+                }
+                auto improve = [&](const float (&y)[4]) {
+                    const float best = fmaxf(fmaxf(fmaxf(y[0], y[1]), y[2]), y[3]);
+                    if (__builtin_amdgcn_ballot_w64(best > m) == 0ull) return;       // uniform, usual once the maxima have settled
 #pragma unroll
-        for (int c = 0; c < kParts - 1; ++c) {
-            const float4 x = merge[(c * kRb * (D / 16) + d) * 64];
-            o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
+                    for (int r = 0; r < 4; ++r)                  // (tokens ascend: strict keeps the lowest)
+                        if (y[r] > m) { m = y[r]; at = first + r; }
+                };
+                if (t0 + p0 + 15 > least) {                      // uniform: not every row sees every token
+                    float y[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) y[r] = first + r <= last ? x[r] : -INFINITY;
+                    improve(y);
+                } else {
+                    improve(x);
+                }
+                *(float4 *)(zp + (t0 - t_begin + p0) * 16) = make_float4(x[0], x[1], x[2], x[3]);      // (room for whole tiles)
+            }
         }
-        *(float4 *)(part_o + out_row * D + d * 16 + 4 * g) = o;
     }
+    best_of_pair<16>(m, at);
+    best_of_pair<32>(m, at);
+    if (lane < 16) best_s[part][rb * 16 + lane] = make_float2(m, __int_as_float(at));
+    __syncthreads();                                         // (also: the logits are written, the digits have been read)
+    const int row_l = rb * 16 + (lane & 15);
+    float2 best = best_s[0][row_l];
+#pragma unroll
+    for (int c = 1; c < kParts; ++c) {
+        const float2 o = best_s[c][row_l];
+        if (o.x > best.x || (o.x == best.x && __float_as_int(o.y) < __float_as_int(best.y))) best = o;
+    }
+    // (a row that sees nothing here, or logits of -infinity alone: every weight is 0)
+    const float reference = best.x == -INFINITY ? 0.f : best.x;
+    const size_t z_head = z_block(w, hl, 0, w.s0);
+    f32x4 acc[D / 16];
+    const float sum = weights_pv<T, D, kRb, kNeedO>(
+        smem, sum_s, span_of(z + z_head, z_block(w, 1, 0, w.s0) * 4),
+        (int)(z_block(w, hl, min(row0 / 16 + rb, blocks - 1), t_begin) - z_head) * 4 + lane * 16,
+        span_of(v + ((size_t)bg * N + t_begin) * D, (size_t)(t_end - t_begin) * D * sizeof(T)), t_begin, t_end, rb, part, lane, []() {},
+        [&](float &ref, int &top, int &last) {
+            ref = row < w.nr ? reference : 0.f;
+            top = __float_as_int(best.y);
+            last = row < w.nr ? min(len - W + (w.r0 + row) % W, t_end - 1) : -1;       // last token the row sees here
+        },
+        acc);
+    if (part > 0 || row >= w.nr) return;
+    const size_t out_row = ((size_t)hl * n_splits + split) * w.nr + row;
+    if (lane < 16) part_head[out_row] = make_float4(best.x, sum, best.y, 0.f);
+    if (kNeedO) write_output<D>(part_o + out_row * D, acc, lane >> 4);
 }
 
 // ------------------------------------------------------------------------------------

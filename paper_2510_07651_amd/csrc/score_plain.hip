@@ -1,6 +1,6 @@
 // General scoring path: fp32 inputs, bf16 with head_dim 64, and anything pinned to it (obc_set_score_path).
-// Logits are accumulated in fp64 on the matrix cores, attention outputs in fp32 there, cross terms in fp64 or, beyond 32
-// window rows per KV head, in fixed point where that is as good (score_fixed.h).
+// Logits are accumulated in fp64 on the matrix cores, attention outputs in fp32 there, cross terms in fp64; calls with
+// more window rows per KV head form both from pieces on faster units where that is as good (score_fixed.h).
 //
 // Four kernels over a group of KV heads (Section 3 of the paper, then Eq. 4-6 summed over the window, Eq. 9, and the
 // query heads of the KV head, Appendix A.5):
@@ -26,9 +26,10 @@
 // fp64 matrix cores (a wave's 16 x 16 x 4 op occupies its SIMD's matrix core for 64 cycles, so operands from LDS, the
 // conversion of fp32 to fp64 and the exponentials ride in its shadow), then P V on the fp32 matrix cores (twice that rate).
 // The vector-ALU kernels this replaced took one fp64 multiply-add per element and lane with a block per query head.
-// Beyond 32 rows: see score_fixed.h.  Short sequences: launches, see short_partial.
+// More rows: see score_fixed.h, and sweeps_digits for which.  Short sequences: launches, see short_partial.
 // Sums run in a fixed order, so results are bit-reproducible.
 #include <algorithm>
+#include <climits>
 
 #include "internal.h"
 #include "wave_util.h"
@@ -41,11 +42,16 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 64;        // tokens per tile; each of the four waves owns 16 of them
 constexpr int kThreads = 256;    // 4 waves
-// Least tiles times 128-row chunks for digit_logits (score_fixed.h).
-constexpr int digit_tiles(int dtype, int d) { return dtype == OBC_F32 && d == 64 ? 1280 : 768; }
+constexpr int kPlainRows = 16;   // up to so many the kernels of this file take a call, beyond 32 those of score_fixed.h (sweeps_digits)
+// Rows of a workgroup of score_fixed.h: 64 where the last 128 would be half empty.
+constexpr int sweep_rows(int rows) { return (rows + 63) / 64 % 2 != 0 ? 64 : 128; }
 constexpr int kMaxRanges = 64;   // token ranges with a row maximum of their own, at most
 constexpr int kMaxSplits = 32;   // sequence splits of P V, at most
+constexpr int kSweepSplits = 64; // of digit_sweep
+constexpr int kMergeEach = 8;    // splits of a row that a wave of the merge has on the way together
 constexpr int kResident = 1024;  // workgroups the chip holds at four per CU: a launch is cut into about this many
+constexpr int kCus = 256;
+constexpr int kSweepOwn = 2;     // what a workgroup of digit_sweep takes beside its tiles (its rows' digits, its record), in tiles
 constexpr int kNoToken = 0x7fffffff;
 
 // What one launch works on: KV heads bg0 .. bg0 + gridDim.z - 1, their window rows r0 .. r0 + nr - 1 (of the G*W rows
@@ -55,7 +61,7 @@ struct Piece {
     int z_stride;                // floats between the logits of consecutive rows
 };
 
-// Constants of one row, written by plain_weights or fixed_weights (m, top) and plain_merge (the rest).
+// Constants of one row, written by plain_weights or fixed_weights (m, top) and plain_merge (the rest; all with digit_sweep).
 struct RowRecord {
     float m;                     // largest visible logit
     int top;                     // lowest token that attains it
@@ -410,38 +416,105 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
 #include "score_fixed.h"
 
 // ------------------------------------------------------------------------------------
-// Merge.  One wave per row, D / 64 consecutive elements per lane.  Grid: x = four rows of the piece, z = KV head.
-// The output is left in fp32, with kFixed also as bf16 pieces.
+// Merge.  `spread` waves per row, D / 64 consecutive elements per lane.  Grid: x = 4 / spread rows of the piece, z = KV head.
+// The output is left in fp32, with kFixed also as bf16 pieces.  kOwn: every split has its own reference and has left out a token of its
+// own (digit_sweep): the largest reference's split stays as it is, the others are brought to it and get their tokens back.
+// What bounds it: loads that wait for one another (heads, then the values that the heads name), each a few us from another die's
+// memory, so a wave asks for all of its splits at once.  Calls of 8 heads x 48 rows, 32 splits, us: a loop over the splits in one wave
+// 56.1, four waves with eight each 47.7; of 32 heads x 128 rows, 8 splits: one wave 49.2, four 54.0.
 // ------------------------------------------------------------------------------------
-template <typename T, int D, bool kNeedO, bool kFixed, typename Lens>
+template <typename T, int D, bool kNeedO, bool kFixed, bool kOwn, typename Lens>
 __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
-                                                        Piece w, int split_len, int n_splits,
-                                                        const float *__restrict__ part_l, const float *__restrict__ part_o,
-                                                        RowRecord *__restrict__ records, float *__restrict__ out,
-                                                        uint16_t *__restrict__ out_pieces) {
-    constexpr int kE = D / 64;
-    const int hl = blockIdx.z, bg = w.bg0 + hl, row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= w.nr) return;                                 // uniform over the wave
+                                                        Piece w, int split_len, int n_splits, int spread,
+                                                        const float *__restrict__ part_l, const float4 *__restrict__ part_head,
+                                                        const float *__restrict__ part_o, RowRecord *__restrict__ records,
+                                                        float *__restrict__ out, uint16_t *__restrict__ out_pieces) {
+    constexpr int kE = D / 64, kWaves = kThreads / 64, kEach = kMergeEach;
+    static_assert(kSweepSplits <= 64, "a split per lane");
+    __shared__ float o_s[kWaves - 1][D];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wave % spread, lane = threadIdx.x & 63;
+    const int hl = blockIdx.z, bg = w.bg0 + hl, row = min((int)blockIdx.x * (kWaves / spread) + wave / spread, w.nr - 1);
     const int len = seq_len_of(lens, ragged, bg / Hkv, N);
     const int live = (len + split_len - 1) / split_len;
     RowRecord *rec = records + (size_t)hl * w.nr + row;
-    const int top = min(rec->top, len - 1);                  // (logits that are not numbers have no largest one)
-    const float m = rec->m;
-    float vt[kE], o[kE];
+    auto part_row = [&](int s) { return ((size_t)hl * n_splits + s) * w.nr + row; };
+    float os[kEach][kE], o[kE];
+    auto load_outputs = [&](int s0) {
 #pragma unroll
-    for (int e = 0; e < kE; ++e) {
-        vt[e] = kNeedO ? load_as_float(v + ((size_t)bg * N + top) * D + lane * kE + e) : 0.f;
-        o[e] = 0.f;
-    }
-    float l = 0.f;
-#pragma unroll 8
-    for (int s = 0; s < live; ++s) {
-        const size_t at = ((size_t)hl * n_splits + s) * w.nr + row;
-        l += part_l[at];
+        for (int i = 0; i < kEach; ++i)
 #pragma unroll
-        for (int e = 0; e < kE; ++e)
-            if (kNeedO) o[e] += part_o[at * D + lane * kE + e];
+            for (int e = 0; e < kE; ++e) os[i][e] = part_o[part_row(min(s0 + part + i * spread, live - 1)) * D + lane * kE + e];
+    };
+    const T *vl = v + (size_t)bg * N * D + lane * kE;        // this lane's elements of a value
+    int top, best = 0, tok = 0;
+    float m, l, wt = 1.f, vt[kE];
+    bool back = false;                                       // this lane's split gets its token back
+    auto load_top = [&]() {
+#pragma unroll
+        for (int e = 0; e < kE; ++e) vt[e] = kNeedO ? load_as_float(vl + (size_t)top * D + e) : 0.f;
+    };
+    // (what has an address is on the way before the first of it is waited for)
+    if constexpr (kOwn) {
+        const float4 h = lane < live ? part_head[part_row(lane)] : make_float4(-INFINITY, 0.f, __int_as_float(kNoToken), 0.f);
+        if (kNeedO) load_outputs(0);
+        m = wave_reduce<MaxOp>(h.x);
+        best = __ffsll(__ballot(h.x == m)) - 1;              // the first split attaining the maximum holds the lowest such token
+        tok = min(__float_as_int(h.z), len - 1);             // (logits that are not numbers have no largest one)
+        top = __builtin_amdgcn_readlane(tok, best);
+        load_top();
+        // (a split without a visible logit above -infinity weighs nothing: exp(-inf); what is not a number stays that)
+        wt = lane == best ? 1.f : lane < live ? exp_nonpositive(h.x - m) : 0.f;
+        back = lane != best && h.x != -INFINITY;
+        l = wave_reduce<SumOp>(lane < live ? fmaf(wt, h.y, back ? wt : 0.f) : 0.f);
+    } else {
+        top = min(rec->top, len - 1);
+        m = rec->m;
+        l = lane < live ? part_l[part_row(lane)] : 0.f;
+        if (kNeedO) load_outputs(0);
+        load_top();
+        for (int s = lane + 64; s < live; s += 64) l += part_l[part_row(s)];       // (a row's tokens taken in segments)
+        l = wave_reduce<SumOp>(l);
     }
+#pragma unroll
+    for (int e = 0; e < kE; ++e) o[e] = 0.f;
+    if (kNeedO) {
+        for (int s0 = 0; s0 < live; s0 += kEach * spread) {
+            if (s0 > 0) load_outputs(s0);
+            if constexpr (kOwn) {
+                float vs[kEach][kE];
+#pragma unroll
+                for (int i = 0; i < kEach; ++i) {
+                    const int t = __builtin_amdgcn_readlane(tok, min(s0 + part + i * spread, live - 1));
+#pragma unroll
+                    for (int e = 0; e < kE; ++e) vs[i][e] = load_as_float(vl + (size_t)t * D + e);
+                }
+#pragma unroll
+                for (int i = 0; i < kEach; ++i) {
+                    const int s = min(s0 + part + i * spread, 63);
+                    const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wt), s));
+                    const bool again = __builtin_amdgcn_readlane((int)back, s) != 0;
+#pragma unroll
+                    for (int e = 0; e < kE; ++e) o[e] = s0 + part + i * spread < live ? fmaf(ws, os[i][e] + (again ? vs[i][e] : 0.f), o[e]) : o[e];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kEach; ++i)
+#pragma unroll
+                    for (int e = 0; e < kE; ++e) o[e] += s0 + part + i * spread < live ? os[i][e] : 0.f;
+            }
+        }
+        if (spread > 1) {                                    // uniform
+            if (part > 0)
+#pragma unroll
+                for (int e = 0; e < kE; ++e) o_s[wave - 1][lane * kE + e] = o[e];
+            __syncthreads();
+            if (part == 0)
+                for (int i = 0; i < spread - 1; ++i)
+#pragma unroll
+                    for (int e = 0; e < kE; ++e) o[e] += o_s[wave + i][lane * kE + e];
+        }
+    }
+    if (part > 0) return;
     const float frac = l / (1.0f + l);                       // 1 - A_{i,top}; the top token's own weight is exp(0) = 1
     const float inv = l > 0.f ? 1.0f / l : 0.f;
     double oo = 0.0, dk = 0.0, dj = 0.0;
@@ -474,6 +547,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
         dj = wave_reduce<SumOp>(dj);
     }
     if (lane == 0) {
+        if (kOwn) { rec->m = m; rec->top = top; }
         rec->last = len - W + (w.r0 + row) % W;
         rec->inv_l = 1.0f / (1.0f + l);
         rec->top_dk = (float)dk;
@@ -847,7 +921,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     float2 *best = (float2 *)(base + ws.pl_best);
     RowRecord *rec = (RowRecord *)(base + ws.pl_records);
     uint16_t *o_pieces = (uint16_t *)(base + ws.pl_o_pieces);
-    // More than 32 rows: score_fixed.h, 64 or 128 of them per workgroup.
+    // score_fixed.h, 64 or 128 rows per workgroup.
     constexpr bool fixed = kRt == 4 || kRt == 8;
     constexpr int kRb = kRt == 8 ? 8 : 4;
     const bool need_o = a.variant == OBC_KEY || a.variant == OBC_JOINT || a.variant == OBC_ALL;
@@ -858,6 +932,9 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     const int mask = one_piece ? a.stage_mask : a.stage_mask & OBC_STAGE_SWEEP2 ? (int)OBC_STAGE_ALL
                      : a.stage_mask & OBC_STAGE_COMBINE ? OBC_STAGE_SWEEP1 | OBC_STAGE_COMBINE : a.stage_mask;
     const int segs = (a.N + ws.pl_seg - 1) / ws.pl_seg;
+    const bool with_digits = fixed && ws.pl_digits;
+    constexpr bool kOwnOnly = fixed && sizeof(T) == 2;       // (sweeps_digits)
+    if (kOwnOnly && !with_digits) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     for (int bg0 = 0; bg0 < BH; bg0 += ws.pl_heads)
         for (int r0 = 0; r0 < M; r0 += ws.pl_rows) {
@@ -868,53 +945,61 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
             const unsigned row_chunks = (w.nr + 16 * kRb - 1) / (16 * kRb);         // (score_fixed.h)
             auto logits = [&]() {
                 const unsigned ranges = (w.s1 - w.s0 + ws.pl_range - 1) / ws.pl_range;
-                if constexpr (fixed) {
-                    if (ws.pl_digit_logits)
-                        digit_logits<T, D, kRb><<<dim3(heads, ranges, row_chunks), dim3(kFixedThreads), 0, stream>>>(
-                            q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
-                    else
-                        blocked_logits<T, D><<<dim3(heads, ranges, (w.nr + kLogitRows - 1) / kLogitRows), dim3(kThreads), 0, stream>>>(
-                            q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
-                } else
+                if constexpr (!fixed)
                     plain_logits<T, D, kRt><<<dim3(ranges, chunks, heads), dim3(kThreads), 0, stream>>>(
+                        q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
+                else if constexpr (!kOwnOnly)
+                    blocked_logits<T, D><<<dim3(heads, ranges, (w.nr + kLogitRows - 1) / kLogitRows), dim3(kThreads), 0, stream>>>(
                         q, k, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, z, best);
                 e = hipGetLastError();
                 return e == hipSuccess;
             };
+            auto weights = [&](auto with_output) {           // (with digits: from the keys on)
+                constexpr bool kNeedO = decltype(with_output)::value;
+                const unsigned splits = (w.s1 - w.s0 + ws.pl_split - 1) / ws.pl_split;
+                if constexpr (fixed)
+                    if (with_digits)
+                        digit_sweep<T, D, kRb, kNeedO><<<dim3(heads, splits, row_chunks), dim3(kWeightThreads), 0, stream>>>(
+                            q, k, v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_split, ws.pl_splits, z, (float4 *)part_l, part_o);
+                if constexpr (!fixed)
+                    plain_weights<T, D, kRt, kNeedO><<<dim3(splits, chunks, heads), dim3(kThreads), 0, stream>>>(
+                        v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z, best, rec,
+                        part_l, part_o);
+                else if constexpr (!kOwnOnly)
+                    if (!with_digits)
+                        fixed_weights<T, D, kRb, kNeedO><<<dim3(heads, splits, row_chunks), dim3(kWeightThreads), 0, stream>>>(
+                            v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z, best, rec,
+                            part_l, part_o);
+            };
             if (mask & OBC_STAGE_SWEEP1) {
-                for (int i = 0; i < segs; ++i) {             // every range's maximum first
+                for (int i = 0; i < segs && !with_digits; ++i) {               // every range's maximum first
                     segment(i);
                     if (!logits()) return e;
                 }
                 for (int i = 0; i < segs; ++i) {
                     segment(i);
                     if (segs > 1 && !logits()) return e;
-                    const dim3 grid((w.s1 - w.s0 + ws.pl_split - 1) / ws.pl_split, chunks, heads);
-                    auto weights = [&](auto with_output) {
-                        constexpr bool kNeedO = decltype(with_output)::value;
-                        if constexpr (fixed)
-                            fixed_weights<T, D, kRb, kNeedO><<<dim3(heads, grid.x, row_chunks), dim3(kWeightThreads), 0, stream>>>(
-                                v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
-                                best, rec, part_l, part_o);
-                        else
-                            plain_weights<T, D, kRt, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
-                                v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z,
-                                best, rec, part_l, part_o);
-                    };
                     if (need_o) weights(std::true_type());
                     else weights(std::false_type());
                     if ((e = hipGetLastError()) != hipSuccess) return e;
                 }
             }
             if (mask & OBC_STAGE_COMBINE) {
-                const dim3 grid((w.nr + 3) / 4, 1, heads);
-                auto merge = [&](auto with_output) {
+                const int spread = ws.pl_splits <= kMergeEach ? 1 : ws.pl_splits <= 2 * kMergeEach ? 2 : 4;
+                const dim3 grid((w.nr * spread + 3) / 4, 1, heads);
+                auto merge = [&](auto with_output, auto own) {
                     constexpr bool kNeedO = decltype(with_output)::value;
-                    plain_merge<T, D, kNeedO, kNeedO && fixed><<<grid, dim3(kThreads), 0, stream>>>(
-                        v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split, ws.pl_splits, part_l, part_o, rec, out, o_pieces);
+                    plain_merge<T, D, kNeedO, kNeedO && fixed, decltype(own)::value><<<grid, dim3(kThreads), 0, stream>>>(
+                        v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split, ws.pl_splits, spread, part_l, (const float4 *)part_l, part_o, rec, out, o_pieces);
                 };
-                if (need_o) merge(std::true_type());
-                else merge(std::false_type());
+                auto merge_own = [&](auto own) {
+                    if (need_o) merge(std::true_type(), own);
+                    else merge(std::false_type(), own);
+                };
+                if constexpr (fixed)
+                    if (with_digits) merge_own(std::true_type());
+                if constexpr (!kOwnOnly)
+                    if (!with_digits) merge_own(std::false_type());
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
             if (!(mask & OBC_STAGE_SWEEP2)) continue;
@@ -958,45 +1043,90 @@ hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hi
     // 16-row tiles of a workgroup.
     const int rows = std::min(ws.pl_rows, a.G * a.W);
     if (rows <= 16) return run<T, D, 1>(a, ws, base, stream);
-    if (rows <= 32) return run<T, D, 2>(a, ws, base, stream);
-    if ((rows + 63) / 64 % 2 != 0) return run<T, D, 4>(a, ws, base, stream);      // (the last 128 would be half empty)
+    if (rows <= 32 && !(ws.pl_digits && rows > kPlainRows)) return run<T, D, 2>(a, ws, base, stream);
+    if (sweep_rows(rows) == 64) return run<T, D, 4>(a, ws, base, stream);
     return run<T, D, 8>(a, ws, base, stream);
 }
 
 }  // namespace
 
+// Which calls digit_sweep takes.  Whole calls, joint, us, without / with it:
+//   bf16, d = 64       8 heads x 32 rows x 64 tokens 18.3 / 17.2, x 1500 23.3 / 19.0, x 8000 40.5 / 30.2; 4 heads x 63 rows x 200 18.8 / 18.1
+//   fp32, over 32 rows, the tiles (all heads, in 128-row chunks) against d = 128 and d = 64
+//     40   2 heads x 128 rows x 1300   27 / 29   23.0 / 23.3        72   8 heads x 128 rows x  513   32.0 / 33.1   25.6 / 25.1
+//     80   4 heads x  64 rows x  600   25.4 / 27.7   20.6 / 20.9   136   8 heads x 128 rows x 1025   37.4 / 36.1   29.4 / 27.6
+//    528  32 heads x  33 rows x 1000   42.1 / 38.7   28.3 / 27.0  2000   8 heads x 128 rows x 16001 (d = 64) 117 / 105
+//   fp32, 17 to 32 rows
+//          8 heads x  32 rows x   700   27.0 / 26.6   21.2 / 20.3   1 head  x  32 rows x 20000   66.7 / 52.8   50.5 / 36.0
+//          8 heads x  32 rows x  1500   28.1 / 28.6   23.4 / 20.7   8 heads x  32 rows x 30000   166 / 154   110 / 102
+//         16 heads x  20 rows x  8000   86.7 / 87.1   56.5 / 59.3  32 heads x  32 rows x  8000   156 / 156   98 / 102
+// so bf16 always, fp32 from 128 tiles up; of up to 32 fp32 rows, which leave half of its waves without any, only few heads (the
+// kernels for up to 32 rows need many to fill the chip).  (The line counts every head of the call, so which kernel forms a
+// sequence's logits, and with it their last bit now and then, depends on the batch.)
+int sweeps_digits(int dtype, int heads, int M, long long tiles) {
+    if (M <= kPlainRows) return 0;
+    if (dtype != OBC_F32) return 1;
+    return (M > 32 || heads <= 8) && tiles * heads * ((M + 127) / 128) >= 128;
+}
+
 // Pieces.  `cap` bounds the workspace: as many KV heads at a time as fit (which leaves every sum as it is), then as many
-// rows of one head, then as many tokens (which does not).  Within it a launch should fill the chip once (kResident), so that
-// no workgroup pays a prologue more than needed and no last wave of workgroups is nearly empty; a row has at most kMaxRanges
+// rows of one head, then as many tokens (which does not).  Within it a launch should fill the chip once (kResident; whole turns of
+// kCus workgroups for digit_sweep), so that no workgroup pays a prologue more than needed and no last turn is nearly empty; a row has at most kMaxRanges
 // maxima, which every workgroup of the weight kernel reads.
 void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv, M = Hq / Hkv * W;
-    const bool fixed = M > 32;
     const long long tiles = (N + kTile - 1) / kTile, logit_chunks = (long long)BH * ((M + 31) / 32);
+    ws->pl_digits = sweeps_digits(dtype, BH, M, tiles);
+    const bool fixed = M > 32 || ws->pl_digits;
     const long long chunks = fixed ? (long long)BH * ((M + 127) / 128) : logit_chunks, resident = fixed ? kResident / 2 : kResident;
-    ws->pl_digit_logits = fixed && tiles * chunks >= digit_tiles(dtype, d) ? 1 : 0;
-    const long long logit_tiles = ws->pl_digit_logits ? (tiles * chunks + resident - 1) / resident : (tiles * logit_chunks + kResident - 1) / kResident;
+    const long long logit_tiles = (tiles * logit_chunks + kResident - 1) / kResident;
     const long long range_tiles = std::max((tiles + kMaxRanges - 1) / kMaxRanges, logit_tiles);
     ws->pl_range = (int)(std::min(range_tiles, tiles) * kTile);
     ws->pl_ranges = (N + ws->pl_range - 1) / ws->pl_range;
-    const long long splits = std::max<long long>(1, std::min<long long>(std::min<long long>(kMaxSplits, tiles), (resident / 2 + chunks - 1) / chunks));
-    ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
-    ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
-    auto row_bytes = [&]() {                                 // of one row, beside its logits
-        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 10 : 4) + (size_t)ws->pl_splits * (d + 1) * 4;
+    auto split_in = [&](long long splits) {
+        splits = std::max<long long>(1, std::min<long long>(splits, tiles));
+        ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
+        ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
     };
-    const size_t per_row = row_bytes() + (size_t)align_up(N, kTile) * 4;
-    cap -= 7 * 256;                                          // alignment of the buffers
+    // digit_sweep has a workgroup per CU: as many splits as make whole turns of the chip of what a launch takes.
+    auto split_turns = [&](int heads) {
+        const long long workgroups = (long long)heads * ((M + sweep_rows(M) - 1) / sweep_rows(M));
+        long long best = 1, least = LLONG_MAX;
+        for (long long s = 1; s <= std::min<long long>(kSweepSplits, tiles); ++s) {
+            const long long time = (workgroups * s + kCus - 1) / kCus * ((tiles + s - 1) / s + kSweepOwn);
+            if (time < least) { least = time; best = s; }
+        }
+        split_in(best);
+    };
+    split_in(std::min<long long>(kMaxSplits, (resident / 2 + chunks - 1) / chunks));
+    auto row_bytes = [&]() {                                 // of one row, beside its logits
+        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 10 : 4) + (size_t)ws->pl_splits * (d + (ws->pl_digits ? 4 : 1)) * 4;
+    };
+    auto per_row = [&]() { return row_bytes() + (size_t)align_up(N, kTile) * 4; };
+    const size_t alignment = 7 * 256;                        // of the buffers
+    // As many heads as fit, in as many launches of about the same size.
+    auto heads_in = [&](size_t bytes) {
+        const int heads = (int)std::min<size_t>(BH, (bytes - alignment) / (per_row() * align_up(M, 16)));
+        const int launches = heads > 0 ? (BH + heads - 1) / heads : 0;
+        return heads > 0 ? (BH + launches - 1) / launches : 0;
+    };
+    if (ws->pl_digits) {                                     // of what a launch takes in the default workspace: the same sums in any
+        int heads = heads_in(kPlainWorkspace);
+        do split_turns(std::max(heads, 1));
+        while (heads_in(kPlainWorkspace) < heads && --heads > 0);              // (more splits need more room)
+    }
     ws->pl_seg = N;
     ws->pl_rows = M;
-    ws->pl_heads = (int)std::min<size_t>(BH, cap / (per_row * align_up(M, 16)));
+    ws->pl_heads = heads_in(cap);
+    cap -= alignment;
     if (ws->pl_heads < 1) {
         ws->pl_heads = 1;
-        ws->pl_rows = (int)std::min<size_t>(M, cap / per_row / 16 * 16);
+        ws->pl_rows = (int)std::min<size_t>(M, cap / per_row() / 16 * 16);
         if (ws->pl_rows < 1) {
             // One tile of rows at a time and as many tokens as fit, in whole splits (here also the ranges).
             ws->pl_rows = std::min(M, 16);
+            ws->pl_digits = 0;                               // (one launch takes a row's whole sequence)
             ws->pl_split = ws->pl_range = (int)align_up((N + 1023) / 1024, kTile);
             ws->pl_splits = ws->pl_ranges = (N + ws->pl_split - 1) / ws->pl_split;
             const size_t room = cap / ws->pl_rows / 4, taken = row_bytes() / 4;
@@ -1028,7 +1158,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t c
     take(&ws->pl_records, rows * sizeof(RowRecord));
     take(&ws->pl_out, rows * d * 4);
     if (fixed) take(&ws->pl_o_pieces, rows * d * 6);
-    take(&ws->pl_part_l, rows * ws->pl_splits * 4);
+    take(&ws->pl_part_l, rows * ws->pl_splits * (ws->pl_digits ? sizeof(float4) : sizeof(float)));
     take(&ws->pl_part_o, rows * ws->pl_splits * d * 4);
 }
 

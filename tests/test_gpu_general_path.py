@@ -29,6 +29,33 @@ def _inputs(dtype, d, G, W, N, B, Hkv, seed):
     return q, k, v
 
 
+# (dtype, d, Hkv, G, W, N, lens) where a sequence is swept in splits with a reference each: one token more than a split's tiles and
+# one short of them, as many splits as there are and a single one, sequences that end splits early, windows as long as a split (whose
+# first rows see nothing of the last one), rows that fill a workgroup's row blocks in part, heads in two launches
+SPLITS = [("bf16", 64, 1, 1, 17, 17, None), ("bf16", 64, 1, 4, 64, 4097, None), ("bf16", 64, 2, 4, 16, 4095, [4095, 130]),
+          ("bf16", 64, 9, 5, 7, 705, None), ("bf16", 128, 1, 4, 33, 8191, None), ("fp32", 128, 1, 3, 44, 8193, [8193, 129]),
+          ("fp32", 64, 8, 4, 5, 1089, None), ("fp32", 128, 3, 3, 43, 2999, None), ("fp32", 64, 2, 3, 63, 4161, [65, 4161]),
+          ("fp32", 128, 40, 4, 32, 4999, None)]
+
+
+@pytest.mark.parametrize("case", SPLITS, ids=lambda c: "%s_d%d_%d_%dx%d_%d" % c[:6])
+def test_splits_with_references_of_their_own_match_oracle(case, score_path):
+    """The largest logit of a row stands in several splits at once (equal keys, unequal values), for half of the heads with most of
+    the row's weight."""
+    dtype, d, Hkv, G, W, N, lens = case
+    B = 1 if lens is None else len(lens)
+    q, k, v = _inputs(dtype, d, G, W, N, B, Hkv, 47)
+    k[:, ::2, 0] *= 4
+    for at in (N // 3, N // 2, N - W):
+        k[:, :, at] = k[:, :, 0]
+    ref = oracle.score(q, k, v, seq_lens=lens)
+    score_path("plain")
+    got = obc.obc_score(q.cuda(), k.cuda(), v.cuda(), "all", seq_lens=lens).cpu().numpy()
+    for i, name in enumerate(("value", "key", "joint")):
+        err, where = score_error(got[i], ref[i], min(lens or [N]) // 8, lens, TOL["fp32"])
+        assert err <= TOL["fp32"], (name, err, where)
+
+
 @pytest.mark.parametrize("case", EDGES, ids=lambda c: "%s_d%d_%dx%d_%d" % c[:5])
 def test_tile_edges_match_oracle(case, score_path):
     dtype, d, G, W, N, lens = case

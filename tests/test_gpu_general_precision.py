@@ -142,8 +142,7 @@ def _apart(q, k, binades):
     return _scaled(q, slice(0, 1), binades), _scaled(k, slice(0, 1), -binades)
 
 
-# Long enough for digits (768 tiles of 64 tokens times chunks of 128 rows over both heads, 1280 for fp32 with d = 64), each
-# followed by shapes that are not.
+# Sequences of many splits and of few, with rows in one chunk and in several; the last one is too short for digits.
 DIGIT_SHAPES = [("fp32", 128, 3, 43, 12301), ("fp32", 64, 1, 64, 40991), ("fp32", 128, 3, 43, 8131), ("fp32", 64, 1, 64, 16332),
                 ("bf16", 64, 5, 40, 12303), ("bf16", 64, 1, 33, 24595), ("bf16", 64, 5, 40, 8145), ("bf16", 64, 1, 33, 16321),
                 ("bf16", 128, 1, 40, 24597), ("bf16", 128, 1, 40, 16323), ("fp32", 128, 3, 43, 129)]
