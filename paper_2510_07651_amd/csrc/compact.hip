@@ -166,24 +166,16 @@ __global__ __launch_bounds__(256) void evict_pick(const float *__restrict__ scor
 
 // Closes the gap the evicted token leaves: row j >= e takes row j + 1, for K, V (blockIdx.y = 0, 1; one 64-byte column
 // slice per workgroup, rows read chunk by chunk before they are overwritten, as in move_rows_in_place) and for the
-// running scores (blockIdx.y = 2), whose slots from len - 1 on are cleared.  Every wave takes the minimum of the head's
-// candidates itself: one memory round trip instead of a kernel of its own.  The head varies fastest in the grid, as in the
-// decode kernels: its workgroups then share an XCD with those that last touched its rows where the head count allows.
+// running scores (blockIdx.y = 2), whose slots from len - 1 on are cleared.
 template <typename Lens>
 __global__ __launch_bounds__(kMoveThreads) void evict_shift(uint4 *__restrict__ k, uint4 *__restrict__ v,
                                                             float *__restrict__ scores,
                                                             int32_t *__restrict__ evicted,
-                                                            const unsigned long long *__restrict__ lowest, int n_lowest,
-                                                            int N, int Hkv, int ragged, Lens lens, int row_vec) {
+                                                            const unsigned long long *__restrict__ lowest, int N, int Hkv, int ragged, Lens lens, int row_vec) {
     const size_t bg = blockIdx.x;
     const int len = seq_len_of(lens, ragged, (int)(bg / Hkv), N);
     if (blockIdx.y == 2 && blockIdx.z != 0) return;
-    unsigned long long low = ~0ull;
-    for (int i = threadIdx.x & 63; i < n_lowest; i += 64) {
-        const unsigned long long c = lowest[bg * n_lowest + i];
-        low = c < low ? c : low;
-    }
-    const int e = evict_candidate_token(wave_min(low));
+    const int e = evict_candidate_token(lowest[bg]);
     if (evicted && blockIdx.y == 2 && threadIdx.x == 0) evicted[bg] = e;
     const int budget = len - 1;                      // rows that remain
     if (e < 0 || e >= len) return;                   // (cannot happen: the candidates are live tokens)
@@ -226,6 +218,84 @@ __global__ __launch_bounds__(kMoveThreads) void evict_shift(uint4 *__restrict__ 
     }
 }
 
+// The same after the decode kernels, in pieces of kEvictPiece words: workgroups of whole consecutive rows, as many as there are
+// pieces, each of which finds the first row behind its own among the edges the scoring kernels have put aside (EvictEdges).  The
+// rows are asked for before the evicted token is known, so that they and the candidates take one memory round trip.
+// Bound by that trip and the launch.  A column slice of 64 bytes per workgroup, as in evict_shift, was walked chunk by chunk.  A step
+// of 8 heads, G = 4, us, with that, and with pieces on 256, 512 and 1024 threads: d = 128, 1600 tokens 16.8, 16.6, 16.1, 16.3; 4096
+// tokens 24.3, 22.0, 21.7, 23.2; d = 64, 4096 tokens 19.4, 17.0, 16.5, 17.7.
+// (The head varies fastest in the grid, as in the decode kernels: its workgroups then share an XCD with those that last touched
+// its rows where the head count allows.)
+constexpr int kPieceThreads = 512;
+constexpr int kPieceOwn = kEvictPiece / kPieceThreads;
+
+template <typename Lens>
+__global__ __launch_bounds__(kPieceThreads) void evict_pieces(uint4 *__restrict__ k, uint4 *__restrict__ v, float *__restrict__ scores,
+                                                              int32_t *__restrict__ evicted,
+                                                              const unsigned long long *__restrict__ lowest, int n_lowest,
+                                                              EvictEdges edges, int heads, int N, int Hkv, int ragged, Lens lens,
+                                                              int row_vec) {
+    __shared__ unsigned long long low_w[kPieceThreads / 64];
+    const int bg = blockIdx.x % heads, piece = blockIdx.x / heads, tid = threadIdx.x;
+    const int row_pieces = evict_row_pieces(N, row_vec * 8);
+    const int len = seq_len_of(lens, ragged, bg / Hkv, N), budget = len - 1;     // rows that remain
+    unsigned long long low = ~0ull;
+    for (int i = tid; i < n_lowest; i += kPieceThreads) {
+        const unsigned long long c = lowest[(size_t)bg * n_lowest + i];
+        low = c < low ? c : low;
+    }
+    // The lowest candidate of the head; ends at a barrier behind which everything read so far has arrived.
+    auto evicted_token = [&]() {
+        low = wave_min(low);
+        if ((tid & 63) == 0) low_w[tid >> 6] = low;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kPieceThreads / 64; ++w) low = low_w[w] < low ? low_w[w] : low;
+        return evict_candidate_token(low);
+    };
+    if (piece < 2 * row_pieces) {
+        const int of_v = piece >= row_pieces, s = piece - of_v * row_pieces;
+        const int base = s * kEvictPiece, end = budget * row_vec;
+        if (base >= end) return;                                 // uniform
+        uint4 *rows = (of_v ? v : k) + (size_t)bg * N * row_vec;
+        const uint4 *edge = edges.rows + (((size_t)bg * 2 + of_v) * row_pieces + s + 1) * row_vec;    // (not read behind the last row)
+        uint4 x[kPieceOwn];
+#pragma unroll
+        for (int u = 0; u < kPieceOwn; ++u) {
+            const int at = u * kPieceThreads + tid, from = at + row_vec;     // (rows of at most kPieceThreads words: 8 or 16)
+            const uint4 *src = u + 1 < kPieceOwn || from < kEvictPiece ? rows + base + from : edge + (from - kEvictPiece);
+            x[u] = make_uint4(0, 0, 0, 0);
+            if (base + at < end) x[u] = *src;
+        }
+        const int e = evicted_token();
+        if (e < 0) return;                                       // (cannot happen: the candidates are live tokens)
+#pragma unroll
+        for (int u = 0; u < kPieceOwn; ++u) {
+            const int to = base + u * kPieceThreads + tid;
+            if (to >= e * row_vec && to < end) rows[to] = x[u];
+        }
+        return;
+    }
+    const int s = piece - 2 * row_pieces, base = s * kEvictPiece;
+    float *out = scores + (size_t)bg * N, x[kPieceOwn];
+#pragma unroll
+    for (int u = 0; u < kPieceOwn; ++u) {
+        const int at = u * kPieceThreads + tid;
+        x[u] = 0.f;
+        const float *src = at + 1 < kEvictPiece ? out + base + at + 1 : edges.scores + (size_t)bg * evict_score_pieces(N) + s + 1;
+        if (base + at < budget) x[u] = *src;
+    }
+    const int e = evicted_token();
+    if (evicted && s == 0 && tid == 0) evicted[bg] = e;
+    if (e < 0) return;
+#pragma unroll
+    for (int u = 0; u < kPieceOwn; ++u) {
+        const int to = base + u * kPieceThreads + tid;
+        if (to >= e && to < N) out[to] = x[u];
+    }
+}
+
 // Measurement hook: reads `n_vec` 16-byte words once with 128-bit loads and folds them
 // into one word per thread (so the loads cannot be dropped).  Its duration gives the box's
 // own streaming-read ceiling, the practical denominator next to the nominal HBM peak.
@@ -263,20 +333,26 @@ hipError_t launch_compact_in_place(void *k, void *v, float *scores, const int32_
     return hipGetLastError();
 }
 
-hipError_t launch_evict_one(void *k, void *v, float *scores, int32_t *evicted, unsigned long long *lowest, int n_lowest,
-                            int B, int Hkv, int N, int ragged, const SeqLens &lens, int first, int tail, int row_bytes,
-                            hipStream_t stream) {
+hipError_t launch_evict_one(void *k, void *v, float *scores, int32_t *evicted, unsigned long long *lowest, int B, int Hkv, int N,
+                            int ragged, const SeqLens &lens, int first, int tail, int row_bytes, hipStream_t stream) {
     return with_lens(ragged, B, lens, [&](const auto &few) {
-        if (n_lowest == 0) {
-            evict_pick<<<dim3(B * Hkv), dim3(256), 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, lowest);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            n_lowest = 1;
-        }
+        evict_pick<<<dim3(B * Hkv), dim3(256), 0, stream>>>(scores, N, Hkv, ragged, few, first, tail, lowest);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
         const int row_vec = row_bytes / 16;
         const dim3 grid(B * Hkv, 3, (row_vec + 3) / 4);
-        evict_shift<<<grid, dim3(kMoveThreads), 0, stream>>>((uint4 *)k, (uint4 *)v, scores, evicted, lowest, n_lowest, N, Hkv,
-                                                             ragged, few, row_vec);
+        evict_shift<<<grid, dim3(kMoveThreads), 0, stream>>>((uint4 *)k, (uint4 *)v, scores, evicted, lowest, N, Hkv, ragged, few, row_vec);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_evict_pieces(void *k, void *v, float *scores, int32_t *evicted, const unsigned long long *lowest, int n_lowest,
+                               const EvictEdges &edges, int B, int Hkv, int N, int ragged, const SeqLens &lens, int row_bytes,
+                               hipStream_t stream) {
+    const int heads = B * Hkv;
+    return with_lens(ragged, B, lens, [&](const auto &few) {
+        evict_pieces<<<dim3((unsigned)heads * (2 * evict_row_pieces(N, row_bytes / 2) + evict_score_pieces(N))), dim3(kPieceThreads), 0, stream>>>(
+            (uint4 *)k, (uint4 *)v, scores, evicted, lowest, n_lowest, edges, heads, N, Hkv, ragged, few, row_bytes / 16);
         return hipGetLastError();
     });
 }

@@ -27,6 +27,18 @@ inline hipError_t with_lens(int ragged, int B, const SeqLens &lens, Launch &&lau
     return launch(few);
 }
 
+// An eviction step closes the gap in pieces of 32 KB of rows and of 2048 scores, each by a workgroup of its own.  The last row
+// of a piece moves up from the first place of the next one, which that one's workgroup overwrites: the scoring kernels
+// put those rows and scores aside.
+constexpr int kEvictPiece = 2048;     // 16-byte words of K or V, scores
+struct EvictEdges {
+    uint4 *rows;                      // [B*Hkv][K, V][evict_row_pieces][row]: rows that begin a piece
+    float *scores;                    // [B*Hkv][evict_score_pieces]: scores that do
+};
+__host__ __device__ constexpr int evict_piece_rows(int d) { return kEvictPiece / (d / 8); }        // (bf16)
+__host__ __device__ inline int evict_row_pieces(int N, int d) { return (N + evict_piece_rows(d) - 1) / evict_piece_rows(d); }
+__host__ __device__ inline int evict_score_pieces(int N) { return (N + kEvictPiece - 1) / kEvictPiece; }
+
 struct ScoreArgs {
     const void *q, *k, *v;
     float *scores;
@@ -38,6 +50,7 @@ struct ScoreArgs {
     int accumulate;   // 1: add to the scores already in `scores` (positions beyond the true length untouched)
     int find_lowest;  // 1 (decode path only): every wave reports its lowest-scored token among evict_first <= p < len - evict_tail
     int evict_first, evict_tail;
+    EvictEdges edges; // with find_lowest: what the decode kernels leave for launch_evict_pieces
     SeqLens lens;     // valid for b < B when ragged
 };
 
@@ -82,6 +95,8 @@ struct ScoreWorkspace {
     size_t dec_vec;    // float [B*Hkv*dec_splits*dec_rows*2d]
     size_t dec_lowest; // uint64 [B*Hkv*dec_lowest_per_head]  evict_candidates of the scoring kernel's waves
     int dec_lowest_per_head;
+    size_t dec_edges, dec_edge_scores;   // EvictEdges, last: a call that evicts nothing does without them
+    size_t score_need; // bytes such a call needs
     size_t dec_final;  // float [B*Hkv*dec_rows*(2d+4)]  merged row records
     int use_decode;    // 1: decode path (takes precedence over the other two)
     int dec_rows;      // query heads per KV head, padded to 1, 2, 4 or 8
@@ -133,11 +148,13 @@ hipError_t launch_compact_in_place(void *k, void *v, float *scores, const int32_
                                    int budget, int row_bytes, hipStream_t stream);
 // Evict-one of a decoding step: the lowest-scored token of each (sequence, KV head) among first <= p < len - tail (ties:
 // the highest index) leaves k, v and scores, the gap is closed, and its position goes to `evicted` if that is not NULL.
-// `lowest` [B*Hkv, n_lowest]: candidates the scoring kernel has reported; with n_lowest == 0 they are found here, one per
-// head, and written there.
-hipError_t launch_evict_one(void *k, void *v, float *scores, int32_t *evicted, unsigned long long *lowest, int n_lowest,
-                            int B, int Hkv, int N, int ragged, const SeqLens &lens, int first, int tail, int row_bytes,
-                            hipStream_t stream);
+// `lowest` [B*Hkv]: scratch for the candidates.
+hipError_t launch_evict_one(void *k, void *v, float *scores, int32_t *evicted, unsigned long long *lowest, int B, int Hkv, int N,
+                            int ragged, const SeqLens &lens, int first, int tail, int row_bytes, hipStream_t stream);
+// The same after the decode kernels, which have left the candidates and the pieces' edges.  bf16 rows.
+hipError_t launch_evict_pieces(void *k, void *v, float *scores, int32_t *evicted, const unsigned long long *lowest, int n_lowest,
+                               const EvictEdges &edges, int B, int Hkv, int N, int ragged, const SeqLens &lens, int row_bytes,
+                               hipStream_t stream);
 hipError_t launch_gather_scores(const float *in, const int32_t *keep_idx, float *out, int BH, int N, int budget,
                                  int n_out, hipStream_t stream);
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, int blocks, hipStream_t stream);

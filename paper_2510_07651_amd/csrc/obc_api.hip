@@ -79,6 +79,7 @@ int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype,
         plain_plan(B, N, W, Hq, Hkv, d, dtype, cap ? cap : kPlainWorkspace, ws, &off);
     }
     ws->total = align_up(off, 256);
+    if (!ws->use_decode) ws->score_need = ws->total;
     return OBC_OK;
 }
 
@@ -158,8 +159,7 @@ int obc_score(const void *q, const void *k, const void *v, int N, int W, int Hq,
 
 static int score_impl(const void *q, const void *k, const void *v, int N, int W, int Hq, int Hkv, int d, int variant,
                       float *scores, int B, int dtype, const int32_t *seq_lens_host, void *workspace,
-                      size_t workspace_bytes, void *hip_stream, int stage_mask, int accumulate, int evict_first = -1,
-                      int evict_tail = 0);
+                      size_t workspace_bytes, void *hip_stream, int stage_mask, int accumulate);
 
 int obc_score_stages(const void *q, const void *k, const void *v, int N, int W, int Hq, int Hkv, int d, int variant,
                      float *scores, int B, int dtype, const int32_t *seq_lens_host, void *workspace,
@@ -183,16 +183,23 @@ int obc_score_static(const void *q, const void *k, const void *v, int N, int W, 
                       OBC_STATIC_SCRATCH_BYTES, hip_stream, OBC_STAGE_ALL, accumulate | 2);
 }
 
+static bool score_pointers_ok(const void *q, const void *k, const void *v, const float *scores) {
+    if (!q || !k || !v || !scores) return false;
+    return (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) & 15) == 0 && ((uintptr_t)scores & 3) == 0;
+}
+
+static hipError_t launch_score(const ScoreArgs &a, const ScoreWorkspace &ws, void *workspace, hipStream_t stream) {
+    return ws.use_decode ? launch_score_decode(a, ws, (char *)workspace, stream)
+           : ws.use_mfma ? launch_score_mfma(a, ws, (char *)workspace, stream)
+                         : launch_score_plain(a, ws, (char *)workspace, stream);
+}
+
 // `accumulate` bit 0: add to the scores; bit 1: use the library's static scratch (workspace must be NULL).
-// `evict_first` >= 0: the decode path also reports eviction candidates among evict_first <= p < len - evict_tail.
 static int score_impl(const void *q, const void *k, const void *v, int N, int W, int Hq, int Hkv, int d, int variant,
                       float *scores, int B, int dtype, const int32_t *seq_lens_host, void *workspace,
-                      size_t workspace_bytes, void *hip_stream, int stage_mask, int accumulate, int evict_first,
-                      int evict_tail) {
+                      size_t workspace_bytes, void *hip_stream, int stage_mask, int accumulate) {
     const bool own_scratch = (accumulate & 2) != 0;
-    accumulate &= 1;
-    if (!q || !k || !v || !scores) return OBC_EINVAL;
-    if ((((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) & 15) != 0 || ((uintptr_t)scores & 3) != 0) return OBC_EINVAL;
+    if (!score_pointers_ok(q, k, v, scores)) return OBC_EINVAL;
     if (stage_mask < 1 || stage_mask > OBC_STAGE_ALL) return OBC_EINVAL;
     ScoreWorkspace ws;
     int rc = plan_score_workspace(B, N, W, Hq, Hkv, d, dtype, variant, &ws, own_scratch ? OBC_STATIC_SCRATCH_BYTES : 0);
@@ -202,23 +209,16 @@ static int score_impl(const void *q, const void *k, const void *v, int N, int W,
     rc = fill_lens(seq_lens_host, B, N, W, &a.ragged, &a.lens);
     if (rc != OBC_OK) return rc;
     if (own_scratch) {
-        if (ws.total > workspace_bytes) return OBC_EWORKSPACE;           // the shape does not fit the static scratch
+        if (ws.score_need > workspace_bytes) return OBC_EWORKSPACE;      // the shape does not fit the static scratch
         if (static_scratch(&workspace) != hipSuccess) return OBC_ELAUNCH;
     }
-    if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < ws.total) return OBC_EWORKSPACE;
+    if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < ws.score_need) return OBC_EWORKSPACE;
     a.q = q; a.k = k; a.v = v; a.scores = scores;
     a.B = B; a.N = N; a.W = W; a.Hq = Hq; a.Hkv = Hkv; a.d = d; a.G = Hq / Hkv;
     a.variant = variant; a.dtype = dtype;
-    hipStream_t stream = (hipStream_t)hip_stream;
     a.stage_mask = stage_mask;
-    a.accumulate = accumulate;
-    a.find_lowest = ws.use_decode && evict_first >= 0;
-    a.evict_first = evict_first;
-    a.evict_tail = evict_tail;
-    const hipError_t e = ws.use_decode ? launch_score_decode(a, ws, (char *)workspace, stream)
-                         : ws.use_mfma ? launch_score_mfma(a, ws, (char *)workspace, stream)
-                                       : launch_score_plain(a, ws, (char *)workspace, stream);
-    return e == hipSuccess ? OBC_OK : OBC_ELAUNCH;
+    a.accumulate = accumulate & 1;
+    return launch_score(a, ws, workspace, (hipStream_t)hip_stream) == hipSuccess ? OBC_OK : OBC_ELAUNCH;
 }
 
 int obc_select_workspace_bytes(int B, int Hkv, int N, size_t *bytes_out) {
@@ -332,13 +332,18 @@ int obc_compact_inplace(void *k, void *v, float *scores, const int32_t *keep_idx
     return e == hipSuccess ? OBC_OK : OBC_ELAUNCH;
 }
 
+// The score's workspace, then a candidate per (sequence, KV head) for the paths that do not leave any.
+static size_t decode_step_bytes(const ScoreWorkspace &ws, int B, int Hkv) {
+    return ws.total + align_up((size_t)B * Hkv * sizeof(unsigned long long), 256);
+}
+
 int obc_decode_step_workspace_bytes(int B, int N, int Hq, int Hkv, int d, int dtype, int variant, size_t *bytes_out) {
     if (!bytes_out) return OBC_EINVAL;
     if (variant == OBC_ALL) return OBC_EINVAL;          // one running score per token
     ScoreWorkspace ws;
     const int rc = plan_score_workspace(B, N, 1, Hq, Hkv, d, dtype, variant, &ws);
     if (rc != OBC_OK) return rc;
-    *bytes_out = ws.total + align_up((size_t)B * Hkv * sizeof(unsigned long long), 256);
+    *bytes_out = decode_step_bytes(ws, B, Hkv);
     return OBC_OK;
 }
 
@@ -347,30 +352,38 @@ int obc_decode_step(const void *q, void *k, void *v, float *scores, int32_t *evi
                     void *workspace, size_t workspace_bytes, void *hip_stream) {
     if (variant == OBC_ALL || num_sinks < 0 || num_recent < 0) return OBC_EINVAL;
     if (((uintptr_t)evicted & 3) != 0) return OBC_EINVAL;
-    size_t need = 0;
-    int rc = obc_decode_step_workspace_bytes(B, N, Hq, Hkv, d, dtype, variant, &need);
+    ScoreWorkspace ws;
+    int rc = plan_score_workspace(B, N, 1, Hq, Hkv, d, dtype, variant, &ws);
     if (rc != OBC_OK) return rc;
     // every sequence must hold a token that competes: num_sinks + num_recent < len_b (checked before anything runs)
-    int ragged = 0;
-    SeqLens lens;
-    std::memset(&lens, 0, sizeof(lens));
+    ScoreArgs a;
+    std::memset(&a, 0, sizeof(a));
     const long long protect = (long long)num_sinks + num_recent;
     if (protect + 1 > N) return OBC_EINVAL;
-    rc = fill_lens(seq_lens_host, B, N, (int)protect + 1, &ragged, &lens);
+    rc = fill_lens(seq_lens_host, B, N, (int)protect + 1, &a.ragged, &a.lens);
     if (rc != OBC_OK) return rc;
-    if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need) return OBC_EWORKSPACE;
-    const size_t score_bytes = need - align_up((size_t)B * Hkv * sizeof(unsigned long long), 256);
-    ScoreWorkspace ws;
-    rc = plan_score_workspace(B, N, 1, Hq, Hkv, d, dtype, variant, &ws);
-    if (rc != OBC_OK) return rc;
-    rc = score_impl(q, k, v, N, 1, Hq, Hkv, d, variant, scores, B, dtype, seq_lens_host, workspace, score_bytes, hip_stream,
-                    OBC_STAGE_ALL, 1, num_sinks, num_recent);
-    if (rc != OBC_OK) return rc;
-    // The decode kernels have left their waves' candidates; after the other paths one pass over the scores finds them.
-    unsigned long long *lowest = (unsigned long long *)((char *)workspace + (ws.use_decode ? ws.dec_lowest : score_bytes));
-    const long long row_bytes = (long long)d * (dtype == OBC_F32 ? 4 : 2);
-    const hipError_t e = launch_evict_one(k, v, scores, evicted, lowest, ws.use_decode ? ws.dec_lowest_per_head : 0, B, Hkv, N, ragged, lens, num_sinks, num_recent, (int)row_bytes,
-                                          (hipStream_t)hip_stream);
+    if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < decode_step_bytes(ws, B, Hkv)) return OBC_EWORKSPACE;
+    if (!score_pointers_ok(q, k, v, scores)) return OBC_EINVAL;
+    char *base = (char *)workspace;
+    const hipStream_t stream = (hipStream_t)hip_stream;
+    a.q = q; a.k = k; a.v = v; a.scores = scores;
+    a.B = B; a.N = N; a.W = 1; a.Hq = Hq; a.Hkv = Hkv; a.d = d; a.G = Hq / Hkv;
+    a.variant = variant; a.dtype = dtype;
+    a.stage_mask = OBC_STAGE_ALL;
+    a.accumulate = 1;
+    a.find_lowest = ws.use_decode;
+    a.evict_first = num_sinks;
+    a.evict_tail = num_recent;
+    if (ws.use_decode) a.edges = {(uint4 *)(base + ws.dec_edges), (float *)(base + ws.dec_edge_scores)};
+    if (launch_score(a, ws, workspace, stream) != hipSuccess) return OBC_ELAUNCH;
+    const int row_bytes = d * (dtype == OBC_F32 ? 4 : 2);
+    hipError_t e;
+    if (ws.use_decode)         // the decode kernels have left their waves' candidates and the pieces' edges
+        e = launch_evict_pieces(k, v, scores, evicted, (const unsigned long long *)(base + ws.dec_lowest), ws.dec_lowest_per_head, a.edges, B,
+                                Hkv, N, a.ragged, a.lens, row_bytes, stream);
+    else                       // after the other paths one pass over the scores finds them
+        e = launch_evict_one(k, v, scores, evicted, (unsigned long long *)(base + ws.total), B, Hkv, N, a.ragged, a.lens, num_sinks, num_recent,
+                             row_bytes, stream);
     return e == hipSuccess ? OBC_OK : OBC_ELAUNCH;
 }
 

@@ -113,12 +113,13 @@ __device__ __forceinline__ int token_of(int t0, int u, int wave, int slot) {
     return t0 + u * tokens_per_step(kD) + wave * (64 / (kD / 8)) + slot;
 }
 
-// The scaled logits of the range, its row maxima and the unnormalised sums around them.
+// The scaled logits of the range, its row maxima and the unnormalised sums around them.  With `edge_rows` also copies of the rows
+// that begin a piece of evict_pieces.
 template <int kG, int kD, int kSteps, bool kNeedO, typename Lens>
 __global__ __launch_bounds__(kThreads) void decode_partial(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, int N, int G,
     int Hkv, int ragged, Lens lens, int splits, float *__restrict__ z_buf, float4 *__restrict__ part_head,
-    float *__restrict__ part_vec) {
+    float *__restrict__ part_vec, uint4 *__restrict__ edge_rows) {
     constexpr int kLpt = kD / 8;        // lanes per token row
     constexpr int kSlots = 64 / kLpt;   // token rows per wave and step
     __shared__ float red_m[kWaves * kG];
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
     for (int u = 0; u < kSteps; ++u) {
         const int p = token_of<kD>(t0, u, wave, slot);
         vw[u] = make_uint4(0, 0, 0, 0);
-        if (kNeedO && p < t1) vw[u] = *(const uint4 *)(vg + (size_t)p * kD + sub * 8);
+        if ((kNeedO || (edge_rows && p % evict_piece_rows(kD) == 0)) && p < t1) vw[u] = *(const uint4 *)(vg + (size_t)p * kD + sub * 8);
     }
 
     float qr[kG][8];
@@ -254,6 +255,17 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
         if (kLpt == 8) l += dpp_pair<0x128>(l);
         l = across_rows<SumOp>(l);
         if (lane == 0) red_l[r * kWaves + wave] = l;
+    }
+    if (edge_rows) {                                // uniform (here, where nobody has to wait for the rows any more)
+        const int pieces = evict_row_pieces(N, kD);
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const int p = token_of<kD>(t0, u, wave, slot);
+            if (p % evict_piece_rows(kD) != 0 || p >= t1) continue;
+            uint4 *to = edge_rows + ((size_t)bh * 2 * pieces + p / evict_piece_rows(kD)) * kLpt + sub;
+            to[0] = kw[u];
+            to[(size_t)pieces * kLpt] = vw[u];
+        }
     }
     if (kNeedO) {
         slot_sums<kLpt>(acc);
@@ -508,13 +520,14 @@ struct DecodeNeeds {
 };
 
 // Scores of the range's tokens from the stored logits, the merged row statistics and V.  With `lowest`, also the
-// lowest (score, highest index) among each wave's tokens first <= p < len - tail, as an evict_candidate.
+// lowest (score, highest index) among each wave's tokens first <= p < len - tail, as an evict_candidate, and copies of the
+// scores that begin a piece of evict_pieces.
 template <int kG, int kD, int kSteps, int kVariant, typename Lens>
 __global__ __launch_bounds__(kThreads) void decode_score(
     const uint16_t *__restrict__ v, int N, int G, int Hkv, int ragged, Lens lens, int splits,
     const float *__restrict__ z_buf, const float4 *__restrict__ part_head, const float *__restrict__ part_vec,
     const float *__restrict__ fin_global, int merge_here, float *__restrict__ scores, size_t plane_stride, int accumulate,
-    unsigned long long *__restrict__ lowest, int first, int tail) {
+    unsigned long long *__restrict__ lowest, int first, int tail, float *__restrict__ edge_scores) {
     constexpr int kLpt = kD / 8;
     constexpr bool kNeedO = DecodeNeeds<kVariant>::o;
     constexpr bool kNeedV = DecodeNeeds<kVariant>::v;
@@ -660,6 +673,7 @@ __global__ __launch_bounds__(kThreads) void decode_score(
                                : kVariant == OBC_JOINT ? s_j : s_a;
                 const float now = old[u][0] + sc;
                 out[p] = now;
+                if (lowest && p % kEvictPiece == 0) edge_scores[(size_t)bh * evict_score_pieces(N) + p / kEvictPiece] = now;
                 if (p >= first && p < len - tail) {
                     const unsigned long long cand = evict_candidate(now, p);
                     low = cand < low ? cand : low;
@@ -689,7 +703,7 @@ hipError_t launch_decode_steps(const ScoreArgs &a, const Lens &lens, const Score
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
         decode_partial<kG, kD, kSteps, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
             (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, lens,
-            ws.dec_splits, z_buf, part_head, part_vec);
+            ws.dec_splits, z_buf, part_head, part_vec, a.edges.rows);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -703,7 +717,8 @@ hipError_t launch_decode_steps(const ScoreArgs &a, const Lens &lens, const Score
         decode_score<kG, kD, kSteps, kVariant><<<grid, dim3(kThreads), 0, stream>>>(
             (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, lens, ws.dec_splits, z_buf, part_head, part_vec, fin,
             ws.dec_merge_inline, a.scores, (size_t)a.B * a.Hkv * a.N, a.accumulate,
-            a.find_lowest ? (unsigned long long *)(base + ws.dec_lowest) : nullptr, a.evict_first, a.evict_tail);
+            a.find_lowest ? (unsigned long long *)(base + ws.dec_lowest) : nullptr, a.evict_first, a.evict_tail,
+            a.edges.scores);
         return hipGetLastError();
     }
     return hipSuccess;
@@ -777,6 +792,9 @@ void decode_plan(int B, int N, int Hq, int Hkv, int d, ScoreWorkspace *ws, size_
     ws->dec_final = *off;  *off = align256(*off + (size_t)BH * ws->dec_rows * final_stride(d) * sizeof(float));
     ws->dec_lowest = *off; *off = align256(*off + (size_t)BH * splits * kWaves * sizeof(unsigned long long));
     ws->dec_lowest_per_head = splits * kWaves;
+    ws->score_need = *off;
+    ws->dec_edges = *off;       *off = align256(*off + (size_t)BH * 2 * evict_row_pieces(N, d) * d * sizeof(uint16_t));
+    ws->dec_edge_scores = *off; *off = align256(*off + (size_t)BH * evict_score_pieces(N) * sizeof(float));
 }
 
 hipError_t launch_score_decode(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStream_t stream) {
