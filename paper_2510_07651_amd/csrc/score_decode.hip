@@ -16,7 +16,7 @@
 //                    the l1-weighted variant of Appendix C, summed over the query heads of
 //                    the KV head (Appendix A.5), written or added to the running scores; for an
 //                    eviction step also every wave's lowest-scored token.
-// Ranges are as short as keeps the inline merge possible while the chip has workgroups to spare
+// Ranges are as short as lets all their workgroups run at once and keeps the inline merge possible
 // (1, 2 or 4 tokens per lane, sixteen waves): instructions of a lone wave issue one by one, so the count per wave is its
 // time.  8 KV heads x 1025 tokens, G = 4, d = 128, joint, per layer: 72 workgroups of 8 tokens per
 // lane, four waves each, 26 us for the two kernels; 136 workgroups of one token per lane, sixteen waves, 13 us.
@@ -777,9 +777,13 @@ bool decode_path_covers(int B, int N, int W, int Hq, int Hkv, int d, int dtype, 
 void decode_plan(int B, int N, int Hq, int Hkv, int d, ScoreWorkspace *ws, size_t *off) {
     const int G = Hq / Hkv;
     const int BH = B * Hkv;
-    // The longest ranges that leave one workgroup per CU, and no shorter ones than the inline merge can take.
-    int steps = kMaxSteps;
-    while (steps > 1 && (long long)BH * splits_for(N, d, steps) < 256 && splits_for(N, d, steps / 2) <= kInlineSplits) steps /= 2;
+    // The shortest ranges whose workgroups fit the compute units, one each (the registers leave no room for two), and no shorter
+    // ones than the inline merge can take.  A second round of workgroups costs more than twice the tokens per lane: a decoding
+    // step of 8 heads, d = 128, G = 1 / 4 / 8, us, with one, two and four tokens per lane: 2100 tokens 18.4 / 23.2 / 34.6, 15.7 / 19.5 /
+    // 25.6 and 18.4 / 23.4 / 35.6; 2 x 1900 20.3 / 24.6 / 37.2, 17.6 / 21.0 / 27.2 and 20.0 / 24.6 / 38.1; within one round 1600 tokens
+    // 13.7 / 16.6 / 21.5, 14.9 / 18.6 / 24.7 and 17.6 / 22.7 / 34.9.
+    int steps = 1;
+    while (steps < kMaxSteps && ((long long)BH * splits_for(N, d, steps) > 256 || splits_for(N, d, steps) > kInlineSplits)) steps *= 2;
     const int splits = splits_for(N, d, steps);
     ws->dec_rows = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
     ws->dec_range = steps * tokens_per_step(d);
