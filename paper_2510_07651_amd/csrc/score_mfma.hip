@@ -1408,7 +1408,10 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
 // Up to 64 rows with output sums the kernels are bound by the reads themselves, and the mark pays always: 32 rows, joint, 67: 40.9 /
 // 41.3, 134: 62.7 / 64.1, 537: 193 / 202; so it does for windows of few rows, the same cache again for every token (4 rows,
 // joint, 268: 82 / 89; value, 201: 44 / 48).
-constexpr long long kCachedBytes = 200ll << 20;
+// (These were calls on the same inputs.  On others each time value and l1 read within 2 % either way from 40 to 200 MB; attention alone
+// with at most 64 rows, its second sweep bound by the read, has the mark from 80 MB of K on: 8 x 44720, 18 rows, 41.4 / 42.1; x 50786 44.8 /
+// 46.3; x 94717 68.3 / 71.6; 32 x 3307 26.7 / 26.0.)
+constexpr long long kCachedBytes = 200ll << 20, kCachedBytesAttn = 80ll << 20;
 static int reads_once(const ScoreArgs &a, const ScoreWorkspace &ws, bool with_v) {
     const int rows = a.G * a.W;
     if (ws.n_chunks > 1) return 0;
@@ -1418,7 +1421,7 @@ static int reads_once(const ScoreArgs &a, const ScoreWorkspace &ws, bool with_v)
         tokens = 0;
         for (int b = 0; b < a.B; ++b) tokens += a.lens.len[b];
     }
-    return tokens * a.Hkv * kRowBytes * (with_v ? 2 : 1) > kCachedBytes;
+    return tokens * a.Hkv * kRowBytes * (with_v ? 2 : 1) > (a.variant == OBC_ATTN && rows <= 64 ? kCachedBytesAttn : kCachedBytes);
 }
 
 // The shares of this call's true lengths (the plan knows only N): shorter splits as far as they fit the workspace, whose
@@ -1474,8 +1477,10 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
         if (e != hipSuccess) return e;
     }
     if (a.stage_mask & OBC_STAGE_COMBINE) {
+        // (score_few_rows reads nothing of the padded rows; the other second sweeps do)
+        const int combine_rows = ws.keep_z ? a.G * a.W : ws.m_pad;
 #define OBC_COMBINE(groups, batch, rows)                                                                               \
-    mfma_combine_hold<groups, batch><<<dim3(ws.m_pad / rows, a.B * a.Hkv), dim3(32 * groups * rows), 0, stream>>>(            \
+    mfma_combine_hold<groups, batch><<<dim3((combine_rows + rows - 1) / rows, a.B * a.Hkv), dim3(32 * groups * rows), 0, stream>>>(            \
         (const uint16_t *)a.v, part_ml, part_o, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.m_pad,         \
         (uint16_t *)(base + ws.out_bf16), (float *)(base + ws.row_const), (float *)(base + ws.special))
         if (need_o && ws.splits <= 16) OBC_COMBINE(1, 16, 4);      // (m_pad: a multiple of 32)
@@ -1484,7 +1489,7 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
         else if (need_o) OBC_COMBINE(8, 16, 1);
 #undef OBC_COMBINE
         else
-            mfma_combine<<<dim3(ws.m_pad / 16, a.B * a.Hkv), dim3(256), 0, stream>>>(
+            mfma_combine<<<dim3((combine_rows + 15) / 16, a.B * a.Hkv), dim3(256), 0, stream>>>(
                 part_ml, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.m_pad, (float *)(base + ws.row_const),
                 (float *)(base + ws.special));
         e = hipGetLastError();
