@@ -605,13 +605,26 @@ __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combin
     // The first splits' records and sums are fetched in one go and stay in registers.
     float T = -INFINITY, c_val = -INFINITY;
     int c_tok = -1, s_star = -1;
+    // What bounds the kernel is these trips to memory one after the other: records, the values that they name, sums.  Records are
+    // asked for first and every candidate's value as soon as they are there, before the groups agree on the winner and while
+    // the sums are still on their way; the winner's then comes from the group that has it.  Kernel, us, records and sums in
+    // turn and values after the agreement / so: 8 heads x 128 rows x 8192 7.9 / 7.3; 4 x 8 heads x 32768, 4 rows 6.3 / 5.5.  Where
+    // the sums' bytes are the limit (4 heads x 448 rows x 128K) nothing changes: 10.3 / 10.4.
     float4 ml[kBatch], po[kBatch];
+    uint2 vo[kBatch];
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-        const size_t prow = (size_t)(slot0 + min(first + j, live_splits - 1)) * m_pad + row;
-        ml[j] = ((const float4 *)part_ml)[prow];
-        po[j] = *(const float4 *)(part_o + prow * kD + dd);
-    }
+    for (int j = 0; j < kBatch; ++j) ml[j] = ((const float4 *)part_ml)[(size_t)(slot0 + min(first + j, live_splits - 1)) * m_pad + row];
+    asm volatile("" ::: "memory");                    // (else the sums are asked for between the records)
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) po[j] = *(const float4 *)(part_o + ((size_t)(slot0 + min(first + j, live_splits - 1)) * m_pad + row) * kD + dd);
+    auto candidate_values = [&](int s0) {             // (padded rows: zero queries, nothing of theirs is used)
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int tok = __float_as_int(ml[j].w);
+            vo[j] = live && s0 + j < live_splits && tok >= 0 ? *(const uint2 *)(vg + (size_t)tok * kD + dd) : make_uint2(0u, 0u);
+        }
+    };
+    candidate_values(first);
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
         if (first + j >= live_splits) continue;
@@ -646,11 +659,10 @@ __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combin
             if (tok >= 0 && (f.y > c_val || (f.y == c_val && star < s_star))) { c_val = f.y; c_tok = tok; s_star = star; }
         }
     }
-    if (!live) { c_tok = -1; s_star = -1; }           // padded rows: zero queries, nothing of theirs is used
-    const uint2 vt_bits = c_tok >= 0 ? *(const uint2 *)(vg + (size_t)c_tok * kD + dd) : make_uint2(0u, 0u);
+    if (!live) { c_tok = -1; s_star = -1; }
+    uint2 vt_bits = make_uint2(0u, 0u);               // the winning candidate's value, in the group that has its split
     float l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = first; s0 < live_splits; s0 += kStride) {
-        uint2 vo[kBatch];
         if (s0 > first) {
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {         // (the records are in cache from the pass above)
@@ -658,12 +670,7 @@ __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combin
                 ml[j] = ((const float4 *)part_ml)[prow];
                 po[j] = *(const float4 *)(part_o + prow * kD + dd);
             }
-        }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const int tok = __float_as_int(ml[j].w);
-            const bool back = live && s0 + j < live_splits && s0 + j != s_star && tok >= 0;
-            vo[j] = back ? *(const uint2 *)(vg + (size_t)tok * kD + dd) : make_uint2(0u, 0u);
+            candidate_values(s0);
         }
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
@@ -674,6 +681,7 @@ __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combin
             o[1] = fmaf(w, po[j].y, o[1]);
             o[2] = fmaf(w, po[j].z, o[2]);
             o[3] = fmaf(w, po[j].w, o[3]);
+            if (s0 + j == s_star) vt_bits = vo[j];
             if (live && s0 + j != s_star && __float_as_int(ml[j].w) >= 0) {   // this split's candidate is an ordinary key
                 const float wc = __builtin_amdgcn_exp2f((ml[j].z - T) * c2);
                 l += wc;
@@ -687,10 +695,13 @@ __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combin
     if constexpr (kGroups > 1) {                      // the groups' sums meet in group order
         __shared__ float sum_l[kGroups];
         __shared__ float4 sum_o[kGroups][32];
+        __shared__ uint2 vt_s[32];
         if (sub == 0) sum_l[group] = l;
+        if (s_star >= 0 && s_star % kStride / kBatch == group) vt_s[sub] = vt_bits;
         sum_o[group][sub] = make_float4(o[0], o[1], o[2], o[3]);
         __syncthreads();
         if (group != 0) return;
+        if (s_star >= 0) vt_bits = vt_s[sub];
         for (int i = 1; i < kGroups; ++i) {
             const float4 x = sum_o[i][sub];
             l += sum_l[i];
