@@ -54,6 +54,7 @@
 // Kernel times, 32/8 heads, joint, in us: digit_sweep (as two kernels, logits / weights) / merge / scores
 //   fp32, d = 128,  8111 tokens   53.9 (36.0 / 27.3) / 5.5 / 24.5 (from digits 27.6)
 //   bf16, d = 64,  16384 tokens   43.0 (28.7 / 21.4) / 5.0 / 28.2 (from digits 34.5)
+// (the same inputs again; on two sets in turn 59 / 8.4 / 27 and 46 / 6.1 / 31).
 // Two kernels met between them: the maxima of all ranges first.  Whole calls, two kernels / one (with as many splits as fill the chip
 // where the calls' heads pass in several launches), joint, us:
 //   fp32, d = 128, 4 x 8 heads x 128 rows x 8000   375 / 302     bf16, d = 64, 8 x 8 heads x 128 rows x 3000   168 / 128
