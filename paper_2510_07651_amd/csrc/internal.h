@@ -82,7 +82,7 @@ struct ScoreWorkspace {
     size_t pl_best;    // float2 [heads*rows*ranges] largest visible logit of a token range, lowest token attaining it
     size_t pl_records; // RowRecord [heads*rows]
     size_t pl_out;     // float [heads*rows*d]       o_i = sum_p A_ip v_p
-    size_t pl_o_pieces;  // bf16 [heads*rows][3][d]  o_i as three pieces (score_fixed.h)
+    size_t pl_o_digits;  // int8 [heads*rows][5][d]  o_i in fixed point (score_fixed.h)
     size_t pl_part_l;  // float [heads*splits*rows]  sum of exp(z - max) of a split, without the row's top token; with pl_digits float4: the
                        // split's own largest logit, the sum without its own top token, that token
     size_t pl_part_o;  // float [heads*splits*rows*d]  unnormalised output of a split, likewise

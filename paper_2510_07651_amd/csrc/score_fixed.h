@@ -27,18 +27,19 @@
 // to 8 % less: what they cost is the fp64 products themselves, at a wave's own pace from memory.)
 // Which calls digit_sweep takes: sweeps_digits (score_plain.hip).
 //
-// v_p . o_i (pieces_score).  v and o as three bf16 pieces each (bf16 values as they are), the six products down to 2^-18 of the
-// largest on the bf16 matrix cores, fp32 accumulation: the highest pieces' products in two halves, everything else apart, put
-// together in fp64.  Left out is 2^-26 of the sum of |v_c o_c|, and each half rounds to 2^-24 of itself.  The norms this goes into,
-// ||v - o||^2 and the joint square, are fp64 sums of it; where a pair that counts has a norm below ||v|| ||o|| / 16 (a v_p that is
-// nearly o_i, values with a common part of three times the rest), the wave forms its 16 x 16 dot products again in fp64
-// (pieces_score's loop), from where on they are what plain_score computes.  Above that line a rounding of v . o is
-// 16 * 2 * 0.2 * 2^-23 of a norm at most, and a score sums the rows' by themselves.  Errors against fp64 in the 2-norm, key / joint, with five
-// base-256 digits (fixed point, 2^-33) before and so: fp32, d = 128, 8111 tokens 3.27e-7 / 3.44e-7 and 3.27e-7 / 3.41e-7; bf16, d = 64,
-// 16384: 4.07e-7 / 3.93e-7 and 4.05e-7 / 3.92e-7; values with a common part, as large as the rest: 2.33e-7 / 2.24e-7 and 2.33e-7 /
-// 2.24e-7, twice as large: 2.17e-7 / 2.57e-7 and 2.28e-7 / 2.75e-7.  (With all sums in one accumulator the last were 2.37e-7 / 2.78e-7, 1 us
-// quicker; with a line of 1/4 they go to fp64, 97 us instead of 68; with one of 1/64 a common part of four times the rest is off by
-// 1.1e-6.)
+// v_p . o_i (fixed_score).  Each row of v and o is scaled by a power of two to fixed point, 38 bits and a sign relative to
+// the row's largest element (30 for bf16 values, whose elements have 8 significant bits), and written as five (four)
+// balanced base-256 digits, |digit| <= 128.  Products of digits are summed exactly in 32-bit integers; pairs of digits
+// beyond the fifth level are left out, and the levels are put together in fp64.  With 2^E for the product of the powers of
+// two just above the rows' largest elements, the arithmetic in a CPU model is off by 2^-35 2^E (rms, 2^-33 at most over
+// millions of pairs: normal elements, channels larger than the others by up to 2^26, elements over 20 binades; there bf16
+// values, which keep fewer bits, reach 2^-30).  The norms it goes into are as good as an fp32 rounding where they are above
+// 2^-4 2^E; where a pair that counts has a smaller one (a v_p that is nearly o_i), the wave forms its 16 x 16 dot products
+// again in fp64 (fixed_score's loop), from where on they are what plain_score computes.
+// Sums in fp32 cannot stand in for this: with three bf16 pieces each, six products and three accumulators on the bf16 matrix cores the
+// kernel took 28 / 32 us instead of 30 / 40 (fp32, d = 128, 8111 tokens / bf16, d = 64, 16384), but where values share a large channel a
+// rounding of v . o is 32 times that in a distance just above the line: errors of single distances, some 10^3 tokens that share a channel
+// of 2.75 sqrt(d), were 6e-7 rms and 1.3e-6 to 2.9e-6 at most, with digits 1e-7 and 3e-7 to 4e-7.
 //
 // P V (weights_pv).  Weights and fp32 values as three bf16 pieces each, all nine products (exact, normal numbers), fp32
 // accumulation: per 32 tokens nine bf16 ops (three for bf16 values) of 16 cycles replace eight fp32 ones of 32.
@@ -48,13 +49,13 @@
 //
 // What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  digit_sweep: vector ALUs and matrix cores, a wave
 // using one after the other (some 18 instructions put a pair's levels together, check and scale them, some 9 take an element apart, some
-// 20 make its weight and the weight's pieces), all four waves of a SIMD at the same stage.  pieces_score: chains of a wave's dependent
-// instructions (exponential, norms in fp64, closeness test: some 40 per 64 pairs) and the logits' way from memory, 67 MB for the second
-// shape below.
-// Kernel times, 32/8 heads, joint, in us: digit_sweep (as two kernels, logits / weights) / merge / scores
-//   fp32, d = 128,  8111 tokens   53.9 (36.0 / 27.3) / 5.5 / 24.5 (from digits 27.6)
-//   bf16, d = 64,  16384 tokens   43.0 (28.7 / 21.4) / 5.0 / 28.2 (from digits 34.5)
-// (the same inputs again; on two sets in turn 59 / 8.4 / 27 and 46 / 6.1 / 31).
+// 20 make its weight and the weight's pieces), all four waves of a SIMD at the same stage.  fixed_score: the vector ALUs, 83
+// instructions per 64 pairs (63 for bf16 values): putting a dot product together about 12, the norms and the closeness test
+// in fp64, and taking an element apart about 15 (7 for bf16), paid once per workgroup of up to 128 rows; matrix cores busy
+// 26 %.
+// Kernel times, 32/8 heads, joint, two sets of inputs in turn, in us: digit_sweep (as two kernels, logits / weights) / merge / scores
+//   fp32, d = 128,  8111 tokens   59.1 (37.2 / 28.2) / 8.5 / 30.4
+//   bf16, d = 64,  16384 tokens   48.1 (29.3 / 23.3) / 6.3 / 39.7
 // Two kernels met between them: the maxima of all ranges first.  Whole calls, two kernels / one (with as many splits as fill the chip
 // where the calls' heads pass in several launches), joint, us:
 //   fp32, d = 128, 4 x 8 heads x 128 rows x 8000   375 / 302     bf16, d = 64, 8 x 8 heads x 128 rows x 3000   168 / 128
@@ -64,6 +65,9 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
+template <typename T> constexpr int kDigits = sizeof(T) == 4 ? 5 : 4;
+constexpr int kRowDigits = 5;                  // of o_i, which is fp32 whatever the inputs are
+constexpr int kLevels = 5;
 template <typename T> constexpr int kLogitDigits = sizeof(T) == 4 ? 6 : 4;
 constexpr int kLogitLevels = 7;
 // Least dot products that the digits give, in units of join_seven: of rows that they hold, and of fp32 rows that they cut.
@@ -80,14 +84,15 @@ template <int D> constexpr int kFixedTile = D == 64 ? 64 : 32;           // toke
 // Layouts in memory, such that a wave reads and writes whole kilobytes (a lane has one row; rows side by side in memory would
 // make every lane's 16 bytes a line of their own: 64 cache accesses instead of 8).
 //   z       [head][row / 16][token / 16][token % 16 / 4][row % 16][token % 4]
-//   pieces  [head][row / 16][piece][element / 32][element % 32 / 8][row % 16][element % 8]
+//   digits  [head][row / 16][digit][element / 64][element % 64 / 16][row % 16][element % 16]
 __device__ __forceinline__ size_t z_block(const Piece &w, int hl, int row_block, int token) {
     return (((size_t)hl * ((w.nr + 15) / 16) + row_block) * (w.z_stride / 16) + (token - w.s0) / 16) * 256;
 }
-template <int D>
-__device__ __forceinline__ size_t row_piece_address(size_t block, int k, int row, int c) {         // in elements
-    return ((block * 3 + k) * (D / 32) + c / 32) * 512 + (c % 32 / 8 * 16 + row % 16) * 8 + c % 8;
+template <int K, int D>
+__device__ __forceinline__ size_t digit_address(size_t block, int k, int row, int c) {
+    return ((block * K + k) * (D / 64) + c / 64) * 1024 + (c % 64 / 16 * 16 + row % 16) * 16 + c % 16;
 }
+
 // Largest |x|, as bits: integers order them like the numbers and put what is not a number on top.
 struct MaxBitsOp { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; } };
 __device__ __forceinline__ uint32_t max_abs(const float (&x)[4]) {
@@ -97,6 +102,9 @@ __device__ __forceinline__ uint32_t max_abs(const float (&x)[4]) {
 }
 // Exponent e with |x|max < 2^e.
 __device__ __forceinline__ int max_exponent(uint32_t amax) { return (int)(amax >> 23) - 126; }
+// A row's share of the unit of a dot product, 2^(e - 18); NaN where an element was infinite or not a number.
+__device__ __forceinline__ double row_unit(int e) { return e > 128 ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, e - 18); }
+
 // The last four planes of digits from four words whose bytes are digits plus 128.
 template <int K>
 __device__ __forceinline__ void byte_planes(const uint32_t (&w)[4], uint32_t (&plane)[K]) {
@@ -129,7 +137,13 @@ __device__ __forceinline__ void digits_of(const double (&x)[4], int e, uint32_t 
                                          __builtin_amdgcn_perm(top[1], top[0], 0x0c0c0501), 0x05040100) ^ 0x80808080u;
 }
 
-// x . y of two fixed-point vectors from the seven levels of a logit, in units of 2^(E - 51); what is cut off is less than two of them.
+// x . y of the two fixed-point vectors from the level sums, in units of row_unit(ex) row_unit(ey).
+__device__ __forceinline__ double join_levels(int l0, int l1, int l2, int l3, int l4) {
+    const int hi = (l0 << 8) + l1, lo = (l2 << 8) + l3 + (l4 >> 8);      // (at most 2^27 and 2^31: |digit| <= 128, the first one <= 64)
+    return fma((double)hi, 65536.0, (double)lo);
+}
+
+// The same from the seven levels of a logit, in units of 2^(E - 51); what is cut off is less than two of them.
 template <int K>
 __device__ __forceinline__ double join_seven(int l0, int l1, int l2, int l3, int l4, int l5, int l6) {
     const int hi = (l0 << 8) + l1, mid = (l2 << 8) + l3;                 // (at most 2^27 and 2^30, as is lo)
@@ -172,27 +186,6 @@ template <int D, int kTok>
 __device__ __forceinline__ int digit_offset(int plane, int row, int c) {
     const int slot = D == 128 ? c ^ (row >> 1 & 7) : c ^ (row >> 2 & 3);
     return (plane * kTok + row) * D + slot * 16;
-}
-
-// Two elements as three bf16 pieces each, rounded to nearest and each remainder exact (9 + 9 + 8 bits and more hold the 24).
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void three_pieces(float a, float b, uint32_t (&p)[3]) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const bf16x2 r = __builtin_convertvector((f32x2{a, b}), bf16x2);     // v_cvt_pk_bf16_f32
-        p[i] = *(const uint32_t *)&r;
-        a -= __uint_as_float(p[i] << 16);
-        b -= __uint_as_float(p[i] & 0xffff0000u);
-    }
-}
-
-// Pieces of tokens in LDS, kTok rows of D bf16 and as many planes as there are pieces.  A row's 16-byte piece c sits at slot c ^ f(row),
-// so that the 16 lanes of a read (same piece of 16 consecutive rows) touch every bank once.
-template <int D, int kTok>
-__device__ __forceinline__ int piece_offset(int plane, int row, int c) {
-    const int slot = D == 128 ? c ^ (row & 15) : c ^ (row >> 1 & 7);
-    return (plane * kTok + row) * D * 2 + slot * 16;
 }
 
 // A span of memory by its bounds: loads beyond its end give zeros.  (One 32-bit address per lane instead of two words per
@@ -291,45 +284,47 @@ struct TokenTile {
         }
         if (sizeof(T) == 4 && threadIdx.x % 64 == 0) cut_s[threadIdx.x / 64] = any_cut;
     }
-    // The elements as bf16 pieces into LDS (bf16 values: themselves) and, where asked for, the rows' norms: ||v||^2 (2), and its root, or
-    // ||v||_1 (1).
-    template <bool kWithPieces, int kNorm>
-    __device__ __forceinline__ void store_pieces(char *pieces, double *norms, float *roots) const {
+    // Digits and units into LDS and, where asked for, the rows' norms: ||v||^2 (2) or ||v||_1 (1).
+    template <bool kWithDigits, int kNorm>
+    __device__ __forceinline__ void store_digits(char *digits, double *units, double *norms) const {
+        constexpr int K = kDigits<T>;
         int thread = threadIdx.x;
         asm volatile("" : "+v"(thread));                     // (addresses anew for every tile: registers)
         const int r0 = thread / kLanes, c = thread % kLanes;
-        char *dst = pieces + piece_offset<D, kTok>(0, r0, c * kPer / 8) + c * kPer % 8 * 2;
+        char *dst = digits + digit_offset<D, kTok>(0, r0, c * kPer / 16) + c * kPer % 16;
 #pragma unroll
         for (int i = 0; i < kCount; ++i) {
             __builtin_amdgcn_sched_barrier(0);               // (one piece at a time: registers)
             float y[kPer / 4][4];
             unpack(i, y);
-            if constexpr (kWithPieces) {
-                char *at = dst + i * kStep * D * 2;
-                if constexpr (kPer == 8) {
-                    *(uint4 *)at = x[i];
-                } else {
-                    uint32_t p[2][3];
-                    three_pieces(y[0][0], y[0][1], p[0]);
-                    three_pieces(y[0][2], y[0][3], p[1]);
+            double yd[kPer / 4][4];
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) *(uint2 *)(at + k * kTok * D * 2) = make_uint2(p[0][k], p[1][k]);
+            for (int q = 0; q < kPer / 4; ++q)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) yd[q][k] = y[q][k];
+            if constexpr (kWithDigits) {
+                uint32_t amax = max_abs(y[0]);
+                if (kPer == 8) amax = MaxBitsOp()(amax, max_abs(y[kPer / 4 - 1]));
+                const int e = max_exponent(over_row<MaxBitsOp>(amax));
+                uint32_t p[kPer / 4][K];
+#pragma unroll
+                for (int q = 0; q < kPer / 4; ++q) digits_of<K>(yd[q], e, p[q]);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    char *at = dst + (k * kTok + i * kStep) * D;
+                    if constexpr (kPer == 4) *(uint32_t *)at = p[0][k];
+                    else *(uint2 *)at = make_uint2(p[0][k], p[1][k]);
                 }
+                if (c == 0) units[r0 + i * kStep] = row_unit(e);
             }
             if (kNorm != 0) {
                 double s = 0.0;
 #pragma unroll
                 for (int q = 0; q < kPer / 4; ++q)
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const double yd = y[q][k];
-                        s = kNorm == 2 ? fma(yd, yd, s) : s + fabs(yd);
-                    }
+                    for (int k = 0; k < 4; ++k) s = kNorm == 2 ? fma(yd[q][k], yd[q][k], s) : s + fabs(yd[q][k]);
                 s = over_row<SumOp>(s);
-                if (c == 0) {
-                    norms[r0 + i * kStep] = s;
-                    if (kWithPieces) roots[r0 + i * kStep] = __builtin_sqrtf((float)s);
-                }
+                if (c == 0) norms[r0 + i * kStep] = s;
             }
         }
     }
@@ -339,6 +334,15 @@ struct TokenTile {
 template <int K, int D>
 struct RowDigits {
     i32x4 x[K][D / 64];
+    __device__ __forceinline__ void load(const int8_t *__restrict__ digits, int hl, int block, int blocks, int lane) {
+        const __amdgpu_buffer_rsrc_t span = span_of(digits + digit_address<K, D>((size_t)hl * blocks, 0, 0, 0), (size_t)blocks * 16 * K * D);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int kk = 0; kk < D / 64; ++kk)
+                x[k][kk] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                         span, (int)digit_address<K, D>(block, k, 0, kk * 64) + lane * 16, 0, 0));
+    }
     // Digits of a row itself, for digit_sweep; returns the row's exponent.  fp32: `any_cut`, whether elements of the wave's
     // rows were cut.
     template <typename T>
@@ -389,9 +393,6 @@ struct RowDigits {
     }
 };
 
-// Buffers of a tile: two where two workgroups fit a CU with them, else one (and a barrier more per tile).
-constexpr int buffers_of(int bytes) { return bytes <= 32 * 1024 ? 2 : 1; }
-
 // Level sums of 16 tokens in LDS (accumulator rows) and 16 window rows (lanes).
 template <int KR, int KT, int D, int kTok, int L>
 __device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const char *digits, int tok, int g, i32x4 (&acc)[L]) {
@@ -409,50 +410,6 @@ __device__ __forceinline__ void level_sums(const RowDigits<KR, D> &rows, const c
             for (int i = 0; i < KR && i + k < L; ++i)
                 acc[i + k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b[k], rows.x[i][kk], acc[i + k], 0, 0, 0);
     }
-}
-
-// A wave's 16 rows as three bf16 pieces each, a matrix operand: lane = row + 16 g holds elements 8 g .. 8 g + 7 of every 32.
-template <int D>
-struct RowPieces {
-    bf16x8 x[3][D / 32];
-    // Rows from `rows` on are zeros (nobody has written them).
-    __device__ __forceinline__ void load(const uint16_t *__restrict__ pieces, int hl, int block, int rows, int lane) {
-        const int blocks = (rows + 15) / 16, at = block * 16 + (lane & 15) < rows ? lane * 16 : 1 << 30;      // (past the span: zeros)
-        const __amdgpu_buffer_rsrc_t span = span_of(pieces + row_piece_address<D>((size_t)hl * blocks, 0, 0, 0), (size_t)blocks * 16 * 3 * D * 2);
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int kk = 0; kk < D / 32; ++kk)
-                x[k][kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                                                          span, (int)row_piece_address<D>(block, k, 0, kk * 32) * 2 + at, 0, 0));
-    }
-};
-// Their dot products with 16 tokens in LDS (accumulator rows; kP pieces each): the products of the highest pieces and the others in
-// sums of their own, which keeps the roundings of the latter small.  (Of nine products the one of the lowest pieces is left out,
-// 2^-36 of the largest.)
-template <int kP, int D, int kTok>
-__device__ __forceinline__ void piece_dots(const RowPieces<D> &rows, const char *pieces, int tok, int g, double (&dot)[4]) {
-    constexpr int kHalves = 2;
-    f32x4 high[kHalves], rest = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int h = 0; h < kHalves; ++h) high[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kk = 0; kk < D / 32; ++kk) {
-        if (kk > 0) __builtin_amdgcn_sched_barrier(0);       // (one piece at a time: registers)
-        bf16x8 b[kP];
-#pragma unroll
-        for (int k = 0; k < kP; ++k) b[k] = *(const bf16x8 *)(pieces + piece_offset<D, kTok>(k, tok, 4 * kk + g));
-#pragma unroll
-        for (int k = 0; k < kP; ++k)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                if (k + i > 2) continue;
-                f32x4 &sum = k == 0 && i == 0 ? high[kk / (D / 32 / kHalves)] : rest;
-                sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[k], rows.x[i][kk], sum, 0, 0, 0);
-            }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) dot[r] = ((double)high[0][r] + (double)high[1][r]) + (double)rest[r];
 }
 
 // fp64 dot products of 16 tokens and 16 rows from memory: lane = row + 16 g, dot[r] that of token 4 g + r.  `tok`: the
@@ -581,6 +538,19 @@ template <int D, int kTok>
 __device__ __forceinline__ int value_offset(int plane, int tok, int c) {
     const int slot = D == 128 ? (c + 2 * (tok & 7)) & 15 : (c + 2 * (tok >> 1 & 3)) & 7;
     return (plane * kTok + tok) * D * 2 + slot * 16;
+}
+
+// Two elements as three bf16 pieces each, rounded to nearest and each remainder exact (9 + 9 + 8 bits and more hold the 24).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void three_pieces(float a, float b, uint32_t (&p)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const bf16x2 r = __builtin_convertvector((f32x2{a, b}), bf16x2);     // v_cvt_pk_bf16_f32
+        p[i] = *(const uint32_t *)&r;
+        a -= __uint_as_float(p[i] << 16);
+        b -= __uint_as_float(p[i] & 0xffff0000u);
+    }
 }
 
 // Tokens of a tile of values: 32 for every part, or 64 where a tile would have fewer 16-byte pieces than threads.
@@ -930,20 +900,19 @@ __global__ __launch_bounds__(kWeightThreads, 4) void digit_sweep(const T *__rest
 // ------------------------------------------------------------------------------------
 constexpr int kScoreTokens = 512;              // most tokens of a workgroup
 template <typename T, int D, int kRb, int kVariant, typename Lens>
-__global__ __launch_bounds__(kFixedThreads, 4) void pieces_score(const T *__restrict__ v, int N, int Hkv, int ragged, Lens lens, Piece w,
+__global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restrict__ v, int N, int Hkv, int ragged, Lens lens, Piece w,
                                                                 int n_tiles, const float *__restrict__ z,
                                                                 const RowRecord *__restrict__ records, const float *__restrict__ o,
-                                                                const uint16_t *__restrict__ o_pieces, float *__restrict__ scores,
+                                                                const int8_t *__restrict__ o_digits, float *__restrict__ scores,
                                                                 size_t variant_stride, int add) {
 #pragma clang fp contract(off)                               // (a score has the same bits alone and among all three)
-    constexpr int kP = sizeof(T) == 4 ? 3 : 1, kTok = kFixedTile<D>, kPart = kTok / (8 / kRb), kRows = 16 * kRb;
+    constexpr int K = kDigits<T>, kTok = kFixedTile<D>, kPart = kTok / (8 / kRb), kRows = 16 * kRb;
     constexpr bool kAttnLike = kVariant == OBC_ATTN || kVariant == OBC_VATP;
     constexpr bool kDoV = kVariant == OBC_ALL || kVariant == OBC_VALUE || kAttnLike, kDoK = kVariant == OBC_ALL || kVariant == OBC_KEY,
                    kDoJ = kVariant == OBC_ALL || kVariant == OBC_JOINT, kNeedO = kDoK || kDoJ, kNeedV = kVariant != OBC_ATTN;
-    constexpr int kSums = kVariant == OBC_ALL ? 3 : 1, kBuf = buffers_of(kP * kTok * D * 2), kNorm = kVariant == OBC_VATP ? 1 : 2;
-    static_assert(kBuf == 2, "one barrier per tile");
-    __shared__ __attribute__((aligned(16))) char pieces[2][kNeedO ? kP * kTok * D * 2 : 16];
-    __shared__ __attribute__((aligned(16))) float root_s[2][kTok];
+    constexpr int kSums = kVariant == OBC_ALL ? 3 : 1, kNorm = kVariant == OBC_VATP ? 1 : 2;
+    __shared__ __attribute__((aligned(16))) char digits[2][kNeedO ? K * kTok * D : 16];
+    __shared__ __attribute__((aligned(16))) double units[2][kTok];
     __shared__ __attribute__((aligned(16))) double norm_s[2][kTok];
     __shared__ __attribute__((aligned(16))) RowRecord rec_s[kRows];
     __shared__ __attribute__((aligned(16))) float sum_s[kSums][kRb][kTok];
@@ -965,8 +934,8 @@ __global__ __launch_bounds__(kFixedThreads, 4) void pieces_score(const T *__rest
         TokenTile<T, D, kTok, kFixedThreads> next;
         if (kNeedV) next.load(vg, 0);
         const int block = min(row0 / 16 + rb, blocks - 1);
-        RowPieces<D> rows;
-        if (kNeedO) rows.load(o_pieces, hl, block, w.nr, lane);
+        RowDigits<kRowDigits, D> rows;
+        if (kNeedO) rows.load(o_digits, hl, block, blocks, lane);
         const __amdgpu_buffer_rsrc_t zg = span_of(z + z_block(w, hl, 0, t_begin), z_block(w, 1, 0, w.s0) * 4);
         const int z_at = (int)(z_block(w, 0, block, w.s0) * 4);
         __syncthreads();                                     // (the chunk before this one is done with)
@@ -976,7 +945,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void pieces_score(const T *__rest
             rec_s[i] = records[(size_t)hl * w.nr + min(row0 + i, w.nr - 1)];
             if (row0 + i >= w.nr) rec_s[i].last = -1;        // no such row: it sees nothing
         }
-        if (kNeedV) next.template store_pieces<kNeedO, kNorm>(pieces[0], norm_s[0], root_s[0]);
+        if (kNeedV) next.template store_digits<kNeedO, kNorm>(digits[0], units[0], norm_s[0]);
         if (kNeedV && t_begin + kTok < t_end) next.load(vg, kTok);
         int slot = 0;
         for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
@@ -984,7 +953,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void pieces_score(const T *__rest
             auto advance = [&]() {
                 if (!kNeedV) return;
                 if (t0 + kTok < t_end)
-                    next.template store_pieces<kNeedO, kNorm>(pieces[slot ^ 1], norm_s[slot ^ 1], root_s[slot ^ 1]);
+                    next.template store_digits<kNeedO, kNorm>(digits[slot ^ 1], units[slot ^ 1], norm_s[slot ^ 1]);
                 if (t0 + 2 * kTok < t_end) next.load(vg, t0 - t_begin + 2 * kTok);
             };
             advance();
@@ -995,7 +964,15 @@ __global__ __launch_bounds__(kFixedThreads, 4) void pieces_score(const T *__rest
                 const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(zg, l * 16, z_at + (t0 - t_begin + p0) * 64, 0);    // (room for whole tiles)
                 const float x[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
                 double vo[4];                                // v_p . o_i
-                if (kNeedO) piece_dots<kP, D, kTok>(rows, pieces[slot], p0 + (l & 15), l >> 4, vo);
+                if (kNeedO) {
+                    i32x4 acc[kLevels];
+                    level_sums<kRowDigits, K, D, kTok>(rows, digits[slot], p0 + (l & 15), l >> 4, acc);
+                    __builtin_amdgcn_sched_barrier(0);       // (the row's record only now: registers)
+                    const double unit = rec_s[rb * 16 + (l & 15)].unit;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        vo[r] = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]) * (units[slot][p0 + 4 * (l >> 4) + r] * unit);
+                }
                 float acc_v[4], acc_k[4], acc_j[4];
                 for (bool again = false;; again = true) {
                     bool close = false;                      // a norm is too small for the digits' error
@@ -1010,7 +987,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void pieces_score(const T *__rest
                         if (!kNeedO) continue;
                         const bool is_top = p == rec.top, counts = a2 != 0.f && !is_top;
                         const double vv = norm_s[slot][tok], d2 = fma(-2.0, vo[r], vv + rec.oo);    // ||v_p - o_i||^2
-                        const float least = root_s[slot][tok] * rec.root;                           // ||v_p|| ||o_i|| / 4
+                        const float least = (float)(units[slot][tok] * rec.unit) * 0x1p32f;         // 2^-4 2^E
                         if (kDoK) {
                             acc_k[r] = a2 * x[r] * x[r] * (is_top ? rec.top_dk : at_least_0((float)d2));
                             close |= counts && (float)d2 < least;

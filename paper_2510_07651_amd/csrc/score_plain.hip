@@ -69,7 +69,7 @@ struct RowRecord {
     float top_dk, top_dj;        // ||v - o||^2 and ||v + Z (v - o)||^2 of the top token
     int last;                    // last token the row sees
     double oo;                   // ||o_i||^2
-    float root;                  // sqrt(oo) / 16 (score_fixed.h); short_partial's merge: the sum of exp(z - m) without the top token
+    double unit;                 // of o_i's digits (score_fixed.h)
 };
 
 template <typename T> __device__ __forceinline__ float load_as_float(const T *p);
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
 
 // ------------------------------------------------------------------------------------
 // Merge.  `spread` waves per row, D / 64 consecutive elements per lane.  Grid: x = 4 / spread rows of the piece, z = KV head.
-// The output is left in fp32, with kFixed also as bf16 pieces.  kOwn: every split has its own reference and has left out a token of its
+// The output is left in fp32, with kFixed also as digits.  kOwn: every split has its own reference and has left out a token of its
 // own (digit_sweep): the largest reference's split stays as it is, the others are brought to it and get their tokens back.
 // What bounds it: loads that wait for one another (heads, then the values that the heads name), each a few us from another die's
 // memory, so a wave asks for all of its splits at once.  Calls of 8 heads x 48 rows, 32 splits, us: a loop over the splits in one wave
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
                                                         Piece w, int split_len, int n_splits, int spread,
                                                         const float *__restrict__ part_l, const float4 *__restrict__ part_head,
                                                         const float *__restrict__ part_o, RowRecord *__restrict__ records,
-                                                        float *__restrict__ out, uint16_t *__restrict__ out_pieces) {
+                                                        float *__restrict__ out, int8_t *__restrict__ out_digits) {
     constexpr int kE = D / 64, kWaves = kThreads / 64, kEach = kMergeEach;
     static_assert(kSweepSplits <= 64, "a split per lane");
     __shared__ float o_s[kWaves - 1][D];
@@ -518,6 +518,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
     const float frac = l / (1.0f + l);                       // 1 - A_{i,top}; the top token's own weight is exp(0) = 1
     const float inv = l > 0.f ? 1.0f / l : 0.f;
     double oo = 0.0, dk = 0.0, dj = 0.0;
+    double unit = 0.0;
     if (kNeedO) {
         float oi[kE];
 #pragma unroll
@@ -531,13 +532,17 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
         }
         const size_t at = (size_t)hl * w.nr + row;
         if constexpr (kFixed) {
-            uint32_t p[3];
-            three_pieces(oi[0], oi[kE - 1], p);
+            const float f[4] = {oi[0], kE > 1 ? oi[kE - 1] : 0.f, 0.f, 0.f};
+            const double x[4] = {f[0], f[1], 0.0, 0.0};
+            const int oe = max_exponent(wave_reduce<MaxBitsOp>(max_abs(f)));
+            unit = row_unit(oe);
+            uint32_t p[kRowDigits];
+            digits_of<kRowDigits>(x, oe, p);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                uint16_t *dst = out_pieces + row_piece_address<D>((size_t)hl * ((w.nr + 15) / 16) + row / 16, k, row, lane * kE);
-                if constexpr (kE == 2) *(uint32_t *)dst = p[k];
-                else *dst = (uint16_t)p[k];
+            for (int k = 0; k < kRowDigits; ++k) {
+                int8_t *dst = out_digits + digit_address<kRowDigits, D>((size_t)hl * ((w.nr + 15) / 16) + row / 16, k, row, lane * kE);
+                if constexpr (kE == 2) *(uint16_t *)dst = (uint16_t)p[k];
+                else *dst = (int8_t)p[k];
             }
         }
 #pragma unroll
@@ -553,7 +558,7 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
         rec->top_dk = (float)dk;
         rec->top_dj = (float)dj;
         rec->oo = oo;
-        rec->root = 0.0625f * __builtin_sqrtf((float)oo);
+        rec->unit = unit;
     }
 }
 
@@ -670,7 +675,7 @@ __device__ __forceinline__ void merge_short(const T *__restrict__ vg, int len, i
                                             const float4 *__restrict__ heads, const float *__restrict__ part_o, float *rows_s,
                                             RowRecord *rec_s) {
     constexpr int kRows = 16 * kRt, kSub = kThreads / kRows, kOwn = kShortTiles / kSub, kE = D / 64;
-    __shared__ float w_s[kRows][kShortTiles];
+    __shared__ float w_s[kRows][kShortTiles], l_s[kRows];         // the tiles' weights; the sum without the top token
     const int live = (len + kTile - 1) / kTile;
     {
         const int row = threadIdx.x / kSub, sub = threadIdx.x % kSub;
@@ -703,7 +708,7 @@ __device__ __forceinline__ void merge_short(const T *__restrict__ vg, int len, i
             rec.top = top;
             rec.inv_l = 1.0f / (1.0f + l);
             rec.last = len - W + row % W;
-            rec.root = l;                                    // (for the vectors below)
+            l_s[row] = l;
         }
     }
     __syncthreads();
@@ -729,7 +734,7 @@ __device__ __forceinline__ void merge_short(const T *__restrict__ vg, int len, i
 #pragma unroll
                 for (int e = 0; e < kE; ++e) o[e] += wt * *(const f32x4 *)(src + 64 * e);
             }
-        const float l = rec_s[rc].root, m = rec_s[rc].m;
+        const float l = l_s[rc], m = rec_s[rc].m;
         const float frac = l / (1.0f + l);                   // 1 - A_{i,top}; the top token's own weight is exp(0) = 1
         const float inv = l > 0.f ? 1.0f / l : 0.f;
         double oo = 0.0, dk = 0.0, dj = 0.0;
@@ -920,7 +925,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
     float *out = (float *)(base + ws.pl_out);
     float2 *best = (float2 *)(base + ws.pl_best);
     RowRecord *rec = (RowRecord *)(base + ws.pl_records);
-    uint16_t *o_pieces = (uint16_t *)(base + ws.pl_o_pieces);
+    int8_t *o_digits = (int8_t *)(base + ws.pl_o_digits);
     // score_fixed.h, 64 or 128 rows per workgroup.
     constexpr bool fixed = kRt == 4 || kRt == 8;
     constexpr int kRb = kRt == 8 ? 8 : 4;
@@ -990,7 +995,7 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                 auto merge = [&](auto with_output, auto own) {
                     constexpr bool kNeedO = decltype(with_output)::value;
                     plain_merge<T, D, kNeedO, kNeedO && fixed, decltype(own)::value><<<grid, dim3(kThreads), 0, stream>>>(
-                        v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split, ws.pl_splits, spread, part_l, (const float4 *)part_l, part_o, rec, out, o_pieces);
+                        v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_split, ws.pl_splits, spread, part_l, (const float4 *)part_l, part_o, rec, out, o_digits);
                 };
                 auto merge_own = [&](auto own) {
                     if (need_o) merge(std::true_type(), own);
@@ -1013,8 +1018,8 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                         constexpr int kTok = kFixedTile<D>;
                         const int tiles = (w.s1 - w.s0 + kTok - 1) / kTok;
                         const int n_tiles = (int)std::min((tiles * (long long)heads + kResident / 2 - 1) / (kResident / 2), kScoreTokens / kTok + 0ll);
-                        pieces_score<T, D, kRb, kVariant><<<dim3(heads, (tiles + n_tiles - 1) / n_tiles), dim3(kFixedThreads), 0, stream>>>(
-                            v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_pieces, a.scores, variant_stride, add);
+                        fixed_score<T, D, kRb, kVariant><<<dim3(heads, (tiles + n_tiles - 1) / n_tiles), dim3(kFixedThreads), 0, stream>>>(
+                            v, a.N, a.Hkv, a.ragged, lens, w, n_tiles, z, rec, out, o_digits, a.scores, variant_stride, add);
                     } else {
                         const int tiles = (w.s1 - w.s0 + kTile - 1) / kTile;
                         const int n_tiles = (int)((tiles * (long long)heads + kResident - 1) / kResident);
@@ -1101,7 +1106,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t c
     };
     split_in(std::min<long long>(kMaxSplits, (resident / 2 + chunks - 1) / chunks));
     auto row_bytes = [&]() {                                 // of one row, beside its logits
-        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 10 : 4) + (size_t)ws->pl_splits * (d + (ws->pl_digits ? 4 : 1)) * 4;
+        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 9 : 4) + (size_t)ws->pl_splits * (d + (ws->pl_digits ? 4 : 1)) * 4;
     };
     auto per_row = [&]() { return row_bytes() + (size_t)align_up(N, kTile) * 4; };
     const size_t alignment = 7 * 256;                        // of the buffers
@@ -1157,7 +1162,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t c
     take(&ws->pl_best, rows * ws->pl_ranges * sizeof(float2));
     take(&ws->pl_records, rows * sizeof(RowRecord));
     take(&ws->pl_out, rows * d * 4);
-    if (fixed) take(&ws->pl_o_pieces, rows * d * 6);
+    if (fixed) take(&ws->pl_o_digits, rows * d * 5);
     take(&ws->pl_part_l, rows * ws->pl_splits * (ws->pl_digits ? sizeof(float4) : sizeof(float)));
     take(&ws->pl_part_o, rows * ws->pl_splits * d * 4);
 }

@@ -61,7 +61,7 @@ VALUES = {
     "nearly_repeated": lambda v: v[:, :, :1] + v * 2.0 ** -4,
     # the same row exactly, but for every eighth token
     "repeated": lambda v: torch.where((torch.arange(v.shape[2]) % 8 == 5)[:, None], v, v[:, :, :1]),
-    # a common part of two and three times the rest: distances on either side of ||v|| ||o|| / 16, where fp64 takes over
+    # a common part of two and three times the rest
     "common_part_2": lambda v: v + 2 * v[:, :, :1],
     "common_part_3": lambda v: v + 3 * v[:, :, :1],
     # multiples of one row: (1 + Z) v cancels Z o for some pairs
@@ -80,6 +80,36 @@ def _set_channel(v, x):
 def test_values_close_to_the_outputs(shape, values):
     q, k, v = _random(shape, 72)
     _check(shape, q, k, VALUES[values](v))
+
+
+# Outputs of about the values' norm, distances between 1/16 and 1/4 of its square.
+COMMON = {
+    "channel": lambda v: _set_channel(v, 2.75 * v.shape[-1] ** 0.5),
+    "part": lambda v: v + 2.75 * v[:, :, :1],
+}
+
+
+@pytest.mark.parametrize("common", COMMON)
+@pytest.mark.parametrize("shape", SHAPES + [("bf16", 64, 1, 20, 1500), ("fp32", 64, 4, 8, 5000), ("fp32", 128, 4, 32, 2100)],
+                         ids=IDS + ["bf16_d64_1x20_1500", "fp32_d64_4x8_5000", "fp32_d128_4x32_2100"])
+def test_squared_distances_element_by_element(shape, common):
+    """Every row asks the same, so key over value score of a token is Z^2 ||v_p - o||^2 / ||v_p||^2: the weights, whose errors are
+    as large as those looked for, cancel.  Left are, in roundings of 2^-24 at most: Z twice (1), three products (3), the distance
+    (1) and the norm (1), their products' sums over a row block and the blocks, key and value (2 * 5), and what the fp32
+    outputs move a distance by: 2 (v - o) . do / ||v - o||^2 with do of some 2 roundings of ||o|| <= 2.75 ||v - o|| and a cosine of
+    5 / sqrt(d) among thousands of tokens (7).  The cross term itself has to add nothing."""
+    dtype, d, G, W, N = shape
+    q, k, v = _random(shape, 77)
+    q = q[:, ::G, :1].repeat_interleave(G, 1).expand(-1, -1, W, -1).contiguous() * 0.5
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    q, k, v = (x.to(dt) for x in (q, k, COMMON[common](v)))
+    sv, sk, _ = (torch.from_numpy(x) for x in oracle.score(q, k, v))
+    got = obc.obc_score(q.cuda(), k.cuda(), v.cuda(), "all").cpu().double()
+    z = (q[:, ::G, :1].double() @ k.double().transpose(2, 3))[:, :, 0] / d ** 0.5
+    seen = (torch.arange(N) <= N - W) & (z.abs() > 2.0 ** -10) & (z < z.amax(2, keepdim=True))     # (the top token is scored apart)
+    err = ((got[1] / got[0]) / (sk / sv) - 1).abs()[seen]
+    print(float(err.max()), float(err.square().mean().sqrt()))
+    assert float(err.max()) <= 23 * 2.0 ** -24
 
 
 @pytest.mark.parametrize("shape", SHAPES + [("fp32", 64, 1, 4, 3000)], ids=IDS + ["fp32_d64_1x4_3000"])
