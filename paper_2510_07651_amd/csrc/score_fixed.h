@@ -16,13 +16,16 @@
 //   element, 2^-40 2^E per dot product and side, 2^-27 of it from 2^-12 2^E up (kLeastDotCut, for the blocks with such a row
 //   in their tile or their window rows).  Normal rows: one in 30000;
 //   bf16 rows with such elements, infinities, NaN: fp64 always.
+// Rows of zeros, keys as padding leaves them and the zeros past a sequence's end among them, are held exactly and pass the test.
 // Of normal keys with channels larger by 8, 0.5 % of the blocks go to fp64.  A block that goes that way does both, and fetches its
 // operands from memory again: whole calls, joint, us, ordinary inputs / every block in fp64 (key channels 2^26 larger that meet query
-// channels as much smaller, or a key of zeros among every sixteen) / fp32 keys that are all cut, and with blocked_logits:
-//   fp32, d = 128,  8 heads x 128 rows x  8111 tokens    93 / 133 /  97    111      1500 tokens    38.5 / 48.5 / 40.9    41.1
-//   fp32, d = 128, 32 heads x 256 rows x  8111 tokens   585 / 960 / 636   1256
-//   fp32, d =  64, 16 heads x 160 rows x 16000 tokens   299 / 441 / 338    364
-//   bf16, d =  64,  8 heads x 128 rows x 16384 tokens    81 / 123          107      1500 tokens    27.8 / 34.2           29.7
+// channels as much smaller) / fp32 keys that are all cut, and with blocked_logits:
+//   fp32, d = 128,  8 heads x 128 rows x  8111 tokens    97 / 147 / 113    114      1500 tokens    38.9 / 48.5 / 42.4    40.5
+//   fp32, d = 128, 32 heads x 256 rows x  8111 tokens   624 / 987 / 719   1112
+//   fp32, d =  64, 16 heads x 160 rows x 16000 tokens   313 / 449 / 366    340
+//   bf16, d =  64,  8 heads x 128 rows x 16384 tokens    84 / 130          107      1500 tokens    28.8 / 35.8           31.1
+// (a key of zeros among every sixteen cost the same as the second figures before such rows passed: 144.9 / 97.9, 48.3 / 40.1, 442.8 / 318.5,
+// 122.3 / 85.2, 34.6 / 29.2 us).
 // (Without the digits while a wave's blocks go to fp64 one after the other, and with four of their loads in flight, such calls took 2
 // to 8 % less: what they cost is the fp64 products themselves, at a wave's own pace from memory.)
 // Which calls digit_sweep takes: sweeps_digits (score_plain.hip).
@@ -150,9 +153,12 @@ __device__ __forceinline__ double join_seven(int l0, int l1, int l2, int l3, int
     const int lo = (l4 << 7) + (K == 4 ? ((l5 << 8) + l6) >> 9 : (l5 + (l6 >> 8)) >> 1);
     return fma(fma((double)hi, 65536.0, (double)mid), 32768.0, (double)lo);
 }
-// Exponent of a row whose elements the digits of a logit cannot hold.
-constexpr int kNoExponent = 1 << 20;
-__device__ __forceinline__ int logit_exponent(uint32_t amax) { return amax >= 0x7f800000u ? kNoExponent : max_exponent(amax); }
+// Exponents of a row whose elements the digits of a logit cannot hold, and of a row of zeros, whose dot products are 0 exactly
+// (with the one: more than kNoExponent / 2, with any other: nothing that ldexp makes of a 0).
+constexpr int kNoExponent = 1 << 20, kZeroExponent = -4096;
+__device__ __forceinline__ int logit_exponent(uint32_t amax) {
+    return amax >= 0x7f800000u ? kNoExponent : amax == 0u ? kZeroExponent : max_exponent(amax);
+}
 // What four elements below 2^e have below the digits' bits, above zero if anything (but for what falls below fp32's range here:
 // 2^-149 of a unit and less).
 template <int K>
@@ -804,7 +810,7 @@ __global__ __launch_bounds__(kWeightThreads, 4) void digit_sweep(const T *__rest
         const T *q_row = q + ((size_t)b * Hq * W + (size_t)(bg % Hkv) * M + w.r0 + min(row, w.nr - 1)) * D;
         RowDigits<K, D> rows;
         bool rows_cut;
-        const int exponent = rows.template take<T>(q_row, lane >> 4, rows_cut) - 51 - 3;
+        const int row_exponent = rows.template take<T>(q_row, lane >> 4, rows_cut), exponent = row_exponent - 51 - 3;
         const int last = min(len - W + (w.r0 + min(row, w.nr - 1)) % W, t_end - 1);                // last token the row sees here
         const int least = __builtin_amdgcn_readfirstlane((int)row16_reduce<MinOp>((uint32_t)last));      // of the 16 rows
         float *zp = z + z_block(w, hl, min(row0 / 16 + rb, blocks - 1), t_begin) + lane * 4;
@@ -830,14 +836,18 @@ __global__ __launch_bounds__(kWeightThreads, 4) void digit_sweep(const T *__rest
                 const int first = t0 + p0 + 4 * (lane >> 4);     // register r has token first + r
                 const i32x4 ex = *(const i32x4 *)&exponents[slot][p0 + 4 * (lane >> 4)];
                 float x[4];
-                bool again = max(max(max(ex[0], ex[1]), ex[2]), ex[3]) + exponent >= kNoExponent / 2;
+                bool again = max(max(max(ex[0], ex[1]), ex[2]), ex[3]) + exponent >= kNoExponent / 2, small[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     double dot = join_seven<K>(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r], acc[5][r], acc[6][r]);
-                    again |= fabs(dot) < least_dot;              // (also of the zeros past the end)
+                    small[r] = fabs(dot) < least_dot;
                     if (D == 128) dot *= 0.088388347648318440550 * 8.0;
                     x[r] = __builtin_amdgcn_ldexpf((float)dot, ex[r] + exponent);
                 }
+                if (__builtin_amdgcn_ballot_w64(again || small[0] || small[1] || small[2] || small[3]) != 0ull)      // uniform, rare
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)              // (keys of zeros, also those past the end, and such queries are held)
+                        again |= small[r] && ex[r] != kZeroExponent && row_exponent != kZeroExponent;
                 if (__builtin_amdgcn_ballot_w64(again) != 0ull) {            // uniform
                     double dot[4];
                     block_dots<T, D>(kg + (size_t)min(t0 + p0 + 4 * (lane & 3) + (lane >> 2 & 3), t_end - 1) * D, q_row, lane >> 4, dot);

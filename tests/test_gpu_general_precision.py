@@ -150,8 +150,10 @@ LOGITS = {
     "channels_2^26": lambda q, k: (_scaled(q, slice(3, 5), -26), _scaled(k, slice(3, 5), 26)),
     # elements far below their rows' largest, in every 16th key and one query row
     "small_elements": lambda q, k: (_put(q, slice(3, 4), 2.0 ** -29), _put(k, slice(5, None, 16), 2.0 ** -27)),
-    # keys that are zero; keys at a right angle to every query
+    # keys that are zero, here and there and in every block; queries that are; keys at a right angle to every query
     "zero_keys": lambda q, k: (q, _put(k, slice(9, None, 50), 0.0, slice(None))),
+    "zero_key_per_block": lambda q, k: (q, _put(k, slice(5, None, 16), -0.0, slice(None))),
+    "zero_queries": lambda q, k: (_put(q, slice(2, None, 5), 0.0, slice(None)), k),
     "right_angles": lambda q, k: (_put(q, slice(None), 0.0, slice(0, 32)), _put(k, slice(2, None, 7), 0.0, slice(32, None))),
 }
 
