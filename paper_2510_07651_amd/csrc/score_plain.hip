@@ -422,6 +422,8 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
 // What bounds it: loads that wait for one another (heads, then the values that the heads name), each a few us from another die's
 // memory, so a wave asks for all of its splits at once.  Calls of 8 heads x 48 rows, 32 splits, us: a loop over the splits in one wave
 // 56.1, four waves with eight each 47.7; of 32 heads x 128 rows, 8 splits: one wave 49.2, four 54.0.
+// Splits that are not there are not asked for: calls of 128 heads x 192 rows x 109 tokens, one split, with eight loads / one 55.2 / 53.1 us
+// (bf16, d = 64), of x 108 rows x 47 (fp32, d = 128) 43.2 / 40.7.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, bool kNeedO, bool kFixed, bool kOwn, typename Lens>
 __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
@@ -439,11 +441,17 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
     RowRecord *rec = records + (size_t)hl * w.nr + row;
     auto part_row = [&](int s) { return ((size_t)hl * n_splits + s) * w.nr + row; };
     float os[kEach][kE], o[kE];
-    auto load_outputs = [&](int s0) {
+    auto load_outputs = [&](int s0) {                        // (of the splits that there are: a uniform branch each)
 #pragma unroll
-        for (int i = 0; i < kEach; ++i)
+        for (int i = 0; i < kEach; ++i) {
+            const int s = s0 + part + i * spread;
+            if (s < live)
 #pragma unroll
-            for (int e = 0; e < kE; ++e) os[i][e] = part_o[part_row(min(s0 + part + i * spread, live - 1)) * D + lane * kE + e];
+                for (int e = 0; e < kE; ++e) os[i][e] = part_o[part_row(s) * D + lane * kE + e];
+            else
+#pragma unroll
+                for (int e = 0; e < kE; ++e) os[i][e] = 0.f;
+        }
     };
     const T *vl = v + (size_t)bg * N * D + lane * kE;        // this lane's elements of a value
     int top, best = 0, tok = 0;
@@ -484,9 +492,14 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
                 float vs[kEach][kE];
 #pragma unroll
                 for (int i = 0; i < kEach; ++i) {
-                    const int t = __builtin_amdgcn_readlane(tok, min(s0 + part + i * spread, live - 1));
+                    const int s = s0 + part + i * spread;
+                    const T *src = vl + (size_t)__builtin_amdgcn_readlane(tok, min(s, live - 1)) * D;
+                    if (s < live)
 #pragma unroll
-                    for (int e = 0; e < kE; ++e) vs[i][e] = load_as_float(vl + (size_t)t * D + e);
+                        for (int e = 0; e < kE; ++e) vs[i][e] = load_as_float(src + e);
+                    else
+#pragma unroll
+                        for (int e = 0; e < kE; ++e) vs[i][e] = 0.f;
                 }
 #pragma unroll
                 for (int i = 0; i < kEach; ++i) {
