@@ -87,6 +87,7 @@ struct ScoreWorkspace {
                        // split's own largest logit, the sum without its own top token, that token
     size_t pl_part_o;  // float [heads*splits*rows*d]  unnormalised output of a split, likewise
     int pl_heads, pl_rows, pl_seg, pl_z_stride, pl_short, pl_digits;
+    int pl_sweep_rows; // with pl_digits: rows of a workgroup of digit_sweep, 64 or 128
     int pl_range, pl_ranges;   // tokens per range, ranges
     int pl_split, pl_splits;   // tokens per split (a multiple of 64), splits
     // Decode path (one window row per query head): see score_decode.hip.

@@ -43,15 +43,19 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTile = 64;        // tokens per tile; each of the four waves owns 16 of them
 constexpr int kThreads = 256;    // 4 waves
 constexpr int kPlainRows = 16;   // up to so many the kernels of this file take a call, beyond 32 those of score_fixed.h (sweeps_digits)
-// Rows of a workgroup of score_fixed.h: 64 where the last 128 would be half empty.
-constexpr int sweep_rows(int rows) { return (rows + 63) / 64 % 2 != 0 ? 64 : 128; }
+// Rows of a workgroup of score_fixed.h, but for digit_sweep: 64 where the last 128 would be half empty.
+constexpr int fixed_rows(int rows) { return (rows + 63) / 64 % 2 != 0 ? 64 : 128; }
 constexpr int kMaxRanges = 64;   // token ranges with a row maximum of their own, at most
 constexpr int kMaxSplits = 32;   // sequence splits of P V, at most
 constexpr int kSweepSplits = 64; // of digit_sweep
 constexpr int kMergeEach = 8;    // splits of a row that a wave of the merge has on the way together
 constexpr int kResident = 1024;  // workgroups the chip holds at four per CU: a launch is cut into about this many
 constexpr int kCus = 256;
-constexpr int kSweepOwn = 2;     // what a workgroup of digit_sweep takes beside its tiles (its rows' digits, its record), in tiles
+// Time of a workgroup of digit_sweep, in hundredths of a tile with 128 rows: its tiles and what it takes beside them (its rows' digits,
+// its record).
+constexpr int sweep_time(int dtype, int rows, int tiles) {
+    return rows == 128 ? 100 * tiles + 200 : dtype == OBC_F32 ? 60 * tiles + 200 : 65 * tiles + 160;
+}
 constexpr int kNoToken = 0x7fffffff;
 
 // What one launch works on: KV heads bg0 .. bg0 + gridDim.z - 1, their window rows r0 .. r0 + nr - 1 (of the G*W rows
@@ -976,9 +980,15 @@ hipError_t run_with(const ScoreArgs &a, const Lens &lens, const ScoreWorkspace &
                 constexpr bool kNeedO = decltype(with_output)::value;
                 const unsigned splits = (w.s1 - w.s0 + ws.pl_split - 1) / ws.pl_split;
                 if constexpr (fixed)
-                    if (with_digits)
-                        digit_sweep<T, D, kRb, kNeedO><<<dim3(heads, splits, row_chunks), dim3(kWeightThreads), 0, stream>>>(
-                            q, k, v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_split, ws.pl_splits, z, (float4 *)part_l, part_o);
+                    if (with_digits) {
+                        auto sweep = [&](auto row_blocks) {
+                            constexpr int kRows = 16 * decltype(row_blocks)::value;
+                            digit_sweep<T, D, decltype(row_blocks)::value, kNeedO><<<dim3(heads, splits, (w.nr + kRows - 1) / kRows), dim3(kWeightThreads), 0, stream>>>(
+                                q, k, v, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, w, ws.pl_split, ws.pl_splits, z, (float4 *)part_l, part_o);
+                        };
+                        if (ws.pl_sweep_rows == 64) sweep(std::integral_constant<int, 4>());
+                        else sweep(std::integral_constant<int, 8>());
+                    }
                 if constexpr (!fixed)
                     plain_weights<T, D, kRt, kNeedO><<<dim3(splits, chunks, heads), dim3(kThreads), 0, stream>>>(
                         v, a.N, a.W, a.Hkv, a.ragged, lens, w, ws.pl_range, ws.pl_ranges, ws.pl_split, ws.pl_splits, z, best, rec,
@@ -1062,7 +1072,7 @@ hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hi
     const int rows = std::min(ws.pl_rows, a.G * a.W);
     if (rows <= 16) return run<T, D, 1>(a, ws, base, stream);
     if (rows <= 32 && !(ws.pl_digits && rows > kPlainRows)) return run<T, D, 2>(a, ws, base, stream);
-    if (sweep_rows(rows) == 64) return run<T, D, 4>(a, ws, base, stream);
+    if (fixed_rows(rows) == 64) return run<T, D, 4>(a, ws, base, stream);
     return run<T, D, 8>(a, ws, base, stream);
 }
 
@@ -1107,13 +1117,21 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t c
         ws->pl_split = (int)align_up((N + splits - 1) / splits, kTile);
         ws->pl_splits = (N + ws->pl_split - 1) / ws->pl_split;
     };
-    // digit_sweep has a workgroup per CU: as many splits as make whole turns of the chip of what a launch takes.
+    // digit_sweep has a workgroup per CU: as many splits as make whole turns of the chip of what a launch takes, and 64 or 128 rows
+    // each.  Random calls of over 64 rows, time with 128 rows over time with 64, geometric means by 64-row chunks times tiles: up to
+    // 256 1.09 (bf16, d = 64), 1.03 (fp32, d = 64), 1.05 (fp32, d = 128); 4096 and more 0.95, 0.92, 0.94.  The better of the two by
+    // sweep_time is within 0.1, 0.2 and 0.2 % of the faster one in the mean, of 870, 790 and 840 calls; 64 rows where the last 128 would be
+    // half empty, and 128 else, lost 4.6, 2.1 and 2.9 %.
     auto split_turns = [&](int heads) {
-        const long long workgroups = (long long)heads * ((M + sweep_rows(M) - 1) / sweep_rows(M));
-        long long best = 1, least = LLONG_MAX;
-        for (long long s = 1; s <= std::min<long long>(kSweepSplits, tiles); ++s) {
-            const long long time = (workgroups * s + kCus - 1) / kCus * ((tiles + s - 1) / s + kSweepOwn);
-            if (time < least) { least = time; best = s; }
+        const unsigned n = (unsigned)tiles, most = std::min<unsigned>(kSweepSplits, n);         // (a 32-bit division takes half the host's time)
+        unsigned best = 1;
+        long long least = LLONG_MAX;
+        for (const int rows : {64, 128}) {
+            const unsigned workgroups = (unsigned)heads * ((M + rows - 1) / rows);               // (heads whose logits fit the workspace: thousands)
+            for (unsigned s = 1; s <= most; ++s) {
+                const long long time = (long long)((workgroups * s + kCus - 1) / kCus) * sweep_time(dtype, rows, (int)((n + s - 1) / s));
+                if (time < least) { least = time; best = s; ws->pl_sweep_rows = rows; }
+            }
         }
         split_in(best);
     };

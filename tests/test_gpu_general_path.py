@@ -35,7 +35,10 @@ def _inputs(dtype, d, G, W, N, B, Hkv, seed):
 SPLITS = [("bf16", 64, 1, 1, 17, 17, None), ("bf16", 64, 1, 4, 64, 4097, None), ("bf16", 64, 2, 4, 16, 4095, [4095, 130]),
           ("bf16", 64, 9, 5, 7, 705, None), ("bf16", 128, 1, 4, 33, 8191, None), ("fp32", 128, 1, 3, 44, 8193, [8193, 129]),
           ("fp32", 64, 8, 4, 5, 1089, None), ("fp32", 128, 3, 3, 43, 2999, None), ("fp32", 64, 2, 3, 63, 4161, [65, 4161]),
-          ("fp32", 128, 40, 4, 32, 4999, None)]
+          ("fp32", 128, 40, 4, 32, 4999, None),
+          # over 64 rows in workgroups of 64, the last one with 2, 36, 50 or all of its rows, and 140 rows in workgroups of 128
+          ("bf16", 64, 2, 4, 25, 300, None), ("fp32", 64, 2, 4, 35, 3910, None), ("fp32", 128, 2, 5, 26, 3000, [3000, 1999]),
+          ("bf16", 64, 1, 2, 64, 5001, None), ("bf16", 64, 2, 2, 50, 9001, [9001, 64])]
 
 
 @pytest.mark.parametrize("case", SPLITS, ids=lambda c: "%s_d%d_%d_%dx%d_%d" % c[:6])
