@@ -117,7 +117,7 @@ int tuned_sweep2_form();     // 0: by shape, 1: 32 rows per wave, 2: 64 rows per
 constexpr size_t kPlainWorkspace = (size_t)96 << 20;      // of the general path, which works in pieces
 int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, ScoreWorkspace *ws, size_t cap = 0);
 // Adds the general path's buffers to the plan, advancing *off (bytes).
-void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t cap, ScoreWorkspace *ws, size_t *off);
+void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, size_t cap, ScoreWorkspace *ws, size_t *off);
 // Adds the matrix-core path's buffers to the plan, advancing *off (bytes).
 void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWorkspace *ws, size_t *off);
 

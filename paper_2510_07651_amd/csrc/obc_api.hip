@@ -76,7 +76,7 @@ int plan_score_workspace(int B, int N, int W, int Hq, int Hkv, int d, int dtype,
     } else if (ws->use_mfma) {
         mfma_plan(B, N, W, Hq, Hkv, d, variant, ws, &off);
     } else {
-        plain_plan(B, N, W, Hq, Hkv, d, dtype, cap ? cap : kPlainWorkspace, ws, &off);
+        plain_plan(B, N, W, Hq, Hkv, d, dtype, variant, cap ? cap : kPlainWorkspace, ws, &off);
     }
     ws->total = align_up(off, 256);
     if (!ws->use_decode) ws->score_need = ws->total;

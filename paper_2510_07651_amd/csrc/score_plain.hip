@@ -1078,34 +1078,50 @@ hipError_t run_rows(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hi
 
 }  // namespace
 
-// Which calls digit_sweep takes.  Whole calls, joint, us, without / with it:
-//   bf16, d = 64       8 heads x 32 rows x 64 tokens 18.3 / 17.2, x 1500 23.3 / 19.0, x 8000 40.5 / 30.2; 4 heads x 63 rows x 200 18.8 / 18.1
-//   fp32, over 32 rows, the tiles (all heads, in 128-row chunks) against d = 128 and d = 64
-//     40   2 heads x 128 rows x 1300   27 / 29   23.0 / 23.3        72   8 heads x 128 rows x  513   32.0 / 33.1   25.6 / 25.1
-//     80   4 heads x  64 rows x  600   25.4 / 27.7   20.6 / 20.9   136   8 heads x 128 rows x 1025   37.4 / 36.1   29.4 / 27.6
-//    528  32 heads x  33 rows x 1000   42.1 / 38.7   28.3 / 27.0  2000   8 heads x 128 rows x 16001 (d = 64) 117 / 105
-//   fp32, 17 to 32 rows
-//          8 heads x  32 rows x   700   27.0 / 26.6   21.2 / 20.3   1 head  x  32 rows x 20000   66.7 / 52.8   50.5 / 36.0
-//          8 heads x  32 rows x  1500   28.1 / 28.6   23.4 / 20.7   8 heads x  32 rows x 30000   166 / 154   110 / 102
-//         16 heads x  20 rows x  8000   86.7 / 87.1   56.5 / 59.3  32 heads x  32 rows x  8000   156 / 156   98 / 102
-// so bf16 always, fp32 from 128 tiles up; of up to 32 fp32 rows, which leave half of its waves without any, only few heads (the
-// kernels for up to 32 rows need many to fill the chip).  (The line counts every head of the call, so which kernel forms a
-// sequence's logits, and with it their last bit now and then, depends on the batch.)
-int sweeps_digits(int dtype, int heads, int M, long long tiles) {
+// Two launches instead of three or four where every tile of a head may merge all of the head's records (short_partial): as long
+// as that reads less than 32 MB, some 5 us, and the buffers fit the static scratch (on either scratch the same kernels).
+bool fits_short(int heads, int M, int d, long long tiles) {
+    const size_t rows = (size_t)heads * ((M + 15) / 16 * 16);
+    return M <= 32 && tiles <= kShortTiles && (size_t)heads * tiles * tiles * M * d * 4 <= (size_t)32 << 20 &&
+           rows * (tiles * (kTile * 4 + 8 * d + 16)) <= (size_t)OBC_STATIC_SCRATCH_BYTES - 7 * 256;
+}
+
+// Which calls digit_sweep takes.  Time without it over time with it, whole calls one after the other, geometric means over 8500 random
+// shapes (1 to 160 heads, 17 to 512 rows, inputs that change from call to call), with outputs (key, joint, all) / without:
+//   17 to 32 rows, up to 16 tiles of 64 tokens (short_partial): tiles      1-2         3-4         5-8        9-16
+//     bf16, d =  64                                                  0.96 / 0.90 0.99 / 0.91 1.02 / 0.93 1.13 / 0.95
+//     fp32, d =  64                                                  0.89 / 0.87 0.90 / 0.88 0.93 / 0.88 1.01 / 0.89
+//     fp32, d = 128                                                  0.88 / 0.84 0.91 / 0.85 0.94 / 0.84 0.99 / 0.84
+//   17 to 32 rows, longer: heads               1-2         3-5        6-11       12-23       24-47        48-
+//     bf16, d =  64                        1.31 / 1.45 1.26 / 1.41 1.23 / 1.35 1.19 / 1.28 1.15 / 1.23 1.09 / 1.18
+//     fp32, d =  64                        1.19 / 1.31 1.13 / 1.28 1.08 / 1.20 0.99 / 1.09 0.98 / 1.04 0.91 / 1.00
+//     fp32, d = 128                        1.13 / 1.22 1.07 / 1.17 1.04 / 1.12 0.99 / 1.04 1.00 / 1.01 0.96 / 1.02
+//   over 32 rows: tiles x 128-row chunks      -63         64-95      96-127      128-159     160-191     192-255     256-383      384-
+//     bf16, d =  64                        1.01 / 1.06 1.01 / 1.04 1.03 / 1.12 1.03 / 1.09 1.06 / 1.13 1.10 / 1.16 1.12 / 1.16 1.19 / 1.28
+//     fp32, d =  64                        0.99 / 1.03 0.98 / 1.02 1.00 / 1.05 1.00 / 1.06 1.04 / 1.07 1.08 / 1.08 1.05 / 1.09 1.10 / 1.11
+//     fp32, d = 128                        0.92 / 0.90 0.91 / 0.89 0.98 / 0.94 0.96 / 0.95 1.02 / 1.02 1.08 / 1.05 1.05 / 1.05 1.13 / 1.14
+// (over 32 rows with 128-row workgroups where digit_sweep takes 64 now, which it gains by).  So: of calls that short_partial would take
+// only bf16 ones with outputs, from five tiles up; else bf16 always; of up to 32 fp32 rows, which leave half of its waves without any,
+// only few heads (the kernels for up to 32 rows need many to fill the chip); beyond, fp32 from 128 and 160 tiles up.  (The line counts
+// every head of the call, so which kernel forms a sequence's logits, and with it their last bit now and then, depends on the batch.)
+int sweeps_digits(int dtype, int variant, int heads, int M, int d, long long tiles) {
     if (M <= kPlainRows) return 0;
+    const bool outputs = variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL;
+    if (fits_short(heads, M, d, tiles)) return dtype != OBC_F32 && outputs && tiles > 4;
     if (dtype != OBC_F32) return 1;
-    return (M > 32 || heads <= 8) && tiles * heads * ((M + 127) / 128) >= 128;
+    if (M <= 32) return heads < (outputs ? 12 : 24);
+    return tiles * heads * ((M + 127) / 128) >= (d == 128 ? 160 : 128);
 }
 
 // Pieces.  `cap` bounds the workspace: as many KV heads at a time as fit (which leaves every sum as it is), then as many
 // rows of one head, then as many tokens (which does not).  Within it a launch should fill the chip once (kResident; whole turns of
 // kCus workgroups for digit_sweep), so that no workgroup pays a prologue more than needed and no last turn is nearly empty; a row has at most kMaxRanges
 // maxima, which every workgroup of the weight kernel reads.
-void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t cap, ScoreWorkspace *ws, size_t *off) {
+void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv, M = Hq / Hkv * W;
     const long long tiles = (N + kTile - 1) / kTile, logit_chunks = (long long)BH * ((M + 31) / 32);
-    ws->pl_digits = sweeps_digits(dtype, BH, M, tiles);
+    ws->pl_digits = sweeps_digits(dtype, variant, BH, M, d, tiles);
     const bool fixed = M > 32 || ws->pl_digits;
     const long long chunks = fixed ? (long long)BH * ((M + 127) / 128) : logit_chunks, resident = fixed ? kResident / 2 : kResident;
     const long long logit_tiles = (tiles * logit_chunks + kResident - 1) / kResident;
@@ -1172,10 +1188,7 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, size_t c
     }
     auto take = [&](size_t *at, size_t bytes) { *at = *off; *off = align_up(*off + bytes, 256); };
     size_t rows = BH * align_up(M, 16);                      // (whole blocks are written)
-    // Two launches instead of four where every tile of a head may merge all of the head's records (short_partial): as long
-    // as that reads less than 32 MB, some 5 us, and the buffers fit the static scratch (on either scratch the same kernels).
-    ws->pl_short = !fixed && tiles <= kShortTiles && (size_t)BH * tiles * tiles * M * d * 4 <= (size_t)32 << 20 &&
-                   rows * (tiles * (kTile * 4 + 8 * d + 16)) <= (size_t)OBC_STATIC_SCRATCH_BYTES - 7 * 256;
+    ws->pl_short = !fixed && fits_short(BH, M, d, tiles);
     if (ws->pl_short) {
         ws->pl_heads = BH;
         ws->pl_rows = M;

@@ -59,6 +59,24 @@ def test_splits_with_references_of_their_own_match_oracle(case, score_path):
         assert err <= TOL["fp32"], (name, err, where)
 
 
+# (dtype, d, Hkv, G, W, N) on either side of where the route changes: five tiles and sixteen of short bf16 calls; twelve heads of 17 to
+# 32 fp32 rows; 128 and 160 tiles of longer windows
+ROUTES = [("bf16", 64, 2, 4, 5, 256), ("bf16", 64, 2, 4, 5, 257), ("bf16", 64, 2, 4, 5, 1025), ("fp32", 64, 11, 1, 20, 1100),
+          ("fp32", 64, 12, 1, 20, 1100), ("fp32", 128, 2, 2, 40, 5120), ("fp32", 128, 2, 2, 40, 5056), ("fp32", 64, 2, 1, 33, 4032)]
+
+
+@pytest.mark.parametrize("variant", ["joint", "value", "attn", "vatp"])
+@pytest.mark.parametrize("case", ROUTES, ids=lambda c: "%s_d%d_%d_%dx%d_%d" % c)
+def test_every_score_on_either_side_of_a_route(case, variant):
+    """Which kernels take a call depends on whether its score needs the outputs."""
+    dtype, d, Hkv, G, W, N = case
+    q, k, v = _inputs(dtype, d, G, W, N, 1, Hkv, 48)
+    ref = {"attn": oracle.attn_score, "vatp": oracle.vatp_score}.get(variant, lambda *x: oracle.score(*x)[("value", "key", "joint").index(variant)])(q, k, v)
+    got = obc.obc_score(q.cuda(), k.cuda(), v.cuda(), variant).cpu().numpy()
+    err, where = score_error(got, ref, N // 8, None, TOL["fp32"])
+    assert err <= TOL["fp32"], (err, where)
+
+
 @pytest.mark.parametrize("case", EDGES, ids=lambda c: "%s_d%d_%dx%d_%d" % c[:5])
 def test_tile_edges_match_oracle(case, score_path):
     dtype, d, G, W, N, lens = case
