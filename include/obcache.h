@@ -41,8 +41,8 @@
  *   - obc_score picks its kernels from the shapes: bf16 with head_dim 128 runs on the matrix
  *     cores; a one-row window (W = 1, the decoding case) over a bf16 cache of up to ~1e5
  *     head-tokens runs on kernels shaped for memory round trips; everything else (fp32,
- *     bf16 with head_dim 64 and W > 1) on general kernels: logits are fp64 sums rounded once to
- *     fp32, attention outputs and scores fp32 sums, ||v_p - o_i||^2 and what goes with it as good
+ *     bf16 with head_dim 64 and W > 1) on general kernels: logits are the exact sums, to within 2^-27
+ *     of them, rounded once to fp32, attention outputs and scores fp32 sums, ||v_p - o_i||^2 and what goes with it as good
  *     as an fp32 rounding of the fp64 value of the fp32 o_i.  The routing depends
  *     on the arguments only (and on obc_set_score_path, a test hook declared at the end of
  *     this file); the process environment is never read.
@@ -84,8 +84,11 @@ typedef enum {
 #define OBC_MAX_GROUP_ROWS 512    /* largest (Hq/Hkv) * W */
 
 /*
- * Bytes of device workspace obc_score needs for these sizes (Section 3's O and
+ * Bytes of device workspace that serve obc_score for these sizes (Section 3's O and
  * softmax statistics of the window rows, plus split-sequence partial results).
+ * For one-row windows on the decode kernels it holds the rows and scores that obc_decode_step puts aside as well
+ * (one row in 32 KB of K and of V, one score in 2048): obc_score, obc_score_accumulate and obc_score_static ask for
+ * that much less.
  * *bytes_out is a multiple of 256.  Host-only; returns OBC_EINVAL /
  * OBC_EUNSUPPORTED like obc_score would for the same sizes.
  */
@@ -136,8 +139,8 @@ int obc_score_accumulate(const void *q, const void *k, const void *v,
  *     head_dim 64), the head's rows or tokens are taken in smaller pieces than with a workspace,
  *     and the sums over the pieces can differ in their low bits.
  *   - The general path works in pieces, so the array serves any shape of it up to millions of tokens
- *     (OBC_EWORKSPACE beyond).  On the matrix cores (bf16, head_dim 128) shapes whose
- *     obc_score_workspace_bytes exceeds OBC_STATIC_SCRATCH_BYTES are rejected with OBC_EWORKSPACE
+ *     (OBC_EWORKSPACE beyond).  On the matrix cores and the decode kernels (bf16) shapes for which obc_score
+ *     asks for more than OBC_STATIC_SCRATCH_BYTES are rejected with OBC_EWORKSPACE
  *     before anything is launched (4 x 32768 tokens of a 32/8-head layer need ~35 MiB and fit;
  *     decode steps need well under 1 MiB).
  *   - Every call on one GPU shares that GPU's array.  The scratch carries no state between

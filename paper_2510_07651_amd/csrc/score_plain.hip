@@ -1104,9 +1104,8 @@ bool fits_short(int heads, int M, int d, long long tiles) {
 // only bf16 ones with outputs, from five tiles up; else bf16 always; of up to 32 fp32 rows, which leave half of its waves without any,
 // only few heads (the kernels for up to 32 rows need many to fill the chip); beyond, fp32 from 128 and 160 tiles up.  (The line counts
 // every head of the call, so which kernel forms a sequence's logits, and with it their last bit now and then, depends on the batch.)
-int sweeps_digits(int dtype, int variant, int heads, int M, int d, long long tiles) {
+int sweeps_digits(int dtype, bool outputs, int heads, int M, int d, long long tiles) {
     if (M <= kPlainRows) return 0;
-    const bool outputs = variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL;
     if (fits_short(heads, M, d, tiles)) return dtype != OBC_F32 && outputs && tiles > 4;
     if (dtype != OBC_F32) return 1;
     if (M <= 32) return heads < (outputs ? 12 : 24);
@@ -1117,11 +1116,11 @@ int sweeps_digits(int dtype, int variant, int heads, int M, int d, long long til
 // rows of one head, then as many tokens (which does not).  Within it a launch should fill the chip once (kResident; whole turns of
 // kCus workgroups for digit_sweep), so that no workgroup pays a prologue more than needed and no last turn is nearly empty; a row has at most kMaxRanges
 // maxima, which every workgroup of the weight kernel reads.
-void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, size_t cap, ScoreWorkspace *ws, size_t *off) {
+static void plan_with(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int digits, size_t cap, ScoreWorkspace *ws, size_t *off) {
     auto align_up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const int BH = B * Hkv, M = Hq / Hkv * W;
     const long long tiles = (N + kTile - 1) / kTile, logit_chunks = (long long)BH * ((M + 31) / 32);
-    ws->pl_digits = sweeps_digits(dtype, variant, BH, M, d, tiles);
+    ws->pl_digits = digits;
     const bool fixed = M > 32 || ws->pl_digits;
     const long long chunks = fixed ? (long long)BH * ((M + 127) / 128) : logit_chunks, resident = fixed ? kResident / 2 : kResident;
     const long long logit_tiles = (tiles * logit_chunks + kResident - 1) / kResident;
@@ -1209,6 +1208,20 @@ void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int vari
     if (fixed) take(&ws->pl_o_digits, rows * d * 5);
     take(&ws->pl_part_l, rows * ws->pl_splits * (ws->pl_digits ? sizeof(float4) : sizeof(float)));
     take(&ws->pl_part_o, rows * ws->pl_splits * d * 4);
+}
+
+void plain_plan(int B, int N, int W, int Hq, int Hkv, int d, int dtype, int variant, size_t cap, ScoreWorkspace *ws, size_t *off) {
+    const bool outputs = variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL;
+    const long long tiles = (N + kTile - 1) / kTile;
+    const int M = Hq / Hkv * W, digits = sweeps_digits(dtype, outputs, B * Hkv, M, d, tiles), other = sweeps_digits(dtype, !outputs, B * Hkv, M, d, tiles);
+    const size_t begin = *off;
+    plan_with(B, N, W, Hq, Hkv, d, dtype, digits, cap, ws, off);
+    if (other == digits) return;
+    // One workspace serves every score of a shape, whichever of them its size was asked for.
+    ScoreWorkspace of_other = *ws;
+    size_t end = begin;
+    plan_with(B, N, W, Hq, Hkv, d, dtype, other, cap, &of_other, &end);
+    *off = std::max(*off, end);
 }
 
 hipError_t launch_score_plain(const ScoreArgs &a, const ScoreWorkspace &ws, char *ws_base, hipStream_t stream) {

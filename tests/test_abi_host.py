@@ -168,6 +168,14 @@ def test_entry_points_reject_bad_arguments_before_launch(lib):
         obc.obc_decode_step_workspace_bytes(1, 1025, 32, 8, 128, obc.OBC_BF16, obc.OBC_ALL)
 
 
+@pytest.mark.parametrize("dtype,d,heads,W,N", [("bf16", 64, 8, 20, 300), ("bf16", 64, 8, 20, 1000), ("bf16", 64, 2, 32, 1024),
+                                               ("fp32", 64, 16, 20, 3000), ("fp32", 128, 12, 17, 9000), ("fp32", 128, 4, 64, 3000)])
+def test_general_path_asks_the_same_for_every_score(dtype, d, heads, W, N):
+    """Its kernels are chosen by the score too; a workspace sized for one score of a shape serves the others."""
+    code = obc.OBC_BF16 if dtype == "bf16" else obc.OBC_F32
+    assert len({obc.obc_score_workspace_bytes(1, N, W, heads, heads, d, code, v) for v in obc.VARIANT_CODES.values()}) == 1
+
+
 def test_plan_ignores_the_process_environment_and_follows_the_hooks(lib, monkeypatch):
     """The workspace plan is a function of the arguments and of obc_set_score_path / obc_set_score_tuning alone:
     changing the environment between the size query and the call cannot make them disagree."""
