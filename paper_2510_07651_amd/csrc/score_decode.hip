@@ -403,7 +403,7 @@ __device__ __forceinline__ void MergeFew<kG, kD, kNeedO>::merge(const float *__r
     }
     if (kParts > 1) __syncthreads();
     if (live && part == 0) {
-#pragma unroll
+#pragma unroll 8                                              // (all 63 of one row of 64 at once do not fit the registers)
         for (int i = 1; i < kParts; ++i) {
             const float4 y = *(const float4 *)(sum_s + i * kG * kD + quad * 4);
             t.x += y.x; t.y += y.y; t.z += y.z; t.w += y.w;
