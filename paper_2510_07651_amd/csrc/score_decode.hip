@@ -113,9 +113,9 @@ __device__ __forceinline__ int token_of(int t0, int u, int wave, int slot) {
     return t0 + u * tokens_per_step(kD) + wave * (64 / (kD / 8)) + slot;
 }
 
-// The scaled logits of the range, its row maxima and the unnormalised sums around them.  With `edge_rows` also copies of the rows
-// that begin a piece of evict_pieces.
-template <int kG, int kD, int kSteps, bool kNeedO, typename Lens>
+// The scaled logits of the range, its row maxima and the unnormalised sums around them.  With kEdges, for an eviction step, also
+// copies of the rows that begin a piece of evict_pieces; other calls carry none of that.
+template <int kG, int kD, int kSteps, bool kNeedO, bool kEdges, typename Lens>
 __global__ __launch_bounds__(kThreads) void decode_partial(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, int N, int G,
     int Hkv, int ragged, Lens lens, int splits, float *__restrict__ z_buf, float4 *__restrict__ part_head,
@@ -163,21 +163,33 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
         if (kNeedO && p < t1) vw[u] = *(const uint4 *)(vg + (size_t)p * kD + sub * 8);
     }
 
-    // Copies of the rows that begin a piece of evict_pieces, at the very end, where nobody waits for them.  Where the sums do not need V,
-    // or ranges are long, both are fetched again: held to the end they take registers from calls that evict nothing (4 x 8 heads x
-    // 22752, d = 64, attention: 30.6 us, with V loaded from the start 39.1).
-    constexpr bool kHeld = kNeedO && kSteps < kMaxSteps;
+    // Copies of the rows that begin a piece of evict_pieces, at the very end, where nobody waits for them: kept as they came by, but for
+    // eight rows and long ranges, whose registers they would spill (8 heads, G = 8, d = 128, key, 5717 tokens 37.8 us, kept 43.7).  V that
+    // the sums do not need is fetched there too, in long ranges with the other loads: those workgroups do not all run at once, and
+    // the next one waits for this one's last trip (32 heads, value, d = 128, 4117 tokens: 9.5 us without copies, V at the end 11.3).
+    // A piece is two steps long: only even steps have any.
+    static_assert(evict_piece_rows(kD) == 2 * tokens_per_step(kD), "pieces begin at even steps");
+    constexpr bool kLong = kSteps == kMaxSteps, kKept = !(kNeedO && kLong && kG == 8), kEarly = !kNeedO && kLong;
+    constexpr int kEdgeSteps = kEdges ? (kSteps + 1) / 2 : 0;
+    uint4 edge_v[kEdgeSteps > 0 ? kEdgeSteps : 1];
+    if constexpr (kEdges && kEarly) {
+#pragma unroll
+        for (int i = 0; i < kEdgeSteps; ++i) {
+            const int p = token_of<kD>(t0, 2 * i, wave, slot);
+            edge_v[i] = make_uint4(0, 0, 0, 0);
+            if (p % evict_piece_rows(kD) == 0 && p != 0 && p < t1) edge_v[i] = *(const uint4 *)(vg + (size_t)p * kD + sub * 8);
+        }
+    }
     auto put_edges_aside = [&]() {
-        if (!edge_rows) return;                     // uniform
         const int pieces = evict_row_pieces(N, kD);
 #pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            const int p = token_of<kD>(t0, u, wave, slot);
-            if (p % evict_piece_rows(kD) != 0 || p >= t1) continue;
+        for (int i = 0; i < kEdgeSteps; ++i) {
+            const int p = token_of<kD>(t0, 2 * i, wave, slot);
+            if (p % evict_piece_rows(kD) != 0 || p == 0 || p >= t1) continue;        // (nothing moves up from the first row)
             uint4 *to = edge_rows + ((size_t)bh * 2 * pieces + p / evict_piece_rows(kD)) * kLpt + sub;
             const size_t at = (size_t)p * kD + sub * 8;
-            to[0] = kHeld ? kw[u] : *(const uint4 *)(kg + at);
-            to[(size_t)pieces * kLpt] = kHeld ? vw[u] : *(const uint4 *)(vg + at);
+            to[0] = kKept ? kw[2 * i] : *(const uint4 *)(kg + at);
+            to[(size_t)pieces * kLpt] = kEarly ? edge_v[i] : kNeedO && kKept ? vw[2 * i] : *(const uint4 *)(vg + at);
         }
     };
 
@@ -712,7 +724,8 @@ hipError_t launch_decode_steps(const ScoreArgs &a, const Lens &lens, const Score
     const dim3 grid(BH, ws.dec_splits);
     if (ws.dec_splits > kMaxSplits || (long long)ws.dec_splits * kSteps * tokens_per_step(kD) < a.N) return hipErrorInvalidValue;
     if (a.stage_mask & OBC_STAGE_SWEEP1) {
-        decode_partial<kG, kD, kSteps, kNeedO><<<grid, dim3(kThreads), 0, stream>>>(
+        const auto partial = a.find_lowest ? decode_partial<kG, kD, kSteps, kNeedO, kVariant != OBC_ALL, Lens> : decode_partial<kG, kD, kSteps, kNeedO, false, Lens>;
+        partial<<<grid, dim3(kThreads), 0, stream>>>(
             (const uint16_t *)a.q, (const uint16_t *)a.k, (const uint16_t *)a.v, a.N, a.G, a.Hkv, a.ragged, lens,
             ws.dec_splits, z_buf, part_head, part_vec, a.edges.rows);
         const hipError_t e = hipGetLastError();
