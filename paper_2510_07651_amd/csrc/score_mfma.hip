@@ -1410,29 +1410,32 @@ void mfma_plan(int B, int N, int W, int Hq, int Hkv, int d, int variant, ScoreWo
 
 // Whether a sweep marks its reads of K and V (of K alone without `with_v`) as non-temporal.  It does where nobody reads them
 // again soon: not with several row chunks, whose workgroups meet in a die's L2, and not where the memory-side cache of 256 MB
-// holds what the next sweep, or the next call, reads again.  Calls, us, marked / not (K and V of the call, MB):
-//   128 rows, joint     17: 39.3 / 31.2    34: 46.6 / 40.4    67: 60.9 / 53.6   134: 88.9 / 82.6   201: 120.7 / 115.6   268: 150.7 / 150.0   537: 273 / 272
-//   128 rows, value     34: 29.3 / 26.8    67: 38.7 / 35.3   134: 56.4 / 50.5   201: 69.6 / 67.3   268: 85.2 / 85.3     537: 155 / 164
-//   32 rows, attention 134: 35.9 / 34.6   268: 54.4 / 54.1   403: 74.9 / 77.3   537: 91.2 / 97.1 (reads K, half of them)
-//   256 rows, joint     34: 61.2 / 55.9   134: 150 / 138     268: 260 / 252     537: 502 / 495    1074: 971 / 961
-//   448 rows, joint     67: 143 / 130     134: 252 / 235     268: 471 / 438     537: 938 / 890    1074: 1825 / 1725
-// Up to 64 rows with output sums the kernels are bound by the reads themselves, and the mark pays always: 32 rows, joint, 67: 40.9 /
-// 41.3, 134: 62.7 / 64.1, 537: 193 / 202; so it does for windows of few rows, the same cache again for every token (4 rows,
-// joint, 268: 82 / 89; value, 201: 44 / 48).
-// (These were calls on the same inputs.  On others each time value and l1 read within 2 % either way from 40 to 200 MB; attention alone
-// with at most 64 rows, its second sweep bound by the read, has the mark from 80 MB of K on: 8 x 44720, 18 rows, 41.4 / 42.1; x 50786 44.8 /
-// 46.3; x 94717 68.3 / 71.6; 32 x 3307 26.7 / 26.0.)
-constexpr long long kCachedBytes = 200ll << 20, kCachedBytesAttn = 80ll << 20;
+// holds them for the second sweep.  Time with both sweeps marked over neither, 1200 random calls on inputs that change from call to
+// call, geometric means by MB of K and V:
+//                                        -20    20-40   40-80  80-150 150-210 210-268 268-350 350-500  500-
+//   9 to 64 rows, with outputs          1.091   1.067   1.032   1.026   1.028   1.020   1.008   0.950   0.919
+//                 value and l1          1.004   1.012   1.005   1.003   1.005   1.017   1.011   0.957   0.931
+//                 attention alone       1.030   1.009   1.006   1.005   1.007   1.002   0.976   0.991   0.963
+//   65 to 128 rows, with outputs        1.081   1.051   1.040   1.030   1.016   1.006   0.995   0.996   0.991
+//                 value and l1          1.005   1.006   0.993   0.996   1.006   1.037   1.016   0.992   0.961
+//                 attention alone       1.029   1.016   0.996   1.008   0.999   1.012   1.013   1.027   0.994
+//   more rows, with outputs             1.035   1.021   1.019   1.023   1.033   1.037   1.046   1.008
+// Value and l1 read K first: from 210 to 400 MB the first sweep leaves it in the cache and the second one marks its reads, 3 % less than
+// neither (101.5 / 97.4 us: 2 x 8 heads x 43904, 128 rows, value).  Attention alone with at most 64 rows, its second sweep bound by the
+// read, has the mark from 80 MB of K on: 32 heads x 14080, 49.9 / 48.8 us.  Windows of few rows always have it: the same cache comes again
+// for every token (4 rows, same inputs: joint, 268 MB 82 / 89 marked / not; value, 201 MB 44 / 48).
+constexpr long long kCachedBytes = 256ll << 20, kCachedBytesValue = 200ll << 20, kCachedBytesAttn = 80ll << 20;
 static int reads_once(const ScoreArgs &a, const ScoreWorkspace &ws, bool with_v) {
     const int rows = a.G * a.W;
     if (ws.n_chunks > 1) return 0;
-    if (ws.keep_z || rows <= kFewRows || (rows <= 64 && needs_output(a.variant))) return 1;
+    if (ws.keep_z || rows <= kFewRows) return 1;
     long long tokens = (long long)a.B * a.N;
     if (a.ragged) {
         tokens = 0;
         for (int b = 0; b < a.B; ++b) tokens += a.lens.len[b];
     }
-    return tokens * a.Hkv * kRowBytes * (with_v ? 2 : 1) > (a.variant == OBC_ATTN && rows <= 64 ? kCachedBytesAttn : kCachedBytes);
+    const long long cached = needs_output(a.variant) ? kCachedBytes : a.variant == OBC_ATTN && rows <= 64 ? kCachedBytesAttn : kCachedBytesValue;
+    return tokens * a.Hkv * kRowBytes * (with_v ? 2 : 1) > cached;
 }
 
 // The shares of this call's true lengths (the plan knows only N): shorter splits as far as they fit the workspace, whose
