@@ -1062,7 +1062,8 @@ hipError_t run(const ScoreArgs &a, const ScoreWorkspace &ws, char *base, hipStre
     return with_lens(a.ragged, a.B, a.lens, [&](const auto &lens) {
         if constexpr (kRt <= 2)
             if (ws.pl_short) return run_short<T, D, kRt>(a, lens, ws, base, stream);
-        return run_with<T, D, kRt>(a, lens, ws, base, stream);
+        if constexpr (kRt == 2 && sizeof(T) == 2) return hipErrorInvalidValue;          // (digit_sweep takes the others: sweeps_digits)
+        else return run_with<T, D, kRt>(a, lens, ws, base, stream);
     });
 }
 
@@ -1150,9 +1151,11 @@ static void plan_with(int B, int N, int W, int Hq, int Hkv, int d, int dtype, in
         }
         split_in(best);
     };
-    split_in(std::min<long long>(kMaxSplits, (resident / 2 + chunks - 1) / chunks));
+    const long long usual_splits = std::min<long long>(kMaxSplits, (resident / 2 + chunks - 1) / chunks);
+    split_in(usual_splits);
+    auto best_bytes = [&]() { return ws->pl_digits ? 0 : ws->pl_ranges * sizeof(float2); };
     auto row_bytes = [&]() {                                 // of one row, beside its logits
-        return (size_t)ws->pl_ranges * sizeof(float2) + sizeof(RowRecord) + (size_t)d * (fixed ? 9 : 4) + (size_t)ws->pl_splits * (d + (ws->pl_digits ? 4 : 1)) * 4;
+        return best_bytes() + sizeof(RowRecord) + (size_t)d * (fixed ? 9 : 4) + (size_t)ws->pl_splits * (d + (ws->pl_digits ? 4 : 1)) * 4;
     };
     auto per_row = [&]() { return row_bytes() + (size_t)align_up(N, kTile) * 4; };
     const size_t alignment = 7 * 256;                        // of the buffers
@@ -1174,10 +1177,14 @@ static void plan_with(int B, int N, int W, int Hq, int Hkv, int d, int dtype, in
     if (ws->pl_heads < 1) {
         ws->pl_heads = 1;
         ws->pl_rows = (int)std::min<size_t>(M, cap / per_row() / 16 * 16);
+        if (ws->pl_digits && ws->pl_rows <= kPlainRows) {    // so few rows at a time are not digit_sweep's
+            ws->pl_digits = 0;
+            split_in(usual_splits);
+            ws->pl_rows = (int)std::min<size_t>(kPlainRows, cap / per_row() / 16 * 16);
+        }
         if (ws->pl_rows < 1) {
             // One tile of rows at a time and as many tokens as fit, in whole splits (here also the ranges).
             ws->pl_rows = std::min(M, 16);
-            ws->pl_digits = 0;                               // (one launch takes a row's whole sequence)
             ws->pl_split = ws->pl_range = (int)align_up((N + 1023) / 1024, kTile);
             ws->pl_splits = ws->pl_ranges = (N + ws->pl_split - 1) / ws->pl_split;
             const size_t room = cap / ws->pl_rows / 4, taken = row_bytes() / 4;
@@ -1202,7 +1209,7 @@ static void plan_with(int B, int N, int W, int Hq, int Hkv, int d, int dtype, in
     rows = ws->pl_heads * align_up(ws->pl_rows, 16);
     ws->pl_z_stride = (int)align_up(ws->pl_seg, kTile);       // (whole tiles are written)
     take(&ws->pl_z, rows * ws->pl_z_stride * 4);
-    take(&ws->pl_best, rows * ws->pl_ranges * sizeof(float2));
+    take(&ws->pl_best, rows * best_bytes());
     take(&ws->pl_records, rows * sizeof(RowRecord));
     take(&ws->pl_out, rows * d * 4);
     if (fixed) take(&ws->pl_o_digits, rows * d * 5);
