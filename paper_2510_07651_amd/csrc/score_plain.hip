@@ -426,9 +426,8 @@ __global__ __launch_bounds__(kThreads, 2) void plain_weights(const T *__restrict
 // What bounds it: loads that wait for one another (heads, then the values that the heads name), each a few us from another die's
 // memory, so a wave asks for all of its splits at once.  Calls of 8 heads x 48 rows, 32 splits, us: a loop over the splits in one wave
 // 56.1, four waves with eight each 47.7; of 32 heads x 128 rows, 8 splits: one wave 49.2, four 54.0.
-// Splits that are not there are not asked for: calls of 128 heads x 192 rows x 109 tokens, one split, with eight loads / one 55.2 / 53.1 us
-// (bf16, d = 64), of x 108 rows x 47 (fp32, d = 128) 43.2 / 40.7.
-// ------------------------------------------------------------------------------------
+// A single split is taken as it is: calls of 128 heads x 192 rows x 109 tokens, with the eight loads / so, 55.3 / 44.0 us (bf16, d = 64; of
+// that 4 by this), of x 212 rows x 56 52.6 / 45.6 (fp32, d = 64).  (A branch around every load instead costs full merges 1.6 us of 6.2.)
 template <typename T, int D, bool kNeedO, bool kFixed, bool kOwn, typename Lens>
 __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v, int N, int W, int Hkv, int ragged, Lens lens,
                                                         Piece w, int split_len, int n_splits, int spread,
@@ -445,17 +444,16 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
     RowRecord *rec = records + (size_t)hl * w.nr + row;
     auto part_row = [&](int s) { return ((size_t)hl * n_splits + s) * w.nr + row; };
     float os[kEach][kE], o[kE];
-    auto load_outputs = [&](int s0) {                        // (of the splits that there are: a uniform branch each)
+    auto load_outputs = [&](int s0) {
+        if (live == 1) {                                     // uniform
 #pragma unroll
-        for (int i = 0; i < kEach; ++i) {
-            const int s = s0 + part + i * spread;
-            if (s < live)
-#pragma unroll
-                for (int e = 0; e < kE; ++e) os[i][e] = part_o[part_row(s) * D + lane * kE + e];
-            else
-#pragma unroll
-                for (int e = 0; e < kE; ++e) os[i][e] = 0.f;
+            for (int e = 0; e < kE; ++e) os[0][e] = part_o[part_row(0) * D + lane * kE + e];
+            return;
         }
+#pragma unroll
+        for (int i = 0; i < kEach; ++i)
+#pragma unroll
+            for (int e = 0; e < kE; ++e) os[i][e] = part_o[part_row(min(s0 + part + i * spread, live - 1)) * D + lane * kE + e];
     };
     const T *vl = v + (size_t)bg * N * D + lane * kE;        // this lane's elements of a value
     int top, best = 0, tok = 0;
@@ -489,21 +487,19 @@ __global__ __launch_bounds__(kThreads) void plain_merge(const T *__restrict__ v,
     }
 #pragma unroll
     for (int e = 0; e < kE; ++e) o[e] = 0.f;
-    if (kNeedO) {
+    if (kNeedO && live == 1) {                               // uniform: its own reference and token are the row's
+#pragma unroll
+        for (int e = 0; e < kE; ++e) o[e] = part == 0 ? os[0][e] : 0.f;
+    } else if (kNeedO) {
         for (int s0 = 0; s0 < live; s0 += kEach * spread) {
             if (s0 > 0) load_outputs(s0);
             if constexpr (kOwn) {
                 float vs[kEach][kE];
 #pragma unroll
                 for (int i = 0; i < kEach; ++i) {
-                    const int s = s0 + part + i * spread;
-                    const T *src = vl + (size_t)__builtin_amdgcn_readlane(tok, min(s, live - 1)) * D;
-                    if (s < live)
+                    const int t = __builtin_amdgcn_readlane(tok, min(s0 + part + i * spread, live - 1));
 #pragma unroll
-                        for (int e = 0; e < kE; ++e) vs[i][e] = load_as_float(src + e);
-                    else
-#pragma unroll
-                        for (int e = 0; e < kE; ++e) vs[i][e] = 0.f;
+                    for (int e = 0; e < kE; ++e) vs[i][e] = load_as_float(vl + (size_t)t * D + e);
                 }
 #pragma unroll
                 for (int i = 0; i < kEach; ++i) {
