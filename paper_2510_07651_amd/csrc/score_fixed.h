@@ -1,4 +1,4 @@
-// Part of score_plain.hip: its kernels for more than 32 window rows per KV head.
+// Part of score_plain.hip: its kernels for more than 32 window rows per KV head, and for more than 16 where sweeps_digits says so.
 //
 // The fp64 matrix cores do 79 TFLOP/s and the fp32 ones 157, the 8-bit integer ones 5000 and the bf16 ones 2500, so
 // contractions whose accuracy allows it are taken apart into pieces the fast ones multiply exactly.
@@ -20,12 +20,12 @@
 // Of normal keys with channels larger by 8, 0.5 % of the blocks go to fp64.  A block that goes that way does both, and fetches its
 // operands from memory again: whole calls, joint, us, ordinary inputs / every block in fp64 (key channels 2^26 larger that meet query
 // channels as much smaller) / fp32 keys that are all cut, and with blocked_logits:
-//   fp32, d = 128,  8 heads x 128 rows x  8111 tokens    97 / 147 / 113    114      1500 tokens    38.9 / 48.5 / 42.4    40.5
-//   fp32, d = 128, 32 heads x 256 rows x  8111 tokens   624 / 987 / 719   1112
+//   fp32, d = 128,  8 heads x 128 rows x  8111 tokens    97 / 146 / 112    114      1500 tokens    39.1 / 48.7 / 42.6    40.7
+//   fp32, d = 128, 32 heads x 256 rows x  8111 tokens   636 / 987 / 731   1114
 //   fp32, d =  64, 16 heads x 160 rows x 16000 tokens   313 / 449 / 366    340
-//   bf16, d =  64,  8 heads x 128 rows x 16384 tokens    84 / 130          107      1500 tokens    28.8 / 35.8           31.1
-// (a key of zeros among every sixteen cost the same as the second figures before such rows passed: 144.9 / 97.9, 48.3 / 40.1, 442.8 / 318.5,
-// 122.3 / 85.2, 34.6 / 29.2 us).
+//   bf16, d =  64,  8 heads x 128 rows x 16384 tokens    84 / 130          108      1500 tokens    25.0 / 31.1           31.4
+// (a key of zeros among every sixteen cost about the same as the second figures before such rows passed, and next to nothing now: 97.9,
+// 40.3, 634, 319, 84.8, 25.3 us).
 // (Without the digits while a wave's blocks go to fp64 one after the other, and with four of their loads in flight, such calls took 2
 // to 8 % less: what they cost is the fp64 products themselves, at a wave's own pace from memory.)
 // Which calls digit_sweep takes: sweeps_digits (score_plain.hip).
@@ -57,13 +57,13 @@
 // in fp64, and taking an element apart about 15 (7 for bf16), paid once per workgroup of up to 128 rows; matrix cores busy
 // 26 %.
 // Kernel times, 32/8 heads, joint, two sets of inputs in turn, in us: digit_sweep (as two kernels, logits / weights) / merge / scores
-//   fp32, d = 128,  8111 tokens   59.1 (37.2 / 28.2) / 8.5 / 30.4
-//   bf16, d = 64,  16384 tokens   48.1 (29.3 / 23.3) / 6.3 / 39.7
-// Two kernels met between them: the maxima of all ranges first.  Whole calls, two kernels / one (with as many splits as fill the chip
-// where the calls' heads pass in several launches), joint, us:
-//   fp32, d = 128, 4 x 8 heads x 128 rows x 8000   375 / 302     bf16, d = 64, 8 x 8 heads x 128 rows x 3000   168 / 128
-//   fp32, d = 128, 1 head x 128 rows x 60000       238 / 165     bf16, d = 64, 8 heads x 48 rows x 16384      51.7 / 47.7
-//   fp32, d =  64, 8 heads x 512 rows x 6000       232 / 168     fp32, d = 128, 8 heads x 128 rows x 8111      91.6 / 87
+//   fp32, d = 128,  8111 tokens   59.0 (37.2 / 28.2) / 8.7 / 29.2
+//   bf16, d = 64,  16384 tokens   47.2 (29.3 / 23.3) / 6.0 / 38.3
+// Two kernels met between them: the maxima of all ranges first.  Whole calls, blocked_logits and fixed_weights / digit_sweep (with as many
+// splits as fill the chip where the calls' heads pass in several launches), joint, inputs that change from call to call, us:
+//   fp32, d = 128, 4 x 8 heads x 128 rows x 8000   406 / 317     bf16, d = 64, 8 x 8 heads x 128 rows x 3000   188 / 140
+//   fp32, d = 128, 1 head x 128 rows x 60000       194 / 125     bf16, d = 64, 8 heads x 48 rows x 16384      64.1 / 52.1
+//   fp32, d =  64, 8 heads x 512 rows x 6000       220 / 177     fp32, d = 128, 8 heads x 128 rows x 8111      115 / 97
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
