@@ -162,15 +162,16 @@ __device__ __forceinline__ void pack_weights(Sweep1Regs &R) {
 // it; then V^T P^T and the weights.  Without kNeedO only the branch of the masks divides it.
 template <int PH, bool kNeedO, bool kStoreZ, bool kOnce>
 __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uint32_t lds0, int n, int t_begin,
-                                            int t_end, int last_row, int vis, int n_plain, const char *kh, const char *vh,
+                                            int t_end, int t_last, int last_row, int vis, int n_plain, const char *kh, const char *vh,
                                             const int (&koff)[8], const int (&voff)[4], const uint32_t (&kdoff)[2],
                                             const uint32_t (&vdoff)[2], int wave, int lane, bool wave_active,
                                             int2 *events, char *z_split, uint32_t z_off) {
     // K and V blocks live in rings of four 8 KB slots each (block j in slot j mod 4): K block
     // n+1 and V block n-1, both started three steps ago, are waited for here while the two
     // younger batches stay in flight; then K block n+4 and V block n+2 start in the slots
-    // the previous step has finished with.  Blocks past the end of the split are fetched
-    // too (rows clamp to the last one), so that every batch has the same number of transfers.
+    // the previous step has finished with.  Past the end of the split every batch has as many transfers, but they fetch
+    // the split's last block again, from the L2 (`t_last`; nothing of it counts a second time): the next split's rows were
+    // three K and two V blocks from memory for nothing, a third of what a split of 256 tokens reads.
     constexpr int kKBase = ((PH + 1) & 3) * kBlkBytes;                  // block n+1
     constexpr int kVBase = (4 + ((PH + 3) & 3)) * kBlkBytes;            // block n-1
     const float c2 = kLog2e * kInvSqrtD;
@@ -183,9 +184,9 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
     else if (kStoreZ && wave_active && n == 1 && 32 < t_end - t_begin) wait_async_loads_keep<2 * kBatch + 4>();
     else wait_async_loads_keep<2 * kBatch>();
     __syncthreads();
-    block_load_async<kXor16, kOnce>(kh, t_begin + (n + 4) * 32, last_row, lds0 + PH * kBlkBytes, wave, lane, kdoff);
+    block_load_async<kXor16, kOnce>(kh, min(t_begin + (n + 4) * 32, t_last), last_row, lds0 + PH * kBlkBytes, wave, lane, kdoff);
     if (kNeedO)
-        block_load_async<kRot4, kOnce>(vh, t_begin + (n + 2) * 32, last_row, lds0 + (4 + ((PH + 2) & 3)) * kBlkBytes, wave, lane, vdoff);
+        block_load_async<kRot4, kOnce>(vh, min(t_begin + (n + 2) * 32, t_last), last_row, lds0 + (4 + ((PH + 2) & 3)) * kBlkBytes, wave, lane, vdoff);
     if (!wave_active) return;
     if (kStoreZ && n * 32 < t_end - t_begin && z_off != ~0u) {      // raw q.k of block n for score_few_rows
 #pragma unroll
@@ -354,6 +355,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     const int b = part.b, g = part.g, bg = b * Hkv + g, chunk = part.chunk, split = part.part, G = Hq / Hkv, M = G * W, len = part.len;
     const int t_begin = split * split_len;
     const int t_end = min(t_begin + split_len, len);
+    const int n_blk = (t_end - t_begin + 31) / 32, t_last = t_begin + (n_blk - 1) * 32;
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5;
@@ -414,11 +416,11 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     block_lane_offsets<kRot4>(vdoff, wave, lane);
     for (int e = threadIdx.x; e < kBlkBytes / 16; e += kThreads) ((uint4 *)(smem + 7 * kBlkBytes))[e] = make_uint4(0, 0, 0, 0);
     block_load_async<kXor16, kOnce>(kh, t_begin, len - 1, lds0, wave, lane, kdoff);
-    block_load_async<kXor16, kOnce>(kh, t_begin + 32, len - 1, lds0 + kBlkBytes, wave, lane, kdoff);
-    block_load_async<kXor16, kOnce>(kh, t_begin + 64, len - 1, lds0 + 2 * kBlkBytes, wave, lane, kdoff);
+    block_load_async<kXor16, kOnce>(kh, min(t_begin + 32, t_last), len - 1, lds0 + kBlkBytes, wave, lane, kdoff);
+    block_load_async<kXor16, kOnce>(kh, min(t_begin + 64, t_last), len - 1, lds0 + 2 * kBlkBytes, wave, lane, kdoff);
     if (kNeedO) block_load_async<kRot4, kOnce>(vh, t_begin, len - 1, lds0 + 4 * kBlkBytes, wave, lane, vdoff);
-    block_load_async<kXor16, kOnce>(kh, t_begin + 96, len - 1, lds0 + 3 * kBlkBytes, wave, lane, kdoff);
-    if (kNeedO) block_load_async<kRot4, kOnce>(vh, t_begin + 32, len - 1, lds0 + 5 * kBlkBytes, wave, lane, vdoff);
+    block_load_async<kXor16, kOnce>(kh, min(t_begin + 96, t_last), len - 1, lds0 + 3 * kBlkBytes, wave, lane, kdoff);
+    if (kNeedO) block_load_async<kRot4, kOnce>(vh, min(t_begin + 32, t_last), len - 1, lds0 + 5 * kBlkBytes, wave, lane, vdoff);
     wait_async_loads_keep<kNeedO ? 10 : 6>();         // everything after K block 0 may still be in flight
     __syncthreads();
     R.s_cur = zero16();
@@ -430,13 +432,12 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
         }
     }
 
-    const int n_blk = (t_end - t_begin + 31) / 32;
     const int n_total = (n_blk + 3) & ~3;
     const int n_plain = max(vis_min + 1 - t_begin, 0) / 32;   // leading blocks every row of this wave sees in full
     // (kStoreZ: at most 32 rows, so they are the first wave's)
     char *z_split = (char *)(z + (size_t)bg * M * z_stride + t_begin);
     const uint32_t z_off = kStoreZ && row_valid ? (uint32_t)row * z_stride * 4 + 16 * half : ~0u;
-#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, len - 1, vis, n_plain, kh, vh, koff, voff, kdoff, vdoff, wave, lane, wave_active, events, z_split, z_off
+#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, t_last, len - 1, vis, n_plain, kh, vh, koff, voff, kdoff, vdoff, wave, lane, wave_active, events, z_split, z_off
     for (int n = 0; n < n_total; n += 4) {
         sweep1_step<0, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;
         sweep1_step<1, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;

@@ -373,7 +373,7 @@ __device__ __forceinline__ int next_tile(int a, int n_tiles) { return a + 1 == n
 // where R.kp points) is read during the step.
 template <int kVariant, bool kOnce>
 __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, const uint32_t lds0, int s, int tile,
-                                          int tile_fetch, int tile_flush, int t_begin,
+                                          int tile_fetch, bool past, int tile_flush, int t_begin,
                                           int t_end, int last_row, const int *vis_i, const int *excl_i, const char *kh,
                                           const char *vh, const uint32_t (&moff)[4], int wave, int lane, int vis_min,
                                           const uint32_t *special_s, float *stage, float *out, size_t variant_stride,
@@ -382,8 +382,8 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
     const int rh = wave & 1, th = wave >> 1;
 
     // Tile s+1 has landed once at most the two younger tiles' transfers are in flight; the barrier also tells that
-    // every wave is done with tile s, whose slot the tile fetched during this step reuses.  (The walk wraps around, so
-    // the ring also prefetches past its end: every step waits for the same number of transfers.)
+    // every wave is done with tile s, whose slot the tile fetched during this step reuses.  (Past the walk's end `past` a step
+    // starts as many transfers, so that every step waits for the same number, but all of them fetch one row of K and of V.)
     wait_async_loads_keep<2 * kTilePerWave>();
     __syncthreads();
     TileFetch fetch;
@@ -392,10 +392,10 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
         fetch.k_base = kh + (size_t)tn * kRowBytes - kBias;
         fetch.v_base = vh + (size_t)tn * kRowBytes - kBias;
         fetch.lds = lds0 + ((s + 3) & 3) * kSlotBytes + wave * 4096;          // (the slot of tile s)
-        const int rmax = last_row - tn;                                    // last row of the tile that exists
+        const int rmax = past ? 0 : last_row - tn;                         // last row of the tile that exists
 #pragma unroll
         for (int n = 0; n < 4; ++n) fetch.voff[n] = moff[n];
-        if (rmax < kTileTok - 1) {                                         // uniform, rare: rows past the end re-read the last one
+        if (rmax < kTileTok - 1) {                                         // uniform, rare: rows past it re-read it
 #pragma unroll
             for (int n = 0; n < 4; ++n) {
                 const int Rn = (wave * 4 + n) * 4 + (lane >> 4);
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     // Positions of the walk: the tile worked on, the one fetched during the step (four ahead), the one flushed (two back).
     int tile = first, tile_fetch = tile_at(4, first, n_tiles), tile_flush = tile_at(2 * n_tiles - 2, first, n_tiles);
     for (int s = 0; s < n_tiles; ++s, tile = next_tile(tile, n_tiles), tile_fetch = next_tile(tile_fetch, n_tiles), tile_flush = next_tile(tile_flush, n_tiles))
-        wide_step<kVariant, kOnce>(R, A, lds0, s, tile, tile_fetch, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, moff, wave, lane, vis_min,
+        wide_step<kVariant, kOnce>(R, A, lds0, s, tile, tile_fetch, s + 4 >= n_tiles, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, moff, wave, lane, vis_min,
                             special_s, stage, out, variant_stride, accumulate);
     if (R.pend) {                                              // set B of the last block
         matrix_results_land();
@@ -803,9 +803,11 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
 
     int here = group == 0 ? n_groups - 1 : group - 1;          // the group worked on; `group` is the one after it
     int tok_prev = 0x7fffffff;
+    int s = 0;
     auto step = [&](auto slot) __attribute__((always_inline)) {        // slot: of the block worked on
         const int after = next_tile(group, n_groups), tok0 = block_of(here), blk = 4 * here + wave;
-        const SoloFetch f = solo_fetch(kh, vh, block_of(after), len - 1, ring + slot.value * kSoloSlot, doff, lane);
+        // (past the walk's end one row of K and of V, for the number of transfers: see wide_step)
+        const SoloFetch f = solo_fetch(kh, vh, block_of(after), s + 2 < n_groups ? len - 1 : min(block_of(after), len - 1), ring + slot.value * kSoloSlot, doff, lane);
         const bool hidden = !(tok0 + 31 <= vis_min);
         const int tok = tok0 + (lane & 31);
         solo_block<kVariant, 1 - slot.value, kOnce>(R, A, f, out, variant_stride, tok, tok_prev, t_end, lane, blk, hidden, special_s[special_word(blk)], vis_i, excl_i, accumulate);
@@ -813,10 +815,11 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
         here = group;
         group = after;
     };
-    for (int s = 0; s < n_groups; s += 2) {
+    while (s < n_groups) {
         step(std::integral_constant<int, 0>{});
-        if (s + 1 == n_groups) break;
+        if (++s == n_groups) break;
         step(std::integral_constant<int, 1>{});
+        ++s;
     }
     matrix_results_land();                                     // set B of the last block
     {
