@@ -137,18 +137,52 @@ __device__ __forceinline__ void add_back(Sweep1Regs &R, const char *vh, int tok,
 }
 
 // P = hi + lo for the matrix cores: hi keeps the top 16 bits of the fp32 weight (a bf16 by truncation), lo is the
-// exact remainder rounded to bf16.
+// exact remainder rounded to bf16.  The remainders come from a dot product of the packed pair with (-1, 0) and (0, -1), exact like
+// the subtraction of one unpacked piece and one instruction less each.
 __device__ __forceinline__ void pack_weights(Sweep1Regs &R) {
+    union { uint32_t u; bf16x2 h; } first, second, pair;
+    first.u = 0x0000bf80u;
+    second.u = 0xbf800000u;
+    asm("" : "+s"(first.u), "+s"(second.u));       // (in registers: written as the inline constant -1.0 the pair comes out as (0, -1))
 #pragma unroll
     for (int sx = 0; sx < 2; ++sx)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float p0 = R.p[8 * sx + 2 * e], p1 = R.p[8 * sx + 2 * e + 1];
-            const uint32_t h0 = __float_as_uint(p0) & 0xffff0000u, h1 = __float_as_uint(p1) & 0xffff0000u;
-            R.phi[sx].u[e] = __builtin_amdgcn_perm(h1, h0, 0x07060302u);     // {h0 >> 16, h1 >> 16}
-            R.plo[sx].u[e] = pack_bf16(p0 - __uint_as_float(h0), p1 - __uint_as_float(h1));
+            pair.u = __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302u);     // {p0 >> 16, p1 >> 16}
+            R.phi[sx].u[e] = pair.u;
+            R.plo[sx].u[e] = pack_bf16(__builtin_amdgcn_fdot2_f32_bf16(pair.h, first.h, p0, false),
+                                       __builtin_amdgcn_fdot2_f32_bf16(pair.h, second.h, p1, false));
         }
 }
+
+// The blocks a wave fetches one after the other from one tensor: two transfers of 1 KB each, rows 8 wave .. 8 wave + 7.  The second
+// one's instruction offset moves its LDS and its memory address along, which its lane offset takes back, so that the LDS address
+// register m0 is written once; kBias keeps the lane offsets from falling below zero.
+struct BlockFetch {
+    static constexpr int kBias = 1024;
+    const char *at;          // kBias bytes ahead of the block that is fetched next (uniform)
+    uint32_t off[2];         // per-lane byte offset inside the block (+ kBias, resp. + kBias - 1024)
+    __device__ __forceinline__ void start(const char *head, int t0, const uint32_t (&doff)[2]) {
+        at = head + (size_t)t0 * kRowBytes - kBias;
+        off[0] = doff[0] + kBias;
+        off[1] = doff[1];
+    }
+    // The block fetched from now on has rows 0 .. rmax only: rows past them re-read row rmax.
+    __device__ __forceinline__ void cut(int rmax, int wave, int lane) {
+        asm volatile("");    // (a branch that is hardly ever taken, not selects in every step)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) off[n] -= (uint32_t)(max((wave * 2 + n) * 4 + (lane >> 4) - rmax, 0) * kRowBytes);
+    }
+    template <bool kOnce>
+    __device__ __forceinline__ void fetch(uint32_t lds, bool more) {         // `more`: another block follows this one
+        if constexpr (kOnce)
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 nt\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024 nt" ::"{m0}"(lds), "v"(off[0]), "v"(off[1]), "s"(at) : "memory");
+        else
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024" ::"{m0}"(lds), "v"(off[0]), "v"(off[1]), "s"(at) : "memory");
+        at += more ? kBlkBytes : 0;
+    }
+};
 
 // One pipeline step n of sweep 1 (PH = n mod 4 fixes every LDS slot at compile time):
 //   matrix cores: O^T += V^T P^T of block n-1, S^T = K Q^T of block n+1
@@ -162,15 +196,15 @@ __device__ __forceinline__ void pack_weights(Sweep1Regs &R) {
 // it; then V^T P^T and the weights.  Without kNeedO only the branch of the masks divides it.
 template <int PH, bool kNeedO, bool kStoreZ, bool kOnce>
 __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uint32_t lds0, int n, int t_begin,
-                                            int t_end, int t_last, int last_row, int vis, int n_plain, const char *kh, const char *vh,
-                                            const int (&koff)[8], const int (&voff)[4], const uint32_t (&kdoff)[2],
-                                            const uint32_t (&vdoff)[2], int wave, int lane, bool wave_active,
+                                            int t_end, int n_last, int n_cut, int rmax, int vis, int n_plain, BlockFetch &kf,
+                                            BlockFetch &vf, const char *vh,
+                                            const int (&koff)[8], const int (&voff)[4], int wave, int lane, bool wave_active,
                                             int2 *events, char *z_split, uint32_t z_off) {
     // K and V blocks live in rings of four 8 KB slots each (block j in slot j mod 4): K block
     // n+1 and V block n-1, both started three steps ago, are waited for here while the two
     // younger batches stay in flight; then K block n+4 and V block n+2 start in the slots
     // the previous step has finished with.  Past the end of the split every batch has as many transfers, but they fetch
-    // the split's last block again, from the L2 (`t_last`; nothing of it counts a second time): the next split's rows were
+    // the split's last block `n_last` again, from the L2 (nothing of it counts a second time): the next split's rows were
     // three K and two V blocks from memory for nothing, a third of what a split of 256 tokens reads.
     constexpr int kKBase = ((PH + 1) & 3) * kBlkBytes;                  // block n+1
     constexpr int kVBase = (4 + ((PH + 3) & 3)) * kBlkBytes;            // block n-1
@@ -184,9 +218,12 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
     else if (kStoreZ && wave_active && n == 1 && 32 < t_end - t_begin) wait_async_loads_keep<2 * kBatch + 4>();
     else wait_async_loads_keep<2 * kBatch>();
     __syncthreads();
-    block_load_async<kXor16, kOnce>(kh, min(t_begin + (n + 4) * 32, t_last), last_row, lds0 + PH * kBlkBytes, wave, lane, kdoff);
-    if (kNeedO)
-        block_load_async<kRot4, kOnce>(vh, min(t_begin + (n + 2) * 32, t_last), last_row, lds0 + (4 + ((PH + 2) & 3)) * kBlkBytes, wave, lane, vdoff);
+    if (n + 4 == n_cut) kf.cut(rmax, wave, lane);                      // uniform: the sequence's last rows
+    kf.fetch<kOnce>(lds0 + PH * kBlkBytes + wave * 2048, n + 4 < n_last);
+    if (kNeedO) {
+        if (n + 2 == n_cut) vf.cut(rmax, wave, lane);
+        vf.fetch<kOnce>(lds0 + (4 + ((PH + 2) & 3)) * kBlkBytes + wave * 2048, n + 2 < n_last);
+    }
     if (!wave_active) return;
     if (kStoreZ && n * 32 < t_end - t_begin && z_off != ~0u) {      // raw q.k of block n for score_few_rows
 #pragma unroll
@@ -434,10 +471,18 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
 
     const int n_total = (n_blk + 3) & ~3;
     const int n_plain = max(vis_min + 1 - t_begin, 0) / 32;   // leading blocks every row of this wave sees in full
+    // What the steps fetch: K from block 4, V from block 2 on.  A last block with rows past the sequence's end (row rmax) is cut
+    // where it comes up, block n_cut, or here.
+    const int rmax = len - 1 - t_last, n_cut = rmax < 31 ? n_blk - 1 : -1;
+    BlockFetch kf, vf;
+    kf.start(kh, min(t_begin + 4 * 32, t_last), kdoff);
+    vf.start(vh, min(t_begin + 2 * 32, t_last), vdoff);
+    if (n_cut >= 0 && n_cut < 4) kf.cut(rmax, wave, lane);
+    if (n_cut >= 0 && n_cut < 2) vf.cut(rmax, wave, lane);
     // (kStoreZ: at most 32 rows, so they are the first wave's)
     char *z_split = (char *)(z + (size_t)bg * M * z_stride + t_begin);
     const uint32_t z_off = kStoreZ && row_valid ? (uint32_t)row * z_stride * 4 + 16 * half : ~0u;
-#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, t_last, len - 1, vis, n_plain, kh, vh, koff, voff, kdoff, vdoff, wave, lane, wave_active, events, z_split, z_off
+#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, n_blk - 1, n_cut, rmax, vis, n_plain, kf, vf, vh, koff, voff, wave, lane, wave_active, events, z_split, z_off
     for (int n = 0; n < n_total; n += 4) {
         sweep1_step<0, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;
         sweep1_step<1, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;
