@@ -244,17 +244,17 @@ __global__ __launch_bounds__(kPieceThreads) void evict_pieces(uint4 *__restrict_
     const int bg = blockIdx.x % heads, piece = blockIdx.x / heads, tid = threadIdx.x;
     const int row_pieces = evict_row_pieces(N, row_vec * 8);
     const int len = seq_len_of(lens, ragged, bg / Hkv, N), budget = len - 1;     // rows that remain
-    unsigned long long low = ~0ull;
-    for (int i = tid; i < n_lowest; i += kPieceThreads) {
-        const unsigned long long c = lowest[(size_t)bg * n_lowest + i];
-        low = c < low ? c : low;
-    }
+    unsigned long long low = tid < n_lowest ? lowest[(size_t)bg * n_lowest + tid] : ~0ull;       // (looked at in evicted_token)
     auto arrive = [&]() {                                        // of everything read so far, by the whole workgroup
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     };
     // The lowest candidate of the head; ends at a barrier behind which everything read so far has arrived.
     auto evicted_token = [&]() {
+        for (int i = tid + kPieceThreads; i < n_lowest; i += kPieceThreads) {
+            const unsigned long long c = lowest[(size_t)bg * n_lowest + i];
+            low = c < low ? c : low;
+        }
         low = wave_min(low);
         if ((tid & 63) == 0) low_w[tid >> 6] = low;
         arrive();

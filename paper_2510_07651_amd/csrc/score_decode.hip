@@ -69,37 +69,55 @@ __device__ __forceinline__ float group_sum(float x) {
     if (kLanes == 16) x += dpp_pair<0x140>(x);
     return x;
 }
-// Sums over the token slots of a wave (the lanes of equal position in their group), for kN values at once: each level
-// adds two values across lane pairs with one register exchange and leaves half of the values in each half of the pair.
-// Lane l then holds the sums of values i * (64 / kLanes) + (l / kLanes, its two or three bits taken highest first) in x[i].
-template <int kLanes, int kN>
-__device__ __forceinline__ void slot_sums(float (&x)[kN]) {
-    constexpr int kSlots = 64 / kLanes;
-    static_assert(kSlots == 4 || kSlots == 8, "head_dim 128 or 64");
+// x of the lane whose index differs in bit 2 alone: the mirror image inside 8 lanes, then inside 4.
+__device__ __forceinline__ float xor4(float x) { return dpp_pair<0x1B>(dpp_pair<0x141>(x)); }
+// Sums over the lanes that share a token for the kG rows at once: lane `sub` of them ends up with the sum of row own_row(sub),
+// and lanes of the same row with the same bits.  Each of the first levels adds two rows across lane pairs with one exchange and
+// leaves one of them in each lane of the pair (10 instructions for four rows of 16 lanes; 16 with every sum in every lane).
+template <int kG>
+__device__ __forceinline__ int own_row(int sub) { return sub & (kG - 1); }
+template <int kLanes, int kG>
+__device__ __forceinline__ float row_sums(float (&x)[kG], int sub) {
+    if constexpr (kG >= 2) {
 #pragma unroll
-    for (int i = 0; i < kN / 2; ++i) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[2 * i]), __float_as_uint(x[2 * i + 1]), false, false);
-        x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-#pragma unroll
-    for (int i = 0; i < kN / 4; ++i) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[2 * i]), __float_as_uint(x[2 * i + 1]), false, false);
-        x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    if (kSlots == 8) {
-        // the two groups of 8 inside a row of 16: each keeps one of two values and gives the other away
-        const bool high = (threadIdx.x & 8) != 0;
-#pragma unroll
-        for (int i = 0; i < kN / 8; ++i) {
-            const float give = high ? x[2 * i] : x[2 * i + 1], keep = high ? x[2 * i + 1] : x[2 * i];
-            x[i] = keep + dpp_pair<0x128>(give);
+        for (int i = 0; i < kG / 2; ++i) {
+            const float keep = sub & 1 ? x[2 * i + 1] : x[2 * i], give = sub & 1 ? x[2 * i] : x[2 * i + 1];
+            x[i] = keep + dpp_pair<0xB1>(give);
         }
+    } else {
+        x[0] += dpp_pair<0xB1>(x[0]);
     }
+    if constexpr (kG >= 4) {
+#pragma unroll
+        for (int i = 0; i < kG / 4; ++i) {
+            const float keep = sub & 2 ? x[2 * i + 1] : x[2 * i], give = sub & 2 ? x[2 * i] : x[2 * i + 1];
+            x[i] = keep + dpp_pair<0x4E>(give);
+        }
+    } else {
+        x[0] += dpp_pair<0x4E>(x[0]);
+    }
+    if constexpr (kG >= 8) {
+        const float keep = sub & 4 ? x[1] : x[0], give = sub & 4 ? x[0] : x[1];
+        x[0] = keep + xor4(give);
+        if (kLanes == 16) x[0] += dpp_pair<0x128>(x[0]);
+    } else if (kLanes == 16) {
+        x[0] += dpp_pair<0x128>(x[0]);
+        x[0] += dpp_pair<0x124>(x[0]);                  // (the two halves of the row are alike: the lane 4 further is that of bit 2)
+    } else {
+        x[0] += xor4(x[0]);
+    }
+    return x[0];
 }
-// Which of the kSlots values of a batch a lane ends up with in slot_sums.
-template <int kLanes>
-__device__ __forceinline__ int slot_sums_index(int lane) {
-    return kLanes == 16 ? 2 * ((lane >> 4) & 1) + (lane >> 5) : 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + (lane >> 5);
+typedef __bf16 bf16_pair __attribute__((ext_vector_type(2)));
+typedef float f32_quad __attribute__((ext_vector_type(4)));
+// acc + the dot product of 8 bf16 values each (exact products, fp32 sums).
+__device__ __forceinline__ float dot8(const uint4 a, const uint4 b, float acc) {
+    union { uint4 w; bf16_pair h[4]; } x, y;
+    x.w = a;
+    y.w = b;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_fdot2_f32_bf16(x.h[e], y.h[e], acc, false);
+    return acc;
 }
 // (larger value, lower index on ties) of two candidates.
 __device__ __forceinline__ void take_better(float &bm, int &ba, float om, int oa) {
@@ -121,11 +139,13 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
     int Hkv, int ragged, Lens lens, int splits, float *__restrict__ z_buf, float4 *__restrict__ part_head,
     float *__restrict__ part_vec, uint4 *__restrict__ edge_rows) {
     constexpr int kLpt = kD / 8;        // lanes per token row
-    constexpr int kSlots = 64 / kLpt;   // token rows per wave and step
     __shared__ float red_m[kWaves * kG];
     __shared__ int red_a[kWaves * kG];
     __shared__ float red_l[kWaves * kG];
-    __shared__ float red_o[kNeedO ? kWaves * kG * kD : 1];
+    // Sums of P V by matrix op: [wave, and with 8 lanes per token its even or odd tokens][channel j of a lane's 8][lane][row]; the
+    // padding between two j takes the closing sum's reads to as many banks.
+    constexpr int kHalves = 16 / kLpt, kChannel = kLpt * kG + 8, kPartSums = kWaves * kHalves;
+    __shared__ __attribute__((aligned(16))) float red_o[kNeedO ? kPartSums * 8 * kChannel : 4];
     __shared__ float top_v[kNeedO ? kG * kD : 1];   // V rows of the top tokens
 
     const int bh = blockIdx.x, b = bh / Hkv, split = blockIdx.y;
@@ -193,117 +213,117 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
         }
     };
 
-    float qr[kG][8];
-#pragma unroll
-    for (int r = 0; r < kG; ++r) unpack8(qw[r], qr[r]);
-    float z[kSteps][kG];
+    // From here on lane `sub` of a token's lanes looks after row own: one logit, one weight, one sum per lane and token.
+    const int own = own_row<kG>(sub);
+    float z[kSteps];
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
         const int p = token_of<kD>(t0, u, wave, slot);
-        float kk[8];
-        unpack8(kw[u], kk);
-        float mine = 0.f;
+        float dot[kG];
 #pragma unroll
-        for (int r = 0; r < kG; ++r) {
-            float dot = 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) dot = fmaf(qr[r][j], kk[j], dot);
-            z[u][r] = group_sum<kLpt>(dot) * scale;
-            if (sub == r) mine = z[u][r];
-        }
-        if (p < t1 && sub < kG) z_buf[((size_t)bh * N + p) * kG + sub] = mine;
+        for (int r = 0; r < kG; ++r) dot[r] = dot8(qw[r], kw[u], 0.f);
+        z[u] = row_sums<kLpt, kG>(dot, sub) * scale;
+        if (p < t1 && sub < kG) z_buf[((size_t)bh * N + p) * kG + sub] = z[u];
     }
 
     // Row maxima of the range and the lowest token attaining each.
-    float m[kG];
-    int top[kG];
-#pragma unroll
-    for (int r = 0; r < kG; ++r) {
+    {
         float bm = -INFINITY;
         int ba = 0x7fffffff;
 #pragma unroll
         for (int u = 0; u < kSteps; ++u) {          // tokens ascend with u: a strict compare keeps the lowest
             const int p = token_of<kD>(t0, u, wave, slot);
-            if (p < t1 && z[u][r] > bm) { bm = z[u][r]; ba = p; }
+            if (p < t1 && z[u] > bm) { bm = z[u]; ba = p; }
         }
         // over the wave's token slots: the value first, then the lowest token that has it
-        const float own = bm;
+        const float mine = bm;
         if (kLpt == 8) bm = fmaxf(bm, dpp_pair<0x128>(bm));
         bm = across_rows<MaxOp>(bm);
-        uint32_t at = own == bm ? (uint32_t)ba : 0x7fffffffu;
+        uint32_t at = mine == bm ? (uint32_t)ba : 0x7fffffffu;
         if (kLpt == 8) at = MinOp()(at, dpp_pair<0x128>(at));
         at = across_rows<MinOp>(at);
-        if (lane == 0) { red_m[r * kWaves + wave] = bm; red_a[r * kWaves + wave] = (int)at; }
+        if (lane < kG) { red_m[lane * kWaves + wave] = bm; red_a[lane * kWaves + wave] = (int)at; }
     }
     __syncthreads();
-    // over the waves: one row of 16 lanes per window row
+    // over the waves: one row of 16 lanes per window row (four at a time; fewer rows than four repeat)
+    constexpr int kQuads = (kG + 3) / 4;
+    float row_m[kQuads];
+    int row_top[kQuads];
 #pragma unroll
-    for (int r0 = 0; r0 < kG; r0 += 4) {
-        const int e = kG >= 4 ? r0 * kWaves + lane : lane % (kG * kWaves);
-        const float own = red_m[e], bm = row16_reduce<MaxOp>(own);
-        const uint32_t at = row16_reduce<MinOp>(own == bm ? (uint32_t)red_a[e] : 0x7fffffffu);
+    for (int i = 0; i < kQuads; ++i) {
+        const int e = kG >= 4 ? 4 * i * kWaves + lane : lane % (kG * kWaves);
+        const float mine = red_m[e];
+        row_m[i] = row16_reduce<MaxOp>(mine);
+        row_top[i] = min((int)row16_reduce<MinOp>(mine == row_m[i] ? (uint32_t)red_a[e] : 0x7fffffffu), t1 - 1);   // (no logit was a number: any token)
+    }
+    float m = 0.f;
+    int top = 0;
 #pragma unroll
-        for (int r = 0; r < 4 && r0 + r < kG; ++r) {
-            m[r0 + r] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(bm), 16 * r));
-            top[r0 + r] = min(__builtin_amdgcn_readlane((int)at, 16 * r), t1 - 1);   // (no logit was a number: any token)
-        }
+    for (int i = 0; i < kQuads; ++i) {
+        const int from = 16 * (own & 3) * 4;
+        const float mi = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(row_m[i])));
+        const int ti = __builtin_amdgcn_ds_bpermute(from, row_top[i]);
+        if (i == 0 || own >= 4 * i) { m = mi; top = ti; }
     }
 
-    // Sums of exp(z - m) and of exp(z - m) v over the range without the top token.
-    float lsum[kG], acc[kG * 8];
+    // Sums of exp(z - m) and of exp(z - m) v over the range without the top token.  The second one is a matrix op per channel:
+    // its first operand's row is a lane's own row, its four k are the wave's token slots, and a lane's channel j is a column of the
+    // second; fp32 throughout.  With 8 lanes per token a row of 16 lanes has an even and an odd token: rows 0 to 7 are the even
+    // ones' weights, 8 to 15 the odd ones', and of the product only what meets its own half counts.
+    // (Weights of every row in every lane, products on the vector ALUs and sums across slots by register exchanges were four
+    // times the instructions of a wave, and four waves share a SIMD: TODO.)
+    float lsum = 0.f;
+    f32_quad acc[8];
 #pragma unroll
-    for (int r = 0; r < kG; ++r) {
-        lsum[r] = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[r * 8 + j] = 0.f;
-    }
+    for (int j = 0; j < 8; ++j) acc[j] = f32_quad{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
         const int p = token_of<kD>(t0, u, wave, slot);
-        if (p < t1) {
+        const bool is_top = p == top;
+        const float w = p < t1 && !is_top ? __expf(z[u] - m) : 0.f;
+        lsum += w;
+        if (kNeedO) {
             float vv[8];
-            if (kNeedO) unpack8(vw[u], vv);
+            unpack8(vw[u], vv);
+            const float a = sub < kG ? w : 0.f;
 #pragma unroll
-            for (int r = 0; r < kG; ++r) {
-                const bool is_top = p == top[r];
-                const float w = is_top ? 0.f : __expf(z[u][r] - m[r]);
-                lsum[r] += w;
-                if (kNeedO) {
+            for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, vv[j], acc[j], 0, 0, 0);
+            if (__any(is_top)) {                    // uniform: the wave holds some row's top token
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[r * 8 + j] = fmaf(w, vv[j], acc[r * 8 + j]);
-                    if (is_top) {
-                        *(float4 *)(top_v + r * kD + sub * 8) = make_float4(vv[0], vv[1], vv[2], vv[3]);
-                        *(float4 *)(top_v + r * kD + sub * 8 + 4) = make_float4(vv[4], vv[5], vv[6], vv[7]);
-                    }
+                for (int r = 0; r < kG; ++r) {
+                    if (p != __builtin_amdgcn_readlane(row_top[r / 4], 16 * (r % 4))) continue;
+                    *(float4 *)(top_v + r * kD + sub * 8) = make_float4(vv[0], vv[1], vv[2], vv[3]);
+                    *(float4 *)(top_v + r * kD + sub * 8 + 4) = make_float4(vv[4], vv[5], vv[6], vv[7]);
                 }
             }
         }
     }
-#pragma unroll
-    for (int r = 0; r < kG; ++r) {
-        float l = lsum[r];                          // (the kLpt lanes of a slot hold the same sum)
-        if (kLpt == 8) l += dpp_pair<0x128>(l);
-        l = across_rows<SumOp>(l);
-        if (lane == 0) red_l[r * kWaves + wave] = l;
-    }
+    if (kLpt == 8) lsum += dpp_pair<0x128>(lsum);
+    lsum = across_rows<SumOp>(lsum);
+    if (lane < kG) red_l[lane * kWaves + wave] = lsum;
     if (kNeedO) {
-        slot_sums<kLpt>(acc);
-        const int c0 = slot_sums_index<kLpt>(lane);
+        // rows 4 (lane / 16) .. + 3 of the product, column lane % 16
+        const int quad = lane >> 4, r0 = 4 * (kHalves == 1 ? quad : quad & 1), odd = kHalves == 1 ? 0 : (lane >> 3) & 1;
+        if (r0 < kG && (kHalves == 1 || quad >> 1 == odd)) {
+            float *to = red_o + (wave * kHalves + odd) * 8 * kChannel + sub * kG + r0;
 #pragma unroll
-        for (int i = 0; i < kG * 8 / kSlots; ++i) {
-            const int e = i * kSlots + c0, r = e / 8, j = e % 8;
-            red_o[(wave * kG + r) * kD + j * kLpt + sub] = acc[i];      // (column-of-eight major: no bank conflicts)
+            for (int j = 0; j < 8; ++j) {
+                if constexpr (kG >= 4) *(f32_quad *)(to + j * kChannel) = acc[j];
+                else
+#pragma unroll
+                    for (int r = 0; r < kG; ++r) to[j * kChannel + r] = acc[j][r];
+            }
         }
     }
     __syncthreads();
-    if (wave < (kG + 3) / 4) {                      // one row of 16 lanes per window row again
+    if (wave < kQuads) {                            // one row of 16 lanes per window row again
         const int r = wave * 4 + (lane >> 4);
         const float l = row16_reduce<SumOp>(r < kG ? red_l[r * kWaves + (lane & 15)] : 0.f);
-        float mr = m[0];
-        int tr = top[0];
+        float mr = row_m[0];
+        int tr = row_top[0];
 #pragma unroll
-        for (int x = 1; x < kG; ++x)
-            if (r == x) { mr = m[x]; tr = top[x]; }
+        for (int i = 1; i < kQuads; ++i)
+            if (wave == i) { mr = row_m[i]; tr = row_top[i]; }
         if ((lane & 15) == 0 && r < kG) head[r] = make_float4(mr, l, __int_as_float(tr), 0.f);
     }
     if (!kNeedO) {
@@ -311,11 +331,11 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
         return;
     }
     float *vec = part_vec + ((size_t)bh * splits + split) * kG * 2 * kD;
-    for (int e = threadIdx.x; e < kG * kD; e += kThreads) {
-        const int r = e / kD, c = e % kD, at = (c % 8) * kLpt + c / 8;
-        float o = red_o[r * kD + at];
+    for (int e = threadIdx.x; e < kG * kD; e += kThreads) {         // (16 channels of each row side by side)
+        const int r = (e >> 4) % kG, c = e / (16 * kG) * 16 + (e & 15), at = (c % 8) * kChannel + c / 8 * kG + r;
+        float o = red_o[at];
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) o += red_o[(w * kG + r) * kD + at];
+        for (int w = 1; w < kPartSums; ++w) o += red_o[w * 8 * kChannel + at];
         vec[r * 2 * kD + c] = o;
         vec[r * 2 * kD + kD + c] = o + top_v[r * kD + c];
     }
