@@ -630,20 +630,32 @@ __global__ __launch_bounds__(256) void mfma_combine(const float *__restrict__ pa
 // trips (4 heads x 128K, 112 rows: 47 us, 14 us in eight groups).
 template <int kGroups, int kBatch, typename Lens>
 __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combine_hold(
-    const uint16_t *__restrict__ v, const float *__restrict__ part_ml, const float *__restrict__ part_o, int N, int W, int Hq,
-    int Hkv, int ragged, Lens lens, int split_len, int m_pad, uint16_t *__restrict__ out_bf16, float *__restrict__ row_const,
+    const uint16_t *__restrict__ v, const float *__restrict__ part_ml, const float *__restrict__ part_o, int N, int W, int M,
+    int Hkv, int ragged, Lens lens, int split_len, int splits, int m_pad, uint16_t *__restrict__ out_bf16, float *__restrict__ row_const,
     float *__restrict__ special) {
     const int group = threadIdx.x >> 5, row = kGroups == 1 ? blockIdx.x * 4 + group : blockIdx.x, bg = blockIdx.y;
     const int first = kGroups == 1 ? 0 : group * kBatch;  // this group's first split
     constexpr int kStride = kBatch * kGroups;
-    const int b = bg / Hkv, G = Hq / Hkv, M = G * W;
-    const int len = seq_len_of(lens, ragged, b, N);
+    // (Equal lengths: every head has `splits`.  The quotients that ragged ones take are some 25 instructions each ahead of the first
+    // load: 1.9 of the kernel's 6.4 us, 8 heads x 128 rows x 8192, with them and with 64-bit addresses per load; 1.45 of 6.0 so.)
+    int len = N, live_splits = splits, slot0 = bg * splits;
+    if (ragged) {
+        const int b = bg / Hkv;
+        len = lens.len[b];
+        live_splits = (len + split_len - 1) / split_len;
+        slot0 = split_slot(lens, ragged, b, bg % Hkv, N, Hkv, split_len);
+    }
     const int sub = threadIdx.x & 31, dd = sub * 4;   // this lane's elements dd .. dd + 3
     const size_t crow = (size_t)bg * m_pad + row;
-    const int slot0 = split_slot(lens, ragged, b, bg % Hkv, N, Hkv, split_len);
     const size_t lo_plane = (size_t)gridDim.y * m_pad * kD;
     const bool live = row < M;                        // the same for the 32 lanes of a row
-    const int live_splits = (len + split_len - 1) / split_len;
+    // Records of the row: byte offsets from the head's first one, a record's sums 32 times as far as its four words.  Splits past
+    // the last one re-read it.
+    const char *ml_head = (const char *)part_ml + (size_t)slot0 * m_pad * 16, *po_head = (const char *)part_o + (size_t)slot0 * m_pad * (kD * 4);
+    const uint32_t split_bytes = (uint32_t)m_pad * 16, row_at = (uint32_t)row * 16, last_at = row_at + (uint32_t)(live_splits - 1) * split_bytes;
+    auto record_at = [&](int s0, int j) { return min(row_at + (uint32_t)s0 * split_bytes + j * split_bytes, last_at); };
+    auto record = [&](uint32_t at) { return *(const float4 *)(ml_head + at); };
+    auto sums = [&](uint32_t at) { return *(const float4 *)(po_head + (size_t)at * 32 + sub * 16); };
     const float c2 = kLog2e * kInvSqrtD;
     const uint16_t *vg = v + (size_t)bg * N * kD;
     // First the common reference T (no sum lies more than the lazy-rescale slack above its own
@@ -659,10 +671,10 @@ __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combin
     float4 ml[kBatch], po[kBatch];
     uint2 vo[kBatch];
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) ml[j] = ((const float4 *)part_ml)[(size_t)(slot0 + min(first + j, live_splits - 1)) * m_pad + row];
+    for (int j = 0; j < kBatch; ++j) ml[j] = record(record_at(first, j));
     asm volatile("" ::: "memory");                    // (else the sums are asked for between the records)
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) po[j] = *(const float4 *)(part_o + ((size_t)(slot0 + min(first + j, live_splits - 1)) * m_pad + row) * kD + dd);
+    for (int j = 0; j < kBatch; ++j) po[j] = sums(record_at(first, j));
     auto candidate_values = [&](int s0) {             // (padded rows: zero queries, nothing of theirs is used)
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
@@ -681,8 +693,7 @@ __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combin
     for (int s0 = first + kStride; s0 < live_splits; s0 += kStride) {
         float4 mm[kBatch];
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j)
-            mm[j] = ((const float4 *)part_ml)[(size_t)(slot0 + min(s0 + j, live_splits - 1)) * m_pad + row];
+        for (int j = 0; j < kBatch; ++j) mm[j] = record(record_at(s0, j));
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             if (s0 + j >= live_splits) continue;
@@ -712,9 +723,8 @@ __global__ __launch_bounds__(kGroups == 1 ? 128 : 32 * kGroups) void mfma_combin
         if (s0 > first) {
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {         // (the records are in cache from the pass above)
-                const size_t prow = (size_t)(slot0 + min(s0 + j, live_splits - 1)) * m_pad + row;
-                ml[j] = ((const float4 *)part_ml)[prow];
-                po[j] = *(const float4 *)(part_o + prow * kD + dd);
+                ml[j] = record(record_at(s0, j));
+                po[j] = sums(record_at(s0, j));
             }
             candidate_values(s0);
         }
@@ -1541,7 +1551,7 @@ static hipError_t launch_with(const ScoreArgs &a, const Lens &lens, const ScoreW
         const int combine_rows = ws.keep_z ? a.G * a.W : ws.m_pad;
 #define OBC_COMBINE(groups, batch, rows)                                                                               \
     mfma_combine_hold<groups, batch><<<dim3((combine_rows + rows - 1) / rows, a.B * a.Hkv), dim3(32 * groups * rows), 0, stream>>>(            \
-        (const uint16_t *)a.v, part_ml, part_o, a.N, a.W, a.Hq, a.Hkv, a.ragged, lens, ws.split_len, ws.m_pad,         \
+        (const uint16_t *)a.v, part_ml, part_o, a.N, a.W, a.G * a.W, a.Hkv, a.ragged, lens, ws.split_len, ws.splits, ws.m_pad,         \
         (uint16_t *)(base + ws.out_bf16), (float *)(base + ws.row_const), (float *)(base + ws.special))
         if (need_o && ws.splits <= 16) OBC_COMBINE(1, 16, 4);      // (m_pad: a multiple of 32)
         else if (need_o && ws.splits <= 32) OBC_COMBINE(4, 8, 1);
