@@ -410,21 +410,27 @@ def obc_decode_step(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scores: t
                     workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Accumulates the new row's scores, drops the lowest-scored unprotected token of every head and closes the gap in
     k, v and scores, all in place.  Returns the dropped positions [B,Hkv] int32."""
-    _require_cuda(q, k, v, scores)
+    # (A call per layer and token, as long on the host as on the GPU: no loop over the tensors, nothing asked twice.)
+    if not (q.is_cuda and k.is_cuda and v.is_cuda and scores.is_cuda and q.is_contiguous() and k.is_contiguous()
+            and v.is_contiguous() and scores.is_contiguous()):
+        raise ValueError("tensors must be contiguous and on the GPU")
     B, Hq, W, d = q.shape
-    _, Hkv, N, _ = k.shape
-    if W != 1 or v.shape != k.shape or tuple(scores.shape) != (B, Hkv, N) or scores.dtype != torch.float32:
+    kv_shape = k.shape
+    _, Hkv, N, _ = kv_shape
+    if W != 1 or v.shape != kv_shape or scores.shape != (B, Hkv, N) or scores.dtype is not torch.float32:
         raise ValueError("q must be [B,Hq,1,d], k, v [B,Hkv,N,d], scores [B,Hkv,N] float32")
     var = VARIANT_CODES[variant] if isinstance(variant, str) else int(variant)
-    dt = _dtype_code(q)
+    dt = OBC_BF16 if q.dtype is torch.bfloat16 else _dtype_code(q)
     if workspace is None:
         workspace = torch.empty(obc_decode_step_workspace_bytes(B, N, Hq, Hkv, d, dt, var), dtype=torch.uint8, device=q.device)
     if evicted is None:
         evicted = torch.empty((B, Hkv), dtype=torch.int32, device=q.device)
-    _require_cuda(evicted, workspace)
-    rc = load_library().obc_decode_step(q.data_ptr(), k.data_ptr(), v.data_ptr(), scores.data_ptr(), evicted.data_ptr(), N,
-                                        Hq, Hkv, d, var, B, dt, _lens_arg(seq_lens, B), int(num_sinks), int(num_recent),
-                                        workspace.data_ptr(), workspace.numel(), _stream_ptr(q))
+    if not (evicted.is_cuda and workspace.is_cuda and evicted.is_contiguous() and workspace.is_contiguous()):
+        raise ValueError("tensors must be contiguous and on the GPU")
+    rc = (_lib or load_library()).obc_decode_step(
+        q.data_ptr(), k.data_ptr(), v.data_ptr(), scores.data_ptr(), evicted.data_ptr(), N, Hq, Hkv, d, var, B, dt,
+        None if seq_lens is None else _lens_arg(seq_lens, B), int(num_sinks), int(num_recent), workspace.data_ptr(),
+        workspace.numel(), _stream_ptr(q))
     if rc != OBC_OK:
         raise ObcError(rc, "obc_decode_step")
     return evicted
