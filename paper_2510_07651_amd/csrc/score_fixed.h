@@ -38,7 +38,7 @@
 // millions of pairs: normal elements, channels larger than the others by up to 2^26, elements over 20 binades; there bf16
 // values, which keep fewer bits, reach 2^-30).  The norms it goes into are as good as an fp32 rounding where they are above
 // 2^-4 2^E; where a pair that counts has a smaller one (a v_p that is nearly o_i), the wave forms its 16 x 16 dot products
-// again in fp64 (fixed_score's loop), from where on they are what plain_score computes.
+// again in fp64 (block_dots), from where on they are what plain_score computes.
 // Sums in fp32 cannot stand in for this: with three bf16 pieces each, six products and three accumulators on the bf16 matrix cores the
 // kernel took 28 / 32 us instead of 30 / 40 (fp32, d = 128, 8111 tokens / bf16, d = 64, 16384), but where values share a large channel a
 // rounding of v . o is 32 times that in a distance just above the line: errors of single distances, some 10^3 tokens that share a channel
@@ -52,13 +52,18 @@
 //
 // What bounds them.  blocked_logits: the fp64 matrix cores, busy 64 % of the kernel.  digit_sweep: vector ALUs and matrix cores, a wave
 // using one after the other (some 18 instructions put a pair's levels together, check and scale them, some 9 take an element apart, some
-// 20 make its weight and the weight's pieces), all four waves of a SIMD at the same stage.  fixed_score: the vector ALUs, 83
-// instructions per 64 pairs (63 for bf16 values): putting a dot product together about 12, the norms and the closeness test
-// in fp64, and taking an element apart about 15 (7 for bf16), paid once per workgroup of up to 128 rows; matrix cores busy
-// 26 %.
+// 20 make its weight and the weight's pieces), all four waves of a SIMD at the same stage, and waits, half of the waves' time: with
+// 7 % fewer vector instructions (maxima by blocks of tokens, weights' pieces by dot products) it took as long, as it did without a
+// branch per weight and with the matrix phases at a higher wave priority.  fixed_score: the vector ALUs, 75 instructions per 64
+// pairs (55 for bf16 values): putting a dot product together about 10, its weight 10, the norms and the closeness test 13, mostly in
+// fp64, and taking an element apart about 15 (7 for bf16), paid once per workgroup of up to 128 rows; matrix cores busy 27 %.  The
+// blocks in which a row's view ends or its top stands, few, have code of their own: in the others no pair is masked.  With that, the
+// token's and the row's share of the closeness test multiplied in fp32, the sums over the rows in half as many steps and a
+// record of 40 bytes (eight more instructions per 64 pairs, and banks met twice, before) 38.6 -> 34.7 us (bf16, d = 64, 16384) and
+// 29.5 -> 28.2 (fp32, d = 128, 8111).
 // Kernel times, 32/8 heads, joint, two sets of inputs in turn, in us: digit_sweep (as two kernels, logits / weights) / merge / scores
-//   fp32, d = 128,  8111 tokens   59.0 (37.2 / 28.2) / 8.7 / 29.2
-//   bf16, d = 64,  16384 tokens   47.2 (29.3 / 23.3) / 6.0 / 38.3
+//   fp32, d = 128,  8111 tokens   59.9 (37.2 / 28.2) / 8.6 / 28.2
+//   bf16, d = 64,  16384 tokens   48.0 (29.3 / 23.3) / 6.0 / 34.7
 // Two kernels met between them: the maxima of all ranges first.  Whole calls, blocked_logits and fixed_weights / digit_sweep (with as many
 // splits as fill the chip where the calls' heads pass in several launches), joint, inputs that change from call to call, us:
 //   fp32, d = 128, 4 x 8 heads x 128 rows x 8000   406 / 317     bf16, d = 64, 8 x 8 heads x 128 rows x 3000   188 / 140
@@ -107,6 +112,8 @@ __device__ __forceinline__ uint32_t max_abs(const float (&x)[4]) {
 __device__ __forceinline__ int max_exponent(uint32_t amax) { return (int)(amax >> 23) - 126; }
 // A row's share of the unit of a dot product, 2^(e - 18); NaN where an element was infinite or not a number.
 __device__ __forceinline__ double row_unit(int e) { return e > 128 ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, e - 18); }
+// Its share of the least norm that the digits are good for, 2^-4 2^E (fp32 holds it, as a subnormal number at worst).
+__device__ __forceinline__ float least_share(double unit) { return (float)(unit * 0x1p16); }
 
 // The last four planes of digits from four words whose bytes are digits plus 128.
 template <int K>
@@ -290,9 +297,9 @@ struct TokenTile {
         }
         if (sizeof(T) == 4 && threadIdx.x % 64 == 0) cut_s[threadIdx.x / 64] = any_cut;
     }
-    // Digits and units into LDS and, where asked for, the rows' norms: ||v||^2 (2) or ||v||_1 (1).
+    // Digits, units and their shares of a closeness test into LDS and, where asked for, the rows' norms: ||v||^2 (2) or ||v||_1 (1).
     template <bool kWithDigits, int kNorm>
-    __device__ __forceinline__ void store_digits(char *digits, double *units, double *norms) const {
+    __device__ __forceinline__ void store_digits(char *digits, double *units, float *least, double *norms) const {
         constexpr int K = kDigits<T>;
         int thread = threadIdx.x;
         asm volatile("" : "+v"(thread));                     // (addresses anew for every tile: registers)
@@ -321,7 +328,10 @@ struct TokenTile {
                     if constexpr (kPer == 4) *(uint32_t *)at = p[0][k];
                     else *(uint2 *)at = make_uint2(p[0][k], p[1][k]);
                 }
-                if (c == 0) units[r0 + i * kStep] = row_unit(e);
+                if (c == 0) {
+                    units[r0 + i * kStep] = row_unit(e);
+                    least[r0 + i * kStep] = least_share(row_unit(e));
+                }
             }
             if (kNorm != 0) {
                 double s = 0.0;
@@ -558,7 +568,6 @@ __device__ __forceinline__ void three_pieces(float a, float b, uint32_t (&p)[3])
         b -= __uint_as_float(p[i] & 0xffff0000u);
     }
 }
-
 // Tokens of a tile of values: 32 for every part, or 64 where a tile would have fewer 16-byte pieces than threads.
 template <typename T, int D, int kRb>
 constexpr int kWeightTile = 16 / kRb * 32 * D * (int)sizeof(T) >= kWeightThreads * 16 ? 16 / kRb * 32 : 16 / kRb * 64;
@@ -909,6 +918,34 @@ __global__ __launch_bounds__(kWeightThreads, 4) void digit_sweep(const T *__rest
 // tokens 4 g .. 4 g + 3 of the 16 at hand.  A workgroup takes its tokens against one chunk of rows after the other.
 // ------------------------------------------------------------------------------------
 constexpr int kScoreTokens = 512;              // most tokens of a workgroup
+// What it needs of a row for every pair (40 bytes: the 16 rows of a read meet every bank once), and what for few of them.
+struct ScoreRow {
+    float m, inv_l;
+    double oo;
+    double unit;                 // -2 times the unit of o_i's digits
+    float least;                 // the row's share of the closeness test
+    int top, last, unused;
+};
+struct ScoreTop { float dk, dj; };
+
+// Sums of four registers over each row of 16 lanes: lanes 4 i .. 4 i + 3 of the row get that of x_i.  (Eight additions instead of sixteen:
+// the first two rounds leave half as many registers each.  The waits are those of a data-parallel read of what was just written.)
+__device__ __forceinline__ float four_sums(float x0, float x1, float x2, float x3) {
+    asm volatile("s_nop 1\n"
+                 "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n"
+                 "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n"
+                 "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+                 "v_add_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n"
+                 "s_nop 0\n"
+                 "v_add_f32_dpp %0, %0, %0 row_shl:4 row_mask:0xf bank_mask:0x5\n"
+                 "v_add_f32_dpp %0, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xa\n"
+                 "s_nop 1\n"
+                 "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
+                 "s_nop 1\n"
+                 "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+                 : "+&v"(x0), "+&v"(x1) : "v"(x2), "v"(x3));
+    return x0;
+}
 template <typename T, int D, int kRb, int kVariant, typename Lens>
 __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restrict__ v, int N, int Hkv, int ragged, Lens lens, Piece w,
                                                                 int n_tiles, const float *__restrict__ z,
@@ -921,10 +958,13 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
     constexpr bool kDoV = kVariant == OBC_ALL || kVariant == OBC_VALUE || kAttnLike, kDoK = kVariant == OBC_ALL || kVariant == OBC_KEY,
                    kDoJ = kVariant == OBC_ALL || kVariant == OBC_JOINT, kNeedO = kDoK || kDoJ, kNeedV = kVariant != OBC_ATTN;
     constexpr int kSums = kVariant == OBC_ALL ? 3 : 1, kNorm = kVariant == OBC_VATP ? 1 : 2;
+    constexpr bool kAhead = D == 64 || !kNeedO;
     __shared__ __attribute__((aligned(16))) char digits[2][kNeedO ? K * kTok * D : 16];
     __shared__ __attribute__((aligned(16))) double units[2][kTok];
     __shared__ __attribute__((aligned(16))) double norm_s[2][kTok];
-    __shared__ __attribute__((aligned(16))) RowRecord rec_s[kRows];
+    __shared__ __attribute__((aligned(16))) float least_s[2][kTok];
+    __shared__ ScoreRow rec_s[kRows];
+    __shared__ ScoreTop top_s[kRows];
     __shared__ __attribute__((aligned(16))) float sum_s[kSums][kRb][kTok];
     __shared__ float run_s[kSums][kScoreTokens];             // sums over the chunks so far
     const int hl = blockIdx.x, bg = w.bg0 + hl, b = bg / Hkv;
@@ -948,78 +988,107 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
         if (kNeedO) rows.load(o_digits, hl, block, blocks, lane);
         const __amdgpu_buffer_rsrc_t zg = span_of(z + z_block(w, hl, 0, t_begin), z_block(w, 1, 0, w.s0) * 4);
         const int z_at = (int)(z_block(w, 0, block, w.s0) * 4);
+        // Of 16 tokens from t on: its next block's, where a wave has the registers.  (Room for whole tiles; the last time anything.)
+        auto logits = [&](int t, int l) { return __builtin_amdgcn_raw_buffer_load_b128(zg, l * 16, z_at + (t - t_begin) * 64, 0); };
+        u32x4 ahead;
+        if (kAhead) ahead = logits(t_begin + part * kPart, lane);
         __syncthreads();                                     // (the chunk before this one is done with)
         int i = threadIdx.x;
         asm volatile("" : "+v"(i));                          // (addresses anew for every chunk: registers)
         if (i < kRows) {
-            rec_s[i] = records[(size_t)hl * w.nr + min(row0 + i, w.nr - 1)];
-            if (row0 + i >= w.nr) rec_s[i].last = -1;        // no such row: it sees nothing
+            const RowRecord r = records[(size_t)hl * w.nr + min(row0 + i, w.nr - 1)];
+            rec_s[i] = ScoreRow{r.m, r.inv_l, r.oo, -2.0 * r.unit, least_share(r.unit), r.top, row0 + i < w.nr ? r.last : -1, 0};
+            top_s[i] = ScoreTop{r.top_dk, r.top_dj};         // (last -1: no such row, it sees nothing)
         }
-        if (kNeedV) next.template store_digits<kNeedO, kNorm>(digits[0], units[0], norm_s[0]);
+        if (kNeedV) next.template store_digits<kNeedO, kNorm>(digits[0], units[0], least_s[0], norm_s[0]);
         if (kNeedV && t_begin + kTok < t_end) next.load(vg, kTok);
-        int slot = 0;
+        const bool live = row0 / 16 + rb < blocks;           // uniform in the wave
+        if (!live && part == 0)                              // (no other wave writes these)
+            for (int j = lane; j < kSums * kTok; j += 64) sum_s[j / kTok][rb][j % kTok] = 0.f;
+        int slot = 0, least_last = 0;
         for (int t0 = t_begin; t0 < t_end; t0 += kTok, slot ^= 1) {
             __syncthreads();                                 // this tile is in LDS, the one before it has been read
+            if (t0 == t_begin)                               // of the wave's rows
+                least_last = __builtin_amdgcn_readfirstlane((int)row16_reduce<MinOp>((uint32_t)(rec_s[rb * 16 + (lane & 15)].last + 1))) - 1;
             auto advance = [&]() {
                 if (!kNeedV) return;
                 if (t0 + kTok < t_end)
-                    next.template store_digits<kNeedO, kNorm>(digits[slot ^ 1], units[slot ^ 1], norm_s[slot ^ 1]);
+                    next.template store_digits<kNeedO, kNorm>(digits[slot ^ 1], units[slot ^ 1], least_s[slot ^ 1], norm_s[slot ^ 1]);
                 if (t0 + 2 * kTok < t_end) next.load(vg, t0 - t_begin + 2 * kTok);
             };
             advance();
 #pragma unroll 1
-            for (int p0 = part * kPart; p0 < (part + 1) * kPart; p0 += 16) {
+            for (int p0 = part * kPart; live && p0 < (part + 1) * kPart; p0 += 16) {
                 int l = lane;
                 asm volatile("" : "+v"(l));                  // (addresses anew: registers)
-                const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(zg, l * 16, z_at + (t0 - t_begin + p0) * 64, 0);    // (room for whole tiles)
-                const float x[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
-                double vo[4];                                // v_p . o_i
+                const u32x4 u = kAhead ? ahead : logits(t0 + p0, l);
+                float x[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
+                i32x4 acc[kLevels];
                 if (kNeedO) {
-                    i32x4 acc[kLevels];
                     level_sums<kRowDigits, K, D, kTok>(rows, digits[slot], p0 + (l & 15), l >> 4, acc);
                     __builtin_amdgcn_sched_barrier(0);       // (the row's record only now: registers)
-                    const double unit = rec_s[rb * 16 + (l & 15)].unit;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        vo[r] = join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]) * (units[slot][p0 + 4 * (l >> 4) + r] * unit);
                 }
+                if (kAhead) ahead = logits(t0 + (p0 + 16 < (part + 1) * kPart ? p0 + 16 : kTok + part * kPart), l);
                 float acc_v[4], acc_k[4], acc_j[4];
-                for (bool again = false;; again = true) {
-                    bool close = false;                      // a norm is too small for the digits' error
-                    const RowRecord rec = rec_s[rb * 16 + (l & 15)];
+                const int tok0 = p0 + 4 * (l >> 4);          // register r has token tok0 + r of the tile
+                const ScoreRow rec = rec_s[rb * 16 + (l & 15)];
+                // The pairs' terms; returns whether one of them that counts has a norm too small for the digits' error.  kAny: a row
+                // may not see a token, or have it as its top.  kExact: v_p . o_i (vo), not the level sums.
+                double vo[4];
+                auto pairs = [&](auto any, auto exact) {
+                    constexpr bool kAny = decltype(any)::value, kExact = decltype(exact)::value;
+                    const ScoreTop top = kAny && kNeedO ? top_s[rb * 16 + (l & 15)] : ScoreTop();
+                    bool close = false;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        const int tok = p0 + 4 * (l >> 4) + r, p = t0 + tok;
-                        const float a = p <= rec.last ? exp_nonpositive(x[r] - rec.m) * rec.inv_l : 0.f;
+                        if (r % (D == 64 ? 2 : 1) == 0) __builtin_amdgcn_sched_barrier(0);
+                        const int p = t0 + tok0 + r;
+                        float a = exp_nonpositive(x[r] - rec.m) * rec.inv_l;
+                        if (kAny && p > rec.last) a = 0.f;
                         const float a2 = a * a;
                         acc_v[r] = kAttnLike ? a : a2;
                         if (!kNeedO) continue;
-                        const bool is_top = p == rec.top, counts = a2 != 0.f && !is_top;
-                        const double vv = norm_s[slot][tok], d2 = fma(-2.0, vo[r], vv + rec.oo);    // ||v_p - o_i||^2
-                        const float least = (float)(units[slot][tok] * rec.unit) * 0x1p32f;         // 2^-4 2^E
+                        const bool is_top = kAny && p == rec.top;
+                        const double vv = norm_s[slot][tok0 + r], with_oo = vv + rec.oo;
+                        const double dot = kExact ? vo[r] : join_levels(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r]);
+                        const double unit = kExact ? -2.0 : units[slot][tok0 + r] * rec.unit;
+                        const double d2 = fma(dot, unit, with_oo);                                  // ||v_p - o_i||^2
+                        const float least = least_s[slot][tok0 + r] * rec.least;                    // 2^-4 2^E
+                        // (what is close and counts: times the pair's weight, so that one of weight 0 is not)
                         if (kDoK) {
-                            acc_k[r] = a2 * x[r] * x[r] * (is_top ? rec.top_dk : at_least_0((float)d2));
-                            close |= counts && (float)d2 < least;
+                            const float w = a2 * x[r] * x[r], dk = at_least_0((float)d2);
+                            acc_k[r] = w * (is_top ? top.dk : dk);
+                            close |= !is_top && acc_k[r] < w * least;
                         }
                         if (kDoJ) {
-                            const double zd = x[r];          // ||v_p + Z (v_p - o_i)||^2 with 2 (v_p - o_i).v_p = d2 + vv - oo
-                            const double dj = fma(zd, fma(zd, d2, d2 + (vv - rec.oo)), vv);
-                            acc_j[r] = a2 * (is_top ? rec.top_dj : at_least_0((float)dj));
-                            close |= counts && (float)dj < least * fabsf(fmaf(x[r], x[r], x[r]));   // (its share of d2's error)
+                            const double zd = x[r];          // ||v_p + Z (v_p - o_i)||^2 = vv + Z (2 (v_p - o_i).v_p + Z d2)
+                            const float dj = at_least_0((float)fma(zd, fma(zd, d2, fma(dot, unit, vv + vv)), vv));
+                            acc_j[r] = a2 * (is_top ? top.dj : dj);
+                            close |= !is_top && acc_j[r] < a2 * (least * fabsf(fmaf(x[r], x[r], x[r])));      // (its share of d2's error)
                         }
                     }
-                    if (!kNeedO || again || __ballot(close) == 0ull) break;      // uniform
+                    return close;
+                };
+                const bool any = t0 + p0 + 15 > least_last || __ballot((uint32_t)(rec.top - (t0 + tok0)) < 4u) != 0ull;      // uniform
+                bool close;
+                if (any) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) asm volatile("" : "+v"(x[r]));       // (nothing of this ahead of the branch)
+                    close = pairs(std::true_type(), std::false_type());
+                } else {
+                    close = pairs(std::false_type(), std::false_type());
+                }
+                if (kNeedO && __ballot(close) != 0ull) {     // uniform, rare
                     asm volatile("" : "+v"(l));              // (and here)
                     block_dots<T, D>(v + ((size_t)bg * N + min(t0 + p0 + 4 * (l & 3) + (l >> 2 & 3), t_end - 1)) * D,
                                      o + ((size_t)hl * w.nr + min(block * 16 + (l & 15), w.nr - 1)) * D, l >> 4, vo);
+                    pairs(std::true_type(), std::true_type());
                 }
                 // over the 16 rows; the other row blocks held others
                 int n = 0;
                 auto put = [&](float (&s)[4]) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) s[r] = row16_reduce<SumOp>(s[r]);
-                    if ((l & 15) == 0) *(float4 *)(&sum_s[n][rb][p0 + 4 * (l >> 4)]) = make_float4(s[0], s[1], s[2], s[3]);
+                    const float sums = four_sums(s[0], s[1], s[2], s[3]);
+                    if ((l & 3) == 0) sum_s[n][rb][p0 + (l >> 2)] = sums;
                     ++n;
                 };
                 if (kDoV) put(acc_v);

@@ -59,6 +59,30 @@ def test_splits_with_references_of_their_own_match_oracle(case, score_path):
         assert err <= TOL["fp32"], (name, err, where)
 
 
+# (dtype, d, G, W, N, lens): windows whose last chunk of 128 (64) rows leaves five, three or two (three) of its row blocks empty, the
+# last one in use full or with 2 or 1 rows, and whose rows stop seeing tokens in each of a block's sixteen places
+EMPTY = [("fp32", 128, 2, 33, 1900, None), ("bf16", 64, 2, 40, 2601, [2601, 1999]), ("fp32", 64, 2, 48, 2055, None),
+         ("bf16", 64, 3, 48, 1500, None), ("fp32", 128, 3, 43, 1203, [1203, 700])]
+
+
+@pytest.mark.parametrize("variant", ["all", "key", "value"])
+@pytest.mark.parametrize("case", EMPTY, ids=lambda c: "%s_d%d_%dx%d_%d" % c[:5])
+def test_row_blocks_without_rows(case, variant, score_path):
+    """A row's largest logit stands in every place of a block of sixteen tokens in turn (row i's at token 100 + 17 i)."""
+    dtype, d, G, W, N, lens = case
+    q, k, v = _inputs(dtype, d, G, W, N, 1 if lens is None else len(lens), 2, 51)
+    rows = q.view(q.shape[0], 2, G * W, d)
+    for i in range(min(G * W, 32)):
+        k[:, :, 100 + 17 * i] = (1.5 if i % 2 else 3) * rows[:, :, i]        # (some with most of the row's weight)
+    ref = oracle.score(q, k, v, seq_lens=lens)
+    score_path("plain")
+    got = obc.obc_score(q.cuda(), k.cuda(), v.cuda(), variant, seq_lens=lens).cpu().numpy()
+    names = ("value", "key", "joint")
+    for i, name in enumerate(names if variant == "all" else (variant,)):
+        err, where = score_error(got[i] if variant == "all" else got, ref[names.index(name)], min(lens or [N]) // 8, lens, TOL["fp32"])
+        assert err <= TOL["fp32"], (name, err, where)
+
+
 # (dtype, d, Hkv, G, W, N) on either side of where the route changes: five tiles and sixteen of short bf16 calls; twelve heads of 17 to
 # 32 fp32 rows; 128 and 160 tiles of longer windows
 ROUTES = [("bf16", 64, 2, 4, 5, 256), ("bf16", 64, 2, 4, 5, 257), ("bf16", 64, 2, 4, 5, 1025), ("fp32", 64, 11, 1, 20, 1100),
