@@ -38,6 +38,7 @@ namespace {
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxSteps = 4;         // most token rows per lane: a range is 1, 2 or 4 workgroup-wide steps
+constexpr int kVectorRows = 4;       // most rows whose sums of P V are vector ops
 constexpr int kInlineSplits = 48;    // most ranges per head the scoring kernel merges itself
 constexpr int kMergeThreads = 1024;
 constexpr int kMergeOwn = 4;         // ranges per merging thread
@@ -109,6 +110,24 @@ __device__ __forceinline__ float row_sums(float (&x)[kG], int sub) {
     return x[0];
 }
 typedef __bf16 bf16_pair __attribute__((ext_vector_type(2)));
+// Sums over the wave's token slots of a lane's eight channels: row q of 16 lanes gets those of channels 2 q and 2 q + 1.  (Each
+// exchange brings two channels together and leaves one of them in either half.)
+template <int kLpt>
+__device__ __forceinline__ float2 sums_over_slots(const float (&x)[8]) {
+    float half[4], two[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[j]), __float_as_uint(x[j + 4]), false, false);
+        half[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(half[j]), __float_as_uint(half[j + 2]), false, false);
+        two[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        if (kLpt == 8) two[j] += dpp_pair<0x128>(two[j]);
+    }
+    return make_float2(two[0], two[1]);
+}
 typedef float f32_quad __attribute__((ext_vector_type(4)));
 // acc + the dot product of 8 bf16 values each (exact products, fp32 sums).
 __device__ __forceinline__ float dot8(const uint4 a, const uint4 b, float acc) {
@@ -145,7 +164,8 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
     // Sums of P V by matrix op: [wave, and with 8 lanes per token its even or odd tokens][channel j of a lane's 8][lane][row]; the
     // padding between two j takes the closing sum's reads to as many banks.
     constexpr int kHalves = 16 / kLpt, kChannel = kLpt * kG + 8, kPartSums = kWaves * kHalves;
-    __shared__ __attribute__((aligned(16))) float red_o[kNeedO ? kPartSums * 8 * kChannel : 4];
+    constexpr bool kVector = kG <= kVectorRows;     // sums of P V by vector ops: [wave][row][channel]
+    __shared__ __attribute__((aligned(16))) float red_o[!kNeedO ? 4 : kVector ? kWaves * kG * kD : kPartSums * 8 * kChannel];
     __shared__ float top_v[kNeedO ? kG * kD : 1];   // V rows of the top tokens
 
     const int bh = blockIdx.x, b = bh / Hkv, split = blockIdx.y;
@@ -266,16 +286,26 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
         if (i == 0 || own >= 4 * i) { m = mi; top = ti; }
     }
 
-    // Sums of exp(z - m) and of exp(z - m) v over the range without the top token.  The second one is a matrix op per channel:
-    // its first operand's row is a lane's own row, its four k are the wave's token slots, and a lane's channel j is a column of the
-    // second; fp32 throughout.  With 8 lanes per token a row of 16 lanes has an even and an odd token: rows 0 to 7 are the even
-    // ones' weights, 8 to 15 the odd ones', and of the product only what meets its own half counts.
-    // (Weights of every row in every lane, products on the vector ALUs and sums across slots by register exchanges were four
-    // times the instructions of a wave, and four waves share a SIMD: TODO.)
+    // Sums of exp(z - m) and of exp(z - m) v over the range without the top token.  The second one, up to kVectorRows rows: products
+    // on the vector ALUs with the weights of a row handed round each four lanes; the sums over the token slots leave two channels in
+    // each slot.  Eight rows, whose 64 sums have no registers beside a long range's loads: a matrix op per channel: its first operand's
+    // row is a lane's own row, its four k are the wave's token slots, and a lane's channel j is a column of the second; fp32
+    // throughout.  With 8 lanes per token a row of 16 lanes has an even and an odd token: rows 0 to 7 are the even ones' weights, 8 to
+    // 15 the odd ones', and of the product only what meets its own half counts.
+    // (The matrix ops take a wave's step 120 ns however many rows are in use.  A decoding step's three kernels in a graph, 8 heads, d = 128,
+    // joint, with every row's weight and sum in every lane and sums by exchanges of whole registers / matrix ops / so, us:
+    //   G = 1, 2000 tokens 13.6 / 13.6 / 13.4      G = 4, 1025 tokens 15.0 / 13.7 / 13.5
+    //   G = 2, 4000 tokens 18.8 / 18.3 / 17.6      G = 4, 4000 tokens 21.5 / 20.2 / 19.9
+    // (with matrix ops 4 x 8 heads, G = 1, 1000 tokens took 16.7, before 15.8, so 15.9).)
     float lsum = 0.f;
     f32_quad acc[8];
+    float sums[kVector ? kG : 1][8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = f32_quad{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 8; ++j) {
+        acc[j] = f32_quad{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < (kVector ? kG : 1); ++r) sums[r][j] = 0.f;
+    }
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
         const int p = token_of<kD>(t0, u, wave, slot);
@@ -285,9 +315,19 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
         if (kNeedO) {
             float vv[8];
             unpack8(vw[u], vv);
-            const float a = sub < kG ? w : 0.f;
+            if constexpr (kVector) {
+                float of_row[4] = {w, w, w, w};     // (lanes r, r + kG, .. of a token's have row r's)
+                if (kG >= 2) { of_row[0] = dpp_pair<0x00>(w); of_row[1] = dpp_pair<0x55>(w); }
+                if (kG >= 4) { of_row[2] = dpp_pair<0xAA>(w); of_row[3] = dpp_pair<0xFF>(w); }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, vv[j], acc[j], 0, 0, 0);
+                for (int r = 0; r < kG; ++r)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) sums[r][j] = fmaf(of_row[r], vv[j], sums[r][j]);
+            } else {
+                const float a = sub < kG ? w : 0.f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, vv[j], acc[j], 0, 0, 0);
+            }
             if (__any(is_top)) {                    // uniform: the wave holds some row's top token
 #pragma unroll
                 for (int r = 0; r < kG; ++r) {
@@ -301,18 +341,19 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
     if (kLpt == 8) lsum += dpp_pair<0x128>(lsum);
     lsum = across_rows<SumOp>(lsum);
     if (lane < kG) red_l[lane * kWaves + wave] = lsum;
-    if (kNeedO) {
+    if constexpr (kNeedO && kVector) {
+#pragma unroll
+        for (int r = 0; r < kG; ++r) {
+            const float2 two = sums_over_slots<kLpt>(sums[r]);
+            if (kLpt == 16 || (lane & 8) == 0) *(float2 *)(red_o + (wave * kG + r) * kD + sub * 8 + 2 * (lane >> 4)) = two;
+        }
+    } else if (kNeedO) {
         // rows 4 (lane / 16) .. + 3 of the product, column lane % 16
         const int quad = lane >> 4, r0 = 4 * (kHalves == 1 ? quad : quad & 1), odd = kHalves == 1 ? 0 : (lane >> 3) & 1;
         if (r0 < kG && (kHalves == 1 || quad >> 1 == odd)) {
             float *to = red_o + (wave * kHalves + odd) * 8 * kChannel + sub * kG + r0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if constexpr (kG >= 4) *(f32_quad *)(to + j * kChannel) = acc[j];
-                else
-#pragma unroll
-                    for (int r = 0; r < kG; ++r) to[j * kChannel + r] = acc[j][r];
-            }
+            for (int j = 0; j < 8; ++j) *(f32_quad *)(to + j * kChannel) = acc[j];
         }
     }
     __syncthreads();
@@ -332,10 +373,10 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
     }
     float *vec = part_vec + ((size_t)bh * splits + split) * kG * 2 * kD;
     for (int e = threadIdx.x; e < kG * kD; e += kThreads) {         // (16 channels of each row side by side)
-        const int r = (e >> 4) % kG, c = e / (16 * kG) * 16 + (e & 15), at = (c % 8) * kChannel + c / 8 * kG + r;
+        const int r = (e >> 4) % kG, c = e / (16 * kG) * 16 + (e & 15), at = kVector ? r * kD + c : (c % 8) * kChannel + c / 8 * kG + r;
         float o = red_o[at];
 #pragma unroll
-        for (int w = 1; w < kPartSums; ++w) o += red_o[w * 8 * kChannel + at];
+        for (int w = 1; w < (kVector ? kWaves : kPartSums); ++w) o += red_o[w * (kVector ? kG * kD : 8 * kChannel) + at];
         vec[r * 2 * kD + c] = o;
         vec[r * 2 * kD + kD + c] = o + top_v[r * kD + c];
     }

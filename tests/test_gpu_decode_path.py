@@ -50,6 +50,18 @@ def test_decode_scores_select_compact_match_oracle(name, score_path):
     print(name, {k: "%.2e" % v for k, v in worst.items()})
 
 
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("step", [1, 2, 4])
+def test_ranges_of_every_length_sum_every_row(G, d, step, score_path):
+    """Sums of P V per row, on either side of where they go to the matrix cores, for ranges of 1, 2 and 4 tokens per lane: a token
+    more than one range, as many tokens as 48 ranges and one, and a token less than that."""
+    score_path("decode")
+    tokens = {64: 128, 128: 64}[d]
+    N = {1: tokens + 1, 2: 49 * tokens, 4: 97 * tokens - 1}[step]
+    run_case(synth.Workload("d_rows", B=1, Hq=2 * G, Hkv=2, d=d, N=N, budget=N // 8, seed=70 + G, sinks=2, outlier_channels=2, **W1))
+
+
 def test_attention_mass_of_the_dominant_case():
     """The guard case is only a test of the guard if one key really takes almost all of some row's attention."""
     x = synth.make_inputs(CASES["d_one_key_takes_all"])
