@@ -355,12 +355,12 @@ def main():
             m = re.search(r"obc_score \(all mfma_\* kernels\):.*?=\s*(\d+) bytes per call", f.read())
         traffic = int(m.group(1)) if m else None
         traffic_source = "profiles/" + os.path.basename(tpath) if m else None
-    # Vector-ALU load of the two sweeps beside the memory roofline: the two kernels issue ~22.5 vector instructions per
+    # Vector-ALU load of the two sweeps beside the memory roofline: the two kernels issue ~21.4 vector instructions per
     # lane and (window row, token) pair, matrix ops included as one each (hardware counter SQ_INSTS_VALU of the two
     # sweeps over the pair count, profiles/sq_counters_c3_*.txt); the chip's published fp32 vector peak, 157.3 TFLOP/s,
     # is 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz fused multiply-adds, i.e. 7.86e13 lane-operations per second.
     pairs = Hq * W * tokens
-    lane_ops_per_pair = 22.5
+    lane_ops_per_pair = 21.4
     valu_rate = 256 * 4 * 32 * 2.4e9
     valu_ms = pairs * lane_ops_per_pair / valu_rate * 1e3
     roofline = {
