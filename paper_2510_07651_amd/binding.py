@@ -415,18 +415,21 @@ def obc_decode_step(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scores: t
             and v.is_contiguous() and scores.is_contiguous()):
         raise ValueError("tensors must be contiguous and on the GPU")
     B, Hq, W, d = q.shape
-    kv_shape = k.shape
-    _, Hkv, N, _ = kv_shape
-    if W != 1 or v.shape != kv_shape or scores.shape != (B, Hkv, N) or scores.dtype is not torch.float32:
-        raise ValueError("q must be [B,Hq,1,d], k, v [B,Hkv,N,d], scores [B,Hkv,N] float32")
+    kv_shape, dtype = k.shape, q.dtype
+    Bk, Hkv, N, dk = kv_shape
+    if (W != 1 or Bk != B or dk != d or v.shape != kv_shape or k.dtype is not dtype or v.dtype is not dtype
+            or scores.shape != (B, Hkv, N) or scores.dtype is not torch.float32):
+        raise ValueError("q must be [B,Hq,1,d], k, v [B,Hkv,N,d] of its type, scores [B,Hkv,N] float32")
     var = VARIANT_CODES[variant] if isinstance(variant, str) else int(variant)
-    dt = OBC_BF16 if q.dtype is torch.bfloat16 else _dtype_code(q)
+    dt = OBC_BF16 if dtype is torch.bfloat16 else _dtype_code(q)
     if workspace is None:
         workspace = torch.empty(obc_decode_step_workspace_bytes(B, N, Hq, Hkv, d, dt, var), dtype=torch.uint8, device=q.device)
     if evicted is None:
         evicted = torch.empty((B, Hkv), dtype=torch.int32, device=q.device)
     if not (evicted.is_cuda and workspace.is_cuda and evicted.is_contiguous() and workspace.is_contiguous()):
         raise ValueError("tensors must be contiguous and on the GPU")
+    if evicted.dtype is not torch.int32 or evicted.numel() < B * Hkv:
+        raise ValueError("evicted must be int32 with room for [B,Hkv]")
     rc = (_lib or load_library()).obc_decode_step(
         q.data_ptr(), k.data_ptr(), v.data_ptr(), scores.data_ptr(), evicted.data_ptr(), N, Hq, Hkv, d, var, B, dt,
         None if seq_lens is None else _lens_arg(seq_lens, B), int(num_sinks), int(num_recent), workspace.data_ptr(),

@@ -5,6 +5,8 @@ import os
 import re
 
 import pytest
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
 
 from paper_2510_07651_amd import binding as obc
 
@@ -166,6 +168,57 @@ def test_entry_points_reject_bad_arguments_before_launch(lib):
     assert step == obc.obc_score_workspace_bytes(1, 1025, 1, 32, 8, 128, obc.OBC_BF16, obc.OBC_JOINT) + 256
     with pytest.raises(obc.ObcError):
         obc.obc_decode_step_workspace_bytes(1, 1025, 32, 8, 128, obc.OBC_BF16, obc.OBC_ALL)
+
+
+class _NoLaunch:
+    """The library, but `entry` only notes that it was reached."""
+
+    def __init__(self, lib, entry):
+        self._lib, self._entry, self.reached = lib, entry, 0
+
+    def __getattr__(self, name):
+        if name != self._entry:
+            return getattr(self._lib, name)
+
+        def note(*args):
+            self.reached += 1
+            return obc.OBC_OK
+        return note
+
+
+@pytest.fixture
+def no_launch(lib, monkeypatch):
+    """no_launch(entry): as above; tensors made until the end of the test claim to be on a GPU and have no memory."""
+    def start(entry):
+        stub = _NoLaunch(lib, entry)
+        monkeypatch.setattr(obc, "_lib", stub)
+        monkeypatch.setattr(obc, "_raw_stream", lambda device: 0)
+        return stub
+    with FakeTensorMode():
+        yield start
+
+
+BF16, FP32, I32, I64 = torch.bfloat16, torch.float32, torch.int32, torch.int64
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer of FakeTensor")
+@pytest.mark.parametrize("change", [dict(k=(1, 2, 40, 128), v=(1, 2, 40, 128)), dict(k=(3, 2, 40, 128), v=(3, 2, 40, 128)),
+                                    dict(k=(2, 2, 40, 64), v=(2, 2, 40, 64)), dict(v=(2, 2, 40, 64)), dict(q=(2, 8, 1, 64)),
+                                    dict(kd=FP32, vd=FP32), dict(kd=FP32), dict(vd=FP32), dict(qd=FP32),
+                                    dict(evicted=(2, 1)), dict(evicted=(0,)), dict(ed=I64)], ids=str)
+def test_decode_step_refuses_what_does_not_fit_together(change, no_launch):
+    """The entry point takes batch, head_dim and type from q: caches that have others would be read and shifted past their end,
+    and the dropped positions need their room."""
+    def call(q=(2, 8, 1, 128), k=(2, 2, 40, 128), v=(2, 2, 40, 128), scores=(2, 2, 40), evicted=(2, 2), qd=BF16, kd=BF16, vd=BF16, ed=I32):
+        make = lambda shape, dtype: torch.empty(shape, dtype=dtype, device="cuda")
+        return obc.obc_decode_step(make(q, qd), make(k, kd), make(v, vd), make(scores, FP32), evicted=None if evicted is None else make(evicted, ed))
+    lib = no_launch("obc_decode_step")
+    for good in (dict(), dict(evicted=None), dict(evicted=(4,)), dict(evicted=(3, 2)), dict(qd=FP32, kd=FP32, vd=FP32)):
+        call(**good)
+    assert lib.reached == 5
+    with pytest.raises(ValueError):
+        call(**change)
+    assert lib.reached == 5
 
 
 @pytest.mark.parametrize("dtype,d,heads,W,N", [("bf16", 64, 8, 20, 300), ("bf16", 64, 8, 20, 1000), ("bf16", 64, 2, 32, 1024),
