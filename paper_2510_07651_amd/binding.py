@@ -227,10 +227,12 @@ def obc_score_static(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, variant,
     tensor, and nothing is allocated (not by torch either)."""
     _require_cuda(q, k, v, scores)
     B, Hq, W, d = q.shape
-    _, Hkv, N, _ = k.shape
+    Bk, Hkv, N, dk = k.shape
+    if (Bk, dk) != (B, d) or v.shape != k.shape or k.dtype != q.dtype or v.dtype != q.dtype:
+        raise ValueError("q, k, v shapes or dtypes disagree")
     var = VARIANT_CODES[variant] if isinstance(variant, str) else int(variant)
     shape = (3, B, Hkv, N) if var == OBC_ALL else (B, Hkv, N)
-    if tuple(scores.shape) != shape or scores.dtype != torch.float32 or v.shape != k.shape:
+    if tuple(scores.shape) != shape or scores.dtype != torch.float32:
         raise ValueError("scores must be a contiguous float32 tensor of shape %s" % (shape,))
     rc = load_library().obc_score_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), N, W, Hq, Hkv, d, var,
                                          scores.data_ptr(), B, _dtype_code(q), _lens_arg(seq_lens, B),

@@ -221,6 +221,22 @@ def test_decode_step_refuses_what_does_not_fit_together(change, no_launch):
     assert lib.reached == 5
 
 
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer of FakeTensor")
+@pytest.mark.parametrize("change", [dict(k=(1, 2, 40, 128), v=(1, 2, 40, 128)), dict(k=(2, 2, 40, 64), v=(2, 2, 40, 64)),
+                                    dict(v=(2, 2, 39, 128)), dict(kd=FP32, vd=FP32), dict(vd=FP32), dict(qd=FP32)], ids=str)
+def test_score_static_refuses_what_does_not_fit_together(change, no_launch):
+    def call(q=(2, 8, 16, 128), k=(2, 2, 40, 128), v=(2, 2, 40, 128), qd=BF16, kd=BF16, vd=BF16):
+        make = lambda shape, dtype: torch.empty(shape, dtype=dtype, device="cuda")
+        return obc.obc_score_static(make(q, qd), make(k, kd), make(v, vd), "joint", make((2, 2, 40), FP32))
+    lib = no_launch("obc_score_static")
+    call()
+    call(qd=FP32, kd=FP32, vd=FP32)
+    assert lib.reached == 2
+    with pytest.raises(ValueError):
+        call(**change)
+    assert lib.reached == 2
+
+
 @pytest.mark.parametrize("dtype,d,heads,W,N", [("bf16", 64, 8, 20, 300), ("bf16", 64, 8, 20, 1000), ("bf16", 64, 2, 32, 1024),
                                                ("fp32", 64, 16, 20, 3000), ("fp32", 128, 12, 17, 9000), ("fp32", 128, 4, 64, 3000)])
 def test_general_path_asks_the_same_for_every_score(dtype, d, heads, W, N):
