@@ -364,12 +364,16 @@ def obc_compact(k: torch.Tensor, v: torch.Tensor, keep_idx: torch.Tensor, k_out=
     _require_cuda(k, v, keep_idx)
     B, Hkv, N, d = k.shape
     budget = keep_idx.shape[-1]
-    if keep_idx.dtype != torch.int32 or keep_idx.shape[:2] != (B, Hkv) or v.shape != k.shape:
+    if (keep_idx.dtype != torch.int32 or keep_idx.shape[:2] != (B, Hkv) or v.shape != k.shape
+            or v.element_size() != k.element_size()):
         raise ValueError("keep_idx must be [B,Hkv,budget] int32 matching k, v")
     if k_out is None:
         k_out = torch.empty((B, Hkv, budget, d), dtype=k.dtype, device=k.device)
     if v_out is None:
         v_out = torch.empty((B, Hkv, budget, d), dtype=v.dtype, device=v.device)
+    _require_cuda(k_out, v_out)
+    if min(k_out.numel() * k_out.element_size(), v_out.numel() * v_out.element_size()) < B * Hkv * budget * d * k.element_size():
+        raise ValueError("k_out, v_out need room for [B,Hkv,budget,d]")
     rc = load_library().obc_compact(k.data_ptr(), v.data_ptr(), keep_idx.data_ptr(), k_out.data_ptr(),
                                     v_out.data_ptr(), B, Hkv, N, budget, d, _dtype_code(k), _stream_ptr(k))
     if rc != OBC_OK:
@@ -383,7 +387,8 @@ def obc_compact_inplace(k: torch.Tensor, v: torch.Tensor, keep_idx: torch.Tensor
     _require_cuda(k, v, keep_idx)
     B, Hkv, N, d = k.shape
     budget = keep_idx.shape[-1]
-    if keep_idx.dtype != torch.int32 or keep_idx.shape[:2] != (B, Hkv) or v.shape != k.shape:
+    if (keep_idx.dtype != torch.int32 or keep_idx.shape[:2] != (B, Hkv) or v.shape != k.shape
+            or v.element_size() != k.element_size()):
         raise ValueError("keep_idx must be [B,Hkv,budget] int32 matching k, v")
     if not (k.is_contiguous() and v.is_contiguous() and keep_idx.is_contiguous()):
         raise ValueError("k, v and keep_idx must be contiguous")

@@ -237,6 +237,38 @@ def test_score_static_refuses_what_does_not_fit_together(change, no_launch):
     assert lib.reached == 2
 
 
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer of FakeTensor")
+@pytest.mark.parametrize("change", [dict(kd=FP32), dict(vd=FP32), dict(k_out=(2, 2, 8, 128)), dict(v_out=(2, 2, 9, 64)),
+                                    dict(v_out=(1,)), dict(turned=True), dict(keep=(2, 1, 9))], ids=str)
+def test_compaction_refuses_what_has_no_room(change, no_launch):
+    """Rows are moved by their bytes, k's: v needs as many per element, the outputs as many in all."""
+    def call(kd=BF16, vd=BF16, k_out=None, v_out=None, keep=(2, 2, 9), turned=False, od=BF16):
+        make = lambda shape, dtype: torch.empty(shape, dtype=dtype, device="cuda")
+        k, v, idx = make((2, 2, 40, 128), kd), make((2, 2, 40, 128), vd), make(keep, I32)
+        out = [None if x is None else make(x, od) for x in (k_out, v_out)]
+        if turned:
+            out[0] = make((2, 2, 128, 9), od).transpose(2, 3)
+        return obc.obc_compact(k, v, idx, *out)
+    lib = no_launch("obc_compact")
+    for good in (dict(), dict(kd=FP32, vd=FP32), dict(k_out=(2, 2, 9, 128), v_out=(2, 2, 10, 128)), dict(vd=torch.int16, v_out=(4608,), od=torch.int16)):
+        call(**good)
+    assert lib.reached == 4
+    with pytest.raises(ValueError):
+        call(**change)
+    assert lib.reached == 4
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer of FakeTensor")
+def test_compaction_in_place_refuses_rows_of_two_sizes(no_launch):
+    make = lambda shape, dtype: torch.empty(shape, dtype=dtype, device="cuda")
+    lib = no_launch("obc_compact_inplace")
+    obc.obc_compact_inplace(make((2, 2, 40, 128), BF16), make((2, 2, 40, 128), torch.int16), make((2, 2, 9), I32))
+    for kd, vd in ((BF16, FP32), (FP32, BF16)):
+        with pytest.raises(ValueError):
+            obc.obc_compact_inplace(make((2, 2, 40, 128), kd), make((2, 2, 40, 128), vd), make((2, 2, 9), I32))
+    assert lib.reached == 1
+
+
 @pytest.mark.parametrize("dtype,d,heads,W,N", [("bf16", 64, 8, 20, 300), ("bf16", 64, 8, 20, 1000), ("bf16", 64, 2, 32, 1024),
                                                ("fp32", 64, 16, 20, 3000), ("fp32", 128, 12, 17, 9000), ("fp32", 128, 4, 64, 3000)])
 def test_general_path_asks_the_same_for_every_score(dtype, d, heads, W, N):
