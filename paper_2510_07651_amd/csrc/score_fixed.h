@@ -91,11 +91,8 @@ template <int D> constexpr int kFixedTile = D == 64 ? 64 : 32;           // toke
 
 // Layouts in memory, such that a wave reads and writes whole kilobytes (a lane has one row; rows side by side in memory would
 // make every lane's 16 bytes a line of their own: 64 cache accesses instead of 8).
-//   z       [head][row / 16][token / 16][token % 16 / 4][row % 16][token % 4]
+//   z       z_block (plain_layout.h)
 //   digits  [head][row / 16][digit][element / 64][element % 64 / 16][row % 16][element % 16]
-__device__ __forceinline__ size_t z_block(const Piece &w, int hl, int row_block, int token) {
-    return (((size_t)hl * ((w.nr + 15) / 16) + row_block) * (w.z_stride / 16) + (token - w.s0) / 16) * 256;
-}
 template <int K, int D>
 __device__ __forceinline__ size_t digit_address(size_t block, int k, int row, int c) {
     return ((block * K + k) * (D / 64) + c / 64) * 1024 + (c % 64 / 16 * 16 + row % 16) * 16 + c % 16;
@@ -986,10 +983,10 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
         const int block = min(row0 / 16 + rb, blocks - 1);
         RowDigits<kRowDigits, D> rows;
         if (kNeedO) rows.load(o_digits, hl, block, blocks, lane);
-        const __amdgpu_buffer_rsrc_t zg = span_of(z + z_block(w, hl, 0, t_begin), z_block(w, 1, 0, w.s0) * 4);
+        const __amdgpu_buffer_rsrc_t zg = span_of(z + z_block(w, hl, 0, w.s0), z_block(w, 1, 0, w.s0) * 4);
         const int z_at = (int)(z_block(w, 0, block, w.s0) * 4);
-        // Of 16 tokens from t on: its next block's, where a wave has the registers.  (Room for whole tiles; the last time anything.)
-        auto logits = [&](int t, int l) { return __builtin_amdgcn_raw_buffer_load_b128(zg, l * 16, z_at + (t - t_begin) * 64, 0); };
+        // Of 16 tokens from t on (there is room for whole tiles); those of the next block are on their way where a wave has the registers.
+        auto logits = [&](int t, int l) { return __builtin_amdgcn_raw_buffer_load_b128(zg, l * 16, z_at + (t - w.s0) * 64, 0); };
         u32x4 ahead;
         if (kAhead) ahead = logits(t_begin + part * kPart, lane);
         __syncthreads();                                     // (the chunk before this one is done with)
@@ -1028,7 +1025,7 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
                     level_sums<kRowDigits, K, D, kTok>(rows, digits[slot], p0 + (l & 15), l >> 4, acc);
                     __builtin_amdgcn_sched_barrier(0);       // (the row's record only now: registers)
                 }
-                if (kAhead) ahead = logits(t0 + (p0 + 16 < (part + 1) * kPart ? p0 + 16 : kTok + part * kPart), l);
+                if (kAhead) ahead = logits(next_scored(t0, p0, part, kPart, kTok, t_end), l);
                 float acc_v[4], acc_k[4], acc_j[4];
                 const int tok0 = p0 + 4 * (l >> 4);          // register r has token tok0 + r of the tile
                 const ScoreRow rec = rec_s[rb * 16 + (l & 15)];

@@ -32,6 +32,7 @@
 #include <climits>
 
 #include "internal.h"
+#include "plain_layout.h"
 #include "wave_util.h"
 
 namespace obc {
@@ -57,13 +58,6 @@ constexpr int sweep_time(int dtype, int rows, int tiles) {
     return rows == 128 ? 100 * tiles + 200 : dtype == OBC_F32 ? 60 * tiles + 200 : 65 * tiles + 160;
 }
 constexpr int kNoToken = 0x7fffffff;
-
-// What one launch works on: KV heads bg0 .. bg0 + gridDim.z - 1, their window rows r0 .. r0 + nr - 1 (of the G*W rows
-// that share the KV head), tokens s0 .. s1 - 1.  Buffers of the group are indexed from (bg0, r0, s0).
-struct Piece {
-    int bg0, r0, nr, s0, s1;
-    int z_stride;                // floats between the logits of consecutive rows
-};
 
 // Constants of one row, written by plain_weights or fixed_weights (m, top) and plain_merge (the rest; all with digit_sweep).
 struct RowRecord {
