@@ -203,9 +203,8 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
     // K and V blocks live in rings of four 8 KB slots each (block j in slot j mod 4): K block
     // n+1 and V block n-1, both started three steps ago, are waited for here while the two
     // younger batches stay in flight; then K block n+4 and V block n+2 start in the slots
-    // the previous step has finished with.  Past the end of the split every batch has as many transfers, but they fetch
-    // the split's last block `n_last` again, from the L2 (nothing of it counts a second time): the next split's rows were
-    // three K and two V blocks from memory for nothing, a third of what a split of 256 tokens reads.
+    // the previous step has finished with.  Past block `n_last` every batch has as many transfers, but they fetch
+    // that block again, from the L2; nothing past the split's end counts (see mfma_sweep1).
     constexpr int kKBase = ((PH + 1) & 3) * kBlkBytes;                  // block n+1
     constexpr int kVBase = (4 + ((PH + 3) & 3)) * kBlkBytes;            // block n-1
     const float c2 = kLog2e * kInvSqrtD;
@@ -377,6 +376,16 @@ __device__ __forceinline__ void sweep1_step(Sweep1Regs &R, const char *smem, uin
 // With kNeedO every row keeps its candidate for a dominant key (see kCandMargin) out of its sums and
 // reports it with the partial record; the combine step then forms v_cand - o_i without
 // cancellation for every row, and no row ever needs a second pass.
+//
+// Past its split's end the ring fetches the last block again: the next split's rows are three K and two V blocks from memory for
+// nothing, a third of what a split of 256 tokens reads.  But splits of up to four blocks fetch on, to the sequence's end, where wide
+// second sweeps follow: the kernel takes 12.2 us with the last block again and 11.5 so among whole calls (8 heads x 128 rows x 2048;
+// alone, its keys in cache, 11.2 and 11.4).  Whole calls, joint, the last block again / on, us (sixteen loads of either build, each at an
+// address of its own, which alone moves a call by up to 3 %):
+//   four blocks   128 rows, 8 heads x 2048 27.2 / 25.6, x 4096 30.4 / 30.2   100 rows, 8 heads x 2049 29.0 / 27.9   112 rows, 4 heads x 4096 27.7 / 26.6
+//                  64 rows, 8 heads x 4096 24.2 / 24.9                        64 rows, 4 heads x 8192 24.1 / 24.7
+//   more          128 rows, 8 heads x 16384 52.7 / 52.8, 4 x 8 heads x 32K 256 / 255
+constexpr int kFetchOnBlocks = 4, kFetchOnRows = 65;
 template <bool kNeedO, bool kStoreZ, bool kOnce, typename Lens>
 __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__restrict__ q,
                                                            const uint16_t *__restrict__ k,
@@ -392,7 +401,9 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     const int b = part.b, g = part.g, bg = b * Hkv + g, chunk = part.chunk, split = part.part, G = Hq / Hkv, M = G * W, len = part.len;
     const int t_begin = split * split_len;
     const int t_end = min(t_begin + split_len, len);
-    const int n_blk = (t_end - t_begin + 31) / 32, t_last = t_begin + (n_blk - 1) * 32;
+    const int n_blk = (t_end - t_begin + 31) / 32;
+    const int n_fetch = kNeedO && M >= kFetchOnRows && n_blk <= kFetchOnBlocks ? (len - t_begin + 31) / 32 : n_blk;
+    const int t_last = t_begin + (n_fetch - 1) * 32;             // the last block that is fetched
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5;
@@ -473,7 +484,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     const int n_plain = max(vis_min + 1 - t_begin, 0) / 32;   // leading blocks every row of this wave sees in full
     // What the steps fetch: K from block 4, V from block 2 on.  A last block with rows past the sequence's end (row rmax) is cut
     // where it comes up, block n_cut, or here.
-    const int rmax = len - 1 - t_last, n_cut = rmax < 31 ? n_blk - 1 : -1;
+    const int rmax = len - 1 - t_last, n_cut = rmax < 31 ? n_fetch - 1 : -1;
     BlockFetch kf, vf;
     kf.start(kh, min(t_begin + 4 * 32, t_last), kdoff);
     vf.start(vh, min(t_begin + 2 * 32, t_last), vdoff);
@@ -482,7 +493,7 @@ __global__ __launch_bounds__(kThreads, 2) void mfma_sweep1(const uint16_t *__res
     // (kStoreZ: at most 32 rows, so they are the first wave's)
     char *z_split = (char *)(z + (size_t)bg * M * z_stride + t_begin);
     const uint32_t z_off = kStoreZ && row_valid ? (uint32_t)row * z_stride * 4 + 16 * half : ~0u;
-#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, n_blk - 1, n_cut, rmax, vis, n_plain, kf, vf, vh, koff, voff, wave, lane, wave_active, events, z_split, z_off
+#define OBC_S1_ARGS smem, lds0, n, t_begin, t_end, n_fetch - 1, n_cut, rmax, vis, n_plain, kf, vf, vh, koff, voff, wave, lane, wave_active, events, z_split, z_off
     for (int n = 0; n < n_total; n += 4) {
         sweep1_step<0, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;
         sweep1_step<1, kNeedO, kStoreZ, kOnce>(R, OBC_S1_ARGS); ++n;

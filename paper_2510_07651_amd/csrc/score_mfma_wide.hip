@@ -373,7 +373,7 @@ __device__ __forceinline__ int next_tile(int a, int n_tiles) { return a + 1 == n
 // where R.kp points) is read during the step.
 template <int kVariant, bool kOnce>
 __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, const uint32_t lds0, int s, int tile,
-                                          int tile_fetch, bool past, int tile_flush, int t_begin,
+                                          int tile_fetch, int tile_flush, int t_begin,
                                           int t_end, int last_row, const int *vis_i, const int *excl_i, const char *kh,
                                           const char *vh, const uint32_t (&moff)[4], int wave, int lane, int vis_min,
                                           const uint32_t *special_s, float *stage, float *out, size_t variant_stride,
@@ -382,8 +382,9 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
     const int rh = wave & 1, th = wave >> 1;
 
     // Tile s+1 has landed once at most the two younger tiles' transfers are in flight; the barrier also tells that
-    // every wave is done with tile s, whose slot the tile fetched during this step reuses.  (Past the walk's end `past` a step
-    // starts as many transfers, so that every step waits for the same number, but all of them fetch one row of K and of V.)
+    // every wave is done with tile s, whose slot the tile fetched during this step reuses.  (The walk wraps around, so
+    // the ring also prefetches past its end: every step waits for the same number of transfers.  One row of K and of V instead of those
+    // tiles: joint, 128 rows, us, so / one row, 8 heads x 8192 37.4 / 37.6, x 10000 40.2 / 40.5, 4 x 8 heads x 32K 257.4 / 258.4.)
     wait_async_loads_keep<2 * kTilePerWave>();
     __syncthreads();
     TileFetch fetch;
@@ -392,10 +393,10 @@ __device__ __forceinline__ void wide_step(WideState &R, const Stationary &A, con
         fetch.k_base = kh + (size_t)tn * kRowBytes - kBias;
         fetch.v_base = vh + (size_t)tn * kRowBytes - kBias;
         fetch.lds = lds0 + ((s + 3) & 3) * kSlotBytes + wave * 4096;          // (the slot of tile s)
-        const int rmax = past ? 0 : last_row - tn;                         // last row of the tile that exists
+        const int rmax = last_row - tn;                                    // last row of the tile that exists
 #pragma unroll
         for (int n = 0; n < 4; ++n) fetch.voff[n] = moff[n];
-        if (rmax < kTileTok - 1) {                                         // uniform, rare: rows past it re-read it
+        if (rmax < kTileTok - 1) {                                         // uniform, rare: rows past the end re-read the last one
 #pragma unroll
             for (int n = 0; n < 4; ++n) {
                 const int Rn = (wave * 4 + n) * 4 + (lane >> 4);
@@ -559,7 +560,7 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_wide(const uint16_t *
     // Positions of the walk: the tile worked on, the one fetched during the step (four ahead), the one flushed (two back).
     int tile = first, tile_fetch = tile_at(4, first, n_tiles), tile_flush = tile_at(2 * n_tiles - 2, first, n_tiles);
     for (int s = 0; s < n_tiles; ++s, tile = next_tile(tile, n_tiles), tile_fetch = next_tile(tile_fetch, n_tiles), tile_flush = next_tile(tile_flush, n_tiles))
-        wide_step<kVariant, kOnce>(R, A, lds0, s, tile, tile_fetch, s + 4 >= n_tiles, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, moff, wave, lane, vis_min,
+        wide_step<kVariant, kOnce>(R, A, lds0, s, tile, tile_fetch, tile_flush, t_begin, t_end, len - 1, vis_i, excl_i, kh, vh, moff, wave, lane, vis_min,
                             special_s, stage, out, variant_stride, accumulate);
     if (R.pend) {                                              // set B of the last block
         matrix_results_land();
@@ -806,7 +807,8 @@ __global__ __launch_bounds__(kThreads, 1) void mfma_sweep2_solo(const uint16_t *
     int s = 0;
     auto step = [&](auto slot) __attribute__((always_inline)) {        // slot: of the block worked on
         const int after = next_tile(group, n_groups), tok0 = block_of(here), blk = 4 * here + wave;
-        // (past the walk's end one row of K and of V, for the number of transfers: see wide_step)
+        // (Past the walk's end one row of K and of V, for the number of transfers.  So / the blocks that the walk comes to there, joint, 64
+        // rows, us: 8 heads x 8192 30.1 / 30.8, x 16384 40.8 / 42.4, 4 x 8 heads x 32K 195.8 / 198.4.)
         const SoloFetch f = solo_fetch(kh, vh, block_of(after), s + 2 < n_groups ? len - 1 : min(block_of(after), len - 1), ring + slot.value * kSoloSlot, doff, lane);
         const bool hidden = !(tok0 + 31 <= vis_min);
         const int tok = tok0 + (lane & 31);

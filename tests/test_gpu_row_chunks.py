@@ -53,6 +53,26 @@ def test_rows_and_shares_match_oracle(shape, range_len, score_path):
         assert torch.allclose(run[b, :, :n], joint[b, :, :n] + 2.0, rtol=1e-6) and bool((run[b, :, n:] == 2.0).all())
 
 
+@pytest.mark.parametrize("G,W", [(1, 64), (5, 13), (3, 43)])
+@pytest.mark.parametrize("N", [385, 451, 512, 1600])
+def test_first_sweep_past_its_splits(G, W, N, score_path):
+    """Splits of four blocks (129 rows: two; 1600 tokens: fourteen) whose ring fetches past their end, 64, 65 and 129 rows: a last
+    split of one token, of two blocks and three tokens, and full ones; behind the shorter sequence's end stands what is not a number."""
+    lens = [N, N - 130]
+    score_path("mfma")
+    if N > 1536:
+        obc.obc_set_score_tuning(4, 0)
+    gen = torch.Generator().manual_seed(23)
+    q, k, v = (torch.randn(2, H, n, 128, generator=gen).to(torch.bfloat16) for H, n in ((2 * G, W), (2, N), (2, N)))
+    ref = oracle.score(q, k, v, seq_lens=lens)
+    k[1, :, lens[1]:] = float("nan")
+    v[1, :, lens[1]:] = float("nan")
+    got = obc.obc_score(q.cuda(), k.cuda(), v.cuda(), "all", seq_lens=lens).cpu().numpy()
+    for i, name in enumerate(("value", "key", "joint")):
+        err, where = score_error(got[i], ref[i], lens[1] // 8, lens, TOL["bf16"])
+        assert err <= TOL["bf16"], (name, err, where)
+
+
 @pytest.mark.parametrize("G,W,N", [(3, 32, 300), (2, 50, 129), (3, 42, 64), (7, 10, 4097), (1, 1, 40), (1, 63, 63)])
 def test_rows_past_the_last_one_weigh_nothing(G, W, N, score_path):
     """96, 100, 126 and 70 rows of a 128-row chunk, 1 and 63 of a 64-row one: on either side of the padded row count."""
