@@ -50,12 +50,12 @@ def test_decode_scores_select_compact_match_oracle(name, score_path):
     print(name, {k: "%.2e" % v for k, v in worst.items()})
 
 
-@pytest.mark.parametrize("G", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 7, 8])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("step", [1, 2, 4])
 def test_ranges_of_every_length_sum_every_row(G, d, step, score_path):
     """Sums of P V per row, on either side of where they go to the matrix cores, for ranges of 1, 2 and 4 tokens per lane: a token
-    more than one range, as many tokens as 48 ranges and one, and a token less than that."""
+    more than one range of one token per lane, 49 such ranges, one more than are merged inline, and a token less than 97 of them."""
     score_path("decode")
     tokens = {64: 128, 128: 64}[d]
     N = {1: tokens + 1, 2: 49 * tokens, 4: 97 * tokens - 1}[step]

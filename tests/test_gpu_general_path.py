@@ -59,10 +59,12 @@ def test_splits_with_references_of_their_own_match_oracle(case, score_path):
         assert err <= TOL["fp32"], (name, err, where)
 
 
-# (dtype, d, G, W, N, lens): windows whose last chunk of 128 (64) rows leaves five, three or two (three) of its row blocks empty, the
-# last one in use full or with 2 or 1 rows, and whose rows stop seeing tokens in each of a block's sixteen places
+# (dtype, d, G, W, N, lens): windows whose last chunk of 128 (64) rows leaves two or three (three) of its row blocks empty, the last
+# one in use full or with 8, 2 or 1 rows, and whose rows stop seeing tokens in each of a block's sixteen places.  66, 80 and 96 rows are
+# one chunk of 128, 144 and 129 three of 64, 200 two of 128
 EMPTY = [("fp32", 128, 2, 33, 1900, None), ("bf16", 64, 2, 40, 2601, [2601, 1999]), ("fp32", 64, 2, 48, 2055, None),
-         ("bf16", 64, 3, 48, 1500, None), ("fp32", 128, 3, 43, 1203, [1203, 700])]
+         ("bf16", 64, 3, 48, 1500, None), ("fp32", 128, 3, 43, 1203, [1203, 700]), ("bf16", 64, 4, 50, 1700, None),
+         ("fp32", 128, 4, 50, 1105, [1105, 640])]
 
 
 @pytest.mark.parametrize("variant", ["all", "key", "value"])
