@@ -203,13 +203,12 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
         if (kNeedO && p < t1) vw[u] = *(const uint4 *)(vg + (size_t)p * kD + sub * 8);
     }
 
-    // Copies of the rows that begin a piece of evict_pieces, at the very end, where nobody waits for them: kept as they came by, but for
-    // eight rows and long ranges, whose registers they would spill (8 heads, G = 8, d = 128, key, 5717 tokens 37.8 us, kept 43.7).  V that
-    // the sums do not need is fetched there too, in long ranges with the other loads: those workgroups do not all run at once, and
+    // Copies of the rows that begin a piece of evict_pieces, at the very end, where nobody waits for them, kept as they came by.  V that
+    // the sums do not need is fetched there, in long ranges with the other loads: those workgroups do not all run at once, and
     // the next one waits for this one's last trip (32 heads, value, d = 128, 4117 tokens: 9.5 us without copies, V at the end 11.3).
     // A piece is two steps long: only even steps have any.
     static_assert(evict_piece_rows(kD) == 2 * tokens_per_step(kD), "pieces begin at even steps");
-    constexpr bool kLong = kSteps == kMaxSteps, kKept = !(kNeedO && kLong && kG == 8), kEarly = !kNeedO && kLong;
+    constexpr bool kEarly = !kNeedO && kSteps == kMaxSteps;
     constexpr int kEdgeSteps = kEdges ? (kSteps + 1) / 2 : 0;
     uint4 edge_v[kEdgeSteps > 0 ? kEdgeSteps : 1];
     if constexpr (kEdges && kEarly) {
@@ -227,9 +226,8 @@ __global__ __launch_bounds__(kThreads) void decode_partial(
             const int p = token_of<kD>(t0, 2 * i, wave, slot);
             if (p % evict_piece_rows(kD) != 0 || p == 0 || p >= t1) continue;        // (nothing moves up from the first row)
             uint4 *to = edge_rows + ((size_t)bh * 2 * pieces + p / evict_piece_rows(kD)) * kLpt + sub;
-            const size_t at = (size_t)p * kD + sub * 8;
-            to[0] = kKept ? kw[2 * i] : *(const uint4 *)(kg + at);
-            to[(size_t)pieces * kLpt] = kEarly ? edge_v[i] : kNeedO && kKept ? vw[2 * i] : *(const uint4 *)(vg + at);
+            to[0] = kw[2 * i];
+            to[(size_t)pieces * kLpt] = kEarly ? edge_v[i] : kNeedO ? vw[2 * i] : *(const uint4 *)(vg + (size_t)p * kD + sub * 8);
         }
     };
 
