@@ -3,9 +3,9 @@
 //
 // With one row per query head a KV head sees only G = Hq/Hkv rows, far too few to fill a
 // matrix-core tile, and at the cache sizes of decoding the call is bound by memory round
-// trips and dependent instructions, not by bandwidth.  The path is vector-ALU kernels with 128-bit
-// coalesced loads (one token row spread over d/8 lanes) in which a workgroup owns a short range of
-// tokens and every lane issues ALL its loads of the range before it computes:
+// trips and dependent instructions, not by bandwidth.  The path is three kernels with 128-bit
+// coalesced loads (one token row spread over d/8 lanes), on the vector ALUs but for the sums of P V of five to eight
+// rows, in which a workgroup owns a short range of tokens and every lane issues ALL its loads of the range before it computes:
 //   decode_partial   per range: scaled logits Z = q.k/sqrt(d) (Section 3), kept in the
 //                    workspace so K is read once; range max, sum and unnormalised output
 //                    (the range's top-logit token is held out of both sums, see below)
@@ -19,7 +19,7 @@
 // Ranges are as short as lets all their workgroups run at once and keeps the inline merge possible
 // (1, 2 or 4 tokens per lane, sixteen waves): instructions of a lone wave issue one by one, so the count per wave is its
 // time.  8 KV heads x 1025 tokens, G = 4, d = 128, joint, per layer: 72 workgroups of 8 tokens per
-// lane, four waves each, 26 us for the two kernels; 136 workgroups of one token per lane, sixteen waves, 13 us.
+// lane, four waves each, 26 us for the two kernels; 136 workgroups of one token per lane, sixteen waves, 11 us.
 //
 // Cancellation guard.  When one key takes almost all of a row's attention, o_i is almost
 // v_p* and fp32 cannot hold their difference.  Every range keeps its top-logit token out of
@@ -74,7 +74,7 @@ __device__ __forceinline__ float group_sum(float x) {
 __device__ __forceinline__ float xor4(float x) { return dpp_pair<0x1B>(dpp_pair<0x141>(x)); }
 // Sums over the lanes that share a token for the kG rows at once: lane `sub` of them ends up with the sum of row own_row(sub),
 // and lanes of the same row with the same bits.  Each of the first levels adds two rows across lane pairs with one exchange and
-// leaves one of them in each lane of the pair (10 instructions for four rows of 16 lanes; 16 with every sum in every lane).
+// leaves one of them in each lane of the pair (11 operations for four rows of 16 lanes; 16 with every sum in every lane).
 template <int kG>
 __device__ __forceinline__ int own_row(int sub) { return sub & (kG - 1); }
 template <int kLanes, int kG>
@@ -850,8 +850,14 @@ bool decode_path_covers(int B, int N, int W, int Hq, int Hkv, int d, int dtype, 
     if (dtype != OBC_BF16 || W != 1 || Hq / Hkv > kDecodeMaxGroup || (d != 64 && d != 128)) return false;
     if (splits_for(N, d, kMaxSteps) > kMaxSplits) return false;            // what one merging workgroup takes
     // These kernels win while the call is bound by round trips.  On long caches the direct forms
-    // of the norms make them vector-ALU bound and the matrix-core path is faster (measured
-    // crossover on gfx950: about 1e5 head-tokens when o_i is needed, 2.6e5 when it is not).
+    // of the norms make them vector-ALU bound and the matrix-core path is faster, the sooner the more rows.  An accumulating call's
+    // time there over its time here, 4 x 8 heads:
+    //              joint, 49K head-tokens  98K   180K  262K      value, 129K   262K  500K
+    //      G = 1          1.60             1.29  1.13  0.92             1.29   0.96  0.95
+    //      G = 4          1.27             0.94  0.82  0.69             1.22   0.94  0.91
+    //      G = 8          0.98             0.70  0.62  0.53             0.94   0.71  0.68
+    // An eviction step there has evict_pick and evict_shift behind it: joint, 98K, 1.41 / 1.14 / 0.92, of one sequence of 8 heads
+    // 2.15 / 1.71 / 1.37.  One line for all G and for both, between the two.
     const bool need_o = variant == OBC_KEY || variant == OBC_JOINT || variant == OBC_ALL;
     const long long head_tokens = (long long)B * Hkv * N;
     return any_size || d != 128 || head_tokens <= (need_o ? 98304 : 262144);   // (head_dim 64 has no matrix-core path)
@@ -860,11 +866,11 @@ bool decode_path_covers(int B, int N, int W, int Hq, int Hkv, int d, int dtype, 
 void decode_plan(int B, int N, int Hq, int Hkv, int d, ScoreWorkspace *ws, size_t *off) {
     const int G = Hq / Hkv;
     const int BH = B * Hkv;
-    // The shortest ranges whose workgroups fit the compute units, one each (the registers leave no room for two), and no shorter
-    // ones than the inline merge can take.  A second round of workgroups costs more than twice the tokens per lane: a decoding
-    // step of 8 heads, d = 128, G = 1 / 4 / 8, us, with one, two and four tokens per lane: 2100 tokens 18.4 / 23.2 / 34.6, 15.7 / 19.5 /
-    // 25.6 and 18.4 / 23.4 / 35.6; 2 x 1900 20.3 / 24.6 / 37.2, 17.6 / 21.0 / 27.2 and 20.0 / 24.6 / 38.1; within one round 1600 tokens
-    // 13.7 / 16.6 / 21.5, 14.9 / 18.6 / 24.7 and 17.6 / 22.7 / 34.9.
+    // The shortest ranges with at most one workgroup per compute unit, and no shorter ones than the inline merge can take.  Two would
+    // fit (decode_partial has 64 registers and 77 KB of LDS at most, decode_score 62 registers up to four rows), but a second one costs more than twice the tokens per lane: a decoding
+    // step of 8 heads, d = 128, joint, G = 1 / 4 / 8, us, with one, two and four tokens per lane: 2100 tokens (264 workgroups with one)
+    // 16.2 / 19.5 / 27.3, 15.5 / 18.0 / 22.5 and 17.7 / 21.9 / 28.3; 2 x 1900 (480) 18.0 / 21.3 / 29.6, 17.7 / 20.1 / 24.5 and 19.4 / 23.6 / 30.0;
+    // within one round 1600 tokens (200) 13.6 / 15.1 / 18.5, 14.3 / 16.7 / 21.1 and 16.6 / 20.7 / 27.1.
     int steps = 1;
     while (steps < kMaxSteps && ((long long)BH * splits_for(N, d, steps) > 256 || splits_for(N, d, steps) > kInlineSplits)) steps *= 2;
     const int splits = splits_for(N, d, steps);

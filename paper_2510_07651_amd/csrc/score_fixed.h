@@ -985,7 +985,9 @@ __global__ __launch_bounds__(kFixedThreads, 4) void fixed_score(const T *__restr
         if (kNeedO) rows.load(o_digits, hl, block, blocks, lane);
         const __amdgpu_buffer_rsrc_t zg = span_of(z + z_block(w, hl, 0, w.s0), z_block(w, 1, 0, w.s0) * 4);
         const int z_at = (int)(z_block(w, 0, block, w.s0) * 4);
-        // Of 16 tokens from t on (there is room for whole tiles); those of the next block are on their way where a wave has the registers.
+        // Of 16 tokens from t on (there is room for whole tiles); those of the next block are on their way, but for scores with
+        // outputs and 128 channels: there the fp32 all-in-one kernels spill up to 8 registers over them (8 heads x 128 rows x 1500 41.2 us, with
+        // them 41.9), and the others take as long.
         auto logits = [&](int t, int l) { return __builtin_amdgcn_raw_buffer_load_b128(zg, l * 16, z_at + (t - w.s0) * 64, 0); };
         u32x4 ahead;
         if (kAhead) ahead = logits(t_begin + part * kPart, lane);
