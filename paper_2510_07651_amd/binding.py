@@ -23,6 +23,7 @@ VARIANT_CODES = {"value": OBC_VALUE, "key": OBC_KEY, "joint": OBC_JOINT, "all": 
                  "vatp": OBC_VATP}
 
 _lib = None
+_F32, _BF16, _I32 = torch.float32, torch.bfloat16, torch.int32
 
 
 class ObcError(RuntimeError):
@@ -112,6 +113,10 @@ def _dtype_code(t: torch.Tensor) -> int:
     if t.dtype == torch.bfloat16:
         return OBC_BF16
     raise TypeError("q, k, v must be float32 or bfloat16, got %s" % t.dtype)
+
+
+def _variant_code(variant) -> int:
+    return VARIANT_CODES[variant] if isinstance(variant, str) else int(variant)
 
 
 def _lens_arg(seq_lens: Optional[Sequence[int]], B: int):
@@ -424,23 +429,24 @@ def obc_decode_step(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scores: t
     B, Hq, W, d = q.shape
     kv_shape, dtype = k.shape, q.dtype
     Bk, Hkv, N, dk = kv_shape
-    if (W != 1 or Bk != B or dk != d or v.shape != kv_shape or k.dtype is not dtype or v.dtype is not dtype
-            or scores.shape != (B, Hkv, N) or scores.dtype is not torch.float32):
+    if not (W == 1 and Bk == B and dk == d and v.shape == kv_shape and k.dtype is dtype and v.dtype is dtype
+            and scores.shape == (B, Hkv, N) and scores.dtype is _F32):
         raise ValueError("q must be [B,Hq,1,d], k, v [B,Hkv,N,d] of its type, scores [B,Hkv,N] float32")
-    var = VARIANT_CODES[variant] if isinstance(variant, str) else int(variant)
-    dt = OBC_BF16 if dtype is torch.bfloat16 else _dtype_code(q)
+    var = VARIANT_CODES[variant] if type(variant) is str else _variant_code(variant)
+    dt = OBC_BF16 if dtype is _BF16 else _dtype_code(q)
     if workspace is None:
         workspace = torch.empty(obc_decode_step_workspace_bytes(B, N, Hq, Hkv, d, dt, var), dtype=torch.uint8, device=q.device)
     if evicted is None:
         evicted = torch.empty((B, Hkv), dtype=torch.int32, device=q.device)
     if not (evicted.is_cuda and workspace.is_cuda and evicted.is_contiguous() and workspace.is_contiguous()):
         raise ValueError("tensors must be contiguous and on the GPU")
-    if evicted.dtype is not torch.int32 or evicted.numel() < B * Hkv:
+    if evicted.dtype is not _I32 or evicted.numel() < B * Hkv:
         raise ValueError("evicted must be int32 with room for [B,Hkv]")
     rc = (_lib or load_library()).obc_decode_step(
         q.data_ptr(), k.data_ptr(), v.data_ptr(), scores.data_ptr(), evicted.data_ptr(), N, Hq, Hkv, d, var, B, dt,
-        None if seq_lens is None else _lens_arg(seq_lens, B), int(num_sinks), int(num_recent), workspace.data_ptr(),
-        workspace.numel(), _stream_ptr(q))
+        None if seq_lens is None else _lens_arg(seq_lens, B), num_sinks if type(num_sinks) is int else int(num_sinks),
+        num_recent if type(num_recent) is int else int(num_recent), workspace.data_ptr(), workspace.numel(),
+        _raw_stream(q.get_device()) if _raw_stream is not None else _stream_ptr(q))
     if rc != OBC_OK:
         raise ObcError(rc, "obc_decode_step")
     return evicted
