@@ -230,17 +230,19 @@ def obc_score_static(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, variant,
                      accumulate: bool = False) -> torch.Tensor:
     """obc_score / obc_score_accumulate on the library's static scratch: the caller passes inputs and the output
     tensor, and nothing is allocated (not by torch either)."""
-    _require_cuda(q, k, v, scores)
+    if not (q.is_cuda and k.is_cuda and v.is_cuda and scores.is_cuda and q.is_contiguous() and k.is_contiguous()
+            and v.is_contiguous() and scores.is_contiguous()):
+        raise ValueError("tensors must be contiguous and on the GPU")
     B, Hq, W, d = q.shape
-    Bk, Hkv, N, dk = k.shape
-    if (Bk, dk) != (B, d) or v.shape != k.shape or k.dtype != q.dtype or v.dtype != q.dtype:
+    Bk, Hkv, N, dk = kv_shape = k.shape
+    if Bk != B or dk != d or v.shape != kv_shape or k.dtype is not q.dtype or v.dtype is not q.dtype:
         raise ValueError("q, k, v shapes or dtypes disagree")
     var = VARIANT_CODES[variant] if isinstance(variant, str) else int(variant)
     shape = (3, B, Hkv, N) if var == OBC_ALL else (B, Hkv, N)
     if tuple(scores.shape) != shape or scores.dtype != torch.float32:
         raise ValueError("scores must be a contiguous float32 tensor of shape %s" % (shape,))
     rc = load_library().obc_score_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), N, W, Hq, Hkv, d, var,
-                                         scores.data_ptr(), B, _dtype_code(q), _lens_arg(seq_lens, B),
+                                         scores.data_ptr(), B, _dtype_code(q), None if seq_lens is None else _lens_arg(seq_lens, B),
                                          1 if accumulate else 0, _stream_ptr(q))
     if rc != OBC_OK:
         raise ObcError(rc, "obc_score_static")
@@ -364,23 +366,38 @@ def obc_select_adaptive(scores: torch.Tensor, budget: int, n_safe: int, cap: Opt
     return keep_idx, counts
 
 
+def _require_room(out: torch.Tensor, nbytes: int):
+    _require_cuda(out)
+    if out.numel() * out.element_size() < nbytes:
+        raise ValueError("k_out, v_out need room for [B,Hkv,budget,d]")
+
+
+def _kept(k: torch.Tensor, v: torch.Tensor, keep_idx: torch.Tensor):
+    """Shape and type of caches and the rows kept per head, where they fit together (rows are moved by k's bytes)."""
+    if not (k.is_cuda and v.is_cuda and keep_idx.is_cuda and k.is_contiguous() and v.is_contiguous() and keep_idx.is_contiguous()):
+        raise ValueError("tensors must be contiguous and on the GPU")
+    shape, kept, dtype = k.shape, keep_idx.shape, k.dtype
+    if (len(kept) < 3 and kept[1:] != (1,) or kept[0] != shape[0] or kept[1] != shape[1] or keep_idx.dtype is not _I32 or v.shape != shape
+            or v.dtype is not dtype and v.element_size() != k.element_size()):
+        raise ValueError("keep_idx must be [B,Hkv,budget] int32 matching k, v")
+    return shape, dtype, kept[-1]
+
+
 def obc_compact(k: torch.Tensor, v: torch.Tensor, keep_idx: torch.Tensor, k_out=None, v_out=None):
     """k,v [B,Hkv,N,d], keep_idx [B,Hkv,budget] int32 -> (k_out, v_out) [B,Hkv,budget,d]."""
-    _require_cuda(k, v, keep_idx)
-    B, Hkv, N, d = k.shape
-    budget = keep_idx.shape[-1]
-    if (keep_idx.dtype != torch.int32 or keep_idx.shape[:2] != (B, Hkv) or v.shape != k.shape
-            or v.element_size() != k.element_size()):
-        raise ValueError("keep_idx must be [B,Hkv,budget] int32 matching k, v")
+    (B, Hkv, N, d), dtype, budget = _kept(k, v, keep_idx)
+    rows = B * Hkv * budget * d
     if k_out is None:
-        k_out = torch.empty((B, Hkv, budget, d), dtype=k.dtype, device=k.device)
+        k_out = torch.empty((B, Hkv, budget, d), dtype=dtype, device=k.device)
+    elif not (k_out.dtype is dtype and k_out.numel() >= rows and k_out.is_cuda and k_out.is_contiguous()):
+        _require_room(k_out, rows * k.element_size())
     if v_out is None:
         v_out = torch.empty((B, Hkv, budget, d), dtype=v.dtype, device=v.device)
-    _require_cuda(k_out, v_out)
-    if min(k_out.numel() * k_out.element_size(), v_out.numel() * v_out.element_size()) < B * Hkv * budget * d * k.element_size():
-        raise ValueError("k_out, v_out need room for [B,Hkv,budget,d]")
-    rc = load_library().obc_compact(k.data_ptr(), v.data_ptr(), keep_idx.data_ptr(), k_out.data_ptr(),
-                                    v_out.data_ptr(), B, Hkv, N, budget, d, _dtype_code(k), _stream_ptr(k))
+    elif not (v_out.dtype is dtype and v_out.numel() >= rows and v_out.is_cuda and v_out.is_contiguous()):
+        _require_room(v_out, rows * k.element_size())
+    rc = (_lib or load_library()).obc_compact(
+        k.data_ptr(), v.data_ptr(), keep_idx.data_ptr(), k_out.data_ptr(), v_out.data_ptr(), B, Hkv, N, budget, d,
+        OBC_BF16 if dtype is _BF16 else _dtype_code(k), _raw_stream(k.get_device()) if _raw_stream is not None else _stream_ptr(k))
     if rc != OBC_OK:
         raise ObcError(rc, "obc_compact")
     return k_out, v_out
@@ -389,14 +406,7 @@ def obc_compact(k: torch.Tensor, v: torch.Tensor, keep_idx: torch.Tensor, k_out=
 def obc_compact_inplace(k: torch.Tensor, v: torch.Tensor, keep_idx: torch.Tensor,
                         scores: Optional[torch.Tensor] = None) -> None:
     """Moves rows keep_idx[b,g,j] of k, v (and entries of scores, whose tail is zeroed) to position j, in place."""
-    _require_cuda(k, v, keep_idx)
-    B, Hkv, N, d = k.shape
-    budget = keep_idx.shape[-1]
-    if (keep_idx.dtype != torch.int32 or keep_idx.shape[:2] != (B, Hkv) or v.shape != k.shape
-            or v.element_size() != k.element_size()):
-        raise ValueError("keep_idx must be [B,Hkv,budget] int32 matching k, v")
-    if not (k.is_contiguous() and v.is_contiguous() and keep_idx.is_contiguous()):
-        raise ValueError("k, v and keep_idx must be contiguous")
+    (B, Hkv, N, d), dtype, budget = _kept(k, v, keep_idx)
     sp = None
     if scores is not None:
         _require_cuda(scores)
@@ -404,7 +414,7 @@ def obc_compact_inplace(k: torch.Tensor, v: torch.Tensor, keep_idx: torch.Tensor
             raise ValueError("scores must be a contiguous [B,Hkv,N] float32 tensor")
         sp = scores.data_ptr()
     rc = load_library().obc_compact_inplace(k.data_ptr(), v.data_ptr(), sp, keep_idx.data_ptr(), B, Hkv, N, budget, d,
-                                            _dtype_code(k), _stream_ptr(k))
+                                            OBC_BF16 if dtype is _BF16 else _dtype_code(k), _stream_ptr(k))
     if rc != OBC_OK:
         raise ObcError(rc, "obc_compact_inplace")
 

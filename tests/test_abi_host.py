@@ -239,7 +239,7 @@ def test_score_static_refuses_what_does_not_fit_together(change, no_launch):
 
 @pytest.mark.filterwarnings("ignore:Accessing the data pointer of FakeTensor")
 @pytest.mark.parametrize("change", [dict(kd=FP32), dict(vd=FP32), dict(k_out=(2, 2, 8, 128)), dict(v_out=(2, 2, 9, 64)),
-                                    dict(v_out=(1,)), dict(turned=True), dict(keep=(2, 1, 9))], ids=str)
+                                    dict(v_out=(1,)), dict(turned=True), dict(keep=(2, 1, 9)), dict(keep=(2, 2)), dict(keep=(2,)), dict(keep=())], ids=str)
 def test_compaction_refuses_what_has_no_room(change, no_launch):
     """Rows are moved by their bytes, k's: v needs as many per element, the outputs as many in all."""
     def call(kd=BF16, vd=BF16, k_out=None, v_out=None, keep=(2, 2, 9), turned=False, od=BF16):
